@@ -52,6 +52,7 @@ struct Layout {
   int32_t *kept_ids, *remap, *counters;
   int32_t *row_ptr, *col_idx, *t_row_ptr, *t_col_idx;
   std::vector<float *> A, H;  // index 1..L
+  std::vector<char *> Wf, Wb;  // index 1..L: the layer's weights packed for H W and for dZ W^T
   std::vector<float *> dZ;    // index 1..L: gradient w.r.t. the pre-activation of layer l (bns_train_step)
 };
 
@@ -145,14 +146,12 @@ size_t carve(Carver &c, const bns_partition_desc *p, const bns_model_desc *m, La
   for (size_t l = 0; l <= L; ++l) d_max = std::max<size_t>(d_max, m->dims[l]);
   for (size_t l = 0; l < L; ++l) {
     d_in_max = std::max<size_t>(d_in_max, m->dims[l]);
-    const size_t mn = (size_t)m->dims[l] * m->dims[l + 1];
-    part_max = std::max(part_max, mn * (size_t)splitk_splits(m->dims[l], m->dims[l + 1], p->n_in));
-    if (m->layer_kind == 1)  // [A | H]^T dZ as one product of twice the height
-      part_max = std::max(part_max, 2 * mn * (size_t)splitk_splits(2 * m->dims[l], m->dims[l + 1], p->n_in));
+    const int kw = m->layer_kind == 1 ? 2 : 1;  // [A | H]^T dZ is one product of twice the height
+    part_max = std::max(part_max, gemm_tn_partials(kw * m->dims[l], m->dims[l + 1], p->n_in));
     if (update_first_shape(m->layer_kind, m->dims[l], m->dims[l + 1])) {
       d_first_max = std::max<size_t>(d_first_max, gather_stride(m->dims[l], m->dims[l + 1]));
       if (p->n_halo > 0)
-        part_max = std::max(part_max, mn * (size_t)splitk_splits(m->dims[l], m->dims[l + 1], p->n_halo));
+        part_max = std::max(part_max, gemm_tn_partials(m->dims[l], m->dims[l + 1], p->n_halo));
     }
   }
   Layout w;
@@ -202,7 +201,12 @@ size_t carve(Carver &c, const bns_partition_desc *p, const bns_model_desc *m, La
   w.A.assign(L + 1, nullptr);
   w.H.assign(L + 1, nullptr);
   w.dZ.assign(L + 1, nullptr);
+  w.Wf.assign(L + 1, nullptr);
+  w.Wb.assign(L + 1, nullptr);
   for (size_t l = 1; l <= L; ++l) {
+    const int32_t kw = m->layer_kind == 1 ? 2 : 1;
+    w.Wf[l] = c.take<char>(packed_bytes(kw * m->dims[l - 1], m->dims[l]));
+    w.Wb[l] = c.take<char>(kw * packed_bytes(m->dims[l], m->dims[l - 1]));
     w.A[l] = c.take<float>(n_in * (size_t)m->dims[l - 1]);
     w.H[l] = c.take<float>(n_in * (size_t)m->dims[l]);
     w.dZ[l] = c.take<float>(n_in * (size_t)m->dims[l]);
@@ -298,10 +302,15 @@ bns_status layer_fwd_impl(bns_ctx *ctx, int layer, double p, const float *H_in, 
     }
     {
       PhaseTimer t(ctx, BNS_PHASE_GEMM_FWD, s);
-      BNS_TRY("gemm_nn(inner)", gemm_nn(n_in, d_out, d_in, H_in, W, A_saved, false, false, Dropout{}, nullptr, s, ld));
-      if (B > 0)
-        BNS_TRY("gemm_nn(boundary)", gemm_nn(B, d_out, d_in, ctx->ws.Hu, W, ctx->ws.Hu2, false, false, Dropout{},
-                                             ctx->cur_n_kept, s, ld));
+      RowsGemm g = rows_gemm(n_in, d_out, d_in, H_in, ctx->ws.Wf[layer], A_saved);
+      g.ldc = ld;
+      g.pad = ld != d_out;
+      BNS_TRY("gemm_rows(inner)", gemm_rows(g, s));
+      g.M = B;
+      g.A = ctx->ws.Hu;
+      g.C = ctx->ws.Hu2;
+      g.m_dev = ctx->cur_n_kept;
+      if (B > 0) BNS_TRY("gemm_rows(boundary)", gemm_rows(g, s));
     }
     PhaseTimer t(ctx, BNS_PHASE_SPMM_FWD, s);
     BNS_TRY("spmm_fwd", spmm_fwd(ctx->ws.plan_f, n_in, ld, ctx->cur_row_ptr, ctx->cur_col_idx, ctx->ws.dis_in,
@@ -350,17 +359,15 @@ bns_status layer_fwd_impl(bns_ctx *ctx, int layer, double p, const float *H_in, 
   }
   {
     PhaseTimer t(ctx, BNS_PHASE_GEMM_FWD, s);
-    if (!sage) {
-      BNS_TRY("gemm_nn", gemm_nn(n_in, d_out, d_in, A_saved, W, H_out, relu, false, dropout_of(ctx, layer, relu),
-                                 nullptr, s));
-    } else if (d_in % 16 == 0) {  // [z | h] [W_n ; W_s] in one product
-      BNS_TRY("gemm_nn_concat", gemm_nn_concat(n_in, d_out, d_in, A_saved, H_in, W, H_out, relu,
-                                               dropout_of(ctx, layer, relu), s));
-    } else {  // [z | h] [W_n ; W_s] = z W_n + h W_s
-      BNS_TRY("gemm_nn(nbr)", gemm_nn(n_in, d_out, d_in, A_saved, W, H_out, false, false, Dropout{}, nullptr, s));
-      BNS_TRY("gemm_nn(self)", gemm_nn(n_in, d_out, d_in, H_in, W + (size_t)d_in * d_out, H_out, relu, true,
-                                       dropout_of(ctx, layer, relu), nullptr, s));
+    RowsGemm g = rows_gemm(n_in, d_out, sage ? 2 * d_in : d_in, A_saved, ctx->ws.Wf[layer], H_out);
+    g.lda = d_in;
+    if (sage) {  // [z | h] [W_n ; W_s] in one product
+      g.A2 = H_in;
+      g.a_split = d_in;
     }
+    g.relu = relu;
+    g.drop = dropout_of(ctx, layer, relu);
+    BNS_TRY("gemm_rows(update)", gemm_rows(g, s));
   }
   return BNS_OK;
 }
@@ -371,10 +378,48 @@ bns_status layer_fwd_impl(bns_ctx *ctx, int layer, double p, const float *H_in, 
 // halo_first (nullable): the boundary features of an update-first layer (A_saved does not hold
 // the aggregate then); the weight gradient is [H_in ; Hu]^T (P^T dZ) instead of A^T dZ.
 bns_status layer_bwd_impl(bns_ctx *ctx, int layer, double p, const float *dZ, const float *A_saved,
-                          const float *H_in, const float *W, float *dW, float *dH_in, float *dhalo,
-                          const float *mask_src, bool update_first, const float *halo_first, hipStream_t s) {
+                          const float *H_in, float *dW, float *dH_in, float *dhalo, const float *mask_src,
+                          bool update_first, const float *halo_first, float *W_step, float lr, hipStream_t s) {
   const int n_in = ctx->part.n_in, B = ctx->part.n_halo;
   const int d_in = ctx->dims[layer - 1], d_out = ctx->dims[layer];
+  const char *Wb = ctx->ws.Wb[layer];
+  // C = alpha * G W^T for rows of G at the output width; C2: the mean aggregator's second half
+  auto gemm_wt = [&](int32_t M, const float *G, float *C, float *C2, const float *mask, float alpha, const int32_t *m_dev) {
+    RowsGemm g = rows_gemm(M, C2 ? 2 * d_in : d_in, d_out, G, Wb, C);
+    g.alpha = alpha;
+    if (C2 && d_in % 4 != 0) {  // no 16-byte store may straddle the two results: one product each
+      g.N = g.ldc = d_in;
+      const hipError_t e = gemm_rows(g, s);
+      if (e != hipSuccess) return e;
+      g.Bp = Wb + packed_bytes(d_out, d_in);
+      g.C = C2;
+      return gemm_rows(g, s);
+    }
+    g.C2 = C2;
+    g.ldc = g.c_split = d_in;
+    g.mask = mask;
+    g.m_dev = m_dev;
+    return gemm_rows(g, s);
+  };
+  // dW (+)= [A | A2]^T G, followed by the plain update when it is the last part of the gradient
+  auto gemm_dw = [&](int32_t K, const float *A, const float *A2, const float *G, bool accumulate, const int32_t *k_dev,
+                     bool last) {
+    TnGemm g{};
+    g.M = A2 ? 2 * d_in : d_in;
+    g.N = d_out;
+    g.K = K;
+    g.A = A;
+    g.A2 = A2;
+    g.B = G;
+    g.a_split = d_in;
+    g.C = dW;
+    g.partials = ctx->ws.partials;
+    g.accumulate = accumulate;
+    g.k_dev = k_dev;
+    g.W = last ? W_step : nullptr;
+    g.lr = lr;
+    return gemm_tn(g, s);
+  };
   if (update_first) {
     float *G_in = ctx->ws.G1, *G_halo = B > 0 ? ctx->ws.Hu2 : nullptr;
     {  // G = P^T dZ at the output width, inner rows and kept boundary rows
@@ -397,18 +442,16 @@ bns_status layer_bwd_impl(bns_ctx *ctx, int layer, double p, const float *dZ, co
     }
     {
       PhaseTimer t(ctx, BNS_PHASE_GEMM_DW, s);
-      BNS_TRY("gemm_tn_splitk(inner)", gemm_tn_splitk(d_in, d_out, n_in, H_in, G_in, dW, ctx->ws.partials, false,
-                                                      nullptr, s));
+      BNS_TRY("gemm_tn(inner)", gemm_dw(n_in, H_in, nullptr, G_in, false, nullptr, B == 0));
       if (B > 0)
-        BNS_TRY("gemm_tn_splitk(boundary)", gemm_tn_splitk(d_in, d_out, B, ctx->ws.Hu, G_halo, dW, ctx->ws.partials,
-                                                           true, ctx->cur_n_kept, s));
+        BNS_TRY("gemm_tn(boundary)", gemm_dw(B, ctx->ws.Hu, nullptr, G_halo, true, ctx->cur_n_kept, true));
     }
     if (dH_in) {
       PhaseTimer t(ctx, BNS_PHASE_GEMM_DA, s);
       const float ms1 = mask_src ? mask_scale_of(ctx) : 1.f;
-      BNS_TRY("gemm_nt", gemm_nt(n_in, d_in, d_out, G_in, W, dH_in, mask_src, ms1, nullptr, s));
+      BNS_TRY("gemm_rows(dH)", gemm_wt(n_in, G_in, dH_in, nullptr, mask_src, ms1, nullptr));
       if (dhalo && B > 0)
-        BNS_TRY("gemm_nt(halo)", gemm_nt(B, d_in, d_out, G_halo, W, dhalo, nullptr, 1.f, ctx->cur_n_kept, s));
+        BNS_TRY("gemm_rows(dhalo)", gemm_wt(B, G_halo, dhalo, nullptr, nullptr, 1.f, ctx->cur_n_kept));
     }
     return BNS_OK;
   }
@@ -417,28 +460,14 @@ bns_status layer_bwd_impl(bns_ctx *ctx, int layer, double p, const float *dZ, co
   // input (the product with W^T) and is divided out of the boundary rows, which are not masked.
   const float ms = mask_src ? mask_scale_of(ctx) : 1.f;
   if (ctx->layer_kind == 1) {
-    const size_t half = (size_t)d_in * d_out;
     {
-      PhaseTimer t(ctx, BNS_PHASE_GEMM_DW, s);
-      if (gemm_tn_concat_supported(d_in)) {  // [A | H]^T dZ in one product: dZ is read once
-        BNS_TRY("gemm_tn_splitk_concat", gemm_tn_splitk_concat(d_in, d_out, n_in, A_saved, H_in, dZ, dW,
-                                                               ctx->ws.partials, false, nullptr, s));
-      } else {
-        BNS_TRY("gemm_tn_splitk(nbr)", gemm_tn_splitk(d_in, d_out, n_in, A_saved, dZ, dW, ctx->ws.partials, false,
-                                                      nullptr, s));
-        BNS_TRY("gemm_tn_splitk(self)", gemm_tn_splitk(d_in, d_out, n_in, H_in, dZ, dW + half, ctx->ws.partials, false,
-                                                       nullptr, s));
-      }
+      PhaseTimer t(ctx, BNS_PHASE_GEMM_DW, s);  // [A | H]^T dZ in one product: dZ is read once
+      BNS_TRY("gemm_tn(concat)", gemm_dw(n_in, A_saved, H_in, dZ, false, nullptr, true));
     }
     if (dH_in) {
       {
-        PhaseTimer t(ctx, BNS_PHASE_GEMM_DA, s);
-        if (gemm_nt_pair_supported(d_in)) {  // dZ [W_n ; W_s]^T in one product, split into the two halves
-          BNS_TRY("gemm_nt_pair", gemm_nt_pair(n_in, d_in, d_out, dZ, W, ctx->ws.G1, ctx->ws.G2, ms, s));
-        } else {
-          BNS_TRY("gemm_nt(nbr)", gemm_nt(n_in, d_in, d_out, dZ, W, ctx->ws.G1, nullptr, ms, nullptr, s));
-          BNS_TRY("gemm_nt(self)", gemm_nt(n_in, d_in, d_out, dZ, W + half, ctx->ws.G2, nullptr, ms, nullptr, s));
-        }
+        PhaseTimer t(ctx, BNS_PHASE_GEMM_DA, s);  // dZ [W_n ; W_s]^T in one product, split into the two halves
+        BNS_TRY("gemm_rows(dA pair)", gemm_wt(n_in, dZ, ctx->ws.G1, ctx->ws.G2, nullptr, ms, nullptr));
       }
       // dH_in = (gradient through the node's own feature) + mean^T (gradient of the neighbour mean)
       PhaseTimer t(ctx, BNS_PHASE_SPMM_BWD, s);
@@ -451,7 +480,7 @@ bns_status layer_bwd_impl(bns_ctx *ctx, int layer, double p, const float *dZ, co
   }
   {
     PhaseTimer t(ctx, BNS_PHASE_GEMM_DW, s);
-    BNS_TRY("gemm_tn_splitk", gemm_tn_splitk(d_in, d_out, n_in, A_saved, dZ, dW, ctx->ws.partials, false, nullptr, s));
+    BNS_TRY("gemm_tn", gemm_dw(n_in, A_saved, nullptr, dZ, false, nullptr, true));
   }
   if (dH_in && d_out < d_in) {
     // (P^T dZ) W^T instead of P^T (dZ W^T): the transposed aggregate runs at the narrower width
@@ -470,19 +499,42 @@ bns_status layer_bwd_impl(bns_ctx *ctx, int layer, double p, const float *dZ, co
                                    ctx->ws.spmm_partials, G_in, G_halo, s, d_out));
     }
     PhaseTimer t(ctx, BNS_PHASE_GEMM_DA, s);
-    BNS_TRY("gemm_nt", gemm_nt(n_in, d_in, d_out, G_in, W, dH_in, mask_src, ms, nullptr, s));
+    BNS_TRY("gemm_rows(dH)", gemm_wt(n_in, G_in, dH_in, nullptr, mask_src, ms, nullptr));
     if (G_halo && B > 0)
-      BNS_TRY("gemm_nt(halo)", gemm_nt(B, d_in, d_out, G_halo, W, dhalo, nullptr, 1.f, ctx->cur_n_kept, s));
+      BNS_TRY("gemm_rows(dhalo)", gemm_wt(B, G_halo, dhalo, nullptr, nullptr, 1.f, ctx->cur_n_kept));
   } else if (dH_in) {
     {
       PhaseTimer t(ctx, BNS_PHASE_GEMM_DA, s);
-      BNS_TRY("gemm_nt", gemm_nt(n_in, d_in, d_out, dZ, W, ctx->ws.G1, nullptr, ms, nullptr, s));
+      BNS_TRY("gemm_rows(dA)", gemm_wt(n_in, dZ, ctx->ws.G1, nullptr, nullptr, ms, nullptr));
     }
     PhaseTimer t(ctx, BNS_PHASE_SPMM_BWD, s);
     BNS_TRY("spmm_bwd", spmm_bwd(ctx->ws.plan_b, n_in, B, d_in, ctx->cur_t_row_ptr, ctx->cur_t_col_idx,
                                  ctx->cur_kept, ctx->cur_n_kept, ctx->ws.dis_in, ctx->ws.dis_in,
                                  ctx->ws.dis_halo, halo_scale(p) / ms, ctx->ws.G1, mask_src, nullptr, false,
                                  ctx->ws.spmm_partials, dH_in, dhalo, s));
+  }
+  return BNS_OK;
+}
+
+// Packs the weights of layers first..last (W[0] is layer `first`'s) for the forward product and / or for
+// dZ W^T (layer 1 of a training step has no such product).
+bns_status pack_layers(bns_ctx *ctx, const float *const *W, int first, int last, bool fwd, bool bwd, hipStream_t s) {
+  PackJob jobs[kMaxPackJobs];
+  int n = 0;
+  const int32_t kw = ctx->layer_kind == 1 ? 2 : 1;
+  for (int l = first; l <= last; ++l) {
+    const int32_t d_in = kw * ctx->dims[l - 1], d_out = ctx->dims[l];
+    if (fwd) jobs[n++] = PackJob{W[l - first], ctx->ws.Wf[l], d_in, d_out, false};
+    if (bwd && (l > 1 || !fwd)) {
+      const int32_t part = kw == 2 && ctx->dims[l - 1] % 4 != 0 ? 2 : 1;  // the two halves apart (see gemm_wt)
+      for (int32_t h = 0; h < part; ++h)
+        jobs[n++] = PackJob{W[l - first] + (size_t)h * ctx->dims[l - 1] * d_out,
+                            ctx->ws.Wb[l] + h * packed_bytes(d_out, ctx->dims[l - 1]), d_out, d_in / part, true};
+    }
+    if (n + 3 > kMaxPackJobs || l == last) {
+      BNS_TRY("pack_weights", pack_weights(jobs, n, s));
+      n = 0;
+    }
   }
   return BNS_OK;
 }
@@ -646,8 +698,10 @@ bns_status bns_gcn_layer_fwd(bns_ctx *ctx, int32_t layer, double p, const float 
   if (!H_in || !W || !A_saved || !H_out || (ctx->part.n_halo > 0 && !halo_h))
     return fail(ctx, BNS_EINVAL, "null pointer");
   if (!ctx->cur_row_ptr) return fail(ctx, BNS_EINVAL, "bns_build_sampled_csr has not been called");
-  return layer_fwd_impl(ctx, layer, p, H_in, halo_h, W, A_saved, H_out, relu != 0, false,
-                        static_cast<hipStream_t>(stream));
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  const bns_status st = pack_layers(ctx, &W, layer, layer, true, false, s);
+  if (st != BNS_OK) return st;
+  return layer_fwd_impl(ctx, layer, p, H_in, halo_h, W, A_saved, H_out, relu != 0, false, s);
 }
 
 bns_status bns_gcn_layer_bwd(bns_ctx *ctx, int32_t layer, double p, const float *dH_out, const float *H_out,
@@ -667,7 +721,11 @@ bns_status bns_gcn_layer_bwd(bns_ctx *ctx, int32_t layer, double p, const float 
     BNS_TRY("relu_mask", relu_mask(n, dH_out, H_out, mask_scale_of(ctx), ctx->ws.G0, s));
     dZ = ctx->ws.G0;
   }
-  return layer_bwd_impl(ctx, layer, p, dZ, A_saved, H_in, W, dW, dH_in, dhalo, nullptr, false, nullptr, s);
+  if (dH_in) {
+    const bns_status st = pack_layers(ctx, &W, layer, layer, false, true, s);
+    if (st != BNS_OK) return st;
+  }
+  return layer_bwd_impl(ctx, layer, p, dZ, A_saved, H_in, dW, dH_in, dhalo, nullptr, false, nullptr, nullptr, 0.f, s);
 }
 
 static bns_status train_step_impl(bns_ctx *ctx, uint64_t seed, uint32_t epoch, const uint32_t *epoch_dev, double p,
@@ -685,6 +743,8 @@ static bns_status train_step_impl(bns_ctx *ctx, uint64_t seed, uint32_t epoch, c
   Layout &w = ctx->ws;
 
   bns_status st = sample_and_build_impl(ctx, seed, epoch, epoch_dev, p, s);
+  if (st != BNS_OK) return st;
+  st = pack_layers(ctx, W, 1, L, true, true, s);
   if (st != BNS_OK) return st;
 
   const float *H_prev = X;
@@ -711,17 +771,11 @@ static bns_status train_step_impl(bns_ctx *ctx, uint64_t seed, uint32_t epoch, c
   // (BNS_VIEW_DZ), so that each stage of the backward pass can be inspected with its exact inputs.
   for (int l = L; l >= 1; --l) {
     float *dh = (dhalo && l > 1) ? dhalo[l - 1] : nullptr;
-    st = layer_bwd_impl(ctx, l, p, w.dZ[l], w.A[l], l > 1 ? w.H[l - 1] : X, W[l - 1], dW[l - 1],
+    st = layer_bwd_impl(ctx, l, p, w.dZ[l], w.A[l], l > 1 ? w.H[l - 1] : X, dW[l - 1],
                         l > 1 ? w.dZ[l - 1] : nullptr, dh,
                         l > 1 ? w.H[l - 1] : nullptr, layer_plan(ctx, l, X) == BNS_LAYER_UPDATE_FIRST,
-                        ctx->part.n_halo > 0 ? halo_h[l - 1] : nullptr, s);
+                        ctx->part.n_halo > 0 ? halo_h[l - 1] : nullptr, W[l - 1], lr, s);
     if (st != BNS_OK) return st;
-  }
-  if (lr > 0.f) {
-    PhaseTimer t(ctx, BNS_PHASE_SGD, s);
-    for (int l = 0; l < L; ++l)
-      BNS_TRY("sgd_update", sgd_update((int64_t)(ctx->layer_kind == 1 ? 2 : 1) * ctx->dims[l] * ctx->dims[l + 1], W[l],
-                                       dW[l], lr, s));
   }
   return BNS_OK;
 }

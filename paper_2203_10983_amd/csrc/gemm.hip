@@ -1,425 +1,530 @@
-// Dense update (Eq. 2) and its backward on the fp32 matrix cores (v_mfma_f32_32x32x2_f32).
+// Dense update (Eq. 2) and its backward on the matrix cores: fp32 operands and results, products by
+// three-way bf16 splitting (split_bf16.hpp).
 //
-// One kernel template covers the three products of a layer:
-//   forward   H = A W            gemm_nn : A [M,K] k-contiguous,  B [K,N] n-contiguous
-//   backward  dA = dZ W^T        gemm_nt : A [M,K] k-contiguous,  B [N,K] k-contiguous
-//   backward  dW = A^T dZ        gemm_tn : A [K,M] m-contiguous,  B [K,N] n-contiguous, split K
-// A block owns a 128 x BN tile of C.  BN = 128 with a k-contiguous A (forward product, dZ W^T): 8
-// wavefronts (2 x 4), each 64 x 32 = two 32x32 accumulators; BN = 128 with an m-contiguous A (the
-// split-K weight gradient): 4 wavefronts (2 x 2), each 64 x 64; BN = 64 (chosen when it wastes
-// fewer padded columns, e.g. N = 172, 47, 41): 4 wavefronts (4 x 1), each 32 x 64.  Measured on
-// gfx950: the matrix pipe itself issues at 98 % of its peak whatever the number of wavefronts per
-// SIMD and of accumulators per wavefront (bns_probe_mfma), so a tile shape is judged by how well it
-// hides operand staging and barriers: stand-alone the 8-wavefront tile (six to eight wavefronts per
-// SIMD instead of four) is 10 - 26 % faster than the 4-wavefront one, inside a training step 3 - 8 %
-// (the weight gradient, which streams both operands, lost 1 - 3 % and keeps four wavefronts).
-// Operand tiles of depth 16 are staged through LDS
-// in k-major order (As[k][m], Bs[k][n]) so that an MFMA operand read is one conflict-free row
-// segment; the next tile is prefetched into registers while the current one is multiplied
-// (double-buffered LDS, one barrier per step).  Split-K partial tiles are summed in a fixed
-// order: no atomics.
+//   gemm_rows   C = [A | A2] B   forward product H = A W and dA = dZ W^T: a tall A [M, K] times a weight
+//               matrix, which pack_weights has split and laid out as operand fragments
+//   gemm_tn     C = [A | A2]^T B  weight gradient dW = A^T dZ, the depth (rows) split over the chip
+//
+// gemm_rows: a workgroup of 4 wavefronts walks row tiles; a wavefront owns 16 R rows and NC column
+// tiles of 16.  Its rows come straight from global memory into the operand layout (a lane reads two
+// 16-byte pieces of its row per 32-deep step, four lanes of a row 64 contiguous bytes) and are split in
+// registers, each element once.  The packed weights of a step go from L2 straight into a
+// double-buffered LDS tile shared by the four wavefronts, one step ahead, across row tiles as well.
+// The weight fragment is the first operand of the instruction, so a lane ends up with four
+// consecutive columns of one row and stores 16 bytes.
+//
+// gemm_tn: a thread reads 16-byte pieces of eight consecutive-depth rows of one operand, which makes
+// it hold eight depths of four columns: after the split each column's eight values are one 16-byte
+// fragment entry in LDS.  The partial tiles are stored as the accumulators lie in the registers;
+// one kernel adds them in a fixed order and puts the elements where they belong.
+//
+// What bounds them: the 128-wide products move 1 KB per row for 32 k flops and are bound by memory,
+// the 512-wide ones by the matrix cores (6 of 16 instruction slots per fp32 product).
+#include <algorithm>
 #include <type_traits>
 
-#include "device_utils.hpp"
 #include "kernels.hpp"
+#include "split_bf16.hpp"
 
 namespace bns {
 
-typedef float floatx16 __attribute__((ext_vector_type(16)));
+// ---- packed weights -----------------------------------------------------------------------------
+// Operand fragments of B [K, N] (or, transposed, of W [N, K]): for depth step s of 32 and column tile t of 16,
+// at ((s * tiles + t) * 3 + piece) KB, lane l's 8 values are column 16 t + l % 16 at the depths
+// 32 s + 16 (e / 4) + 4 (l / 16) + e % 4, e = 0..7, negated in even steps (mfma_split); zero outside the matrix.
+__host__ __device__ static inline int k_steps(int K) { return (K + 31) / 32; }
+__host__ __device__ static inline int col_tiles(int N) { return (N + 15) / 16; }
 
-constexpr int BM = 128, BK = 16;
-constexpr int gemm_threads(int bn, bool a_kcontig) { return (bn == 128 && a_kcontig) ? 512 : 256; }
+size_t packed_bytes(int32_t K, int32_t N) { return (size_t)k_steps(K) * col_tiles(N) * kFragSet; }
 
-// Tile of an operand stored [rows][K] (k-contiguous): ROWS rows x 16 k, one float4 per thread and pass.
-template <int ROWS, int NT> struct FragK { float4 v[ROWS * 4 / NT]; };
-// Tile of an operand stored [K][cols] (contiguous along the tile's COLS columns).
-template <int COLS, int NT> struct FragN { float4 v[BK * COLS / 4 / NT]; };
+struct PackJobs {
+  PackJob j[kMaxPackJobs];
+  int n;
+};
 
-__device__ __forceinline__ float4 load4_guarded(const float *p, bool vec_ok, int valid) {
-  // valid = number of leading elements (0..4) that are in range
-  if (vec_ok && valid == 4) return *reinterpret_cast<const float4 *>(p);
-  float4 r = make_float4(0.f, 0.f, 0.f, 0.f);
-  if (valid > 0) r.x = p[0];
-  if (valid > 1) r.y = p[1];
-  if (valid > 2) r.z = p[2];
-  if (valid > 3) r.w = p[3];
-  return r;
+__global__ void __launch_bounds__(256) pack_weights_kernel(const PackJobs jobs) {
+  int u = blockIdx.x * 4 + (threadIdx.x >> 6);  // one wavefront per fragment set
+  int q = 0, units = 0;
+  for (; q < jobs.n; ++q) {
+    units = k_steps(jobs.j[q].K) * col_tiles(jobs.j[q].N);
+    if (u < units) break;
+    u -= units;
+  }
+  if (q == jobs.n) return;
+  const PackJob &job = jobs.j[q];
+  const int T = col_tiles(job.N);
+  const int s = u / T, t = u % T, lane = lane_id();
+  const int n = t * 16 + (lane & 15), g = lane >> 4;
+  f32x4 v[2];
+#pragma unroll
+  for (int j = 0; j < 2; ++j)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int k = s * 32 + j * 16 + g * 4 + e;
+      const bool ok = k < job.K && n < job.N;
+      v[j][e] = ok ? job.W[job.transposed ? (size_t)n * job.K + k : (size_t)k * job.N + n] : 0.f;
+    }
+  const Frag3 f = s % 2 == 0 ? split8<true>(v[0], v[1]) : split8(v[0], v[1]);
+  char *out = static_cast<char *>(job.out) + (size_t)u * kFragSet + lane * 16;
+#pragma unroll
+  for (int p = 0; p < 3; ++p) *reinterpret_cast<bf16x8 *>(out + p * kFragBytes) = f.p[p];
 }
 
-__device__ __forceinline__ int clamp04(int x) { return x < 0 ? 0 : (x > 4 ? 4 : x); }
-
-// rows row0.. of an operand [R][ld] (k-contiguous); k range [k0, k0+16) limited by k_end
-template <int ROWS, int NT>
-__device__ __forceinline__ void load_kcontig(FragK<ROWS, NT> &f, const float *__restrict__ base, int ld,
-                                             int row0, int n_rows, int k0, int k_end, bool vec_ok) {
-  constexpr int PASSES = ROWS * 4 / NT, RPP = NT / 4;  // rows per pass
-  const int t = threadIdx.x;
-  const int kq = (t & 3) * 4;
-  if (vec_ok && row0 + ROWS <= n_rows && k0 + BK <= k_end) {  // whole tile in range (uniform over the block)
-#pragma unroll
-    for (int p = 0; p < PASSES; ++p)
-      f.v[p] = *reinterpret_cast<const float4 *>(base + (size_t)(row0 + (t >> 2) + p * RPP) * ld + k0 + kq);
-    return;
+hipError_t pack_weights(const PackJob *jobs, int32_t n, hipStream_t s) {
+  for (int32_t i0 = 0; i0 < n; i0 += kMaxPackJobs) {
+    PackJobs pj;
+    pj.n = std::min<int32_t>(kMaxPackJobs, n - i0);
+    int64_t units = 0;
+    for (int i = 0; i < pj.n; ++i) {
+      pj.j[i] = jobs[i0 + i];
+      units += (int64_t)k_steps(pj.j[i].K) * col_tiles(pj.j[i].N);
+    }
+    if (units) pack_weights_kernel<<<(unsigned)((units + 3) / 4), 256, 0, s>>>(pj);
   }
-#pragma unroll
-  for (int p = 0; p < PASSES; ++p) {
-    const int r = row0 + (t >> 2) + p * RPP;
-    const int valid = r < n_rows ? clamp04(k_end - (k0 + kq)) : 0;
-    f.v[p] = load4_guarded(base + (size_t)r * ld + k0 + kq, vec_ok, valid);
-  }
-}
-template <int ROWS, int NT>
-__device__ __forceinline__ void store_kcontig(const FragK<ROWS, NT> &f, float *__restrict__ tile) {
-  constexpr int LD = ROWS + 4;
-  constexpr int PASSES = ROWS * 4 / NT, RPP = NT / 4;
-  const int t = threadIdx.x;
-  const int kq = (t & 3) * 4;
-#pragma unroll
-  for (int p = 0; p < PASSES; ++p) {
-    const int r = (t >> 2) + p * RPP;
-    tile[(kq + 0) * LD + r] = f.v[p].x;
-    tile[(kq + 1) * LD + r] = f.v[p].y;
-    tile[(kq + 2) * LD + r] = f.v[p].z;
-    tile[(kq + 3) * LD + r] = f.v[p].w;
-  }
+  return hipGetLastError();
 }
 
-// operand [K][ld] with the tile's COLS columns starting at col0
-template <int COLS, int NT>
-__device__ __forceinline__ void load_ncontig(FragN<COLS, NT> &f, const float *__restrict__ base, int ld,
-                                             int col0, int n_cols, int k0, int k_end, bool vec_ok) {
-  constexpr int TPR = COLS / 4;              // threads per k-row
-  constexpr int KPP = NT / TPR;              // k-rows per pass
-  const int t = threadIdx.x;
-  const int cq = (t % TPR) * 4;
-  if (vec_ok && col0 + COLS <= n_cols && k0 + BK <= k_end) {  // whole tile in range (uniform over the block)
-#pragma unroll
-    for (int p = 0; p < BK / KPP; ++p)
-      f.v[p] = *reinterpret_cast<const float4 *>(base + (size_t)(k0 + t / TPR + p * KPP) * ld + col0 + cq);
-    return;
-  }
-#pragma unroll
-  for (int p = 0; p < BK / KPP; ++p) {
-    const int k = k0 + t / TPR + p * KPP;
-    const int valid = k < k_end ? clamp04(n_cols - (col0 + cq)) : 0;
-    f.v[p] = load4_guarded(base + (size_t)k * ld + col0 + cq, vec_ok, valid);
-  }
-}
-template <int COLS, int LD, int NT>
-__device__ __forceinline__ void store_ncontig(const FragN<COLS, NT> &f, float *__restrict__ tile) {
-  constexpr int TPR = COLS / 4;
-  constexpr int KPP = NT / TPR;
-  const int t = threadIdx.x;
-  const int cq = (t % TPR) * 4;
-#pragma unroll
-  for (int p = 0; p < BK / KPP; ++p) {
-    const int k = t / TPR + p * KPP;
-    *reinterpret_cast<float4 *>(&tile[k * LD + cq]) = f.v[p];
-  }
-}
+// ---- rows x packed weights ------------------------------------------------------------------------
+struct RowsArgs {
+  RowsGemm g;
+  int T, S, nblk;  // column tiles, depth steps, column blocks
+};
 
-// EPI: 0 = store alpha * product, 1 = ReLU, 2 = zero where mask_src <= 0, alpha * product elsewhere
-// (ReLU/dropout mask of the backward pass), 3 = add to C, 4 = add to C then ReLU.  With EPI 1 or 4 and drop.scale != 0
-// the ReLU output goes through dropout (one counter-based draw per element).
-// m_dev (nullable): the row count lives on the device (*m_dev <= M); tiles past it do nothing.
-// k_dev (nullable): the depth lives on the device (*k_dev <= K); steps past it contribute nothing.
-// A2 (nullable, k-contiguous A only): the operand is the concatenation [A | A2] along the depth,
-// both with row stride lda = a_split (a multiple of 16); for the m-contiguous A of the transposed
-// product it is the concatenation along M (a_split a multiple of 128).  C2 (nullable): the result is the pair
-// [C | C2] split at column c_split (a multiple of the column tile), both with row stride ldc.
-template <int BN, bool A_KCONTIG, bool B_KCONTIG, int EPI>
-// The 8-wavefront tile is held to 64 registers, so that four workgroups (eight wavefronts per SIMD) fit a
-// compute unit: 1 - 2 % on the 512-wide products over three workgroups at 68 registers.
-__global__ void __launch_bounds__(gemm_threads(BN, A_KCONTIG), (BN == 128 && A_KCONTIG) ? 8 : 4)
-gemm_kernel(int M, int N, int K, const float *__restrict__ A, int lda, const float *__restrict__ B,
-            int ldb, float *__restrict__ C, int ldc, int k_chunk, bool vec_a, bool vec_b,
-            const float *__restrict__ mask_src, float alpha, const int *__restrict__ m_dev,
-            const int *__restrict__ k_dev, const Dropout drop, const float *__restrict__ A2, int a_split,
-            float *__restrict__ C2, int c_split) {
-  // Every tile is staged through registers.  (Filling the W tile of the forward product straight
-  // into LDS with global_load_lds paid with four wavefronts per block, costs 3 % with eight; doing
-  // it for both tiles of the transposed product was 25 % slower.)
-  constexpr int LDA = BM + 4, LDB = BN + 4;
-  constexpr int NT = gemm_threads(BN, A_KCONTIG);
-  constexpr bool kEight = NT == 512;
-  constexpr int TI = BN == 128 ? 2 : 1, TJ = kEight ? 1 : 2;  // 32 x 32 MFMA tiles per wavefront: TI x TJ
-  const int m_full = M;
-  if (m_dev) M = min(M, *m_dev);
-  if (k_dev) K = min(K, *k_dev);  // the depth lives on the device (kept boundary rows)
-  __shared__ __attribute__((aligned(16))) float As[2][BK * LDA];
-  __shared__ __attribute__((aligned(16))) float Bs[2][BK * LDB];
+enum RowsEpilogue { kPlain = 0, kRelu = 1, kMask = 2, kPair = 3 };
 
-  const int tiles_n = (N + BN - 1) / BN;
-  const int tm = blockIdx.x / tiles_n, tn = blockIdx.x % tiles_n;
-  const int bm0 = tm * BM, bn0 = tn * BN;
-  if (bm0 >= M) return;
-  const int k_begin = blockIdx.y * k_chunk;
-  const int k_end = min(K, k_begin + k_chunk);
-  C += (size_t)blockIdx.y * m_full * ldc;  // split-K: one partial matrix per split
+template <int R, int NC, int EPI>
+__global__ void __launch_bounds__(256, R * NC > 8 ? 3 : 4) gemm_rows_kernel(const RowsArgs a) {
+  constexpr int kRows = 64 * R;  // rows of a workgroup's tile
+  __shared__ __attribute__((aligned(16))) char Bs[2][NC * kFragSet];
+  const RowsGemm &p = a.g;
+  const int M = p.m_dev ? min(p.M, *p.m_dev) : p.M;
+  // workgroup b runs on XCD b % 8: the column blocks of one row tile follow each other on one XCD, so
+  // that they find its rows in that XCD's L2
+  const int x = blockIdx.x & 7, q = blockIdx.x >> 3;
+  const int nb = q % a.nblk, stride = (gridDim.x / (8 * a.nblk)) * 8;
+  const int t0 = nb * NC;
+  int tile = (q / a.nblk) * 8 + x;
+  const int n_tiles = (M + kRows - 1) / kRows;
+  if (tile >= n_tiles) return;
 
-  const int lane = lane_id(), wid = threadIdx.x >> 6;
-  const int wm = kEight ? (wid >> 2) * 64 : BN == 128 ? (wid >> 1) * 64 : wid * 32;
-  const int wn = kEight ? (wid & 3) * 32 : BN == 128 ? (wid & 1) * 64 : 0;
-  const int l32 = lane & 31, lhi = lane >> 5;
+  const int lane = lane_id(), wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int l16 = lane & 15, g = lane >> 4;
+  const int S = a.S;
+  const bool two = p.A2 != nullptr;
+  const bool vec = !two || p.a_split % 4 == 0;  // a 16-byte piece never straddles the two operands
 
-  floatx16 acc[TI][TJ];
+  f32x4 ar[R][2];
+  const float *row_a[R], *row_a2[R];
+  auto set_rows = [&](int tl) {
 #pragma unroll
-  for (int i = 0; i < TI; ++i)
+    for (int r = 0; r < R; ++r) {
+      const int row = min(M - 1, tl * kRows + wid * 16 * R + r * 16 + l16);  // rows past the end are not stored
+      row_a[r] = p.A + (size_t)row * p.lda;
+      row_a2[r] = two ? p.A2 + (size_t)row * p.lda - p.a_split : nullptr;
+    }
+  };
+  auto load_a = [&](int s) {
 #pragma unroll
-    for (int j = 0; j < TJ; ++j)
+    for (int j = 0; j < 2; ++j) {
+      const int k = s * 32 + j * 16 + g * 4;
+      if (vec && (s + 1) * 32 <= p.K) {
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-  using FA = typename std::conditional<A_KCONTIG, FragK<BM, NT>, FragN<BM, NT>>::type;
-  using FB = typename std::conditional<B_KCONTIG, FragK<BN, NT>, FragN<BN, NT>>::type;
-  FA fa;
-  FB fb;
-  auto load_tiles = [&](int k0) {
-    if constexpr (A_KCONTIG) {
-      const float *Ab = A;
-      int k0a = k0, kea = k_end;
-      if (A2) {  // a depth tile never straddles the seam: a_split is a multiple of BK
-        if (k0 >= a_split) { Ab = A2; k0a = k0 - a_split; kea = k_end - a_split; }
-        else kea = min(k_end, a_split);
+        for (int r = 0; r < R; ++r)
+          ar[r][j] = *reinterpret_cast<const f32x4u *>((two && k >= p.a_split ? row_a2[r] : row_a[r]) + k);
+      } else {
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            ar[r][j][e] = k + e < p.K ? (two && k + e >= p.a_split ? row_a2[r] : row_a[r])[k + e] : 0.f;
       }
-      load_kcontig<BM, NT>(fa, Ab, lda, bm0, M, k0a, kea, vec_a);
-    } else {
-      // [A | A2] along the columns of the m-contiguous operand: a row tile lies in one of them
-      const float *Ab = (A2 && bm0 >= a_split) ? A2 : A;
-      const int c0 = (A2 && bm0 >= a_split) ? bm0 - a_split : bm0;
-      const int nc = A2 ? a_split : M;
-      load_ncontig<BM, NT>(fa, Ab, lda, c0, nc, k0, k_end, vec_a);
-    }
-    if constexpr (B_KCONTIG) {
-      load_kcontig<BN, NT>(fb, B, ldb, bn0, N, k0, k_end, vec_b);
-    } else {
-      load_ncontig<BN, NT>(fb, B, ldb, bn0, N, k0, k_end, vec_b);
     }
   };
-  auto store_tiles = [&](int buf) {
-    if constexpr (A_KCONTIG) store_kcontig<BM, NT>(fa, As[buf]);
-    else store_ncontig<BM, LDA, NT>(fa, As[buf]);
-    if constexpr (B_KCONTIG) store_kcontig<BN, NT>(fb, Bs[buf]);
-    else store_ncontig<BN, LDB, NT>(fb, Bs[buf]);
+  const unsigned lds0 = lds_offset_of(&Bs[0][0]);
+  const int nt = min(NC, a.T - t0);  // column tiles of this block (uniform)
+  auto load_b = [&](int s, int buf) {  // pieces of 1 KB, dealt to the four wavefronts
+    const char *src = static_cast<const char *>(p.Bp) + (size_t)(s * a.T + t0) * kFragSet + lane * 16;
+    for (int c = wid; c < nt * 3; c += 4)
+      lds_dma16(src + c * kFragBytes, lds0 + buf * (NC * kFragSet) + c * kFragBytes);
   };
 
-  const int nk = (k_end - k_begin + BK - 1) / BK;
-  if (nk > 0) {
-    load_tiles(k_begin);
-    store_tiles(0);
-  }
-  __syncthreads();
-  for (int kt = 0; kt < nk; ++kt) {
-    const int buf = kt & 1;
-    if (kt + 1 < nk) load_tiles(k_begin + (kt + 1) * BK);
-    const float *as = As[buf] + wm + l32;
-    const float *bs = Bs[buf] + wn + l32;
+  f32x4 acc[NC][R];
+  auto clear = [&]() {
 #pragma unroll
-    for (int kk = 0; kk < BK; kk += 2) {
-      float a[TI], b[TJ];
+    for (int c = 0; c < NC; ++c)
 #pragma unroll
-      for (int i = 0; i < TI; ++i) a[i] = as[(kk + lhi) * LDA + i * 32];
+      for (int r = 0; r < R; ++r) acc[c][r] = f32x4{0.f, 0.f, 0.f, 0.f};
+  };
+  set_rows(tile);
+  load_b(0, 0);
+  load_a(0);
+  clear();
+  int buf = 0;
+  for (int s = 0;;) {
+    Frag3 fa[R];
+    lds_dma_wait();
+    __syncthreads();  // this step's weights are in LDS, and everybody is done with the other buffer
 #pragma unroll
-      for (int j = 0; j < TJ; ++j) b[j] = bs[(kk + lhi) * LDB + j * 32];
-#pragma unroll
-      for (int i = 0; i < TI; ++i)
-#pragma unroll
-        for (int j = 0; j < TJ; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], acc[i][j], 0, 0, 0);
+    for (int r = 0; r < R; ++r) fa[r] = split8(ar[r][0], ar[r][1]);
+    const bool last = s + 1 == S;
+    const int ntile = last ? tile + stride : tile, ns = last ? 0 : s + 1;
+    if (ntile < n_tiles) {
+      if (last) set_rows(ntile);
+      load_b(ns, buf ^ 1);
+      load_a(ns);
     }
-    if (kt + 1 < nk) store_tiles(buf ^ 1);
-    __syncthreads();
-  }
-
-  // C tile element held by (lane, register r): row = 8*(r/4) + 4*(lane/32) + r%4, col = lane%32
+    const char *bs = &Bs[buf][0] + lane * 16;
 #pragma unroll
-  for (int i = 0; i < TI; ++i)
+    for (int c = 0; c < NC; ++c) {
+      Frag3 fb;
 #pragma unroll
-    for (int j = 0; j < TJ; ++j) {
-      int col = bn0 + wn + j * 32 + l32;
-      // a result with padded rows (ldc > N, plain store only): columns N..ldc-1 are cleared
-      const bool pad_col = col >= N;
-      if (pad_col && !(EPI == 0 && C2 == nullptr && col < ldc)) continue;
-      float *Cd = C;
-      if (C2 && col >= c_split) { Cd = C2; col -= c_split; }  // column tiles never straddle c_split
+      for (int i = 0; i < 3; ++i) fb.p[i] = *reinterpret_cast<const bf16x8 *>(bs + c * kFragSet + i * kFragBytes);
+      mfma_split<R>(acc[c], fb, fa, s & 1 ? 1.f : -1.f);
+    }
+    buf ^= 1;
+    if (last) {
+      // lane: row l16 of the row tile, columns 16 c + 4 g .. + 3.  A result with padded rows: the columns
+      // N..ldc-1 hold the zeros of the packed weights
+      const int n_end = EPI == kPlain && p.pad ? p.ldc : p.N, col0 = t0 * 16 + g * 4;
 #pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        const int row4 = bm0 + wm + i * 32 + q4 * 8 + lhi * 4;  // a multiple of 4
+      for (int r = 0; r < R; ++r) {
+        const int row = tile * kRows + wid * 16 * R + r * 16 + l16;
+        if (row >= M) continue;
+        const size_t at = (size_t)row * p.ldc + col0;
+        float *const dst = p.C + at;
+        float *const dst2 = EPI == kPair ? p.C2 + at - p.c_split : nullptr;  // c_split % 4 == 0
+        const float *const ms = EPI == kMask ? p.mask + at : nullptr;
 #pragma unroll
-        for (int rr = 0; rr < 4; ++rr) {
-          const int row = row4 + rr;
-          if (row < M) {
-            float x = acc[i][j][q4 * 4 + rr];
-            if (EPI == 3 || EPI == 4) x += Cd[(size_t)row * ldc + col];
-            if (EPI == 1 || EPI == 4) {
-              x = fmaxf(x, 0.f);
-              if (drop.scale != 0.f) x = dropout_keeps(drop, row, col) ? x * drop.scale : 0.f;
+        for (int c = 0; c < NC; ++c) {
+          const int left = n_end - (col0 + c * 16);  // columns from this lane's first one to the end
+          f32x4 v = acc[c][r];
+          if constexpr (EPI == kMask) {
+            f32x4 m = {0.f, 0.f, 0.f, 0.f};
+            if (left >= 4) m = *reinterpret_cast<const f32x4u *>(ms + c * 16);
+            else
+#pragma unroll
+              for (int e = 0; e < 3; ++e)
+                if (e < left) m[e] = ms[c * 16 + e];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = m[e] > 0.f ? v[e] * p.alpha : 0.f;
+          } else if constexpr (EPI == kRelu) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = fmaxf(v[e], 0.f);
+            if (p.drop.scale != 0.f) {
+#pragma unroll 1
+              for (int e = 0; e < 4; ++e) {
+                const float y = dropout_keeps(p.drop, row, col0 + c * 16 + e) ? v[0] * p.drop.scale : 0.f;
+                v = f32x4{v[1], v[2], v[3], y};
+              }
             }
-            if (EPI == 2) x = mask_src[(size_t)row * ldc + col] > 0.f ? x * alpha : 0.f;
-            if (EPI == 0) x = pad_col ? 0.f : x * alpha;
-            Cd[(size_t)row * ldc + col] = x;
+          } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] *= p.alpha;
           }
+          float *const d = (EPI == kPair && col0 + c * 16 >= p.c_split ? dst2 : dst) + c * 16;
+          if (left >= 4) *reinterpret_cast<f32x4u *>(d) = v;
+          else
+#pragma unroll
+            for (int e = 0; e < 3; ++e)
+              if (e < left) d[e] = v[e];
         }
       }
+      if (ntile >= n_tiles) break;
+      clear();
+      tile = ntile;
     }
-}
-
-static inline bool aligned16(const void *p) { return ((uintptr_t)p & 15) == 0; }
-
-// Column-tile width: the one that pads N to fewer columns (ties go to the wider tile).
-static inline int pick_bn(int N) {
-  const int pad128 = (N + 127) / 128 * 128, pad64 = (N + 63) / 64 * 64;
-  return pad64 < pad128 ? 64 : 128;
-}
-static inline unsigned n_tiles(int M, int N, int bn) {
-  return (unsigned)(((M + BM - 1) / BM) * ((N + bn - 1) / bn));
-}
-
-#define BNS_GEMM_LAUNCH(AK, BK_, EPI, grid, ...)                                                 \
-  do {                                                                                           \
-    if (bn == 64) gemm_kernel<64, AK, BK_, EPI><<<grid, gemm_threads(64, AK), 0, s>>>(__VA_ARGS__);  \
-    else gemm_kernel<128, AK, BK_, EPI><<<grid, gemm_threads(128, AK), 0, s>>>(__VA_ARGS__);         \
-  } while (0)
-
-hipError_t gemm_nn(int32_t M, int32_t N, int32_t K, const float *A, const float *B, float *C,
-                   bool relu, bool accumulate, const Dropout &drop, const int32_t *m_dev, hipStream_t s,
-                   int32_t ldc) {
-  if (ldc == 0) ldc = N;
-  if (ldc < N) return hipErrorInvalidValue;
-  const int bn = pick_bn(N);
-  const unsigned tiles = n_tiles(M, N, bn);
-  if (tiles == 0) return hipSuccess;
-  const bool va = (K % 4 == 0) && aligned16(A), vb = (N % 4 == 0) && aligned16(B);
-  const dim3 grid(tiles, 1);
-  if (accumulate && relu) BNS_GEMM_LAUNCH(true, false, 4, grid, M, N, K, A, K, B, N, C, ldc, K, va, vb, nullptr, 1.f, m_dev, nullptr, drop, nullptr, 0, nullptr, 0);
-  else if (accumulate) BNS_GEMM_LAUNCH(true, false, 3, grid, M, N, K, A, K, B, N, C, ldc, K, va, vb, nullptr, 1.f, m_dev, nullptr, drop, nullptr, 0, nullptr, 0);
-  else if (relu) BNS_GEMM_LAUNCH(true, false, 1, grid, M, N, K, A, K, B, N, C, ldc, K, va, vb, nullptr, 1.f, m_dev, nullptr, drop, nullptr, 0, nullptr, 0);
-  else BNS_GEMM_LAUNCH(true, false, 0, grid, M, N, K, A, K, B, N, C, ldc, K, va, vb, nullptr, 1.f, m_dev, nullptr, drop, nullptr, 0, nullptr, 0);
-  return hipGetLastError();
-}
-
-hipError_t gemm_nn_concat(int32_t M, int32_t N, int32_t K_half, const float *A1, const float *A2,
-                          const float *B, float *C, bool relu, const Dropout &drop, hipStream_t s) {
-  if (K_half % BK != 0) return hipErrorInvalidValue;
-  const int bn = pick_bn(N);
-  const unsigned tiles = n_tiles(M, N, bn);
-  if (tiles == 0) return hipSuccess;
-  const int K = 2 * K_half;
-  const bool va = (K_half % 4 == 0) && aligned16(A1) && aligned16(A2), vb = (N % 4 == 0) && aligned16(B);
-  const dim3 grid(tiles, 1);
-  if (relu) BNS_GEMM_LAUNCH(true, false, 1, grid, M, N, K, A1, K_half, B, N, C, N, K, va, vb, nullptr, 1.f, nullptr, nullptr, drop, A2, K_half, nullptr, 0);
-  else BNS_GEMM_LAUNCH(true, false, 0, grid, M, N, K, A1, K_half, B, N, C, N, K, va, vb, nullptr, 1.f, nullptr, nullptr, drop, A2, K_half, nullptr, 0);
-  return hipGetLastError();
-}
-
-bool gemm_nt_pair_supported(int32_t N_half) { return N_half % 64 == 0; }
-
-hipError_t gemm_nt_pair(int32_t M, int32_t N_half, int32_t K, const float *A, const float *B, float *C1,
-                        float *C2, float alpha, hipStream_t s) {
-  if (!gemm_nt_pair_supported(N_half)) return hipErrorInvalidValue;
-  const int N = 2 * N_half;
-  const int bn = N_half % 128 == 0 ? 128 : 64;  // a column tile must not straddle the two results
-  const unsigned tiles = n_tiles(M, N, bn);
-  if (tiles == 0) return hipSuccess;
-  const bool va = (K % 4 == 0) && aligned16(A), vb = (K % 4 == 0) && aligned16(B);
-  const dim3 grid(tiles, 1);
-  BNS_GEMM_LAUNCH(true, true, 0, grid, M, N, K, A, K, B, K, C1, N_half, K, va, vb, nullptr, alpha, nullptr, nullptr, Dropout{}, nullptr, 0, C2, N_half);
-  return hipGetLastError();
-}
-
-hipError_t gemm_nt(int32_t M, int32_t N, int32_t K, const float *A, const float *B, float *C,
-                   const float *mask_src, float alpha, const int32_t *m_dev, hipStream_t s) {
-  const int bn = pick_bn(N);
-  const unsigned tiles = n_tiles(M, N, bn);
-  if (tiles == 0) return hipSuccess;
-  const bool va = (K % 4 == 0) && aligned16(A), vb = (K % 4 == 0) && aligned16(B);
-  const dim3 grid(tiles, 1);
-  if (mask_src) BNS_GEMM_LAUNCH(true, true, 2, grid, M, N, K, A, K, B, K, C, N, K, va, vb, mask_src, alpha, m_dev, nullptr, Dropout{}, nullptr, 0, nullptr, 0);
-  else BNS_GEMM_LAUNCH(true, true, 0, grid, M, N, K, A, K, B, K, C, N, K, va, vb, nullptr, alpha, m_dev, nullptr, Dropout{}, nullptr, 0, nullptr, 0);
-  return hipGetLastError();
-}
-
-// ---- split-K -----------------------------------------------------------------------------------
-// one round of resident workgroups: 256 compute units x 4 (LDS and registers allow four); measured
-// against 512, 768, 1536 and 2048 on workloads 2 - 5
-constexpr int kSplitTargetBlocks = 1024;
-constexpr int kReduceGroup = 16;
-
-static inline int splitk_chunk(int32_t M, int32_t N, int32_t K, int *splits_out) {
-  const int tiles = (int)n_tiles(M, N, pick_bn(N));
-  int splits = (kSplitTargetBlocks + tiles - 1) / tiles;
-  const int max_splits = (K + 4 * BK - 1) / (4 * BK);  // at least 64 rows of K per split
-  if (splits > max_splits) splits = max_splits;
-  if (splits < 1) splits = 1;
-  int chunk = (K + splits - 1) / splits;
-  chunk = ((chunk + BK - 1) / BK) * BK;
-  splits = (K + chunk - 1) / chunk;
-  if (splits < 1) splits = 1;
-  *splits_out = splits;
-  return chunk;
-}
-
-int32_t splitk_splits(int32_t M, int32_t N, int32_t K) {
-  int s;
-  splitk_chunk(M, N, K, &s);
-  // first-level partials plus the second-level buffer of the grouped reduction
-  return s + (s + kReduceGroup - 1) / kReduceGroup;
-}
-
-// out[g][i] = sum over the splits z of group g (in ascending z) of in[z][i]
-__global__ void __launch_bounds__(256)
-splitk_reduce_kernel(const float *__restrict__ in, float *__restrict__ out, int64_t mn, int splits,
-                     bool add_to_out) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= mn) return;
-  const int z0 = blockIdx.y * kReduceGroup;
-  const int z1 = min(splits, z0 + kReduceGroup);
-  float sum = 0.f;
-  for (int z = z0; z < z1; ++z) sum += in[(size_t)z * mn + i];
-  if (add_to_out) sum += out[(size_t)blockIdx.y * mn + i];
-  out[(size_t)blockIdx.y * mn + i] = sum;
-}
-
-hipError_t gemm_tn_splitk(int32_t M, int32_t N, int32_t K, const float *A, const float *B,
-                          float *C, float *partials, bool accumulate, const int32_t *k_dev, hipStream_t s) {
-  return gemm_tn_splitk_concat(M, N, K, A, nullptr, B, C, partials, accumulate, k_dev, s);
-}
-
-bool gemm_tn_concat_supported(int32_t M_half) { return M_half % BM == 0; }
-
-// A2 != nullptr: C[2 M, N] = [A | A2]^T B with A, A2 [K, M] (M here is the width of one of them).
-hipError_t gemm_tn_splitk_concat(int32_t M, int32_t N, int32_t K, const float *A, const float *A2, const float *B,
-                                 float *C, float *partials, bool accumulate, const int32_t *k_dev,
-                                 hipStream_t s) {
-  const int M_half = M;
-  if (A2) {
-    if (!gemm_tn_concat_supported(M_half)) return hipErrorInvalidValue;
-    M = 2 * M_half;
+    s = ns;
   }
-  const int bn = pick_bn(N);
-  const unsigned tiles = n_tiles(M, N, bn);
-  if (tiles == 0) return hipSuccess;
-  int splits;
-  const int chunk = splitk_chunk(M, N, K, &splits);
-  const bool va = (M_half % 4 == 0) && aligned16(A) && aligned16(A2), vb = (N % 4 == 0) && aligned16(B);
-  const int64_t mn = (int64_t)M * N;
-  float *dst = splits == 1 ? C : partials;
-  const dim3 grid(tiles, splits);
-  if (splits == 1 && accumulate)
-    BNS_GEMM_LAUNCH(false, false, 3, grid, M, N, K, A, M_half, B, N, dst, N, chunk, va, vb, nullptr, 1.f, nullptr, k_dev, Dropout{}, A2, M_half, nullptr, 0);
-  else
-    BNS_GEMM_LAUNCH(false, false, 0, grid, M, N, K, A, M_half, B, N, dst, N, chunk, va, vb, nullptr, 1.f, nullptr, k_dev, Dropout{}, A2, M_half, nullptr, 0);
-  // grouped, fixed-order reduction: partials -> level 2 -> ... -> C
-  float *cur = partials;
-  float *nxt = partials + (size_t)splits * mn;
-  int n = splits;
-  while (n > 1) {
-    const int groups = (n + kReduceGroup - 1) / kReduceGroup;
-    float *out = groups == 1 ? C : nxt;
-    splitk_reduce_kernel<<<dim3((unsigned)((mn + 255) / 256), groups), 256, 0, s>>>(cur, out, mn, n,
-                                                                                  accumulate && groups == 1);
-    float *t = cur; cur = nxt; nxt = t;   // ping-pong (level >= 3 reuses the first buffer)
-    n = groups;
+}
+
+template <int R, int EPI>
+static void launch_rows(const RowsArgs &a, int nc, unsigned grid, hipStream_t s) {
+  switch (nc) {
+    case 1: gemm_rows_kernel<R, 1, EPI><<<grid, 256, 0, s>>>(a); break;
+    case 2: gemm_rows_kernel<R, 2, EPI><<<grid, 256, 0, s>>>(a); break;
+    case 3: gemm_rows_kernel<R, 3, EPI><<<grid, 256, 0, s>>>(a); break;
+    case 4: gemm_rows_kernel<R, 4, EPI><<<grid, 256, 0, s>>>(a); break;
+    case 5: gemm_rows_kernel<R, 5, EPI><<<grid, 256, 0, s>>>(a); break;
+    case 6: gemm_rows_kernel<R, 6, EPI><<<grid, 256, 0, s>>>(a); break;
+    case 7: gemm_rows_kernel<R, 7, EPI><<<grid, 256, 0, s>>>(a); break;
+    default: gemm_rows_kernel<R, 8, EPI><<<grid, 256, 0, s>>>(a); break;
   }
+}
+template <int R>
+static void launch_rows(const RowsArgs &a, int nc, unsigned grid, hipStream_t s) {
+  if (a.g.C2) launch_rows<R, kPair>(a, nc, grid, s);
+  else if (a.g.mask) launch_rows<R, kMask>(a, nc, grid, s);
+  else if (a.g.relu) launch_rows<R, kRelu>(a, nc, grid, s);
+  else launch_rows<R, kPlain>(a, nc, grid, s);
+}
+
+hipError_t gemm_rows(const RowsGemm &g, hipStream_t s) {
+  if (g.M <= 0 || g.N <= 0) return hipSuccess;
+  if (g.C2 ? g.c_split % 4 != 0 || g.ldc < g.c_split || g.N > 2 * g.c_split : g.ldc < g.N) return hipErrorInvalidValue;
+  if (g.pad && g.ldc > (g.N + 3) / 4 * 4) return hipErrorInvalidValue;
+  if ((g.C2 != nullptr) + (g.mask != nullptr) + g.relu + g.pad > 1) return hipErrorInvalidValue;
+  RowsArgs a;
+  a.g = g;
+  a.T = col_tiles(g.N);
+  a.S = k_steps(g.K);
+  // Up to 8 column tiles per wavefront, evenly dealt.  Where that leaves the chip short of workgroups
+  // (three fit a compute unit), smaller tiles: first half the rows, then half the columns.
+  constexpr int kWanted = 512;
+  a.nblk = (a.T + 7) / 8;
+  int R = 2;
+  auto groups = [&]() { return (int64_t)((g.M + 64 * R - 1) / (64 * R)) * a.nblk; };
+  if (groups() < kWanted) R = 1;
+  while (groups() < kWanted && a.nblk * 2 <= a.T) a.nblk *= 2;
+  int nc = (a.T + a.nblk - 1) / a.nblk;
+  a.nblk = (a.T + nc - 1) / nc;
+  const int64_t row_tiles = (g.M + 64 * R - 1) / (64 * R);
+  // a grid of whole octets of row tiles, every column block of each; the tiles past one resident round are walked
+  int64_t octets = std::min<int64_t>((row_tiles + 7) / 8, std::max<int64_t>(1, 768 / (8 * a.nblk)));
+  const unsigned grid = (unsigned)(octets * 8 * a.nblk);
+  if (R == 2) launch_rows<2>(a, nc, grid, s);
+  else launch_rows<1>(a, nc, grid, s);
+  return hipGetLastError();
+}
+
+// ---- transposed product, depth split over the chip -----------------------------------------------
+struct TnArgs {
+  const float *A, *A2, *B;
+  int M, N, K, a_split, lda;
+  const int *k_dev;
+  float *partials;
+  int tiles_m, tiles_n, splits;
+};
+
+// Bytes between the fragment sets of neighbouring 16-column tiles in LDS: 64 more than a set, so
+// that the eight lanes that store together (four columns of two tiles) hit different banks.
+constexpr int kTnTile = kFragSet + 64;
+
+template <int MB, int NB>
+__global__ void __launch_bounds__(256, 3) gemm_tn_kernel(const TnArgs a) {
+  constexpr int KS = MB + NB > 128 ? 32 : 64;          // depth of a step: keeps all 256 threads loading
+  constexpr int TM = MB / 16, TN = NB / 16, TILES = TM + TN;
+  constexpr int GA = MB / 4, GB = NB / 4;              // 4-column groups of the two operands
+  constexpr int KG = KS / 8;                           // groups of eight depths
+  constexpr int MT = TM / 2, NT = TN / 2;              // 16 x 16 tiles of a wavefront (2 x 2 wavefronts)
+  static_assert((GA + GB) * KG <= 256, "one load unit per thread");
+  __shared__ __attribute__((aligned(16))) char lds[(KS / 32) * TILES * kTnTile];
+
+  const int nt = a.tiles_m * a.tiles_n;
+  int tile, split;
+  if (a.splits % 8 == 0) {  // the tiles of one depth chunk follow each other on one XCD
+    const int x = blockIdx.x & 7, q = blockIdx.x >> 3;
+    tile = q % nt;
+    split = (q / nt) * 8 + x;
+  } else {
+    tile = blockIdx.x % nt;
+    split = blockIdx.x / nt;
+  }
+  const int m0 = (tile / a.tiles_n) * MB, n0 = (tile % a.tiles_n) * NB;
+  const int K = a.k_dev ? min(a.K, *a.k_dev) : a.K;
+  const int chunk = ((K + a.splits - 1) / a.splits + KS - 1) / KS * KS;  // from the real depth, which may live on the device
+  const int k_begin = split * chunk, k_end = min(K, k_begin + chunk);
+
+  // load unit of this thread: operand, 4-column group, group of eight depths
+  const int t = threadIdx.x;
+  const bool is_b = t >= GA * KG;
+  const int u = is_b ? t - GA * KG : t;
+  const int gcount = is_b ? GB : GA;
+  const int c4 = u % gcount, kg = u / gcount;
+  const bool active = kg < KG;
+  const float *src;
+  int ld, cols;  // columns in range at src (0..4)
+  if (is_b) {
+    src = a.B + n0 + c4 * 4;
+    ld = a.N;
+    cols = a.N - (n0 + c4 * 4);
+  } else {
+    int c = m0 + c4 * 4;
+    src = a.A + c;
+    ld = a.lda;
+    cols = (a.A2 ? a.a_split : a.M) - c;
+    if (a.A2 && cols <= 0) {
+      src = a.A2 + c - a.a_split;
+      cols = a.M - c;
+    }
+  }
+  const bool straddle = !is_b && a.A2 && cols > 0 && cols < 4;  // a_split % 4 != 0: one group takes from both
+  const int row_of_a2 = straddle ? m0 + c4 * 4 - a.a_split : 0;
+  cols = straddle ? min(4, a.M - (m0 + c4 * 4)) : max(0, min(4, cols));
+  f32x4 v[8];
+  auto load = [&](int k0) {
+    const int k = k0 + kg * 8;
+    if (!active) return;
+    if (cols == 4 && !straddle && k + 8 <= k_end) {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) v[j] = *reinterpret_cast<const f32x4u *>(src + (size_t)(k + j) * ld);
+    } else {
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          float xv = 0.f;
+          if (e < cols && k + j < k_end)
+            xv = straddle && row_of_a2 + e >= 0 ? a.A2[(size_t)(k + j) * ld + row_of_a2 + e] : src[(size_t)(k + j) * ld + e];
+          v[j][e] = xv;
+        }
+    }
+  };
+  // column 4 c4 + i sits in slot 4 i + c4 % 4 of its tile (so that four lanes store 64 contiguous bytes)
+  char *dst = lds + ((size_t)(kg / 4) * TILES + (is_b ? TM : 0) + c4 / 4) * kTnTile + ((kg & 3) * 16 + (c4 & 3)) * 16;
+  // odd splits work on the negated A (mfma_split) and negate their sums when they store them
+  auto stage = [&](auto neg) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const Frag3 f = split8<decltype(neg)::value>(f32x4{v[0][i], v[1][i], v[2][i], v[3][i]}, f32x4{v[4][i], v[5][i], v[6][i], v[7][i]});
+#pragma unroll
+      for (int p = 0; p < 3; ++p) *reinterpret_cast<bf16x8 *>(dst + p * kFragBytes + i * 64) = f.p[p];
+    }
+  };
+  const bool neg = (split & 1) && !is_b;
+
+  const int lane = lane_id(), wid = t >> 6, wm = wid >> 1, wn = wid & 1;
+  f32x4 acc[NT][MT];
+#pragma unroll
+  for (int j = 0; j < NT; ++j)
+#pragma unroll
+    for (int i = 0; i < MT; ++i) acc[j][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  if (k_begin < k_end) load(k_begin);
+  for (int k0 = k_begin; k0 < k_end; k0 += KS) {
+    __syncthreads();  // the previous step's fragments have been read
+    if (active) {
+      if (neg) stage(std::true_type{});
+      else stage(std::false_type{});
+    }
+    __syncthreads();
+    if (k0 + KS < k_end) load(k0 + KS);
+#pragma unroll
+    for (int ks = 0; ks < KS / 32; ++ks) {
+      const char *base = lds + (size_t)ks * TILES * kTnTile + lane * 16;
+      Frag3 fm[MT];
+#pragma unroll
+      for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int p = 0; p < 3; ++p)
+          fm[i].p[p] = *reinterpret_cast<const bf16x8 *>(base + (wm * MT + i) * kTnTile + p * kFragBytes);
+#pragma unroll
+      for (int j = 0; j < NT; ++j) {
+        Frag3 fn;
+#pragma unroll
+        for (int p = 0; p < 3; ++p)
+          fn.p[p] = *reinterpret_cast<const bf16x8 *>(base + (TM + wn * NT + j) * kTnTile + p * kFragBytes);
+        mfma_split<MT>(acc[j], fn, fm);
+      }
+    }
+  }
+  float *out = a.partials + (size_t)(split * nt + tile) * (MB * NB) + (size_t)wid * (MT * NT * 256) + lane * 4;
+#pragma unroll
+  for (int j = 0; j < NT; ++j)
+#pragma unroll
+    for (int i = 0; i < MT; ++i) *reinterpret_cast<f32x4 *>(out + (j * MT + i) * 256) = split & 1 ? -acc[j][i] : acc[j][i];
+}
+
+// C = (C +) sum over the splits, in a fixed order; optionally W -= lr * C (the update step of
+// Algorithm 1 takes its gradient from the registers).  A workgroup owns one 16 x 16 accumulator
+// tile: NW wavefronts add every NW-th partial of it, then their sums are added in ascending order.
+struct TnReduce {
+  const float *partials;
+  float *C, *W;
+  float lr;
+  int M, N, tiles_n, nt, splits;
+  bool accumulate;
+};
+
+template <int MB, int NB, int NW>
+__global__ void __launch_bounds__(NW * 64) gemm_tn_reduce_kernel(const TnReduce a) {
+  constexpr int MT = MB / 32, NT = NB / 32, F = MB * NB / 256;
+  __shared__ float part[NW][256];
+  const int lane = lane_id(), wid = threadIdx.x >> 6;
+  const int tile = blockIdx.x / F, f = blockIdx.x % F;
+  const size_t stride = (size_t)a.nt * (MB * NB);
+  const float *in = a.partials + (size_t)tile * (MB * NB) + f * 256 + lane * 4;
+  f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+  constexpr int U = 4;
+  for (int z0 = wid; z0 < a.splits; z0 += U * NW) {
+    f32x4 x[U];
+#pragma unroll
+    for (int i = 0; i < U; ++i)
+      x[i] = z0 + i * NW < a.splits ? *reinterpret_cast<const f32x4 *>(in + (size_t)(z0 + i * NW) * stride) : f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < U; ++i) sum += x[i];
+  }
+  *reinterpret_cast<f32x4 *>(&part[wid][lane * 4]) = sum;
+  __syncthreads();
+  const int e = threadIdx.x;
+  if (e >= 256) return;
+  float s = 0.f;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) s += part[w][e];
+  // element e: lane e / 4, register e % 4; its slots in the two 16-column tiles are 4 (lane / 16) + e % 4
+  // (columns of B) and lane % 16 (columns of A), slot q standing for column 4 (q % 4) + q / 4
+  const int l = e >> 2, w4 = f / (MT * NT), ji = f % (MT * NT);
+  const int j = ji / MT, i = ji % MT, sa = l & 15;
+  const int m = (tile / a.tiles_n) * MB + ((w4 >> 1) * MT + i) * 16 + 4 * (sa & 3) + (sa >> 2);
+  const int n = (tile % a.tiles_n) * NB + ((w4 & 1) * NT + j) * 16 + 4 * (e & 3) + (l >> 4);
+  if (m >= a.M || n >= a.N) return;
+  const size_t at = (size_t)m * a.N + n;
+  if (a.accumulate) s += a.C[at];
+  a.C[at] = s;
+  if (a.W) a.W[at] -= a.lr * s;
+}
+
+namespace {
+
+struct TnPlan { int mb, nb, tiles_m, tiles_n, splits; };
+
+// Tile shape: the one that pads the result least; among equals the larger one (an operand is read
+// once per tile of the other).  Splits: three workgroups per compute unit, at least 64 rows each.
+TnPlan tn_plan(int32_t M, int32_t N, int32_t K) {
+  static const int mbs[2] = {128, 64}, nbs[4] = {128, 96, 64, 32};
+  TnPlan b{};
+  int64_t best = 0;
+  for (int mb : mbs)
+    for (int nb : nbs) {
+      const int64_t area = (int64_t)((M + mb - 1) / mb * mb) * ((N + nb - 1) / nb * nb);
+      if (b.mb == 0 || area * 10 < best * 9) {
+        b.mb = mb;
+        b.nb = nb;
+        best = area;
+      }
+    }
+  b.tiles_m = (M + b.mb - 1) / b.mb;
+  b.tiles_n = (N + b.nb - 1) / b.nb;
+  const int nt = b.tiles_m * b.tiles_n;
+  int64_t splits = std::max(1, 768 / nt);
+  splits = std::max<int64_t>(1, std::min<int64_t>(splits, (K + 63) / 64));
+  if (splits >= 8) splits = splits / 8 * 8;
+  b.splits = (int)splits;  // trailing splits may be empty: they store zeros
+  return b;
+}
+
+template <int MB, int NB>
+void launch_tn(const TnArgs &a, const TnReduce &r, hipStream_t s) {
+  gemm_tn_kernel<MB, NB><<<(unsigned)(r.nt * a.splits), 256, 0, s>>>(a);
+  const unsigned blocks = (unsigned)(r.nt * (MB * NB / 256));
+  if (a.splits > 32) gemm_tn_reduce_kernel<MB, NB, 16><<<blocks, 1024, 0, s>>>(r);
+  else gemm_tn_reduce_kernel<MB, NB, 4><<<blocks, 256, 0, s>>>(r);
+}
+
+}  // namespace
+
+size_t gemm_tn_partials(int32_t M, int32_t N, int32_t K) {
+  const TnPlan b = tn_plan(M, N, K);
+  return (size_t)b.splits * b.tiles_m * b.tiles_n * b.mb * b.nb;
+}
+
+hipError_t gemm_tn(const TnGemm &g, hipStream_t s) {
+  if (g.M <= 0 || g.N <= 0) return hipSuccess;
+  const TnPlan b = tn_plan(g.M, g.N, g.K);
+  TnArgs a{g.A, g.A2, g.B, g.M, g.N, g.K, g.a_split, g.A2 ? g.a_split : g.M, g.k_dev, g.partials, b.tiles_m, b.tiles_n, b.splits};
+  TnReduce r{g.partials, g.C, g.lr > 0.f ? g.W : nullptr, g.lr, g.M, g.N, b.tiles_n, b.tiles_m * b.tiles_n, b.splits, g.accumulate};
+#define BNS_TN(MB_, NB_) if (b.mb == MB_ && b.nb == NB_) launch_tn<MB_, NB_>(a, r, s)
+  BNS_TN(128, 128); BNS_TN(128, 96); BNS_TN(128, 64); BNS_TN(128, 32);
+  BNS_TN(64, 128); BNS_TN(64, 96); BNS_TN(64, 64); BNS_TN(64, 32);
+#undef BNS_TN
   return hipGetLastError();
 }
 

@@ -166,40 +166,63 @@ struct Dropout {
   uint32_t k0 = 0, k1 = 0, c2 = 0, epoch = 0;
   const uint32_t *epoch_dev = nullptr;  // nullable: the epoch index is read from device memory
 };
-// C[M,N] = A[M,K] B[K,N] (+ the previous C if accumulate), then optional ReLU (followed by dropout
-// when drop.scale != 0).
-// m_dev (nullable): device-side row count, *m_dev <= M; rows past it are not touched.
-// ldc: row stride of C (0 = N); without relu / accumulate the columns N..ldc-1 are set to zero.
-hipError_t gemm_nn(int32_t M, int32_t N, int32_t K, const float *A, const float *B, float *C,
-                   bool relu, bool accumulate, const Dropout &drop, const int32_t *m_dev, hipStream_t s,
-                   int32_t ldc = 0);
-// C[M,N] = [A1 | A2] B with A1, A2 [M,K_half] and B [2 K_half, N] (the concat update of the mean
-// aggregator layer, Section 2), then optional ReLU / dropout.  Needs K_half % 16 == 0.
-hipError_t gemm_nn_concat(int32_t M, int32_t N, int32_t K_half, const float *A1, const float *A2,
-                          const float *B, float *C, bool relu, const Dropout &drop, hipStream_t s);
-// [C1 | C2] = alpha * A[M,K] B[2 N_half,K]^T, C1 and C2 dense [M,N_half].  Needs N_half % 64 == 0.
-bool gemm_nt_pair_supported(int32_t N_half);
-hipError_t gemm_nt_pair(int32_t M, int32_t N_half, int32_t K, const float *A, const float *B, float *C1,
-                        float *C2, float alpha, hipStream_t s);
+// A weight matrix laid out for the products below: split into bf16 pieces, operand fragments in the order
+// they are read.  W [K, N], or W [N, K] when transposed; out: packed_bytes(K, N), 16-byte aligned.
+struct PackJob {
+  const float *W;
+  void *out;
+  int32_t K, N;
+  bool transposed;
+};
+constexpr int kMaxPackJobs = 16;  // per launch
+size_t packed_bytes(int32_t K, int32_t N);
+hipError_t pack_weights(const PackJob *jobs, int32_t n, hipStream_t s);
+
+// C[M,N] = alpha * [A | A2] B with B [K,N] packed.  A, A2 [M, lda]: the depth below a_split is A's, the rest A2's
+// (A2 nullable).  At most one of: C2 (nullable): columns from c_split (a multiple of 4) on go to C2, both with row
+// stride ldc; mask (nullable, [M, ldc]): C is zeroed where mask <= 0; relu (without alpha): max(., 0), then dropout
+// when drop.scale != 0; pad: the columns N..ldc-1 are set to zero (ldc at most N rounded up to a multiple of 4).
+// m_dev (nullable): row count on
+// the device, *m_dev <= M; rows past it are not touched.
+struct RowsGemm {
+  int32_t M, N, K;
+  const float *A, *A2;
+  int32_t lda, a_split;
+  const void *Bp;
+  float *C, *C2;
+  int32_t ldc, c_split;
+  float alpha;
+  bool relu, pad;
+  const float *mask;
+  const int32_t *m_dev;
+  Dropout drop;
+};
+inline RowsGemm rows_gemm(int32_t M, int32_t N, int32_t K, const float *A, const void *Bp, float *C) {
+  RowsGemm g{};
+  g.M = M; g.N = N; g.K = K; g.A = A; g.lda = K; g.Bp = Bp; g.C = C; g.ldc = N; g.alpha = 1.f;
+  return g;
+}
+hipError_t gemm_rows(const RowsGemm &g, hipStream_t s);
+
 // inv[i] = deg[i] > 1 ? 1 / (deg[i] - 1) : 0   (deg counts the self-loop)
 hipError_t degree_inverse(const int32_t *deg, int32_t n, float *inv, hipStream_t s);
-// C[M,N] = alpha * A[M,K] B[N,K]^T.  mask_src (nullable, [M,N]): C is zeroed where mask_src <= 0.
-// m_dev (nullable): device-side row count, *m_dev <= M; rows past it are not touched.
-hipError_t gemm_nt(int32_t M, int32_t N, int32_t K, const float *A, const float *B, float *C,
-                   const float *mask_src, float alpha, const int32_t *m_dev, hipStream_t s);
-// C[M,N] = A[K,M]^T B[K,N] with K split over the grid; partials: scratch f32[splits*M*N],
-// summed in a fixed order.  splitk_splits() gives the split count used for (M,N,K).
-int32_t splitk_splits(int32_t M, int32_t N, int32_t K);
-// accumulate: the product is added to C.  k_dev (nullable): device-side depth, *k_dev <= K (the
-// partial buffer is still sized by splitk_splits(M, N, K)).
-hipError_t gemm_tn_splitk(int32_t M, int32_t N, int32_t K, const float *A, const float *B,
-                          float *C, float *partials, bool accumulate, const int32_t *k_dev, hipStream_t s);
-// C[2 M, N] = [A | A2]^T B with A, A2 [K, M] (weight gradient of the concat update); needs M % 128 == 0
-// and partials sized by splitk_splits(2 M, N, K).
-bool gemm_tn_concat_supported(int32_t M_half);
-hipError_t gemm_tn_splitk_concat(int32_t M, int32_t N, int32_t K, const float *A, const float *A2, const float *B,
-                                 float *C, float *partials, bool accumulate, const int32_t *k_dev,
-                                 hipStream_t s);
+
+// C[M,N] = (C +) [A | A2]^T B with B [K,N] and A [K, M], or A, A2 [K, a_split] and [K, M - a_split] (both with row
+// stride a_split, M = 2 a_split).  The depth is split over the chip and summed in a fixed order; partials: scratch of
+// gemm_tn_partials(M, N, K) floats.  k_dev (nullable): depth on the device, *k_dev <= K.  lr > 0: also
+// W -= lr * C, the plain update of Algorithm 1.
+struct TnGemm {
+  int32_t M, N, K;
+  const float *A, *A2, *B;
+  int32_t a_split;
+  float *C, *partials;
+  bool accumulate;
+  const int32_t *k_dev;
+  float *W;
+  float lr;
+};
+size_t gemm_tn_partials(int32_t M, int32_t N, int32_t K);
+hipError_t gemm_tn(const TnGemm &g, hipStream_t s);
 
 // ---- loss.hip (Algorithm 1, loss step) ---------------------------------------------------------
 constexpr int kLossBlocks = 8192;  // partials: scratch f32[kLossBlocks]
@@ -217,7 +240,5 @@ hipError_t adam_update(int64_t n, float *W, const float *dW, float *m, float *v,
 // *counter = value / *counter += 1 (one thread; the device-side epoch index of graph replay)
 hipError_t set_counter(uint32_t *counter, uint32_t value, hipStream_t s);
 hipError_t bump_counter(uint32_t *counter, hipStream_t s);
-// W -= lr * dW  (Algorithm 1, update step)
-hipError_t sgd_update(int64_t n, float *W, const float *dW, float lr, hipStream_t s);
 
 }  // namespace bns

@@ -1,5 +1,5 @@
 // Loss summed over the inner nodes (Algorithm 1, loss step) with its gradient, the ReLU mask of
-// the backward pass and the SGD update (Algorithm 1, update step).  The loss is reduced in a
+// the backward pass and the Adam update.  The loss is reduced in a
 // fixed order (per wavefront, per block, then one block over the block partials): two runs give
 // the same bits.
 #include <cmath>
@@ -198,12 +198,6 @@ hipError_t relu_mask(int64_t n, const float *dH, const float *H, float scale, fl
   return hipGetLastError();
 }
 
-__global__ void __launch_bounds__(kT)
-sgd_kernel(int64_t n, float *__restrict__ W, const float *__restrict__ dW, float lr) {
-  const int64_t i = (int64_t)blockIdx.x * kT + threadIdx.x;
-  if (i < n) W[i] -= lr * dW[i];
-}
-
 // Adam (Kingma & Ba, 2015): m <- b1 m + (1-b1) g, v <- b2 v + (1-b2) g^2,
 // w <- w - lr * (m / (1 - b1^t)) / (sqrt(v / (1 - b2^t)) + eps)
 __global__ void __launch_bounds__(kT)
@@ -237,12 +231,6 @@ hipError_t set_counter(uint32_t *counter, uint32_t value, hipStream_t s) {
 }
 hipError_t bump_counter(uint32_t *counter, hipStream_t s) {
   counter_kernel<<<1, 1, 0, s>>>(counter, 0u, true);
-  return hipGetLastError();
-}
-
-hipError_t sgd_update(int64_t n, float *W, const float *dW, float lr, hipStream_t s) {
-  if (n <= 0) return hipSuccess;
-  sgd_kernel<<<(unsigned)((n + kT - 1) / kT), kT, 0, s>>>(n, W, dW, lr);
   return hipGetLastError();
 }
 

@@ -1,0 +1,96 @@
+// fp32 products on the bf16 matrix instruction.
+//
+// An fp32 value is the exact sum of three bf16 values: hi = bf16(x), mid = bf16(x - hi) and
+// lo = x - hi - mid (both differences are exact, and 3 x 8 significand bits hold the 24 of x).  A
+// product of two such sums needs six of its nine partial products: the three left out (mid lo,
+// lo mid, lo lo) are below 2^-26 of the product, a quarter of the rounding that an fp32 sum makes
+// at every step.  Each partial product is exact in fp32, and sums are fp32 as in v_mfma_f32_32x32x2_f32.
+// v_mfma_f32_16x16x32_bf16 runs at sixteen times the rate of the fp32 instruction, so six of them
+// take 6/16 of its time.  (|x| above 3.389e38 rounds to an infinite hi: such an element gives NaN
+// instead of an overflowing product.)
+#pragma once
+#include <hip/hip_runtime.h>
+
+#include "device_utils.hpp"
+
+namespace bns {
+
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));  // global memory takes any 4-byte alignment
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+
+constexpr int kFragBytes = 1024;             // one operand fragment: 64 lanes x 8 bf16 (16 rows x 32 k)
+constexpr int kFragSet = 3 * kFragBytes;     // its three pieces
+
+// The pieces of two values, packed in pairs (first value in the low half).
+__device__ __forceinline__ void split_pair(float x, float y, unsigned &hi, unsigned &mid, unsigned &lo) {
+  hi = __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2){x, y}, bf16x2));
+  const float rx = x - __builtin_bit_cast(float, hi << 16), ry = y - __builtin_bit_cast(float, hi & 0xffff0000u);
+  mid = __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2){rx, ry}, bf16x2));
+  const float sx = rx - __builtin_bit_cast(float, mid << 16), sy = ry - __builtin_bit_cast(float, mid & 0xffff0000u);
+  lo = __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2){sx, sy}, bf16x2));
+}
+
+struct Frag3 { bf16x8 p[3]; };  // hi, mid, lo of 8 values
+
+// NEG: the pieces of the negated values.
+template <bool NEG = false>
+__device__ __forceinline__ Frag3 split8(const f32x4 &a_in, const f32x4 &b_in) {
+  const f32x4 a = NEG ? -a_in : a_in, b = NEG ? -b_in : b_in;
+  u32x4 h, m, l;
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    unsigned x, y, z;
+    split_pair(a[2 * i], a[2 * i + 1], x, y, z);
+    h[i] = x; m[i] = y; l[i] = z;
+    split_pair(b[2 * i], b[2 * i + 1], x, y, z);
+    h[2 + i] = x; m[2 + i] = y; l[2 + i] = z;
+  }
+  Frag3 f;
+  f.p[0] = __builtin_bit_cast(bf16x8, h);
+  f.p[1] = __builtin_bit_cast(bf16x8, m);
+  f.p[2] = __builtin_bit_cast(bf16x8, l);
+  return f;
+}
+
+// acc[r] += x . y[r] for R second operands.  The six partial products of a step are summed from zero,
+// smallest first, and one fp32 addition takes them to the accumulator: the instruction cuts off what an
+// addend has below the accumulator's last bit (downwards: a bias), which is harmless at the size of
+// one step's sum and would not be at the size of a long running one.  sign = -1 takes a step whose first
+// (or second) operand is negated: alternating it makes what is left of that bias cancel.  Two second operands at a time: their chains alternate, and few registers are held.
+template <int R>
+__device__ __forceinline__ void mfma_split(f32x4 (&acc)[R], const Frag3 &x, const Frag3 (&y)[R], float sign = 1.f) {
+  constexpr int px[6] = {0, 2, 1, 0, 1, 0}, py[6] = {2, 0, 1, 1, 0, 0};
+  constexpr int P = R > 1 ? 2 : 1;
+#pragma unroll
+  for (int r0 = 0; r0 < R; r0 += P) {
+    f32x4 t[P];
+#pragma unroll
+    for (int r = 0; r < P; ++r) t[r] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < 6; ++i)
+#pragma unroll
+      for (int r = 0; r < P; ++r)
+        t[r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x.p[px[i]], y[r0 + r].p[py[i]], t[r], 0, 0, 0);
+#pragma unroll
+    for (int r = 0; r < P; ++r)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[r0 + r][e] = fmaf(t[r][e], sign, acc[r0 + r][e]);
+  }
+}
+
+// One 16-byte-per-lane copy from global memory straight into LDS (lane i lands at lds + 16 i; both
+// arguments as the whole wavefront sees them).  Written as assembly so that the compiler does not
+// wait for it before unrelated LDS reads: the caller waits with lds_dma_wait() and a barrier.
+__device__ __forceinline__ void lds_dma16(const void *src_lane, unsigned lds_offset) {
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src_lane), "s"(lds_offset) : "memory");
+}
+__device__ __forceinline__ void lds_dma_wait() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+__device__ __forceinline__ unsigned lds_offset_of(const void *p) {  // LDS pointers: the low half of the generic address
+  return __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)p);
+}
+
+}  // namespace bns

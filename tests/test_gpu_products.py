@@ -1,0 +1,60 @@
+"""The dense products of a layer (H W, dZ W^T, A^T dZ) at the edges of their tiles, against fp64.
+
+The graph has a self-loop per node and nothing else, so the GCN layer's aggregate is its input bit for bit
+and the mean aggregator's is zero: what comes out of the layer calls is the product alone."""
+import types
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [(1, 1, 1), (63, 17, 15), (64, 32, 16), (65, 33, 129), (130, 602, 41), (1000, 127, 130), (517, 66, 9),
+          (4099, 128, 172), (40000, 100, 47), (70001, 128, 128)]
+
+
+def _loops(n):
+    ptr, col = np.arange(n + 1, dtype=np.int32), np.arange(n, dtype=np.int32)
+    none = np.zeros(0, np.int32)
+    return types.SimpleNamespace(part_id=0, n_in=n, n_halo=0, nnz0=n, e_in=n, e_bd=0, row_ptr0=ptr, col0=col, t_in_ptr=ptr.copy(),
+                                 t_in_col=col.copy(), halo_ptr=np.zeros(1, np.int32), halo_col=none, halo_gid=np.zeros(0, np.int64),
+                                 deg_in=np.ones(n, np.int32), deg_halo=none)
+
+
+@pytest.mark.parametrize("kind", [0, 1], ids=["gcn", "sage"])
+@pytest.mark.parametrize("n,d_in,d_out", SHAPES, ids=[f"{a}x{b}x{c}" for a, b, c in SHAPES])
+def test_products(n, d_in, d_out, kind):
+    import torch
+    import paper_2203_10983_amd as pkg
+    dev = torch.device("cuda:0")
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(n + 7 * d_in + 13 * d_out)
+    f32 = lambda *s: torch.randn(*s, device=dev, generator=gen)  # noqa: E731
+    i32 = lambda k: torch.zeros(k, dtype=torch.int32, device=dev)  # noqa: E731
+    ctx = pkg.Context(_loops(n), [d_in, d_out], 0, device=dev, layer_kind=kind)
+    kept, remap, n_kept, nnz = i32(1), i32(1), i32(1), i32(1)
+    ctx.sample_boundary(1, 0, 0.5, kept, remap, n_kept)
+    csr = i32(n + 1), i32(n), i32(n + 1), i32(n)    # must outlive the layer calls
+    ctx.build_sampled_csr(remap, kept, n_kept, *csr, nnz)
+    # a factor of 2^-20 .. 2^20 per element: no piece of a split value may get lost
+    X = f32(n, d_in) * torch.exp2(torch.randint(-20, 21, (n, d_in), device=dev, generator=gen).float())
+    W, dH = f32((1 + kind) * d_in, d_out), f32(n, d_out)
+    A, H = torch.full((n, d_in), 7.0, device=dev), torch.full((n, d_out), 7.0, device=dev)
+    dW, dX = torch.full_like(W, 7.0), torch.full_like(X, 7.0)
+    ctx.gcn_layer_fwd(1, 0.5, X, None, W, A, H, False)
+    ctx.gcn_layer_bwd(1, 0.5, dH, None, A, X, W, dW, dX, None)
+    torch.cuda.synchronize()
+    Ad = torch.zeros_like(X) if kind else X
+    assert torch.equal(A, Ad)
+    Z = torch.cat([Ad, X], 1).double() if kind else X.double()
+    Wd = W.double()
+
+    def check(name, got, a, b):
+        ref, size = a @ b, a.abs() @ b.abs()
+        over = (got.double() - ref).abs() / (4.0 * 2.0 ** -24 * (1 + a.shape[1] ** 0.5) * size + 1e-300)
+        assert over.max() <= 1.0, f"{name}: {over.max().item():.3g} of the allowance"
+
+    check("H W", H, Z, Wd)
+    check("A^T dZ", dW, Z.t().contiguous(), dH.double())
+    check("dZ W^T", dX, dH.double(), Wd[d_in * kind:].t().contiguous())
+    ctx.close()
