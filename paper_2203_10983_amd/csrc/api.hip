@@ -118,6 +118,10 @@ bool one_kernel_layer(const bns_partition_desc &part, int layer_kind, int d_in, 
   return 2.0 * d_out <= 6.5 * avg_len;
 }
 
+// The concatenated update [z | h] [W_n ; W_s] of the mean-aggregator layer as one product: the seam must
+// not cut the 16-deep groups that a depth is zero-padded to.
+bool concat_in_one(int d_in) { return d_in % 16 == 0; }
+
 bool valid_desc(const bns_partition_desc *p, const bns_model_desc *m) {
   if (!p || !m || !m->dims) return false;
   if (p->n_in < 1 || p->n_halo < 0 || p->nnz0 < p->n_in || p->e_in < p->n_in || p->e_bd < 0) return false;
@@ -205,7 +209,7 @@ size_t carve(Carver &c, const bns_partition_desc *p, const bns_model_desc *m, La
   w.Wb.assign(L + 1, nullptr);
   for (size_t l = 1; l <= L; ++l) {
     const int32_t kw = m->layer_kind == 1 ? 2 : 1;
-    w.Wf[l] = c.take<char>(packed_bytes(kw * m->dims[l - 1], m->dims[l]));
+    w.Wf[l] = c.take<char>(std::max(packed_bytes_f32(kw * m->dims[l - 1], m->dims[l]), kw * packed_bytes_f32(m->dims[l - 1], m->dims[l])));
     w.Wb[l] = c.take<char>(kw * packed_bytes(m->dims[l], m->dims[l - 1]));
     w.A[l] = c.take<float>(n_in * (size_t)m->dims[l - 1]);
     w.H[l] = c.take<float>(n_in * (size_t)m->dims[l]);
@@ -302,15 +306,21 @@ bns_status layer_fwd_impl(bns_ctx *ctx, int layer, double p, const float *H_in, 
     }
     {
       PhaseTimer t(ctx, BNS_PHASE_GEMM_FWD, s);
-      RowsGemm g = rows_gemm(n_in, d_out, d_in, H_in, ctx->ws.Wf[layer], A_saved);
+      RowsF32 g{};
+      g.M = n_in;
+      g.N = d_out;
+      g.K = g.lda = d_in;
+      g.A = H_in;
+      g.Bp = ctx->ws.Wf[layer];
+      g.C = A_saved;
       g.ldc = ld;
       g.pad = ld != d_out;
-      BNS_TRY("gemm_rows(inner)", gemm_rows(g, s));
+      BNS_TRY("gemm_rows_f32(inner)", gemm_rows_f32(g, s));
       g.M = B;
       g.A = ctx->ws.Hu;
       g.C = ctx->ws.Hu2;
       g.m_dev = ctx->cur_n_kept;
-      if (B > 0) BNS_TRY("gemm_rows(boundary)", gemm_rows(g, s));
+      if (B > 0) BNS_TRY("gemm_rows_f32(boundary)", gemm_rows_f32(g, s));
     }
     PhaseTimer t(ctx, BNS_PHASE_SPMM_FWD, s);
     BNS_TRY("spmm_fwd", spmm_fwd(ctx->ws.plan_f, n_in, ld, ctx->cur_row_ptr, ctx->cur_col_idx, ctx->ws.dis_in,
@@ -359,15 +369,26 @@ bns_status layer_fwd_impl(bns_ctx *ctx, int layer, double p, const float *H_in, 
   }
   {
     PhaseTimer t(ctx, BNS_PHASE_GEMM_FWD, s);
-    RowsGemm g = rows_gemm(n_in, d_out, sage ? 2 * d_in : d_in, A_saved, ctx->ws.Wf[layer], H_out);
-    g.lda = d_in;
-    if (sage) {  // [z | h] [W_n ; W_s] in one product
+    RowsF32 g{};
+    g.M = n_in;
+    g.N = g.ldc = d_out;
+    g.K = g.lda = d_in;
+    g.A = A_saved;
+    g.Bp = ctx->ws.Wf[layer];
+    g.C = H_out;
+    if (sage && concat_in_one(d_in)) {  // [z | h] [W_n ; W_s] in one product
       g.A2 = H_in;
       g.a_split = d_in;
+      g.K = 2 * d_in;
+    } else if (sage) {  // z W_n + h W_s
+      BNS_TRY("gemm_rows_f32(nbr)", gemm_rows_f32(g, s));
+      g.A = H_in;
+      g.Bp = ctx->ws.Wf[layer] + packed_bytes_f32(d_in, d_out);
+      g.accumulate = true;
     }
     g.relu = relu;
     g.drop = dropout_of(ctx, layer, relu);
-    BNS_TRY("gemm_rows(update)", gemm_rows(g, s));
+    BNS_TRY("gemm_rows_f32(update)", gemm_rows_f32(g, s));
   }
   return BNS_OK;
 }
@@ -385,7 +406,13 @@ bns_status layer_bwd_impl(bns_ctx *ctx, int layer, double p, const float *dZ, co
   const char *Wb = ctx->ws.Wb[layer];
   // C = alpha * G W^T for rows of G at the output width; C2: the mean aggregator's second half
   auto gemm_wt = [&](int32_t M, const float *G, float *C, float *C2, const float *mask, float alpha, const int32_t *m_dev) {
-    RowsGemm g = rows_gemm(M, C2 ? 2 * d_in : d_in, d_out, G, Wb, C);
+    RowsGemm g{};
+    g.M = M;
+    g.N = C2 ? 2 * d_in : d_in;
+    g.K = d_out;
+    g.A = G;
+    g.Bp = Wb;
+    g.C = C;
     g.alpha = alpha;
     if (C2 && d_in % 4 != 0) {  // no 16-byte store may straddle the two results: one product each
       g.N = g.ldc = d_in;
@@ -524,14 +551,21 @@ bns_status pack_layers(bns_ctx *ctx, const float *const *W, int first, int last,
   const int32_t kw = ctx->layer_kind == 1 ? 2 : 1;
   for (int l = first; l <= last; ++l) {
     const int32_t d_in = kw * ctx->dims[l - 1], d_out = ctx->dims[l];
-    if (fwd) jobs[n++] = PackJob{W[l - first], ctx->ws.Wf[l], d_in, d_out, false};
+    // a layer in one kernel reads its weights as they are
+    if (fwd && (!one_kernel_layer(ctx->part, ctx->layer_kind, ctx->dims[l - 1], d_out) ||
+                update_first_shape(ctx->layer_kind, ctx->dims[l - 1], d_out))) {
+      const int32_t part = kw == 2 && !concat_in_one(ctx->dims[l - 1]) ? 2 : 1;  // the two halves apart
+      for (int32_t h = 0; h < part; ++h)
+        jobs[n++] = PackJob{W[l - first] + (size_t)h * ctx->dims[l - 1] * d_out,
+                            ctx->ws.Wf[l] + h * packed_bytes_f32(ctx->dims[l - 1], d_out), d_in / part, d_out, false};
+    }
     if (bwd && (l > 1 || !fwd)) {
       const int32_t part = kw == 2 && ctx->dims[l - 1] % 4 != 0 ? 2 : 1;  // the two halves apart (see gemm_wt)
       for (int32_t h = 0; h < part; ++h)
         jobs[n++] = PackJob{W[l - first] + (size_t)h * ctx->dims[l - 1] * d_out,
                             ctx->ws.Wb[l] + h * packed_bytes(d_out, ctx->dims[l - 1]), d_out, d_in / part, true};
     }
-    if (n + 3 > kMaxPackJobs || l == last) {
+    if (n + 4 > kMaxPackJobs || l == last) {
       BNS_TRY("pack_weights", pack_weights(jobs, n, s));
       n = 0;
     }

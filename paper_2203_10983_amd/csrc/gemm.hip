@@ -1,8 +1,8 @@
-// Dense update (Eq. 2) and its backward on the matrix cores: fp32 operands and results, products by
+// The backward products of the update (Eq. 2) on the matrix cores: fp32 operands and results, products by
 // three-way bf16 splitting (split_bf16.hpp).
 //
-//   gemm_rows   C = [A | A2] B   forward product H = A W and dA = dZ W^T: a tall A [M, K] times a weight
-//               matrix, which pack_weights has split and laid out as operand fragments
+//   gemm_rows   C = A B   dA = dZ W^T: a tall A [M, K] times a weight matrix, which pack_weights has
+//               split and laid out as operand fragments
 //   gemm_tn     C = [A | A2]^T B  weight gradient dW = A^T dZ, the depth (rows) split over the chip
 //
 // gemm_rows: a workgroup of 4 wavefronts walks row tiles; a wavefront owns 16 R rows and NC column
@@ -29,13 +29,21 @@
 namespace bns {
 
 // ---- packed weights -----------------------------------------------------------------------------
-// Operand fragments of B [K, N] (or, transposed, of W [N, K]): for depth step s of 32 and column tile t of 16,
-// at ((s * tiles + t) * 3 + piece) KB, lane l's 8 values are column 16 t + l % 16 at the depths
-// 32 s + 16 (e / 4) + 4 (l / 16) + e % 4, e = 0..7, negated in even steps (mfma_split); zero outside the matrix.
+// Operand fragments, 1 KB each (64 lanes x 16 bytes), zero outside the matrix.
+//   split: of W [N, K] transposed, for gemm_rows.  For depth step s of 32 and column tile t of 16, at
+//     ((s * tiles + t) * 3 + piece) KB, lane l's 8 values are column 16 t + l % 16 at the depths
+//     32 s + 16 (e / 4) + 4 (l / 16) + e % 4, e = 0..7, negated in even steps (mfma_split)
+//   fp32: of W [K, N], for gemm_rows_f32.  For depth step s of 32, column tile t of 32 and depth group j of 8, at
+//     ((s * tiles + t) * 4 + j) KB, lane l's 4 values are column 32 t + l % 32 at the depths
+//     32 s + 8 j + 2 i + l / 32, i = 0..3
 __host__ __device__ static inline int k_steps(int K) { return (K + 31) / 32; }
 __host__ __device__ static inline int col_tiles(int N) { return (N + 15) / 16; }
+__host__ __device__ static inline int pack_units(const PackJob &j) {  // a wavefront's work: one fragment set
+  return k_steps(j.K) * (j.split ? col_tiles(j.N) : (j.N + 31) / 32);
+}
 
 size_t packed_bytes(int32_t K, int32_t N) { return (size_t)k_steps(K) * col_tiles(N) * kFragSet; }
+size_t packed_bytes_f32(int32_t K, int32_t N) { return (size_t)k_steps(K) * ((N + 31) / 32) * 4096; }
 
 struct PackJobs {
   PackJob j[kMaxPackJobs];
@@ -43,31 +51,46 @@ struct PackJobs {
 };
 
 __global__ void __launch_bounds__(256) pack_weights_kernel(const PackJobs jobs) {
-  int u = blockIdx.x * 4 + (threadIdx.x >> 6);  // one wavefront per fragment set
-  int q = 0, units = 0;
+  int u = blockIdx.x * 4 + (threadIdx.x >> 6);
+  int q = 0;
   for (; q < jobs.n; ++q) {
-    units = k_steps(jobs.j[q].K) * col_tiles(jobs.j[q].N);
+    const int units = pack_units(jobs.j[q]);
     if (u < units) break;
     u -= units;
   }
   if (q == jobs.n) return;
   const PackJob &job = jobs.j[q];
-  const int T = col_tiles(job.N);
-  const int s = u / T, t = u % T, lane = lane_id();
-  const int n = t * 16 + (lane & 15), g = lane >> 4;
-  f32x4 v[2];
+  const int lane = lane_id();
+  if (job.split) {
+    const int T = col_tiles(job.N), s = u / T, t = u % T;
+    const int n = t * 16 + (lane & 15), g = lane >> 4;
+    f32x4 v[2];
 #pragma unroll
-  for (int j = 0; j < 2; ++j)
+    for (int j = 0; j < 2; ++j)
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int k = s * 32 + j * 16 + g * 4 + e;
-      const bool ok = k < job.K && n < job.N;
-      v[j][e] = ok ? job.W[job.transposed ? (size_t)n * job.K + k : (size_t)k * job.N + n] : 0.f;
+      for (int e = 0; e < 4; ++e) {
+        const int k = s * 32 + j * 16 + g * 4 + e;
+        v[j][e] = k < job.K && n < job.N ? job.W[(size_t)n * job.K + k] : 0.f;
+      }
+    const Frag3 f = s % 2 == 0 ? split8<true>(v[0], v[1]) : split8(v[0], v[1]);
+    char *out = static_cast<char *>(job.out) + (size_t)u * kFragSet + lane * 16;
+#pragma unroll
+    for (int p = 0; p < 3; ++p) *reinterpret_cast<bf16x8 *>(out + p * kFragBytes) = f.p[p];
+  } else {
+    const int T = (job.N + 31) / 32, s = u / T, t = u % T;
+    const int n = t * 32 + (lane & 31);
+    char *out = static_cast<char *>(job.out) + (size_t)u * 4096 + lane * 16;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      f32x4 v;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int k = s * 32 + j * 8 + i * 2 + (lane >> 5);
+        v[i] = k < job.K && n < job.N ? job.W[(size_t)k * job.N + n] : 0.f;
+      }
+      *reinterpret_cast<f32x4 *>(out + j * 1024) = v;
     }
-  const Frag3 f = s % 2 == 0 ? split8<true>(v[0], v[1]) : split8(v[0], v[1]);
-  char *out = static_cast<char *>(job.out) + (size_t)u * kFragSet + lane * 16;
-#pragma unroll
-  for (int p = 0; p < 3; ++p) *reinterpret_cast<bf16x8 *>(out + p * kFragBytes) = f.p[p];
+  }
 }
 
 hipError_t pack_weights(const PackJob *jobs, int32_t n, hipStream_t s) {
@@ -77,7 +100,7 @@ hipError_t pack_weights(const PackJob *jobs, int32_t n, hipStream_t s) {
     int64_t units = 0;
     for (int i = 0; i < pj.n; ++i) {
       pj.j[i] = jobs[i0 + i];
-      units += (int64_t)k_steps(pj.j[i].K) * col_tiles(pj.j[i].N);
+      units += pack_units(pj.j[i]);
     }
     if (units) pack_weights_kernel<<<(unsigned)((units + 3) / 4), 256, 0, s>>>(pj);
   }
@@ -90,7 +113,7 @@ struct RowsArgs {
   int T, S, nblk;  // column tiles, depth steps, column blocks
 };
 
-enum RowsEpilogue { kPlain = 0, kRelu = 1, kMask = 2, kPair = 3 };
+enum RowsEpilogue { kPlain = 0, kMask = 1, kPair = 2 };
 
 template <int R, int NC, int EPI>
 __global__ void __launch_bounds__(256, R * NC > 8 ? 3 : 4) gemm_rows_kernel(const RowsArgs a) {
@@ -110,33 +133,28 @@ __global__ void __launch_bounds__(256, R * NC > 8 ? 3 : 4) gemm_rows_kernel(cons
   const int lane = lane_id(), wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int l16 = lane & 15, g = lane >> 4;
   const int S = a.S;
-  const bool two = p.A2 != nullptr;
-  const bool vec = !two || p.a_split % 4 == 0;  // a 16-byte piece never straddles the two operands
 
   f32x4 ar[R][2];
-  const float *row_a[R], *row_a2[R];
+  const float *row_a[R];
   auto set_rows = [&](int tl) {
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       const int row = min(M - 1, tl * kRows + wid * 16 * R + r * 16 + l16);  // rows past the end are not stored
-      row_a[r] = p.A + (size_t)row * p.lda;
-      row_a2[r] = two ? p.A2 + (size_t)row * p.lda - p.a_split : nullptr;
+      row_a[r] = p.A + (size_t)row * p.K;
     }
   };
   auto load_a = [&](int s) {
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
       const int k = s * 32 + j * 16 + g * 4;
-      if (vec && (s + 1) * 32 <= p.K) {
+      if ((s + 1) * 32 <= p.K) {
 #pragma unroll
-        for (int r = 0; r < R; ++r)
-          ar[r][j] = *reinterpret_cast<const f32x4u *>((two && k >= p.a_split ? row_a2[r] : row_a[r]) + k);
+        for (int r = 0; r < R; ++r) ar[r][j] = *reinterpret_cast<const f32x4u *>(row_a[r] + k);
       } else {
 #pragma unroll
         for (int r = 0; r < R; ++r)
 #pragma unroll
-          for (int e = 0; e < 4; ++e)
-            ar[r][j][e] = k + e < p.K ? (two && k + e >= p.a_split ? row_a2[r] : row_a[r])[k + e] : 0.f;
+          for (int e = 0; e < 4; ++e) ar[r][j][e] = k + e < p.K ? row_a[r][k + e] : 0.f;
       }
     }
   };
@@ -183,9 +201,8 @@ __global__ void __launch_bounds__(256, R * NC > 8 ? 3 : 4) gemm_rows_kernel(cons
     }
     buf ^= 1;
     if (last) {
-      // lane: row l16 of the row tile, columns 16 c + 4 g .. + 3.  A result with padded rows: the columns
-      // N..ldc-1 hold the zeros of the packed weights
-      const int n_end = EPI == kPlain && p.pad ? p.ldc : p.N, col0 = t0 * 16 + g * 4;
+      // lane: row l16 of the row tile, columns 16 c + 4 g .. + 3
+      const int n_end = p.N, col0 = t0 * 16 + g * 4;
 #pragma unroll
       for (int r = 0; r < R; ++r) {
         const int row = tile * kRows + wid * 16 * R + r * 16 + l16;
@@ -207,16 +224,6 @@ __global__ void __launch_bounds__(256, R * NC > 8 ? 3 : 4) gemm_rows_kernel(cons
                 if (e < left) m[e] = ms[c * 16 + e];
 #pragma unroll
             for (int e = 0; e < 4; ++e) v[e] = m[e] > 0.f ? v[e] * p.alpha : 0.f;
-          } else if constexpr (EPI == kRelu) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = fmaxf(v[e], 0.f);
-            if (p.drop.scale != 0.f) {
-#pragma unroll 1
-              for (int e = 0; e < 4; ++e) {
-                const float y = dropout_keeps(p.drop, row, col0 + c * 16 + e) ? v[0] * p.drop.scale : 0.f;
-                v = f32x4{v[1], v[2], v[3], y};
-              }
-            }
           } else {
 #pragma unroll
             for (int e = 0; e < 4; ++e) v[e] *= p.alpha;
@@ -254,15 +261,13 @@ template <int R>
 static void launch_rows(const RowsArgs &a, int nc, unsigned grid, hipStream_t s) {
   if (a.g.C2) launch_rows<R, kPair>(a, nc, grid, s);
   else if (a.g.mask) launch_rows<R, kMask>(a, nc, grid, s);
-  else if (a.g.relu) launch_rows<R, kRelu>(a, nc, grid, s);
   else launch_rows<R, kPlain>(a, nc, grid, s);
 }
 
 hipError_t gemm_rows(const RowsGemm &g, hipStream_t s) {
   if (g.M <= 0 || g.N <= 0) return hipSuccess;
   if (g.C2 ? g.c_split % 4 != 0 || g.ldc < g.c_split || g.N > 2 * g.c_split : g.ldc < g.N) return hipErrorInvalidValue;
-  if (g.pad && g.ldc > (g.N + 3) / 4 * 4) return hipErrorInvalidValue;
-  if ((g.C2 != nullptr) + (g.mask != nullptr) + g.relu + g.pad > 1) return hipErrorInvalidValue;
+  if (g.C2 && g.mask) return hipErrorInvalidValue;
   RowsArgs a;
   a.g = g;
   a.T = col_tiles(g.N);

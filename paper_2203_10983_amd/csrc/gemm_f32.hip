@@ -1,0 +1,202 @@
+// The forward product H = [A | A2] W (Eq. 2) on the fp32 matrix instruction, v_mfma_f32_32x32x2_f32.
+//
+// The forward chain decides which hidden units a ReLU switches on, and a unit within rounding of
+// zero is switched by another order of summation.  So every forward product, whatever its kernel, adds
+// the same terms in the same order: a chain over depth pairs (0,1), (2,3), ... from zero.  The backward
+// products have no such decision behind them and run faster on split bf16 operands (gemm.hip).
+//
+// A workgroup of 4 wavefronts walks row tiles of 128; a wavefront owns 32 rows and NC column tiles of
+// 32.  Its rows come straight from global memory: a lane reads four consecutive depths of its row, and
+// a swap of wavefront halves per pair of registers turns the eight depths of the two halves into the
+// operands of four instructions in depth order.  The weights, packed once per step as operand fragments,
+// are copied from L2 into a double-buffered LDS tile, one 32-deep step ahead, across row tiles as well:
+// one 16-byte LDS read feeds four instructions, and the matrix pipe is what is left to wait for.
+#include <algorithm>
+
+#include "kernels.hpp"
+#include "split_bf16.hpp"
+
+namespace bns {
+
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+
+constexpr int kF32Step = 4096;  // bytes of the packed weights of one 32-deep step and one column tile of 32
+
+struct F32Args {
+  RowsF32 g;
+  int T, S, nblk;  // column tiles of 32, depth steps of 32, column blocks
+};
+
+template <int NC, bool ACC>
+__global__ void __launch_bounds__(256, 4) gemm_rows_f32_kernel(const F32Args a) {
+  constexpr int kRows = 128;
+  __shared__ __attribute__((aligned(16))) char Bs[2][NC * kF32Step];
+  const RowsF32 &p = a.g;
+  const int M = p.m_dev ? min(p.M, *p.m_dev) : p.M;
+  // workgroup b runs on XCD b % 8: the column blocks of one row tile follow each other on one XCD
+  const int x = blockIdx.x & 7, q = blockIdx.x >> 3;
+  const int nb = q % a.nblk, stride = (gridDim.x / (8 * a.nblk)) * 8;
+  const int t0 = nb * NC;
+  int tile = (q / a.nblk) * 8 + x;
+  const int n_tiles = (M + kRows - 1) / kRows;
+  if (tile >= n_tiles) return;
+
+  const int lane = lane_id(), wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int l32 = lane & 31, hi = lane >> 5;
+  const int S = a.S;
+  const bool two = p.A2 != nullptr;  // then a_split % 16 == 0
+
+  f32x4 ar[4];
+  const float *row_a, *row_a2;
+  auto set_rows = [&](int tl) {
+    const int row = min(M - 1, tl * kRows + wid * 32 + l32);  // rows past the end are not stored
+    row_a = p.A + (size_t)row * p.lda;
+    row_a2 = two ? p.A2 + (size_t)row * p.lda - p.a_split : nullptr;
+  };
+  auto load_a = [&](int s) {
+    const float *src[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int k = s * 32 + j * 8 + hi * 4;
+      src[j] = (two && k >= p.a_split ? row_a2 : row_a) + k;
+    }
+    if ((s + 1) * 32 <= p.K) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) ar[j] = *reinterpret_cast<const f32x4u *>(src[j]);
+    } else {
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) ar[j][e] = s * 32 + j * 8 + hi * 4 + e < p.K ? src[j][e] : 0.f;
+    }
+  };
+  const unsigned lds0 = lds_offset_of(&Bs[0][0]);
+  const int nt = min(NC, a.T - t0);
+  auto load_b = [&](int s, int buf) {  // pieces of 1 KB, dealt to the four wavefronts
+    const char *src = static_cast<const char *>(p.Bp) + (size_t)(s * a.T + t0) * kF32Step + lane * 16;
+    for (int c = wid; c < nt * 4; c += 4) lds_dma16(src + c * 1024, lds0 + buf * (NC * kF32Step) + c * 1024);
+  };
+
+  f32x16 acc[NC];
+  auto clear = [&]() {
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[c][i] = 0.f;
+  };
+  set_rows(tile);
+  load_b(0, 0);
+  load_a(0);
+  clear();
+  int buf = 0;
+  for (int s = 0;;) {
+    lds_dma_wait();
+    __syncthreads();  // this step's weights are in LDS, and everybody is done with the other buffer
+    // depths 8 j + 4 hi + 0..3 -> pairs (8 j + 2 i, 8 j + 2 i + 1) in the two halves
+    float op[4][4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const u32x2 w = __builtin_amdgcn_permlane32_swap(__float_as_uint(ar[j][2 * h]), __float_as_uint(ar[j][2 * h + 1]),
+                                                         false, false);
+        op[j][h] = __uint_as_float(w[0]);
+        op[j][2 + h] = __uint_as_float(w[1]);
+      }
+    const bool last = s + 1 == S;
+    const int ntile = last ? tile + stride : tile, ns = last ? 0 : s + 1;
+    if (ntile < n_tiles) {
+      if (last) set_rows(ntile);
+      load_b(ns, buf ^ 1);
+      load_a(ns);
+    }
+    const char *bs = &Bs[buf][0] + lane * 16;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      f32x4 b[NC];
+#pragma unroll
+      for (int c = 0; c < NC; ++c) b[c] = *reinterpret_cast<const f32x4 *>(bs + c * kF32Step + j * 1024);
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int c = 0; c < NC; ++c) acc[c] = __builtin_amdgcn_mfma_f32_32x32x2f32(b[c][i], op[j][i], acc[c], 0, 0, 0);
+    }
+    buf ^= 1;
+    if (last) {
+      // lane: row l32 of the wavefront's 32; register 4 q + e of tile c: column 32 c + 8 q + 4 hi + e
+      const int row = tile * kRows + wid * 32 + l32;
+      if (row < M) {
+        const int n_end = p.pad ? p.ldc : p.N, col0 = t0 * 32 + hi * 4;  // pad: the packed weights are zero there
+        float *const dst = p.C + (size_t)row * p.ldc + col0;
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+          for (int q4 = 0; q4 < 4; ++q4) {
+            const int at = c * 32 + q4 * 8, left = n_end - (col0 + at);
+            if (left <= 0) continue;
+            float *const d = dst + at;
+            f32x4 v = {acc[c][4 * q4], acc[c][4 * q4 + 1], acc[c][4 * q4 + 2], acc[c][4 * q4 + 3]};
+            if constexpr (ACC) {
+#pragma unroll
+              for (int e = 0; e < 4; ++e)
+                if (e < left) v[e] += d[e];
+            }
+            if (p.relu) {
+#pragma unroll
+              for (int e = 0; e < 4; ++e) v[e] = fmaxf(v[e], 0.f);
+              if (p.drop.scale != 0.f) {
+#pragma unroll 1
+                for (int e = 0; e < 4; ++e) {
+                  const float y = dropout_keeps(p.drop, row, col0 + at + e) ? v[0] * p.drop.scale : 0.f;
+                  v = f32x4{v[1], v[2], v[3], y};
+                }
+              }
+            }
+            if (left >= 4) *reinterpret_cast<f32x4u *>(d) = v;
+            else
+#pragma unroll
+              for (int e = 0; e < 3; ++e)
+                if (e < left) d[e] = v[e];
+          }
+      }
+      if (ntile >= n_tiles) break;
+      clear();
+      tile = ntile;
+    }
+    s = ns;
+  }
+}
+
+hipError_t gemm_rows_f32(const RowsF32 &g, hipStream_t s) {
+  if (g.M <= 0 || g.N <= 0) return hipSuccess;
+  if (g.ldc < g.N || (g.pad && (g.ldc > (g.N + 3) / 4 * 4 || g.relu || g.accumulate)) || (g.A2 && g.a_split % 16 != 0))
+    return hipErrorInvalidValue;
+  F32Args a;
+  a.g = g;
+  a.T = (g.N + 31) / 32;
+  a.S = (g.K + 31) / 32;
+  // up to 4 column tiles per wavefront, evenly dealt; fewer where that leaves the chip short of workgroups
+  const int64_t row_tiles = (g.M + 127) / 128;
+  a.nblk = (a.T + 3) / 4;
+  while (row_tiles * a.nblk < 512 && a.nblk < a.T) a.nblk = std::min(a.nblk * 2, a.T);
+  const int nc = (a.T + a.nblk - 1) / a.nblk;
+  a.nblk = (a.T + nc - 1) / nc;
+  const int64_t octets = std::min<int64_t>((row_tiles + 7) / 8, std::max<int64_t>(1, 1024 / (8 * a.nblk)));
+  const unsigned grid = (unsigned)(octets * 8 * a.nblk);
+#define BNS_ROWS_F32(NC)                                                          \
+  do {                                                                          \
+    if (g.accumulate) gemm_rows_f32_kernel<NC, true><<<grid, 256, 0, s>>>(a);   \
+    else gemm_rows_f32_kernel<NC, false><<<grid, 256, 0, s>>>(a);               \
+  } while (0)
+  switch (nc) {
+    case 1: BNS_ROWS_F32(1); break;
+    case 2: BNS_ROWS_F32(2); break;
+    case 3: BNS_ROWS_F32(3); break;
+    default: BNS_ROWS_F32(4); break;
+  }
+#undef BNS_ROWS_F32
+  return hipGetLastError();
+}
+
+}  // namespace bns

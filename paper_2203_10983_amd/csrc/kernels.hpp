@@ -166,42 +166,50 @@ struct Dropout {
   uint32_t k0 = 0, k1 = 0, c2 = 0, epoch = 0;
   const uint32_t *epoch_dev = nullptr;  // nullable: the epoch index is read from device memory
 };
-// A weight matrix laid out for the products below: split into bf16 pieces, operand fragments in the order
-// they are read.  W [K, N], or W [N, K] when transposed; out: packed_bytes(K, N), 16-byte aligned.
+// A weight matrix laid out for the products below: operand fragments in the order they are read.  split: W [N, K],
+// transposed and cut into bf16 pieces, for gemm_rows (packed_bytes(K, N)); else W [K, N] for gemm_rows_f32
+// (packed_bytes_f32(K, N)).  out is 16-byte aligned.
 struct PackJob {
   const float *W;
   void *out;
   int32_t K, N;
-  bool transposed;
+  bool split;
 };
 constexpr int kMaxPackJobs = 16;  // per launch
 size_t packed_bytes(int32_t K, int32_t N);
+size_t packed_bytes_f32(int32_t K, int32_t N);
 hipError_t pack_weights(const PackJob *jobs, int32_t n, hipStream_t s);
 
-// C[M,N] = alpha * [A | A2] B with B [K,N] packed.  A, A2 [M, lda]: the depth below a_split is A's, the rest A2's
-// (A2 nullable).  At most one of: C2 (nullable): columns from c_split (a multiple of 4) on go to C2, both with row
-// stride ldc; mask (nullable, [M, ldc]): C is zeroed where mask <= 0; relu (without alpha): max(., 0), then dropout
-// when drop.scale != 0; pad: the columns N..ldc-1 are set to zero (ldc at most N rounded up to a multiple of 4).
-// m_dev (nullable): row count on
-// the device, *m_dev <= M; rows past it are not touched.
-struct RowsGemm {
+// C[M,N] = [A | A2] B (+ the previous C if accumulate), B [K,N] packed; then, if relu, max(., 0) and dropout (when
+// drop.scale != 0).  A, A2 [M, lda]: the depth below a_split (a multiple of 16) is A's, the rest A2's (nullable).
+// pad: the columns N..ldc-1 are set to zero (ldc at most N rounded up to a multiple of 4; not with relu or
+// accumulate).  m_dev (nullable): row count on the device, *m_dev <= M; rows past it are not touched.
+struct RowsF32 {
   int32_t M, N, K;
   const float *A, *A2;
   int32_t lda, a_split;
   const void *Bp;
-  float *C, *C2;
-  int32_t ldc, c_split;
-  float alpha;
-  bool relu, pad;
-  const float *mask;
+  float *C;
+  int32_t ldc;
+  bool relu, pad, accumulate;
   const int32_t *m_dev;
   Dropout drop;
 };
-inline RowsGemm rows_gemm(int32_t M, int32_t N, int32_t K, const float *A, const void *Bp, float *C) {
-  RowsGemm g{};
-  g.M = M; g.N = N; g.K = K; g.A = A; g.lda = K; g.Bp = Bp; g.C = C; g.ldc = N; g.alpha = 1.f;
-  return g;
-}
+hipError_t gemm_rows_f32(const RowsF32 &g, hipStream_t s);
+
+// C[M,N] = alpha * A B with A [M,K], B [K,N] packed and split.  At most one of: C2 (nullable): columns from c_split (a
+// multiple of 4) on go to C2, both with row stride ldc; mask (nullable, [M, ldc]): C is zeroed where mask <= 0.
+// m_dev as above.
+struct RowsGemm {
+  int32_t M, N, K;
+  const float *A;
+  const void *Bp;
+  float *C, *C2;
+  int32_t ldc, c_split;
+  float alpha;
+  const float *mask;
+  const int32_t *m_dev;
+};
 hipError_t gemm_rows(const RowsGemm &g, hipStream_t s);
 
 // inv[i] = deg[i] > 1 ? 1 / (deg[i] - 1) : 0   (deg counts the self-loop)
