@@ -41,7 +41,7 @@ struct Layout {
   int32_t *tile_sums, *kept_start;
   uint64_t *ballots;
   int32_t *kpos;
-  float *Hu, *Hu2, *G0, *G1, *G2, *partials, *loss_partials;  // Hu2: boundary rows at the output width
+  float *Hu, *Hu2, *G0, *G1, *G2, *loss_partials;  // Hu, Hu2: boundary rows at the output width
   int2 *halo_rec;  // per kept boundary node: (boundary index, weight) for the aggregates that read the rows in place
   float *inv_deg;            // 1 / (full-graph degree) of the inner nodes, for the mean aggregator
   SegPlan plan_f, plan_b;   // segmentation of the static CSR and of the transposed inner block
@@ -53,6 +53,9 @@ struct Layout {
   int32_t *row_ptr, *col_idx, *t_row_ptr, *t_col_idx;
   std::vector<float *> A, H;  // index 1..L
   std::vector<char *> Wf, Wb;  // index 1..L: the layer's weights packed for H W and for dZ W^T
+  // index 1..L: partial sums of the layer's weight gradient (of its boundary part); transposed aggregate of an
+  // update-first layer's gradient, inner and boundary rows
+  std::vector<float *> tn, tn2, G_in, G_halo;
   std::vector<float *> dZ;    // index 1..L: gradient w.r.t. the pre-activation of layer l (bns_train_step)
 };
 
@@ -111,7 +114,11 @@ int gather_stride(int d_in, int d_out) {
 // workloads, up to about 6.5 multiply-adds of the update per gathered feature element (GCN layers of
 // workload 5: 4.4 and 6.0, faster in one kernel; mean-aggregator layers, whose update is twice as
 // deep: workload 3 at 5.1 faster, workload 5 at 8.9 and 11.9 slower).
+// Its workgroups own 64 rows: below kOneKernelMinRows they are too few for the chip (9 570 rows of 128 floats: 64 us with
+// the pass over the long rows, 37 in two kernels).
+constexpr int kOneKernelMinRows = 32768;
 bool one_kernel_layer(const bns_partition_desc &part, int layer_kind, int d_in, int d_out) {
+  if (part.n_in < kOneKernelMinRows) return false;
   if (layer_kind == 0) return spmm_gemm_fwd_supported(d_in);  // every GCN shape measured so far gains
   if (!spmm_gemm_fwd_concat_supported(d_in, d_out)) return false;
   const double avg_len = (double)part.nnz0 / (double)part.n_in;
@@ -146,17 +153,12 @@ bool fits_int32(const bns_partition_desc *p, const bns_model_desc *m) {
 
 size_t carve(Carver &c, const bns_partition_desc *p, const bns_model_desc *m, Layout *out) {
   const size_t n_in = p->n_in, B = p->n_halo, L = m->n_layers;
-  size_t d_in_max = 0, d_max = 0, part_max = 0, d_first_max = 0;
+  size_t d_max = 0, d_out_max = 0, d_first_max = 0;
   for (size_t l = 0; l <= L; ++l) d_max = std::max<size_t>(d_max, m->dims[l]);
   for (size_t l = 0; l < L; ++l) {
-    d_in_max = std::max<size_t>(d_in_max, m->dims[l]);
-    const int kw = m->layer_kind == 1 ? 2 : 1;  // [A | H]^T dZ is one product of twice the height
-    part_max = std::max(part_max, gemm_tn_partials(kw * m->dims[l], m->dims[l + 1], p->n_in));
-    if (update_first_shape(m->layer_kind, m->dims[l], m->dims[l + 1])) {
+    d_out_max = std::max<size_t>(d_out_max, m->dims[l + 1]);
+    if (update_first_shape(m->layer_kind, m->dims[l], m->dims[l + 1]))
       d_first_max = std::max<size_t>(d_first_max, gather_stride(m->dims[l], m->dims[l + 1]));
-      if (p->n_halo > 0)
-        part_max = std::max(part_max, gemm_tn_partials(m->dims[l], m->dims[l + 1], p->n_halo));
-    }
   }
   Layout w;
   w.dis_in = c.take<float>(n_in);
@@ -172,14 +174,13 @@ size_t carve(Carver &c, const bns_partition_desc *p, const bns_model_desc *m, La
   w.kept_start = c.take<int32_t>((int64_t)B + 1);
   w.ballots = c.take<uint64_t>((B + 63) / 64 + 1);
   w.kpos = c.take<int32_t>(p->e_bd + 1);
-  w.Hu = c.take<float>(B * d_in_max);
+  w.Hu = c.take<float>(B * d_out_max);
   w.Hu2 = c.take<float>(B * d_first_max);
   w.halo_rec = c.take<int2>(B + 1);
   w.G0 = c.take<float>(n_in * d_max);
   w.G1 = c.take<float>(n_in * d_max);
   w.G2 = c.take<float>(n_in * d_max);
   w.inv_deg = c.take<float>(n_in);
-  w.partials = c.take<float>(part_max);
   w.loss_partials = c.take<float>(kLossBlocks);
   for (int k = 0; k < 2; ++k) {
     SegPlan &pl = k == 0 ? w.plan_f : w.plan_b;
@@ -207,8 +208,20 @@ size_t carve(Carver &c, const bns_partition_desc *p, const bns_model_desc *m, La
   w.dZ.assign(L + 1, nullptr);
   w.Wf.assign(L + 1, nullptr);
   w.Wb.assign(L + 1, nullptr);
+  w.tn.assign(L + 1, nullptr);
+  w.tn2.assign(L + 1, nullptr);
+  w.G_in.assign(L + 1, nullptr);
+  w.G_halo.assign(L + 1, nullptr);
   for (size_t l = 1; l <= L; ++l) {
     const int32_t kw = m->layer_kind == 1 ? 2 : 1;
+    const bool first = update_first_shape(m->layer_kind, m->dims[l - 1], m->dims[l]);
+    w.tn[l] = c.take<float>(std::max(gemm_tn_partials(kw * m->dims[l - 1], m->dims[l], p->n_in, 0),
+                                     first ? gemm_tn_partials(m->dims[l - 1], m->dims[l], p->n_in, p->n_halo) : 0));
+    if (first) {
+      w.tn2[l] = c.take<float>(gemm_tn_partials(m->dims[l - 1], m->dims[l], p->n_halo, p->n_in));
+      w.G_in[l] = c.take<float>(n_in * m->dims[l]);
+      w.G_halo[l] = c.take<float>(B * m->dims[l]);
+    }
     w.Wf[l] = c.take<char>(std::max(packed_bytes_f32(kw * m->dims[l - 1], m->dims[l]), kw * packed_bytes_f32(m->dims[l - 1], m->dims[l])));
     w.Wb[l] = c.take<char>(kw * packed_bytes(m->dims[l], m->dims[l - 1]));
     w.A[l] = c.take<float>(n_in * (size_t)m->dims[l - 1]);
@@ -290,20 +303,16 @@ int layer_plan(const bns_ctx *ctx, int layer, const float *X) {
 }
 
 // update_first: H_out = act(P [H_in W ; Hu W]) instead of act((P [H_in ; Hu]) W); A_saved then
-// receives H_in W (the aggregate of the inputs is never formed).
+// receives H_in W (the aggregate of the inputs is never formed).  prepare (nullable): the weights to pack, when
+// neither they nor the boundary records are ready.
 bns_status layer_fwd_impl(bns_ctx *ctx, int layer, double p, const float *H_in, const float *halo_h,
                           const float *W, float *A_saved, float *H_out, bool relu, bool update_first,
-                          hipStream_t s) {
+                          const PackJobs *prepare, hipStream_t s) {
   const int n_in = ctx->part.n_in, B = ctx->part.n_halo;
   const int d_in = ctx->dims[layer - 1], d_out = ctx->dims[layer];
   const bool sage = ctx->layer_kind == 1;
   if (update_first) {
     const int ld = gather_stride(d_in, d_out);  // row stride of H W and H_U W
-    {
-      PhaseTimer t(ctx, BNS_PHASE_GATHER, s);
-      BNS_TRY("halo_gather", halo_gather(halo_h, ctx->cur_kept, ctx->cur_n_kept, B, ctx->ws.dis_halo, halo_scale(p),
-                                         d_in, ctx->ws.Hu, s));
-    }
     {
       PhaseTimer t(ctx, BNS_PHASE_GEMM_FWD, s);
       RowsF32 g{};
@@ -317,7 +326,8 @@ bns_status layer_fwd_impl(bns_ctx *ctx, int layer, double p, const float *H_in, 
       g.pad = ld != d_out;
       BNS_TRY("gemm_rows_f32(inner)", gemm_rows_f32(g, s));
       g.M = B;
-      g.A = ctx->ws.Hu;
+      g.A = halo_h;  // the kept boundary rows where the caller holds them, scaled on their way in
+      g.rec = ctx->ws.halo_rec;
       g.C = ctx->ws.Hu2;
       g.m_dev = ctx->cur_n_kept;
       if (B > 0) BNS_TRY("gemm_rows_f32(boundary)", gemm_rows_f32(g, s));
@@ -329,13 +339,14 @@ bns_status layer_fwd_impl(bns_ctx *ctx, int layer, double p, const float *H_in, 
     BNS_TRY("dropout_inplace", dropout_inplace(n_in, d_out, H_out, dropout_of(ctx, layer, relu), s));
     return BNS_OK;
   }
-  {
-    // The aggregate reads the kept boundary rows where the caller holds them; it only needs, per
-    // kept node, the row index and the weight S_uu = 1/p (GCN: times d~^-1/2).  A gathered, scaled
-    // copy of the rows would cost a read and a write of every kept row on top of the same reads.
+  // The aggregate reads the kept boundary rows where the caller holds them; it only needs, per
+  // kept node, the row index and the weight S_uu = 1/p (GCN: times d~^-1/2).  A gathered, scaled
+  // copy of the rows would cost a read and a write of every kept row on top of the same reads.
+  // In a training step the sampler has written these records and the weights are packed.
+  if (prepare) {
     PhaseTimer t(ctx, BNS_PHASE_GATHER, s);
     BNS_TRY("halo_records", halo_records(ctx->cur_kept, ctx->cur_n_kept, B, sage ? nullptr : ctx->ws.dis_halo,
-                                         halo_scale(p), ctx->ws.halo_rec, s));
+                                         halo_scale(p), ctx->ws.halo_rec, *prepare, s));
   }
   SpmmRowPart part;
   part.halo_rec = B > 0 ? ctx->ws.halo_rec : nullptr;
@@ -393,6 +404,19 @@ bns_status layer_fwd_impl(bns_ctx *ctx, int layer, double p, const float *H_in, 
   return BNS_OK;
 }
 
+// The weight gradients of several layers, to be run together.
+struct TnBatch {
+  TnGemm g[kMaxTnJobs];
+  int n = 0;
+  bool full() const { return n + 2 > kMaxTnJobs; }
+};
+bns_status run_batch(bns_ctx *ctx, TnBatch *batch, const TnLoss &loss, hipStream_t s) {
+  PhaseTimer t(ctx, BNS_PHASE_GEMM_DW, s);
+  BNS_TRY("gemm_tn", gemm_tn(batch->g, batch->n, loss, s));
+  batch->n = 0;
+  return BNS_OK;
+}
+
 // dZ is the gradient of the layer's pre-activation.  mask_src (nullable): activations of the
 // layer below; when given, dH_in receives the masked gradient (= dZ of the layer below).
 // H_in is needed by the mean-aggregator layer only (its self half of the weight gradient).
@@ -400,7 +424,8 @@ bns_status layer_fwd_impl(bns_ctx *ctx, int layer, double p, const float *H_in, 
 // the aggregate then); the weight gradient is [H_in ; Hu]^T (P^T dZ) instead of A^T dZ.
 bns_status layer_bwd_impl(bns_ctx *ctx, int layer, double p, const float *dZ, const float *A_saved,
                           const float *H_in, float *dW, float *dH_in, float *dhalo, const float *mask_src,
-                          bool update_first, const float *halo_first, float *W_step, float lr, hipStream_t s) {
+                          bool update_first, const float *halo_first, float *W_step, float lr, TnBatch *batch,
+                          hipStream_t s) {
   const int n_in = ctx->part.n_in, B = ctx->part.n_halo;
   const int d_in = ctx->dims[layer - 1], d_out = ctx->dims[layer];
   const char *Wb = ctx->ws.Wb[layer];
@@ -428,10 +453,10 @@ bns_status layer_bwd_impl(bns_ctx *ctx, int layer, double p, const float *dZ, co
     g.m_dev = m_dev;
     return gemm_rows(g, s);
   };
-  // dW (+)= [A | A2]^T G, followed by the plain update when it is the last part of the gradient
-  auto gemm_dw = [&](int32_t K, const float *A, const float *A2, const float *G, bool accumulate, const int32_t *k_dev,
-                     bool last) {
-    TnGemm g{};
+  // dW = [A | A2]^T G joins the batch of weight gradients, which runs when the chain of the layers is through
+  auto add_dw = [&](int32_t K, const float *A, const float *A2, const float *G, float *partials) {
+    TnGemm &g = batch->g[batch->n++];
+    g = TnGemm{};
     g.M = A2 ? 2 * d_in : d_in;
     g.N = d_out;
     g.K = K;
@@ -440,15 +465,13 @@ bns_status layer_bwd_impl(bns_ctx *ctx, int layer, double p, const float *dZ, co
     g.B = G;
     g.a_split = d_in;
     g.C = dW;
-    g.partials = ctx->ws.partials;
-    g.accumulate = accumulate;
-    g.k_dev = k_dev;
-    g.W = last ? W_step : nullptr;
+    g.partials = partials;
+    g.W = W_step;
     g.lr = lr;
-    return gemm_tn(g, s);
+    return &g;
   };
   if (update_first) {
-    float *G_in = ctx->ws.G1, *G_halo = B > 0 ? ctx->ws.Hu2 : nullptr;
+    float *G_in = ctx->ws.G_in[layer], *G_halo = B > 0 ? ctx->ws.G_halo[layer] : nullptr;
     {  // G = P^T dZ at the output width, inner rows and kept boundary rows
       PhaseTimer t(ctx, BNS_PHASE_SPMM_BWD, s);
       const int ld = gather_stride(d_in, d_out);
@@ -462,16 +485,12 @@ bns_status layer_bwd_impl(bns_ctx *ctx, int layer, double p, const float *dZ, co
                                    halo_scale(p), dZ_g, nullptr, nullptr, false, ctx->ws.spmm_partials, G_in, G_halo,
                                    s, d_out));
     }
-    if (B > 0) {  // the kept boundary features once more, unscaled: G_halo carries the 1/p and degree factors
-      PhaseTimer t(ctx, BNS_PHASE_GATHER, s);
-      BNS_TRY("halo_gather", halo_gather(halo_first, ctx->cur_kept, ctx->cur_n_kept, B, nullptr, 1.f, d_in,
-                                         ctx->ws.Hu, s));
-    }
-    {
-      PhaseTimer t(ctx, BNS_PHASE_GEMM_DW, s);
-      BNS_TRY("gemm_tn(inner)", gemm_dw(n_in, H_in, nullptr, G_in, false, nullptr, B == 0));
-      if (B > 0)
-        BNS_TRY("gemm_tn(boundary)", gemm_dw(B, ctx->ws.Hu, nullptr, G_halo, true, ctx->cur_n_kept, true));
+    add_dw(n_in, H_in, nullptr, G_in, ctx->ws.tn[layer]);
+    if (B > 0) {  // the kept boundary features where the caller holds them: G_halo carries the 1/p and degree factors
+      TnGemm *g = add_dw(B, halo_first, nullptr, G_halo, ctx->ws.tn2[layer]);
+      g->rows = ctx->cur_kept;
+      g->k_dev = ctx->cur_n_kept;
+      g->accumulate = true;
     }
     if (dH_in) {
       PhaseTimer t(ctx, BNS_PHASE_GEMM_DA, s);
@@ -487,10 +506,7 @@ bns_status layer_bwd_impl(bns_ctx *ctx, int layer, double p, const float *dZ, co
   // input (the product with W^T) and is divided out of the boundary rows, which are not masked.
   const float ms = mask_src ? mask_scale_of(ctx) : 1.f;
   if (ctx->layer_kind == 1) {
-    {
-      PhaseTimer t(ctx, BNS_PHASE_GEMM_DW, s);  // [A | H]^T dZ in one product: dZ is read once
-      BNS_TRY("gemm_tn(concat)", gemm_dw(n_in, A_saved, H_in, dZ, false, nullptr, true));
-    }
+    add_dw(n_in, A_saved, H_in, dZ, ctx->ws.tn[layer]);  // [A | H]^T dZ in one product: dZ is read once
     if (dH_in) {
       {
         PhaseTimer t(ctx, BNS_PHASE_GEMM_DA, s);  // dZ [W_n ; W_s]^T in one product, split into the two halves
@@ -505,10 +521,7 @@ bns_status layer_bwd_impl(bns_ctx *ctx, int layer, double p, const float *dZ, co
     }
     return BNS_OK;
   }
-  {
-    PhaseTimer t(ctx, BNS_PHASE_GEMM_DW, s);
-    BNS_TRY("gemm_tn", gemm_dw(n_in, A_saved, nullptr, dZ, false, nullptr, true));
-  }
+  add_dw(n_in, A_saved, nullptr, dZ, ctx->ws.tn[layer]);
   if (dH_in && d_out < d_in) {
     // (P^T dZ) W^T instead of P^T (dZ W^T): the transposed aggregate runs at the narrower width
     float *G_in = ctx->ws.G1, *G_halo = dhalo ? ctx->ws.Hu : nullptr;
@@ -543,44 +556,46 @@ bns_status layer_bwd_impl(bns_ctx *ctx, int layer, double p, const float *dZ, co
   return BNS_OK;
 }
 
-// Packs the weights of layers first..last (W[0] is layer `first`'s) for the forward product and / or for
-// dZ W^T (layer 1 of a training step has no such product).
-bns_status pack_layers(bns_ctx *ctx, const float *const *W, int first, int last, bool fwd, bool bwd, hipStream_t s) {
-  PackJob jobs[kMaxPackJobs];
-  int n = 0;
-  const int32_t kw = ctx->layer_kind == 1 ? 2 : 1;
-  for (int l = first; l <= last; ++l) {
-    const int32_t d_in = kw * ctx->dims[l - 1], d_out = ctx->dims[l];
-    // a layer in one kernel reads its weights as they are
-    if (fwd && (!one_kernel_layer(ctx->part, ctx->layer_kind, ctx->dims[l - 1], d_out) ||
-                update_first_shape(ctx->layer_kind, ctx->dims[l - 1], d_out))) {
-      const int32_t part = kw == 2 && !concat_in_one(ctx->dims[l - 1]) ? 2 : 1;  // the two halves apart
-      for (int32_t h = 0; h < part; ++h)
-        jobs[n++] = PackJob{W[l - first] + (size_t)h * ctx->dims[l - 1] * d_out,
-                            ctx->ws.Wf[l] + h * packed_bytes_f32(ctx->dims[l - 1], d_out), d_in / part, d_out, false};
-    }
-    if (bwd && (l > 1 || !fwd)) {
-      const int32_t part = kw == 2 && ctx->dims[l - 1] % 4 != 0 ? 2 : 1;  // the two halves apart (see gemm_wt)
-      for (int32_t h = 0; h < part; ++h)
-        jobs[n++] = PackJob{W[l - first] + (size_t)h * ctx->dims[l - 1] * d_out,
-                            ctx->ws.Wb[l] + h * packed_bytes(d_out, ctx->dims[l - 1]), d_out, d_in / part, true};
-    }
-    if (n + 4 > kMaxPackJobs || l == last) {
-      BNS_TRY("pack_weights", pack_weights(jobs, n, s));
-      n = 0;
+// Adds the weights of layer l to the packing jobs, for the forward product and / or for dZ W^T.
+void add_pack_jobs(const bns_ctx *ctx, int l, const float *W, bool fwd, bool bwd, PackJobs *jobs) {
+  const int32_t kw = ctx->layer_kind == 1 ? 2 : 1, d_in = ctx->dims[l - 1], d_out = ctx->dims[l];
+  const size_t half = (size_t)d_in * d_out;
+  auto add = [&](const float *w, char *out, int32_t K, int32_t N, bool split) {
+    PackJob &j = jobs->j[jobs->n++];
+    j = PackJob{w, out, K, N, split};
+    jobs->units += pack_units(j);
+  };
+  // a layer in one kernel reads its weights as they are
+  if (fwd && (!one_kernel_layer(ctx->part, ctx->layer_kind, d_in, d_out) ||
+              update_first_shape(ctx->layer_kind, d_in, d_out))) {
+    if (kw == 2 && !concat_in_one(d_in)) {  // the two halves apart
+      add(W, ctx->ws.Wf[l], d_in, d_out, false);
+      add(W + half, ctx->ws.Wf[l] + packed_bytes_f32(d_in, d_out), d_in, d_out, false);
+    } else {
+      add(W, ctx->ws.Wf[l], kw * d_in, d_out, false);
     }
   }
-  return BNS_OK;
+  if (bwd) {
+    if (kw == 2 && d_in % 4 != 0) {  // the two halves apart (see gemm_wt)
+      add(W, ctx->ws.Wb[l], d_out, d_in, true);
+      add(W + half, ctx->ws.Wb[l] + packed_bytes(d_out, d_in), d_out, d_in, true);
+    } else {
+      add(W, ctx->ws.Wb[l], d_out, kw * d_in, true);
+    }
+  }
 }
+constexpr int kPackLayers = kMaxPackJobs / 4;  // layers whose jobs fit one launch
 
+// pack (nullable): a training step's: weights to pack beside the sampling, and the records of the kept nodes too
 bns_status sample_impl(bns_ctx *ctx, uint64_t seed, uint32_t epoch, const uint32_t *epoch_dev, double p,
-                       int32_t *kept_ids, int32_t *remap, int32_t *n_kept, hipStream_t s) {
+                       int32_t *kept_ids, int32_t *remap, int32_t *n_kept, const PackJobs *pack, hipStream_t s) {
   const uint64_t threshold = (uint64_t)std::floor(p * 4294967296.0);
   PhaseTimer t(ctx, BNS_PHASE_SAMPLE, s);
   BNS_TRY("sample_boundary",
           sample_boundary(ctx->part.halo_gid, ctx->part.n_halo, seed, epoch, epoch_dev, (uint32_t)ctx->part.part_id,
                           threshold, ctx->ws.ballots, ctx->ws.tile_sums, kept_ids, remap, n_kept, ctx->part.halo_ptr,
-                          (int32_t)ctx->part.e_in, ctx->ws.kept_start, s));
+                          (int32_t)ctx->part.e_in, ctx->ws.kept_start, pack ? ctx->ws.halo_rec : nullptr,
+                          ctx->layer_kind == 1 ? nullptr : ctx->ws.dis_halo, halo_scale(p), pack, s));
   ctx->cur_kept = kept_ids;
   ctx->cur_remap = remap;
   ctx->cur_n_kept = n_kept;
@@ -613,11 +628,11 @@ bns_status build_impl(bns_ctx *ctx, int32_t *row_ptr, int32_t *col_idx, int32_t 
 // Selection step + subgraph step of a training step, into the workspace arrays: one launch for a
 // small partition (timed as the sample phase), else the two calls above.
 bns_status sample_and_build_impl(bns_ctx *ctx, uint64_t seed, uint32_t epoch, const uint32_t *epoch_dev, double p,
-                                 hipStream_t s) {
+                                 const PackJobs &pack, hipStream_t s) {
   Layout &w = ctx->ws;
   const bns_partition_desc &P = ctx->part;
   if (!sample_build_small_fits(P.n_in, P.n_halo, P.e_in, P.e_bd)) {
-    const bns_status st = sample_impl(ctx, seed, epoch, epoch_dev, p, w.kept_ids, w.remap, w.counters, s);
+    const bns_status st = sample_impl(ctx, seed, epoch, epoch_dev, p, w.kept_ids, w.remap, w.counters, &pack, s);
     if (st != BNS_OK) return st;
     return build_impl(ctx, w.row_ptr, w.col_idx, w.t_row_ptr, w.t_col_idx, w.counters + 1, s);
   }
@@ -627,7 +642,7 @@ bns_status sample_and_build_impl(bns_ctx *ctx, uint64_t seed, uint32_t epoch, co
           sample_build_small(P.halo_gid, P.n_halo, seed, epoch, epoch_dev, (uint32_t)P.part_id, threshold, w.ballots,
                              w.kept_ids, w.remap, w.counters, w.kept_start, P.n_in, P.e_in, P.e_bd, w.split, w.kpos,
                              w.row_ptr, w.col_idx, w.counters + 1, P.halo_ptr, P.halo_col, w.t_row_ptr, w.t_col_idx,
-                             s));
+                             w.halo_rec, ctx->layer_kind == 1 ? nullptr : w.dis_halo, halo_scale(p), &pack, s));
   ctx->cur_kept = w.kept_ids;
   ctx->cur_remap = w.remap;
   ctx->cur_n_kept = w.counters;
@@ -708,7 +723,7 @@ bns_status bns_sample_boundary(bns_ctx *ctx, uint64_t seed, uint32_t epoch, doub
   if (bad_p(p)) return fail(ctx, BNS_EINVAL, "p must lie in [0, 1]");
   if (!n_kept || (ctx->part.n_halo > 0 && (!kept_ids || !remap)))
     return fail(ctx, BNS_EINVAL, "null output pointer");
-  return sample_impl(ctx, seed, epoch, nullptr, p, kept_ids, remap, n_kept, static_cast<hipStream_t>(stream));
+  return sample_impl(ctx, seed, epoch, nullptr, p, kept_ids, remap, n_kept, nullptr, static_cast<hipStream_t>(stream));
 }
 
 bns_status bns_build_sampled_csr(bns_ctx *ctx, const int32_t *remap, const int32_t *kept_ids, const int32_t *n_kept,
@@ -733,9 +748,9 @@ bns_status bns_gcn_layer_fwd(bns_ctx *ctx, int32_t layer, double p, const float 
     return fail(ctx, BNS_EINVAL, "null pointer");
   if (!ctx->cur_row_ptr) return fail(ctx, BNS_EINVAL, "bns_build_sampled_csr has not been called");
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const bns_status st = pack_layers(ctx, &W, layer, layer, true, false, s);
-  if (st != BNS_OK) return st;
-  return layer_fwd_impl(ctx, layer, p, H_in, halo_h, W, A_saved, H_out, relu != 0, false, s);
+  PackJobs jobs;
+  add_pack_jobs(ctx, layer, W, true, false, &jobs);
+  return layer_fwd_impl(ctx, layer, p, H_in, halo_h, W, A_saved, H_out, relu != 0, false, &jobs, s);
 }
 
 bns_status bns_gcn_layer_bwd(bns_ctx *ctx, int32_t layer, double p, const float *dH_out, const float *H_out,
@@ -750,16 +765,19 @@ bns_status bns_gcn_layer_bwd(bns_ctx *ctx, int32_t layer, double p, const float 
   if (!ctx->cur_t_row_ptr) return fail(ctx, BNS_EINVAL, "bns_build_sampled_csr has not been called");
   hipStream_t s = static_cast<hipStream_t>(stream);
   const float *dZ = dH_out;
+  PackJobs jobs;
+  if (dH_in) add_pack_jobs(ctx, layer, W, false, true, &jobs);
   if (H_out) {
     const int64_t n = (int64_t)ctx->part.n_in * ctx->dims[layer];
-    BNS_TRY("relu_mask", relu_mask(n, dH_out, H_out, mask_scale_of(ctx), ctx->ws.G0, s));
+    BNS_TRY("relu_mask", relu_mask(n, dH_out, H_out, mask_scale_of(ctx), ctx->ws.G0, jobs, s));
     dZ = ctx->ws.G0;
+  } else {
+    BNS_TRY("pack_weights", pack_weights(jobs, s));
   }
-  if (dH_in) {
-    const bns_status st = pack_layers(ctx, &W, layer, layer, false, true, s);
-    if (st != BNS_OK) return st;
-  }
-  return layer_bwd_impl(ctx, layer, p, dZ, A_saved, H_in, dW, dH_in, dhalo, nullptr, false, nullptr, nullptr, 0.f, s);
+  TnBatch batch;
+  const bns_status st = layer_bwd_impl(ctx, layer, p, dZ, A_saved, H_in, dW, dH_in, dhalo, nullptr, false, nullptr, nullptr,
+                                       0.f, &batch, s);
+  return st != BNS_OK ? st : run_batch(ctx, &batch, TnLoss{}, s);
 }
 
 static bns_status train_step_impl(bns_ctx *ctx, uint64_t seed, uint32_t epoch, const uint32_t *epoch_dev, double p,
@@ -776,40 +794,53 @@ static bns_status train_step_impl(bns_ctx *ctx, uint64_t seed, uint32_t epoch, c
   hipStream_t s = static_cast<hipStream_t>(stream);
   Layout &w = ctx->ws;
 
-  bns_status st = sample_and_build_impl(ctx, seed, epoch, epoch_dev, p, s);
-  if (st != BNS_OK) return st;
-  st = pack_layers(ctx, W, 1, L, true, true, s);
+  // the weights of up to kPackLayers layers are packed beside the sampling, those of deeper models before it
+  PackJobs jobs;
+  for (int l = L; l >= 1; --l) {
+    add_pack_jobs(ctx, l, W[l - 1], true, l > 1, &jobs);
+    if (l > 1 && (l - 1) % kPackLayers == 0) {
+      BNS_TRY("pack_weights", pack_weights(jobs, s));
+      jobs = PackJobs{};
+    }
+  }
+  bns_status st = sample_and_build_impl(ctx, seed, epoch, epoch_dev, p, jobs, s);
   if (st != BNS_OK) return st;
 
   const float *H_prev = X;
   for (int l = 1; l <= L; ++l) {
     st = layer_fwd_impl(ctx, l, p, H_prev, ctx->part.n_halo > 0 ? halo_h[l - 1] : nullptr, W[l - 1], w.A[l],
-                        w.H[l], l < L, layer_plan(ctx, l, X) == BNS_LAYER_UPDATE_FIRST, s);
+                        w.H[l], l < L, layer_plan(ctx, l, X) == BNS_LAYER_UPDATE_FIRST, nullptr, s);
     if (st != BNS_OK) return st;
     H_prev = w.H[l];
   }
 
   const int C = ctx->dims[L];
+  TnLoss loss_sum{w.loss_partials, 0, loss};
   {
     PhaseTimer t(ctx, BNS_PHASE_LOSS, s);
     if (ctx->loss_kind == 0)
       BNS_TRY("loss_softmax_ce", loss_softmax_ce(n_in, C, w.H[L], static_cast<const int32_t *>(labels), w.dZ[L],
-                                                 w.loss_partials, loss, s));
+                                                 w.loss_partials, &loss_sum.n, s));
     else
       BNS_TRY("loss_sigmoid_bce", loss_sigmoid_bce(n_in, C, w.H[L], static_cast<const uint8_t *>(labels), w.dZ[L],
-                                                   w.loss_partials, loss, s));
+                                                   w.loss_partials, &loss_sum.n, s));
   }
 
   // dZ[l] is the gradient w.r.t. the pre-activation of layer l; the backward pass of layer l writes
   // dZ[l-1], already masked by the activations of the layer below.  Every layer keeps its own buffer
   // (BNS_VIEW_DZ), so that each stage of the backward pass can be inspected with its exact inputs.
+  TnBatch batch;
   for (int l = L; l >= 1; --l) {
     float *dh = (dhalo && l > 1) ? dhalo[l - 1] : nullptr;
     st = layer_bwd_impl(ctx, l, p, w.dZ[l], w.A[l], l > 1 ? w.H[l - 1] : X, dW[l - 1],
                         l > 1 ? w.dZ[l - 1] : nullptr, dh,
                         l > 1 ? w.H[l - 1] : nullptr, layer_plan(ctx, l, X) == BNS_LAYER_UPDATE_FIRST,
-                        ctx->part.n_halo > 0 ? halo_h[l - 1] : nullptr, W[l - 1], lr, s);
+                        ctx->part.n_halo > 0 ? halo_h[l - 1] : nullptr, W[l - 1], lr, &batch, s);
     if (st != BNS_OK) return st;
+    if (l == 1 || batch.full()) {
+      st = run_batch(ctx, &batch, l == 1 ? loss_sum : TnLoss{}, s);
+      if (st != BNS_OK) return st;
+    }
   }
   return BNS_OK;
 }

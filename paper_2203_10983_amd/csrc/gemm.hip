@@ -23,87 +23,23 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "device_utils.hpp"
 #include "kernels.hpp"
+#include "pack_device.hpp"
 #include "split_bf16.hpp"
 
 namespace bns {
 
 // ---- packed weights -----------------------------------------------------------------------------
-// Operand fragments, 1 KB each (64 lanes x 16 bytes), zero outside the matrix.
-//   split: of W [N, K] transposed, for gemm_rows.  For depth step s of 32 and column tile t of 16, at
-//     ((s * tiles + t) * 3 + piece) KB, lane l's 8 values are column 16 t + l % 16 at the depths
-//     32 s + 16 (e / 4) + 4 (l / 16) + e % 4, e = 0..7, negated in even steps (mfma_split)
-//   fp32: of W [K, N], for gemm_rows_f32.  For depth step s of 32, column tile t of 32 and depth group j of 8, at
-//     ((s * tiles + t) * 4 + j) KB, lane l's 4 values are column 32 t + l % 32 at the depths
-//     32 s + 8 j + 2 i + l / 32, i = 0..3
-__host__ __device__ static inline int k_steps(int K) { return (K + 31) / 32; }
-__host__ __device__ static inline int col_tiles(int N) { return (N + 15) / 16; }
-__host__ __device__ static inline int pack_units(const PackJob &j) {  // a wavefront's work: one fragment set
-  return k_steps(j.K) * (j.split ? col_tiles(j.N) : (j.N + 31) / 32);
-}
-
 size_t packed_bytes(int32_t K, int32_t N) { return (size_t)k_steps(K) * col_tiles(N) * kFragSet; }
 size_t packed_bytes_f32(int32_t K, int32_t N) { return (size_t)k_steps(K) * ((N + 31) / 32) * 4096; }
 
-struct PackJobs {
-  PackJob j[kMaxPackJobs];
-  int n;
-};
-
 __global__ void __launch_bounds__(256) pack_weights_kernel(const PackJobs jobs) {
-  int u = blockIdx.x * 4 + (threadIdx.x >> 6);
-  int q = 0;
-  for (; q < jobs.n; ++q) {
-    const int units = pack_units(jobs.j[q]);
-    if (u < units) break;
-    u -= units;
-  }
-  if (q == jobs.n) return;
-  const PackJob &job = jobs.j[q];
-  const int lane = lane_id();
-  if (job.split) {
-    const int T = col_tiles(job.N), s = u / T, t = u % T;
-    const int n = t * 16 + (lane & 15), g = lane >> 4;
-    f32x4 v[2];
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int k = s * 32 + j * 16 + g * 4 + e;
-        v[j][e] = k < job.K && n < job.N ? job.W[(size_t)n * job.K + k] : 0.f;
-      }
-    const Frag3 f = s % 2 == 0 ? split8<true>(v[0], v[1]) : split8(v[0], v[1]);
-    char *out = static_cast<char *>(job.out) + (size_t)u * kFragSet + lane * 16;
-#pragma unroll
-    for (int p = 0; p < 3; ++p) *reinterpret_cast<bf16x8 *>(out + p * kFragBytes) = f.p[p];
-  } else {
-    const int T = (job.N + 31) / 32, s = u / T, t = u % T;
-    const int n = t * 32 + (lane & 31);
-    char *out = static_cast<char *>(job.out) + (size_t)u * 4096 + lane * 16;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      f32x4 v;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int k = s * 32 + j * 8 + i * 2 + (lane >> 5);
-        v[i] = k < job.K && n < job.N ? job.W[(size_t)k * job.N + n] : 0.f;
-      }
-      *reinterpret_cast<f32x4 *>(out + j * 1024) = v;
-    }
-  }
+  pack_unit(jobs, blockIdx.x * 4 + (threadIdx.x >> 6));
 }
 
-hipError_t pack_weights(const PackJob *jobs, int32_t n, hipStream_t s) {
-  for (int32_t i0 = 0; i0 < n; i0 += kMaxPackJobs) {
-    PackJobs pj;
-    pj.n = std::min<int32_t>(kMaxPackJobs, n - i0);
-    int64_t units = 0;
-    for (int i = 0; i < pj.n; ++i) {
-      pj.j[i] = jobs[i0 + i];
-      units += pack_units(pj.j[i]);
-    }
-    if (units) pack_weights_kernel<<<(unsigned)((units + 3) / 4), 256, 0, s>>>(pj);
-  }
+hipError_t pack_weights(const PackJobs &jobs, hipStream_t s) {
+  if (jobs.units) pack_weights_kernel<<<(unsigned)((jobs.units + 3) / 4), 256, 0, s>>>(jobs);
   return hipGetLastError();
 }
 
@@ -197,7 +133,7 @@ __global__ void __launch_bounds__(256, R * NC > 8 ? 3 : 4) gemm_rows_kernel(cons
       Frag3 fb;
 #pragma unroll
       for (int i = 0; i < 3; ++i) fb.p[i] = *reinterpret_cast<const bf16x8 *>(bs + c * kFragSet + i * kFragBytes);
-      mfma_split<R>(acc[c], fb, fa, s & 1 ? 1.f : -1.f);
+      mfma_split<R>(acc[c], fb, fa);
     }
     buf ^= 1;
     if (last) {
@@ -215,6 +151,7 @@ __global__ void __launch_bounds__(256, R * NC > 8 ? 3 : 4) gemm_rows_kernel(cons
         for (int c = 0; c < NC; ++c) {
           const int left = n_end - (col0 + c * 16);  // columns from this lane's first one to the end
           f32x4 v = acc[c][r];
+          const float alpha = (t0 + c) & 1 ? -p.alpha : p.alpha;  // odd tiles are summed negated
           if constexpr (EPI == kMask) {
             f32x4 m = {0.f, 0.f, 0.f, 0.f};
             if (left >= 4) m = *reinterpret_cast<const f32x4u *>(ms + c * 16);
@@ -223,10 +160,10 @@ __global__ void __launch_bounds__(256, R * NC > 8 ? 3 : 4) gemm_rows_kernel(cons
               for (int e = 0; e < 3; ++e)
                 if (e < left) m[e] = ms[c * 16 + e];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = m[e] > 0.f ? v[e] * p.alpha : 0.f;
+            for (int e = 0; e < 4; ++e) v[e] = m[e] > 0.f ? v[e] * alpha : 0.f;
           } else {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] *= p.alpha;
+            for (int e = 0; e < 4; ++e) v[e] *= alpha;
           }
           float *const d = (EPI == kPair && col0 + c * 16 >= p.c_split ? dst2 : dst) + c * 16;
           if (left >= 4) *reinterpret_cast<f32x4u *>(d) = v;
@@ -291,13 +228,21 @@ hipError_t gemm_rows(const RowsGemm &g, hipStream_t s) {
   return hipGetLastError();
 }
 
-// ---- transposed product, depth split over the chip -----------------------------------------------
-struct TnArgs {
+// ---- transposed products, depth split over the chip ----------------------------------------------
+// The weight gradients of a training step are independent of each other and of the backward chain once
+// its gradients are known, so all of them run as one batch: one launch of the products per tile shape (the
+// splits dealt by work), one launch that adds up every partial.
+struct TnJob {
   const float *A, *A2, *B;
-  int M, N, K, a_split, lda;
-  const int *k_dev;
+  const int32_t *rows, *k_dev;
   float *partials;
-  int tiles_m, tiles_n, splits;
+  int M, N, K, a_split, lda;
+  int tiles_n, nt, splits;
+  int first;  // first workgroup of the job
+};
+struct TnJobs {
+  TnJob j[kMaxTnJobs];
+  int n;
 };
 
 // Bytes between the fragment sets of neighbouring 16-column tiles in LDS: 64 more than a set, so
@@ -305,7 +250,7 @@ struct TnArgs {
 constexpr int kTnTile = kFragSet + 64;
 
 template <int MB, int NB>
-__global__ void __launch_bounds__(256, 3) gemm_tn_kernel(const TnArgs a) {
+__global__ void __launch_bounds__(256, 3) gemm_tn_kernel(const TnJobs jobs) {
   constexpr int KS = MB + NB > 128 ? 32 : 64;          // depth of a step: keeps all 256 threads loading
   constexpr int TM = MB / 16, TN = NB / 16, TILES = TM + TN;
   constexpr int GA = MB / 4, GB = NB / 4;              // 4-column groups of the two operands
@@ -314,16 +259,13 @@ __global__ void __launch_bounds__(256, 3) gemm_tn_kernel(const TnArgs a) {
   static_assert((GA + GB) * KG <= 256, "one load unit per thread");
   __shared__ __attribute__((aligned(16))) char lds[(KS / 32) * TILES * kTnTile];
 
-  const int nt = a.tiles_m * a.tiles_n;
-  int tile, split;
-  if (a.splits % 8 == 0) {  // the tiles of one depth chunk follow each other on one XCD
-    const int x = blockIdx.x & 7, q = blockIdx.x >> 3;
-    tile = q % nt;
-    split = (q / nt) * 8 + x;
-  } else {
-    tile = blockIdx.x % nt;
-    split = blockIdx.x / nt;
-  }
+  int q = 0;
+  while (q + 1 < jobs.n && (int)blockIdx.x >= jobs.j[q + 1].first) ++q;
+  const TnJob &a = jobs.j[q];
+  const int b = (int)blockIdx.x - a.first;
+  // the tiles of one depth chunk follow each other on one XCD (workgroup b runs on XCD b % 8)
+  const int tile = (b >> 3) % a.nt, split = ((b >> 3) / a.nt) * 8 + (b & 7);
+  if (split >= a.splits) return;
   const int m0 = (tile / a.tiles_n) * MB, n0 = (tile % a.tiles_n) * NB;
   const int K = a.k_dev ? min(a.K, *a.k_dev) : a.K;
   const int chunk = ((K + a.splits - 1) / a.splits + KS - 1) / KS * KS;  // from the real depth, which may live on the device
@@ -343,7 +285,7 @@ __global__ void __launch_bounds__(256, 3) gemm_tn_kernel(const TnArgs a) {
     ld = a.N;
     cols = a.N - (n0 + c4 * 4);
   } else {
-    int c = m0 + c4 * 4;
+    const int c = m0 + c4 * 4;
     src = a.A + c;
     ld = a.lda;
     cols = (a.A2 ? a.a_split : a.M) - c;
@@ -355,23 +297,34 @@ __global__ void __launch_bounds__(256, 3) gemm_tn_kernel(const TnArgs a) {
   const bool straddle = !is_b && a.A2 && cols > 0 && cols < 4;  // a_split % 4 != 0: one group takes from both
   const int row_of_a2 = straddle ? m0 + c4 * 4 - a.a_split : 0;
   cols = straddle ? min(4, a.M - (m0 + c4 * 4)) : max(0, min(4, cols));
+  const int32_t *rows = is_b ? nullptr : a.rows;  // A's rows by index
   f32x4 v[8];
   auto load = [&](int k0) {
     const int k = k0 + kg * 8;
     if (!active) return;
     if (cols == 4 && !straddle && k + 8 <= k_end) {
+      if (rows) {
+        int r[8];
 #pragma unroll
-      for (int j = 0; j < 8; ++j) v[j] = *reinterpret_cast<const f32x4u *>(src + (size_t)(k + j) * ld);
+        for (int j = 0; j < 8; ++j) r[j] = rows[k + j];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) v[j] = *reinterpret_cast<const f32x4u *>(src + (size_t)r[j] * ld);
+      } else {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) v[j] = *reinterpret_cast<const f32x4u *>(src + (size_t)(k + j) * ld);
+      }
     } else {
 #pragma unroll
-      for (int j = 0; j < 8; ++j)
+      for (int j = 0; j < 8; ++j) {
+        const int r = k + j < k_end ? (rows ? rows[k + j] : k + j) : 0;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           float xv = 0.f;
           if (e < cols && k + j < k_end)
-            xv = straddle && row_of_a2 + e >= 0 ? a.A2[(size_t)(k + j) * ld + row_of_a2 + e] : src[(size_t)(k + j) * ld + e];
+            xv = straddle && row_of_a2 + e >= 0 ? a.A2[(size_t)r * ld + row_of_a2 + e] : src[(size_t)r * ld + e];
           v[j][e] = xv;
         }
+      }
     }
   };
   // column 4 c4 + i sits in slot 4 i + c4 % 4 of its tile (so that four lanes store 64 contiguous bytes)
@@ -421,115 +374,220 @@ __global__ void __launch_bounds__(256, 3) gemm_tn_kernel(const TnArgs a) {
       }
     }
   }
-  float *out = a.partials + (size_t)(split * nt + tile) * (MB * NB) + (size_t)wid * (MT * NT * 256) + lane * 4;
+  float *out = a.partials + (size_t)(split * a.nt + tile) * (MB * NB) + (size_t)wid * (MT * NT * 256) + lane * 4;
 #pragma unroll
   for (int j = 0; j < NT; ++j)
 #pragma unroll
     for (int i = 0; i < MT; ++i) *reinterpret_cast<f32x4 *>(out + (j * MT + i) * 256) = split & 1 ? -acc[j][i] : acc[j][i];
 }
 
-// C = (C +) sum over the splits, in a fixed order; optionally W -= lr * C (the update step of
-// Algorithm 1 takes its gradient from the registers).  A workgroup owns one 16 x 16 accumulator
-// tile: NW wavefronts add every NW-th partial of it, then their sums are added in ascending order.
-struct TnReduce {
-  const float *partials;
+// The sums over the splits, in a fixed order: C = sum (+ the sum of the next job, for a gradient of two parts),
+// optionally W -= lr * C (the plain update of Algorithm 1 takes its gradient from the registers).  A workgroup owns
+// one 16 x 16 accumulator tile: NW wavefronts add every NW-th partial of it, then their sums are added
+// in pairs.  One more workgroup adds up the partial losses of the step.
+struct TnSum {
+  const float *partials, *partials2;  // partials2 (nullable): the second part's, same tiles
   float *C, *W;
+  int M, N, mt, nt_wave, tiles_n, nt, splits, splits2;  // mt x nt_wave accumulator tiles per wavefront
+  int first;
+};
+struct TnSums {
+  TnSum j[kMaxTnJobs];
+  int n, blocks;
   float lr;
-  int M, N, tiles_n, nt, splits;
-  bool accumulate;
+  const float *loss_partials;
+  int n_loss;
+  float *loss;
 };
 
-template <int MB, int NB, int NW>
-__global__ void __launch_bounds__(NW * 64) gemm_tn_reduce_kernel(const TnReduce a) {
-  constexpr int MT = MB / 32, NT = NB / 32, F = MB * NB / 256;
+template <int NW>
+__global__ void __launch_bounds__(NW * 64) gemm_tn_reduce_kernel(const TnSums jobs) {
   __shared__ float part[NW][256];
   const int lane = lane_id(), wid = threadIdx.x >> 6;
-  const int tile = blockIdx.x / F, f = blockIdx.x % F;
-  const size_t stride = (size_t)a.nt * (MB * NB);
-  const float *in = a.partials + (size_t)tile * (MB * NB) + f * 256 + lane * 4;
-  f32x4 sum = {0.f, 0.f, 0.f, 0.f};
-  constexpr int U = 4;
-  for (int z0 = wid; z0 < a.splits; z0 += U * NW) {
-    f32x4 x[U];
-#pragma unroll
-    for (int i = 0; i < U; ++i)
-      x[i] = z0 + i * NW < a.splits ? *reinterpret_cast<const f32x4 *>(in + (size_t)(z0 + i * NW) * stride) : f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int i = 0; i < U; ++i) sum += x[i];
+  if ((int)blockIdx.x == jobs.blocks) {
+    float x = 0.f;
+    for (int i = threadIdx.x; i < jobs.n_loss; i += NW * 64) x += jobs.loss_partials[i];
+    x = wave_sum(x);
+    if (lane == 0) part[0][wid] = x;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      float s = 0.f;
+      for (int w = 0; w < NW; ++w) s += part[0][w];
+      *jobs.loss = s;
+    }
+    return;
   }
+  int q = 0;
+  while (q + 1 < jobs.n && (int)blockIdx.x >= jobs.j[q + 1].first) ++q;
+  const TnSum &a = jobs.j[q];
+  const int F = 4 * a.mt * a.nt_wave;
+  const int tile = ((int)blockIdx.x - a.first) / F, f = ((int)blockIdx.x - a.first) % F;
+  f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+  auto add = [&](const float *partials, int splits) {
+    const size_t stride = (size_t)a.nt * F * 256;
+    const float *in = partials + ((size_t)tile * F + f) * 256 + lane * 4;
+    constexpr int U = 4;
+    for (int z0 = wid; z0 < splits; z0 += U * NW) {
+      f32x4 x[U];
+#pragma unroll
+      for (int i = 0; i < U; ++i)
+        x[i] = z0 + i * NW < splits ? *reinterpret_cast<const f32x4 *>(in + (size_t)(z0 + i * NW) * stride) : f32x4{0.f, 0.f, 0.f, 0.f};
+      sum += (x[0] + x[1]) + (x[2] + x[3]);
+    }
+  };
+  add(a.partials, a.splits);
+  if (a.partials2) add(a.partials2, a.splits2);
   *reinterpret_cast<f32x4 *>(&part[wid][lane * 4]) = sum;
   __syncthreads();
   const int e = threadIdx.x;
   if (e >= 256) return;
-  float s = 0.f;
+  float p[NW];
 #pragma unroll
-  for (int w = 0; w < NW; ++w) s += part[w][e];
+  for (int w = 0; w < NW; ++w) p[w] = part[w][e];
+#pragma unroll
+  for (int h = NW / 2; h > 0; h /= 2)
+#pragma unroll
+    for (int w = 0; w < h; ++w) p[w] += p[w + h];
+  const float s = p[0];
   // element e: lane e / 4, register e % 4; its slots in the two 16-column tiles are 4 (lane / 16) + e % 4
   // (columns of B) and lane % 16 (columns of A), slot q standing for column 4 (q % 4) + q / 4
-  const int l = e >> 2, w4 = f / (MT * NT), ji = f % (MT * NT);
-  const int j = ji / MT, i = ji % MT, sa = l & 15;
-  const int m = (tile / a.tiles_n) * MB + ((w4 >> 1) * MT + i) * 16 + 4 * (sa & 3) + (sa >> 2);
-  const int n = (tile % a.tiles_n) * NB + ((w4 & 1) * NT + j) * 16 + 4 * (e & 3) + (l >> 4);
+  const int per_wave = a.mt * a.nt_wave, l = e >> 2, w4 = f / per_wave, ji = f % per_wave;
+  const int j = ji / a.mt, i = ji % a.mt, sa = l & 15;
+  const int m = (tile / a.tiles_n) * (32 * a.mt) + ((w4 >> 1) * a.mt + i) * 16 + 4 * (sa & 3) + (sa >> 2);
+  const int n = (tile % a.tiles_n) * (32 * a.nt_wave) + ((w4 & 1) * a.nt_wave + j) * 16 + 4 * (e & 3) + (l >> 4);
   if (m >= a.M || n >= a.N) return;
   const size_t at = (size_t)m * a.N + n;
-  if (a.accumulate) s += a.C[at];
   a.C[at] = s;
-  if (a.W) a.W[at] -= a.lr * s;
+  if (a.W) a.W[at] -= jobs.lr * s;
 }
 
 namespace {
 
 struct TnPlan { int mb, nb, tiles_m, tiles_n, splits; };
 
-// Tile shape: the one that pads the result least; among equals the larger one (an operand is read
-// once per tile of the other).  Splits: three workgroups per compute unit, at least 64 rows each.
-TnPlan tn_plan(int32_t M, int32_t N, int32_t K) {
+constexpr int kTnBlocks = 768;   // workgroups of a launch: three per compute unit, one resident round
+constexpr int kTnMinRows = 64;   // per split
+constexpr int kTnAlone = 512;    // rows per split from which a job is not batched
+
+// Tile shape: the cheapest cover of the result.  A step of 32 depths costs a workgroup (in cycles, and what the
+// matrix and vector pipes do hardly overlaps) 24 per 16 x 16 products, 2.75 per column that it splits, and a
+// fixed part.  Where 128 x 128 tiles and depth chunks of 256 rows would leave most of the chip idle, tiles of at most
+// 64 x 64: smaller chunks would store more in partial sums than they read.
+void tn_tiles(int32_t M, int32_t N, int64_t K, TnPlan *b) {
   static const int mbs[2] = {128, 64}, nbs[4] = {128, 96, 64, 32};
-  TnPlan b{};
-  int64_t best = 0;
+  const bool shallow = (int64_t)((M + 127) / 128) * ((N + 127) / 128) * (K / 256) < kTnBlocks / 3;
+  double best = 0.0;
+  b->mb = 0;
   for (int mb : mbs)
     for (int nb : nbs) {
-      const int64_t area = (int64_t)((M + mb - 1) / mb * mb) * ((N + nb - 1) / nb * nb);
-      if (b.mb == 0 || area * 10 < best * 9) {
-        b.mb = mb;
-        b.nb = nb;
-        best = area;
+      if (shallow && (mb > 64 || nb > 64)) continue;
+      const double cost = (double)((M + mb - 1) / mb) * ((N + nb - 1) / nb) * (24.0 * (mb / 16) * (nb / 16) + 2.75 * (mb + nb) + 200.0);
+      if (b->mb == 0 || cost < best) {
+        b->mb = mb;
+        b->nb = nb;
+        best = cost;
       }
     }
-  b.tiles_m = (M + b.mb - 1) / b.mb;
-  b.tiles_n = (N + b.nb - 1) / b.nb;
-  const int nt = b.tiles_m * b.tiles_n;
-  int64_t splits = std::max(1, 768 / nt);
-  splits = std::max<int64_t>(1, std::min<int64_t>(splits, (K + 63) / 64));
-  if (splits >= 8) splits = splits / 8 * 8;
-  b.splits = (int)splits;  // trailing splits may be empty: they store zeros
-  return b;
+  b->tiles_m = (M + b->mb - 1) / b->mb;
+  b->tiles_n = (N + b->nb - 1) / b->nb;
 }
 
+int tn_splits(int64_t K, int64_t chunk) { return (int)std::max<int64_t>(1, (K + chunk - 1) / chunk); }
+
 template <int MB, int NB>
-void launch_tn(const TnArgs &a, const TnReduce &r, hipStream_t s) {
-  gemm_tn_kernel<MB, NB><<<(unsigned)(r.nt * a.splits), 256, 0, s>>>(a);
-  const unsigned blocks = (unsigned)(r.nt * (MB * NB / 256));
-  if (a.splits > 32) gemm_tn_reduce_kernel<MB, NB, 16><<<blocks, 1024, 0, s>>>(r);
-  else gemm_tn_reduce_kernel<MB, NB, 4><<<blocks, 256, 0, s>>>(r);
+void launch_tn(const TnJobs &jobs, unsigned blocks, hipStream_t s) {
+  gemm_tn_kernel<MB, NB><<<blocks, 256, 0, s>>>(jobs);
 }
 
 }  // namespace
 
-size_t gemm_tn_partials(int32_t M, int32_t N, int32_t K) {
-  const TnPlan b = tn_plan(M, N, K);
-  return (size_t)b.splits * b.tiles_m * b.tiles_n * b.mb * b.nb;
+size_t gemm_tn_partials(int32_t M, int32_t N, int32_t K, int32_t K_other) {
+  TnPlan b;
+  tn_tiles(M, N, std::max(K, K_other), &b);
+  const int64_t nt = (int64_t)b.tiles_m * b.tiles_n;
+  const int64_t splits = std::min<int64_t>(std::max<int64_t>(1, kTnBlocks / nt), tn_splits(K, kTnMinRows));
+  return (size_t)(splits * nt * b.mb * b.nb);
 }
 
-hipError_t gemm_tn(const TnGemm &g, hipStream_t s) {
-  if (g.M <= 0 || g.N <= 0) return hipSuccess;
-  const TnPlan b = tn_plan(g.M, g.N, g.K);
-  TnArgs a{g.A, g.A2, g.B, g.M, g.N, g.K, g.a_split, g.A2 ? g.a_split : g.M, g.k_dev, g.partials, b.tiles_m, b.tiles_n, b.splits};
-  TnReduce r{g.partials, g.C, g.lr > 0.f ? g.W : nullptr, g.lr, g.M, g.N, b.tiles_n, b.tiles_m * b.tiles_n, b.splits, g.accumulate};
-#define BNS_TN(MB_, NB_) if (b.mb == MB_ && b.nb == NB_) launch_tn<MB_, NB_>(a, r, s)
-  BNS_TN(128, 128); BNS_TN(128, 96); BNS_TN(128, 64); BNS_TN(128, 32);
-  BNS_TN(64, 128); BNS_TN(64, 96); BNS_TN(64, 64); BNS_TN(64, 32);
+hipError_t gemm_tn(const TnGemm *g, int32_t n, const TnLoss &loss, hipStream_t s) {
+  if (n > kMaxTnJobs) return hipErrorInvalidValue;
+  TnPlan plan[kMaxTnJobs];
+  int64_t depth[kMaxTnJobs];
+  for (int i = 0; i < n; ++i) {
+    if (g[i].accumulate) plan[i] = plan[i - 1];  // the two parts of one gradient have the same result tiles
+    else tn_tiles(g[i].M, g[i].N, std::max<int64_t>(g[i].K, i + 1 < n && g[i + 1].accumulate ? g[i + 1].K : 0), &plan[i]);
+    // a depth on the device is usually a fraction of its bound: price it at a quarter
+    depth[i] = g[i].k_dev ? (g[i].K + 3) / 4 : g[i].K;
+  }
+  // A job that fills the chip with chunks of kTnAlone rows or more gets a launch of its own, its splits dealt
+  // evenly over the XCDs.  The smaller jobs of one tile shape share a launch and the length of a chunk: the
+  // smallest with which their workgroups are one resident round, so that all of them end together.
+  bool alone[kMaxTnJobs];
+  for (int i = 0; i < n; ++i) {
+    const int64_t nt = (int64_t)plan[i].tiles_m * plan[i].tiles_n;
+    int64_t splits = std::max<int64_t>(1, kTnBlocks / nt);
+    if (splits >= 8) splits = splits / 8 * 8;
+    alone[i] = depth[i] / splits >= kTnAlone;
+    if (alone[i]) plan[i].splits = (int)splits;
+  }
+  auto same = [&](int i, int k) { return !alone[k] && !alone[i] && plan[k].mb == plan[i].mb && plan[k].nb == plan[i].nb; };
+  for (int i = 0; i < n; ++i) {
+    if (alone[i]) continue;
+    auto blocks = [&](int64_t chunk) {
+      int64_t b = 0;
+      for (int k = 0; k < n; ++k)
+        if (same(i, k)) b += (int64_t)plan[k].tiles_m * plan[k].tiles_n * tn_splits(depth[k], chunk);
+      return b;
+    };
+    int64_t lo = kTnMinRows, hi = (int64_t)1 << 31;  // blocks(hi): one split each
+    while (lo < hi) {
+      const int64_t mid = (lo + hi) / 2;
+      if (blocks(mid) <= kTnBlocks) hi = mid; else lo = mid + 1;
+    }
+    plan[i].splits = tn_splits(depth[i], lo);
+  }
+  TnSums sums{};
+  for (int i = 0; i < n; ++i) {
+    const int nt = plan[i].tiles_m * plan[i].tiles_n;
+    if (g[i].accumulate) {
+      TnSum &t = sums.j[sums.n - 1];
+      t.partials2 = g[i].partials;
+      t.splits2 = plan[i].splits;
+      continue;
+    }
+    TnSum &t = sums.j[sums.n++];
+    t = TnSum{g[i].partials, nullptr, g[i].C, g[i].lr > 0.f ? g[i].W : nullptr, g[i].M, g[i].N, plan[i].mb / 32, plan[i].nb / 32,
+              plan[i].tiles_n, nt, plan[i].splits, 0, sums.blocks};
+    if (g[i].lr > 0.f) sums.lr = g[i].lr;
+    sums.blocks += nt * (plan[i].mb * plan[i].nb / 256);
+  }
+  bool done[kMaxTnJobs] = {};
+  for (int i = 0; i < n; ++i) {
+    if (done[i]) continue;
+    TnJobs jobs{};
+    int blocks = 0;
+    for (int k = i; k < n; ++k) {
+      if (k != i && (done[k] || !same(i, k))) continue;
+      done[k] = true;
+      const int nt = plan[k].tiles_m * plan[k].tiles_n;
+      jobs.j[jobs.n++] = TnJob{g[k].A, g[k].A2, g[k].B, g[k].rows, g[k].k_dev, g[k].partials, g[k].M, g[k].N, g[k].K, g[k].a_split,
+                               g[k].A2 ? g[k].a_split : g[k].M, plan[k].tiles_n, nt, plan[k].splits, blocks};
+      blocks += nt * ((plan[k].splits + 7) / 8 * 8);  // every job starts on XCD 0
+    }
+#define BNS_TN(MB_, NB_) if (plan[i].mb == MB_ && plan[i].nb == NB_) launch_tn<MB_, NB_>(jobs, (unsigned)blocks, s)
+    BNS_TN(128, 128); BNS_TN(128, 96); BNS_TN(128, 64); BNS_TN(128, 32);
+    BNS_TN(64, 128); BNS_TN(64, 96); BNS_TN(64, 64); BNS_TN(64, 32);
 #undef BNS_TN
+  }
+  bool many = false;
+  for (int i = 0; i < sums.n; ++i) many |= std::max(sums.j[i].splits, sums.j[i].splits2) > 32;
+  sums.loss_partials = loss.partials;
+  sums.n_loss = loss.n;
+  sums.loss = loss.out;
+  const unsigned blocks = (unsigned)(sums.blocks + (loss.out ? 1 : 0));
+  if (blocks == 0) return hipSuccess;
+  if (many) gemm_tn_reduce_kernel<16><<<blocks, 1024, 0, s>>>(sums);
+  else gemm_tn_reduce_kernel<4><<<blocks, 256, 0, s>>>(sums);
   return hipGetLastError();
 }
 

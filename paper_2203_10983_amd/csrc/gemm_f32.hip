@@ -28,7 +28,7 @@ struct F32Args {
   int T, S, nblk;  // column tiles of 32, depth steps of 32, column blocks
 };
 
-template <int NC, bool ACC>
+template <int NC, bool ACC, bool REC>
 __global__ void __launch_bounds__(256, 4) gemm_rows_f32_kernel(const F32Args a) {
   constexpr int kRows = 128;
   __shared__ __attribute__((aligned(16))) char Bs[2][NC * kF32Step];
@@ -49,8 +49,14 @@ __global__ void __launch_bounds__(256, 4) gemm_rows_f32_kernel(const F32Args a) 
 
   f32x4 ar[4];
   const float *row_a, *row_a2;
+  float row_scale = 1.f;  // REC: of the row whose values ar holds
   auto set_rows = [&](int tl) {
-    const int row = min(M - 1, tl * kRows + wid * 32 + l32);  // rows past the end are not stored
+    int row = min(M - 1, tl * kRows + wid * 32 + l32);  // rows past the end are not stored
+    if constexpr (REC) {
+      const int2 r = p.rec[row];
+      row = r.x;
+      row_scale = __int_as_float(r.y);
+    }
     row_a = p.A + (size_t)row * p.lda;
     row_a2 = two ? p.A2 + (size_t)row * p.lda - p.a_split : nullptr;
   };
@@ -93,6 +99,12 @@ __global__ void __launch_bounds__(256, 4) gemm_rows_f32_kernel(const F32Args a) 
   for (int s = 0;;) {
     lds_dma_wait();
     __syncthreads();  // this step's weights are in LDS, and everybody is done with the other buffer
+    if constexpr (REC) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) ar[j][e] *= row_scale;
+    }
     // depths 8 j + 4 hi + 0..3 -> pairs (8 j + 2 i, 8 j + 2 i + 1) in the two halves
     float op[4][4];
 #pragma unroll
@@ -170,7 +182,8 @@ __global__ void __launch_bounds__(256, 4) gemm_rows_f32_kernel(const F32Args a) 
 
 hipError_t gemm_rows_f32(const RowsF32 &g, hipStream_t s) {
   if (g.M <= 0 || g.N <= 0) return hipSuccess;
-  if (g.ldc < g.N || (g.pad && (g.ldc > (g.N + 3) / 4 * 4 || g.relu || g.accumulate)) || (g.A2 && g.a_split % 16 != 0))
+  if (g.ldc < g.N || (g.pad && (g.ldc > (g.N + 3) / 4 * 4 || g.relu || g.accumulate)) || (g.A2 && g.a_split % 16 != 0) ||
+      (g.rec && (g.A2 || g.accumulate)))
     return hipErrorInvalidValue;
   F32Args a;
   a.g = g;
@@ -186,8 +199,9 @@ hipError_t gemm_rows_f32(const RowsF32 &g, hipStream_t s) {
   const unsigned grid = (unsigned)(octets * 8 * a.nblk);
 #define BNS_ROWS_F32(NC)                                                          \
   do {                                                                          \
-    if (g.accumulate) gemm_rows_f32_kernel<NC, true><<<grid, 256, 0, s>>>(a);   \
-    else gemm_rows_f32_kernel<NC, false><<<grid, 256, 0, s>>>(a);               \
+    if (g.accumulate) gemm_rows_f32_kernel<NC, true, false><<<grid, 256, 0, s>>>(a); \
+    else if (g.rec) gemm_rows_f32_kernel<NC, false, true><<<grid, 256, 0, s>>>(a);   \
+    else gemm_rows_f32_kernel<NC, false, false><<<grid, 256, 0, s>>>(a);             \
   } while (0)
   switch (nc) {
     case 1: BNS_ROWS_F32(1); break;

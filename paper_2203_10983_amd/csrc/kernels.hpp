@@ -17,16 +17,41 @@ hipError_t scan_exclusive_i32(const int32_t *in, int32_t *out, int64_t n_max, co
                               int32_t *tile_sums, int32_t *total_out, int32_t add_base,
                               hipStream_t s);
 
+// ---- packed weights (gemm.hip, pack_device.hpp) ------------------------------------------------
+// A weight matrix laid out for the products of Eq. 2 and its backward: operand fragments in the order they are read.  split: W [N, K],
+// transposed and cut into bf16 pieces, for gemm_rows (packed_bytes(K, N)); else W [K, N] for gemm_rows_f32
+// (packed_bytes_f32(K, N)).  out is 16-byte aligned.
+struct PackJob {
+  const float *W;
+  void *out;
+  int32_t K, N;
+  bool split;
+};
+constexpr int kMaxPackJobs = 16;
+struct PackJobs {
+  PackJob j[kMaxPackJobs];
+  int32_t n = 0, units = 0;  // jobs; wavefronts' worth of work in them
+};
+__host__ __device__ inline int32_t pack_units(const PackJob &j) {
+  return ((j.K + 31) / 32) * (j.split ? (j.N + 15) / 16 : (j.N + 31) / 32);
+}
+size_t packed_bytes(int32_t K, int32_t N);
+size_t packed_bytes_f32(int32_t K, int32_t N);
+hipError_t pack_weights(const PackJobs &jobs, hipStream_t s);
+
 // ---- sample.hip (Algorithm 1, selection step) -------------------------------------------------
 // ballots: scratch uint64[ceil(B/64)]; tile_sums: scratch int32[2 * scan_tiles(B) + 1] (half of it
 // without kept_start).  epoch_dev (nullable): the epoch index is read from device memory instead of
 // `epoch`.  halo_ptr + kept_start (both nullable): kept_start[r] = first + the summed lengths
 // halo_ptr[b+1] - halo_ptr[b] of the kept nodes before the r-th one, r = 0..n_kept (int32[B+1]): the
 // row starts of the kept nodes in the transposed subgraph, which build_transposed_csr reads.
+// rec (nullable): rec[r] = (kept_ids[r], s_halo * dis_halo[kept_ids[r]]), as halo_records writes it.
+// pack (nullable): weights to pack in the same launch, on workgroups of their own.
 hipError_t sample_boundary(const int64_t *halo_gid, int32_t n_halo, uint64_t seed, uint32_t epoch,
                            const uint32_t *epoch_dev, uint32_t part_id, uint64_t threshold, uint64_t *ballots,
                            int32_t *tile_sums, int32_t *kept_ids, int32_t *remap, int32_t *n_kept,
-                           const int32_t *halo_ptr, int32_t first, int32_t *kept_start, hipStream_t s);
+                           const int32_t *halo_ptr, int32_t first, int32_t *kept_start, int2 *rec, const float *dis_halo, float s_halo,
+                           const PackJobs *pack, hipStream_t s);
 
 // ---- build_csr.hip (Algorithm 1, subgraph step) -----------------------------------------------
 struct StaticSplit {       // inner / boundary split of the static CSR, built once
@@ -72,7 +97,8 @@ hipError_t sample_build_small(const int64_t *halo_gid, int32_t n_halo, uint64_t 
                               int32_t *kept_ids, int32_t *remap, int32_t *n_kept, int32_t *kept_start,
                               int32_t n_in, int64_t e_in, int64_t e_bd, const StaticSplit &sp, int32_t *kpos,
                               int32_t *row_ptr, int32_t *col_idx, int32_t *nnz, const int32_t *halo_ptr,
-                              const int32_t *halo_col, int32_t *t_row_ptr, int32_t *t_col_idx, hipStream_t s);
+                              const int32_t *halo_col, int32_t *t_row_ptr, int32_t *t_col_idx, int2 *rec, const float *dis_halo,
+                              float s_halo, const PackJobs *pack, hipStream_t s);
 
 struct Dropout;  // defined with the GEMMs below
 
@@ -98,10 +124,6 @@ inline int64_t seg_max_multi(int64_t nnz) { return nnz / kSegLen + 1; }
 hipError_t build_seg_plan(int32_t n_rows, int64_t nnz, const int32_t *row_ptr, SegPlan *plan, int32_t *tmp_a,
                           int32_t *tmp_b, int32_t *tile_sums, hipStream_t s);
 
-// Hu[r,:] = (s_halo * dis_halo[b]) * halo_h[b,:], b = kept_ids[r], r < *n_kept (dis_halo nullable = 1).
-hipError_t halo_gather(const float *halo_h, const int32_t *kept_ids, const int32_t *n_kept,
-                       int32_t n_halo, const float *dis_halo, float s_halo, int32_t d, float *Hu,
-                       hipStream_t s);
 // A[v,:] = row_scale[v] * ( init[v,:] + sum_{u<n_in in row v} w_col[u] H_in[u,:] + sum_{kept r in row v} Hu[r,:] )
 // w_col / row_scale nullable (= 1).  GCN layer: both = d~^-1/2; mean aggregator: w_col = null,
 // row_scale = 1/degree, skip_self.  plan: segmentation of the static local CSR; partials: scratch
@@ -118,8 +140,9 @@ struct SpmmRowPart {
 };
 // rec[r] = (kept_ids[r], s_halo * dis_halo[kept_ids[r]]) for r < *n_kept (dis_halo nullable = 1): what the
 // aggregate needs to read the kept boundary rows where they are instead of a gathered, scaled copy.
+// pack: weights to pack in the same launch.
 hipError_t halo_records(const int32_t *kept_ids, const int32_t *n_kept, int32_t n_halo, const float *dis_halo,
-                        float s_halo, int2 *rec, hipStream_t s);
+                        float s_halo, int2 *rec, const PackJobs &pack, hipStream_t s);
 hipError_t spmm_fwd(const SegPlan &plan, int32_t n_in, int32_t d, const int32_t *row_ptr,
                     const int32_t *col_idx, const float *w_col, const float *row_scale,
                     const float *H_in, const float *Hu, float *partials, float *A,
@@ -166,20 +189,6 @@ struct Dropout {
   uint32_t k0 = 0, k1 = 0, c2 = 0, epoch = 0;
   const uint32_t *epoch_dev = nullptr;  // nullable: the epoch index is read from device memory
 };
-// A weight matrix laid out for the products below: operand fragments in the order they are read.  split: W [N, K],
-// transposed and cut into bf16 pieces, for gemm_rows (packed_bytes(K, N)); else W [K, N] for gemm_rows_f32
-// (packed_bytes_f32(K, N)).  out is 16-byte aligned.
-struct PackJob {
-  const float *W;
-  void *out;
-  int32_t K, N;
-  bool split;
-};
-constexpr int kMaxPackJobs = 16;  // per launch
-size_t packed_bytes(int32_t K, int32_t N);
-size_t packed_bytes_f32(int32_t K, int32_t N);
-hipError_t pack_weights(const PackJob *jobs, int32_t n, hipStream_t s);
-
 // C[M,N] = [A | A2] B (+ the previous C if accumulate), B [K,N] packed; then, if relu, max(., 0) and dropout (when
 // drop.scale != 0).  A, A2 [M, lda]: the depth below a_split (a multiple of 16) is A's, the rest A2's (nullable).
 // pad: the columns N..ldc-1 are set to zero (ldc at most N rounded up to a multiple of 4; not with relu or
@@ -193,6 +202,7 @@ struct RowsF32 {
   int32_t ldc;
   bool relu, pad, accumulate;
   const int32_t *m_dev;
+  const int2 *rec;  // nullable: row r of A is row rec[r].x, times as_float(rec[r].y) (halo_records)
   Dropout drop;
 };
 hipError_t gemm_rows_f32(const RowsF32 &g, hipStream_t s);
@@ -215,33 +225,45 @@ hipError_t gemm_rows(const RowsGemm &g, hipStream_t s);
 // inv[i] = deg[i] > 1 ? 1 / (deg[i] - 1) : 0   (deg counts the self-loop)
 hipError_t degree_inverse(const int32_t *deg, int32_t n, float *inv, hipStream_t s);
 
-// C[M,N] = (C +) [A | A2]^T B with B [K,N] and A [K, M], or A, A2 [K, a_split] and [K, M - a_split] (both with row
-// stride a_split, M = 2 a_split).  The depth is split over the chip and summed in a fixed order; partials: scratch of
-// gemm_tn_partials(M, N, K) floats.  k_dev (nullable): depth on the device, *k_dev <= K.  lr > 0: also
-// W -= lr * C, the plain update of Algorithm 1.
+// C[M,N] = [A | A2]^T B with B [K,N] and A [K, M], or A, A2 [K, a_split] and [K, M - a_split] (both with row
+// stride a_split, M = 2 a_split); accumulate: adds to the C of the job before it instead (same M, N).  The depth is split
+// over the chip and summed in a fixed order; partials: scratch of
+// gemm_tn_partials(M, N, K, depth of the other part of the same gradient or 0) floats per job.  rows
+// (nullable, [K]): the rows of A are those.  k_dev (nullable): depth on the device, *k_dev <= K.  lr > 0: also
+// W -= lr * C, the plain update of Algorithm 1.  A batch of up to kMaxTnJobs jobs shares its launches; in the last of
+// them *loss.out (nullable) becomes the sum of loss.n partial losses.
 struct TnGemm {
   int32_t M, N, K;
   const float *A, *A2, *B;
   int32_t a_split;
+  const int32_t *rows;
   float *C, *partials;
   bool accumulate;
   const int32_t *k_dev;
   float *W;
   float lr;
 };
-size_t gemm_tn_partials(int32_t M, int32_t N, int32_t K);
-hipError_t gemm_tn(const TnGemm &g, hipStream_t s);
+struct TnLoss {
+  const float *partials = nullptr;
+  int32_t n = 0;
+  float *out = nullptr;
+};
+constexpr int kMaxTnJobs = 16;
+size_t gemm_tn_partials(int32_t M, int32_t N, int32_t K, int32_t K_other);
+hipError_t gemm_tn(const TnGemm *g, int32_t n, const TnLoss &loss, hipStream_t s);
 
 // ---- loss.hip (Algorithm 1, loss step) ---------------------------------------------------------
 constexpr int kLossBlocks = 8192;  // partials: scratch f32[kLossBlocks]
+// Leave *n_partials partial losses, which gemm_tn adds up.
 hipError_t loss_softmax_ce(int32_t n, int32_t C, const float *logits, const int32_t *labels,
-                           float *dZ, float *partials, float *loss, hipStream_t s);
+                           float *dZ, float *partials, int32_t *n_partials, hipStream_t s);
 hipError_t loss_sigmoid_bce(int32_t n, int32_t C, const float *logits, const uint8_t *labels,
-                            float *dZ, float *partials, float *loss, hipStream_t s);
+                            float *dZ, float *partials, int32_t *n_partials, hipStream_t s);
 // Dropout applied in place to H[n_rows, d] (for layers whose ReLU sits in the aggregate's store).
 hipError_t dropout_inplace(int32_t n_rows, int32_t d, float *H, const Dropout &drop, hipStream_t s);
-// out = scale * dH where H > 0 else 0
-hipError_t relu_mask(int64_t n, const float *dH, const float *H, float scale, float *out, hipStream_t s);
+// out = scale * dH where H > 0 else 0.  pack: weights to pack in the same launch.
+hipError_t relu_mask(int64_t n, const float *dH, const float *H, float scale, float *out, const PackJobs &pack,
+                     hipStream_t s);
 // Adam step t (1-based) on n weights; m, v are the caller's moment buffers.
 hipError_t adam_update(int64_t n, float *W, const float *dW, float *m, float *v, float lr, float b1,
                        float b2, float eps, int32_t t, hipStream_t s);

@@ -2,10 +2,12 @@
 // the backward pass and the Adam update.  The loss is reduced in a
 // fixed order (per wavefront, per block, then one block over the block partials): two runs give
 // the same bits.
+#include <algorithm>
 #include <cmath>
 
 #include "device_utils.hpp"
 #include "kernels.hpp"
+#include "pack_device.hpp"
 
 namespace bns {
 
@@ -22,21 +24,6 @@ __device__ __forceinline__ float block_sum_fixed(float x) {  // valid on thread 
     for (int w = 0; w < kT / kWave; ++w) s += part[w];
   __syncthreads();
   return s;
-}
-
-__global__ void __launch_bounds__(1024)
-final_sum_kernel(const float *__restrict__ partials, int n, float *__restrict__ out) {
-  __shared__ float part[1024 / kWave];
-  float x = 0.f;
-  for (int i = threadIdx.x; i < n; i += 1024) x += partials[i];
-  x = wave_sum(x);
-  if (lane_id() == 0) part[threadIdx.x / kWave] = x;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    float s = 0.f;
-    for (int w = 0; w < 1024 / kWave; ++w) s += part[w];
-    *out = s;
-  }
 }
 
 // softmax cross-entropy: one wavefront per node; loss_v = logsumexp(z_v) - z_v[y_v],
@@ -151,16 +138,19 @@ sigmoid_bce_kernel(int64_t total, const float *__restrict__ logits, const uint8_
 }
 
 hipError_t loss_softmax_ce(int32_t n, int32_t C, const float *logits, const int32_t *labels,
-                           float *dZ, float *partials, float *loss, hipStream_t s) {
-  softmax_ce_kernel<<<kLossBlocks, kT, 0, s>>>(n, C, logits, labels, dZ, partials);
-  final_sum_kernel<<<1, 1024, 0, s>>>(partials, kLossBlocks, loss);
+                           float *dZ, float *partials, int32_t *n_partials, hipStream_t s) {
+  // a wavefront per node, two nodes at a time; no more workgroups than there is work for
+  const int64_t blocks = std::min<int64_t>(kLossBlocks, ((int64_t)n + 7) / 8);
+  softmax_ce_kernel<<<(unsigned)blocks, kT, 0, s>>>(n, C, logits, labels, dZ, partials);
+  *n_partials = (int32_t)blocks;
   return hipGetLastError();
 }
 
 hipError_t loss_sigmoid_bce(int32_t n, int32_t C, const float *logits, const uint8_t *labels,
-                            float *dZ, float *partials, float *loss, hipStream_t s) {
-  sigmoid_bce_kernel<<<kLossBlocks, kT, 0, s>>>((int64_t)n * C, logits, labels, dZ, partials);
-  final_sum_kernel<<<1, 1024, 0, s>>>(partials, kLossBlocks, loss);
+                            float *dZ, float *partials, int32_t *n_partials, hipStream_t s) {
+  const int64_t total = (int64_t)n * C, blocks = std::min<int64_t>(kLossBlocks, (total + kT - 1) / kT);
+  sigmoid_bce_kernel<<<(unsigned)blocks, kT, 0, s>>>(total, logits, labels, dZ, partials);
+  *n_partials = (int32_t)blocks;
   return hipGetLastError();
 }
 
@@ -184,17 +174,23 @@ hipError_t dropout_inplace(int32_t n_rows, int32_t d, float *H, const Dropout &d
 
 __global__ void __launch_bounds__(kT)
 relu_mask_kernel(int64_t n, const float *__restrict__ dH, const float *__restrict__ H, float scale,
-                 float *__restrict__ out) {
-  const int64_t stride = (int64_t)gridDim.x * kT;
+                 float *__restrict__ out, int blocks, const PackJobs pack) {
+  if ((int)blockIdx.x >= blocks) {
+    pack_unit(pack, (blockIdx.x - blocks) * (kT / kWave) + threadIdx.x / kWave);
+    return;
+  }
+  const int64_t stride = (int64_t)blocks * kT;
   for (int64_t i = (int64_t)blockIdx.x * kT + threadIdx.x; i < n; i += stride)
     out[i] = H[i] > 0.f ? dH[i] * scale : 0.f;
 }
 
-hipError_t relu_mask(int64_t n, const float *dH, const float *H, float scale, float *out, hipStream_t s) {
+hipError_t relu_mask(int64_t n, const float *dH, const float *H, float scale, float *out, const PackJobs &pack,
+                     hipStream_t s) {
   if (n <= 0) return hipSuccess;
   int64_t blocks = (n + kT * 4 - 1) / (kT * 4);
   if (blocks > 65536) blocks = 65536;
-  relu_mask_kernel<<<(unsigned)blocks, kT, 0, s>>>(n, dH, H, scale, out);
+  const int pack_blocks = (pack.units + kT / kWave - 1) / (kT / kWave);
+  relu_mask_kernel<<<(unsigned)(blocks + pack_blocks), kT, 0, s>>>(n, dH, H, scale, out, (int)blocks, pack);
   return hipGetLastError();
 }
 

@@ -4,6 +4,7 @@
 // ascending order with wavefront ballots and prefix sums.
 #include "device_utils.hpp"
 #include "kernels.hpp"
+#include "pack_device.hpp"
 
 namespace bns {
 
@@ -27,7 +28,11 @@ __global__ void __launch_bounds__(kSampleThreads)
 sample_flags_kernel(const int64_t *__restrict__ halo_gid, int32_t n_halo, uint32_t k0, uint32_t k1,
                     uint32_t epoch, const uint32_t *__restrict__ epoch_dev, uint32_t part_id,
                     uint64_t threshold, const int32_t *__restrict__ halo_ptr, uint64_t *__restrict__ ballots,
-                    int32_t *__restrict__ tile_sums) {
+                    int32_t *__restrict__ tile_sums, int tiles, const PackJobs pack) {
+  if ((int)blockIdx.x >= tiles) {
+    pack_unit(pack, (blockIdx.x - tiles) * (kSampleThreads / kWave) + threadIdx.x / kWave);
+    return;
+  }
   if (epoch_dev) epoch = *epoch_dev;  // epoch counter kept on the device (graph replay)
   const int lane = lane_id();
   int cnt = 0, len = 0;
@@ -62,7 +67,7 @@ sample_flags_kernel(const int64_t *__restrict__ halo_gid, int32_t n_halo, uint32
       len_total += red[1][w];
     }
     tile_sums[blockIdx.x] = total;
-    if (halo_ptr) tile_sums[gridDim.x + blockIdx.x] = len_total;
+    if (halo_ptr) tile_sums[tiles + blockIdx.x] = len_total;
   }
 }
 
@@ -71,13 +76,15 @@ sample_flags_kernel(const int64_t *__restrict__ halo_gid, int32_t n_halo, uint32
 // nodes are first compacted into LDS in rank order; the block then walks the ranks, so that
 // kept_ids is written with consecutive addresses and (with halo_ptr) the start of each kept node's
 // row in the transposed subgraph, first + the list lengths of the kept nodes before it, comes from a
-// block scan over just the kept ones: kept_start[rank], and kept_start[n_kept] = the end.
+// block scan over just the kept ones: kept_start[rank], and kept_start[n_kept] = the end.  With rec, the
+// record that the forward aggregates read per kept node (its boundary index and weight) goes with it.
 // Block 0 also writes the totals.
 __global__ void __launch_bounds__(kSampleThreads)
 sample_write_kernel(int32_t n_halo, const uint64_t *__restrict__ ballots,
                     const int32_t *__restrict__ tile_counts, int32_t *__restrict__ kept_ids,
                     int32_t *__restrict__ remap, int32_t *__restrict__ n_kept,
-                    const int32_t *__restrict__ halo_ptr, int32_t first, int32_t *__restrict__ kept_start) {
+                    const int32_t *__restrict__ halo_ptr, int32_t first, int32_t *__restrict__ kept_start,
+                    int2 *__restrict__ rec, const float *__restrict__ dis_halo, float s_halo) {
   __shared__ int word_prefix[kWordsPerTile + 1];
   __shared__ int kept_b[kScanTile];
   const int lane = lane_id();
@@ -121,7 +128,10 @@ sample_write_kernel(int32_t n_halo, const uint64_t *__restrict__ ballots,
   for (int r0 = 0; r0 < tile_kept; r0 += kSampleThreads) {  // block-uniform trip count
     const int r = r0 + threadIdx.x;
     const int b = r < tile_kept ? kept_b[r] : -1;
-    if (b >= 0) kept_ids[base + r] = b;
+    if (b >= 0) {
+      kept_ids[base + r] = b;
+      if (rec) rec[base + r] = make_int2(b, __float_as_int(dis_halo ? s_halo * dis_halo[b] : s_halo));
+    }
     if (halo_ptr) {
       const int len = b >= 0 ? halo_ptr[b + 1] - halo_ptr[b] : 0;
       int sum;
@@ -135,16 +145,19 @@ sample_write_kernel(int32_t n_halo, const uint64_t *__restrict__ ballots,
 hipError_t sample_boundary(const int64_t *halo_gid, int32_t n_halo, uint64_t seed, uint32_t epoch,
                            const uint32_t *epoch_dev, uint32_t part_id, uint64_t threshold, uint64_t *ballots,
                            int32_t *tile_sums, int32_t *kept_ids, int32_t *remap, int32_t *n_kept,
-                           const int32_t *halo_ptr, int32_t first, int32_t *kept_start, hipStream_t s) {
+                           const int32_t *halo_ptr, int32_t first, int32_t *kept_start, int2 *rec, const float *dis_halo, float s_halo,
+                           const PackJobs *pack, hipStream_t s) {
   if (!kept_start) halo_ptr = nullptr;
   const int nb = scan_tiles(n_halo) > 0 ? scan_tiles(n_halo) : 1;
-  sample_flags_kernel<<<nb, kSampleThreads, 0, s>>>(halo_gid, n_halo, (uint32_t)seed,
+  const PackJobs jobs = pack ? *pack : PackJobs{};
+  const int pack_blocks = (jobs.units + kSampleThreads / kWave - 1) / (kSampleThreads / kWave);
+  sample_flags_kernel<<<nb + pack_blocks, kSampleThreads, 0, s>>>(halo_gid, n_halo, (uint32_t)seed,
                                                     (uint32_t)(seed >> 32), epoch, epoch_dev, part_id,
-                                                    threshold, halo_ptr, ballots, tile_sums);
+                                                    threshold, halo_ptr, ballots, tile_sums, nb, jobs);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   sample_write_kernel<<<nb, kSampleThreads, 0, s>>>(n_halo, ballots, tile_sums, kept_ids, remap, n_kept,
-                                                    halo_ptr, first, kept_start);
+                                                    halo_ptr, first, kept_start, rec, dis_halo, s_halo);
   return hipGetLastError();
 }
 

@@ -9,6 +9,7 @@
 // Every output is an integer array with a unique value: both paths write the same bits.
 #include "device_utils.hpp"
 #include "kernels.hpp"
+#include "pack_device.hpp"
 
 namespace bns {
 
@@ -34,9 +35,17 @@ struct SmallArgs {
   // transposed rows of the kept nodes
   const int32_t *halo_ptr, *halo_col;
   int32_t *t_tail_ptr, *t_col_idx;
+  int2 *rec;  // per kept node: boundary index, weight
+  const float *dis_halo;
+  float s_halo;
 };
 
-__global__ void __launch_bounds__(kSmallThreads) sample_build_small_kernel(const SmallArgs a) {
+// Workgroup 0 does all of it; the others pack weights.
+__global__ void __launch_bounds__(kSmallThreads) sample_build_small_kernel(const SmallArgs a, const PackJobs pack) {
+  if (blockIdx.x > 0) {
+    pack_unit(pack, (blockIdx.x - 1) * (kSmallThreads / kWave) + threadIdx.x / kWave);
+    return;
+  }
   __shared__ uint64_t words[kSmallWords];      // keep bits, one word per 64 boundary nodes
   __shared__ int word_prefix[kSmallWords + 1];  // kept nodes before each word; [n_words] = all
   __shared__ int kept_b[kSmallMaxHalo];         // the kept list
@@ -84,6 +93,7 @@ __global__ void __launch_bounds__(kSmallThreads) sample_build_small_kernel(const
       const int r = rank_of(b);
       kept_b[r] = b;
       a.kept_ids[r] = b;
+      a.rec[r] = make_int2(b, __float_as_int(a.dis_halo ? a.s_halo * a.dis_halo[b] : a.s_halo));
       a.remap[b] = r;
     } else {
       a.remap[b] = -1;
@@ -165,7 +175,8 @@ hipError_t sample_build_small(const int64_t *halo_gid, int32_t n_halo, uint64_t 
                               int32_t *kept_ids, int32_t *remap, int32_t *n_kept, int32_t *kept_start,
                               int32_t n_in, int64_t e_in, int64_t e_bd, const StaticSplit &sp, int32_t *kpos,
                               int32_t *row_ptr, int32_t *col_idx, int32_t *nnz, const int32_t *halo_ptr,
-                              const int32_t *halo_col, int32_t *t_row_ptr, int32_t *t_col_idx, hipStream_t s) {
+                              const int32_t *halo_col, int32_t *t_row_ptr, int32_t *t_col_idx, int2 *rec, const float *dis_halo,
+                              float s_halo, const PackJobs *pack, hipStream_t s) {
   if (!sample_build_small_fits(n_in, n_halo, e_in, e_bd)) return hipErrorInvalidValue;
   SmallArgs a;
   a.halo_gid = halo_gid;
@@ -193,7 +204,12 @@ hipError_t sample_build_small(const int64_t *halo_gid, int32_t n_halo, uint64_t 
   a.halo_col = halo_col;
   a.t_tail_ptr = t_row_ptr + n_in;
   a.t_col_idx = t_col_idx;
-  sample_build_small_kernel<<<1, kSmallThreads, 0, s>>>(a);
+  a.rec = rec;
+  a.dis_halo = dis_halo;
+  a.s_halo = s_halo;
+  const PackJobs jobs = pack ? *pack : PackJobs{};
+  const int pack_blocks = (jobs.units + kSmallThreads / kWave - 1) / (kSmallThreads / kWave);
+  sample_build_small_kernel<<<1 + pack_blocks, kSmallThreads, 0, s>>>(a, jobs);
   return hipGetLastError();
 }
 

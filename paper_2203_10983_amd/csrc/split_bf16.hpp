@@ -56,30 +56,18 @@ __device__ __forceinline__ Frag3 split8(const f32x4 &a_in, const f32x4 &b_in) {
   return f;
 }
 
-// acc[r] += x . y[r] for R second operands.  The six partial products of a step are summed from zero,
-// smallest first, and one fp32 addition takes them to the accumulator: the instruction cuts off what an
-// addend has below the accumulator's last bit (downwards: a bias), which is harmless at the size of
-// one step's sum and would not be at the size of a long running one.  sign = -1 takes a step whose first
-// (or second) operand is negated: alternating it makes what is left of that bias cancel.  Two second operands at a time: their chains alternate, and few registers are held.
+// acc[r] += x . y[r] for R second operands, smallest partial products first; the accumulators are taken in
+// turn so that consecutive instructions do not wait for each other.  The instruction cuts off what an addend has below
+// the accumulator's last bit, downwards.  So that these cuts do not add up to a bias, half of the sums run on a
+// negated operand and are negated at the end: every other column tile of gemm_rows, every other split of gemm_tn.
 template <int R>
-__device__ __forceinline__ void mfma_split(f32x4 (&acc)[R], const Frag3 &x, const Frag3 (&y)[R], float sign = 1.f) {
+__device__ __forceinline__ void mfma_split(f32x4 (&acc)[R], const Frag3 &x, const Frag3 (&y)[R]) {
   constexpr int px[6] = {0, 2, 1, 0, 1, 0}, py[6] = {2, 0, 1, 1, 0, 0};
-  constexpr int P = R > 1 ? 2 : 1;
 #pragma unroll
-  for (int r0 = 0; r0 < R; r0 += P) {
-    f32x4 t[P];
+  for (int i = 0; i < 6; ++i)
 #pragma unroll
-    for (int r = 0; r < P; ++r) t[r] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int i = 0; i < 6; ++i)
-#pragma unroll
-      for (int r = 0; r < P; ++r)
-        t[r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x.p[px[i]], y[r0 + r].p[py[i]], t[r], 0, 0, 0);
-#pragma unroll
-    for (int r = 0; r < P; ++r)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) acc[r0 + r][e] = fmaf(t[r][e], sign, acc[r0 + r][e]);
-  }
+    for (int r = 0; r < R; ++r)
+      acc[r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x.p[px[i]], y[r].p[py[i]], acc[r], 0, 0, 0);
 }
 
 // One 16-byte-per-lane copy from global memory straight into LDS (lane i lands at lds + 16 i; both

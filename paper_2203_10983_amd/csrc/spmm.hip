@@ -14,6 +14,7 @@
 // and handed to the loop by cross-lane reads, four neighbours in flight per step.
 #include <algorithm>
 
+#include "pack_device.hpp"
 #include "spmm_device.hpp"
 
 namespace bns {
@@ -318,82 +319,30 @@ hipError_t pad_rows(int32_t n_rows, int32_t d, int32_t ld, const float *src, flo
 }
 
 // ------------------------------------------------------------------------------------------
-// Stand-in for "receive H_U" (Algorithm 1, feature exchange): gather the kept rows of the
-// preloaded boundary features, scaled by S_uu = 1/p and by d~_u^-1/2 so that the aggregate
-// adds them with weight one.
-template <int VEC>
-__global__ void __launch_bounds__(256)
-halo_gather_kernel(const float *__restrict__ halo_h, const int32_t *__restrict__ kept_ids,
-                   const int32_t *__restrict__ n_kept, const float *__restrict__ dis_halo,
-                   float s_halo, int32_t d, float *__restrict__ Hu) {
-  // one VEC-piece of one kept row per thread and step, consecutive threads on consecutive pieces
-  // (a wavefront covers 64 / (d / VEC) rows); four independent pieces in flight per thread
-  using V = typename Vec<VEC>::T;
-  constexpr int UNR = 4;
-  const unsigned nvec = (unsigned)(d / VEC);
-  const long long total = (long long)*n_kept * nvec;
-  const long long stride = (long long)gridDim.x * 256;
-  const bool small = total + stride * UNR < 0x7fffffffLL;  // 32-bit division suffices
-  for (long long t0 = (long long)blockIdx.x * 256 + threadIdx.x; t0 < total; t0 += stride * UNR) {
-    int b[UNR];
-    unsigned iv[UNR];
-    long long t[UNR];
-#pragma unroll
-    for (int u = 0; u < UNR; ++u) {
-      t[u] = t0 + u * stride;
-      const unsigned r = small ? (unsigned)t[u] / nvec : (unsigned)(t[u] / nvec);
-      iv[u] = (unsigned)(t[u] - (long long)r * nvec);
-      b[u] = t[u] < total ? kept_ids[r] : -1;
-    }
-    float sc[UNR];
-    V x[UNR];
-#pragma unroll
-    for (int u = 0; u < UNR; ++u) {
-      sc[u] = (b[u] >= 0 && dis_halo) ? s_halo * dis_halo[b[u]] : s_halo;
-      if (b[u] >= 0) x[u] = reinterpret_cast<const V *>(halo_h + (size_t)b[u] * d)[iv[u]];
-    }
-#pragma unroll
-    for (int u = 0; u < UNR; ++u) {
-      if (b[u] < 0) continue;
-      float *px = reinterpret_cast<float *>(&x[u]);
-#pragma unroll
-      for (int i = 0; i < VEC; ++i) px[i] *= sc[u];
-      reinterpret_cast<V *>(Hu)[t[u]] = x[u];   // row r, piece iv: Hu is dense, so the piece index is t
-    }
-  }
-}
-
+// Stand-in for "receive H_U" (Algorithm 1, feature exchange): the kept rows of the preloaded boundary
+// features are read where they are; a record per kept node says where, and with which weight
+// (S_uu = 1/p, times d~_u^-1/2 for the GCN layer).
 __global__ void __launch_bounds__(256)
 halo_records_kernel(const int32_t *__restrict__ kept_ids, const int32_t *__restrict__ n_kept,
-                    const float *__restrict__ dis_halo, float s_halo, int2 *__restrict__ rec) {
+                    const float *__restrict__ dis_halo, float s_halo, int2 *__restrict__ rec, int blocks,
+                    const PackJobs pack) {
+  if ((int)blockIdx.x >= blocks) {
+    pack_unit(pack, (blockIdx.x - blocks) * 4 + (threadIdx.x >> 6));
+    return;
+  }
   const int n = *n_kept;
-  for (int r = blockIdx.x * 256 + threadIdx.x; r < n; r += gridDim.x * 256) {
+  for (int r = blockIdx.x * 256 + threadIdx.x; r < n; r += blocks * 256) {
     const int b = kept_ids[r];
     rec[r] = make_int2(b, __float_as_int(dis_halo ? s_halo * dis_halo[b] : s_halo));
   }
 }
 
 hipError_t halo_records(const int32_t *kept_ids, const int32_t *n_kept, int32_t n_halo, const float *dis_halo,
-                        float s_halo, int2 *rec, hipStream_t s) {
-  if (n_halo <= 0) return hipSuccess;
-  const unsigned blocks = (unsigned)std::min<int64_t>(((int64_t)n_halo + 255) / 256, 2048);
-  halo_records_kernel<<<blocks, 256, 0, s>>>(kept_ids, n_kept, dis_halo, s_halo, rec);
-  return hipGetLastError();
-}
-
-hipError_t halo_gather(const float *halo_h, const int32_t *kept_ids, const int32_t *n_kept,
-                       int32_t n_halo, const float *dis_halo, float s_halo, int32_t d, float *Hu,
-                       hipStream_t s) {
-  if (n_halo <= 0) return hipSuccess;
-  const int vec = d % 4 == 0 ? 4 : d % 2 == 0 ? 2 : 1;
-  int64_t blocks = ((int64_t)n_halo * (d / vec) + 1023) / 1024;  // sized for every boundary node kept
-  if (blocks > 4096) blocks = 4096;
-  if (d % 4 == 0)
-    halo_gather_kernel<4><<<(unsigned)blocks, 256, 0, s>>>(halo_h, kept_ids, n_kept, dis_halo, s_halo, d, Hu);
-  else if (d % 2 == 0)
-    halo_gather_kernel<2><<<(unsigned)blocks, 256, 0, s>>>(halo_h, kept_ids, n_kept, dis_halo, s_halo, d, Hu);
-  else
-    halo_gather_kernel<1><<<(unsigned)blocks, 256, 0, s>>>(halo_h, kept_ids, n_kept, dis_halo, s_halo, d, Hu);
+                        float s_halo, int2 *rec, const PackJobs &pack, hipStream_t s) {
+  const int blocks = n_halo > 0 ? (int)std::min<int64_t>(((int64_t)n_halo + 255) / 256, 2048) : 0;
+  const unsigned grid = (unsigned)(blocks + (pack.units + 3) / 4);
+  if (grid == 0) return hipSuccess;
+  halo_records_kernel<<<grid, 256, 0, s>>>(kept_ids, n_kept, dis_halo, s_halo, rec, blocks, pack);
   return hipGetLastError();
 }
 
