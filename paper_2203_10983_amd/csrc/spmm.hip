@@ -22,7 +22,7 @@ namespace bns {
 // Measured on gfx950: the same code runs 3-6 % slower as soon as the wavefront needs more than 96
 // scalar registers (seven 16-register granules instead of six), so the budget is pinned.
 template <int VEC, int MAXCH, int LPR, bool NARROW = false>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_num_sgpr(96))) spmm_kernel(const SpmmArgs a) {
+__global__ void __launch_bounds__(256, MAXCH == 1 ? 8 : 1) __attribute__((amdgpu_num_sgpr(96))) spmm_kernel(const SpmmArgs a) {
   using V = typename Vec<VEC>::T;
   const int lane = lane_id();
   const int g = lane / LPR, sl = lane % LPR;
@@ -38,7 +38,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_num_sgpr(96))) spmm
   }
   // work units: the static segments, then one unit per kept boundary row (count on the device)
   const int n_units = a.multi_only ? a.plan.n_part : a.plan.n_seg + (a.n_extra_dev ? *a.n_extra_dev : 0);
-  for (int unit = bid * 4 + (threadIdx.x >> 6); unit < n_units; unit += nblk * 4) {
+  // (the unit is the same for the whole wavefront: its bounds then come through the scalar cache)
+  for (int unit = bid * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); unit < n_units; unit += nblk * 4) {
   int row, seg = 0, nseg = 1;
   if (a.multi_only) {  // units are the partial-sum slots, i.e. the segments of the long rows
     row = a.plan.part_row[unit];

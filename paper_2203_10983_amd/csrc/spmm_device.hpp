@@ -1,6 +1,8 @@
 // Device code shared by the aggregate kernels (Eq. 1 in the sampled matrix form of Appendix A):
 // argument block, the gather of one row segment, and the scale / mask / store of a finished row.
 #pragma once
+#include <type_traits>
+
 #include "device_utils.hpp"
 #include "kernels.hpp"
 
@@ -157,19 +159,90 @@ __device__ __forceinline__ void entry_source(const SpmmArgs &a, int row, int c, 
   }
 }
 
-// acc += sum over the cnt <= 64 entries held one per lane (address p_l, weight w_l) of
+// Rows of at most 64 floats sit in L2 more often than not, and then the three cross-lane reads per load (two address
+// halves and the weight, through the LDS pipe) bound the gather: that pipe was busy half of the time.  With 16 lanes
+// per row the broadcast inside a lane group is one DPP move instead (a plain vector instruction): 685 -> 651 us on
+// 32.9 M entries of 64 floats in L2, 228 -> 195 us for the padded 41-float rows of the same graph.  Rows of 32 lanes
+// come from beyond L2 and are bound by the fabric: there the DPP form only costs registers (569 -> 588 us on
+// 16.6 M entries), so they keep the cross-lane reads, as does the one-kernel layer.
+constexpr bool dpp_gather(int maxch, int lpr) { return maxch == 1 && lpr == 16; }
+
+// Which entry of a batch of 64 a lane fetches.  The wavefront walks EP = 64 / LPR entries per step, lane group g
+// entry EP t + g in step t; for the DPP form that entry is fetched by lane t of the group.
+template <int LPR, bool DPP>
+__device__ __forceinline__ int batch_entry() {
+  const int lane = lane_id();
+  return DPP ? (lane % LPR) * (kWave / LPR) + lane / LPR : lane;
+}
+
+// The value of lane T of every row of 16 lanes, on all lanes of the row.
+template <int T>
+__device__ __forceinline__ unsigned row_bcast(unsigned x) {
+  return (unsigned)__builtin_amdgcn_mov_dpp((int)x, 0x150 + T, 0xf, 0xf, true);  // row_newbcast:T
+}
+
+// 4 VEC bytes at an address that was put together from its halves.  The address space has to be said: the compiler
+// takes such a pointer for a generic one and makes a flat load of it, which also waits for the LDS pipe.
+template <typename V>
+__device__ __forceinline__ V load_row_piece(unsigned hi, unsigned lo, int at) {
+  using G = const __attribute__((address_space(1))) V;
+  typedef unsigned u2 __attribute__((ext_vector_type(2)));
+  return *reinterpret_cast<G *>(__builtin_bit_cast(unsigned long long, (u2){lo, hi}) + (unsigned)at * 4u);
+}
+
+struct Entries { unsigned lo, hi, w; };  // feature-row address and weight of one entry per lane
+
+// Steps T0 .. T0 + 7 of a batch.  MASKED: the batch ends among them.
+template <bool MASKED, int T0, typename V, int VEC>
+__device__ __forceinline__ void gather_steps(const Entries &e, int first, int ep, int cnt, int at, float (&acc)[1][VEC]) {
+  V v[8];
+  float w[8];
+  auto step = [&](auto tc) {
+    constexpr int t = decltype(tc)::value, T = T0 + t;
+    const unsigned hi = row_bcast<T>(e.hi), lo = row_bcast<T>(e.lo);
+    if (MASKED) {
+      v[t] = V{};
+      if (first + t * ep < cnt) v[t] = load_row_piece<V>(hi, lo, at);
+    } else {
+      v[t] = load_row_piece<V>(hi, lo, at);
+    }
+    w[t] = __uint_as_float(row_bcast<T>(e.w));  // lanes past the end carry weight zero
+  };
+  step(std::integral_constant<int, 0>{}); step(std::integral_constant<int, 1>{});
+  step(std::integral_constant<int, 2>{}); step(std::integral_constant<int, 3>{});
+  step(std::integral_constant<int, 4>{}); step(std::integral_constant<int, 5>{});
+  step(std::integral_constant<int, 6>{}); step(std::integral_constant<int, 7>{});
+#pragma unroll
+  for (int t = 0; t < 8; ++t) vec_fma<VEC>(acc[0], w[t], v[t]);
+}
+
+// acc += sum over the cnt <= 64 entries of a batch, held one per lane (batch_entry; address p_l, weight w_l), of
 // w * feature row.  The lanes span the feature dimension (VEC floats per lane, MAXCH pieces of 64
-// lanes); with LPR < 64 lanes per row the wavefront walks 64/LPR neighbours at once, four steps in
-// flight, and every lane group keeps its own partial sums (fold_groups adds them).
-template <int VEC, int MAXCH, int LPR>
+// lanes); with LPR < 64 lanes per row the wavefront walks 64/LPR neighbours at once, 4 or 8 loads in flight, and
+// every lane group keeps its own partial sums (fold_groups adds them).
+template <int VEC, int MAXCH, int LPR, bool DPP = false>
 __device__ __forceinline__ void gather_batch(unsigned long long p_l, float w_l, int cnt, int nvec,
                                              float (&acc)[MAXCH][VEC]) {
   using V = typename Vec<VEC>::T;
   constexpr int EP = kWave / LPR;  // neighbours walked at once
-  constexpr int UNR = (MAXCH == 1 && LPR >= 32) ? 8 : 4;
   const int lane = lane_id();
   const int g = lane / LPR, sl = lane % LPR;
   const unsigned p_lo = (unsigned)p_l, p_hi = (unsigned)(p_l >> 32);
+  if constexpr (DPP) {
+    static_assert(MAXCH == 1 && LPR == 16, "one DPP row of 16 lanes per feature row");
+    const int at = min(sl, nvec - 1) * VEC;  // lanes past the row's pieces repeat the last one and store nothing
+    const Entries e{p_lo, p_hi, __float_as_uint(w_l)};
+    auto chunk = [&](auto t0c) {  // steps T0 .. T0 + 7 of the batch's 16
+      constexpr int T0 = decltype(t0c)::value;
+      if (T0 * EP >= cnt) return;
+      if ((T0 + 8) * EP <= cnt) gather_steps<false, T0, V, VEC>(e, T0 * EP + g, EP, cnt, at, acc);
+      else gather_steps<true, T0, V, VEC>(e, T0 * EP + g, EP, cnt, at, acc);
+    };
+    chunk(std::integral_constant<int, 0>{});
+    chunk(std::integral_constant<int, 8>{});
+    return;
+  }
+  constexpr int UNR = (MAXCH == 1 && LPR >= 32) ? 8 : 4;
   for (int j = 0; j < cnt; j += UNR * EP) {
     V v[UNR][MAXCH];
     float w[UNR];
@@ -190,12 +263,11 @@ __device__ __forceinline__ void gather_batch(unsigned long long p_l, float w_l, 
         wt = __shfl(w_l, jj & (kWave - 1), kWave);
       }
       w[t] = valid ? wt : 0.f;
-      const V *src = reinterpret_cast<const V *>(((unsigned long long)hi << 32) | lo);
 #pragma unroll
       for (int c = 0; c < MAXCH; ++c) {
         const int iv = c * kWave + sl;
-        if (valid && iv < nvec) v[t][c] = src[iv];
-        else v[t][c] = V{};
+        v[t][c] = V{};
+                if (valid && iv < nvec) v[t][c] = load_row_piece<V>(hi, lo, iv * VEC);
       }
     }
 #pragma unroll
@@ -222,7 +294,6 @@ __device__ __forceinline__ void fold_groups(float (&acc)[MAXCH][VEC]) {
 template <int VEC, int MAXCH, int LPR>
 __device__ __forceinline__ void gather_segment(const SpmmArgs &a, int row, int e0, int e1, int d_off, int nvec,
                                                float (&acc)[MAXCH][VEC]) {
-  const int lane = lane_id();
 #pragma unroll
   for (int c = 0; c < MAXCH; ++c)
 #pragma unroll
@@ -232,8 +303,10 @@ __device__ __forceinline__ void gather_segment(const SpmmArgs &a, int row, int e
     // one neighbour per lane: its feature-row address and weight
     unsigned long long p_l = 0;
     float w_l = 0.f;
-    if (lane < cnt) entry_source(a, row, a.col_idx[base + lane], d_off, p_l, w_l);
-    gather_batch<VEC, MAXCH, LPR>(p_l, w_l, cnt, nvec, acc);
+    constexpr bool DPP = dpp_gather(MAXCH, LPR);
+    const int mine = batch_entry<LPR, DPP>();
+    if (mine < cnt) entry_source(a, row, a.col_idx[base + mine], d_off, p_l, w_l);
+    gather_batch<VEC, MAXCH, LPR, DPP>(p_l, w_l, cnt, nvec, acc);
   }
   fold_groups<VEC, MAXCH, LPR>(acc);
 }
