@@ -43,6 +43,8 @@ struct Layout {
   int32_t *kpos;
   float *Hu, *Hu2, *G0, *G1, *G2, *loss_partials;  // Hu, Hu2: boundary rows at the output width
   int2 *halo_rec;  // per kept boundary node: (boundary index, weight) for the aggregates that read the rows in place
+  // weight of every static entry with an inner column: forward (GCN only), transposed inner block, boundary nodes' lists
+  float *w_fwd, *w_bwd, *w_halo;
   float *inv_deg;            // 1 / (full-graph degree) of the inner nodes, for the mean aggregator
   SegPlan plan_f, plan_b;   // segmentation of the static CSR and of the transposed inner block
   int32_t *seg_tmp_a, *seg_tmp_b;
@@ -181,6 +183,9 @@ size_t carve(Carver &c, const bns_partition_desc *p, const bns_model_desc *m, La
   w.G1 = c.take<float>(n_in * d_max);
   w.G2 = c.take<float>(n_in * d_max);
   w.inv_deg = c.take<float>(n_in);
+  w.w_fwd = m->layer_kind == 0 ? c.take<float>(p->e_in) : nullptr;
+  w.w_bwd = c.take<float>(p->e_in);
+  w.w_halo = c.take<float>(p->e_bd);
   w.loss_partials = c.take<float>(kLossBlocks);
   for (int k = 0; k < 2; ++k) {
     SegPlan &pl = k == 0 ? w.plan_f : w.plan_b;
@@ -333,8 +338,8 @@ bns_status layer_fwd_impl(bns_ctx *ctx, int layer, double p, const float *H_in, 
       if (B > 0) BNS_TRY("gemm_rows_f32(boundary)", gemm_rows_f32(g, s));
     }
     PhaseTimer t(ctx, BNS_PHASE_SPMM_FWD, s);
-    BNS_TRY("spmm_fwd", spmm_fwd(ctx->ws.plan_f, n_in, ld, ctx->cur_row_ptr, ctx->cur_col_idx, ctx->ws.dis_in,
-                                 ctx->ws.dis_in, A_saved, ctx->ws.Hu2, ctx->ws.spmm_partials, H_out, SpmmRowPart{},
+    BNS_TRY("spmm_fwd", spmm_fwd(ctx->ws.plan_f, n_in, ld, ctx->cur_row_ptr, ctx->cur_col_idx, ctx->ws.w_fwd,
+                                 ctx->ws.split.inner_ptr, ctx->ws.dis_in, A_saved, ctx->ws.Hu2, ctx->ws.spmm_partials, H_out, SpmmRowPart{},
                                  false, relu, s, d_out));
     BNS_TRY("dropout_inplace", dropout_inplace(n_in, d_out, H_out, dropout_of(ctx, layer, relu), s));
     return BNS_OK;
@@ -357,25 +362,26 @@ bns_status layer_fwd_impl(bns_ctx *ctx, int layer, double p, const float *H_in, 
     part.row_skip = ctx->ws.split.n_inner;
     part.init = ctx->ws.C0;
   }
-  const float *w_col = sage ? nullptr : ctx->ws.dis_in;
+  const float *w_in = ctx->ws.w_fwd;
+  const int32_t *w_ptr = ctx->ws.split.inner_ptr;
   const float *row_scale = sage ? ctx->ws.inv_deg : ctx->ws.dis_in;
   if (one_kernel_layer(ctx->part, ctx->layer_kind, d_in, d_out)) {
     // aggregate and update in one kernel; the rows cut into several segments are finished first
     {
       PhaseTimer t(ctx, BNS_PHASE_SPMM_LONG, s);
-      BNS_TRY("spmm_fwd(long rows)", spmm_fwd(ctx->ws.plan_f, n_in, d_in, ctx->cur_row_ptr, ctx->cur_col_idx, w_col,
+      BNS_TRY("spmm_fwd(long rows)", spmm_fwd(ctx->ws.plan_f, n_in, d_in, ctx->cur_row_ptr, ctx->cur_col_idx, w_in, w_ptr,
                                               row_scale, H_in, halo_h, ctx->ws.spmm_partials, A_saved, part,
                                               true, false, s));
     }
     PhaseTimer t(ctx, BNS_PHASE_SPMM_FWD, s);
     BNS_TRY("spmm_gemm_fwd", spmm_gemm_fwd(ctx->ws.plan_f, n_in, d_in, d_out, ctx->cur_row_ptr, ctx->cur_col_idx,
-                                           w_col, row_scale, H_in, halo_h, ctx->ws.spmm_partials, A_saved,
+                                           w_in, w_ptr, row_scale, H_in, halo_h, ctx->ws.spmm_partials, A_saved,
                                            part, W, H_out, relu, dropout_of(ctx, layer, relu), s, sage));
     return BNS_OK;
   }
   {
     PhaseTimer t(ctx, BNS_PHASE_SPMM_FWD, s);
-    BNS_TRY("spmm_fwd", spmm_fwd(ctx->ws.plan_f, n_in, d_in, ctx->cur_row_ptr, ctx->cur_col_idx, w_col, row_scale,
+    BNS_TRY("spmm_fwd", spmm_fwd(ctx->ws.plan_f, n_in, d_in, ctx->cur_row_ptr, ctx->cur_col_idx, w_in, w_ptr, row_scale,
                                  H_in, halo_h, ctx->ws.spmm_partials, A_saved, part, false, false, s));
   }
   {
@@ -481,7 +487,8 @@ bns_status layer_bwd_impl(bns_ctx *ctx, int layer, double p, const float *dZ, co
         dZ_g = ctx->ws.G2;
       }
       BNS_TRY("spmm_bwd", spmm_bwd(ctx->ws.plan_b, n_in, B, ld, ctx->cur_t_row_ptr, ctx->cur_t_col_idx,
-                                   ctx->cur_kept, ctx->cur_n_kept, ctx->ws.dis_in, ctx->ws.dis_in, ctx->ws.dis_halo,
+                                   ctx->cur_kept, ctx->cur_n_kept, ctx->ws.w_bwd, ctx->ws.w_halo, ctx->part.halo_ptr, ctx->ws.dis_in,
+                                   ctx->ws.dis_halo,
                                    halo_scale(p), dZ_g, nullptr, nullptr, false, ctx->ws.spmm_partials, G_in, G_halo,
                                    s, d_out));
     }
@@ -515,7 +522,7 @@ bns_status layer_bwd_impl(bns_ctx *ctx, int layer, double p, const float *dZ, co
       // dH_in = (gradient through the node's own feature) + mean^T (gradient of the neighbour mean)
       PhaseTimer t(ctx, BNS_PHASE_SPMM_BWD, s);
       BNS_TRY("spmm_bwd", spmm_bwd(ctx->ws.plan_b, n_in, B, d_in, ctx->cur_t_row_ptr, ctx->cur_t_col_idx,
-                                   ctx->cur_kept, ctx->cur_n_kept, ctx->ws.inv_deg, nullptr, nullptr,
+                                   ctx->cur_kept, ctx->cur_n_kept, ctx->ws.w_bwd, ctx->ws.w_halo, ctx->part.halo_ptr, nullptr, nullptr,
                                    halo_scale(p) / ms, ctx->ws.G1, mask_src, ctx->ws.G2, true,
                                    ctx->ws.spmm_partials, dH_in, dhalo, s));
     }
@@ -534,7 +541,7 @@ bns_status layer_bwd_impl(bns_ctx *ctx, int layer, double p, const float *dZ, co
         dZ_g = ctx->ws.G2;
       }
       BNS_TRY("spmm_bwd", spmm_bwd(ctx->ws.plan_b, n_in, B, ld, ctx->cur_t_row_ptr, ctx->cur_t_col_idx,
-                                   ctx->cur_kept, ctx->cur_n_kept, ctx->ws.dis_in, ctx->ws.dis_in,
+                                   ctx->cur_kept, ctx->cur_n_kept, ctx->ws.w_bwd, ctx->ws.w_halo, ctx->part.halo_ptr, ctx->ws.dis_in,
                                    ctx->ws.dis_halo, halo_scale(p), dZ_g, nullptr, nullptr, false,
                                    ctx->ws.spmm_partials, G_in, G_halo, s, d_out));
     }
@@ -549,7 +556,7 @@ bns_status layer_bwd_impl(bns_ctx *ctx, int layer, double p, const float *dZ, co
     }
     PhaseTimer t(ctx, BNS_PHASE_SPMM_BWD, s);
     BNS_TRY("spmm_bwd", spmm_bwd(ctx->ws.plan_b, n_in, B, d_in, ctx->cur_t_row_ptr, ctx->cur_t_col_idx,
-                                 ctx->cur_kept, ctx->cur_n_kept, ctx->ws.dis_in, ctx->ws.dis_in,
+                                 ctx->cur_kept, ctx->cur_n_kept, ctx->ws.w_bwd, ctx->ws.w_halo, ctx->part.halo_ptr, ctx->ws.dis_in,
                                  ctx->ws.dis_halo, halo_scale(p) / ms, ctx->ws.G1, mask_src, nullptr, false,
                                  ctx->ws.spmm_partials, dH_in, dhalo, s));
   }
@@ -693,6 +700,10 @@ bns_status bns_create(bns_ctx **out, const bns_partition_desc *part, const bns_m
   BNS_TRY("degree_rsqrt(halo)", degree_rsqrt(part->deg_halo, part->n_halo, ctx->ws.dis_halo, s));
   BNS_TRY("build_static_split", build_static_split(part->n_in, part->row_ptr0, part->col0, ctx->ws.split,
                                                    ctx->ws.tile_sums, s));
+  const float *w_col = ctx->layer_kind == 1 ? ctx->ws.inv_deg : ctx->ws.dis_in;
+  if (ctx->ws.w_fwd) BNS_TRY("entry_weights(fwd)", entry_weights(part->e_in, ctx->ws.split.in_col, w_col, ctx->ws.w_fwd, s));
+  BNS_TRY("entry_weights(bwd)", entry_weights(part->e_in, part->t_in_col, w_col, ctx->ws.w_bwd, s));
+  BNS_TRY("entry_weights(halo)", entry_weights(part->e_bd, part->halo_col, w_col, ctx->ws.w_halo, s));
   BNS_TRY("build_seg_plan(fwd)", build_seg_plan(part->n_in, part->nnz0, part->row_ptr0, &ctx->ws.plan_f, ctx->ws.seg_tmp_a,
                                                  ctx->ws.seg_tmp_b, ctx->ws.tile_sums, s));
   BNS_TRY("build_seg_plan(bwd)", build_seg_plan(part->n_in, part->e_in, part->t_in_ptr, &ctx->ws.plan_b, ctx->ws.seg_tmp_a,
@@ -920,7 +931,7 @@ bns_status bns_cache_input_aggregate(bns_ctx *ctx, const float *X, void *stream)
   part.row_take = ctx->ws.split.n_inner;
   part.skip_self = sage;
   BNS_TRY("spmm_fwd(cache)", spmm_fwd(ctx->ws.plan_f, ctx->part.n_in, ctx->dims[0], ctx->part.row_ptr0,
-                                      ctx->part.col0, sage ? nullptr : ctx->ws.dis_in, nullptr, X, nullptr,
+                                      ctx->part.col0, ctx->ws.w_fwd, ctx->ws.split.inner_ptr, nullptr, X, nullptr,
                                       ctx->ws.spmm_partials, ctx->ws.C0, part, false, false, s));
   ctx->cache_X = X;
   return BNS_OK;

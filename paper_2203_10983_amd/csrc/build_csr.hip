@@ -85,6 +85,17 @@ hipError_t degree_rsqrt(const int32_t *deg, int32_t n, float *dis, hipStream_t s
   return hipGetLastError();
 }
 
+__global__ void __launch_bounds__(kThreads)
+entry_weights_kernel(int64_t n, const int32_t *__restrict__ col, const float *__restrict__ of, float *__restrict__ w) {
+  const int64_t j = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+  if (j < n) w[j] = of[col[j]];
+}
+
+hipError_t entry_weights(int64_t n, const int32_t *col, const float *of, float *w, hipStream_t s) {
+  if (n > 0) entry_weights_kernel<<<(unsigned)((n + kThreads - 1) / kThreads), kThreads, 0, s>>>(n, col, of, w);
+  return hipGetLastError();
+}
+
 hipError_t build_static_split(int32_t n_in, const int32_t *row_ptr0, const int32_t *col0,
                               const StaticSplit &sp, int32_t *tile_sums, hipStream_t s) {
   count_inner_kernel<<<(n_in + kThreads - 1) / kThreads, kThreads, 0, s>>>(n_in, row_ptr0, col0,

@@ -50,20 +50,22 @@ __global__ void __launch_bounds__(kFThreads, 6) __attribute__((amdgpu_num_sgpr(9
 
   // ---- phase 0: the tile's row bounds into LDS (one coalesced read instead of a dependent chain
   // per row).  s_e0/s_e1: entries to gather; s_e1 < 0 marks a row finished by the segmented pass.
-  __shared__ int s_e0[kFM], s_e1[kFM];
+  __shared__ int s_e0[kFM], s_e1[kFM], s_wd[kFM];  // s_wd: from an entry to its place in w_in
   __shared__ int next_row;
   if (threadIdx.x < kFM) {
     const int row = row0 + threadIdx.x;
-    int e0 = 0, e1 = 0;
+    int e0 = 0, e1 = 0, wd = 0;
     if (row < a.n_split) {
       e0 = a.row_ptr[row];
       e1 = a.row_ptr[row + 1];
+      if (a.w_in) wd = a.w_ptr[row] - e0;
       if (a.row_skip) e0 += a.row_skip[row];
       if (a.row_take) e1 = e0 + a.row_take[row];
       if (a.plan.seg_ptr[row + 1] - a.plan.seg_ptr[row] > 1) e1 = -1;
     }
     s_e0[threadIdx.x] = e0;
     s_e1[threadIdx.x] = e1;
+    s_wd[threadIdx.x] = wd;
   }
   if (threadIdx.x == 0) next_row = 0;
   __syncthreads();
@@ -86,19 +88,22 @@ __global__ void __launch_bounds__(kFThreads, 6) __attribute__((amdgpu_num_sgpr(9
     const int cnt = first_cnt(lrow);
     return lane < cnt ? a.col_idx[s_e0[lrow] + lane] : 0;
   };
+  auto source = [&](int lrow, int e, int c, unsigned long long &p, float &w) {
+    entry_source(a, row0 + lrow, c, 0, p, w, [&] { return a.w_in ? a.w_in[e + s_wd[lrow]] : 1.f; });
+  };
   int j0 = grab();
   int c0 = stage_a(j0);
   int j1 = grab();
   int c1 = stage_a(j1);
   unsigned long long p0 = 0;
   float w0 = 0.f;
-  if (lane < first_cnt(j0)) entry_source(a, row0 + j0, c0, 0, p0, w0);
+  if (lane < first_cnt(j0)) source(j0, s_e0[j0] + lane, c0, p0, w0);
   while (j0 < kFM) {
     const int j2 = grab();
     const int c2 = stage_a(j2);
     unsigned long long p1 = 0;
     float w1 = 0.f;
-    if (lane < first_cnt(j1)) entry_source(a, row0 + j1, c1, 0, p1, w1);
+    if (lane < first_cnt(j1)) source(j1, s_e0[j1] + lane, c1, p1, w1);
     {  // stage C on row j0
       const int lrow = j0, row = row0 + lrow;
       float *lds_row = As + lrow * kFLda;
@@ -124,7 +129,7 @@ __global__ void __launch_bounds__(kFThreads, 6) __attribute__((amdgpu_num_sgpr(9
           const int cnt = min(kWave, e1 - base);
           unsigned long long p_l = 0;
           float w_l = 0.f;
-          if (lane < cnt) entry_source(a, row, a.col_idx[base + lane], 0, p_l, w_l);
+          if (lane < cnt) source(lrow, base + lane, a.col_idx[base + lane], p_l, w_l);
           gather_batch<VEC, 1, LPR>(p_l, w_l, cnt, nvec, acc);
         }
         fold_groups<VEC, 1, LPR>(acc);
@@ -276,7 +281,7 @@ bool spmm_gemm_fwd_concat_supported(int32_t d_in, int32_t d_out) {
 }
 
 hipError_t spmm_gemm_fwd(const SegPlan &plan, int32_t n_in, int32_t d_in, int32_t d_out, const int32_t *row_ptr,
-                         const int32_t *col_idx, const float *w_col, const float *row_scale,
+                         const int32_t *col_idx, const float *w_in, const int32_t *w_ptr, const float *row_scale,
                          const float *H_in, const float *Hu, float *partials, float *A,
                          const SpmmRowPart &part, const float *W, float *H_out, bool relu,
                          const Dropout &drop, hipStream_t s, bool concat_self) {
@@ -284,7 +289,7 @@ hipError_t spmm_gemm_fwd(const SegPlan &plan, int32_t n_in, int32_t d_in, int32_
   if (concat_self && !spmm_gemm_fwd_concat_supported(d_in, d_out)) return hipErrorInvalidValue;
   if (n_in <= 0) return hipSuccess;
   FusedArgs f;
-  f.sp = spmm_fwd_args(plan, n_in, d_in, row_ptr, col_idx, w_col, row_scale, H_in, Hu, partials, A, part);
+  f.sp = spmm_fwd_args(plan, n_in, d_in, row_ptr, col_idx, w_in, w_ptr, row_scale, H_in, Hu, partials, A, part);
   f.W = W;
   f.H_self = concat_self ? H_in : nullptr;
   f.H_out = H_out;

@@ -65,6 +65,8 @@ struct StaticSplit {       // inner / boundary split of the static CSR, built on
 };
 hipError_t build_static_split(int32_t n_in, const int32_t *row_ptr0, const int32_t *col0,
                               const StaticSplit &sp, int32_t *tile_sums, hipStream_t s);
+// w[j] = of[col[j]]
+hipError_t entry_weights(int64_t n, const int32_t *col, const float *of, float *w, hipStream_t s);
 hipError_t degree_rsqrt(const int32_t *deg, int32_t n, float *dis, hipStream_t s);
 
 // ballots: the keep bits written by sample_boundary (bit b%64 of word b/64); kpos: scratch
@@ -124,8 +126,9 @@ inline int64_t seg_max_multi(int64_t nnz) { return nnz / kSegLen + 1; }
 hipError_t build_seg_plan(int32_t n_rows, int64_t nnz, const int32_t *row_ptr, SegPlan *plan, int32_t *tmp_a,
                           int32_t *tmp_b, int32_t *tile_sums, hipStream_t s);
 
-// A[v,:] = row_scale[v] * ( init[v,:] + sum_{u<n_in in row v} w_col[u] H_in[u,:] + sum_{kept r in row v} Hu[r,:] )
-// w_col / row_scale nullable (= 1).  GCN layer: both = d~^-1/2; mean aggregator: w_col = null,
+// A[v,:] = row_scale[v] * ( init[v,:] + sum_{u<n_in in row v} w_u H_in[u,:] + sum_{kept r in row v} Hu[r,:] )
+// w_in (one weight per entry of the static inner list, which starts at w_ptr[v] for row v) / row_scale nullable (= 1).
+// GCN layer: both hold d~^-1/2; mean aggregator: w_in = null,
 // row_scale = 1/degree, skip_self.  plan: segmentation of the static local CSR; partials: scratch
 // f32[plan.n_part * d].  part (all optional) restricts every row to entries [skip, skip+take) of
 // its list, adds the initial row vector, or skips the stored self-loop.
@@ -144,7 +147,7 @@ struct SpmmRowPart {
 hipError_t halo_records(const int32_t *kept_ids, const int32_t *n_kept, int32_t n_halo, const float *dis_halo,
                         float s_halo, int2 *rec, const PackJobs &pack, hipStream_t s);
 hipError_t spmm_fwd(const SegPlan &plan, int32_t n_in, int32_t d, const int32_t *row_ptr,
-                    const int32_t *col_idx, const float *w_col, const float *row_scale,
+                    const int32_t *col_idx, const float *w_in, const int32_t *w_ptr, const float *row_scale,
                     const float *H_in, const float *Hu, float *partials, float *A,
                     const SpmmRowPart &part, bool long_rows_only, bool relu, hipStream_t s,
                     int32_t d_store = 0);
@@ -164,17 +167,18 @@ hipError_t pad_rows(int32_t n_rows, int32_t d, int32_t ld, const float *src, flo
 bool spmm_gemm_fwd_supported(int32_t d_in);
 bool spmm_gemm_fwd_concat_supported(int32_t d_in, int32_t d_out);
 hipError_t spmm_gemm_fwd(const SegPlan &plan, int32_t n_in, int32_t d_in, int32_t d_out, const int32_t *row_ptr,
-                         const int32_t *col_idx, const float *w_col, const float *row_scale,
+                         const int32_t *col_idx, const float *w_in, const int32_t *w_ptr, const float *row_scale,
                          const float *H_in, const float *Hu, float *partials, float *A,
                          const SpmmRowPart &part, const float *W, float *H_out, bool relu,
                          const Dropout &drop, hipStream_t s, bool concat_self = false);
-// For stacked column u < n_in + *n_kept:  g = sum_{v in t_row u} w_col[v] dA[v,:];
+// For stacked column u < n_in + *n_kept:  g = sum_{v in t_row u} w_v dA[v,:];
 //   u <  n_in: dH_in[u,:] = row_scale[u] * (init[u,:] + g)  (zeroed where mask_src[u,:] <= 0 if given)
 //   u >= n_in: dhalo[u-n_in,:] = s_halo * dis_halo[kept_ids[u-n_in]] * g   (skipped if dhalo null)
-// row_scale, dis_halo, init nullable.  plan: segmentation of the transposed inner-inner block.
+// Weights per entry: w_in in the order of the transposed inner-inner block, w_halo in that of the boundary nodes' static
+// lists (halo_ptr).  row_scale, dis_halo, init nullable.  plan: segmentation of the transposed inner-inner block.
 hipError_t spmm_bwd(const SegPlan &plan, int32_t n_in, int32_t n_halo, int32_t d,
                     const int32_t *t_row_ptr, const int32_t *t_col_idx, const int32_t *kept_ids,
-                    const int32_t *n_kept, const float *w_col, const float *row_scale,
+                    const int32_t *n_kept, const float *w_in, const float *w_halo, const int32_t *halo_ptr, const float *row_scale,
                     const float *dis_halo, float s_halo, const float *dA, const float *mask_src,
                     const float *init, bool skip_self, float *partials, float *dH_in, float *dhalo,
                     hipStream_t s, int32_t d_store = 0);

@@ -19,73 +19,70 @@
 
 namespace bns {
 
-// Measured on gfx950: the same code runs 3-6 % slower as soon as the wavefront needs more than 96
-// scalar registers (seven 16-register granules instead of six), so the budget is pinned.
 template <int VEC, int MAXCH, int LPR, bool NARROW = false>
-__global__ void __launch_bounds__(256, MAXCH == 1 ? 8 : 1) __attribute__((amdgpu_num_sgpr(96))) spmm_kernel(const SpmmArgs a) {
+__global__ void __launch_bounds__(256, MAXCH == 1 ? 8 : 1) spmm_kernel(const SpmmArgs) {
   using V = typename Vec<VEC>::T;
   const int lane = lane_id();
   const int g = lane / LPR, sl = lane % LPR;
-  const int d = a.d;
-  int nvec = d / VEC, d_off = 0;
-  int bid = blockIdx.x, nblk = gridDim.x;
-  if (a.n_slices > 1) {  // gridDim.x is a multiple of 8
-    const int x = bid & 7, per = 8 / a.n_slices;
-    d_off = (x % a.n_slices) * a.d_slice;
-    nvec = a.d_slice / VEC;
-    bid = (bid >> 3) * per + x / a.n_slices;
-    nblk = (nblk >> 3) * per;
+  int bid = blockIdx.x, nblk = gridDim.x, d_off = 0, n_units;
+  {
+    ArgBlock &a = unit_args();
+    if (const int ls = a.log2_slices) {  // gridDim.x is a multiple of 8
+      const int x = bid & 7;
+      d_off = (x & ((1 << ls) - 1)) * a.d_slice;
+      bid = ((bid >> 3) << (3 - ls)) + (x >> ls);
+      nblk = (nblk >> 3) << (3 - ls);
+    }
+    // the static units, then one unit per kept boundary row (count on the device)
+    n_units = a.n_units + (a.n_extra_dev ? scalar_load(a.n_extra_dev, 0) : 0);
   }
-  // work units: the static segments, then one unit per kept boundary row (count on the device)
-  const int n_units = a.multi_only ? a.plan.n_part : a.plan.n_seg + (a.n_extra_dev ? *a.n_extra_dev : 0);
-  // (the unit is the same for the whole wavefront: its bounds then come through the scalar cache)
+  // (the unit is the same for the whole wavefront, so that its bounds come through the scalar cache)
   for (int unit = bid * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); unit < n_units; unit += nblk * 4) {
-  int row, seg = 0, nseg = 1;
-  if (a.multi_only) {  // units are the partial-sum slots, i.e. the segments of the long rows
-    row = a.plan.part_row[unit];
-    seg = unit - a.plan.part_ptr[row];
-    nseg = a.plan.seg_ptr[row + 1] - a.plan.seg_ptr[row];
-  } else if (unit < a.plan.n_seg) {
-    row = a.plan.seg_row[unit];
-    const int s0 = a.plan.seg_ptr[row];
-    seg = unit - s0;
-    nseg = a.plan.seg_ptr[row + 1] - s0;
-  } else {
-    row = a.n_split + (unit - a.plan.n_seg);
-  }
-  int e0 = a.row_ptr[row], e1 = a.row_ptr[row + 1];
-  if (row < a.n_split) {
-    if (a.row_skip) e0 += a.row_skip[row];
-    if (a.row_take) e1 = e0 + a.row_take[row];
-  }
-  if (nseg > 1) {  // this wavefront's slice of the row as it is in this epoch
-    const int chunk = (e1 - e0 + nseg - 1) / nseg;
-    e0 = min(e1, e0 + seg * chunk);
-    e1 = min(e1, e0 + chunk);
-  }
+    ArgBlock &a = unit_args();
+    const int nvec = a.d_slice / VEC;
+    int row, seg = 0, nseg = 1;
+    if (unit < a.n_units) {
+      row = scalar_load(a.unit_row, unit);
+      seg = unit - scalar_load(a.unit_first, row);
+      nseg = scalar_load(a.plan.seg_ptr, row + 1) - scalar_load(a.plan.seg_ptr, row);
+    } else {
+      row = a.n_split + (unit - a.n_units);
+    }
+    int e0 = scalar_load(a.row_ptr, row), e1 = scalar_load(a.row_ptr, row + 1);
+    const InnerWeights iw = inner_weights(a, row, e0, e1);
+    if (row < a.n_split) {
+      if (a.row_skip) e0 += scalar_load(a.row_skip, row);
+      if (a.row_take) e1 = e0 + scalar_load(a.row_take, row);
+    }
+    if (nseg > 1) {  // this wavefront's slice of the row as it is in this epoch
+      const int chunk = (e1 - e0 + nseg - 1) / nseg;
+      e0 = min(e1, e0 + seg * chunk);
+      e1 = min(e1, e0 + chunk);
+    }
 
-  float acc[MAXCH][VEC];
-  gather_segment<VEC, MAXCH, LPR>(a, row, e0, e1, d_off, nvec, acc);
+    float acc[MAXCH][VEC];
+    gather_segment<VEC, MAXCH, LPR>(a, row, iw, e0, e1, d_off, nvec, acc);
 
-  if (g != 0) {
-    // only the first lane group holds the folded sums
-  } else if (nseg == 1) {
-    finish_row<VEC, MAXCH, NARROW>(a, row, sl, nvec, d_off, acc);
-  } else {
-    V *part = reinterpret_cast<V *>(a.partials + (size_t)(a.plan.part_ptr[row] + seg) * d + d_off);
+    ArgBlock &b = unit_args();
+    if (g != 0) {
+      // only the first lane group holds the folded sums
+    } else if (nseg == 1) {
+      finish_row<VEC, MAXCH, NARROW>(b, row, sl, nvec, d_off, acc);
+    } else {
+      V *part = reinterpret_cast<V *>(b.partials + (size_t)(scalar_load(b.plan.part_ptr, row) + seg) * b.d + d_off);
 #pragma unroll
-    for (int c = 0; c < MAXCH; ++c) {
-      const int iv = c * kWave + sl;
-      if (iv < nvec) {
-        V o;
-        float *po = reinterpret_cast<float *>(&o);
+      for (int c = 0; c < MAXCH; ++c) {
+        const int iv = c * kWave + sl;
+        if (iv < nvec) {
+          V o;
+          float *po = reinterpret_cast<float *>(&o);
 #pragma unroll
-        for (int i = 0; i < VEC; ++i) po[i] = acc[c][i];
-        part[iv] = o;
+          for (int i = 0; i < VEC; ++i) po[i] = acc[c][i];
+          part[iv] = o;
+        }
       }
     }
   }
-  }  // unit loop
 }
 
 // Rows cut into several segments: add the partial sums in ascending segment order.
@@ -129,33 +126,33 @@ __global__ void __launch_bounds__(256) spmm_combine_kernel(const SpmmArgs a) {
 }
 
 template <int VEC>
-static hipError_t launch_spmm_vec(const SpmmArgs &a_in, int64_t max_units, hipStream_t s) {
+static hipError_t launch_spmm_vec(const SpmmArgs &a_in, int64_t max_units, bool multi_only, hipStream_t s) {
   SpmmArgs a = a_in;
-  a.n_slices = 1;
-  a.d_slice = a.d;
+  // multi_only: the segments of the multi-segment rows, i.e. the partial-sum slots
+  a.n_units = multi_only ? a.plan.n_part : a.plan.n_seg;
+  a.unit_row = multi_only ? a.plan.part_row : a.plan.seg_row;
+  a.unit_first = multi_only ? a.plan.part_ptr : a.plan.seg_ptr;
   // Wide rows are cut into slices of 128 floats (64 where rows are long enough to keep a
   // wavefront busy with a quarter of its lanes per neighbour); measured on the five workloads,
   // narrower slices lose more to the repeated index walk than the L2 gains.
-  if (VEC == 4 && !a.multi_only) {
+  int ls = 0;
+  if (VEC == 4 && !multi_only) {
     const int target = a.plan.avg_len >= 64 ? 64 : 128;
-    int S = 1;
-    while (S < 8 && a.d / (2 * S) >= target && a.d % (2 * S * VEC) == 0) S *= 2;
-    a.n_slices = S;
-    a.d_slice = a.d / S;
+    while (ls < 3 && (a.d >> (ls + 1)) >= target && a.d % (VEC << (ls + 1)) == 0) ++ls;
   }
+  a.log2_slices = ls;
+  a.d_slice = a.d >> ls;
   const int nvec = a.d_slice / VEC;
   const int full_nvec = a.d / VEC;
   // one wavefront per static segment; the kept boundary rows, whose count lives on the device,
   // are strided over by a bounded number of extra blocks (blocks past the count would only cost
   // dispatch time)
-  const int64_t seg_blocks = ((int64_t)a.plan.n_seg + 3) / 4;
-  const int64_t extra_blocks = std::min<int64_t>((max_units - a.plan.n_seg + 3) / 4, 8192);
-  unsigned blocks = (unsigned)(seg_blocks + std::max<int64_t>(extra_blocks, 0));
-  if (a.multi_only) blocks = (unsigned)((a.plan.n_part + 3) / 4);
+  const int64_t extra_blocks = multi_only ? 0 : std::min<int64_t>((max_units - a.n_units + 3) / 4, 8192);
+  unsigned blocks = (unsigned)(((int64_t)a.n_units + 3) / 4 + std::max<int64_t>(extra_blocks, 0));
   const unsigned cblocks = (unsigned)((a.plan.n_multi + 3) / 4);
   if (blocks == 0) return hipSuccess;
-  if (a.n_slices > 1) {
-    const unsigned per = 8 / a.n_slices;
+  if (ls > 0) {
+    const unsigned per = 8 >> ls;
     blocks = (blocks + per - 1) / per * 8;
   }
   if (a.d_store != a.d) {  // padded sources, dense narrower outputs: d < 128, four floats per lane
@@ -197,28 +194,27 @@ static hipError_t launch_spmm_vec(const SpmmArgs &a_in, int64_t max_units, hipSt
   return hipGetLastError();
 }
 
-static hipError_t launch_spmm(const SpmmArgs &a, int64_t max_units, hipStream_t s) {
+static hipError_t launch_spmm(const SpmmArgs &a, int64_t max_units, hipStream_t s, bool multi_only = false) {
   if (a.d_store != a.d && (a.d_store < 1 || a.d_store > a.d || a.d >= 128 || a.d % 4 != 0 || a.mask_src || a.init))
     return hipErrorInvalidValue;  // padded sources: narrow rows without mask or initial value only
-  if (a.d % 4 == 0) return launch_spmm_vec<4>(a, max_units, s);
-  if (a.d % 2 == 0) return launch_spmm_vec<2>(a, max_units, s);
-  return launch_spmm_vec<1>(a, max_units, s);
+  if (a.d % 4 == 0) return launch_spmm_vec<4>(a, max_units, multi_only, s);
+  if (a.d % 2 == 0) return launch_spmm_vec<2>(a, max_units, multi_only, s);
+  return launch_spmm_vec<1>(a, max_units, multi_only, s);
 }
 
 hipError_t spmm_fwd(const SegPlan &plan, int32_t n_in, int32_t d, const int32_t *row_ptr,
-                    const int32_t *col_idx, const float *w_col, const float *row_scale,
+                    const int32_t *col_idx, const float *w_in, const int32_t *w_ptr, const float *row_scale,
                     const float *H_in, const float *Hu, float *partials, float *A,
                     const SpmmRowPart &part, bool long_rows_only, bool relu, hipStream_t s, int32_t d_store) {
-  SpmmArgs a = spmm_fwd_args(plan, n_in, d, row_ptr, col_idx, w_col, row_scale, H_in, Hu, partials, A, part);
-  a.multi_only = long_rows_only;
+  SpmmArgs a = spmm_fwd_args(plan, n_in, d, row_ptr, col_idx, w_in, w_ptr, row_scale, H_in, Hu, partials, A, part);
   a.relu = relu;
   if (d_store > 0) a.d_store = d_store;
-  return launch_spmm(a, plan.n_seg, s);
+  return launch_spmm(a, plan.n_seg, s, long_rows_only);
 }
 
 hipError_t spmm_bwd(const SegPlan &plan, int32_t n_in, int32_t n_halo, int32_t d,
                     const int32_t *t_row_ptr, const int32_t *t_col_idx, const int32_t *kept_ids,
-                    const int32_t *n_kept, const float *w_col, const float *row_scale,
+                    const int32_t *n_kept, const float *w_in, const float *w_halo, const int32_t *halo_ptr, const float *row_scale,
                     const float *dis_halo, float s_halo, const float *dA, const float *mask_src,
                     const float *init, bool skip_self, float *partials, float *dH_in, float *dhalo,
                     hipStream_t s, int32_t d_store) {
@@ -226,7 +222,7 @@ hipError_t spmm_bwd(const SegPlan &plan, int32_t n_in, int32_t n_halo, int32_t d
   const bool halo_rows = dhalo && n_halo > 0;
   a.plan = plan; a.n_extra_dev = halo_rows ? n_kept : nullptr; a.d = d; a.d_store = d_store > 0 ? d_store : d;
   a.row_ptr = t_row_ptr; a.col_idx = t_col_idx; a.n_split = n_in;
-  a.src0 = dA; a.src1 = nullptr; a.w_col = w_col; a.partials = partials;
+  a.src0 = dA; a.src1 = nullptr; a.w_in = w_in; a.w_ptr = nullptr; a.w_halo = w_halo; a.halo_ptr = halo_ptr; a.partials = partials;
   a.out0 = dH_in; a.out1 = dhalo; a.out_scale0 = row_scale; a.mask_src = mask_src;
   a.kept_ids = kept_ids; a.dis_halo = dis_halo; a.s_halo = s_halo;
   a.init = init; a.skip_self = skip_self;

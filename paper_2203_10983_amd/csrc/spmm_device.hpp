@@ -24,11 +24,23 @@ __device__ __forceinline__ void vec_fma(float (&acc)[VEC], float w, const typena
 
 struct SpmmArgs {
   SegPlan plan;                // static segmentation of rows 0..n_split-1
+  // work units of the kernel: unit u < n_units is a segment of row unit_row[u], the (u - unit_first[row])th of it
+  int32_t n_units;
+  const int32_t *unit_row, *unit_first;
   const int32_t *n_extra_dev;  // nullable: *n_extra_dev further single-segment rows follow (kept boundary)
   int32_t d;                   // floats per gathered row = row stride of src0, src1 and the partial sums
   const int32_t *row_ptr, *col_idx;
-  int32_t n_split;             // columns < n_split read src0 (weight w_col[c]); others src1 (weight 1)
-  const float *src0, *src1, *w_col;
+  int32_t n_split;             // columns < n_split read src0; others src1 (weight 1)
+  const float *src0, *src1;
+  // Weights of the entries with a column < n_split, in the order of the static lists (null: 1).  They come first in a
+  // row; the list of row v < n_split starts at w_ptr[v] (null: row_ptr[v]), that of a kept boundary row at
+  // w_halo + halo_ptr[its node].
+  // A weight per entry, read in step with the column indices, instead of a gather from a table by column: the gather cost a
+  // request of its own per entry, and the table (4 bytes per node, 2.3 MB on 578 125 nodes) was hot enough to keep
+  // half of every L2 from the feature rows.  Same values, same sums; transposed aggregate of 16.6 M entries of 128 floats
+  // 955 -> 838 us (bytes from the fabric 6.6 -> 5.6 GB), 32.9 M entries of 64 floats in L2 651 -> 551 us.
+  const float *w_in, *w_halo;
+  const int32_t *w_ptr, *halo_ptr;
   // nullable: src1 is the boundary-feature table as the caller holds it (one row per boundary
   // node) and stacked column n_split + r reads its row halo_rec[r].x with weight
   // as_float(halo_rec[r].y); else src1 holds the kept rows in kept order, already scaled
@@ -46,40 +58,55 @@ struct SpmmArgs {
   const int32_t *row_take;     // then use row_take[row] entries instead of the rest (nullable)
   const float *init;           // out0 row = scale * (init row + sum) (nullable)
   bool skip_self;              // entries with column == row contribute nothing (mean aggregator)
-  // feature slicing over the XCDs (n_slices = 1: off).  Workgroups are handed to the 8 XCDs in
-  // turn, so workgroup b runs on XCD b % 8; with n_slices = S that XCD only ever touches the
+  // feature slicing over the XCDs (log2_slices = 0: off).  Workgroups are handed to the 8 XCDs in
+  // turn, so workgroup b runs on XCD b % 8; with S = 2^log2_slices that XCD only ever touches the
   // d_slice = d / S floats of slice (b % 8) % S of every feature row, and its private L2 holds S
   // times as many distinct rows.
-  int32_t n_slices, d_slice;
-  bool multi_only;             // work units = segments of the multi-segment rows only
+  int32_t log2_slices, d_slice;
   bool relu;                   // rows < n_split: max(., 0) after the scale (update-first layers)
   // columns stored per output row = row stride of out0 / out1; less than d when the sources are
   // padded to a multiple of 4 floats (then no mask, no init, no slices; read by the NARROW kernels only)
   int32_t d_store;
 };
 
+// A kernel that walks many work units keeps every argument in scalar registers across its loop, and this block is
+// larger than they are: the overflow went to lanes of vector registers and on to scratch memory.  unit_args() gives the block
+// (the kernel's only parameter) where it lies in constant memory, anew for every unit, so that each argument is read where it is used.
+using ArgBlock = const __attribute__((address_space(4))) SpmmArgs;
+__device__ __forceinline__ ArgBlock &unit_args() {
+  auto *p = (ArgBlock *)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return *p;
+}
+
+// p[i] through the scalar cache, for an i that is the same on the whole wavefront and memory that the kernel does not write.
+template <typename T>
+__device__ __forceinline__ T scalar_load(const T *p, int i) {
+  return reinterpret_cast<const __attribute__((address_space(4))) T *>(reinterpret_cast<uintptr_t>(p))[i];
+}
+
 // Argument block of the forward aggregate (the transposed pass fills its own).
 inline SpmmArgs spmm_fwd_args(const SegPlan &plan, int32_t n_in, int32_t d, const int32_t *row_ptr,
-                              const int32_t *col_idx, const float *w_col, const float *row_scale,
+                              const int32_t *col_idx, const float *w_in, const int32_t *w_ptr, const float *row_scale,
                               const float *H_in, const float *Hu, float *partials, float *A,
                               const SpmmRowPart &part) {
   SpmmArgs a{};
   a.plan = plan; a.n_extra_dev = nullptr; a.d = d; a.d_store = d;
   a.row_ptr = row_ptr; a.col_idx = col_idx; a.n_split = n_in;
-  a.src0 = H_in; a.src1 = Hu; a.w_col = w_col; a.partials = partials; a.halo_rec = part.halo_rec;
+  a.src0 = H_in; a.src1 = Hu; a.w_in = w_in; a.w_ptr = w_ptr; a.w_halo = nullptr; a.halo_ptr = nullptr; a.partials = partials; a.halo_rec = part.halo_rec;
   a.out0 = A; a.out1 = nullptr; a.out_scale0 = row_scale; a.mask_src = nullptr;
   a.kept_ids = nullptr; a.dis_halo = nullptr; a.s_halo = 0.f;
   a.row_skip = part.row_skip; a.row_take = part.row_take; a.init = part.init;
   a.skip_self = part.skip_self;
-  a.n_slices = 1; a.d_slice = d; a.multi_only = false; a.relu = false;
+  a.log2_slices = 0; a.d_slice = d; a.relu = false;
   return a;
 }
 
 // Scale, optional ReLU mask and store of one finished row slice held as acc[c][i].
 // lds_row (nullable): the finished values are also written there, element iv*VEC+i at lds_row[iv*VEC+i].
 // NARROW: the sources are padded (d_store < d), the output rows are dense with d_store columns.
-template <int VEC, int MAXCH, bool NARROW = false>
-__device__ __forceinline__ void finish_row(const SpmmArgs &a, int row, int sl, int nvec, int d_off,
+template <int VEC, int MAXCH, bool NARROW = false, typename Args>
+__device__ __forceinline__ void finish_row(Args &a, int row, int sl, int nvec, int d_off,
                                            float (&acc)[MAXCH][VEC], float *lds_row = nullptr) {
   using V = typename Vec<VEC>::T;
   const int d = a.d, ds = NARROW ? (int)a.d_store : d;
@@ -89,13 +116,13 @@ __device__ __forceinline__ void finish_row(const SpmmArgs &a, int row, int sl, i
   const float *init = nullptr;
   if (row < a.n_split) {
     if (a.init) init = a.init + (size_t)row * d + d_off;
-    scale = a.out_scale0 ? a.out_scale0[row] : 1.f;
+    scale = a.out_scale0 ? scalar_load(a.out_scale0, row) : 1.f;
     out = a.out0 + (size_t)row * ds + d_off;
     if (a.mask_src) mask = a.mask_src + (size_t)row * d + d_off;
   } else {
     if (a.out1 == nullptr) return;
     const int r = row - a.n_split;
-    scale = a.dis_halo ? a.s_halo * a.dis_halo[a.kept_ids[r]] : a.s_halo;
+    scale = a.dis_halo ? a.s_halo * scalar_load(a.dis_halo, scalar_load(a.kept_ids, r)) : a.s_halo;
     out = a.out1 + (size_t)r * ds + d_off;
   }
 #pragma unroll
@@ -141,13 +168,29 @@ __device__ __forceinline__ void finish_row(const SpmmArgs &a, int row, int sl, i
   }
 }
 
-// Feature-row address and weight of entry `col` (stacked column index c) of row `row`.
-__device__ __forceinline__ void entry_source(const SpmmArgs &a, int row, int c, int d_off,
-                                             unsigned long long &p, float &w) {
+// Weights of a row's entries [.., end) with an inner column: w[e] for entry e (w null: 1).
+struct InnerWeights {
+  const float *w;
+  int end;
+};
+template <typename Args>
+__device__ __forceinline__ InnerWeights inner_weights(Args &a, int row, int r0, int r1) {  // r0, r1: its entries
+  if (!a.w_in) return {nullptr, r0};
+  if (row >= a.n_split) return {a.w_halo + (scalar_load(a.halo_ptr, scalar_load(a.kept_ids, row - a.n_split)) - r0), r1};
+  if (!a.w_ptr) return {a.w_in, r1};
+  const int i0 = scalar_load(a.w_ptr, row);
+  return {a.w_in + (i0 - r0), r0 + (scalar_load(a.w_ptr, row + 1) - i0)};
+}
+
+// Feature-row address and weight of an entry with the stacked column index c of row `row`; inner(): its weight if c
+// is an inner column.
+template <typename F, typename Args>
+__device__ __forceinline__ void entry_source(Args &a, int row, int c, int d_off,
+                                             unsigned long long &p, float &w, F inner) {
   const int d = a.d;
   if (c < a.n_split) {
     p = (unsigned long long)(a.src0 + (size_t)c * d + d_off);
-    w = a.w_col ? a.w_col[c] : 1.f;
+    w = inner();
     if (a.skip_self && c == row) w = 0.f;  // the stored self-loop is not a neighbour
   } else if (a.halo_rec) {
     const int2 r = a.halo_rec[c - a.n_split];
@@ -291,9 +334,9 @@ __device__ __forceinline__ void fold_groups(float (&acc)[MAXCH][VEC]) {
 // Sum of w * (feature row) over the entries [e0, e1) of `row`, at most a few hundred of them;
 // lane group 0 (lanes < LPR) ends up with the result.  d_off / nvec: first feature column and
 // number of VEC-pieces handled.
-template <int VEC, int MAXCH, int LPR>
-__device__ __forceinline__ void gather_segment(const SpmmArgs &a, int row, int e0, int e1, int d_off, int nvec,
-                                               float (&acc)[MAXCH][VEC]) {
+template <int VEC, int MAXCH, int LPR, typename Args>
+__device__ __forceinline__ void gather_segment(Args &a, int row, const InnerWeights iw, int e0, int e1,
+                                               int d_off, int nvec, float (&acc)[MAXCH][VEC]) {
 #pragma unroll
   for (int c = 0; c < MAXCH; ++c)
 #pragma unroll
@@ -305,7 +348,12 @@ __device__ __forceinline__ void gather_segment(const SpmmArgs &a, int row, int e
     float w_l = 0.f;
     constexpr bool DPP = dpp_gather(MAXCH, LPR);
     const int mine = batch_entry<LPR, DPP>();
-    if (mine < cnt) entry_source(a, row, a.col_idx[base + mine], d_off, p_l, w_l);
+    if (mine < cnt) {
+      const int e = base + mine;
+      const float w_e = e < iw.end ? iw.w[e] : 0.f;  // (asked for beside the column index, not after it)
+      const int c = a.col_idx[e];
+      entry_source(a, row, c, d_off, p_l, w_l, [&] { return iw.w ? w_e : 1.f; });
+    }
     gather_batch<VEC, MAXCH, LPR, DPP>(p_l, w_l, cnt, nvec, acc);
   }
   fold_groups<VEC, MAXCH, LPR>(acc);
