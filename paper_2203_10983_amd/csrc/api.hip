@@ -191,10 +191,10 @@ size_t carve(Carver &c, const bns_partition_desc *p, const bns_model_desc *m, La
     SegPlan &pl = k == 0 ? w.plan_f : w.plan_b;
     const int64_t nnz = k == 0 ? p->nnz0 : p->e_in;
     pl.seg_ptr = c.take<int32_t>(n_in + 1);
-    pl.seg_row = c.take<int32_t>(seg_max_segments(n_in, nnz));
+    pl.seg_unit = c.take<int2>(seg_max_segments(n_in, nnz));
     pl.part_ptr = c.take<int32_t>(n_in + 1);
     pl.mrow = c.take<int32_t>(seg_max_multi(nnz));
-    pl.part_row = c.take<int32_t>(seg_max_parts(nnz));
+    pl.part_unit = c.take<int2>(seg_max_parts(nnz));
     pl.n_seg = pl.n_part = pl.n_multi = 0;
   }
   w.seg_tmp_a = c.take<int32_t>(n_in + 1);
@@ -217,6 +217,8 @@ size_t carve(Carver &c, const bns_partition_desc *p, const bns_model_desc *m, La
   w.tn2.assign(L + 1, nullptr);
   w.G_in.assign(L + 1, nullptr);
   w.G_halo.assign(L + 1, nullptr);
+  std::vector<size_t> behind(L + 1, 0);
+  bool hu2_taken = false;
   for (size_t l = 1; l <= L; ++l) {
     const int32_t kw = m->layer_kind == 1 ? 2 : 1;
     const bool first = update_first_shape(m->layer_kind, m->dims[l - 1], m->dims[l]);
@@ -224,12 +226,19 @@ size_t carve(Carver &c, const bns_partition_desc *p, const bns_model_desc *m, La
                                      first ? gemm_tn_partials(m->dims[l - 1], m->dims[l], p->n_in, p->n_halo) : 0));
     if (first) {
       w.tn2[l] = c.take<float>(gemm_tn_partials(m->dims[l - 1], m->dims[l], p->n_halo, p->n_in));
-      w.G_in[l] = c.take<float>(n_in * m->dims[l]);
-      w.G_halo[l] = c.take<float>(B * m->dims[l]);
+      // what the forward pass leaves free, where it is enough: the rest of A[l] behind H W, and the boundary rows H_U W
+      // (one buffer for all layers: for the first such layer)
+      behind[l] = align_up(n_in * gather_stride(m->dims[l - 1], m->dims[l]) * sizeof(float)) / sizeof(float);
+      if (behind[l] + n_in * m->dims[l] > n_in * (size_t)m->dims[l - 1]) behind[l] = 0;
+      if (!behind[l]) w.G_in[l] = c.take<float>(n_in * m->dims[l]);
+      if (hu2_taken) w.G_halo[l] = c.take<float>(B * m->dims[l]);
+      else w.G_halo[l] = w.Hu2;
+      hu2_taken = true;
     }
     w.Wf[l] = c.take<char>(std::max(packed_bytes_f32(kw * m->dims[l - 1], m->dims[l]), kw * packed_bytes_f32(m->dims[l - 1], m->dims[l])));
     w.Wb[l] = c.take<char>(kw * packed_bytes(m->dims[l], m->dims[l - 1]));
     w.A[l] = c.take<float>(n_in * (size_t)m->dims[l - 1]);
+    if (behind[l] && w.A[l]) w.G_in[l] = w.A[l] + behind[l];
     w.H[l] = c.take<float>(n_in * (size_t)m->dims[l]);
     w.dZ[l] = c.take<float>(n_in * (size_t)m->dims[l]);
   }

@@ -111,10 +111,10 @@ constexpr int kSegLen = 256;  // a wavefront aggregates at most this many neighb
 //   segments <= rows + nnz/kSegLen, partial slots <= 2*nnz/kSegLen, multi-segment rows <= nnz/kSegLen
 struct SegPlan {
   int32_t *seg_ptr;   // int32[n_rows+1] first segment of each row
-  int32_t *seg_row;   // int32[n_seg]    row of each segment
+  int2 *seg_unit;     // int2[n_seg]     row of each segment and its partial-sum slot (-1: the row's only segment)
   int32_t *part_ptr;  // int32[n_rows+1] first partial-sum slot of each multi-segment row
   int32_t *mrow;      // int32[n_multi]  rows with more than one segment
-  int32_t *part_row;  // int32[n_part]   row of each partial-sum slot
+  int2 *part_unit;    // int2[n_part]    row of each partial-sum slot, slot
   int32_t n_seg, n_part, n_multi;  // host copies of the totals
   int32_t avg_len;                 // entries per row of the static pattern (launch heuristics)
 };

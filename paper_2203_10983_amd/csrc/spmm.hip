@@ -40,21 +40,22 @@ __global__ void __launch_bounds__(256, MAXCH == 1 ? 8 : 1) spmm_kernel(const Spm
   for (int unit = bid * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); unit < n_units; unit += nblk * 4) {
     ArgBlock &a = unit_args();
     const int nvec = a.d_slice / VEC;
-    int row, seg = 0, nseg = 1;
+    int row = a.n_split + (unit - a.n_units), slot = -1;
     if (unit < a.n_units) {
-      row = scalar_load(a.unit_row, unit);
-      seg = unit - scalar_load(a.unit_first, row);
-      nseg = scalar_load(a.plan.seg_ptr, row + 1) - scalar_load(a.plan.seg_ptr, row);
-    } else {
-      row = a.n_split + (unit - a.n_units);
+      const int2 u = scalar_load(a.units, unit);
+      row = u.x;
+      slot = u.y;
     }
-    int e0 = scalar_load(a.row_ptr, row), e1 = scalar_load(a.row_ptr, row + 1);
+    const int2 ee = scalar_load_pair(a.row_ptr, row);
+    int e0 = ee.x, e1 = ee.y;
     const InnerWeights iw = inner_weights(a, row, e0, e1);
     if (row < a.n_split) {
       if (a.row_skip) e0 += scalar_load(a.row_skip, row);
       if (a.row_take) e1 = e0 + scalar_load(a.row_take, row);
     }
-    if (nseg > 1) {  // this wavefront's slice of the row as it is in this epoch
+    if (slot >= 0) {  // this wavefront's slice of the row as it is in this epoch
+      const int seg = slot - scalar_load(a.plan.part_ptr, row);
+      const int nseg = scalar_load(a.plan.seg_ptr, row + 1) - scalar_load(a.plan.seg_ptr, row);
       const int chunk = (e1 - e0 + nseg - 1) / nseg;
       e0 = min(e1, e0 + seg * chunk);
       e1 = min(e1, e0 + chunk);
@@ -66,10 +67,10 @@ __global__ void __launch_bounds__(256, MAXCH == 1 ? 8 : 1) spmm_kernel(const Spm
     ArgBlock &b = unit_args();
     if (g != 0) {
       // only the first lane group holds the folded sums
-    } else if (nseg == 1) {
+    } else if (slot < 0) {
       finish_row<VEC, MAXCH, NARROW>(b, row, sl, nvec, d_off, acc);
     } else {
-      V *part = reinterpret_cast<V *>(b.partials + (size_t)(scalar_load(b.plan.part_ptr, row) + seg) * b.d + d_off);
+      V *part = reinterpret_cast<V *>(b.partials + (size_t)slot * b.d + d_off);
 #pragma unroll
       for (int c = 0; c < MAXCH; ++c) {
         const int iv = c * kWave + sl;
@@ -126,18 +127,19 @@ __global__ void __launch_bounds__(256) spmm_combine_kernel(const SpmmArgs a) {
 }
 
 template <int VEC>
-static hipError_t launch_spmm_vec(const SpmmArgs &a_in, int64_t max_units, bool multi_only, hipStream_t s) {
+static hipError_t launch_spmm_vec(const SpmmArgs &a_in, int64_t max_units, bool multi_only, bool backward, hipStream_t s) {
   SpmmArgs a = a_in;
   // multi_only: the segments of the multi-segment rows, i.e. the partial-sum slots
   a.n_units = multi_only ? a.plan.n_part : a.plan.n_seg;
-  a.unit_row = multi_only ? a.plan.part_row : a.plan.seg_row;
-  a.unit_first = multi_only ? a.plan.part_ptr : a.plan.seg_ptr;
+  a.units = multi_only ? a.plan.part_unit : a.plan.seg_unit;
   // Wide rows are cut into slices of 128 floats (64 where rows are long enough to keep a
   // wavefront busy with a quarter of its lanes per neighbour); measured on the five workloads,
-  // narrower slices lose more to the repeated index walk than the L2 gains.
+  // narrower slices lose more to the repeated index walk than the L2 gains: transposed aggregates of 128-float rows
+  // with 45 entries 875 us whole, 811 in two slices, 927 in four; with 21 entries 836, 972 and 1695.
+  // A forward row keeps the slices, and with them the order of its sum, that it has always had (from 64 entries on).
   int ls = 0;
   if (VEC == 4 && !multi_only) {
-    const int target = a.plan.avg_len >= 64 ? 64 : 128;
+    const int target = a.plan.avg_len >= (backward ? 32 : 64) ? 64 : 128;
     while (ls < 3 && (a.d >> (ls + 1)) >= target && a.d % (VEC << (ls + 1)) == 0) ++ls;
   }
   a.log2_slices = ls;
@@ -194,12 +196,12 @@ static hipError_t launch_spmm_vec(const SpmmArgs &a_in, int64_t max_units, bool 
   return hipGetLastError();
 }
 
-static hipError_t launch_spmm(const SpmmArgs &a, int64_t max_units, hipStream_t s, bool multi_only = false) {
+static hipError_t launch_spmm(const SpmmArgs &a, int64_t max_units, bool multi_only, bool backward, hipStream_t s) {
   if (a.d_store != a.d && (a.d_store < 1 || a.d_store > a.d || a.d >= 128 || a.d % 4 != 0 || a.mask_src || a.init))
     return hipErrorInvalidValue;  // padded sources: narrow rows without mask or initial value only
-  if (a.d % 4 == 0) return launch_spmm_vec<4>(a, max_units, multi_only, s);
-  if (a.d % 2 == 0) return launch_spmm_vec<2>(a, max_units, multi_only, s);
-  return launch_spmm_vec<1>(a, max_units, multi_only, s);
+  if (a.d % 4 == 0) return launch_spmm_vec<4>(a, max_units, multi_only, backward, s);
+  if (a.d % 2 == 0) return launch_spmm_vec<2>(a, max_units, multi_only, backward, s);
+  return launch_spmm_vec<1>(a, max_units, multi_only, backward, s);
 }
 
 hipError_t spmm_fwd(const SegPlan &plan, int32_t n_in, int32_t d, const int32_t *row_ptr,
@@ -209,7 +211,7 @@ hipError_t spmm_fwd(const SegPlan &plan, int32_t n_in, int32_t d, const int32_t 
   SpmmArgs a = spmm_fwd_args(plan, n_in, d, row_ptr, col_idx, w_in, w_ptr, row_scale, H_in, Hu, partials, A, part);
   a.relu = relu;
   if (d_store > 0) a.d_store = d_store;
-  return launch_spmm(a, plan.n_seg, s, long_rows_only);
+  return launch_spmm(a, plan.n_seg, long_rows_only, false, s);
 }
 
 hipError_t spmm_bwd(const SegPlan &plan, int32_t n_in, int32_t n_halo, int32_t d,
@@ -222,11 +224,11 @@ hipError_t spmm_bwd(const SegPlan &plan, int32_t n_in, int32_t n_halo, int32_t d
   const bool halo_rows = dhalo && n_halo > 0;
   a.plan = plan; a.n_extra_dev = halo_rows ? n_kept : nullptr; a.d = d; a.d_store = d_store > 0 ? d_store : d;
   a.row_ptr = t_row_ptr; a.col_idx = t_col_idx; a.n_split = n_in;
-  a.src0 = dA; a.src1 = nullptr; a.w_in = w_in; a.w_ptr = nullptr; a.w_halo = w_halo; a.halo_ptr = halo_ptr; a.partials = partials;
+  a.src0 = dA; a.src1 = nullptr; a.w_in = w_in; a.w_ptr = t_row_ptr; a.w_halo = w_halo; a.halo_ptr = halo_ptr; a.partials = partials;
   a.out0 = dH_in; a.out1 = dhalo; a.out_scale0 = row_scale; a.mask_src = mask_src;
   a.kept_ids = kept_ids; a.dis_halo = dis_halo; a.s_halo = s_halo;
   a.init = init; a.skip_self = skip_self;
-  return launch_spmm(a, (int64_t)plan.n_seg + (halo_rows ? n_halo : 0), s);
+  return launch_spmm(a, (int64_t)plan.n_seg + (halo_rows ? n_halo : 0), false, true, s);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -250,15 +252,15 @@ seg_multi_kernel(int32_t n_rows, const int32_t *__restrict__ seg_ptr, int which,
 
 __global__ void __launch_bounds__(256)
 seg_fill_kernel(int32_t n_rows, const int32_t *__restrict__ seg_ptr, const int32_t *__restrict__ mpos,
-                const int32_t *__restrict__ part_ptr, int32_t *__restrict__ seg_row,
-                int32_t *__restrict__ mrow, int32_t *__restrict__ part_row) {
+                const int32_t *__restrict__ part_ptr, int2 *__restrict__ seg_unit,
+                int32_t *__restrict__ mrow, int2 *__restrict__ part_unit) {
   const int v = blockIdx.x * 256 + threadIdx.x;
   if (v >= n_rows) return;
   const int s0 = seg_ptr[v], s1 = seg_ptr[v + 1];
-  for (int s = s0; s < s1; ++s) seg_row[s] = v;
+  for (int s = s0; s < s1; ++s) seg_unit[s] = make_int2(v, s1 - s0 > 1 ? part_ptr[v] + s - s0 : -1);
   if (s1 - s0 > 1) {
     mrow[mpos[v]] = v;
-    for (int s = 0; s < s1 - s0; ++s) part_row[part_ptr[v] + s] = v;
+    for (int s = 0; s < s1 - s0; ++s) part_unit[part_ptr[v] + s] = make_int2(v, part_ptr[v] + s);
   }
 }
 
@@ -274,8 +276,8 @@ hipError_t build_seg_plan(int32_t n_rows, int64_t nnz, const int32_t *row_ptr, S
   seg_multi_kernel<<<blocks, 256, 0, s>>>(n_rows, plan->seg_ptr, 1, tmp_a);
   e = scan_exclusive_i32(tmp_a, tmp_b, n_rows, nullptr, tile_sums, nullptr, 0, s);
   if (e != hipSuccess) return e;
-  seg_fill_kernel<<<blocks, 256, 0, s>>>(n_rows, plan->seg_ptr, tmp_b, plan->part_ptr, plan->seg_row, plan->mrow,
-                                         plan->part_row);
+  seg_fill_kernel<<<blocks, 256, 0, s>>>(n_rows, plan->seg_ptr, tmp_b, plan->part_ptr, plan->seg_unit, plan->mrow,
+                                         plan->part_unit);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   // the three totals size the launches: bring them to the host (set-up only)

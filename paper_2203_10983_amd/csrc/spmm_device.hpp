@@ -24,16 +24,15 @@ __device__ __forceinline__ void vec_fma(float (&acc)[VEC], float w, const typena
 
 struct SpmmArgs {
   SegPlan plan;                // static segmentation of rows 0..n_split-1
-  // work units of the kernel: unit u < n_units is a segment of row unit_row[u], the (u - unit_first[row])th of it
-  int32_t n_units;
-  const int32_t *unit_row, *unit_first;
+  int32_t n_units;             // work units of the kernel: segments of the plan, (row, partial-sum slot or -1)
+  const int2 *units;
   const int32_t *n_extra_dev;  // nullable: *n_extra_dev further single-segment rows follow (kept boundary)
   int32_t d;                   // floats per gathered row = row stride of src0, src1 and the partial sums
   const int32_t *row_ptr, *col_idx;
   int32_t n_split;             // columns < n_split read src0; others src1 (weight 1)
   const float *src0, *src1;
   // Weights of the entries with a column < n_split, in the order of the static lists (null: 1).  They come first in a
-  // row; the list of row v < n_split starts at w_ptr[v] (null: row_ptr[v]), that of a kept boundary row at
+  // row; the list of row v < n_split is w_ptr[v] .. w_ptr[v + 1], that of a kept boundary row at
   // w_halo + halo_ptr[its node].
   // A weight per entry, read in step with the column indices, instead of a gather from a table by column: the gather cost a
   // request of its own per entry, and the table (4 bytes per node, 2.3 MB on 578 125 nodes) was hot enough to keep
@@ -83,6 +82,14 @@ __device__ __forceinline__ ArgBlock &unit_args() {
 template <typename T>
 __device__ __forceinline__ T scalar_load(const T *p, int i) {
   return reinterpret_cast<const __attribute__((address_space(4))) T *>(reinterpret_cast<uintptr_t>(p))[i];
+}
+
+__device__ __forceinline__ int2 scalar_load(const int2 *p, int i) {
+  const long long x = scalar_load(reinterpret_cast<const long long *>(p), i);
+  return make_int2((int)x, (int)(x >> 32));
+}
+__device__ __forceinline__ int2 scalar_load_pair(const int32_t *p, int i) {
+  return make_int2(scalar_load(p, i), scalar_load(p, i + 1));
 }
 
 // Argument block of the forward aggregate (the transposed pass fills its own).
@@ -177,9 +184,8 @@ template <typename Args>
 __device__ __forceinline__ InnerWeights inner_weights(Args &a, int row, int r0, int r1) {  // r0, r1: its entries
   if (!a.w_in) return {nullptr, r0};
   if (row >= a.n_split) return {a.w_halo + (scalar_load(a.halo_ptr, scalar_load(a.kept_ids, row - a.n_split)) - r0), r1};
-  if (!a.w_ptr) return {a.w_in, r1};
-  const int i0 = scalar_load(a.w_ptr, row);
-  return {a.w_in + (i0 - r0), r0 + (scalar_load(a.w_ptr, row + 1) - i0)};
+  const int2 ii = scalar_load_pair(a.w_ptr, row);
+  return {a.w_in + (ii.x - r0), r0 + (ii.y - ii.x)};
 }
 
 // Feature-row address and weight of an entry with the stacked column index c of row `row`; inner(): its weight if c
@@ -206,8 +212,8 @@ __device__ __forceinline__ void entry_source(Args &a, int row, int c, int d_off,
 // halves and the weight, through the LDS pipe) bound the gather: that pipe was busy half of the time.  With 16 lanes
 // per row the broadcast inside a lane group is one DPP move instead (a plain vector instruction): 685 -> 651 us on
 // 32.9 M entries of 64 floats in L2, 228 -> 195 us for the padded 41-float rows of the same graph.  Rows of 32 lanes
-// come from beyond L2 and are bound by the fabric: there the DPP form only costs registers (569 -> 588 us on
-// 16.6 M entries), so they keep the cross-lane reads, as does the one-kernel layer.
+// come from beyond L2 and are bound by the fabric, and the DPP form (over two rows of 16 lanes) was the slower one
+// there: 836 -> 910 us on 12.8 M entries of 128 floats, one-kernel layer 694 -> 780.
 constexpr bool dpp_gather(int maxch, int lpr) { return maxch == 1 && lpr == 16; }
 
 // Which entry of a batch of 64 a lane fetches.  The wavefront walks EP = 64 / LPR entries per step, lane group g
@@ -233,90 +239,85 @@ __device__ __forceinline__ V load_row_piece(unsigned hi, unsigned lo, int at) {
   return *reinterpret_cast<G *>(__builtin_bit_cast(unsigned long long, (u2){lo, hi}) + (unsigned)at * 4u);
 }
 
-struct Entries { unsigned lo, hi, w; };  // feature-row address and weight of one entry per lane
-
-// Steps T0 .. T0 + 7 of a batch.  MASKED: the batch ends among them.
-template <bool MASKED, int T0, typename V, int VEC>
-__device__ __forceinline__ void gather_steps(const Entries &e, int first, int ep, int cnt, int at, float (&acc)[1][VEC]) {
-  V v[8];
-  float w[8];
-  auto step = [&](auto tc) {
-    constexpr int t = decltype(tc)::value, T = T0 + t;
-    const unsigned hi = row_bcast<T>(e.hi), lo = row_bcast<T>(e.lo);
-    if (MASKED) {
-      v[t] = V{};
-      if (first + t * ep < cnt) v[t] = load_row_piece<V>(hi, lo, at);
-    } else {
-      v[t] = load_row_piece<V>(hi, lo, at);
-    }
-    w[t] = __uint_as_float(row_bcast<T>(e.w));  // lanes past the end carry weight zero
-  };
-  step(std::integral_constant<int, 0>{}); step(std::integral_constant<int, 1>{});
-  step(std::integral_constant<int, 2>{}); step(std::integral_constant<int, 3>{});
-  step(std::integral_constant<int, 4>{}); step(std::integral_constant<int, 5>{});
-  step(std::integral_constant<int, 6>{}); step(std::integral_constant<int, 7>{});
-#pragma unroll
-  for (int t = 0; t < 8; ++t) vec_fma<VEC>(acc[0], w[t], v[t]);
-}
-
-// acc += sum over the cnt <= 64 entries of a batch, held one per lane (batch_entry; address p_l, weight w_l), of
-// w * feature row.  The lanes span the feature dimension (VEC floats per lane, MAXCH pieces of 64
-// lanes); with LPR < 64 lanes per row the wavefront walks 64/LPR neighbours at once, 4 or 8 loads in flight, and
+// acc += sum over the cnt <= 64 entries of a batch, held one per lane (batch_entry; address p_l, weight w_l, zero past
+// the end), of w * feature row.  The lanes span the feature dimension (VEC floats per lane, MAXCH pieces of 64
+// lanes); with LPR < 64 lanes per row the wavefront walks EP = 64/LPR neighbours at once, UNR loads in flight, and
 // every lane group keeps its own partial sums (fold_groups adds them).
 template <int VEC, int MAXCH, int LPR, bool DPP = false>
 __device__ __forceinline__ void gather_batch(unsigned long long p_l, float w_l, int cnt, int nvec,
                                              float (&acc)[MAXCH][VEC]) {
   using V = typename Vec<VEC>::T;
+  static_assert(!DPP || (MAXCH == 1 && LPR == 16), "a feature row per DPP row of 16 lanes");
   constexpr int EP = kWave / LPR;  // neighbours walked at once
+  constexpr int UNR = MAXCH == 1 && LPR >= 16 ? 8 : 4;
   const int lane = lane_id();
   const int g = lane / LPR, sl = lane % LPR;
-  const unsigned p_lo = (unsigned)p_l, p_hi = (unsigned)(p_l >> 32);
-  if constexpr (DPP) {
-    static_assert(MAXCH == 1 && LPR == 16, "one DPP row of 16 lanes per feature row");
-    const int at = min(sl, nvec - 1) * VEC;  // lanes past the row's pieces repeat the last one and store nothing
-    const Entries e{p_lo, p_hi, __float_as_uint(w_l)};
-    auto chunk = [&](auto t0c) {  // steps T0 .. T0 + 7 of the batch's 16
-      constexpr int T0 = decltype(t0c)::value;
-      if (T0 * EP >= cnt) return;
-      if ((T0 + 8) * EP <= cnt) gather_steps<false, T0, V, VEC>(e, T0 * EP + g, EP, cnt, at, acc);
-      else gather_steps<true, T0, V, VEC>(e, T0 * EP + g, EP, cnt, at, acc);
-    };
-    chunk(std::integral_constant<int, 0>{});
-    chunk(std::integral_constant<int, 8>{});
-    return;
-  }
-  constexpr int UNR = (MAXCH == 1 && LPR >= 32) ? 8 : 4;
-  for (int j = 0; j < cnt; j += UNR * EP) {
+  const unsigned lo_l = (unsigned)p_l, hi_l = (unsigned)(p_l >> 32), w_u = __float_as_uint(w_l);
+  // address and weight of this lane group's entry in step t (T: the same where it has to be a constant)
+  auto bcast = [&](auto tc, int t, unsigned &lo, unsigned &hi, unsigned &w) {
+    if constexpr (DPP) {
+      constexpr int T = decltype(tc)::value;
+      lo = row_bcast<T>(lo_l);
+      hi = row_bcast<T>(hi_l);
+      w = row_bcast<T>(w_u);
+    } else if constexpr (EP == 1) {
+      lo = __builtin_amdgcn_readlane(lo_l, t);
+      hi = __builtin_amdgcn_readlane(hi_l, t);
+      w = __builtin_amdgcn_readlane(w_u, t);
+    } else {
+      lo = __shfl(lo_l, t * EP + g, kWave);
+      hi = __shfl(hi_l, t * EP + g, kWave);
+      w = __shfl(w_u, t * EP + g, kWave);
+    }
+  };
+  // UNR steps from t0 (T0, where the step has to be a constant) on; TAIL: the batch ends among them
+  auto steps = [&](auto tail, auto t0c, int t0) {
+    constexpr bool TAIL = decltype(tail)::value;
+    constexpr int T0 = decltype(t0c)::value;
     V v[UNR][MAXCH];
-    float w[UNR];
-#pragma unroll
-    for (int t = 0; t < UNR; ++t) {
-      const int jj = j + t * EP + g;
-      const bool valid = jj < cnt;
+    unsigned w[UNR];
+    auto step = [&](auto tc) {
+      constexpr int t = decltype(tc)::value;
+      if (TAIL && (t0 + t) * EP >= cnt) return;
       unsigned lo, hi;
-      float wt;
-      if constexpr (EP == 1) {  // jj is uniform over the wavefront
-        const int js = __builtin_amdgcn_readfirstlane(jj) & (kWave - 1);
-        lo = __builtin_amdgcn_readlane(p_lo, js);
-        hi = __builtin_amdgcn_readlane(p_hi, js);
-        wt = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, w_l), js));
-      } else {
-        lo = __shfl(p_lo, jj & (kWave - 1), kWave);
-        hi = __shfl(p_hi, jj & (kWave - 1), kWave);
-        wt = __shfl(w_l, jj & (kWave - 1), kWave);
-      }
-      w[t] = valid ? wt : 0.f;
+      bcast(std::integral_constant<int, T0 + t>{}, t0 + t, lo, hi, w[t]);
 #pragma unroll
       for (int c = 0; c < MAXCH; ++c) {
         const int iv = c * kWave + sl;
-        v[t][c] = V{};
-                if (valid && iv < nvec) v[t][c] = load_row_piece<V>(hi, lo, iv * VEC);
+        if (TAIL || MAXCH > 1) {
+          v[t][c] = V{};
+          if ((EP == 1 || (t0 + t) * EP + g < cnt) && iv < nvec) v[t][c] = load_row_piece<V>(hi, lo, iv * VEC);
+        } else {  // lanes past the row's pieces repeat the last one and store nothing
+          v[t][c] = load_row_piece<V>(hi, lo, min(iv, nvec - 1) * VEC);
+        }
       }
+    };
+    step(std::integral_constant<int, 0>{}); step(std::integral_constant<int, 1>{});
+    step(std::integral_constant<int, 2>{}); step(std::integral_constant<int, 3>{});
+    if constexpr (UNR == 8) {
+      step(std::integral_constant<int, 4>{}); step(std::integral_constant<int, 5>{});
+      step(std::integral_constant<int, 6>{}); step(std::integral_constant<int, 7>{});
     }
 #pragma unroll
-    for (int t = 0; t < UNR; ++t)
+    for (int t = 0; t < UNR; ++t) {
+      if (TAIL && (t0 + t) * EP >= cnt) break;
 #pragma unroll
-      for (int c = 0; c < MAXCH; ++c) vec_fma<VEC>(acc[c], w[t], v[t][c]);
+      for (int c = 0; c < MAXCH; ++c) vec_fma<VEC>(acc[c], __uint_as_float(w[t]), v[t][c]);
+    }
+  };
+  if constexpr (DPP) {
+    auto chunk = [&](auto t0c) {
+      constexpr int T0 = decltype(t0c)::value;
+      if (T0 * EP >= cnt) return;
+      if ((T0 + UNR) * EP <= cnt) steps(std::false_type{}, t0c, T0);
+      else steps(std::true_type{}, t0c, T0);
+    };
+    chunk(std::integral_constant<int, 0>{});
+    chunk(std::integral_constant<int, 8>{});
+  } else {
+    int t0 = 0;
+    for (; (t0 + UNR) * EP <= cnt; t0 += UNR) steps(std::false_type{}, std::integral_constant<int, 0>{}, t0);
+    if (t0 * EP < cnt) steps(std::true_type{}, std::integral_constant<int, 0>{}, t0);
   }
 }
 
