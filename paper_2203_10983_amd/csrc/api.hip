@@ -41,6 +41,8 @@ struct Layout {
   int32_t *tile_sums, *kept_start;
   uint64_t *ballots;
   int32_t *kpos;
+  uint64_t *bd_mask;   // keep flags of the boundary entries and their number per tile
+  int32_t *bd_sums;
   float *Hu, *Hu2, *G0, *G1, *G2, *loss_partials;  // Hu, Hu2: boundary rows at the output width
   int2 *halo_rec;  // per kept boundary node: (boundary index, weight) for the aggregates that read the rows in place
   // weight of every static entry with an inner column: forward (GCN only), transposed inner block, boundary nodes' lists
@@ -175,6 +177,8 @@ size_t carve(Carver &c, const bns_partition_desc *p, const bns_model_desc *m, La
   w.tile_sums = c.take<int32_t>(scan_tiles(p->nnz0 + n_in + B) + 4);
   w.kept_start = c.take<int32_t>((int64_t)B + 1);
   w.ballots = c.take<uint64_t>((B + 63) / 64 + 1);
+  w.bd_mask = c.take<uint64_t>((p->e_bd + 63) / 64);
+  w.bd_sums = c.take<int32_t>(scan_tiles(p->e_bd));
   w.kpos = c.take<int32_t>(p->e_bd + 1);
   w.Hu = c.take<float>(B * d_out_max);
   w.Hu2 = c.take<float>(B * d_first_max);
@@ -602,16 +606,20 @@ void add_pack_jobs(const bns_ctx *ctx, int l, const float *W, bool fwd, bool bwd
 }
 constexpr int kPackLayers = kMaxPackJobs / 4;  // layers whose jobs fit one launch
 
-// pack (nullable): a training step's: weights to pack beside the sampling, and the records of the kept nodes too
+BdCount bd_count(const bns_ctx *ctx) { return BdCount{ctx->part.e_bd, ctx->ws.split.bd_b, ctx->ws.bd_mask, ctx->ws.bd_sums}; }
+
+// pack (nullable): a training step's: weights to pack beside the sampling, and the records of the kept nodes and the
+// count of the kept boundary entries too
 bns_status sample_impl(bns_ctx *ctx, uint64_t seed, uint32_t epoch, const uint32_t *epoch_dev, double p,
                        int32_t *kept_ids, int32_t *remap, int32_t *n_kept, const PackJobs *pack, hipStream_t s) {
   const uint64_t threshold = (uint64_t)std::floor(p * 4294967296.0);
+  const BdCount count = bd_count(ctx);
   PhaseTimer t(ctx, BNS_PHASE_SAMPLE, s);
   BNS_TRY("sample_boundary",
           sample_boundary(ctx->part.halo_gid, ctx->part.n_halo, seed, epoch, epoch_dev, (uint32_t)ctx->part.part_id,
                           threshold, ctx->ws.ballots, ctx->ws.tile_sums, kept_ids, remap, n_kept, ctx->part.halo_ptr,
                           (int32_t)ctx->part.e_in, ctx->ws.kept_start, pack ? ctx->ws.halo_rec : nullptr,
-                          ctx->layer_kind == 1 ? nullptr : ctx->ws.dis_halo, halo_scale(p), pack, s));
+                          ctx->layer_kind == 1 ? nullptr : ctx->ws.dis_halo, halo_scale(p), pack, pack ? &count : nullptr, s));
   ctx->cur_kept = kept_ids;
   ctx->cur_remap = remap;
   ctx->cur_n_kept = n_kept;
@@ -622,18 +630,21 @@ bns_status sample_impl(bns_ctx *ctx, uint64_t seed, uint32_t epoch, const uint32
 }
 
 bns_status build_impl(bns_ctx *ctx, int32_t *row_ptr, int32_t *col_idx, int32_t *t_row_ptr,
-                      int32_t *t_col_idx, int32_t *nnz, hipStream_t s) {
+                      int32_t *t_col_idx, int32_t *nnz, bool counted, hipStream_t s) {
   const bns_partition_desc &P = ctx->part;
   PhaseTimer t(ctx, BNS_PHASE_BUILD, s);
-  BNS_TRY("build_sampled_csr",
-          build_sampled_csr(P.n_in, P.e_in, P.e_bd, ctx->ws.split, ctx->ws.ballots, ctx->cur_remap, ctx->ws.kpos,
-                            ctx->ws.tile_sums, row_ptr, col_idx, nnz, s));
-  BNS_TRY("build_transposed_csr",
-          build_transposed_csr(P.n_in, P.n_halo, P.e_in, P.t_in_ptr, P.t_in_col, P.halo_ptr, P.halo_col,
-                               ctx->cur_kept, ctx->cur_n_kept, ctx->ws.kept_start,
-                               t_row_ptr, t_col_idx,
-                               // the workspace arrays hold the static rows since bns_create
-                               !(t_row_ptr == ctx->ws.t_row_ptr && t_col_idx == ctx->ws.t_col_idx), true, s));
+  SubgraphBuild g{};
+  g.n_in = P.n_in; g.n_halo = P.n_halo; g.e_in = P.e_in;
+  g.sp = ctx->ws.split;
+  g.bd = bd_count(ctx);
+  g.ballots = ctx->ws.ballots;
+  g.remap = ctx->cur_remap; g.kept_ids = ctx->cur_kept; g.n_kept = ctx->cur_n_kept; g.kept_start = ctx->ws.kept_start;
+  g.t_in_ptr = P.t_in_ptr; g.t_in_col = P.t_in_col; g.halo_ptr = P.halo_ptr; g.halo_col = P.halo_col;
+  g.kpos = ctx->ws.kpos;
+  g.row_ptr = row_ptr; g.col_idx = col_idx; g.nnz = nnz; g.t_row_ptr = t_row_ptr; g.t_col_idx = t_col_idx;
+  // the workspace arrays hold the static rows since bns_create
+  g.static_rows = !(t_row_ptr == ctx->ws.t_row_ptr && t_col_idx == ctx->ws.t_col_idx);
+  BNS_TRY("build_subgraph", build_subgraph(g, counted, s));
   ctx->cur_row_ptr = row_ptr;
   ctx->cur_col_idx = col_idx;
   ctx->cur_t_row_ptr = t_row_ptr;
@@ -650,7 +661,7 @@ bns_status sample_and_build_impl(bns_ctx *ctx, uint64_t seed, uint32_t epoch, co
   if (!sample_build_small_fits(P.n_in, P.n_halo, P.e_in, P.e_bd)) {
     const bns_status st = sample_impl(ctx, seed, epoch, epoch_dev, p, w.kept_ids, w.remap, w.counters, &pack, s);
     if (st != BNS_OK) return st;
-    return build_impl(ctx, w.row_ptr, w.col_idx, w.t_row_ptr, w.t_col_idx, w.counters + 1, s);
+    return build_impl(ctx, w.row_ptr, w.col_idx, w.t_row_ptr, w.t_col_idx, w.counters + 1, true, s);
   }
   const uint64_t threshold = (uint64_t)std::floor(p * 4294967296.0);
   PhaseTimer t(ctx, BNS_PHASE_SAMPLE, s);
@@ -718,10 +729,8 @@ bns_status bns_create(bns_ctx **out, const bns_partition_desc *part, const bns_m
   BNS_TRY("build_seg_plan(bwd)", build_seg_plan(part->n_in, part->e_in, part->t_in_ptr, &ctx->ws.plan_b, ctx->ws.seg_tmp_a,
                                                  ctx->ws.seg_tmp_b, ctx->ws.tile_sums, s));
   // the rows of the inner nodes in the workspace's transposed CSR are the same in every epoch
-  BNS_TRY("build_transposed_csr(static rows)",
-          build_transposed_csr(part->n_in, part->n_halo, part->e_in, part->t_in_ptr, part->t_in_col, part->halo_ptr,
-                               part->halo_col, nullptr, nullptr, ctx->ws.kept_start, ctx->ws.t_row_ptr,
-                               ctx->ws.t_col_idx, true, false, s));
+  BNS_TRY("copy_static_rows", copy_static_rows(part->n_in, part->e_in, part->t_in_ptr, part->t_in_col, ctx->ws.t_row_ptr,
+                                               ctx->ws.t_col_idx, s));
   BNS_TRY("set-up sync", hipStreamSynchronize(s));
   return BNS_OK;
 }
@@ -756,7 +765,7 @@ bns_status bns_build_sampled_csr(bns_ctx *ctx, const int32_t *remap, const int32
   // the keep bits of the latest sample sit in the workspace: the three arrays must be that sample's
   if (remap != ctx->cur_remap || kept_ids != ctx->cur_kept || n_kept != ctx->cur_n_kept)
     return fail(ctx, BNS_EINVAL, "remap / kept_ids / n_kept are not the outputs of the latest bns_sample_boundary");
-  return build_impl(ctx, row_ptr, col_idx, t_row_ptr, t_col_idx, nnz, static_cast<hipStream_t>(stream));
+  return build_impl(ctx, row_ptr, col_idx, t_row_ptr, t_col_idx, nnz, false, static_cast<hipStream_t>(stream));
 }
 
 bns_status bns_gcn_layer_fwd(bns_ctx *ctx, int32_t layer, double p, const float *H_in, const float *halo_h,

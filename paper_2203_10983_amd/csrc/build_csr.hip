@@ -14,8 +14,7 @@
 //   kept boundary entry k, row v -> col_idx[inner_ptr[v+1] + kpos[k]]
 #include <algorithm>
 
-#include "device_utils.hpp"
-#include "kernels.hpp"
+#include "build_device.hpp"
 
 namespace bns {
 
@@ -109,173 +108,193 @@ hipError_t build_static_split(int32_t n_in, const int32_t *row_ptr0, const int32
 }
 
 // ---------------------------------------------------------------------------------- per epoch
-// The keep decision of a boundary node is one bit of the sampler's ballot words (a table of
-// n_halo/8 bytes that stays in L2); the 4-byte rank is only fetched for kept entries.
-__device__ __forceinline__ bool kept_bit(const uint64_t *__restrict__ ballots, int b) {
-  return (ballots[b >> 6] >> (b & 63)) & 1ull;
+__global__ void __launch_bounds__(kBdThreads)
+bd_count_kernel(const BdCount c, const uint64_t *__restrict__ ballots) {
+  bd_count_tile(c, ballots, blockIdx.x);
 }
 
-// A tile of kScanTile boundary entries per workgroup; every wavefront owns a contiguous piece of
-// it and walks the piece 64 entries at a time, so that all reads and the kpos writes are
-// consecutive over the lanes.  The keep flags of a pass are one ballot word; positions inside a
-// pass come from the population count of the lower lanes' bits.
-constexpr int kWavesPerBlock = kThreads / kWave;
-constexpr int kPasses = kScanTile / kThreads;  // passes of 64 entries per wavefront
+struct FillArgs {
+  // kept boundary entries of the sampled CSR
+  int32_t n_in;
+  BdCount bd;
+  int bd_tiles;
+  const int32_t *bd_row, *remap, *inner_ptr;
+  int32_t *kpos, *col_idx;
+  // rows of the kept boundary nodes in the transposed CSR
+  const int32_t *n_kept, *kept_ids, *halo_ptr, *halo_col, *kept_start;
+  int32_t *t_tail_ptr, *t_col_idx;
+};
 
-__global__ void __launch_bounds__(kThreads)
-bd_keep_tile_sums_kernel(int64_t e_bd, const int32_t *__restrict__ bd_b,
-                         const uint64_t *__restrict__ ballots, int32_t *__restrict__ tile_sums) {
-  __shared__ int wave_cnt[kWavesPerBlock];
+// Positions of a tile's boundary entries, from the keep flags: those inside a pass come from the population count of
+// the lower lanes' bits.  A kept entry also gets its place in col_idx; the 4-byte rank is only fetched for those.
+__device__ __forceinline__ void bd_fill_tile(const FillArgs &a) {
+  __shared__ int wave_cnt[kBdWaves];
   const int lane = lane_id(), wid = threadIdx.x / kWave;
-  const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)wid * (kPasses * kWave);
+  const int64_t e_bd = a.bd.e_bd;
+  const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)wid * (kBdPasses * kWave);
+  unsigned long long mask[kBdPasses];
   int cnt = 0;
 #pragma unroll
-  for (int i = 0; i < kPasses; ++i) {
-    const int64_t k = base + i * kWave + lane;
-    const bool kept = k < e_bd && kept_bit(ballots, bd_b[k]);
-    cnt += __popcll(__ballot(kept));
-  }
-  if (lane == 0) wave_cnt[wid] = cnt;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    int total = 0;
-#pragma unroll
-    for (int w = 0; w < kWavesPerBlock; ++w) total += wave_cnt[w];
-    tile_sums[blockIdx.x] = total;
-  }
-}
-
-__global__ void __launch_bounds__(kThreads)
-bd_fill_kernel(int32_t n_in, int64_t e_bd, const int32_t *__restrict__ bd_b,
-               const int32_t *__restrict__ bd_row, const uint64_t *__restrict__ ballots,
-               const int32_t *__restrict__ remap, const int32_t *__restrict__ tile_counts, const int32_t *__restrict__ inner_ptr,
-               int32_t *__restrict__ kpos, int32_t *__restrict__ col_idx) {
-  __shared__ int wave_cnt[kWavesPerBlock];
-  const int lane = lane_id(), wid = threadIdx.x / kWave;
-  // kept boundary entries in the tiles before this one: summed here from the raw per-tile counts
-  const int tile_offset = tiles_before<kThreads>(tile_counts, blockIdx.x, gridDim.x, nullptr);
-  const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)wid * (kPasses * kWave);
-  int b[kPasses];
-  unsigned long long mask[kPasses];
-  int cnt = 0;
-#pragma unroll
-  for (int i = 0; i < kPasses; ++i) {
-    const int64_t k = base + i * kWave + lane;
-    b[i] = k < e_bd ? bd_b[k] : -1;
-    mask[i] = __ballot(b[i] >= 0 && kept_bit(ballots, b[i]));
+  for (int i = 0; i < kBdPasses; ++i) {
+    mask[i] = base + i * kWave < e_bd ? a.bd.mask[(base >> 6) + i] : 0ull;
     cnt += __popcll(mask[i]);
   }
   if (lane == 0) wave_cnt[wid] = cnt;
-  __syncthreads();
-  int run = tile_offset;  // kept boundary entries before this wavefront's piece
+  // kept boundary entries in the tiles before this one: summed here from the raw per-tile counts (ends with a barrier)
+  int run = tiles_before<kBdThreads>(a.bd.sums, blockIdx.x, a.bd_tiles, nullptr);
   for (int w = 0; w < wid; ++w) run += wave_cnt[w];
   const unsigned long long lower = (1ull << lane) - 1ull;
 #pragma unroll
-  for (int i = 0; i < kPasses; ++i) {
+  for (int i = 0; i < kBdPasses; ++i) {
     const int64_t k = base + i * kWave + lane;
     const bool kept = (mask[i] >> lane) & 1ull;
     const int pos = run + __popcll(mask[i] & lower);
     if (k < e_bd) {
-      kpos[k] = pos;
-      if (kept) col_idx[inner_ptr[bd_row[k] + 1] + pos] = n_in + remap[b[i]];
-      if (k == e_bd - 1) kpos[e_bd] = pos + (kept ? 1 : 0);
+      a.kpos[k] = pos;
+      if (kept) a.col_idx[a.inner_ptr[a.bd_row[k] + 1] + pos] = a.n_in + a.remap[a.bd.bd_b[k]];
+      if (k == e_bd - 1) a.kpos[e_bd] = pos + (kept ? 1 : 0);
     }
     run += __popcll(mask[i]);
   }
 }
 
+// Rows of the kept boundary nodes in the transposed CSR: kept node r (boundary node b =
+// kept_ids[r]) gets b's static list of inner neighbours.  Where each row starts was settled by the
+// sampler (a prefix sum of the list lengths in kept order, kept_start[0..n_kept]); eight lanes copy
+// one list and write the row's start.  The lists that are too long for eight lanes are left to the whole workgroup
+// (197 758 boundary nodes with up to 5 800 neighbours: 81 us with eight lanes for each list, now 16).
+constexpr int kLongList = 256;
+constexpr int kListsPerBlock = kBdThreads / 8;
+__device__ __forceinline__ void kept_rows_fill(const FillArgs &a, int block, int n_blocks) {
+  __shared__ int n_long, long_src[kListsPerBlock], long_len[kListsPerBlock], long_dst[kListsPerBlock];
+  const int sub = threadIdx.x & 7;
+  const int n = *a.n_kept;
+  if (block == 0 && threadIdx.x == 0) a.t_tail_ptr[n] = a.kept_start[n];
+  for (int r0 = block * kListsPerBlock; r0 < n; r0 += n_blocks * kListsPerBlock) {  // trip count uniform over the block
+    if (threadIdx.x == 0) n_long = 0;
+    __syncthreads();
+    const int r = r0 + (threadIdx.x >> 3);
+    if (r < n) {
+      const int b = a.kept_ids[r];
+      const int src = a.halo_ptr[b], len = a.halo_ptr[b + 1] - src;
+      const int dst = a.kept_start[r];
+      if (sub == 0) a.t_tail_ptr[r] = dst;
+      if (len <= kLongList) {
+        for (int i = sub; i < len; i += 8) a.t_col_idx[dst + i] = a.halo_col[src + i];
+      } else if (sub == 0) {
+        const int q = atomicAdd(&n_long, 1);
+        long_src[q] = src;
+        long_len[q] = len;
+        long_dst[q] = dst;
+      }
+    }
+    __syncthreads();
+    for (int q = 0; q < n_long; ++q)
+#pragma unroll 4
+      for (int i = threadIdx.x; i < long_len[q]; i += kBdThreads)
+        a.t_col_idx[long_dst[q] + i] = a.halo_col[long_src[q] + i];
+    __syncthreads();
+  }
+}
+
+__global__ void __launch_bounds__(kBdThreads) fill_kernel(const FillArgs a) {
+  if ((int)blockIdx.x < a.bd_tiles) bd_fill_tile(a);
+  else kept_rows_fill(a, blockIdx.x - a.bd_tiles, gridDim.x - a.bd_tiles);
+}
+
 // Row starts and the inner entries in one launch: both follow in closed form from kpos (row v's
 // entries move down by the kept boundary entries of the rows before it, kpos[bd_ptr[v]]; every
 // inner entry carries its row's bd_ptr, so it needs one gather).
+// The workgroups from `blocks` on copy the rows of the inner nodes in the transposed CSR, which never change (the
+// transpose of the inner-inner block), where the destination does not hold them yet.
+struct StaticRows {
+  const int32_t *ptr, *col;
+  int32_t *t_row_ptr, *t_col_idx;
+};
+
+__device__ __forceinline__ void copy_static(const StaticRows &st, int32_t n_in, int64_t e_in, int block, int n_blocks) {
+  for (int64_t i = (int64_t)block * kThreads + threadIdx.x; i < n_in + 1 + e_in; i += (int64_t)n_blocks * kThreads) {
+    if (i <= n_in) st.t_row_ptr[i] = st.ptr[i];
+    else st.t_col_idx[i - n_in - 1] = st.col[i - n_in - 1];
+  }
+}
+
+constexpr int kFinishPasses = 8, kFinishTile = kFinishPasses * kThreads;
+
 __global__ void __launch_bounds__(kThreads)
 finish_csr_kernel(int32_t n_in, int64_t e_in, int64_t e_bd, const int32_t *__restrict__ inner_ptr,
                   const int32_t *__restrict__ bd_ptr, const int32_t *__restrict__ kpos,
                   const int32_t *__restrict__ in_col, const int32_t *__restrict__ in_bdp,
-                  int32_t *__restrict__ row_ptr, int32_t *__restrict__ col_idx, int32_t *__restrict__ nnz) {
-  const int64_t stride = (int64_t)gridDim.x * kThreads;
+                  int32_t *__restrict__ row_ptr, int32_t *__restrict__ col_idx, int32_t *__restrict__ nnz, int blocks,
+                  const StaticRows st) {
+  if ((int)blockIdx.x >= blocks) {
+    copy_static(st, n_in, e_in, blockIdx.x - blocks, gridDim.x - blocks);
+    return;
+  }
+  const int64_t stride = (int64_t)blocks * kThreads;
   const int64_t t0 = (int64_t)blockIdx.x * kThreads + threadIdx.x;
   for (int64_t v = t0; v <= n_in; v += stride) {
     const int r = inner_ptr[v] + (e_bd > 0 ? kpos[bd_ptr[v]] : 0);
     row_ptr[v] = r;
     if (v == n_in) *nnz = r;
   }
-  for (int64_t j = t0; j < e_in; j += stride) col_idx[j + (e_bd > 0 ? kpos[in_bdp[j]] : 0)] = in_col[j];
+  // a tile of kFinishTile entries per workgroup and its reads all at once: they hang on each other (in_bdp, kpos, place)
+  const int64_t j0 = (int64_t)blockIdx.x * kFinishTile + threadIdx.x;
+  int c[kFinishPasses], k[kFinishPasses];
+#pragma unroll
+  for (int i = 0; i < kFinishPasses; ++i) {
+    const int64_t j = j0 + i * kThreads;
+    c[i] = j < e_in ? in_col[j] : 0;
+    k[i] = j < e_in && e_bd > 0 ? in_bdp[j] : -1;
+  }
+#pragma unroll
+  for (int i = 0; i < kFinishPasses; ++i) k[i] = k[i] >= 0 ? kpos[k[i]] : 0;
+#pragma unroll
+  for (int i = 0; i < kFinishPasses; ++i)
+    if (j0 + i * kThreads < e_in) col_idx[j0 + i * kThreads + k[i]] = c[i];
 }
 
-hipError_t build_sampled_csr(int32_t n_in, int64_t e_in, int64_t e_bd, const StaticSplit &sp,
-                             const uint64_t *ballots, const int32_t *remap, int32_t *kpos, int32_t *tile_sums,
-                             int32_t *row_ptr, int32_t *col_idx, int32_t *nnz, hipStream_t s) {
-  if (e_bd > 0) {
-    const int nb = scan_tiles(e_bd);
-    bd_keep_tile_sums_kernel<<<nb, kThreads, 0, s>>>(e_bd, sp.bd_b, ballots, tile_sums);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    bd_fill_kernel<<<nb, kThreads, 0, s>>>(n_in, e_bd, sp.bd_b, sp.bd_row, ballots, remap, tile_sums,
-                                           sp.inner_ptr, kpos, col_idx);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
+hipError_t build_subgraph(const SubgraphBuild &g, bool counted, hipStream_t s) {
+  hipError_t e = hipSuccess;
+  const int tiles = scan_tiles(g.bd.e_bd);
+  if (tiles > 0 && !counted) {
+    bd_count_kernel<<<tiles, kBdThreads, 0, s>>>(g.bd, g.ballots);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  int64_t blocks = (std::max<int64_t>(e_in, (int64_t)n_in + 1) + kThreads * 4 - 1) / (kThreads * 4);
-  if (blocks < 1) blocks = 1;
-  finish_csr_kernel<<<(unsigned)blocks, kThreads, 0, s>>>(n_in, e_in, e_bd, sp.inner_ptr, sp.bd_ptr, kpos, sp.in_col,
-                                                          sp.in_bdp, row_ptr, col_idx, nnz);
+  // eight lanes per list, for as many lists as there may be: beyond this many workgroups, most of which would find no
+  // kept node left, each one takes several
+  const int list_blocks = (int)std::min<int64_t>(((int64_t)g.n_halo + kListsPerBlock - 1) / kListsPerBlock, 4096);
+  if (tiles + list_blocks > 0) {
+    FillArgs a{};
+    a.n_in = g.n_in;
+    a.bd = g.bd;
+    a.bd_tiles = tiles;
+    a.bd_row = g.sp.bd_row; a.remap = g.remap; a.inner_ptr = g.sp.inner_ptr;
+    a.kpos = g.kpos; a.col_idx = g.col_idx;
+    a.n_kept = g.n_kept; a.kept_ids = g.kept_ids; a.halo_ptr = g.halo_ptr; a.halo_col = g.halo_col; a.kept_start = g.kept_start;
+    a.t_tail_ptr = g.t_row_ptr + g.n_in; a.t_col_idx = g.t_col_idx;
+    fill_kernel<<<tiles + list_blocks, kBdThreads, 0, s>>>(a);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
+  const int64_t work = std::max<int64_t>(g.e_in, (int64_t)g.n_in + 1);
+  const int blocks = (int)((work + kFinishTile - 1) / kFinishTile);
+  const int copy = g.static_rows ? std::min(blocks, 16384) : 0;
+  finish_csr_kernel<<<blocks + copy, kThreads, 0, s>>>(g.n_in, g.e_in, g.bd.e_bd, g.sp.inner_ptr, g.sp.bd_ptr, g.kpos,
+                                                       g.sp.in_col, g.sp.in_bdp, g.row_ptr, g.col_idx, g.nnz, blocks,
+                                                       StaticRows{g.t_in_ptr, g.t_in_col, g.t_row_ptr, g.t_col_idx});
   return hipGetLastError();
 }
 
-// ---------------------------------------------------------------------------------- transpose
-// Rows of the kept boundary nodes in the transposed CSR: kept node r (boundary node b =
-// kept_ids[r]) gets b's static list of inner neighbours.  Where each row starts was settled by the
-// sampler (a prefix sum of the list lengths in kept order, kept_start[0..n_kept]); eight lanes copy
-// one list and write the row's start.
+// ---------------------------------------------------------------------------------- set-up
 __global__ void __launch_bounds__(kThreads)
-kept_rows_fill_kernel(const int32_t *__restrict__ n_kept, const int32_t *__restrict__ kept_ids,
-                      const int32_t *__restrict__ halo_ptr, const int32_t *__restrict__ halo_col,
-                      const int32_t *__restrict__ kept_start, int32_t *__restrict__ t_tail_ptr,
-                      int32_t *__restrict__ t_col_idx) {
-  const int r = (blockIdx.x * kThreads + threadIdx.x) >> 3;
-  const int sub = threadIdx.x & 7;
-  const int n = *n_kept;
-  if (r == 0 && sub == 0) t_tail_ptr[n] = kept_start[n];
-  if (r >= n) return;
-  const int b = kept_ids[r];
-  const int src = halo_ptr[b], len = halo_ptr[b + 1] - src;
-  const int dst = kept_start[r];
-  if (sub == 0) t_tail_ptr[r] = dst;
-  for (int i = sub; i < len; i += 8) t_col_idx[dst + i] = halo_col[src + i];
+copy_static_kernel(const StaticRows st, int32_t n_in, int64_t e_in) {
+  copy_static(st, n_in, e_in, blockIdx.x, gridDim.x);
 }
 
-__global__ void __launch_bounds__(kThreads)
-copy_static_kernel(const int32_t *__restrict__ a_src, int64_t a_n, int32_t *__restrict__ a_dst,
-                   const int32_t *__restrict__ b_src, int64_t b_n, int32_t *__restrict__ b_dst) {
-  const int64_t stride = (int64_t)gridDim.x * kThreads;
-  for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < a_n + b_n; i += stride) {
-    if (i < a_n) a_dst[i] = a_src[i];
-    else b_dst[i - a_n] = b_src[i - a_n];
-  }
-}
-
-hipError_t build_transposed_csr(int32_t n_in, int32_t n_halo, int64_t e_in,
-                                const int32_t *t_in_ptr, const int32_t *t_in_col,
-                                const int32_t *halo_ptr, const int32_t *halo_col,
-                                const int32_t *kept_ids, const int32_t *n_kept,
-                                const int32_t *kept_start, int32_t *t_row_ptr, int32_t *t_col_idx,
-                                bool static_rows, bool kept_rows, hipStream_t s) {
-  // rows of inner nodes never change: the transpose of the inner-inner block (copied by a kernel,
-  // so that the whole step stays a plain chain of kernel nodes under graph capture)
-  if (static_rows) {
-    const int64_t n4 = ((int64_t)n_in + 1 + e_in + 3) / 4;
-    int64_t blocks = (n4 + kThreads - 1) / kThreads;
-    if (blocks > 16384) blocks = 16384;
-    copy_static_kernel<<<(unsigned)blocks, kThreads, 0, s>>>(t_in_ptr, (int64_t)n_in + 1, t_row_ptr, t_in_col,
-                                                            e_in, t_col_idx);
-  }
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  if (n_halo == 0 || !kept_rows) return hipSuccess;
-  // rows of kept boundary nodes: their static lists of inner neighbours, in kept order
-  const int64_t threads = (int64_t)n_halo * 8;
-  kept_rows_fill_kernel<<<(unsigned)((threads + kThreads - 1) / kThreads), kThreads, 0, s>>>(
-      n_kept, kept_ids, halo_ptr, halo_col, kept_start, t_row_ptr + n_in, t_col_idx);
+hipError_t copy_static_rows(int32_t n_in, int64_t e_in, const int32_t *t_in_ptr, const int32_t *t_in_col,
+                            int32_t *t_row_ptr, int32_t *t_col_idx, hipStream_t s) {
+  const int64_t blocks = std::min<int64_t>(((int64_t)n_in + 1 + e_in + 4 * kThreads - 1) / (4 * kThreads), 16384);
+  copy_static_kernel<<<(unsigned)blocks, kThreads, 0, s>>>(StaticRows{t_in_ptr, t_in_col, t_row_ptr, t_col_idx}, n_in, e_in);
   return hipGetLastError();
 }
 

@@ -1,0 +1,48 @@
+// Device code of the subgraph step that more than one launch carries: the keep flags of a tile of boundary entries.
+#pragma once
+#include "device_utils.hpp"
+#include "kernels.hpp"
+
+namespace bns {
+
+// The keep decision of a boundary node is one bit of the sampler's ballot words (a table of
+// n_halo/8 bytes that stays in L2).
+__device__ __forceinline__ bool kept_bit(const uint64_t *__restrict__ ballots, int b) {
+  return (ballots[b >> 6] >> (b & 63)) & 1ull;
+}
+
+// A tile of kScanTile boundary entries per workgroup; every wavefront owns a contiguous piece of
+// it and walks the piece 64 entries at a time.  The keep flags of a pass are one ballot word, written out for the
+// pass over the same tile that places the entries; the number of kept entries per tile goes to sums.
+constexpr int kBdThreads = 256;
+constexpr int kBdWaves = kBdThreads / kWave;
+constexpr int kBdPasses = kScanTile / kBdThreads;  // passes of 64 entries per wavefront
+
+__device__ __forceinline__ void bd_count_tile(const BdCount &c, const uint64_t *__restrict__ ballots, int tile) {
+  __shared__ int wave_cnt[kBdWaves];
+  const int lane = lane_id(), wid = threadIdx.x / kWave;
+  const int64_t base = (int64_t)tile * kScanTile + (int64_t)wid * (kBdPasses * kWave);
+  int b[kBdPasses];
+#pragma unroll
+  for (int i = 0; i < kBdPasses; ++i) {
+    const int64_t k = base + i * kWave + lane;
+    b[i] = k < c.e_bd ? c.bd_b[k] : -1;
+  }
+  int cnt = 0;
+#pragma unroll
+  for (int i = 0; i < kBdPasses; ++i) {
+    const unsigned long long word = __ballot(b[i] >= 0 && kept_bit(ballots, b[i]));
+    if (lane == 0 && base + i * kWave < c.e_bd) c.mask[(base >> 6) + i] = word;
+    cnt += __popcll(word);
+  }
+  if (lane == 0) wave_cnt[wid] = cnt;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    int total = 0;
+#pragma unroll
+    for (int w = 0; w < kBdWaves; ++w) total += wave_cnt[w];
+    c.sums[tile] = total;
+  }
+}
+
+}  // namespace bns

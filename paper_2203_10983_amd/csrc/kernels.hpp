@@ -44,14 +44,22 @@ hipError_t pack_weights(const PackJobs &jobs, hipStream_t s);
 // without kept_start).  epoch_dev (nullable): the epoch index is read from device memory instead of
 // `epoch`.  halo_ptr + kept_start (both nullable): kept_start[r] = first + the summed lengths
 // halo_ptr[b+1] - halo_ptr[b] of the kept nodes before the r-th one, r = 0..n_kept (int32[B+1]): the
-// row starts of the kept nodes in the transposed subgraph, which build_transposed_csr reads.
+// row starts of the kept nodes in the transposed subgraph, which build_subgraph reads.
 // rec (nullable): rec[r] = (kept_ids[r], s_halo * dis_halo[kept_ids[r]]), as halo_records writes it.
 // pack (nullable): weights to pack in the same launch, on workgroups of their own.
+// count (nullable): flags and per-tile numbers of the kept boundary entries, for build_subgraph, also on workgroups of
+// their own.
+struct BdCount {
+  int64_t e_bd = 0;
+  const int32_t *bd_b = nullptr;  // boundary node of every boundary entry
+  uint64_t *mask = nullptr;       // uint64[ceil(e_bd/64)]: keep flags
+  int32_t *sums = nullptr;        // int32[scan_tiles(e_bd)]: kept entries per tile
+};
 hipError_t sample_boundary(const int64_t *halo_gid, int32_t n_halo, uint64_t seed, uint32_t epoch,
                            const uint32_t *epoch_dev, uint32_t part_id, uint64_t threshold, uint64_t *ballots,
                            int32_t *tile_sums, int32_t *kept_ids, int32_t *remap, int32_t *n_kept,
                            const int32_t *halo_ptr, int32_t first, int32_t *kept_start, int2 *rec, const float *dis_halo, float s_halo,
-                           const PackJobs *pack, hipStream_t s);
+                           const PackJobs *pack, const BdCount *count, hipStream_t s);
 
 // ---- build_csr.hip (Algorithm 1, subgraph step) -----------------------------------------------
 struct StaticSplit {       // inner / boundary split of the static CSR, built once
@@ -69,26 +77,29 @@ hipError_t build_static_split(int32_t n_in, const int32_t *row_ptr0, const int32
 hipError_t entry_weights(int64_t n, const int32_t *col, const float *of, float *w, hipStream_t s);
 hipError_t degree_rsqrt(const int32_t *deg, int32_t n, float *dis, hipStream_t s);
 
-// ballots: the keep bits written by sample_boundary (bit b%64 of word b/64); kpos: scratch
-// int32[e_bd+1]; tile_sums: scratch int32[scan_tiles(e_bd)+1].
-hipError_t build_sampled_csr(int32_t n_in, int64_t e_in, int64_t e_bd, const StaticSplit &sp,
-                             const uint64_t *ballots, const int32_t *remap, int32_t *kpos, int32_t *tile_sums,
-                             int32_t *row_ptr, int32_t *col_idx, int32_t *nnz, hipStream_t s);
-// kept_start: the row starts of the kept nodes as sample_boundary left them (int32[n_kept+1]).
-// static_rows: write the rows of the inner nodes (the transposed inner-inner block, the same every
-// epoch: a destination that already holds them can skip it); kept_rows: write the rows of the kept
-// boundary nodes.
-hipError_t build_transposed_csr(int32_t n_in, int32_t n_halo, int64_t e_in,
-                                const int32_t *t_in_ptr, const int32_t *t_in_col,
-                                const int32_t *halo_ptr, const int32_t *halo_col,
-                                const int32_t *kept_ids, const int32_t *n_kept,
-                                const int32_t *kept_start, int32_t *t_row_ptr, int32_t *t_col_idx,
-                                bool static_rows, bool kept_rows, hipStream_t s);
+// Subgraph step: the sampled CSR and the rows of the kept boundary nodes in its transpose.
+struct SubgraphBuild {
+  int32_t n_in, n_halo;
+  int64_t e_in;
+  StaticSplit sp;
+  BdCount bd;
+  const uint64_t *ballots;     // the keep bits written by sample_boundary (bit b%64 of word b/64)
+  const int32_t *remap, *kept_ids, *n_kept;
+  const int32_t *kept_start;   // row starts of the kept nodes as sample_boundary left them, int32[n_kept+1]
+  const int32_t *t_in_ptr, *t_in_col, *halo_ptr, *halo_col;
+  int32_t *kpos;               // scratch int32[e_bd+1]
+  int32_t *row_ptr, *col_idx, *nnz, *t_row_ptr, *t_col_idx;
+  bool static_rows;            // also write the rows of the inner nodes (the transposed inner-inner block, the same every
+                               // epoch: a destination that already holds them can skip it)
+};
+// counted: the launch of sample_boundary has filled bd.mask and bd.sums.
+hipError_t build_subgraph(const SubgraphBuild &g, bool counted, hipStream_t s);
+hipError_t copy_static_rows(int32_t n_in, int64_t e_in, const int32_t *t_in_ptr, const int32_t *t_in_col,
+                            int32_t *t_row_ptr, int32_t *t_col_idx, hipStream_t s);
 
 // ---- small.hip: selection step + subgraph step of a small partition in one launch -------------
-// One workgroup runs the stages of sample_boundary, build_sampled_csr and the kept rows of
-// build_transposed_csr back to back and writes the same arrays (t_row_ptr / t_col_idx must already
-// hold the static rows of the inner nodes).  Only for sizes within the limits below, where the six
+// One workgroup runs the stages of sample_boundary and build_subgraph back to back and writes the same arrays (t_row_ptr / t_col_idx must already
+// hold the static rows of the inner nodes).  Only for sizes within the limits below, where the four
 // launches of the general path cost more than the work itself.
 constexpr int kSmallMaxHalo = 4096;              // boundary nodes
 constexpr int kSmallMaxBoundaryEntries = 8192;   // entries with a boundary column

@@ -2,8 +2,7 @@
 // independently with probability p, decided by a counter-based draw so that the decision
 // depends only on (seed, epoch, partition, global node id).  Kept nodes are compacted in
 // ascending order with wavefront ballots and prefix sums.
-#include "device_utils.hpp"
-#include "kernels.hpp"
+#include "build_device.hpp"
 #include "pack_device.hpp"
 
 namespace bns {
@@ -78,21 +77,26 @@ sample_flags_kernel(const int64_t *__restrict__ halo_gid, int32_t n_halo, uint32
 // row in the transposed subgraph, first + the list lengths of the kept nodes before it, comes from a
 // block scan over just the kept ones: kept_start[rank], and kept_start[n_kept] = the end.  With rec, the
 // record that the forward aggregates read per kept node (its boundary index and weight) goes with it.
-// Block 0 also writes the totals.
+// Block 0 also writes the totals.  The blocks from `tiles` on count the kept boundary entries, which needs the keep
+// bits alone.
 __global__ void __launch_bounds__(kSampleThreads)
 sample_write_kernel(int32_t n_halo, const uint64_t *__restrict__ ballots,
                     const int32_t *__restrict__ tile_counts, int32_t *__restrict__ kept_ids,
                     int32_t *__restrict__ remap, int32_t *__restrict__ n_kept,
                     const int32_t *__restrict__ halo_ptr, int32_t first, int32_t *__restrict__ kept_start,
-                    int2 *__restrict__ rec, const float *__restrict__ dis_halo, float s_halo) {
+                    int2 *__restrict__ rec, const float *__restrict__ dis_halo, float s_halo, int tiles, const BdCount count) {
+  if ((int)blockIdx.x >= tiles) {
+    bd_count_tile(count, ballots, blockIdx.x - tiles);
+    return;
+  }
   __shared__ int word_prefix[kWordsPerTile + 1];
   __shared__ int kept_b[kScanTile];
   const int lane = lane_id();
   int total = 0, len_total = 0;
-  const int base = tiles_before<kSampleThreads>(tile_counts, blockIdx.x, gridDim.x, blockIdx.x == 0 ? &total : nullptr);
+  const int base = tiles_before<kSampleThreads>(tile_counts, blockIdx.x, tiles, blockIdx.x == 0 ? &total : nullptr);
   int run = first;
   if (halo_ptr)
-    run += tiles_before<kSampleThreads>(tile_counts + gridDim.x, blockIdx.x, gridDim.x,
+    run += tiles_before<kSampleThreads>(tile_counts + tiles, blockIdx.x, tiles,
                                         blockIdx.x == 0 ? &len_total : nullptr);
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     *n_kept = total;
@@ -146,7 +150,8 @@ hipError_t sample_boundary(const int64_t *halo_gid, int32_t n_halo, uint64_t see
                            const uint32_t *epoch_dev, uint32_t part_id, uint64_t threshold, uint64_t *ballots,
                            int32_t *tile_sums, int32_t *kept_ids, int32_t *remap, int32_t *n_kept,
                            const int32_t *halo_ptr, int32_t first, int32_t *kept_start, int2 *rec, const float *dis_halo, float s_halo,
-                           const PackJobs *pack, hipStream_t s) {
+                           const PackJobs *pack, const BdCount *count, hipStream_t s) {
+  static_assert(kSampleThreads == kBdThreads, "one launch carries both");
   if (!kept_start) halo_ptr = nullptr;
   const int nb = scan_tiles(n_halo) > 0 ? scan_tiles(n_halo) : 1;
   const PackJobs jobs = pack ? *pack : PackJobs{};
@@ -156,8 +161,8 @@ hipError_t sample_boundary(const int64_t *halo_gid, int32_t n_halo, uint64_t see
                                                     threshold, halo_ptr, ballots, tile_sums, nb, jobs);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  sample_write_kernel<<<nb, kSampleThreads, 0, s>>>(n_halo, ballots, tile_sums, kept_ids, remap, n_kept,
-                                                    halo_ptr, first, kept_start, rec, dis_halo, s_halo);
+  sample_write_kernel<<<nb + (count ? scan_tiles(count->e_bd) : 0), kSampleThreads, 0, s>>>(n_halo, ballots, tile_sums, kept_ids, remap, n_kept,
+                                                    halo_ptr, first, kept_start, rec, dis_halo, s_halo, nb, count ? *count : BdCount{});
   return hipGetLastError();
 }
 
