@@ -51,6 +51,7 @@ __global__ void __launch_bounds__(kFThreads, 6) __attribute__((amdgpu_num_sgpr(9
   // ---- phase 0: the tile's row bounds into LDS (one coalesced read instead of a dependent chain
   // per row).  s_e0/s_e1: entries to gather; s_e1 < 0 marks a row finished by the segmented pass.
   __shared__ int s_e0[kFM], s_e1[kFM], s_wd[kFM];  // s_wd: from an entry to its place in w_in
+  __shared__ unsigned char s_order[kFM];  // the tile's rows, longest class first
   __shared__ int next_row;
   if (threadIdx.x < kFM) {
     const int row = row0 + threadIdx.x;
@@ -66,6 +67,17 @@ __global__ void __launch_bounds__(kFThreads, 6) __attribute__((amdgpu_num_sgpr(9
     s_e0[threadIdx.x] = e0;
     s_e1[threadIdx.x] = e1;
     s_wd[threadIdx.x] = wd;
+    // A long row that is taken last keeps the whole tile waiting: the rows are taken in classes of falling length
+    // (21 entries a row and a power-law tail: 696 -> 677 us).  The lanes of this wavefront are the rows.
+    const int len = e1 - e0, cls = len > 0 ? 32 - __clz(len) : 0;
+    int before = 0, place = 0;
+#pragma unroll
+    for (int c = 9; c >= 0; --c) {  // lengths up to kSegLen = 256
+      const unsigned long long m = __ballot(cls == c);
+      if (cls == c) place = before + __popcll(m & ((1ull << lane) - 1ull));
+      before += __popcll(m);
+    }
+    s_order[place] = (unsigned char)threadIdx.x;
   }
   if (threadIdx.x == 0) next_row = 0;
   __syncthreads();
@@ -77,7 +89,7 @@ __global__ void __launch_bounds__(kFThreads, 6) __attribute__((amdgpu_num_sgpr(9
   auto grab = [&]() -> int {
     int r = 0;
     if (lane == 0) r = atomicAdd(&next_row, 1);
-    return __builtin_amdgcn_readfirstlane(r);
+    return __builtin_amdgcn_readfirstlane(r < kFM ? s_order[r] : kFM);
   };
   auto first_cnt = [&](int lrow) -> int {  // entries of the row's first batch
     if (lrow >= kFM) return 0;
