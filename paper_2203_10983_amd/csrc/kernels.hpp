@@ -127,6 +127,7 @@ struct SegPlan {
   int32_t *mrow;      // int32[n_multi]  rows with more than one segment
   int2 *part_unit;    // int2[n_part]    row of each partial-sum slot, slot
   int32_t n_seg, n_part, n_multi;  // host copies of the totals
+  int32_t max_seg;                 // segments of the longest row
   int32_t avg_len;                 // entries per row of the static pattern (launch heuristics)
 };
 inline int64_t seg_max_segments(int64_t rows, int64_t nnz) { return rows + nnz / kSegLen + 1; }

@@ -19,9 +19,13 @@
 
 namespace bns {
 
-template <int VEC, int MAXCH, int LPR, bool NARROW = false>
-__global__ void __launch_bounds__(256, MAXCH == 1 ? 8 : 1) spmm_kernel(const SpmmArgs) {
+// BLOCK: workgroups of kBlockWaves wavefronts; the first a.n_block_rows of them own a multi-segment row each, one
+// wavefront per segment, and add the partial sums in LDS (same order as spmm_combine_kernel, same bits).
+constexpr int kBlockWaves = 8;
+template <int VEC, int MAXCH, int LPR, bool NARROW = false, bool BLOCK = false>
+__global__ void __launch_bounds__(BLOCK ? kBlockWaves * kWave : 256, MAXCH == 1 ? 8 : 1) spmm_kernel(const SpmmArgs) {
   using V = typename Vec<VEC>::T;
+  constexpr int kWaves = BLOCK ? kBlockWaves : 4;
   const int lane = lane_id();
   const int g = lane / LPR, sl = lane % LPR;
   int bid = blockIdx.x, nblk = gridDim.x, d_off = 0, n_units;
@@ -37,7 +41,53 @@ __global__ void __launch_bounds__(256, MAXCH == 1 ? 8 : 1) spmm_kernel(const Spm
     n_units = a.n_units + (a.n_extra_dev ? scalar_load(a.n_extra_dev, 0) : 0);
   }
   // (the unit is the same for the whole wavefront, so that its bounds come through the scalar cache)
-  for (int unit = bid * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); unit < n_units; unit += nblk * 4) {
+  const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if constexpr (BLOCK) {
+    ArgBlock &a = unit_args();
+    const int n_rows = a.n_block_rows;
+    if (bid < n_rows) {
+      extern __shared__ __attribute__((aligned(16))) float block_part[];
+      const int nvec = a.d_slice / VEC;
+      const int row = scalar_load(a.plan.mrow, bid);
+      const int2 ee = scalar_load_pair(a.row_ptr, row);
+      int e0 = ee.x, e1 = ee.y;
+      const InnerWeights iw = inner_weights(a, row, e0, e1);
+      if (a.row_skip) e0 += scalar_load(a.row_skip, row);
+      if (a.row_take) e1 = e0 + scalar_load(a.row_take, row);
+      const int2 seg = scalar_load_pair(a.plan.seg_ptr, row);
+      const int nseg = seg.y - seg.x;  // <= kWaves
+      const int chunk = (e1 - e0 + nseg - 1) / nseg;
+      float acc[MAXCH][VEC];
+      if (wid < nseg) {
+        const int b = min(e1, e0 + wid * chunk);
+        gather_segment<VEC, MAXCH, LPR>(a, row, iw, b, min(e1, b + chunk), d_off, nvec, acc);
+        if (g == 0) {
+#pragma unroll
+          for (int c = 0; c < MAXCH; ++c)
+            if (c * kWave + sl < nvec)
+#pragma unroll
+              for (int i = 0; i < VEC; ++i) block_part[wid * nvec * VEC + (c * kWave + sl) * VEC + i] = acc[c][i];
+        }
+      }
+      __syncthreads();
+      if (wid != 0) return;
+#pragma unroll
+      for (int c = 0; c < MAXCH; ++c)
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) acc[c][i] = 0.f;
+      for (int s = 0; s < nseg; ++s)
+#pragma unroll
+        for (int c = 0; c < MAXCH; ++c)
+          if (c * kWave + lane < nvec)
+#pragma unroll
+            for (int i = 0; i < VEC; ++i) acc[c][i] += block_part[s * nvec * VEC + (c * kWave + lane) * VEC + i];
+      finish_row<VEC, MAXCH, NARROW>(unit_args(), row, lane, nvec, d_off, acc);
+      return;
+    }
+    bid -= n_rows;
+    nblk -= n_rows;
+  }
+  for (int unit = bid * kWaves + wid; unit < n_units; unit += nblk * kWaves) {
     ArgBlock &a = unit_args();
     const int nvec = a.d_slice / VEC;
     int row = a.n_split + (unit - a.n_units), slot = -1;
@@ -45,6 +95,7 @@ __global__ void __launch_bounds__(256, MAXCH == 1 ? 8 : 1) spmm_kernel(const Spm
       const int2 u = scalar_load(a.units, unit);
       row = u.x;
       slot = u.y;
+      if (BLOCK && slot >= 0) continue;
     }
     const int2 ee = scalar_load_pair(a.row_ptr, row);
     int e0 = ee.x, e1 = ee.y;
@@ -126,12 +177,20 @@ __global__ void __launch_bounds__(256) spmm_combine_kernel(const SpmmArgs a) {
   finish_row<VEC, MAXCH, NARROW>(a, row, lane, nvec, 0, acc);
 }
 
+constexpr int kBlockRowsMaxSeg = 65536;
+
 template <int VEC>
 static hipError_t launch_spmm_vec(const SpmmArgs &a_in, int64_t max_units, bool multi_only, bool backward, hipStream_t s) {
   SpmmArgs a = a_in;
   // multi_only: the segments of the multi-segment rows, i.e. the partial-sum slots
   a.n_units = multi_only ? a.plan.n_part : a.plan.n_seg;
   a.units = multi_only ? a.plan.part_unit : a.plan.seg_unit;
+  // The pass over the partial sums is a launch of about 5 us.  Where the longest row has few segments and the launch is
+  // short, a workgroup per such row saves it; on more rows than fill the chip a few times the launch is nothing, and
+  // workgroups of eight wavefronts that wait for their longest row cost more.
+  const bool block_rows = !multi_only && a.plan.n_multi > 0 && a.plan.max_seg <= kBlockWaves && a.plan.n_seg <= kBlockRowsMaxSeg;
+  a.n_block_rows = block_rows ? a.plan.n_multi : 0;
+  const int waves = block_rows ? kBlockWaves : 4;
   // Wide rows are cut into slices of 128 floats (64 where rows are long enough to keep a
   // wavefront busy with a quarter of its lanes per neighbour); measured on the five workloads,
   // narrower slices lose more to the repeated index walk than the L2 gains: transposed aggregates of 128-float rows
@@ -149,9 +208,10 @@ static hipError_t launch_spmm_vec(const SpmmArgs &a_in, int64_t max_units, bool 
   // one wavefront per static segment; the kept boundary rows, whose count lives on the device,
   // are strided over by a bounded number of extra blocks (blocks past the count would only cost
   // dispatch time)
-  const int64_t extra_blocks = multi_only ? 0 : std::min<int64_t>((max_units - a.n_units + 3) / 4, 8192);
-  unsigned blocks = (unsigned)(((int64_t)a.n_units + 3) / 4 + std::max<int64_t>(extra_blocks, 0));
-  const unsigned cblocks = (unsigned)((a.plan.n_multi + 3) / 4);
+  const int64_t extra_blocks = multi_only ? 0 : std::min<int64_t>((max_units - a.n_units + waves - 1) / waves, 8192);
+  unsigned blocks = (unsigned)(a.n_block_rows + ((int64_t)a.n_units + waves - 1) / waves + std::max<int64_t>(extra_blocks, 0));
+  const unsigned cblocks = block_rows ? 0u : (unsigned)((a.plan.n_multi + 3) / 4);
+  const size_t block_lds = (size_t)kBlockWaves * a.d_slice * sizeof(float);  // at most 64 KB
   if (blocks == 0) return hipSuccess;
   if (ls > 0) {
     const unsigned per = 8 >> ls;
@@ -159,7 +219,11 @@ static hipError_t launch_spmm_vec(const SpmmArgs &a_in, int64_t max_units, bool 
   }
   if (a.d_store != a.d) {  // padded sources, dense narrower outputs: d < 128, four floats per lane
     if constexpr (VEC == 4) {
-#define BNS_SPMM_NARROW(LPR) spmm_kernel<4, 1, LPR, true><<<blocks, 256, 0, s>>>(a)
+#define BNS_SPMM_NARROW(LPR)                                                                                \
+  do {                                                                                                      \
+    if (block_rows) spmm_kernel<4, 1, LPR, true, true><<<blocks, kBlockWaves * kWave, block_lds, s>>>(a); \
+    else spmm_kernel<4, 1, LPR, true><<<blocks, 256, 0, s>>>(a);                                          \
+  } while (0)
       if (nvec <= 4) BNS_SPMM_NARROW(4);
       else if (nvec <= 8) BNS_SPMM_NARROW(8);
       else if (nvec <= 16) BNS_SPMM_NARROW(16);
@@ -170,7 +234,11 @@ static hipError_t launch_spmm_vec(const SpmmArgs &a_in, int64_t max_units, bool 
     }
     return hipErrorInvalidValue;
   }
-#define BNS_SPMM(MAXCH, LPR) spmm_kernel<VEC, MAXCH, LPR><<<blocks, 256, 0, s>>>(a)
+#define BNS_SPMM(MAXCH, LPR)                                                                                     \
+  do {                                                                                                           \
+    if (block_rows) spmm_kernel<VEC, MAXCH, LPR, false, true><<<blocks, kBlockWaves * kWave, block_lds, s>>>(a); \
+    else spmm_kernel<VEC, MAXCH, LPR><<<blocks, 256, 0, s>>>(a);                                               \
+  } while (0)
   if (nvec <= 1) BNS_SPMM(1, 1);
   else if (nvec <= 2) BNS_SPMM(1, 2);
   else if (nvec <= 4) BNS_SPMM(1, 4);
@@ -264,6 +332,22 @@ seg_fill_kernel(int32_t n_rows, const int32_t *__restrict__ seg_ptr, const int32
   }
 }
 
+// *out = the most segments of a row, over the *n multi-segment rows (1 if there is none)
+__global__ void __launch_bounds__(1024)
+seg_max_kernel(const int32_t *__restrict__ n, const int32_t *__restrict__ mrow, const int32_t *__restrict__ seg_ptr,
+               int32_t *__restrict__ out) {
+  __shared__ int part[1024 / kWave];
+  int m = 1;
+  for (int j = threadIdx.x; j < *n; j += 1024) m = max(m, seg_ptr[mrow[j] + 1] - seg_ptr[mrow[j]]);
+  for (int off = kWave / 2; off > 0; off >>= 1) m = max(m, __shfl_xor(m, off, kWave));
+  if (lane_id() == 0) part[threadIdx.x / kWave] = m;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < 1024 / kWave; ++w) m = max(m, part[w]);
+    *out = m;
+  }
+}
+
 hipError_t build_seg_plan(int32_t n_rows, int64_t nnz, const int32_t *row_ptr, SegPlan *plan, int32_t *tmp_a,
                           int32_t *tmp_b, int32_t *tile_sums, hipStream_t s) {
   const unsigned blocks = (unsigned)((n_rows + 255) / 256);
@@ -278,21 +362,25 @@ hipError_t build_seg_plan(int32_t n_rows, int64_t nnz, const int32_t *row_ptr, S
   if (e != hipSuccess) return e;
   seg_fill_kernel<<<blocks, 256, 0, s>>>(n_rows, plan->seg_ptr, tmp_b, plan->part_ptr, plan->seg_unit, plan->mrow,
                                          plan->part_unit);
+  seg_max_kernel<<<1, 1024, 0, s>>>(tmp_b + n_rows, plan->mrow, plan->seg_ptr, tmp_a);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  // the three totals size the launches: bring them to the host (set-up only)
-  int32_t tot[3];
+  // the totals size the launches: bring them to the host (set-up only)
+  int32_t tot[4];
   e = hipMemcpyAsync(&tot[0], plan->seg_ptr + n_rows, 4, hipMemcpyDeviceToHost, s);
   if (e != hipSuccess) return e;
   e = hipMemcpyAsync(&tot[1], plan->part_ptr + n_rows, 4, hipMemcpyDeviceToHost, s);
   if (e != hipSuccess) return e;
   e = hipMemcpyAsync(&tot[2], tmp_b + n_rows, 4, hipMemcpyDeviceToHost, s);
   if (e != hipSuccess) return e;
+  e = hipMemcpyAsync(&tot[3], tmp_a, 4, hipMemcpyDeviceToHost, s);
+  if (e != hipSuccess) return e;
   e = hipStreamSynchronize(s);
   if (e != hipSuccess) return e;
   plan->n_seg = tot[0];
   plan->n_part = tot[1];
   plan->n_multi = tot[2];
+  plan->max_seg = tot[3];
   plan->avg_len = n_rows > 0 ? (int32_t)(nnz / n_rows) : 0;
   return hipSuccess;
 }

@@ -26,6 +26,7 @@ struct SpmmArgs {
   SegPlan plan;                // static segmentation of rows 0..n_split-1
   int32_t n_units;             // work units of the kernel: segments of the plan, (row, partial-sum slot or -1)
   const int2 *units;
+  int32_t n_block_rows;        // BLOCK kernels: workgroups in front that own a multi-segment row of the plan each
   const int32_t *n_extra_dev;  // nullable: *n_extra_dev further single-segment rows follow (kept boundary)
   int32_t d;                   // floats per gathered row = row stride of src0, src1 and the partial sums
   const int32_t *row_ptr, *col_idx;
