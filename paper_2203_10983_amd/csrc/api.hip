@@ -423,6 +423,13 @@ bns_status layer_fwd_impl(bns_ctx *ctx, int layer, double p, const float *H_in, 
   return BNS_OK;
 }
 
+// Does the backward pass of `layer` gather its dZ at the output width, in padded rows?
+bool pads_gradient(const bns_ctx *ctx, int layer, bool update_first, bool input_gradient) {
+  const int d_in = ctx->dims[layer - 1], d_out = ctx->dims[layer];
+  if (gather_stride(d_in, d_out) == d_out) return false;
+  return update_first || (ctx->layer_kind == 0 && input_gradient && d_out < d_in);
+}
+
 // The weight gradients of several layers, to be run together.
 struct TnBatch {
   TnGemm g[kMaxTnJobs];
@@ -441,10 +448,11 @@ bns_status run_batch(bns_ctx *ctx, TnBatch *batch, const TnLoss &loss, hipStream
 // H_in is needed by the mean-aggregator layer only (its self half of the weight gradient).
 // halo_first (nullable): the boundary features of an update-first layer (A_saved does not hold
 // the aggregate then); the weight gradient is [H_in ; Hu]^T (P^T dZ) instead of A^T dZ.
+// dz_padded: G2 holds dZ with padded rows already (pads_gradient).
 bns_status layer_bwd_impl(bns_ctx *ctx, int layer, double p, const float *dZ, const float *A_saved,
                           const float *H_in, float *dW, float *dH_in, float *dhalo, const float *mask_src,
-                          bool update_first, const float *halo_first, float *W_step, float lr, TnBatch *batch,
-                          hipStream_t s) {
+                          bool update_first, const float *halo_first, float *W_step, float lr, bool dz_padded,
+                          TnBatch *batch, hipStream_t s) {
   const int n_in = ctx->part.n_in, B = ctx->part.n_halo;
   const int d_in = ctx->dims[layer - 1], d_out = ctx->dims[layer];
   const char *Wb = ctx->ws.Wb[layer];
@@ -496,7 +504,7 @@ bns_status layer_bwd_impl(bns_ctx *ctx, int layer, double p, const float *dZ, co
       const int ld = gather_stride(d_in, d_out);
       const float *dZ_g = dZ;
       if (ld != d_out) {  // the gathered operand with padded rows
-        BNS_TRY("pad_rows", pad_rows(n_in, d_out, ld, dZ, ctx->ws.G2, s));
+        if (!dz_padded) BNS_TRY("pad_rows", pad_rows(n_in, d_out, ld, dZ, ctx->ws.G2, s));
         dZ_g = ctx->ws.G2;
       }
       BNS_TRY("spmm_bwd", spmm_bwd(ctx->ws.plan_b, n_in, B, ld, ctx->cur_t_row_ptr, ctx->cur_t_col_idx,
@@ -550,7 +558,7 @@ bns_status layer_bwd_impl(bns_ctx *ctx, int layer, double p, const float *dZ, co
       const int ld = gather_stride(d_in, d_out);
       const float *dZ_g = dZ;
       if (ld != d_out) {  // the gathered operand with padded rows
-        BNS_TRY("pad_rows", pad_rows(n_in, d_out, ld, dZ, ctx->ws.G2, s));
+        if (!dz_padded) BNS_TRY("pad_rows", pad_rows(n_in, d_out, ld, dZ, ctx->ws.G2, s));
         dZ_g = ctx->ws.G2;
       }
       BNS_TRY("spmm_bwd", spmm_bwd(ctx->ws.plan_b, n_in, B, ld, ctx->cur_t_row_ptr, ctx->cur_t_col_idx,
@@ -805,7 +813,7 @@ bns_status bns_gcn_layer_bwd(bns_ctx *ctx, int32_t layer, double p, const float 
   }
   TnBatch batch;
   const bns_status st = layer_bwd_impl(ctx, layer, p, dZ, A_saved, H_in, dW, dH_in, dhalo, nullptr, false, nullptr, nullptr,
-                                       0.f, &batch, s);
+                                       0.f, false, &batch, s);
   return st != BNS_OK ? st : run_batch(ctx, &batch, TnLoss{}, s);
 }
 
@@ -845,13 +853,17 @@ static bns_status train_step_impl(bns_ctx *ctx, uint64_t seed, uint32_t epoch, c
 
   const int C = ctx->dims[L];
   TnLoss loss_sum{w.loss_partials, 0, loss};
+  // where the last layer's backward pass gathers padded rows of dZ, the loss leaves them beside dZ
+  const bool pad_last = pads_gradient(ctx, L, layer_plan(ctx, L, X) == BNS_LAYER_UPDATE_FIRST, L > 1);
+  const int ld = gather_stride(ctx->dims[L - 1], C);
+  float *dZ_pad = pad_last ? w.G2 : nullptr;
   {
     PhaseTimer t(ctx, BNS_PHASE_LOSS, s);
     if (ctx->loss_kind == 0)
-      BNS_TRY("loss_softmax_ce", loss_softmax_ce(n_in, C, w.H[L], static_cast<const int32_t *>(labels), w.dZ[L],
+      BNS_TRY("loss_softmax_ce", loss_softmax_ce(n_in, C, w.H[L], static_cast<const int32_t *>(labels), w.dZ[L], ld, dZ_pad,
                                                  w.loss_partials, &loss_sum.n, s));
     else
-      BNS_TRY("loss_sigmoid_bce", loss_sigmoid_bce(n_in, C, w.H[L], static_cast<const uint8_t *>(labels), w.dZ[L],
+      BNS_TRY("loss_sigmoid_bce", loss_sigmoid_bce(n_in, C, w.H[L], static_cast<const uint8_t *>(labels), w.dZ[L], ld, dZ_pad,
                                                    w.loss_partials, &loss_sum.n, s));
   }
 
@@ -864,7 +876,7 @@ static bns_status train_step_impl(bns_ctx *ctx, uint64_t seed, uint32_t epoch, c
     st = layer_bwd_impl(ctx, l, p, w.dZ[l], w.A[l], l > 1 ? w.H[l - 1] : X, dW[l - 1],
                         l > 1 ? w.dZ[l - 1] : nullptr, dh,
                         l > 1 ? w.H[l - 1] : nullptr, layer_plan(ctx, l, X) == BNS_LAYER_UPDATE_FIRST,
-                        ctx->part.n_halo > 0 ? halo_h[l - 1] : nullptr, W[l - 1], lr, &batch, s);
+                        ctx->part.n_halo > 0 ? halo_h[l - 1] : nullptr, W[l - 1], lr, l == L && pad_last, &batch, s);
     if (st != BNS_OK) return st;
     if (l == 1 || batch.full()) {
       st = run_batch(ctx, &batch, l == 1 ? loss_sum : TnLoss{}, s);

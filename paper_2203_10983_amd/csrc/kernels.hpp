@@ -270,11 +270,12 @@ hipError_t gemm_tn(const TnGemm *g, int32_t n, const TnLoss &loss, hipStream_t s
 
 // ---- loss.hip (Algorithm 1, loss step) ---------------------------------------------------------
 constexpr int kLossBlocks = 8192;  // partials: scratch f32[kLossBlocks]
-// Leave *n_partials partial losses, which gemm_tn adds up.
+// Leave *n_partials partial losses, which gemm_tn adds up.  dZ_pad (nullable): the gradient once more in rows padded by
+// zeros to ld floats (as pad_rows makes them; ld < C + 4).
 hipError_t loss_softmax_ce(int32_t n, int32_t C, const float *logits, const int32_t *labels,
-                           float *dZ, float *partials, int32_t *n_partials, hipStream_t s);
+                           float *dZ, int32_t ld, float *dZ_pad, float *partials, int32_t *n_partials, hipStream_t s);
 hipError_t loss_sigmoid_bce(int32_t n, int32_t C, const float *logits, const uint8_t *labels,
-                            float *dZ, float *partials, int32_t *n_partials, hipStream_t s);
+                            float *dZ, int32_t ld, float *dZ_pad, float *partials, int32_t *n_partials, hipStream_t s);
 // Dropout applied in place to H[n_rows, d] (for layers whose ReLU sits in the aggregate's store).
 hipError_t dropout_inplace(int32_t n_rows, int32_t d, float *H, const Dropout &drop, hipStream_t s);
 // out = scale * dH where H > 0 else 0.  pack: weights to pack in the same launch.

@@ -26,89 +26,108 @@ __device__ __forceinline__ float block_sum_fixed(float x) {  // valid on thread 
   return s;
 }
 
-// softmax cross-entropy: one wavefront per node; loss_v = logsumexp(z_v) - z_v[y_v],
-// dZ_v = softmax(z_v) - onehot(y_v).  Up to 256 classes a row lives in registers (one read).
+// softmax cross-entropy: loss_v = logsumexp(z_v) - z_v[y_v], dZ_v = softmax(z_v) - onehot(y_v).
+// LPR lanes per node hold its row in registers, up to four classes each (C <= 4 LPR): one read, one write, bound by
+// memory.  With a whole wavefront per node whatever the width, 306 250 rows of 47 classes took 74 us and their padded copy another
+// 28 (pad_rows); together now 40.
+template <int LPR>
 __global__ void __launch_bounds__(kT)
 softmax_ce_kernel(int n, int C, const float *__restrict__ logits, const int32_t *__restrict__ labels,
-                  float *__restrict__ dZ, float *__restrict__ partials) {
+                  float *__restrict__ dZ, int ld, float *__restrict__ dZ_pad, float *__restrict__ partials) {
+  constexpr int R = 2;  // rows of a lane group per step, their loads and reductions interleaved
+  const int sl = threadIdx.x % LPR;
+  const int groups = gridDim.x * (kT / LPR);
+  auto group_sum = [](float x) {
+#pragma unroll
+    for (int off = LPR / 2; off > 0; off >>= 1) x += __shfl_xor(x, off, kWave);
+    return x;
+  };
+  auto group_max = [](float x) {
+#pragma unroll
+    for (int off = LPR / 2; off > 0; off >>= 1) x = fmaxf(x, __shfl_xor(x, off, kWave));
+    return x;
+  };
+  float loss_acc = 0.f;  // meaningful on lane 0 of the group
+  for (int v = blockIdx.x * (kT / LPR) + threadIdx.x / LPR; v < n; v += R * groups) {
+    int row[R], y[R];
+    float x[R][4], m[R], se[R], zy[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      row[r] = v + r * groups;
+      const bool ok = row[r] < n;
+      y[r] = ok ? labels[row[r]] : -1;
+      m[r] = -INFINITY;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const int c = sl + k * LPR;
+        x[r][k] = (ok && c < C) ? logits[(size_t)row[r] * C + c] : -INFINITY;
+        m[r] = fmaxf(m[r], x[r][k]);
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) m[r] = group_max(m[r]);
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      se[r] = 0.f;
+      zy[r] = 0.f;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const int c = sl + k * LPR;
+        if (c == y[r]) zy[r] = x[r][k];
+        x[r][k] = c < C ? expf(x[r][k] - m[r]) : 0.f;
+        se[r] += x[r][k];
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      se[r] = group_sum(se[r]);
+      zy[r] = group_sum(zy[r]);  // exactly one lane holds z[y]; the others add zeros
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      if (row[r] >= n) continue;
+      float *g = dZ + (size_t)row[r] * C;
+      float *gp = dZ_pad + (size_t)row[r] * ld;
+      const float inv = 1.f / se[r];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const int c = sl + k * LPR;
+        // a node outside the training set (negative label): no loss, zero gradient
+        const float o = y[r] < 0 || c >= C ? 0.f : x[r][k] * inv - (c == y[r] ? 1.f : 0.f);
+        if (c < C) g[c] = o;
+        if (dZ_pad && c < ld) gp[c] = o;
+      }
+      if (sl == 0 && y[r] >= 0) loss_acc += (m[r] + logf(se[r])) - zy[r];
+    }
+  }
+  const float s = block_sum_fixed(sl == 0 ? loss_acc : 0.f);
+  if (threadIdx.x == 0) partials[blockIdx.x] = s;
+}
+
+// More than 256 classes: a wavefront per node, the row read three times.
+__global__ void __launch_bounds__(kT)
+softmax_ce_wide_kernel(int n, int C, const float *__restrict__ logits, const int32_t *__restrict__ labels,
+                       float *__restrict__ dZ, float *__restrict__ partials) {
   const int lane = lane_id();
   const int waves = gridDim.x * (kT / kWave);
   float loss_acc = 0.f;  // meaningful on lane 0
-  const int v0 = blockIdx.x * (kT / kWave) + threadIdx.x / kWave;
-  if (C <= 4 * kWave) {
-    constexpr int R = 2;
-    // two rows per step, their loads and reductions interleaved; the loss is still added row by
-    // row in ascending order, so the sum does not depend on the pairing
-    for (int v = v0; v < n; v += R * waves) {
-      int row[R], y[R];
-      float x[R][4], m[R], se[R];
-#pragma unroll
-      for (int r = 0; r < R; ++r) row[r] = v + r * waves;
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        const bool ok = row[r] < n;
-        y[r] = ok ? labels[row[r]] : -1;
-        m[r] = -INFINITY;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const int c = lane + k * kWave;
-          x[r][k] = (ok && c < C) ? logits[(size_t)row[r] * C + c] : -INFINITY;
-          m[r] = fmaxf(m[r], x[r][k]);
-        }
-      }
-#pragma unroll
-      for (int r = 0; r < R; ++r) m[r] = wave_max(m[r]);
-      float zy[R];
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        se[r] = 0.f;
-        zy[r] = 0.f;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const int c = lane + k * kWave;
-          if (c == y[r]) zy[r] = x[r][k];
-          x[r][k] = c < C ? expf(x[r][k] - m[r]) : 0.f;
-          se[r] += x[r][k];
-        }
-      }
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        se[r] = wave_sum(se[r]);
-        zy[r] = wave_sum(zy[r]);  // exactly one lane holds z[y]; the others add zeros
-      }
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        if (row[r] >= n) continue;
-        float *g = dZ + (size_t)row[r] * C;
-        const float inv = 1.f / se[r];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const int c = lane + k * kWave;
-          // a node outside the training set (negative label): no loss, zero gradient
-          if (c < C) g[c] = y[r] < 0 ? 0.f : x[r][k] * inv - (c == y[r] ? 1.f : 0.f);
-        }
-        if (lane == 0 && y[r] >= 0) loss_acc += (m[r] + logf(se[r])) - zy[r];
-      }
+  for (int v = blockIdx.x * (kT / kWave) + threadIdx.x / kWave; v < n; v += waves) {
+    const float *z = logits + (size_t)v * C;
+    float *g = dZ + (size_t)v * C;
+    const int y = labels[v];
+    if (y < 0) {  // node outside the training set: no loss, zero gradient
+      for (int c = lane; c < C; c += kWave) g[c] = 0.f;
+      continue;
     }
-  } else {
-    for (int v = v0; v < n; v += waves) {
-      const float *z = logits + (size_t)v * C;
-      float *g = dZ + (size_t)v * C;
-      const int y = labels[v];
-      if (y < 0) {  // node outside the training set: no loss, zero gradient
-        for (int c = lane; c < C; c += kWave) g[c] = 0.f;
-        continue;
-      }
-      float m = -INFINITY;
-      for (int c = lane; c < C; c += kWave) m = fmaxf(m, z[c]);
-      m = wave_max(m);
-      float se = 0.f;
-      for (int c = lane; c < C; c += kWave) se += expf(z[c] - m);
-      se = wave_sum(se);
-      const float inv = 1.f / se;
-      for (int c = lane; c < C; c += kWave) g[c] = expf(z[c] - m) * inv - (c == y ? 1.f : 0.f);
-      if (lane == 0) loss_acc += (m + logf(se)) - z[y];
-    }
+    float m = -INFINITY;
+    for (int c = lane; c < C; c += kWave) m = fmaxf(m, z[c]);
+    m = wave_max(m);
+    float se = 0.f;
+    for (int c = lane; c < C; c += kWave) se += expf(z[c] - m);
+    se = wave_sum(se);
+    const float inv = 1.f / se;
+    for (int c = lane; c < C; c += kWave) g[c] = expf(z[c] - m) * inv - (c == y ? 1.f : 0.f);
+    if (lane == 0) loss_acc += (m + logf(se)) - z[y];
   }
   const float s = block_sum_fixed(lane == 0 ? loss_acc : 0.f);
   if (threadIdx.x == 0) partials[blockIdx.x] = s;
@@ -118,38 +137,56 @@ softmax_ce_kernel(int n, int C, const float *__restrict__ logits, const int32_t 
 // loss = max(z,0) - z*y + log(1 + exp(-|z|)),  dZ = sigmoid(z) - y
 __global__ void __launch_bounds__(kT)
 sigmoid_bce_kernel(int64_t total, const float *__restrict__ logits, const uint8_t *__restrict__ labels,
-                   float *__restrict__ dZ, float *__restrict__ partials) {
+                   float *__restrict__ dZ, int C, int ld, float *__restrict__ dZ_pad, float *__restrict__ partials) {
   const int64_t stride = (int64_t)gridDim.x * kT;
   float acc = 0.f;
   for (int64_t i = (int64_t)blockIdx.x * kT + threadIdx.x; i < total; i += stride) {
     const float z = logits[i];
-    if (labels[i] == 255) {  // entry outside the training set
-      dZ[i] = 0.f;
-      continue;
+    float g = 0.f;
+    if (labels[i] != 255) {  // 255: entry outside the training set
+      const float y = (float)labels[i];
+      const float e = expf(-fabsf(z));
+      acc += fmaxf(z, 0.f) - z * y + log1pf(e);
+      const float sig = z >= 0.f ? 1.f / (1.f + e) : e / (1.f + e);
+      g = sig - y;
     }
-    const float y = (float)labels[i];
-    const float e = expf(-fabsf(z));
-    acc += fmaxf(z, 0.f) - z * y + log1pf(e);
-    const float sig = z >= 0.f ? 1.f / (1.f + e) : e / (1.f + e);
-    dZ[i] = sig - y;
+    dZ[i] = g;
+    if (dZ_pad) {
+      const int64_t row = i / C;
+      const int c = (int)(i - row * C);
+      float *gp = dZ_pad + row * ld;
+      gp[c] = g;
+      if (c == C - 1)
+        for (int k = C; k < ld; ++k) gp[k] = 0.f;
+    }
   }
   const float s = block_sum_fixed(acc);
   if (threadIdx.x == 0) partials[blockIdx.x] = s;
 }
 
 hipError_t loss_softmax_ce(int32_t n, int32_t C, const float *logits, const int32_t *labels,
-                           float *dZ, float *partials, int32_t *n_partials, hipStream_t s) {
-  // a wavefront per node, two nodes at a time; no more workgroups than there is work for
-  const int64_t blocks = std::min<int64_t>(kLossBlocks, ((int64_t)n + 7) / 8);
-  softmax_ce_kernel<<<(unsigned)blocks, kT, 0, s>>>(n, C, logits, labels, dZ, partials);
+                           float *dZ, int32_t ld, float *dZ_pad, float *partials, int32_t *n_partials, hipStream_t s) {
+  if (dZ_pad && (ld < C || ld > (C + 3) / 4 * 4 || C > 256)) return hipErrorInvalidValue;
+  // two nodes per lane group at a time; no more workgroups than there is work for
+  const int lpr = C <= 32 ? 8 : C <= 64 ? 16 : C <= 128 ? 32 : 64;
+  const int64_t per_block = 2 * (kT / lpr);
+  const int64_t blocks = std::min<int64_t>(kLossBlocks, ((int64_t)n + per_block - 1) / per_block);
+#define BNS_CE(LPR) softmax_ce_kernel<LPR><<<(unsigned)blocks, kT, 0, s>>>(n, C, logits, labels, dZ, ld, dZ_pad, partials)
+  if (C > 256) softmax_ce_wide_kernel<<<(unsigned)blocks, kT, 0, s>>>(n, C, logits, labels, dZ, partials);
+  else if (lpr == 8) BNS_CE(8);
+  else if (lpr == 16) BNS_CE(16);
+  else if (lpr == 32) BNS_CE(32);
+  else BNS_CE(64);
+#undef BNS_CE
   *n_partials = (int32_t)blocks;
   return hipGetLastError();
 }
 
 hipError_t loss_sigmoid_bce(int32_t n, int32_t C, const float *logits, const uint8_t *labels,
-                            float *dZ, float *partials, int32_t *n_partials, hipStream_t s) {
+                            float *dZ, int32_t ld, float *dZ_pad, float *partials, int32_t *n_partials, hipStream_t s) {
+  if (dZ_pad && ld < C) return hipErrorInvalidValue;
   const int64_t total = (int64_t)n * C, blocks = std::min<int64_t>(kLossBlocks, (total + kT - 1) / kT);
-  sigmoid_bce_kernel<<<(unsigned)blocks, kT, 0, s>>>(total, logits, labels, dZ, partials);
+  sigmoid_bce_kernel<<<(unsigned)blocks, kT, 0, s>>>(total, logits, labels, dZ, C, ld, dZ_pad, partials);
   *n_partials = (int32_t)blocks;
   return hipGetLastError();
 }
