@@ -342,13 +342,14 @@ bns_status layer_fwd_impl(bns_ctx *ctx, int layer, double p, const float *H_in, 
       g.C = A_saved;
       g.ldc = ld;
       g.pad = ld != d_out;
-      BNS_TRY("gemm_rows_f32(inner)", gemm_rows_f32(g, s));
-      g.M = B;
-      g.A = halo_h;  // the kept boundary rows where the caller holds them, scaled on their way in
-      g.rec = ctx->ws.halo_rec;
-      g.C = ctx->ws.Hu2;
-      g.m_dev = ctx->cur_n_kept;
-      if (B > 0) BNS_TRY("gemm_rows_f32(boundary)", gemm_rows_f32(g, s));
+      if (B > 0) {  // the kept boundary rows where the caller holds them, scaled on their way in
+        g.rec = ctx->ws.halo_rec;
+        g.A_rec = halo_h;
+        g.C_rec = ctx->ws.Hu2;
+        g.M2 = B;
+        g.m2_dev = ctx->cur_n_kept;
+      }
+      BNS_TRY("gemm_rows_f32", gemm_rows_f32(g, s));
     }
     PhaseTimer t(ctx, BNS_PHASE_SPMM_FWD, s);
     BNS_TRY("spmm_fwd", spmm_fwd(ctx->ws.plan_f, n_in, ld, ctx->cur_row_ptr, ctx->cur_col_idx, ctx->ws.w_fwd,
@@ -456,10 +457,11 @@ bns_status layer_bwd_impl(bns_ctx *ctx, int layer, double p, const float *dZ, co
   const int n_in = ctx->part.n_in, B = ctx->part.n_halo;
   const int d_in = ctx->dims[layer - 1], d_out = ctx->dims[layer];
   const char *Wb = ctx->ws.Wb[layer];
-  // C = alpha * G W^T for rows of G at the output width; C2: the mean aggregator's second half
-  auto gemm_wt = [&](int32_t M, const float *G, float *C, float *C2, const float *mask, float alpha, const int32_t *m_dev) {
+  // C = alpha * G W^T for the inner rows of G at the output width; C2: the mean aggregator's second half; G_more: the
+  // rows of the kept boundary nodes
+  auto gemm_wt = [&](const float *G, float *C, float *C2, const float *mask, float alpha, const float *G_more, float *C_more) {
     RowsGemm g{};
-    g.M = M;
+    g.M = n_in;
     g.N = C2 ? 2 * d_in : d_in;
     g.K = d_out;
     g.A = G;
@@ -477,7 +479,10 @@ bns_status layer_bwd_impl(bns_ctx *ctx, int layer, double p, const float *dZ, co
     g.C2 = C2;
     g.ldc = g.c_split = d_in;
     g.mask = mask;
-    g.m_dev = m_dev;
+    g.A_more = G_more;
+    g.C_more = C_more;
+    g.M2 = B;
+    g.m2_dev = ctx->cur_n_kept;
     return gemm_rows(g, s);
   };
   // dW = [A | A2]^T G joins the batch of weight gradients, which runs when the chain of the layers is through
@@ -523,9 +528,7 @@ bns_status layer_bwd_impl(bns_ctx *ctx, int layer, double p, const float *dZ, co
     if (dH_in) {
       PhaseTimer t(ctx, BNS_PHASE_GEMM_DA, s);
       const float ms1 = mask_src ? mask_scale_of(ctx) : 1.f;
-      BNS_TRY("gemm_rows(dH)", gemm_wt(n_in, G_in, dH_in, nullptr, mask_src, ms1, nullptr));
-      if (dhalo && B > 0)
-        BNS_TRY("gemm_rows(dhalo)", gemm_wt(B, G_halo, dhalo, nullptr, nullptr, 1.f, ctx->cur_n_kept));
+      BNS_TRY("gemm_rows(dH)", gemm_wt(G_in, dH_in, nullptr, mask_src, ms1, dhalo ? G_halo : nullptr, dhalo));
     }
     return BNS_OK;
   }
@@ -538,7 +541,7 @@ bns_status layer_bwd_impl(bns_ctx *ctx, int layer, double p, const float *dZ, co
     if (dH_in) {
       {
         PhaseTimer t(ctx, BNS_PHASE_GEMM_DA, s);  // dZ [W_n ; W_s]^T in one product, split into the two halves
-        BNS_TRY("gemm_rows(dA pair)", gemm_wt(n_in, dZ, ctx->ws.G1, ctx->ws.G2, nullptr, ms, nullptr));
+        BNS_TRY("gemm_rows(dA pair)", gemm_wt(dZ, ctx->ws.G1, ctx->ws.G2, nullptr, ms, nullptr, nullptr));
       }
       // dH_in = (gradient through the node's own feature) + mean^T (gradient of the neighbour mean)
       PhaseTimer t(ctx, BNS_PHASE_SPMM_BWD, s);
@@ -552,7 +555,7 @@ bns_status layer_bwd_impl(bns_ctx *ctx, int layer, double p, const float *dZ, co
   add_dw(n_in, A_saved, nullptr, dZ, ctx->ws.tn[layer]);
   if (dH_in && d_out < d_in) {
     // (P^T dZ) W^T instead of P^T (dZ W^T): the transposed aggregate runs at the narrower width
-    float *G_in = ctx->ws.G1, *G_halo = dhalo ? ctx->ws.Hu : nullptr;
+    float *G_in = ctx->ws.G1, *G_halo = dhalo && B > 0 ? ctx->ws.Hu : nullptr;
     {
       PhaseTimer t(ctx, BNS_PHASE_SPMM_BWD, s);
       const int ld = gather_stride(d_in, d_out);
@@ -567,13 +570,11 @@ bns_status layer_bwd_impl(bns_ctx *ctx, int layer, double p, const float *dZ, co
                                    ctx->ws.spmm_partials, G_in, G_halo, s, d_out));
     }
     PhaseTimer t(ctx, BNS_PHASE_GEMM_DA, s);
-    BNS_TRY("gemm_rows(dH)", gemm_wt(n_in, G_in, dH_in, nullptr, mask_src, ms, nullptr));
-    if (G_halo && B > 0)
-      BNS_TRY("gemm_rows(dhalo)", gemm_wt(B, G_halo, dhalo, nullptr, nullptr, 1.f, ctx->cur_n_kept));
+    BNS_TRY("gemm_rows(dH)", gemm_wt(G_in, dH_in, nullptr, mask_src, ms, G_halo, dhalo));
   } else if (dH_in) {
     {
       PhaseTimer t(ctx, BNS_PHASE_GEMM_DA, s);
-      BNS_TRY("gemm_rows(dA)", gemm_wt(n_in, dZ, ctx->ws.G1, nullptr, nullptr, ms, nullptr));
+      BNS_TRY("gemm_rows(dA)", gemm_wt(dZ, ctx->ws.G1, nullptr, nullptr, ms, nullptr, nullptr));
     }
     PhaseTimer t(ctx, BNS_PHASE_SPMM_BWD, s);
     BNS_TRY("spmm_bwd", spmm_bwd(ctx->ws.plan_b, n_in, B, d_in, ctx->cur_t_row_ptr, ctx->cur_t_col_idx,

@@ -56,14 +56,15 @@ __global__ void __launch_bounds__(256, R * NC > 8 ? 3 : 4) gemm_rows_kernel(cons
   constexpr int kRows = 64 * R;  // rows of a workgroup's tile
   __shared__ __attribute__((aligned(16))) char Bs[2][NC * kFragSet];
   const RowsGemm &p = a.g;
-  const int M = p.m_dev ? min(p.M, *p.m_dev) : p.M;
+  const int M = p.M, M2 = EPI != kPair && p.A_more ? min(p.M2, *p.m2_dev) : 0;
   // workgroup b runs on XCD b % 8: the column blocks of one row tile follow each other on one XCD, so
   // that they find its rows in that XCD's L2
   const int x = blockIdx.x & 7, q = blockIdx.x >> 3;
   const int nb = q % a.nblk, stride = (gridDim.x / (8 * a.nblk)) * 8;
   const int t0 = nb * NC;
   int tile = (q / a.nblk) * 8 + x;
-  const int n_tiles = (M + kRows - 1) / kRows;
+  const int n_first = (M + kRows - 1) / kRows;  // row tiles of C; those of C_more follow
+  const int n_tiles = n_first + (M2 + kRows - 1) / kRows;
   if (tile >= n_tiles) return;
 
   const int lane = lane_id(), wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -73,10 +74,13 @@ __global__ void __launch_bounds__(256, R * NC > 8 ? 3 : 4) gemm_rows_kernel(cons
   f32x4 ar[R][2];
   const float *row_a[R];
   auto set_rows = [&](int tl) {
+    const bool more = EPI != kPair && tl >= n_first;
+    const float *A = more ? p.A_more : p.A;
+    const int end = more ? M2 : M, first = (more ? tl - n_first : tl) * kRows;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      const int row = min(M - 1, tl * kRows + wid * 16 * R + r * 16 + l16);  // rows past the end are not stored
-      row_a[r] = p.A + (size_t)row * p.K;
+      const int row = min(end - 1, first + wid * 16 * R + r * 16 + l16);  // rows past the end are not stored
+      row_a[r] = A + (size_t)row * p.K;
     }
   };
   auto load_a = [&](int s) {
@@ -139,20 +143,23 @@ __global__ void __launch_bounds__(256, R * NC > 8 ? 3 : 4) gemm_rows_kernel(cons
     if (last) {
       // lane: row l16 of the row tile, columns 16 c + 4 g .. + 3
       const int n_end = p.N, col0 = t0 * 16 + g * 4;
+      const bool more = EPI != kPair && tile >= n_first;
+      const int end = more ? M2 : M, first = (more ? tile - n_first : tile) * kRows;
+      const float scale = more ? 1.f : p.alpha;
 #pragma unroll
       for (int r = 0; r < R; ++r) {
-        const int row = tile * kRows + wid * 16 * R + r * 16 + l16;
-        if (row >= M) continue;
+        const int row = first + wid * 16 * R + r * 16 + l16;
+        if (row >= end) continue;
         const size_t at = (size_t)row * p.ldc + col0;
-        float *const dst = p.C + at;
+        float *const dst = (more ? p.C_more : p.C) + at;
         float *const dst2 = EPI == kPair ? p.C2 + at - p.c_split : nullptr;  // c_split % 4 == 0
         const float *const ms = EPI == kMask ? p.mask + at : nullptr;
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
           const int left = n_end - (col0 + c * 16);  // columns from this lane's first one to the end
           f32x4 v = acc[c][r];
-          const float alpha = (t0 + c) & 1 ? -p.alpha : p.alpha;  // odd tiles are summed negated
-          if constexpr (EPI == kMask) {
+          const float alpha = (t0 + c) & 1 ? -scale : scale;  // odd tiles are summed negated
+          if (EPI == kMask && !more) {
             f32x4 m = {0.f, 0.f, 0.f, 0.f};
             if (left >= 4) m = *reinterpret_cast<const f32x4u *>(ms + c * 16);
             else
@@ -204,7 +211,7 @@ static void launch_rows(const RowsArgs &a, int nc, unsigned grid, hipStream_t s)
 hipError_t gemm_rows(const RowsGemm &g, hipStream_t s) {
   if (g.M <= 0 || g.N <= 0) return hipSuccess;
   if (g.C2 ? g.c_split % 4 != 0 || g.ldc < g.c_split || g.N > 2 * g.c_split : g.ldc < g.N) return hipErrorInvalidValue;
-  if (g.C2 && g.mask) return hipErrorInvalidValue;
+  if (g.C2 && (g.mask || g.A_more)) return hipErrorInvalidValue;
   RowsArgs a;
   a.g = g;
   a.T = col_tiles(g.N);
@@ -214,14 +221,15 @@ hipError_t gemm_rows(const RowsGemm &g, hipStream_t s) {
   constexpr int kWanted = 512;
   a.nblk = (a.T + 7) / 8;
   int R = 2;
-  auto groups = [&]() { return (int64_t)((g.M + 64 * R - 1) / (64 * R)) * a.nblk; };
+  const int64_t m2 = g.A_more ? g.M2 / 4 : 0;  // a row count on the device is usually a fraction of its bound
+  auto row_tiles = [&]() { return (g.M + 64 * R - 1) / (64 * R) + (m2 + 64 * R - 1) / (64 * R); };
+  auto groups = [&]() { return row_tiles() * a.nblk; };
   if (groups() < kWanted) R = 1;
   while (groups() < kWanted && a.nblk * 2 <= a.T) a.nblk *= 2;
   int nc = (a.T + a.nblk - 1) / a.nblk;
   a.nblk = (a.T + nc - 1) / nc;
-  const int64_t row_tiles = (g.M + 64 * R - 1) / (64 * R);
   // a grid of whole octets of row tiles, every column block of each; the tiles past one resident round are walked
-  int64_t octets = std::min<int64_t>((row_tiles + 7) / 8, std::max<int64_t>(1, 768 / (8 * a.nblk)));
+  int64_t octets = std::min<int64_t>((row_tiles() + 7) / 8, std::max<int64_t>(1, 768 / (8 * a.nblk)));
   const unsigned grid = (unsigned)(octets * 8 * a.nblk);
   if (R == 2) launch_rows<2>(a, nc, grid, s);
   else launch_rows<1>(a, nc, grid, s);

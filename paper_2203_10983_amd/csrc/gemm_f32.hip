@@ -28,18 +28,20 @@ struct F32Args {
   int T, S, nblk;  // column tiles of 32, depth steps of 32, column blocks
 };
 
+// REC: the rows of A are followed by the ones that g.rec names (a second result, row tiles of its own).
 template <int NC, bool ACC, bool REC>
 __global__ void __launch_bounds__(256, 4) gemm_rows_f32_kernel(const F32Args a) {
   constexpr int kRows = 128;
   __shared__ __attribute__((aligned(16))) char Bs[2][NC * kF32Step];
   const RowsF32 &p = a.g;
-  const int M = p.m_dev ? min(p.M, *p.m_dev) : p.M;
+  const int M = p.M, M2 = REC ? min(p.M2, *p.m2_dev) : 0;
   // workgroup b runs on XCD b % 8: the column blocks of one row tile follow each other on one XCD
   const int x = blockIdx.x & 7, q = blockIdx.x >> 3;
   const int nb = q % a.nblk, stride = (gridDim.x / (8 * a.nblk)) * 8;
   const int t0 = nb * NC;
   int tile = (q / a.nblk) * 8 + x;
-  const int n_tiles = (M + kRows - 1) / kRows;
+  const int n_first = (M + kRows - 1) / kRows;  // row tiles of the first result
+  const int n_tiles = n_first + (M2 + kRows - 1) / kRows;
   if (tile >= n_tiles) return;
 
   const int lane = lane_id(), wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -52,12 +54,17 @@ __global__ void __launch_bounds__(256, 4) gemm_rows_f32_kernel(const F32Args a) 
   float row_scale = 1.f;  // REC: of the row whose values ar holds
   auto set_rows = [&](int tl) {
     int row = min(M - 1, tl * kRows + wid * 32 + l32);  // rows past the end are not stored
+    const float *A = p.A;
     if constexpr (REC) {
-      const int2 r = p.rec[row];
-      row = r.x;
-      row_scale = __int_as_float(r.y);
+      row_scale = 1.f;
+      if (tl >= n_first) {
+        const int2 r = p.rec[min(M2 - 1, (tl - n_first) * kRows + wid * 32 + l32)];
+        row = r.x;
+        row_scale = __int_as_float(r.y);
+        A = p.A_rec;
+      }
     }
-    row_a = p.A + (size_t)row * p.lda;
+    row_a = A + (size_t)row * p.lda;
     row_a2 = two ? p.A2 + (size_t)row * p.lda - p.a_split : nullptr;
   };
   auto load_a = [&](int s) {
@@ -137,10 +144,11 @@ __global__ void __launch_bounds__(256, 4) gemm_rows_f32_kernel(const F32Args a) 
     buf ^= 1;
     if (last) {
       // lane: row l32 of the wavefront's 32; register 4 q + e of tile c: column 32 c + 8 q + 4 hi + e
-      const int row = tile * kRows + wid * 32 + l32;
-      if (row < M) {
+      const bool second = REC && tile >= n_first;
+      const int row = (second ? tile - n_first : tile) * kRows + wid * 32 + l32;
+      if (row < (second ? M2 : M)) {
         const int n_end = p.pad ? p.ldc : p.N, col0 = t0 * 32 + hi * 4;  // pad: the packed weights are zero there
-        float *const dst = p.C + (size_t)row * p.ldc + col0;
+        float *const dst = (second ? p.C_rec : p.C) + (size_t)row * p.ldc + col0;
 #pragma unroll
         for (int c = 0; c < NC; ++c)
 #pragma unroll
@@ -183,14 +191,15 @@ __global__ void __launch_bounds__(256, 4) gemm_rows_f32_kernel(const F32Args a) 
 hipError_t gemm_rows_f32(const RowsF32 &g, hipStream_t s) {
   if (g.M <= 0 || g.N <= 0) return hipSuccess;
   if (g.ldc < g.N || (g.pad && (g.ldc > (g.N + 3) / 4 * 4 || g.relu || g.accumulate)) || (g.A2 && g.a_split % 16 != 0) ||
-      (g.rec && (g.A2 || g.accumulate)))
+      (g.rec && (g.A2 || g.accumulate || g.relu || !g.m2_dev)))
     return hipErrorInvalidValue;
   F32Args a;
   a.g = g;
   a.T = (g.N + 31) / 32;
   a.S = (g.K + 31) / 32;
   // up to 4 column tiles per wavefront, evenly dealt; fewer where that leaves the chip short of workgroups
-  const int64_t row_tiles = (g.M + 127) / 128;
+  // (a row count on the device is usually a fraction of its bound: priced at a quarter)
+  const int64_t row_tiles = (g.M + 127) / 128 + (g.rec ? (g.M2 / 4 + 127) / 128 : 0);
   a.nblk = (a.T + 3) / 4;
   while (row_tiles * a.nblk < 512 && a.nblk < a.T) a.nblk = std::min(a.nblk * 2, a.T);
   const int nc = (a.T + a.nblk - 1) / a.nblk;

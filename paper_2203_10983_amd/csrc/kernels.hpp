@@ -208,7 +208,9 @@ struct Dropout {
 // C[M,N] = [A | A2] B (+ the previous C if accumulate), B [K,N] packed; then, if relu, max(., 0) and dropout (when
 // drop.scale != 0).  A, A2 [M, lda]: the depth below a_split (a multiple of 16) is A's, the rest A2's (nullable).
 // pad: the columns N..ldc-1 are set to zero (ldc at most N rounded up to a multiple of 4; not with relu or
-// accumulate).  m_dev (nullable): row count on the device, *m_dev <= M; rows past it are not touched.
+// accumulate).
+// rec (nullable; from halo_records): in the same launch C_rec[r] = as_float(rec[r].y) * A_rec[rec[r].x] B for r < *m2_dev
+// (<= M2); not with A2, relu or accumulate.
 struct RowsF32 {
   int32_t M, N, K;
   const float *A, *A2;
@@ -217,15 +219,18 @@ struct RowsF32 {
   float *C;
   int32_t ldc;
   bool relu, pad, accumulate;
-  const int32_t *m_dev;
-  const int2 *rec;  // nullable: row r of A is row rec[r].x, times as_float(rec[r].y) (halo_records)
+  const int2 *rec;
+  const float *A_rec;
+  float *C_rec;
+  int32_t M2;
+  const int32_t *m2_dev;
   Dropout drop;
 };
 hipError_t gemm_rows_f32(const RowsF32 &g, hipStream_t s);
 
 // C[M,N] = alpha * A B with A [M,K], B [K,N] packed and split.  At most one of: C2 (nullable): columns from c_split (a
 // multiple of 4) on go to C2, both with row stride ldc; mask (nullable, [M, ldc]): C is zeroed where mask <= 0.
-// m_dev as above.
+// A_more (nullable): in the same launch C_more[r] = A_more[r] B for r < *m2_dev (<= M2); not with C2.
 struct RowsGemm {
   int32_t M, N, K;
   const float *A;
@@ -234,7 +239,10 @@ struct RowsGemm {
   int32_t ldc, c_split;
   float alpha;
   const float *mask;
-  const int32_t *m_dev;
+  const float *A_more;
+  float *C_more;
+  int32_t M2;
+  const int32_t *m2_dev;
 };
 hipError_t gemm_rows(const RowsGemm &g, hipStream_t s);
 
