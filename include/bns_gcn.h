@@ -171,7 +171,9 @@ bns_status bns_gcn_layer_fwd(bns_ctx *ctx, int32_t layer, double p, const float 
  *   transposed aggregate, as for layer 1); dhalo dev f32[n_halo*d_in] (capacity; first *n_kept
  *   rows valid: gradient w.r.t. the unscaled features of the kept boundary nodes; NULL to skip).
  * H_in (the layer's input, dev f32[n_in*d_in]) is read by the mean-aggregator layer only
- * (dW = [A_saved | H_in]^T dZ, f32[2*d_in*d_out]); it may be NULL for the GCN layer. */
+ * (dW = [A_saved | H_in]^T dZ, f32[2*d_in*d_out]); it may be NULL for the GCN layer.
+ * dH_in and dhalo are written after dH_out, H_out, A_saved and H_in have been read: either may share
+ * memory with them (a gradient in place of the one it came from, say), but not with W, dW or each other. */
 bns_status bns_gcn_layer_bwd(bns_ctx *ctx, int32_t layer, double p, const float *dH_out,
                              const float *H_out, const float *A_saved, const float *H_in,
                              const float *W, float *dW, float *dH_in, float *dhalo, void *stream);

@@ -450,6 +450,8 @@ bns_status run_batch(bns_ctx *ctx, TnBatch *batch, const TnLoss &loss, hipStream
 // halo_first (nullable): the boundary features of an update-first layer (A_saved does not hold
 // the aggregate then); the weight gradient is [H_in ; Hu]^T (P^T dZ) instead of A^T dZ.
 // dz_padded: G2 holds dZ with padded rows already (pads_gradient).
+// batch (nullable): collects the weight gradient, to be run when the chain of the layers is through; without one it is
+// run before dH_in and dhalo are written, which may then share memory with dZ, A_saved or H_in.
 bns_status layer_bwd_impl(bns_ctx *ctx, int layer, double p, const float *dZ, const float *A_saved,
                           const float *H_in, float *dW, float *dH_in, float *dhalo, const float *mask_src,
                           bool update_first, const float *halo_first, float *W_step, float lr, bool dz_padded,
@@ -485,9 +487,10 @@ bns_status layer_bwd_impl(bns_ctx *ctx, int layer, double p, const float *dZ, co
     g.m2_dev = ctx->cur_n_kept;
     return gemm_rows(g, s);
   };
-  // dW = [A | A2]^T G joins the batch of weight gradients, which runs when the chain of the layers is through
-  auto add_dw = [&](int32_t K, const float *A, const float *A2, const float *G, float *partials) {
-    TnGemm &g = batch->g[batch->n++];
+  TnBatch own;
+  TnBatch *const jobs = batch ? batch : &own;
+  auto add_dw = [&](int32_t K, const float *A, const float *A2, const float *G, float *partials) {  // dW = [A | A2]^T G
+    TnGemm &g = jobs->g[jobs->n++];
     g = TnGemm{};
     g.M = A2 ? 2 * d_in : d_in;
     g.N = d_out;
@@ -536,8 +539,13 @@ bns_status layer_bwd_impl(bns_ctx *ctx, int layer, double p, const float *dZ, co
   // gradient only.  Where the transposed aggregate applies the mask, the factor rides on its
   // input (the product with W^T) and is divided out of the boundary rows, which are not masked.
   const float ms = mask_src ? mask_scale_of(ctx) : 1.f;
+  // mean aggregator: [A | H]^T dZ in one product, dZ is read once
+  add_dw(n_in, A_saved, ctx->layer_kind == 1 ? H_in : nullptr, dZ, ctx->ws.tn[layer]);
+  if (!batch) {
+    const bns_status st = run_batch(ctx, &own, TnLoss{}, s);
+    if (st != BNS_OK) return st;
+  }
   if (ctx->layer_kind == 1) {
-    add_dw(n_in, A_saved, H_in, dZ, ctx->ws.tn[layer]);  // [A | H]^T dZ in one product: dZ is read once
     if (dH_in) {
       {
         PhaseTimer t(ctx, BNS_PHASE_GEMM_DA, s);  // dZ [W_n ; W_s]^T in one product, split into the two halves
@@ -552,7 +560,6 @@ bns_status layer_bwd_impl(bns_ctx *ctx, int layer, double p, const float *dZ, co
     }
     return BNS_OK;
   }
-  add_dw(n_in, A_saved, nullptr, dZ, ctx->ws.tn[layer]);
   if (dH_in && d_out < d_in) {
     // (P^T dZ) W^T instead of P^T (dZ W^T): the transposed aggregate runs at the narrower width
     float *G_in = ctx->ws.G1, *G_halo = dhalo && B > 0 ? ctx->ws.Hu : nullptr;
@@ -812,10 +819,8 @@ bns_status bns_gcn_layer_bwd(bns_ctx *ctx, int32_t layer, double p, const float 
   } else {
     BNS_TRY("pack_weights", pack_weights(jobs, s));
   }
-  TnBatch batch;
-  const bns_status st = layer_bwd_impl(ctx, layer, p, dZ, A_saved, H_in, dW, dH_in, dhalo, nullptr, false, nullptr, nullptr,
-                                       0.f, false, &batch, s);
-  return st != BNS_OK ? st : run_batch(ctx, &batch, TnLoss{}, s);
+  return layer_bwd_impl(ctx, layer, p, dZ, A_saved, H_in, dW, dH_in, dhalo, nullptr, false, nullptr, nullptr, 0.f, false,
+                        nullptr, s);
 }
 
 static bns_status train_step_impl(bns_ctx *ctx, uint64_t seed, uint32_t epoch, const uint32_t *epoch_dev, double p,

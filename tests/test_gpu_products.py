@@ -58,3 +58,35 @@ def test_products(n, d_in, d_out, kind):
     check("A^T dZ", dW, Z.t().contiguous(), dH.double())
     check("dZ W^T", dX, dH.double(), Wd[d_in * kind:].t().contiguous())
     ctx.close()
+
+
+@pytest.mark.parametrize("kind,shared,d_out", [(0, "dH_out", 48), (0, "A_saved", 48), (0, "H_out", 48), (0, "A_saved", 20),
+                                               (1, "dH_out", 48), (1, "A_saved", 48), (1, "H_in", 48), (1, "H_in", 20)])
+def test_input_gradient_may_overwrite_what_it_came_from(kind, shared, d_out):
+    """dH_in in the place of an operand of the same call (bns_gcn_layer_bwd) changes neither gradient."""
+    import torch
+    import paper_2203_10983_amd as pkg
+    n, d_in, dev = 1000, 48, torch.device("cuda:0")
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(n + d_out)
+    f32 = lambda *s: torch.randn(*s, device=dev, generator=gen)  # noqa: E731
+    i32 = lambda k: torch.zeros(k, dtype=torch.int32, device=dev)  # noqa: E731
+    ctx = pkg.Context(_loops(n), [d_in, d_out], 0, device=dev, layer_kind=kind)
+    kept, remap, n_kept, nnz = i32(1), i32(1), i32(1), i32(1)
+    ctx.sample_boundary(1, 0, 0.5, kept, remap, n_kept)
+    csr = i32(n + 1), i32(n), i32(n + 1), i32(n)
+    ctx.build_sampled_csr(remap, kept, n_kept, *csr, nnz)
+    W = f32((1 + kind) * d_in, d_out)
+    ops = dict(dH_out=f32(n, d_out), H_out=f32(n, d_out) if shared == "H_out" else None, A_saved=f32(n, d_in), H_in=f32(n, d_in))
+
+    def bwd(o, dX):
+        dW = torch.zeros_like(W)
+        ctx.gcn_layer_bwd(1, 0.5, o["dH_out"], o["H_out"], o["A_saved"], o["H_in"], W, dW, dX, None)
+        torch.cuda.synchronize()
+        return dW, dX
+
+    dW, dX = bwd(ops, torch.zeros(n, d_in, device=dev))
+    copies = {k: v if v is None else v.clone() for k, v in ops.items()}
+    dW2, dX2 = bwd(copies, copies[shared])
+    assert torch.equal(dX, dX2) and torch.equal(dW, dW2)
+    ctx.close()
