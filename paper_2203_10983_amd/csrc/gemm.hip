@@ -137,7 +137,10 @@ __global__ void __launch_bounds__(256, R * NC > 8 ? 3 : 4) gemm_rows_kernel(cons
       Frag3 fb;
 #pragma unroll
       for (int i = 0; i < 3; ++i) fb.p[i] = *reinterpret_cast<const bf16x8 *>(bs + c * kFragSet + i * kFragBytes);
-      mfma_split<R>(acc[c], fb, fa);
+      f32x4 part[R];
+      mfma_split<R>(part, fb, fa);
+#pragma unroll
+      for (int r = 0; r < R; ++r) acc[c][r] += part[r];
     }
     buf ^= 1;
     if (last) {
@@ -366,19 +369,29 @@ __global__ void __launch_bounds__(256, 3) gemm_tn_kernel(const TnJobs jobs) {
 #pragma unroll
     for (int ks = 0; ks < KS / 32; ++ks) {
       const char *base = lds + (size_t)ks * TILES * kTnTile + lane * 16;
-      Frag3 fm[MT];
+      // A's tiles two at a time where the wavefront has more than eight results: the step's own sums beside the running
+      // ones are 168 registers and 29 spilled with all four (A^T dZ of 89625 x 512 x 512: 273 us, 265 like this)
+      constexpr int H = MT * NT > 8 ? 2 : MT;
 #pragma unroll
-      for (int i = 0; i < MT; ++i)
+      for (int h = 0; h < MT; h += H) {
+        Frag3 fm[H];
 #pragma unroll
-        for (int p = 0; p < 3; ++p)
-          fm[i].p[p] = *reinterpret_cast<const bf16x8 *>(base + (wm * MT + i) * kTnTile + p * kFragBytes);
+        for (int i = 0; i < H; ++i)
 #pragma unroll
-      for (int j = 0; j < NT; ++j) {
-        Frag3 fn;
+          for (int p = 0; p < 3; ++p)
+            fm[i].p[p] = *reinterpret_cast<const bf16x8 *>(base + (wm * MT + h + i) * kTnTile + p * kFragBytes);
 #pragma unroll
-        for (int p = 0; p < 3; ++p)
-          fn.p[p] = *reinterpret_cast<const bf16x8 *>(base + (TM + wn * NT + j) * kTnTile + p * kFragBytes);
-        mfma_split<MT>(acc[j], fn, fm);
+        for (int j = 0; j < NT; ++j) {
+          Frag3 fn;
+#pragma unroll
+          for (int p = 0; p < 3; ++p)
+            fn.p[p] = *reinterpret_cast<const bf16x8 *>(base + (TM + wn * NT + j) * kTnTile + p * kFragBytes);
+          f32x4 part[H];
+          mfma_split<H>(part, fn, fm);
+#pragma unroll
+          for (int i = 0; i < H; ++i) acc[j][h + i] += part[i];
+        }
+        if (H < MT) asm volatile("" ::: "memory");  // B's fragments again
       }
     }
   }

@@ -1,10 +1,20 @@
-// fp32 products on the bf16 matrix instruction.
+// fp32 products on the bf16 matrix instruction, by three-way splitting (Henry, Tang, Heinecke: Leveraging the bfloat16
+// artificial intelligence datatype for higher-precision computations, ARITH 2019).
 //
 // An fp32 value is the exact sum of three bf16 values: hi = bf16(x), mid = bf16(x - hi) and
 // lo = x - hi - mid (both differences are exact, and 3 x 8 significand bits hold the 24 of x).  A
 // product of two such sums needs six of its nine partial products: the three left out (mid lo,
 // lo mid, lo lo) are below 2^-26 of the product, a quarter of the rounding that an fp32 sum makes
-// at every step.  Each partial product is exact in fp32, and sums are fp32 as in v_mfma_f32_32x32x2_f32.
+// at every step.  Each partial product is exact in fp32.
+//
+// The six instructions of a 32-deep step start from zero, smallest products first, so that only the last one rounds at
+// the size of the step's sum; that sum is then added to the running one in fp32.  Error against fp64 (2-norm, normal
+// operands), beside a chain of v_mfma_f32_32x32x2_f32 and beside one accumulator through all instructions:
+//   dZ W^T, depth  64: 4.7e-8 (1.4e-7, 0.9e-7)   128: 5.7e-8 (2.0e-7, 1.5e-7)   512: 8.9e-8 (4.1e-7, 3.4e-7)
+//   A^T dZ, 60000 rows of 128 x 128: 1.0e-7 (1.9e-7, 2.7e-7)   300000: 1.2e-7 (3.4e-7, 3.2e-7)
+// The additions are free in gemm_rows; in gemm_tn they cost 4 to 8 % on tiles of 128 x 128.
+// Below 2^-110 the lo piece, then the mid piece are subnormal: such an operand is held to an absolute 2^-134.
+//
 // v_mfma_f32_16x16x32_bf16 runs at sixteen times the rate of the fp32 instruction, so six of them
 // take 6/16 of its time.  (|x| above 3.389e38 rounds to an infinite hi: such an element gives NaN
 // instead of an overflowing product.)
@@ -39,7 +49,7 @@ struct Frag3 { bf16x8 p[3]; };  // hi, mid, lo of 8 values
 // NEG: the pieces of the negated values.
 template <bool NEG = false>
 __device__ __forceinline__ Frag3 split8(const f32x4 &a_in, const f32x4 &b_in) {
-  const f32x4 a = NEG ? -a_in : a_in, b = NEG ? -b_in : b_in;
+    const f32x4 a = NEG ? -a_in : a_in, b = NEG ? -b_in : b_in;
   u32x4 h, m, l;
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
@@ -56,18 +66,20 @@ __device__ __forceinline__ Frag3 split8(const f32x4 &a_in, const f32x4 &b_in) {
   return f;
 }
 
-// acc[r] += x . y[r] for R second operands, smallest partial products first; the accumulators are taken in
+// t[r] = x . y[r] for R second operands, smallest partial products first; the results are taken in
 // turn so that consecutive instructions do not wait for each other.  The instruction cuts off what an addend has below
-// the accumulator's last bit, downwards.  So that these cuts do not add up to a bias, half of the sums run on a
+// the last bit of the sum, downwards.  So that these cuts do not add up to a bias, half of the sums run on a
 // negated operand and are negated at the end: every other column tile of gemm_rows, every other split of gemm_tn.
 template <int R>
-__device__ __forceinline__ void mfma_split(f32x4 (&acc)[R], const Frag3 &x, const Frag3 (&y)[R]) {
+__device__ __forceinline__ void mfma_split(f32x4 (&t)[R], const Frag3 &x, const Frag3 (&y)[R]) {
   constexpr int px[6] = {0, 2, 1, 0, 1, 0}, py[6] = {2, 0, 1, 1, 0, 0};
+#pragma unroll
+  for (int r = 0; r < R; ++r) t[r] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int i = 0; i < 6; ++i)
 #pragma unroll
     for (int r = 0; r < R; ++r)
-      acc[r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x.p[px[i]], y[r].p[py[i]], acc[r], 0, 0, 0);
+      t[r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x.p[px[i]], y[r].p[py[i]], t[r], 0, 0, 0);
 }
 
 // One 16-byte-per-lane copy from global memory straight into LDS (lane i lands at lds + 16 i; both

@@ -60,6 +60,41 @@ def test_products(n, d_in, d_out, kind):
     ctx.close()
 
 
+@pytest.mark.parametrize("half_zero", [False, True], ids=["normal", "masked"])
+@pytest.mark.parametrize("n,d_in,d_out", [(2000, 96, 128), (2000, 64, 512), (4000, 512, 512), (4099, 128, 172), (60000, 128, 128)],
+                         ids=lambda v: str(v))
+def test_backward_products_round_once_a_step(n, d_in, d_out, half_zero):
+    """The error of dZ W^T and A^T dZ over the whole result, which the element-wise allowance above is too wide for.
+
+    A 32-deep step is rounded once at its own size and once where it joins the running sum.  The rounding of a sum x to the
+    nearest has a standard deviation of 0.42 * 2^-24 |x| on average, and the running sum of n steps of random terms has at
+    step i the size sqrt(i / n) of the whole: 0.42 * 2^-24 sqrt(n / 2) for all n, and once more that of one step, 2^-24 at
+    most.  Taken with a factor 1.7: 2^-24 (1 + 0.5 sqrt(n)).  A^T dZ is cut into splits of at most 1024 rows here."""
+    import torch
+    import paper_2203_10983_amd as pkg
+    dev = torch.device("cuda:0")
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(n + d_out)
+    f32 = lambda *s: torch.randn(*s, device=dev, generator=gen)  # noqa: E731
+    i32 = lambda k: torch.zeros(k, dtype=torch.int32, device=dev)  # noqa: E731
+    ctx = pkg.Context(_loops(n), [d_in, d_out], 0, device=dev)
+    kept, remap, n_kept, nnz = i32(1), i32(1), i32(1), i32(1)
+    ctx.sample_boundary(1, 0, 0.5, kept, remap, n_kept)
+    csr = i32(n + 1), i32(n), i32(n + 1), i32(n)
+    ctx.build_sampled_csr(remap, kept, n_kept, *csr, nnz)
+    A, W, dZ = f32(n, d_in), f32(d_in, d_out), f32(n, d_out)
+    if half_zero:
+        dZ *= f32(n, d_out) > 0
+    dW, dX = torch.zeros_like(W), torch.zeros_like(A)
+    ctx.gcn_layer_bwd(1, 0.5, dZ, None, A, None, W, dW, dX, None)
+    torch.cuda.synchronize()
+    for name, got, a, b, depth in (("dZ W^T", dX, dZ, W.t().contiguous(), d_out), ("A^T dZ", dW, A.t().contiguous(), dZ, min(n, 1024))):
+        ref = a.double() @ b.double()
+        err = ((got.double() - ref).norm() / ref.norm()).item()
+        assert err <= 2.0 ** -24 * (1 + 0.5 * (depth / 32) ** 0.5), f"{name}: {err:.3g}"
+    ctx.close()
+
+
 @pytest.mark.parametrize("kind,shared,d_out", [(0, "dH_out", 48), (0, "A_saved", 48), (0, "H_out", 48), (0, "A_saved", 20),
                                                (1, "dH_out", 48), (1, "A_saved", 48), (1, "H_in", 48), (1, "H_in", 20)])
 def test_input_gradient_may_overwrite_what_it_came_from(kind, shared, d_out):
