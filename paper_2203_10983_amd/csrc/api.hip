@@ -453,7 +453,7 @@ bns_status run_batch(bns_ctx *ctx, TnBatch *batch, const TnLoss &loss, hipStream
 // batch (nullable): collects the weight gradient, to be run when the chain of the layers is through; without one it is
 // run before dH_in and dhalo are written, which may then share memory with dZ, A_saved or H_in.
 bns_status layer_bwd_impl(bns_ctx *ctx, int layer, double p, const float *dZ, const float *A_saved,
-                          const float *H_in, float *dW, float *dH_in, float *dhalo, const float *mask_src,
+                          const float *H_in, const float *W, float *dW, float *dH_in, float *dhalo, const float *mask_src,
                           bool update_first, const float *halo_first, float *W_step, float lr, bool dz_padded,
                           TnBatch *batch, hipStream_t s) {
   const int n_in = ctx->part.n_in, B = ctx->part.n_halo;
@@ -467,6 +467,7 @@ bns_status layer_bwd_impl(bns_ctx *ctx, int layer, double p, const float *dZ, co
     g.N = C2 ? 2 * d_in : d_in;
     g.K = d_out;
     g.A = G;
+    g.W = W;
     g.Bp = Wb;
     g.C = C;
     g.alpha = alpha;
@@ -474,6 +475,7 @@ bns_status layer_bwd_impl(bns_ctx *ctx, int layer, double p, const float *dZ, co
       g.N = g.ldc = d_in;
       const hipError_t e = gemm_rows(g, s);
       if (e != hipSuccess) return e;
+      g.W = W + (size_t)d_in * d_out;
       g.Bp = Wb + packed_bytes(d_out, d_in);
       g.C = C2;
       return gemm_rows(g, s);
@@ -819,7 +821,7 @@ bns_status bns_gcn_layer_bwd(bns_ctx *ctx, int32_t layer, double p, const float 
   } else {
     BNS_TRY("pack_weights", pack_weights(jobs, s));
   }
-  return layer_bwd_impl(ctx, layer, p, dZ, A_saved, H_in, dW, dH_in, dhalo, nullptr, false, nullptr, nullptr, 0.f, false,
+  return layer_bwd_impl(ctx, layer, p, dZ, A_saved, H_in, W, dW, dH_in, dhalo, nullptr, false, nullptr, nullptr, 0.f, false,
                         nullptr, s);
 }
 
@@ -879,7 +881,7 @@ static bns_status train_step_impl(bns_ctx *ctx, uint64_t seed, uint32_t epoch, c
   TnBatch batch;
   for (int l = L; l >= 1; --l) {
     float *dh = (dhalo && l > 1) ? dhalo[l - 1] : nullptr;
-    st = layer_bwd_impl(ctx, l, p, w.dZ[l], w.A[l], l > 1 ? w.H[l - 1] : X, dW[l - 1],
+    st = layer_bwd_impl(ctx, l, p, w.dZ[l], w.A[l], l > 1 ? w.H[l - 1] : X, W[l - 1], dW[l - 1],
                         l > 1 ? w.dZ[l - 1] : nullptr, dh,
                         l > 1 ? w.H[l - 1] : nullptr, layer_plan(ctx, l, X) == BNS_LAYER_UPDATE_FIRST,
                         ctx->part.n_halo > 0 ? halo_h[l - 1] : nullptr, W[l - 1], lr, l == L && pad_last, &batch, s);

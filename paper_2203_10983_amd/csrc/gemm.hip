@@ -51,6 +51,17 @@ struct RowsArgs {
 
 enum RowsEpilogue { kPlain = 0, kMask = 1, kPair = 2 };
 
+// An infinite operand has no split (its other pieces are NaN), nor has one beyond 3.389e38, which rounds to an infinite
+// piece, and a product near the top of the range can overflow in its first piece alone.  All of these end in a result that
+// is not finite, and such a result is formed once more as the plain fp32 sum, so that infinities and NaN come out as from the operands
+// themselves.  Looking costs an instruction per result and tile.
+__device__ __forceinline__ float nonfinite_seed(float z, const f32x4 &v) {  // z stays 0 while all values are finite
+#pragma unroll
+  for (int e = 0; e < 4; ++e) z = fmaf(v[e], 0.f, z);
+  return z;
+}
+__device__ __forceinline__ bool is_finite(float x) { return fabsf(x) <= 3.40282347e38f; }
+
 template <int R, int NC, int EPI>
 __global__ void __launch_bounds__(256, R * NC > 8 ? 3 : 4) gemm_rows_kernel(const RowsArgs a) {
   constexpr int kRows = 64 * R;  // rows of a workgroup's tile
@@ -149,8 +160,12 @@ __global__ void __launch_bounds__(256, R * NC > 8 ? 3 : 4) gemm_rows_kernel(cons
       const bool more = EPI != kPair && tile >= n_first;
       const int end = more ? M2 : M, first = (more ? tile - n_first : tile) * kRows;
       const float scale = more ? 1.f : p.alpha;
+      float nonfinite = 0.f;
 #pragma unroll
       for (int r = 0; r < R; ++r) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+          if (c < nt) nonfinite = nonfinite_seed(nonfinite, acc[c][r]);  // (nothing was loaded for tiles past the last)
         const int row = first + wid * 16 * R + r * 16 + l16;
         if (row >= end) continue;
         const size_t at = (size_t)row * p.ldc + col0;
@@ -181,6 +196,20 @@ __global__ void __launch_bounds__(256, R * NC > 8 ? 3 : 4) gemm_rows_kernel(cons
 #pragma unroll
             for (int e = 0; e < 3; ++e)
               if (e < left) d[e] = v[e];
+        }
+      }
+      if (nonfinite != 0.f) {  // (NaN)
+        const float *A = more ? p.A_more : p.A;
+#pragma unroll 1
+        for (int q = 0; q < R * NC * 4; ++q) {
+          const int row = first + wid * 16 * R + q / (NC * 4) * 16 + l16, col = col0 + q / 4 % NC * 16 + q % 4;
+          if (row >= end || col >= n_end) continue;
+          float *const d = (EPI == kPair && col >= p.c_split ? p.C2 - p.c_split : more ? p.C_more : p.C) + (size_t)row * p.ldc + col;
+          if (is_finite(*d)) continue;
+          float x = 0.f;
+#pragma unroll 1
+          for (int k = 0; k < p.K; ++k) x = fmaf(A[(size_t)row * p.K + k], p.W[(size_t)col * p.K + k], x);
+          *d = x * scale;
         }
       }
       if (ntile >= n_tiles) break;
@@ -396,10 +425,28 @@ __global__ void __launch_bounds__(256, 3) gemm_tn_kernel(const TnJobs jobs) {
     }
   }
   float *out = a.partials + (size_t)(split * a.nt + tile) * (MB * NB) + (size_t)wid * (MT * NT * 256) + lane * 4;
+  float nonfinite = 0.f;
 #pragma unroll
   for (int j = 0; j < NT; ++j)
 #pragma unroll
-    for (int i = 0; i < MT; ++i) *reinterpret_cast<f32x4 *>(out + (j * MT + i) * 256) = split & 1 ? -acc[j][i] : acc[j][i];
+    for (int i = 0; i < MT; ++i) {
+      nonfinite = nonfinite_seed(nonfinite, acc[j][i]);
+      *reinterpret_cast<f32x4 *>(out + (j * MT + i) * 256) = split & 1 ? -acc[j][i] : acc[j][i];
+    }
+  if (nonfinite != 0.f) {  // (NaN)
+#pragma unroll 1
+    for (int q = 0; q < NT * MT * 4; ++q) {  // element q % 4 of tile (j, i) as gemm_tn_reduce_kernel places it
+      const int j = q / 4 / MT, i = q / 4 % MT, sa = lane & 15;
+      const int m = m0 + (wm * MT + i) * 16 + 4 * (sa & 3) + (sa >> 2), n = n0 + (wn * NT + j) * 16 + 4 * (q % 4) + (lane >> 4);
+      float *const d = out + (j * MT + i) * 256 + q % 4;
+      if (m >= a.M || n >= a.N || is_finite(*d)) continue;
+      const float *A = a.A2 && m >= a.a_split ? a.A2 + (m - a.a_split) : a.A + m;
+      float x = 0.f;
+#pragma unroll 1
+      for (int k = k_begin; k < k_end; ++k) x = fmaf(A[(size_t)(a.rows ? a.rows[k] : k) * a.lda], a.B[(size_t)k * a.N + n], x);
+      *d = x;
+    }
+  }
 }
 
 // The sums over the splits, in a fixed order: C = sum (+ the sum of the next job, for a gradient of two parts),

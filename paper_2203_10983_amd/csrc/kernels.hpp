@@ -228,12 +228,12 @@ struct RowsF32 {
 };
 hipError_t gemm_rows_f32(const RowsF32 &g, hipStream_t s);
 
-// C[M,N] = alpha * A B with A [M,K], B [K,N] packed and split.  At most one of: C2 (nullable): columns from c_split (a
+// C[M,N] = alpha * A B with A [M,K], B [K,N] packed and split, from W [N,K].  At most one of: C2 (nullable): columns from c_split (a
 // multiple of 4) on go to C2, both with row stride ldc; mask (nullable, [M, ldc]): C is zeroed where mask <= 0.
 // A_more (nullable): in the same launch C_more[r] = A_more[r] B for r < *m2_dev (<= M2); not with C2.
 struct RowsGemm {
   int32_t M, N, K;
-  const float *A;
+  const float *A, *W;
   const void *Bp;
   float *C, *C2;
   int32_t ldc, c_split;

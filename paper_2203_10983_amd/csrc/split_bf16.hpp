@@ -16,8 +16,8 @@
 // Below 2^-110 the lo piece, then the mid piece are subnormal: such an operand is held to an absolute 2^-134.
 //
 // v_mfma_f32_16x16x32_bf16 runs at sixteen times the rate of the fp32 instruction, so six of them
-// take 6/16 of its time.  (|x| above 3.389e38 rounds to an infinite hi: such an element gives NaN
-// instead of an overflowing product.)
+// take 6/16 of its time.  Operands that are not finite, or round to an infinite hi (above 3.389e38), have no split:
+// gemm.hip forms their results once more without one.
 #pragma once
 #include <hip/hip_runtime.h>
 
