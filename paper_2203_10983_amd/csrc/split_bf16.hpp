@@ -84,10 +84,14 @@ __device__ __forceinline__ void mfma_split(f32x4 (&t)[R], const Frag3 &x, const 
 
 // One 16-byte-per-lane copy from global memory straight into LDS (lane i lands at lds + 16 i; both
 // arguments as the whole wavefront sees them).  Written as assembly so that the compiler does not
-// wait for it before unrelated LDS reads: the caller waits with lds_dma_wait() and a barrier.
+// wait for it before unrelated LDS reads: the caller waits with lds_dma_wait() and a barrier.  It overwrites M0, which
+// the compiler reserves (it says so when the register is named) but would otherwise take for unchanged.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 __device__ __forceinline__ void lds_dma16(const void *src_lane, unsigned lds_offset) {
-  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src_lane), "s"(lds_offset) : "memory");
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src_lane), "s"(lds_offset) : "m0", "memory");
 }
+#pragma clang diagnostic pop
 __device__ __forceinline__ void lds_dma_wait() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 __device__ __forceinline__ unsigned lds_offset_of(const void *p) {  // LDS pointers: the low half of the generic address
   return __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)p);
