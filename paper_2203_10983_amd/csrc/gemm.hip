@@ -9,9 +9,11 @@
 // tiles of 16.  Its rows come straight from global memory into the operand layout (a lane reads two
 // 16-byte pieces of its row per 32-deep step, four lanes of a row 64 contiguous bytes) and are split in
 // registers, each element once.  The packed weights of a step go from L2 straight into a
-// double-buffered LDS tile shared by the four wavefronts, one step ahead, across row tiles as well.
+// double-buffered LDS tile shared by the four wavefronts, one step ahead, across row tiles as well; those of a product of a
+// single step (K <= 32) are copied once and stay, without a wait or a barrier per tile.
 // The weight fragment is the first operand of the instruction, so a lane ends up with four
-// consecutive columns of one row and stores 16 bytes.
+// consecutive columns of one row; lanes of neighbouring rows trade pieces so that whole lines are stored (pieces of 64 bytes:
+// 578125 rows of 128 columns at depth 128 146 us, lines 128; at depth 16 65 and 58).
 //
 // gemm_tn: a thread reads 16-byte pieces of eight consecutive-depth rows of one operand, which makes
 // it hold eight depths of four columns: after the split each column's eight values are one 16-byte
@@ -60,10 +62,14 @@ __device__ __forceinline__ float nonfinite_seed(float z, const f32x4 &v) {  // z
   for (int e = 0; e < 4; ++e) z = fmaf(v[e], 0.f, z);
   return z;
 }
+// The value of the lane whose number differs in the last bit.
+__device__ __forceinline__ float quad_swap(float x) {
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0xb1, 0xf, 0xf, true));  // quad_perm:[1,0,3,2]
+}
 __device__ __forceinline__ bool is_finite(float x) { return fabsf(x) <= 3.40282347e38f; }
 
 template <int R, int NC, int EPI>
-__global__ void __launch_bounds__(256, R * NC > 8 ? 3 : 4) gemm_rows_kernel(const RowsArgs a) {
+__global__ void __launch_bounds__(256, R * NC > 8 || NC > 6 ? 3 : 4) gemm_rows_kernel(const RowsArgs a) {
   constexpr int kRows = 64 * R;  // rows of a workgroup's tile
   __shared__ __attribute__((aligned(16))) char Bs[2][NC * kFragSet];
   const RowsGemm &p = a.g;
@@ -101,6 +107,9 @@ __global__ void __launch_bounds__(256, R * NC > 8 ? 3 : 4) gemm_rows_kernel(cons
       if ((s + 1) * 32 <= p.K) {
 #pragma unroll
         for (int r = 0; r < R; ++r) ar[r][j] = *reinterpret_cast<const f32x4u *>(row_a[r] + k);
+      } else if (k + 4 <= p.K) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) ar[r][j] = *reinterpret_cast<const f32x4u *>(row_a[r] + k);
       } else {
 #pragma unroll
         for (int r = 0; r < R; ++r)
@@ -124,22 +133,29 @@ __global__ void __launch_bounds__(256, R * NC > 8 ? 3 : 4) gemm_rows_kernel(cons
 #pragma unroll
       for (int r = 0; r < R; ++r) acc[c][r] = f32x4{0.f, 0.f, 0.f, 0.f};
   };
+  const bool stay = S == 1;  // the weights of a single step stay in LDS for all tiles
   set_rows(tile);
   load_b(0, 0);
   load_a(0);
   clear();
+  if (stay) {
+    lds_dma_wait();
+    __syncthreads();
+  }
   int buf = 0;
   for (int s = 0;;) {
     Frag3 fa[R];
-    lds_dma_wait();
-    __syncthreads();  // this step's weights are in LDS, and everybody is done with the other buffer
+    if (!stay) {
+      lds_dma_wait();
+      __syncthreads();  // this step's weights are in LDS, and everybody is done with the other buffer
+    }
 #pragma unroll
     for (int r = 0; r < R; ++r) fa[r] = split8(ar[r][0], ar[r][1]);
     const bool last = s + 1 == S;
     const int ntile = last ? tile + stride : tile, ns = last ? 0 : s + 1;
     if (ntile < n_tiles) {
       if (last) set_rows(ntile);
-      load_b(ns, buf ^ 1);
+      if (!stay) load_b(ns, buf ^ 1);
       load_a(ns);
     }
     const char *bs = &Bs[buf][0] + lane * 16;
@@ -153,57 +169,73 @@ __global__ void __launch_bounds__(256, R * NC > 8 ? 3 : 4) gemm_rows_kernel(cons
 #pragma unroll
       for (int r = 0; r < R; ++r) acc[c][r] += part[r];
     }
-    buf ^= 1;
+    buf = stay ? ns : buf ^ 1;
     if (last) {
-      // lane: row l16 of the row tile, columns 16 c + 4 g .. + 3
-      const int n_end = p.N, col0 = t0 * 16 + g * 4;
+      // A lane holds columns 16 c + 4 g .. + 3 of row l16 for every tile c.  Of two tiles it trades one with the lane of the
+      // row beside its own, so that eight lanes hold 128 consecutive bytes of one row.
+      constexpr bool kTrade = NC > 1;
+      constexpr int W = kTrade ? 2 : 1, NP = (NC + W - 1) / W;  // tiles, and rows, of a trade
+      const int odd = kTrade ? l16 & 1 : 0;
+      const int n_end = p.N, col0 = (t0 + odd) * 16 + g * 4;
       const bool more = EPI != kPair && tile >= n_first;
-      const int end = more ? M2 : M, first = (more ? tile - n_first : tile) * kRows;
+      const int end = more ? M2 : M, row0 = (more ? tile - n_first : tile) * kRows + wid * 16 * R + l16 - odd;
       const float scale = more ? 1.f : p.alpha;
+      const float alpha = (t0 + odd) & 1 ? -scale : scale;  // odd tiles are summed negated
       float nonfinite = 0.f;
 #pragma unroll
-      for (int r = 0; r < R; ++r) {
+      for (int r = 0; r < R; ++r)
 #pragma unroll
-        for (int c = 0; c < NC; ++c)
-          if (c < nt) nonfinite = nonfinite_seed(nonfinite, acc[c][r]);  // (nothing was loaded for tiles past the last)
-        const int row = first + wid * 16 * R + r * 16 + l16;
-        if (row >= end) continue;
-        const size_t at = (size_t)row * p.ldc + col0;
-        float *const dst = (more ? p.C_more : p.C) + at;
-        float *const dst2 = EPI == kPair ? p.C2 + at - p.c_split : nullptr;  // c_split % 4 == 0
-        const float *const ms = EPI == kMask ? p.mask + at : nullptr;
+        for (int c = 0; c < NP; ++c) {
+          f32x4 out[W];
+          if constexpr (kTrade) {
+            const f32x4 x = acc[2 * c][r], y = 2 * c + 1 < NC ? acc[2 * c + 1 < NC ? 2 * c + 1 : 0][r] : f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int c = 0; c < NC; ++c) {
-          const int left = n_end - (col0 + c * 16);  // columns from this lane's first one to the end
-          f32x4 v = acc[c][r];
-          const float alpha = (t0 + c) & 1 ? -scale : scale;  // odd tiles are summed negated
-          if (EPI == kMask && !more) {
-            f32x4 m = {0.f, 0.f, 0.f, 0.f};
-            if (left >= 4) m = *reinterpret_cast<const f32x4u *>(ms + c * 16);
+            for (int e = 0; e < 4; ++e) {
+              const float got = quad_swap(odd ? x[e] : y[e]);
+              out[0][e] = odd ? got : x[e];
+              out[W - 1][e] = odd ? y[e] : got;
+            }
+          } else {
+            out[0] = acc[c][r];
+          }
+          const int col = col0 + c * 16 * W;
+          const int left = c * W + odd < nt ? n_end - col : 0;  // columns from this lane's first one to the end; none of other blocks' tiles
+#pragma unroll
+          for (int h = 0; h < W; ++h) {
+            const int row = row0 + r * 16 + h;
+            if (row >= end || left <= 0) continue;
+            f32x4 v = out[h];
+            nonfinite = nonfinite_seed(nonfinite, v);
+            const size_t at = (size_t)row * p.ldc + col;
+            const float a = W == 1 && (t0 + c) & 1 ? -scale : alpha;
+            if (EPI == kMask && !more) {
+              const float *const ms = p.mask + at;
+              f32x4 m = {0.f, 0.f, 0.f, 0.f};
+              if (left >= 4) m = *reinterpret_cast<const f32x4u *>(ms);
+              else
+#pragma unroll
+                for (int e = 0; e < 3; ++e)
+                  if (e < left) m[e] = ms[e];
+#pragma unroll
+              for (int e = 0; e < 4; ++e) v[e] = m[e] > 0.f ? v[e] * a : 0.f;
+            } else {
+#pragma unroll
+              for (int e = 0; e < 4; ++e) v[e] *= a;
+            }
+            float *const d = (EPI == kPair && col >= p.c_split ? p.C2 - p.c_split : more ? p.C_more : p.C) + at;  // c_split % 4 == 0
+            if (left >= 4) *reinterpret_cast<f32x4u *>(d) = v;
             else
 #pragma unroll
               for (int e = 0; e < 3; ++e)
-                if (e < left) m[e] = ms[c * 16 + e];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = m[e] > 0.f ? v[e] * alpha : 0.f;
-          } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] *= alpha;
+                if (e < left) d[e] = v[e];
           }
-          float *const d = (EPI == kPair && col0 + c * 16 >= p.c_split ? dst2 : dst) + c * 16;
-          if (left >= 4) *reinterpret_cast<f32x4u *>(d) = v;
-          else
-#pragma unroll
-            for (int e = 0; e < 3; ++e)
-              if (e < left) d[e] = v[e];
         }
-      }
       if (nonfinite != 0.f) {  // (NaN)
         const float *A = more ? p.A_more : p.A;
 #pragma unroll 1
-        for (int q = 0; q < R * NC * 4; ++q) {
-          const int row = first + wid * 16 * R + q / (NC * 4) * 16 + l16, col = col0 + q / 4 % NC * 16 + q % 4;
-          if (row >= end || col >= n_end) continue;
+        for (int q = 0; q < R * NP * W * 4; ++q) {
+          const int c = q / (4 * W) % NP, row = row0 + q / (NP * W * 4) * 16 + q / 4 % W, col = col0 + c * 16 * W + q % 4;
+          if (row >= end || col >= n_end || c * W + odd >= nt) continue;
           float *const d = (EPI == kPair && col >= p.c_split ? p.C2 - p.c_split : more ? p.C_more : p.C) + (size_t)row * p.ldc + col;
           if (is_finite(*d)) continue;
           float x = 0.f;
@@ -260,8 +292,11 @@ hipError_t gemm_rows(const RowsGemm &g, hipStream_t s) {
   while (groups() < kWanted && a.nblk * 2 <= a.T) a.nblk *= 2;
   int nc = (a.T + a.nblk - 1) / a.nblk;
   a.nblk = (a.T + nc - 1) / nc;
-  // a grid of whole octets of row tiles, every column block of each; the tiles past one resident round are walked
-  int64_t octets = std::min<int64_t>((row_tiles() + 7) / 8, std::max<int64_t>(1, 768 / (8 * a.nblk)));
+  // A grid of whole octets of row tiles, every column block of each; the tiles past one resident round are walked.  A
+  // single step in a single column block is over before the next tile's rows have come: a workgroup per tile there
+  // (128 columns at depth 16: 578125 rows 65 -> 58 us; 512 columns, four blocks, 89625 rows: 42 us, 38 when walked).
+  int64_t octets = (row_tiles() + 7) / 8;
+  if (a.S > 1 || a.nblk > 1) octets = std::min<int64_t>(octets, std::max<int64_t>(1, 768 / (8 * a.nblk)));
   const unsigned grid = (unsigned)(octets * 8 * a.nblk);
   if (R == 2) launch_rows<2>(a, nc, grid, s);
   else launch_rows<1>(a, nc, grid, s);

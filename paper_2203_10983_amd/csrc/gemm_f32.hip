@@ -9,9 +9,12 @@
 // 32.  Its rows come straight from global memory: a lane reads four consecutive depths of its row, and
 // a swap of wavefront halves per pair of registers turns the eight depths of the two halves into the
 // operands of four instructions in depth order.  The weights, packed once per step as operand fragments,
-// are copied from L2 into a double-buffered LDS tile, one 32-deep step ahead, across row tiles as well:
-// one 16-byte LDS read feeds four instructions, and the matrix pipe is what is left to wait for.
+// are copied from L2 into a double-buffered LDS tile, one 32-deep step ahead, across row tiles as well (those of a
+// product of a single step once, to stay): one 16-byte LDS read feeds four instructions, and the matrix pipe is what is left
+// to wait for.  The weights are the second operand of the instruction: a lane ends up with a column, and a wavefront stores
+// 128 consecutive bytes of a row (with four columns per lane, 32-byte pieces of 32 rows: 32 -> 128 on 578125 rows 94 us, 79).
 #include <algorithm>
+#include <type_traits>
 
 #include "kernels.hpp"
 #include "split_bf16.hpp"
@@ -30,7 +33,7 @@ struct F32Args {
 
 // REC: the rows of A are followed by the ones that g.rec names (a second result, row tiles of its own).
 template <int NC, bool ACC, bool REC>
-__global__ void __launch_bounds__(256, 4) gemm_rows_f32_kernel(const F32Args a) {
+__global__ void __launch_bounds__(256, NC > 2 ? 3 : 4) gemm_rows_f32_kernel(const F32Args a) {
   constexpr int kRows = 128;
   __shared__ __attribute__((aligned(16))) char Bs[2][NC * kF32Step];
   const RowsF32 &p = a.g;
@@ -79,9 +82,13 @@ __global__ void __launch_bounds__(256, 4) gemm_rows_f32_kernel(const F32Args a) 
       for (int j = 0; j < 4; ++j) ar[j] = *reinterpret_cast<const f32x4u *>(src[j]);
     } else {
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
+      for (int j = 0; j < 4; ++j) {
+        const int k = s * 32 + j * 8 + hi * 4;
+        if (k + 4 <= p.K) ar[j] = *reinterpret_cast<const f32x4u *>(src[j]);
+        else
 #pragma unroll
-        for (int e = 0; e < 4; ++e) ar[j][e] = s * 32 + j * 8 + hi * 4 + e < p.K ? src[j][e] : 0.f;
+          for (int e = 0; e < 4; ++e) ar[j][e] = k + e < p.K ? src[j][e] : 0.f;
+      }
     }
   };
   const unsigned lds0 = lds_offset_of(&Bs[0][0]);
@@ -98,14 +105,21 @@ __global__ void __launch_bounds__(256, 4) gemm_rows_f32_kernel(const F32Args a) 
 #pragma unroll
       for (int i = 0; i < 16; ++i) acc[c][i] = 0.f;
   };
+  const bool stay = S == 1;  // the weights of a single step stay in LDS for all tiles
   set_rows(tile);
   load_b(0, 0);
   load_a(0);
   clear();
+  if (stay) {
+    lds_dma_wait();
+    __syncthreads();
+  }
   int buf = 0;
   for (int s = 0;;) {
-    lds_dma_wait();
-    __syncthreads();  // this step's weights are in LDS, and everybody is done with the other buffer
+    if (!stay) {
+      lds_dma_wait();
+      __syncthreads();  // this step's weights are in LDS, and everybody is done with the other buffer
+    }
     if constexpr (REC) {
 #pragma unroll
       for (int j = 0; j < 4; ++j)
@@ -127,7 +141,7 @@ __global__ void __launch_bounds__(256, 4) gemm_rows_f32_kernel(const F32Args a) 
     const int ntile = last ? tile + stride : tile, ns = last ? 0 : s + 1;
     if (ntile < n_tiles) {
       if (last) set_rows(ntile);
-      load_b(ns, buf ^ 1);
+      if (!stay) load_b(ns, buf ^ 1);
       load_a(ns);
     }
     const char *bs = &Bs[buf][0] + lane * 16;
@@ -139,47 +153,47 @@ __global__ void __launch_bounds__(256, 4) gemm_rows_f32_kernel(const F32Args a) 
 #pragma unroll
       for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int c = 0; c < NC; ++c) acc[c] = __builtin_amdgcn_mfma_f32_32x32x2f32(b[c][i], op[j][i], acc[c], 0, 0, 0);
+        for (int c = 0; c < NC; ++c) acc[c] = __builtin_amdgcn_mfma_f32_32x32x2f32(op[j][i], b[c][i], acc[c], 0, 0, 0);
     }
-    buf ^= 1;
+    buf = stay ? ns : buf ^ 1;
     if (last) {
-      // lane: row l32 of the wavefront's 32; register 4 q + e of tile c: column 32 c + 8 q + 4 hi + e
+      // lane: column 32 c + l32; register 4 q + e of tile c: row 8 q + 4 hi + e of the wavefront's 32
       const bool second = REC && tile >= n_first;
-      const int row = (second ? tile - n_first : tile) * kRows + wid * 32 + l32;
-      if (row < (second ? M2 : M)) {
-        const int n_end = p.pad ? p.ldc : p.N, col0 = t0 * 32 + hi * 4;  // pad: the packed weights are zero there
-        float *const dst = (second ? p.C_rec : p.C) + (size_t)row * p.ldc + col0;
+      const int row0 = (second ? tile - n_first : tile) * kRows + wid * 32, rows = (second ? M2 : M) - row0;
+      const int n_end = p.pad ? p.ldc : p.N;  // pad: the packed weights are zero there
+      float *const dst = (second ? p.C_rec : p.C) + (size_t)row0 * p.ldc;
+      auto store = [&](auto full) {  // full: all 32 rows are there
 #pragma unroll
-        for (int c = 0; c < NC; ++c)
+        for (int c = 0; c < NC; ++c) {
+          const int col = (t0 + c) * 32 + l32;
+          if (col >= n_end) continue;
+          const unsigned at = (unsigned)(hi * 4 * p.ldc + col) * 4u;  // bytes
 #pragma unroll
-          for (int q4 = 0; q4 < 4; ++q4) {
-            const int at = c * 32 + q4 * 8, left = n_end - (col0 + at);
-            if (left <= 0) continue;
-            float *const d = dst + at;
-            f32x4 v = {acc[c][4 * q4], acc[c][4 * q4 + 1], acc[c][4 * q4 + 2], acc[c][4 * q4 + 3]};
-            if constexpr (ACC) {
+          for (int q = 0; q < 4; ++q) {
+            f32x4 v = {acc[c][4 * q], acc[c][4 * q + 1], acc[c][4 * q + 2], acc[c][4 * q + 3]};
+            auto each = [&](auto f) {
 #pragma unroll
               for (int e = 0; e < 4; ++e)
-                if (e < left) v[e] += d[e];
-            }
+                if (decltype(full)::value || q * 8 + hi * 4 + e < rows) v[e] = f(reinterpret_cast<float *>(reinterpret_cast<char *>(dst + (size_t)(q * 8 + e) * p.ldc) + at), v[e]);
+            };
+            if constexpr (ACC) each([](const float *d, float x) { return x + *d; });
             if (p.relu) {
 #pragma unroll
               for (int e = 0; e < 4; ++e) v[e] = fmaxf(v[e], 0.f);
               if (p.drop.scale != 0.f) {
 #pragma unroll 1
                 for (int e = 0; e < 4; ++e) {
-                  const float y = dropout_keeps(p.drop, row, col0 + at + e) ? v[0] * p.drop.scale : 0.f;
+                  const float y = dropout_keeps(p.drop, row0 + q * 8 + hi * 4 + e, col) ? v[0] * p.drop.scale : 0.f;
                   v = f32x4{v[1], v[2], v[3], y};
                 }
               }
             }
-            if (left >= 4) *reinterpret_cast<f32x4u *>(d) = v;
-            else
-#pragma unroll
-              for (int e = 0; e < 3; ++e)
-                if (e < left) d[e] = v[e];
+            each([](float *d, float x) { return *d = x; });
           }
-      }
+        }
+      };
+      if (rows >= 32) store(std::true_type{});
+      else store(std::false_type{});
       if (ntile >= n_tiles) break;
       clear();
       tile = ntile;
@@ -197,14 +211,18 @@ hipError_t gemm_rows_f32(const RowsF32 &g, hipStream_t s) {
   a.g = g;
   a.T = (g.N + 31) / 32;
   a.S = (g.K + 31) / 32;
-  // up to 4 column tiles per wavefront, evenly dealt; fewer where that leaves the chip short of workgroups
-  // (a row count on the device is usually a fraction of its bound: priced at a quarter)
+  // Up to 4 column tiles per wavefront, evenly dealt; fewer where that leaves the chip short of workgroups
+  // (a row count on the device is usually a fraction of its bound: priced at a quarter).  Three or four are held to three
+  // workgroups per compute unit, which spills nothing (four: 26 registers of the four-tile kernel, 423 us instead of 369 for
+  // 89625 x 512 x 512).  A product of a single step is bound by its stores: two tiles and a workgroup per row tile
+  // (578125 rows, 16 -> 172: 126 us walked with four tiles, 103; 32 -> 128: 82, 73).
   const int64_t row_tiles = (g.M + 127) / 128 + (g.rec ? (g.M2 / 4 + 127) / 128 : 0);
-  a.nblk = (a.T + 3) / 4;
+  a.nblk = a.S == 1 ? (a.T + 1) / 2 : (a.T + 3) / 4;
   while (row_tiles * a.nblk < 512 && a.nblk < a.T) a.nblk = std::min(a.nblk * 2, a.T);
   const int nc = (a.T + a.nblk - 1) / a.nblk;
   a.nblk = (a.T + nc - 1) / nc;
-  const int64_t octets = std::min<int64_t>((row_tiles + 7) / 8, std::max<int64_t>(1, 1024 / (8 * a.nblk)));
+  int64_t octets = (row_tiles + 7) / 8;
+  if (a.S > 1) octets = std::min<int64_t>(octets, std::max<int64_t>(1, (nc > 2 ? 768 : 1024) / (8 * a.nblk)));
   const unsigned grid = (unsigned)(octets * 8 * a.nblk);
 #define BNS_ROWS_F32(NC)                                                          \
   do {                                                                          \

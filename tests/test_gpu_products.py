@@ -11,6 +11,9 @@ pytestmark = pytest.mark.gpu
 
 SHAPES = [(1, 1, 1), (63, 17, 15), (64, 32, 16), (65, 33, 129), (130, 602, 41), (1000, 127, 130), (517, 66, 9),
           (4099, 128, 172), (40000, 100, 47), (70001, 128, 128)]
+# one depth step, forward (d_in <= 32) or backward (d_out <= 32): weights that stay in LDS, a workgroup per row tile or a walk
+SHAPES += [(130001, 16, 172), (30001, 9, 47), (50000, 32, 128), (129, 31, 33), (100001, 602, 9), (50001, 100, 16), (33000, 16, 16),
+           (200000, 128, 32)]
 
 
 def _loops(n):
