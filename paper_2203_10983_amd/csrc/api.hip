@@ -287,6 +287,8 @@ struct PhaseTimer {
 };
 
 bool bad_p(double p) { return !(p >= 0.0 && p <= 1.0); }
+// Kept boundary nodes to be expected: launches are shaped for it, buffers for all of them.
+int32_t expected_kept(const bns_ctx *ctx, double p) { return (int32_t)std::ceil(p * ctx->part.n_halo); }
 float halo_scale(double p) { return p > 0.0 ? (float)(1.0 / p) : 0.f; }  // 1/p is never formed at p = 0
 
 // Dropout of hidden layer `layer` in the current epoch (off when the rate is 0 or the layer has no ReLU).
@@ -347,6 +349,7 @@ bns_status layer_fwd_impl(bns_ctx *ctx, int layer, double p, const float *H_in, 
         g.A_rec = halo_h;
         g.C_rec = ctx->ws.Hu2;
         g.M2 = B;
+        g.m2_expected = expected_kept(ctx, p);
         g.m2_dev = ctx->cur_n_kept;
       }
       BNS_TRY("gemm_rows_f32", gemm_rows_f32(g, s));
@@ -486,6 +489,7 @@ bns_status layer_bwd_impl(bns_ctx *ctx, int layer, double p, const float *dZ, co
     g.A_more = G_more;
     g.C_more = C_more;
     g.M2 = B;
+    g.m2_expected = expected_kept(ctx, p);
     g.m2_dev = ctx->cur_n_kept;
     return gemm_rows(g, s);
   };
@@ -528,6 +532,7 @@ bns_status layer_bwd_impl(bns_ctx *ctx, int layer, double p, const float *dZ, co
       TnGemm *g = add_dw(B, halo_first, nullptr, G_halo, ctx->ws.tn2[layer]);
       g->rows = ctx->cur_kept;
       g->k_dev = ctx->cur_n_kept;
+      g->k_expected = expected_kept(ctx, p);
       g->accumulate = true;
     }
     if (dH_in) {

@@ -285,7 +285,7 @@ hipError_t gemm_rows(const RowsGemm &g, hipStream_t s) {
   constexpr int kWanted = 512;
   a.nblk = (a.T + 7) / 8;
   int R = 2;
-  const int64_t m2 = g.A_more ? g.M2 / 4 : 0;  // a row count on the device is usually a fraction of its bound
+  const int64_t m2 = g.A_more ? g.m2_expected : 0;
   auto row_tiles = [&]() { return (g.M + 64 * R - 1) / (64 * R) + (m2 + 64 * R - 1) / (64 * R); };
   auto groups = [&]() { return row_tiles() * a.nblk; };
   if (groups() < kWanted) R = 1;
@@ -619,8 +619,7 @@ hipError_t gemm_tn(const TnGemm *g, int32_t n, const TnLoss &loss, hipStream_t s
   for (int i = 0; i < n; ++i) {
     if (g[i].accumulate) plan[i] = plan[i - 1];  // the two parts of one gradient have the same result tiles
     else tn_tiles(g[i].M, g[i].N, std::max<int64_t>(g[i].K, i + 1 < n && g[i + 1].accumulate ? g[i + 1].K : 0), &plan[i]);
-    // a depth on the device is usually a fraction of its bound: price it at a quarter
-    depth[i] = g[i].k_dev ? (g[i].K + 3) / 4 : g[i].K;
+    depth[i] = g[i].k_dev ? g[i].k_expected : g[i].K;
   }
   // A job that fills the chip with chunks of kTnAlone rows or more gets a launch of its own, its splits dealt
   // evenly over the XCDs.  The smaller jobs of one tile shape share a launch and the length of a chunk: the

@@ -211,12 +211,11 @@ hipError_t gemm_rows_f32(const RowsF32 &g, hipStream_t s) {
   a.g = g;
   a.T = (g.N + 31) / 32;
   a.S = (g.K + 31) / 32;
-  // Up to 4 column tiles per wavefront, evenly dealt; fewer where that leaves the chip short of workgroups
-  // (a row count on the device is usually a fraction of its bound: priced at a quarter).  Three or four are held to three
+  // Up to 4 column tiles per wavefront, evenly dealt; fewer where that leaves the chip short of workgroups.  Three or four are held to three
   // workgroups per compute unit, which spills nothing (four: 26 registers of the four-tile kernel, 423 us instead of 369 for
   // 89625 x 512 x 512).  A product of a single step is bound by its stores: two tiles and a workgroup per row tile
   // (578125 rows, 16 -> 172: 126 us walked with four tiles, 103; 32 -> 128: 82, 73).
-  const int64_t row_tiles = (g.M + 127) / 128 + (g.rec ? (g.M2 / 4 + 127) / 128 : 0);
+  const int64_t row_tiles = (g.M + 127) / 128 + (g.rec ? (g.m2_expected + 127) / 128 : 0);
   a.nblk = a.S == 1 ? (a.T + 1) / 2 : (a.T + 3) / 4;
   while (row_tiles * a.nblk < 512 && a.nblk < a.T) a.nblk = std::min(a.nblk * 2, a.T);
   const int nc = (a.T + a.nblk - 1) / a.nblk;

@@ -210,7 +210,7 @@ struct Dropout {
 // pad: the columns N..ldc-1 are set to zero (ldc at most N rounded up to a multiple of 4; not with relu or
 // accumulate).
 // rec (nullable; from halo_records): in the same launch C_rec[r] = as_float(rec[r].y) * A_rec[rec[r].x] B for r < *m2_dev
-// (<= M2); not with A2, relu or accumulate.
+// (<= M2, about m2_expected, which shapes the launch); not with A2, relu or accumulate.
 struct RowsF32 {
   int32_t M, N, K;
   const float *A, *A2;
@@ -222,7 +222,7 @@ struct RowsF32 {
   const int2 *rec;
   const float *A_rec;
   float *C_rec;
-  int32_t M2;
+  int32_t M2, m2_expected;
   const int32_t *m2_dev;
   Dropout drop;
 };
@@ -230,7 +230,7 @@ hipError_t gemm_rows_f32(const RowsF32 &g, hipStream_t s);
 
 // C[M,N] = alpha * A B with A [M,K], B [K,N] packed and split, from W [N,K].  At most one of: C2 (nullable): columns from c_split (a
 // multiple of 4) on go to C2, both with row stride ldc; mask (nullable, [M, ldc]): C is zeroed where mask <= 0.
-// A_more (nullable): in the same launch C_more[r] = A_more[r] B for r < *m2_dev (<= M2); not with C2.
+// A_more (nullable): in the same launch C_more[r] = A_more[r] B for r < *m2_dev (<= M2, about m2_expected); not with C2.
 struct RowsGemm {
   int32_t M, N, K;
   const float *A, *W;
@@ -241,7 +241,7 @@ struct RowsGemm {
   const float *mask;
   const float *A_more;
   float *C_more;
-  int32_t M2;
+  int32_t M2, m2_expected;
   const int32_t *m2_dev;
 };
 hipError_t gemm_rows(const RowsGemm &g, hipStream_t s);
@@ -253,7 +253,7 @@ hipError_t degree_inverse(const int32_t *deg, int32_t n, float *inv, hipStream_t
 // stride a_split, M = 2 a_split); accumulate: adds to the C of the job before it instead (same M, N).  The depth is split
 // over the chip and summed in a fixed order; partials: scratch of
 // gemm_tn_partials(M, N, K, depth of the other part of the same gradient or 0) floats per job.  rows
-// (nullable, [K]): the rows of A are those.  k_dev (nullable): depth on the device, *k_dev <= K.  lr > 0: also
+// (nullable, [K]): the rows of A are those.  k_dev (nullable): depth on the device, *k_dev <= K and about k_expected.  lr > 0: also
 // W -= lr * C, the plain update of Algorithm 1.  A batch of up to kMaxTnJobs jobs shares its launches; in the last of
 // them *loss.out (nullable) becomes the sum of loss.n partial losses.
 struct TnGemm {
@@ -264,6 +264,7 @@ struct TnGemm {
   float *C, *partials;
   bool accumulate;
   const int32_t *k_dev;
+  int32_t k_expected;
   float *W;
   float lr;
 };
