@@ -282,20 +282,25 @@ bns_status bns_ws_view(const bns_ctx *ctx, bns_view which, int32_t layer, void *
  * with two HIP events on the call's stream.  At most max_records brackets are kept between two
  * reads; further ones are dropped.  bns_profile_read waits for the recorded events, returns per
  * phase the summed milliseconds and the number of brackets since the last read, and clears them.
- * Events are host objects: no device memory is allocated. */
+ * Events are host objects: no device memory is allocated.
+ * Untimed, a step packs its weights for the products in the launch of the selection step (the layer calls: in that of the
+ * gather) and updates them in the last launch of the weight gradients.  While SAMPLE (GATHER) or SGD is
+ * timed, that work gets launches of its own, with the same results, so that a phase holds its own kernels only; the
+ * packing then belongs to no phase.  Two smaller things stay where they ride along: the flags of the kept boundary
+ * entries and the records of the kept rows in SAMPLE, the sum of the partial losses in GEMM_DW. */
 typedef enum {
   BNS_PHASE_SAMPLE = 0,   /* sample_boundary kernels; in bns_train_step on a small partition (at most 4096
                              boundary nodes, 8192 boundary entries, 16384 inner nodes + inner entries) the one
                              launch that runs the selection and the subgraph step together               */
   BNS_PHASE_BUILD = 1,    /* sampled CSR + transposed CSR (no bracket where the sample phase covers it)  */
-  BNS_PHASE_GATHER = 2,   /* gather of kept boundary features (x 1/p)      */
+  BNS_PHASE_GATHER = 2,   /* layer calls: records of the kept boundary rows (x 1/p); a step has them from SAMPLE */
   BNS_PHASE_SPMM_FWD = 3, /* aggregate                                     */
   BNS_PHASE_GEMM_FWD = 4, /* update  A W                                   */
   BNS_PHASE_LOSS = 5,
   BNS_PHASE_GEMM_DW = 6,  /* A^T dZ (split-K + reduction)                  */
   BNS_PHASE_GEMM_DA = 7,  /* dZ W^T                                        */
   BNS_PHASE_SPMM_BWD = 8, /* transposed aggregate                          */
-  BNS_PHASE_SGD = 9,
+  BNS_PHASE_SGD = 9,      /* w <- w - lr * g, where lr > 0                 */
   BNS_PHASE_SPMM_LONG = 10, /* forward aggregate of the rows longer than one segment, where it
                                runs as a pass of its own before a one-kernel layer */
   BNS_PHASE_COUNT = 11

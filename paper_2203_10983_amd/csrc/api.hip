@@ -268,6 +268,9 @@ bns_status hip_fail(bns_ctx *ctx, const char *what, hipError_t e) {
     if (_e != hipSuccess) return hip_fail(ctx, what, _e);     \
   } while (0)
 
+// A launch that carries work of two kinds is taken apart while the phase that it would be counted for is timed.
+bool timed(const bns_ctx *ctx, int phase) { return ((ctx->prof.mask >> phase) & 1u) && ctx->prof.used < ctx->prof.start.size(); }
+
 // Brackets the kernels enqueued during its lifetime with two events (only if the phase is enabled).
 struct PhaseTimer {
   Profiler *p = nullptr;
@@ -366,9 +369,11 @@ bns_status layer_fwd_impl(bns_ctx *ctx, int layer, double p, const float *H_in, 
   // copy of the rows would cost a read and a write of every kept row on top of the same reads.
   // In a training step the sampler has written these records and the weights are packed.
   if (prepare) {
+    const bool apart = timed(ctx, BNS_PHASE_GATHER);
+    if (apart) BNS_TRY("pack_weights", pack_weights(*prepare, s));
     PhaseTimer t(ctx, BNS_PHASE_GATHER, s);
     BNS_TRY("halo_records", halo_records(ctx->cur_kept, ctx->cur_n_kept, B, sage ? nullptr : ctx->ws.dis_halo,
-                                         halo_scale(p), ctx->ws.halo_rec, *prepare, s));
+                                         halo_scale(p), ctx->ws.halo_rec, apart ? PackJobs{} : *prepare, s));
   }
   SpmmRowPart part;
   part.halo_rec = B > 0 ? ctx->ws.halo_rec : nullptr;
@@ -853,6 +858,10 @@ static bns_status train_step_impl(bns_ctx *ctx, uint64_t seed, uint32_t epoch, c
       jobs = PackJobs{};
     }
   }
+  if (timed(ctx, BNS_PHASE_SAMPLE)) {
+    BNS_TRY("pack_weights", pack_weights(jobs, s));
+    jobs = PackJobs{};
+  }
   bns_status st = sample_and_build_impl(ctx, seed, epoch, epoch_dev, p, jobs, s);
   if (st != BNS_OK) return st;
 
@@ -883,18 +892,25 @@ static bns_status train_step_impl(bns_ctx *ctx, uint64_t seed, uint32_t epoch, c
   // dZ[l] is the gradient w.r.t. the pre-activation of layer l; the backward pass of layer l writes
   // dZ[l-1], already masked by the activations of the layer below.  Every layer keeps its own buffer
   // (BNS_VIEW_DZ), so that each stage of the backward pass can be inspected with its exact inputs.
+  const bool update_apart = lr > 0.f && timed(ctx, BNS_PHASE_SGD);
   TnBatch batch;
   for (int l = L; l >= 1; --l) {
     float *dh = (dhalo && l > 1) ? dhalo[l - 1] : nullptr;
     st = layer_bwd_impl(ctx, l, p, w.dZ[l], w.A[l], l > 1 ? w.H[l - 1] : X, W[l - 1], dW[l - 1],
                         l > 1 ? w.dZ[l - 1] : nullptr, dh,
                         l > 1 ? w.H[l - 1] : nullptr, layer_plan(ctx, l, X) == BNS_LAYER_UPDATE_FIRST,
-                        ctx->part.n_halo > 0 ? halo_h[l - 1] : nullptr, W[l - 1], lr, l == L && pad_last, &batch, s);
+                        ctx->part.n_halo > 0 ? halo_h[l - 1] : nullptr, W[l - 1], update_apart ? 0.f : lr, l == L && pad_last,
+                        &batch, s);
     if (st != BNS_OK) return st;
     if (l == 1 || batch.full()) {
       st = run_batch(ctx, &batch, l == 1 ? loss_sum : TnLoss{}, s);
       if (st != BNS_OK) return st;
     }
+  }
+  if (update_apart) {
+    PhaseTimer t(ctx, BNS_PHASE_SGD, s);
+    for (int l = 1; l <= L; ++l)
+      BNS_TRY("sgd_update", sgd_update((int64_t)(ctx->layer_kind == 1 ? 2 : 1) * ctx->dims[l - 1] * ctx->dims[l], W[l - 1], dW[l - 1], lr, s));
   }
   return BNS_OK;
 }

@@ -290,6 +290,8 @@ hipError_t dropout_inplace(int32_t n_rows, int32_t d, float *H, const Dropout &d
 // out = scale * dH where H > 0 else 0.  pack: weights to pack in the same launch.
 hipError_t relu_mask(int64_t n, const float *dH, const float *H, float scale, float *out, const PackJobs &pack,
                      hipStream_t s);
+// W -= lr * dW on n weights, as gemm_tn does it on the way (same bits): for a step whose update is timed by itself.
+hipError_t sgd_update(int64_t n, float *W, const float *dW, float lr, hipStream_t s);
 // Adam step t (1-based) on n weights; m, v are the caller's moment buffers.
 hipError_t adam_update(int64_t n, float *W, const float *dW, float *m, float *v, float lr, float b1,
                        float b2, float eps, int32_t t, hipStream_t s);

@@ -246,6 +246,16 @@ adam_kernel(int64_t n, float *__restrict__ W, const float *__restrict__ dW, floa
   W[i] -= lr * (mi * c1) / (sqrtf(vi * c2) + eps);
 }
 
+__global__ void __launch_bounds__(kT)
+sgd_kernel(int64_t n, float *__restrict__ W, const float *__restrict__ dW, float lr) {
+  const int64_t i = (int64_t)blockIdx.x * kT + threadIdx.x;
+  if (i < n) W[i] -= lr * dW[i];
+}
+hipError_t sgd_update(int64_t n, float *W, const float *dW, float lr, hipStream_t s) {
+  if (n > 0) sgd_kernel<<<(unsigned)((n + kT - 1) / kT), kT, 0, s>>>(n, W, dW, lr);
+  return hipGetLastError();
+}
+
 hipError_t adam_update(int64_t n, float *W, const float *dW, float *m, float *v, float lr, float b1,
                        float b2, float eps, int32_t t, hipStream_t s) {
   if (n <= 0) return hipSuccess;
