@@ -292,6 +292,12 @@ struct PhaseTimer {
 bool bad_p(double p) { return !(p >= 0.0 && p <= 1.0); }
 // Kept boundary nodes to be expected: launches are shaped for it, buffers for all of them.
 int32_t expected_kept(const bns_ctx *ctx, double p) { return (int32_t)std::ceil(p * ctx->part.n_halo); }
+// Entries per row of a transposed aggregate, to be expected.
+int32_t transposed_len(const bns_ctx *ctx, double p, bool halo_rows) {
+  const bns_partition_desc &P = ctx->part;
+  const double q = halo_rows ? p : 0.0;
+  return (int32_t)(((double)P.e_in + q * (double)P.e_bd) / ((double)P.n_in + q * P.n_halo));
+}
 float halo_scale(double p) { return p > 0.0 ? (float)(1.0 / p) : 0.f; }  // 1/p is never formed at p = 0
 
 // Dropout of hidden layer `layer` in the current epoch (off when the rate is 0 or the layer has no ReLU).
@@ -529,7 +535,7 @@ bns_status layer_bwd_impl(bns_ctx *ctx, int layer, double p, const float *dZ, co
       BNS_TRY("spmm_bwd", spmm_bwd(ctx->ws.plan_b, n_in, B, ld, ctx->cur_t_row_ptr, ctx->cur_t_col_idx,
                                    ctx->cur_kept, ctx->cur_n_kept, ctx->ws.w_bwd, ctx->ws.w_halo, ctx->part.halo_ptr, ctx->ws.dis_in,
                                    ctx->ws.dis_halo,
-                                   halo_scale(p), dZ_g, nullptr, nullptr, false, ctx->ws.spmm_partials, G_in, G_halo,
+                                   halo_scale(p), dZ_g, nullptr, nullptr, false, transposed_len(ctx, p, G_halo), ctx->ws.spmm_partials, G_in, G_halo,
                                    s, d_out));
     }
     add_dw(n_in, H_in, nullptr, G_in, ctx->ws.tn[layer]);
@@ -568,7 +574,7 @@ bns_status layer_bwd_impl(bns_ctx *ctx, int layer, double p, const float *dZ, co
       BNS_TRY("spmm_bwd", spmm_bwd(ctx->ws.plan_b, n_in, B, d_in, ctx->cur_t_row_ptr, ctx->cur_t_col_idx,
                                    ctx->cur_kept, ctx->cur_n_kept, ctx->ws.w_bwd, ctx->ws.w_halo, ctx->part.halo_ptr, nullptr, nullptr,
                                    halo_scale(p) / ms, ctx->ws.G1, mask_src, ctx->ws.G2, true,
-                                   ctx->ws.spmm_partials, dH_in, dhalo, s));
+                                   transposed_len(ctx, p, dhalo), ctx->ws.spmm_partials, dH_in, dhalo, s));
     }
     return BNS_OK;
   }
@@ -586,7 +592,7 @@ bns_status layer_bwd_impl(bns_ctx *ctx, int layer, double p, const float *dZ, co
       BNS_TRY("spmm_bwd", spmm_bwd(ctx->ws.plan_b, n_in, B, ld, ctx->cur_t_row_ptr, ctx->cur_t_col_idx,
                                    ctx->cur_kept, ctx->cur_n_kept, ctx->ws.w_bwd, ctx->ws.w_halo, ctx->part.halo_ptr, ctx->ws.dis_in,
                                    ctx->ws.dis_halo, halo_scale(p), dZ_g, nullptr, nullptr, false,
-                                   ctx->ws.spmm_partials, G_in, G_halo, s, d_out));
+                                   transposed_len(ctx, p, G_halo), ctx->ws.spmm_partials, G_in, G_halo, s, d_out));
     }
     PhaseTimer t(ctx, BNS_PHASE_GEMM_DA, s);
     BNS_TRY("gemm_rows(dH)", gemm_wt(G_in, dH_in, nullptr, mask_src, ms, G_halo, dhalo));
@@ -599,7 +605,7 @@ bns_status layer_bwd_impl(bns_ctx *ctx, int layer, double p, const float *dZ, co
     BNS_TRY("spmm_bwd", spmm_bwd(ctx->ws.plan_b, n_in, B, d_in, ctx->cur_t_row_ptr, ctx->cur_t_col_idx,
                                  ctx->cur_kept, ctx->cur_n_kept, ctx->ws.w_bwd, ctx->ws.w_halo, ctx->part.halo_ptr, ctx->ws.dis_in,
                                  ctx->ws.dis_halo, halo_scale(p) / ms, ctx->ws.G1, mask_src, nullptr, false,
-                                 ctx->ws.spmm_partials, dH_in, dhalo, s));
+                                 transposed_len(ctx, p, dhalo), ctx->ws.spmm_partials, dH_in, dhalo, s));
   }
   return BNS_OK;
 }

@@ -180,7 +180,7 @@ __global__ void __launch_bounds__(256) spmm_combine_kernel(const SpmmArgs a) {
 constexpr int kBlockRowsMaxSeg = 65536;
 
 template <int VEC>
-static hipError_t launch_spmm_vec(const SpmmArgs &a_in, int64_t max_units, bool multi_only, bool backward, hipStream_t s) {
+static hipError_t launch_spmm_vec(const SpmmArgs &a_in, int64_t max_units, bool multi_only, int32_t avg_len, int32_t slice_from, hipStream_t s) {
   SpmmArgs a = a_in;
   // multi_only: the segments of the multi-segment rows, i.e. the partial-sum slots
   a.n_units = multi_only ? a.plan.n_part : a.plan.n_seg;
@@ -192,13 +192,14 @@ static hipError_t launch_spmm_vec(const SpmmArgs &a_in, int64_t max_units, bool 
   a.n_block_rows = block_rows ? a.plan.n_multi : 0;
   const int waves = block_rows ? kBlockWaves : 4;
   // Wide rows are cut into slices of 128 floats (64 where rows are long enough to keep a
-  // wavefront busy with a quarter of its lanes per neighbour); measured on the five workloads,
-  // narrower slices lose more to the repeated index walk than the L2 gains: transposed aggregates of 128-float rows
-  // with 45 entries 875 us whole, 811 in two slices, 927 in four; with 21 entries 836, 972 and 1695.
+  // wavefront busy with a quarter of its lanes per neighbour): narrower slices lose more to the repeated index walk than
+  // the L2 gains.  Where the line lies depends on the entries per row of the whole launch, the short rows of the boundary
+  // nodes among them (from 19 on): transposed aggregates of 128-float rows, 60000 rows with 17.6 entries 74 us whole, 77 in slices; 150000
+  // with 17.6 228, 212; 60000 with 21.3 87, 80; 300000 with 21.3 508, 474; 886000 with 14.5 853, 991; with 19.6 1108, 1132.
   // A forward row keeps the slices, and with them the order of its sum, that it has always had (from 64 entries on).
   int ls = 0;
   if (VEC == 4 && !multi_only) {
-    const int target = a.plan.avg_len >= (backward ? 32 : 64) ? 64 : 128;
+    const int target = avg_len >= slice_from ? 64 : 128;
     while (ls < 3 && (a.d >> (ls + 1)) >= target && a.d % (VEC << (ls + 1)) == 0) ++ls;
   }
   a.log2_slices = ls;
@@ -264,12 +265,12 @@ static hipError_t launch_spmm_vec(const SpmmArgs &a_in, int64_t max_units, bool 
   return hipGetLastError();
 }
 
-static hipError_t launch_spmm(const SpmmArgs &a, int64_t max_units, bool multi_only, bool backward, hipStream_t s) {
+static hipError_t launch_spmm(const SpmmArgs &a, int64_t max_units, bool multi_only, int32_t avg_len, int32_t slice_from, hipStream_t s) {
   if (a.d_store != a.d && (a.d_store < 1 || a.d_store > a.d || a.d >= 128 || a.d % 4 != 0 || a.mask_src || a.init))
     return hipErrorInvalidValue;  // padded sources: narrow rows without mask or initial value only
-  if (a.d % 4 == 0) return launch_spmm_vec<4>(a, max_units, multi_only, backward, s);
-  if (a.d % 2 == 0) return launch_spmm_vec<2>(a, max_units, multi_only, backward, s);
-  return launch_spmm_vec<1>(a, max_units, multi_only, backward, s);
+  if (a.d % 4 == 0) return launch_spmm_vec<4>(a, max_units, multi_only, avg_len, slice_from, s);
+  if (a.d % 2 == 0) return launch_spmm_vec<2>(a, max_units, multi_only, avg_len, slice_from, s);
+  return launch_spmm_vec<1>(a, max_units, multi_only, avg_len, slice_from, s);
 }
 
 hipError_t spmm_fwd(const SegPlan &plan, int32_t n_in, int32_t d, const int32_t *row_ptr,
@@ -279,14 +280,14 @@ hipError_t spmm_fwd(const SegPlan &plan, int32_t n_in, int32_t d, const int32_t 
   SpmmArgs a = spmm_fwd_args(plan, n_in, d, row_ptr, col_idx, w_in, w_ptr, row_scale, H_in, Hu, partials, A, part);
   a.relu = relu;
   if (d_store > 0) a.d_store = d_store;
-  return launch_spmm(a, plan.n_seg, long_rows_only, false, s);
+  return launch_spmm(a, plan.n_seg, long_rows_only, plan.avg_len, 64, s);
 }
 
 hipError_t spmm_bwd(const SegPlan &plan, int32_t n_in, int32_t n_halo, int32_t d,
                     const int32_t *t_row_ptr, const int32_t *t_col_idx, const int32_t *kept_ids,
                     const int32_t *n_kept, const float *w_in, const float *w_halo, const int32_t *halo_ptr, const float *row_scale,
                     const float *dis_halo, float s_halo, const float *dA, const float *mask_src,
-                    const float *init, bool skip_self, float *partials, float *dH_in, float *dhalo,
+                    const float *init, bool skip_self, int32_t avg_len, float *partials, float *dH_in, float *dhalo,
                     hipStream_t s, int32_t d_store) {
   SpmmArgs a{};
   const bool halo_rows = dhalo && n_halo > 0;
@@ -296,7 +297,7 @@ hipError_t spmm_bwd(const SegPlan &plan, int32_t n_in, int32_t n_halo, int32_t d
   a.out0 = dH_in; a.out1 = dhalo; a.out_scale0 = row_scale; a.mask_src = mask_src;
   a.kept_ids = kept_ids; a.dis_halo = dis_halo; a.s_halo = s_halo;
   a.init = init; a.skip_self = skip_self;
-  return launch_spmm(a, (int64_t)plan.n_seg + (halo_rows ? n_halo : 0), false, true, s);
+  return launch_spmm(a, (int64_t)plan.n_seg + (halo_rows ? n_halo : 0), false, avg_len, 19, s);
 }
 
 // ------------------------------------------------------------------------------------------
