@@ -177,7 +177,6 @@ __global__ void __launch_bounds__(256) spmm_combine_kernel(const SpmmArgs a) {
   finish_row<VEC, MAXCH, NARROW>(a, row, lane, nvec, 0, acc);
 }
 
-constexpr int kBlockRowsMaxSeg = 65536;
 
 template <int VEC>
 static hipError_t launch_spmm_vec(const SpmmArgs &a_in, int64_t max_units, bool multi_only, int32_t avg_len, int32_t slice_from, hipStream_t s) {
@@ -185,12 +184,6 @@ static hipError_t launch_spmm_vec(const SpmmArgs &a_in, int64_t max_units, bool 
   // multi_only: the segments of the multi-segment rows, i.e. the partial-sum slots
   a.n_units = multi_only ? a.plan.n_part : a.plan.n_seg;
   a.units = multi_only ? a.plan.part_unit : a.plan.seg_unit;
-  // The pass over the partial sums is a launch of about 5 us.  Where the longest row has few segments and the launch is
-  // short, a workgroup per such row saves it; on more rows than fill the chip a few times the launch is nothing, and
-  // workgroups of eight wavefronts that wait for their longest row cost more.
-  const bool block_rows = !multi_only && a.plan.n_multi > 0 && a.plan.max_seg <= kBlockWaves && a.plan.n_seg <= kBlockRowsMaxSeg;
-  a.n_block_rows = block_rows ? a.plan.n_multi : 0;
-  const int waves = block_rows ? kBlockWaves : 4;
   // Wide rows are cut into slices of 128 floats (64 where rows are long enough to keep a
   // wavefront busy with a quarter of its lanes per neighbour): narrower slices lose more to the repeated index walk than
   // the L2 gains.  Where the line lies depends on the entries per row of the whole launch, the short rows of the boundary
@@ -204,6 +197,16 @@ static hipError_t launch_spmm_vec(const SpmmArgs &a_in, int64_t max_units, bool 
   }
   a.log2_slices = ls;
   a.d_slice = a.d >> ls;
+  // The pass over the partial sums is a launch of 3 to 5 us.  Where the longest row has few segments, a workgroup per such
+  // row saves it; its workgroups of eight wavefronts wait for their longest row, which costs more where wavefronts are many and
+  // run at the rate of the LDS or vector pipes, i.e. in slices of 33 to 64 floats: those cross at about 20000 units (12000
+  // rows in 2 slices 29.2 us, in blocks 30.2; 20000 in 2 38, 43; in 4 67, 80; 30000 whole rows 26.4, 27.6), rows of 9 to 32
+  // floats at 50000 to 100000, wider ones not up to 100000 (128 floats: 12000 rows 36 and 33 us, 100000 155 and 149).
+  const bool narrow_slice = a.d_slice > 32 && a.d_slice <= 64;
+  const bool block_rows = !multi_only && a.plan.n_multi > 0 && a.plan.max_seg <= kBlockWaves &&
+                          ((int64_t)a.plan.n_seg << ls) <= (narrow_slice ? 20480 : 65536);
+  a.n_block_rows = block_rows ? a.plan.n_multi : 0;
+  const int waves = block_rows ? kBlockWaves : 4;
   const int nvec = a.d_slice / VEC;
   const int full_nvec = a.d / VEC;
   // one wavefront per static segment; the kept boundary rows, whose count lives on the device,
