@@ -212,7 +212,8 @@ bns_status bns_graph_replay(bns_ctx *ctx, int32_t n_epochs, void *stream);
  * timers attribute to BNS_PHASE_SPMM_FWD / BNS_PHASE_GEMM_FWD.
  *   BNS_LAYER_TWO_KERNELS  aggregate (Eq. 1), then update (Eq. 2); BNS_VIEW_A = the aggregate.
  *   BNS_LAYER_ONE_KERNEL   the same two steps in one kernel: input width a multiple of 4 between 68
- *                          and 128; the mean-aggregator layer, whose update is twice as deep, only
+ *                          and 128, at least 32768 inner nodes (98304 if a row of the local graph has
+ *                          more than 256 entries); the mean-aggregator layer, whose update is twice as deep, only
  *                          with an output width of at most 256 and at most 3.25 times the average
  *                          number of entries per row (a longer update is faster as a kernel of its
  *                          own); BNS_VIEW_A = the aggregate.

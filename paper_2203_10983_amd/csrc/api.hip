@@ -118,11 +118,15 @@ int gather_stride(int d_in, int d_out) {
 // workloads, up to about 6.5 multiply-adds of the update per gathered feature element (GCN layers of
 // workload 5: 4.4 and 6.0, faster in one kernel; mean-aggregator layers, whose update is twice as
 // deep: workload 3 at 5.1 faster, workload 5 at 8.9 and 11.9 slower).
-// Its workgroups own 64 rows: below kOneKernelMinRows they are too few for the chip (9 570 rows of 128 floats: 64 us with
-// the pass over the long rows, 37 in two kernels).
-constexpr int kOneKernelMinRows = 32768;
-bool one_kernel_layer(const bns_partition_desc &part, int layer_kind, int d_in, int d_out) {
-  if (part.n_in < kOneKernelMinRows) return false;
+// Its workgroups own 64 rows, so that few rows leave the chip short of them, and rows of several segments need a launch
+// before it.  Both sides timed, one kernel / two (us, 128 x 128): without such rows 20000 rows of 20 entries 50 / 42, 30000
+// 61 / 62, 45000 88 / 90, 100000 197 / 205; with them 45000 80 / 77, 65000 115 / 106, 100000 174 / 168, 200000 314 / 317 (steps
+// of 65000, 130000 and 300000 rows, hidden width 128: 385 / 372, 662 / 672, 1344 / 1391).
+constexpr int kOneKernelMinRows = 32768, kOneKernelMinRowsLong = 98304;
+bool one_kernel_layer(const bns_ctx *ctx, int d_in, int d_out) {
+  const bns_partition_desc &part = ctx->part;
+  const int layer_kind = ctx->layer_kind;
+  if (part.n_in < (ctx->ws.plan_f.n_multi > 0 ? kOneKernelMinRowsLong : kOneKernelMinRows)) return false;
   if (layer_kind == 0) return spmm_gemm_fwd_supported(d_in);  // every GCN shape measured so far gains
   if (!spmm_gemm_fwd_concat_supported(d_in, d_out)) return false;
   const double avg_len = (double)part.nnz0 / (double)part.n_in;
@@ -327,7 +331,7 @@ int layer_plan(const bns_ctx *ctx, int layer, const float *X) {
   // worth its extra launches only when the aggregate is big: at least 2^24 fewer floats gathered
   const bool big = (int64_t)ctx->part.nnz0 * (d_in - d_out) >= ((int64_t)1 << 24);
   if (!cached && big && update_first_shape(ctx->layer_kind, d_in, d_out)) return BNS_LAYER_UPDATE_FIRST;
-  if (one_kernel_layer(ctx->part, ctx->layer_kind, d_in, d_out)) return BNS_LAYER_ONE_KERNEL;
+  if (one_kernel_layer(ctx, d_in, d_out)) return BNS_LAYER_ONE_KERNEL;
   return BNS_LAYER_TWO_KERNELS;
 }
 
@@ -393,7 +397,7 @@ bns_status layer_fwd_impl(bns_ctx *ctx, int layer, double p, const float *H_in, 
   const float *w_in = ctx->ws.w_fwd;
   const int32_t *w_ptr = ctx->ws.split.inner_ptr;
   const float *row_scale = sage ? ctx->ws.inv_deg : ctx->ws.dis_in;
-  if (one_kernel_layer(ctx->part, ctx->layer_kind, d_in, d_out)) {
+  if (one_kernel_layer(ctx, d_in, d_out)) {
     // aggregate and update in one kernel; the rows cut into several segments are finished first
     {
       PhaseTimer t(ctx, BNS_PHASE_SPMM_LONG, s);
@@ -620,7 +624,7 @@ void add_pack_jobs(const bns_ctx *ctx, int l, const float *W, bool fwd, bool bwd
     jobs->units += pack_units(j);
   };
   // a layer in one kernel reads its weights as they are
-  if (fwd && (!one_kernel_layer(ctx->part, ctx->layer_kind, d_in, d_out) ||
+  if (fwd && (!one_kernel_layer(ctx, d_in, d_out) ||
               update_first_shape(ctx->layer_kind, d_in, d_out))) {
     if (kw == 2 && !concat_in_one(d_in)) {  // the two halves apart
       add(W, ctx->ws.Wf[l], d_in, d_out, false);

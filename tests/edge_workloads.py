@@ -58,11 +58,10 @@ def narrow_first():
     return _finish("edge-narrow-first", part, [512, 101, 7], 0, 19)
 
 
-def star():
+def star(n=3000):
     """One inner hub adjacent to every inner node (a row of 3000 entries: many segments) and one
     boundary hub adjacent to every inner node (a transposed row far longer than a segment), plus
     boundary leaves; odd feature widths (scalar-load path)."""
-    n = 3000
     others = np.arange(1, n)
     src_in = np.concatenate([np.zeros(n - 1, np.int64), others])
     dst_in = np.concatenate([others, np.zeros(n - 1, np.int64)])
@@ -73,13 +72,17 @@ def star():
     return _finish("edge-star", part, [7, 5, 3], 0, 12)
 
 
-def star_wide():
-    """The star graph again with widths between 65 and 128 that are multiples of 4: the layers that
-    aggregate and update in one kernel.  The hub row (3000 entries) is finished by the segmented
-    pass and read back; 3000 rows leave a ragged last tile of 56; 72 and 100 need depth padding."""
-    w = star()
+def star_wide(n=3000):
+    """The star graph again with widths between 65 and 128 that are multiples of 4; 72 and 100 need depth
+    padding.  At star_wide_large's size its layers aggregate and update in one kernel: the hub row is
+    finished by the segmented pass and read back, and the rows leave a ragged last tile of 56."""
+    w = star(n)
     dims = [72, 100, 128, 5]
     return _finish("edge-star-wide", w.part, dims, 0, 16)
+
+
+def star_wide_large():
+    return star_wide(98304 + 56)
 
 
 def single_node():
@@ -112,13 +115,13 @@ def widest():
     return _finish("edge-widest", w.part, [2048, 1022, 511, 3], 0, 18)
 
 
-def dense_rows():
+def dense_rows(n=1500):
     """Rows of about 65 entries (a circulant of 60 neighbours plus boundary nodes of 20 neighbours each)
-    and a 96 -> 172 first layer: long enough rows that the mean-aggregator layer aggregates and
-    updates in one kernel, an output of two column tiles (128 + 44), depth padding from 96 to 128,
-    and a 1500-row partition that leaves a ragged last tile of 28 rows."""
+    and a 96 -> 172 first layer, whose output takes two column tiles (128 + 44) and whose depth is padded
+    from 96 to 128.  At dense_rows_large's size the rows are many and long enough that the mean-aggregator
+    layer, too, aggregates and updates in one kernel; its partition leaves a ragged last tile of 28 rows."""
     rng = np.random.Generator(np.random.PCG64(19))
-    n, nb = 1500, 300
+    nb = n // 5
     offs = np.concatenate([np.arange(1, 31), -np.arange(1, 31)])
     src = np.repeat(np.arange(n), offs.size)
     dst = (src + np.tile(offs, n)) % n
@@ -128,6 +131,10 @@ def dense_rows():
     return _finish("edge-dense-rows", part, [96, 172, 128, 6], 0, 19)
 
 
+def dense_rows_large():
+    return dense_rows(32768 + 28)
+
+
 def degree_ordered():
     """Workload 3 at 1/32 of its size with the inner nodes numbered by descending degree (the hub rows
     first): local ids are the partitioner's choice, and every kernel must be indifferent to it."""
@@ -135,4 +142,4 @@ def degree_ordered():
     return make_workload(3, scale=32, local_order="degree")
 
 
-EDGE = {"e-degree": degree_ordered, "e-dense": dense_rows, "e-nobd": no_boundary, "e-max": widest, "e-nobdw": no_boundary_wide, "e-narrow": narrow_first, "e-star": star, "e-starw": star_wide, "e-single": single_node, "e-wide": wide_odd}
+EDGE = {"e-starw-large": star_wide_large, "e-dense-large": dense_rows_large, "e-degree": degree_ordered, "e-dense": dense_rows, "e-nobd": no_boundary, "e-max": widest, "e-nobdw": no_boundary_wide, "e-narrow": narrow_first, "e-star": star, "e-starw": star_wide, "e-single": single_node, "e-wide": wide_odd}
