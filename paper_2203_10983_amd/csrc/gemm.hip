@@ -107,6 +107,9 @@ __global__ void __launch_bounds__(256, R * NC > 8 || NC > 6 ? 3 : 4) gemm_rows_k
       if ((s + 1) * 32 <= p.K) {
 #pragma unroll
         for (int r = 0; r < R; ++r) ar[r][j] = *reinterpret_cast<const f32x4u *>(row_a[r] + k);
+      } else if ((p.K & 3) == 0) {  // pieces in or out as a whole
+#pragma unroll
+        for (int r = 0; r < R; ++r) ar[r][j] = k < p.K ? *reinterpret_cast<const f32x4u *>(row_a[r] + k) : f32x4{0.f, 0.f, 0.f, 0.f};
       } else if (k + 4 <= p.K) {
 #pragma unroll
         for (int r = 0; r < R; ++r) ar[r][j] = *reinterpret_cast<const f32x4u *>(row_a[r] + k);

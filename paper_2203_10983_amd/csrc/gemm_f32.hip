@@ -80,6 +80,10 @@ __global__ void __launch_bounds__(256, NC > 2 ? 3 : 4) gemm_rows_f32_kernel(cons
     if ((s + 1) * 32 <= p.K) {
 #pragma unroll
       for (int j = 0; j < 4; ++j) ar[j] = *reinterpret_cast<const f32x4u *>(src[j]);
+    } else if ((p.K & 3) == 0) {  // pieces in or out as a whole
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        ar[j] = s * 32 + j * 8 + hi * 4 < p.K ? *reinterpret_cast<const f32x4u *>(src[j]) : f32x4{0.f, 0.f, 0.f, 0.f};
     } else {
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
