@@ -27,6 +27,9 @@ if ROOT not in sys.path:
 
 HBM_PEAK_GBS = 8000.0          # MI355X HBM3E, published
 FP32_MFMA_PEAK_TFLOPS = 157.3  # MI355X dense fp32 matrix, published
+BF16_MFMA_PEAK_TFLOPS = 2500.0 # MI355X dense bf16 matrix, published
+# the forward products run on the fp32 instruction, the backward ones as six bf16 instructions per fp32 product
+GEMM_PEAK_TFLOPS = {"gemm_fwd": FP32_MFMA_PEAK_TFLOPS, "gemm_dw": BF16_MFMA_PEAK_TFLOPS / 6, "gemm_da": BF16_MFMA_PEAK_TFLOPS / 6}
 
 # (config, p) of the other workloads reported in `workloads`
 SWEEP = [(1, 0.1), (2, 1.0), (2, 0.1), (2, 0.01), (3, 0.1), (4, 0.1)]
@@ -204,8 +207,8 @@ def run_workload(cfg, p, kind, steps, warmup, dropout=0.0, extras=False, cpu_bas
     else:
         fl = gemm_flops[dom]
         achieved = fl / (per_step_ms[dom] * 1e-3) / 1e12
-        roof = {"kernel": dom, "bound": "mfma", "achieved": achieved, "peak": FP32_MFMA_PEAK_TFLOPS,
-                "unit": "TFLOP/s", "frac": achieved / FP32_MFMA_PEAK_TFLOPS, "traffic": None,
+        roof = {"kernel": dom, "bound": "mfma", "achieved": achieved, "peak": GEMM_PEAK_TFLOPS[dom],
+                "unit": "TFLOP/s", "frac": achieved / GEMM_PEAK_TFLOPS[dom], "traffic": None,
                 "launches_per_step": launches[dom], "avg_launch_ms": per_step_ms[dom] / max(launches[dom], 1),
                 "algorithmic_flops_per_step": fl}
     # HBM-side bytes per launch from the committed rocprofv3 PMC summary of this workload, if there is one
@@ -331,13 +334,14 @@ def run_workload(cfg, p, kind, steps, warmup, dropout=0.0, extras=False, cpu_bas
                       "gemm_dw": sum(4 * n_in * (kw * dims[l - 1] + dims[l]) for l in range(1, L + 1)),
                       "gemm_da": sum(4 * n_in * (kw * dims[l - 1] + dims[l]) for l in range(2, L + 1))}
         t_roof = (fwd_bytes + bwd_bytes) / (HBM_PEAK_GBS * 1e9)
-        t_roof += sum(max(gemm_flops[k] / (FP32_MFMA_PEAK_TFLOPS * 1e12), gemm_bytes[k] / (HBM_PEAK_GBS * 1e9))
+        t_roof += sum(max(gemm_flops[k] / (GEMM_PEAK_TFLOPS[k] * 1e12), gemm_bytes[k] / (HBM_PEAK_GBS * 1e9))
                       for k in gemm_flops)
         t_roof += sum(2 * n_in * dims[l - 1] * dims[l] for l in fused) / (FP32_MFMA_PEAK_TFLOPS * 1e12)  # fused updates
         t_roof += 8 * n_in * dims[L] / (HBM_PEAK_GBS * 1e9)                                          # loss
         t_roof += int_bytes / (HBM_PEAK_GBS * 1e9)                                                   # sample + CSRs
         out["step_roofline"] = {"t_roof_ms": t_roof * 1e3, "frac": t_roof * 1e3 / ms_median,
-                                "note": "sum over kernel classes of max(compulsory bytes / 8 TB/s, flops / 157.3 TFLOP/s) / ms_per_step"}
+                                "note": "sum over kernel classes of max(compulsory bytes / 8 TB/s, flops / peak) / ms_per_step; "
+                                        "peak 157.3 TFLOP/s forward (fp32 matrix), 416.7 backward (six bf16 products per fp32 one)"}
         # activations held for the backward pass per layer (floats), beside the memory model of Eq. 4
         held = [n_in * dims[l - 1] + n_in * dims[l] + n_kept * dims[l - 1] for l in range(1, L + 1)]
         eq4 = [(3 * n_in + n_kept) * dims[l] for l in range(1, L + 1)]

@@ -298,7 +298,7 @@ typedef enum {
   BNS_PHASE_SPMM_FWD = 3, /* aggregate                                     */
   BNS_PHASE_GEMM_FWD = 4, /* update  A W                                   */
   BNS_PHASE_LOSS = 5,
-  BNS_PHASE_GEMM_DW = 6,  /* A^T dZ (split-K + reduction)                  */
+  BNS_PHASE_GEMM_DW = 6,  /* A^T dZ of all layers (split depth + reduction) */
   BNS_PHASE_GEMM_DA = 7,  /* dZ W^T                                        */
   BNS_PHASE_SPMM_BWD = 8, /* transposed aggregate                          */
   BNS_PHASE_SGD = 9,      /* w <- w - lr * g, where lr > 0                 */

@@ -43,7 +43,8 @@ struct Layout {
   int32_t *kpos;
   uint64_t *bd_mask;   // keep flags of the boundary entries and their number per tile
   int32_t *bd_sums;
-  float *Hu, *Hu2, *G0, *G1, *G2, *loss_partials;  // Hu, Hu2: boundary rows at the output width
+  // boundary rows at the output width: Hu of GCN layers that shrink (their gradient), Hu2 of update-first layers
+  float *Hu, *Hu2, *G0, *G1, *G2, *loss_partials;
   int2 *halo_rec;  // per kept boundary node: (boundary index, weight) for the aggregates that read the rows in place
   // weight of every static entry with an inner column: forward (GCN only), transposed inner block, boundary nodes' lists
   float *w_fwd, *w_bwd, *w_halo;
@@ -161,10 +162,10 @@ bool fits_int32(const bns_partition_desc *p, const bns_model_desc *m) {
 
 size_t carve(Carver &c, const bns_partition_desc *p, const bns_model_desc *m, Layout *out) {
   const size_t n_in = p->n_in, B = p->n_halo, L = m->n_layers;
-  size_t d_max = 0, d_out_max = 0, d_first_max = 0;
+  size_t d_max = 0, d_out_max = 0, d_first_max = 0;  // d_out_max: of the GCN layers that shrink
   for (size_t l = 0; l <= L; ++l) d_max = std::max<size_t>(d_max, m->dims[l]);
   for (size_t l = 0; l < L; ++l) {
-    d_out_max = std::max<size_t>(d_out_max, m->dims[l + 1]);
+    if (m->layer_kind == 0 && m->dims[l + 1] < m->dims[l]) d_out_max = std::max<size_t>(d_out_max, m->dims[l + 1]);
     if (update_first_shape(m->layer_kind, m->dims[l], m->dims[l + 1]))
       d_first_max = std::max<size_t>(d_first_max, gather_stride(m->dims[l], m->dims[l + 1]));
   }
@@ -322,8 +323,6 @@ float mask_scale_of(const bns_ctx *ctx) {
   return ctx->drop_q > 0.0 ? (float)(1.0 / (1.0 - ctx->drop_q)) : 1.f;
 }
 
-// update_first: H_out = act(P [H_in W ; Hu W]) instead of act((P [H_in ; Hu]) W); A_saved then
-// receives H_in W (the aggregate of the inputs is never formed).
 // How bns_train_step runs the forward pass of `layer` when its first-layer input is X.
 int layer_plan(const bns_ctx *ctx, int layer, const float *X) {
   const int d_in = ctx->dims[layer - 1], d_out = ctx->dims[layer];

@@ -13,6 +13,8 @@
 // product of a single step once, to stay): one 16-byte LDS read feeds four instructions, and the matrix pipe is what is left
 // to wait for.  The weights are the second operand of the instruction: a lane ends up with a column, and a wavefront stores
 // 128 consecutive bytes of a row (with four columns per lane, 32-byte pieces of 32 rows: 32 -> 128 on 578125 rows 94 us, 79).
+// What bounds it: the matrix pipe where the depth is large (89625 x 512 x 512 369 us, 127 of 157 TFLOP/s), the stores where
+// it is a step or two.
 #include <algorithm>
 #include <type_traits>
 

@@ -195,7 +195,7 @@ hipError_t spmm_bwd(const SegPlan &plan, int32_t n_in, int32_t n_halo, int32_t d
                     const float *init, bool skip_self, int32_t avg_len, float *partials, float *dH_in, float *dhalo,
                     hipStream_t s, int32_t d_store = 0);
 
-// ---- gemm.hip (Eq. 2 and its backward; fp32 MFMA) ----------------------------------------------
+// ---- gemm_f32.hip (Eq. 2; fp32 MFMA), gemm.hip (its backward; fp32 on the bf16 MFMA) -------------
 // Dropout on a hidden layer's output (training set-up of Section 4): element (row, col) is kept iff
 // the first word of Philox-4x32-10 on the counter (row, col, c2, epoch) under key (k0, k1) is below
 // `threshold`; kept elements are multiplied by `scale` = 1/(1-q).  scale == 0: no dropout.

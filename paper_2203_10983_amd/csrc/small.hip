@@ -1,6 +1,6 @@
 // Selection step and subgraph step of Algorithm 1 for a small partition, in one launch.
 //
-// The general path spends six launches per epoch on these two steps, each a few microseconds long
+// The general path spends four launches per epoch on these two steps, each a few microseconds long
 // whatever the size; for a partition of a few thousand entries that is a third of the whole
 // training step.  Here one workgroup of 1024 threads runs the same stages back to back, with a
 // barrier where the general path has a kernel boundary (a barrier also publishes the workgroup's

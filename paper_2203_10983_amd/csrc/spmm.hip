@@ -4,7 +4,7 @@
 // neighbours.  Power-law graphs put a large share of all edges into a few very long rows; cutting
 // every row into bounded segments keeps the wavefronts balanced.  A row with one segment is
 // finished by its wavefront; a row with several gets one partial sum per segment, and a second
-// small kernel adds them in ascending order.  No atomics anywhere: the backward pass walks the
+// small kernel adds them in ascending order (or, in short launches, the workgroup that owns the row).  No atomics anywhere: the backward pass walks the
 // transposed pattern, and every output element is produced in a fixed order.
 //
 // Inside a segment the lanes span the feature dimension with VEC-wide loads, so every neighbour

@@ -60,6 +60,24 @@ def test_workspace_bytes_is_host_arithmetic(pkg):
         assert lib.bns_workspace_bytes(C.byref(pdo), C.byref(mdo)) > 0
 
 
+def test_boundary_rows_take_workspace_only_where_a_layer_shrinks(pkg):
+    """The gradient of a GCN layer that shrinks passes through rows of its output width, one per boundary node; other
+    layers need only the integers and records of the boundary nodes (about 30 bytes each)."""
+    lib = pkg.load_library()
+
+    def per_node(dims, kind):
+        size = []
+        for n_halo in (1_000_000, 2_000_000):
+            pd, md, keep = _descs(pkg, n_halo=n_halo, dims=dims)
+            md.layer_kind = kind
+            size.append(lib.bns_workspace_bytes(C.byref(pd), C.byref(md)))
+        return (size[1] - size[0]) / 1_000_000
+
+    assert 20 < per_node((128, 128, 172), 0) < 64
+    assert 20 < per_node((172, 128, 128), 1) < 64
+    assert per_node((172, 160, 160), 0) == pytest.approx(per_node((128, 128, 172), 0) + 4 * 160, abs=1)
+
+
 def test_int32_overflow_is_reported(pkg):
     lib = pkg.load_library()
     pd, md, _ = _descs(pkg, n_in=10, nnz0=2**31 + 10, e_in=2**31 + 10)

@@ -414,7 +414,7 @@ def test_train_step_with_cached_input_aggregate(case):
                          ids=["tiny", "e-star", "cfg3-s32"])
 def test_which_path_builds_the_subgraph(cfg, scale, one_launch):
     """A training step of a small partition runs the selection and subgraph steps as one launch (timed
-    as the sample phase: no record in the build phase), a larger one as the six launches of the
+    as the sample phase: no record in the build phase), a larger one as the launches of the
     general path; the integer results of both are compared with the oracle by the end-to-end test,
     and here against the stand-alone calls, which always take the general path."""
     c = _Case.get(cfg, scale, 0)
