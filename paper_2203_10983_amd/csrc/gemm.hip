@@ -58,7 +58,8 @@ enum RowsEpilogue { kPlain = 0, kMask = 1, kPair = 2 };
 // An infinite operand has no split (its other pieces are NaN), nor has one beyond 3.389e38, which rounds to an infinite
 // piece, and a product near the top of the range can overflow in its first piece alone.  All of these end in a result that
 // is not finite, and such a result is formed once more as the plain fp32 sum, so that infinities and NaN come out as from the operands
-// themselves.  Looking costs an instruction per result and tile.
+// themselves.  Looking costs an instruction per result and tile; a product all of whose results are NaN takes some 50 to 80
+// times as long (89625 x 512 x 512: 11 and 20 ms), one infinite element a few times.
 __device__ __forceinline__ float nonfinite_seed(float z, const f32x4 &v) {  // z stays 0 while all values are finite
 #pragma unroll
   for (int e = 0; e < 4; ++e) z = fmaf(v[e], 0.f, z);
@@ -238,15 +239,26 @@ __global__ void __launch_bounds__(256, R * NC > 8 || NC > 6 ? 3 : 4) gemm_rows_k
       if (nonfinite != 0.f) {  // (NaN)
         const float *A = more ? p.A_more : p.A;
 #pragma unroll 1
-        for (int q = 0; q < R * NP * W * 4; ++q) {
-          const int c = q / (4 * W) % NP, row = row0 + q / (NP * W * 4) * 16 + q / 4 % W, col = col0 + c * 16 * W + q % 4;
-          if (row >= end || col >= n_end || c * W + odd >= nt) continue;
+        for (int q = 0; q < R * NP * W; ++q) {
+          const int c = q / W % NP, row = row0 + q / (NP * W) * 16 + q % W, col = col0 + c * 16 * W;
+          const int left = c * W + odd < nt ? n_end - col : 0;
+          if (row >= end || left <= 0) continue;
           float *const d = (EPI == kPair && col >= p.c_split ? p.C2 - p.c_split : more ? p.C_more : p.C) + (size_t)row * p.ldc + col;
-          if (is_finite(*d)) continue;
-          float x = 0.f;
+          bool fine = true;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) fine &= e >= left || is_finite(d[e]);
+          if (fine) continue;
+          const float *const w = p.W + (size_t)col * p.K;
+          float x[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll 1
-          for (int k = 0; k < p.K; ++k) x = fmaf(A[(size_t)row * p.K + k], p.W[(size_t)col * p.K + k], x);
-          *d = x * scale;
+          for (int k = 0; k < p.K; ++k) {
+            const float y = A[(size_t)row * p.K + k];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) x[e] = fmaf(y, w[(e < left ? (size_t)e * p.K : 0) + k], x[e]);
+          }
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (e < left && !is_finite(d[e])) d[e] = x[e] * scale;
         }
       }
       if (ntile >= n_tiles) break;
@@ -475,16 +487,24 @@ __global__ void __launch_bounds__(256, 3) gemm_tn_kernel(const TnJobs jobs) {
     }
   if (nonfinite != 0.f) {  // (NaN)
 #pragma unroll 1
-    for (int q = 0; q < NT * MT * 4; ++q) {  // element q % 4 of tile (j, i) as gemm_tn_reduce_kernel places it
-      const int j = q / 4 / MT, i = q / 4 % MT, sa = lane & 15;
-      const int m = m0 + (wm * MT + i) * 16 + 4 * (sa & 3) + (sa >> 2), n = n0 + (wn * NT + j) * 16 + 4 * (q % 4) + (lane >> 4);
-      float *const d = out + (j * MT + i) * 256 + q % 4;
-      if (m >= a.M || n >= a.N || is_finite(*d)) continue;
+    for (int q = 0; q < NT * MT; ++q) {  // the elements of tile (j, i) as gemm_tn_reduce_kernel places them
+      const int j = q / MT, i = q % MT, sa = lane & 15;
+      const int m = m0 + (wm * MT + i) * 16 + 4 * (sa & 3) + (sa >> 2), n = n0 + (wn * NT + j) * 16 + (lane >> 4);  // n + 4 e
+      if (m >= a.M || n >= a.N) continue;
+      float *const d = out + q * 256;
+      if (is_finite(d[0]) && is_finite(d[1]) && is_finite(d[2]) && is_finite(d[3])) continue;
       const float *A = a.A2 && m >= a.a_split ? a.A2 + (m - a.a_split) : a.A + m;
-      float x = 0.f;
-#pragma unroll 1
-      for (int k = k_begin; k < k_end; ++k) x = fmaf(A[(size_t)(a.rows ? a.rows[k] : k) * a.lda], a.B[(size_t)k * a.N + n], x);
-      *d = x;
+      float x[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 2
+      for (int k = k_begin; k < k_end; ++k) {
+        const float y = A[(size_t)(a.rows ? a.rows[k] : k) * a.lda];
+        const float *const b = a.B + (size_t)k * a.N + n;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[e] = fmaf(y, b[n + 4 * e < a.N ? 4 * e : 0], x[e]);
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (!is_finite(d[e])) d[e] = x[e];
     }
   }
 }
