@@ -172,17 +172,28 @@ __global__ void __launch_bounds__(256, NC > 2 ? 3 : 4) gemm_rows_f32_kernel(cons
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
           const int col = (t0 + c) * 32 + l32;
-          if (col >= n_end) continue;
+          if (NC > 1 && col >= n_end) continue;
+          const bool in = NC > 1 || col < n_end;
           const unsigned at = (unsigned)(hi * 4 * p.ldc + col) * 4u;  // bytes
+          auto each = [&](int q, f32x4 &v, auto f) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              if (in && (decltype(full)::value || q * 8 + hi * 4 + e < rows)) v[e] = f(reinterpret_cast<float *>(reinterpret_cast<char *>(dst + (size_t)(q * 8 + e) * p.ldc) + at), v[e]);
+          };
+          // Where the tiles are few and small, latency counts: all lanes draw for the dropout, those past the last column too (a
+          // wavefront with two of its columns active took three times as long over it: 512 rows, 64 -> 66 15.2 us, 10.0), and what
+          // is added to is read before the first store, which a later load would wait for (1211 rows, 300 -> 300 29.6 us, 27.4).
+          // With more tiles per wavefront neither pays (60000 rows, 130 -> 130 95 us, 104).
+          constexpr bool kOldFirst = ACC && NC == 1;
+          f32x4 old[4];
+          if constexpr (kOldFirst)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) each(q, old[q], [](const float *d, float) { return *d; });
 #pragma unroll
           for (int q = 0; q < 4; ++q) {
             f32x4 v = {acc[c][4 * q], acc[c][4 * q + 1], acc[c][4 * q + 2], acc[c][4 * q + 3]};
-            auto each = [&](auto f) {
-#pragma unroll
-              for (int e = 0; e < 4; ++e)
-                if (decltype(full)::value || q * 8 + hi * 4 + e < rows) v[e] = f(reinterpret_cast<float *>(reinterpret_cast<char *>(dst + (size_t)(q * 8 + e) * p.ldc) + at), v[e]);
-            };
-            if constexpr (ACC) each([](const float *d, float x) { return x + *d; });
+            if constexpr (kOldFirst) v += old[q];
+            else if constexpr (ACC) each(q, v, [](const float *d, float x) { return x + *d; });
             if (p.relu) {
 #pragma unroll
               for (int e = 0; e < 4; ++e) v[e] = fmaxf(v[e], 0.f);
@@ -194,7 +205,7 @@ __global__ void __launch_bounds__(256, NC > 2 ? 3 : 4) gemm_rows_f32_kernel(cons
                 }
               }
             }
-            each([](float *d, float x) { return *d = x; });
+            each(q, v, [](float *d, float x) { return *d = x; });
           }
         }
       };

@@ -167,3 +167,39 @@ def test_input_gradient_may_overwrite_what_it_came_from(kind, shared, d_out):
     dW2, dX2 = bwd(copies, copies[shared])
     assert torch.equal(dX, dX2) and torch.equal(dW, dW2)
     ctx.close()
+
+
+@pytest.mark.parametrize("kind", [0, 1], ids=["gcn", "sage"])
+@pytest.mark.parametrize("d_in,d_out", [(64, 33), (64, 66), (36, 98), (64, 129), (16, 1)])
+def test_dropout_of_few_rows_is_that_of_many(d_in, d_out, kind):
+    """An element's draw depends on its row, column, layer and epoch alone, and its sum on nothing but its terms: the same
+    rows give the same bits whatever tiles the number of rows leads to."""
+    import torch
+    import paper_2203_10983_amd as pkg
+    dev = torch.device("cuda:0")
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(d_in + 13 * d_out)
+    X = torch.randn(70001, d_in, device=dev, generator=gen)
+    W = torch.randn((1 + kind) * d_in, d_out, device=dev, generator=gen)
+    i32 = lambda k: torch.zeros(k, dtype=torch.int32, device=dev)  # noqa: E731
+    got = {}
+    for n in (1, 500, 70001):
+        for q in (0.0, 0.5):
+            ctx = pkg.Context(_loops(n), [d_in, d_out], 0, device=dev, layer_kind=kind)
+            ctx.set_dropout(q)
+            kept, remap, n_kept, nnz = i32(1), i32(1), i32(1), i32(1)
+            ctx.sample_boundary(1, 3, 0.5, kept, remap, n_kept)
+            csr = i32(n + 1), i32(n), i32(n + 1), i32(n)
+            ctx.build_sampled_csr(remap, kept, n_kept, *csr, nnz)
+            H = torch.full((n, d_out), 7.0, device=dev)
+            ctx.gcn_layer_fwd(1, 0.5, X[:n], None, W, torch.empty(n, d_in, device=dev), H, True)
+            torch.cuda.synchronize()
+            got[n, q] = H
+            ctx.close()
+    for q in (0.0, 0.5):
+        assert torch.equal(got[1, q], got[70001, q][:1]) and torch.equal(got[500, q], got[70001, q][:500])
+    dropped = got[70001, 0.5] == 0
+    assert torch.equal(got[70001, 0.5], torch.where(dropped, 0.0, 2.0 * got[70001, 0.0]))
+    on = got[70001, 0.0] > 0
+    k, m = int((on & dropped).sum()), int(on.sum())
+    assert abs(k - m / 2) <= 5 * (m / 4) ** 0.5
