@@ -179,21 +179,34 @@ __global__ void __launch_bounds__(256) spmm_combine_kernel(const SpmmArgs a) {
 
 
 template <int VEC>
-static hipError_t launch_spmm_vec(const SpmmArgs &a_in, int64_t max_units, bool multi_only, int32_t avg_len, int32_t slice_from, hipStream_t s) {
+static hipError_t launch_spmm_vec(const SpmmArgs &a_in, int64_t max_units, bool multi_only, int32_t avg_len, bool transposed, hipStream_t s) {
   SpmmArgs a = a_in;
   // multi_only: the segments of the multi-segment rows, i.e. the partial-sum slots
   a.n_units = multi_only ? a.plan.n_part : a.plan.n_seg;
   a.units = multi_only ? a.plan.part_unit : a.plan.seg_unit;
   // Wide rows are cut into slices of 128 floats (64 where rows are long enough to keep a
   // wavefront busy with a quarter of its lanes per neighbour): narrower slices lose more to the repeated index walk than
-  // the L2 gains.  Where the line lies depends on the entries per row of the whole launch, the short rows of the boundary
-  // nodes among them (from 19 on): transposed aggregates of 128-float rows, 60000 rows with 17.6 entries 74 us whole, 77 in slices; 150000
-  // with 17.6 228, 212; 60000 with 21.3 87, 80; 300000 with 21.3 508, 474; 886000 with 14.5 853, 991; with 19.6 1108, 1132.
+  // the L2 gains.  In the transposed pass that line is counted in entries per row of the whole launch, the short rows of the
+  // boundary nodes among them, and depends on what the narrower slices bring (slices of 128 -> of 64, us):
+  //   more wavefronts, where those of 128 do not fill the chip: 4600 rows of 128 floats with 20.4 entries 19 -> 17, 2500 of
+  //     256 with 26.9 14 -> 13;
+  //   room in the L2 for rows that do not fit it: 2 slices instead of 1 from 19 entries on (60000 rows with 17.6 74 -> 77,
+  //     with 21.3 87 -> 80; 300000 with 21.3 508 -> 474; 886000 with 14.5 853 -> 991, with 19.6 1108 -> 1132), more slices from
+  //     24 on (60000 rows of 256 with 21.3 150 -> 153, with 26 182 -> 165; of 512 277 -> 289, 332 -> 307);
+  //   neither, in between: from 32 on (9000 rows of 512 with 26.9 entries 41 -> 48, 16000 70 -> 81; 16000 of 256 with 56.6 70 -> 68).
   // A forward row keeps the slices, and with them the order of its sum, that it has always had (from 64 entries on).
   int ls = 0;
   if (VEC == 4 && !multi_only) {
-    const int target = avg_len >= slice_from ? 64 : 128;
-    while (ls < 3 && (a.d >> (ls + 1)) >= target && a.d % (VEC << (ls + 1)) == 0) ++ls;
+    auto slices = [&](int target) {
+      int l = 0;
+      while (l < 3 && (a.d >> (l + 1)) >= target && a.d % (VEC << (l + 1)) == 0) ++l;
+      return l;
+    };
+    ls = slices(128);
+    int from = 64;
+    if (transposed)
+      from = ((int64_t)a.n_units << ls) <= 8192 ? 19 : a.n_units < 24576 ? 32 : ls == 0 ? 19 : 24;
+    if (avg_len >= from) ls = slices(64);
   }
   a.log2_slices = ls;
   a.d_slice = a.d >> ls;
@@ -268,12 +281,12 @@ static hipError_t launch_spmm_vec(const SpmmArgs &a_in, int64_t max_units, bool 
   return hipGetLastError();
 }
 
-static hipError_t launch_spmm(const SpmmArgs &a, int64_t max_units, bool multi_only, int32_t avg_len, int32_t slice_from, hipStream_t s) {
+static hipError_t launch_spmm(const SpmmArgs &a, int64_t max_units, bool multi_only, int32_t avg_len, bool transposed, hipStream_t s) {
   if (a.d_store != a.d && (a.d_store < 1 || a.d_store > a.d || a.d >= 128 || a.d % 4 != 0 || a.mask_src || a.init))
     return hipErrorInvalidValue;  // padded sources: narrow rows without mask or initial value only
-  if (a.d % 4 == 0) return launch_spmm_vec<4>(a, max_units, multi_only, avg_len, slice_from, s);
-  if (a.d % 2 == 0) return launch_spmm_vec<2>(a, max_units, multi_only, avg_len, slice_from, s);
-  return launch_spmm_vec<1>(a, max_units, multi_only, avg_len, slice_from, s);
+  if (a.d % 4 == 0) return launch_spmm_vec<4>(a, max_units, multi_only, avg_len, transposed, s);
+  if (a.d % 2 == 0) return launch_spmm_vec<2>(a, max_units, multi_only, avg_len, transposed, s);
+  return launch_spmm_vec<1>(a, max_units, multi_only, avg_len, transposed, s);
 }
 
 hipError_t spmm_fwd(const SegPlan &plan, int32_t n_in, int32_t d, const int32_t *row_ptr,
@@ -283,7 +296,7 @@ hipError_t spmm_fwd(const SegPlan &plan, int32_t n_in, int32_t d, const int32_t 
   SpmmArgs a = spmm_fwd_args(plan, n_in, d, row_ptr, col_idx, w_in, w_ptr, row_scale, H_in, Hu, partials, A, part);
   a.relu = relu;
   if (d_store > 0) a.d_store = d_store;
-  return launch_spmm(a, plan.n_seg, long_rows_only, plan.avg_len, 64, s);
+  return launch_spmm(a, plan.n_seg, long_rows_only, plan.avg_len, false, s);
 }
 
 hipError_t spmm_bwd(const SegPlan &plan, int32_t n_in, int32_t n_halo, int32_t d,
@@ -300,7 +313,7 @@ hipError_t spmm_bwd(const SegPlan &plan, int32_t n_in, int32_t n_halo, int32_t d
   a.out0 = dH_in; a.out1 = dhalo; a.out_scale0 = row_scale; a.mask_src = mask_src;
   a.kept_ids = kept_ids; a.dis_halo = dis_halo; a.s_halo = s_halo;
   a.init = init; a.skip_self = skip_self;
-  return launch_spmm(a, (int64_t)plan.n_seg + (halo_rows ? n_halo : 0), false, avg_len, 19, s);
+  return launch_spmm(a, (int64_t)plan.n_seg + (halo_rows ? n_halo : 0), false, avg_len, true, s);
 }
 
 // ------------------------------------------------------------------------------------------
