@@ -60,9 +60,14 @@ struct SpmmArgs {
   bool skip_self;              // entries with column == row contribute nothing (mean aggregator)
   // feature slicing over the XCDs (log2_slices = 0: off).  Workgroups are handed to the 8 XCDs in
   // turn, so workgroup b runs on XCD b % 8; with S = 2^log2_slices that XCD only ever touches the
-  // d_slice = d / S floats of slice (b % 8) % S of every feature row, and its private L2 holds S
-  // times as many distinct rows.
+  // d_slice = d / S floats of one slice of every feature row at a time, and its private L2 holds S
+  // times as many distinct rows.  The slices are not equally fast:
+  // where rows are a multiple of 1 KB apart, one 128-byte line in eight is gathered as if half of the L2's channels held it
+  // (5.1 M random pieces of 128 bytes out of rows of 1 KB: 8000 rows 30 us, that line 37; 29125 rows 32 us, 46), and with one
+  // slice for the whole launch the XCDs of that slice end last (10 M entries of 256 floats: 628 us, the others 490 to 517).
+  // So an XCD takes the slices in turn.
   int32_t log2_slices, d_slice;
+  int32_t turn_blocks;  // workgroups of a slice after which its XCDs go on to the next slice (0: they stay)
   bool relu;                   // rows < n_split: max(., 0) after the scale (update-first layers)
   // columns stored per output row = row stride of out0 / out1; less than d when the sources are
   // padded to a multiple of 4 floats (then no mask, no init, no slices; read by the NARROW kernels only)

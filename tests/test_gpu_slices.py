@@ -1,0 +1,75 @@
+"""Aggregates whose XCDs take the feature slices in turn, and their rows of boundary nodes, against fp64.
+
+Cliques with self-loops, large and many enough for the launch to take turns (1 250 000 entries), each boundary node next to a
+few inner ones; degrees count the entries, so that the inner part of A H0 is a clique sum."""
+import types
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def _partition(cliques, size, n_halo, rng):
+    n = cliques * size
+    first = np.repeat(np.arange(cliques) * size, size)
+    lists = [np.sort(rng.choice(n, size=1 + b % 5, replace=False)) for b in range(n_halo)]  # inner neighbours per boundary node
+    halo_ptr = np.concatenate([[0], np.cumsum([len(x) for x in lists])])
+    halo_col = np.concatenate(lists)
+    row, col = np.repeat(np.arange(n), size), (first[:, None] + np.arange(size)).reshape(-1)
+    row = np.concatenate([row, halo_col])
+    col = np.concatenate([col, n + np.repeat(np.arange(n_halo), np.diff(halo_ptr))])
+    order = np.lexsort((col, row))
+    ptr = np.concatenate([[0], np.cumsum(np.bincount(row, minlength=n))])
+    i32 = lambda x: np.ascontiguousarray(x, dtype=np.int32)  # noqa: E731
+    return types.SimpleNamespace(
+        part_id=0, n_in=n, n_halo=n_halo, nnz0=len(col), e_in=n * size, e_bd=len(halo_col), row_ptr0=i32(ptr), col0=i32(col[order]),
+        t_in_ptr=i32(np.arange(n + 1) * size), t_in_col=i32((first[:, None] + np.arange(size)).reshape(-1)), halo_ptr=i32(halo_ptr),
+        halo_col=i32(halo_col), halo_gid=np.arange(n, n + n_halo, dtype=np.int64), deg_in=i32(np.diff(ptr)), deg_halo=i32(np.diff(halo_ptr) + 1))
+
+
+@pytest.mark.parametrize("cliques,size,d,n_halo,p", [(20, 257, 256, 1, 1.0), (20, 257, 512, 3001, 0.5), (79, 128, 128, 5000, 0.3),
+                                                     (79, 128, 200, 700, 1.0), (5, 515, 256, 9000, 1.0)])
+def test_aggregate_in_turns(cliques, size, d, n_halo, p):
+    import torch
+    import paper_2203_10983_amd as pkg
+    dev = torch.device("cuda:0")
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(d + n_halo)
+    P = _partition(cliques, size, n_halo, np.random.default_rng(size))
+    assert P.e_in >= 1250000
+    n = P.n_in
+    i32 = lambda k: torch.zeros(k, dtype=torch.int32, device=dev)  # noqa: E731
+    ctx = pkg.Context(P, [d, d], 0, device=dev)
+    kept, remap, n_kept, nnz = i32(n_halo), i32(n_halo), i32(1), i32(1)
+    ctx.sample_boundary(1, 0, p, kept, remap, n_kept)
+    csr = i32(n + 1), i32(P.nnz0), i32(n + n_halo + 1), i32(P.nnz0)  # must outlive the layer calls
+    ctx.build_sampled_csr(remap, kept, n_kept, *csr, nnz)
+    X, Xb, dH = (torch.randn(k, d, device=dev, generator=gen) for k in (n, n_halo, n))
+    A, H, dX = (torch.full((n, d), 7.0, device=dev) for _ in range(3))
+    dW, dhalo = torch.zeros(d, d, device=dev), torch.full((n_halo, d), 7.0, device=dev)
+    ctx.gcn_layer_fwd(1, p, X, Xb, torch.eye(d, device=dev), A, H, False)
+    ctx.gcn_layer_bwd(1, p, dH, None, A, X, torch.eye(d, device=dev), dW, dX, dhalo)
+    torch.cuda.synchronize()
+    K = int(n_kept)
+    kept = kept[:K].long()
+    s_in = torch.from_numpy(P.deg_in).to(dev).double().rsqrt()[:, None]
+    s_bd = torch.from_numpy(P.deg_halo).to(dev).double().rsqrt()[:, None] / p
+    clique = torch.arange(n, device=dev) // size
+
+    def inner(x):
+        return torch.zeros(cliques, d, device=dev, dtype=torch.float64).index_add_(0, clique, x)[clique]
+
+    node = torch.repeat_interleave(torch.arange(n_halo, device=dev), torch.from_numpy(np.diff(P.halo_ptr)).to(dev))
+    of = torch.from_numpy(P.halo_col).long().to(dev)
+    is_kept = (remap >= 0)[node]
+    node, of = node[is_kept], of[is_kept]
+    ref_A = s_in * inner(s_in * X).index_add_(0, of, (s_bd * Xb)[node])
+    ref_dhalo = torch.zeros(n_halo, d, device=dev, dtype=torch.float64).index_add_(0, node, (s_in * dH)[of]) * s_bd
+    # sums of up to 600 terms of size 1 with weights of about 1 / 300: a rounding is 2^-24 of a running sum below 1
+    tol = dict(rtol=1e-5, atol=1e-5)
+    torch.testing.assert_close(A.double(), ref_A, **tol)
+    torch.testing.assert_close(dX.double(), s_in * inner(s_in * dH), **tol)
+    torch.testing.assert_close(dhalo[:K].double(), ref_dhalo[kept], **tol)
+    assert bool((dhalo[K:] == 7.0).all())
+    ctx.close()
