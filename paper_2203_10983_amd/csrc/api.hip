@@ -539,7 +539,7 @@ bns_status layer_bwd_impl(bns_ctx *ctx, int layer, double p, const float *dZ, co
                                    ctx->cur_kept, ctx->cur_n_kept, ctx->ws.w_bwd, ctx->ws.w_halo, ctx->part.halo_ptr, ctx->ws.dis_in,
                                    ctx->ws.dis_halo,
                                    halo_scale(p), dZ_g, nullptr, nullptr, false, transposed_len(ctx, p, G_halo), ctx->ws.spmm_partials, G_in, G_halo,
-                                   s, d_out));
+                                   expected_kept(ctx, p), s, d_out));
     }
     add_dw(n_in, H_in, nullptr, G_in, ctx->ws.tn[layer]);
     if (B > 0) {  // the kept boundary features where the caller holds them: G_halo carries the 1/p and degree factors
@@ -577,7 +577,7 @@ bns_status layer_bwd_impl(bns_ctx *ctx, int layer, double p, const float *dZ, co
       BNS_TRY("spmm_bwd", spmm_bwd(ctx->ws.plan_b, n_in, B, d_in, ctx->cur_t_row_ptr, ctx->cur_t_col_idx,
                                    ctx->cur_kept, ctx->cur_n_kept, ctx->ws.w_bwd, ctx->ws.w_halo, ctx->part.halo_ptr, nullptr, nullptr,
                                    halo_scale(p) / ms, ctx->ws.G1, mask_src, ctx->ws.G2, true,
-                                   transposed_len(ctx, p, dhalo), ctx->ws.spmm_partials, dH_in, dhalo, s));
+                                   transposed_len(ctx, p, dhalo), ctx->ws.spmm_partials, dH_in, dhalo, expected_kept(ctx, p), s));
     }
     return BNS_OK;
   }
@@ -595,7 +595,7 @@ bns_status layer_bwd_impl(bns_ctx *ctx, int layer, double p, const float *dZ, co
       BNS_TRY("spmm_bwd", spmm_bwd(ctx->ws.plan_b, n_in, B, ld, ctx->cur_t_row_ptr, ctx->cur_t_col_idx,
                                    ctx->cur_kept, ctx->cur_n_kept, ctx->ws.w_bwd, ctx->ws.w_halo, ctx->part.halo_ptr, ctx->ws.dis_in,
                                    ctx->ws.dis_halo, halo_scale(p), dZ_g, nullptr, nullptr, false,
-                                   transposed_len(ctx, p, G_halo), ctx->ws.spmm_partials, G_in, G_halo, s, d_out));
+                                   transposed_len(ctx, p, G_halo), ctx->ws.spmm_partials, G_in, G_halo, expected_kept(ctx, p), s, d_out));
     }
     PhaseTimer t(ctx, BNS_PHASE_GEMM_DA, s);
     BNS_TRY("gemm_rows(dH)", gemm_wt(G_in, dH_in, nullptr, mask_src, ms, G_halo, dhalo));
@@ -608,7 +608,7 @@ bns_status layer_bwd_impl(bns_ctx *ctx, int layer, double p, const float *dZ, co
     BNS_TRY("spmm_bwd", spmm_bwd(ctx->ws.plan_b, n_in, B, d_in, ctx->cur_t_row_ptr, ctx->cur_t_col_idx,
                                  ctx->cur_kept, ctx->cur_n_kept, ctx->ws.w_bwd, ctx->ws.w_halo, ctx->part.halo_ptr, ctx->ws.dis_in,
                                  ctx->ws.dis_halo, halo_scale(p) / ms, ctx->ws.G1, mask_src, nullptr, false,
-                                 transposed_len(ctx, p, dhalo), ctx->ws.spmm_partials, dH_in, dhalo, s));
+                                 transposed_len(ctx, p, dhalo), ctx->ws.spmm_partials, dH_in, dhalo, expected_kept(ctx, p), s));
   }
   return BNS_OK;
 }

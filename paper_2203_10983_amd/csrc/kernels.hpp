@@ -187,13 +187,13 @@ hipError_t spmm_gemm_fwd(const SegPlan &plan, int32_t n_in, int32_t d_in, int32_
 //   u <  n_in: dH_in[u,:] = row_scale[u] * (init[u,:] + g)  (zeroed where mask_src[u,:] <= 0 if given)
 //   u >= n_in: dhalo[u-n_in,:] = s_halo * dis_halo[kept_ids[u-n_in]] * g   (skipped if dhalo null)
 // Weights per entry: w_in in the order of the transposed inner-inner block, w_halo in that of the boundary nodes' static
-// lists (halo_ptr).  avg_len: entries to be expected per row of the launch.  row_scale, dis_halo, init nullable.  plan: segmentation of the transposed inner-inner block.
+// lists (halo_ptr).  avg_len: entries to be expected per row of the launch, expected_halo: about *n_kept (any number is walked).  row_scale, dis_halo, init nullable.  plan: segmentation of the transposed inner-inner block.
 hipError_t spmm_bwd(const SegPlan &plan, int32_t n_in, int32_t n_halo, int32_t d,
                     const int32_t *t_row_ptr, const int32_t *t_col_idx, const int32_t *kept_ids,
                     const int32_t *n_kept, const float *w_in, const float *w_halo, const int32_t *halo_ptr, const float *row_scale,
                     const float *dis_halo, float s_halo, const float *dA, const float *mask_src,
                     const float *init, bool skip_self, int32_t avg_len, float *partials, float *dH_in, float *dhalo,
-                    hipStream_t s, int32_t d_store = 0);
+                    int32_t expected_halo, hipStream_t s, int32_t d_store = 0);
 
 // ---- gemm_f32.hip (Eq. 2; fp32 MFMA), gemm.hip (its backward; fp32 on the bf16 MFMA) -------------
 // Dropout on a hidden layer's output (training set-up of Section 4): element (row, col) is kept iff

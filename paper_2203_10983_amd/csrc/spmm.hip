@@ -28,27 +28,22 @@ __global__ void __launch_bounds__(BLOCK ? kBlockWaves * kWave : 256, MAXCH == 1 
   constexpr int kWaves = BLOCK ? kBlockWaves : 4;
   const int lane = lane_id();
   const int g = lane / LPR, sl = lane % LPR;
-  int bid = blockIdx.x, nblk = gridDim.x, d_off = 0, n_units;
-  {
-    ArgBlock &a = unit_args();
-    if (const int ls = a.log2_slices) {  // gridDim.x is a multiple of 8
-      const int x = bid & 7;
-      bid = ((bid >> 3) << (3 - ls)) + (x >> ls);
-      nblk = (nblk >> 3) << (3 - ls);
-      const int turn = a.turn_blocks ? bid / a.turn_blocks : 0;
-      d_off = ((x + turn) & ((1 << ls) - 1)) * a.d_slice;
-    }
-    // the static units, then one unit per kept boundary row (count on the device)
-    n_units = a.n_units + (a.n_extra_dev ? scalar_load(a.n_extra_dev, 0) : 0);
+  int bid = blockIdx.x, d_off = 0;
+  const SpmmArgs::Head start = unit_head();
+  if (const int ls = start.log2_slices) {  // gridDim.x is a multiple of 8
+    const int x = bid & 7;
+    bid = ((bid >> 3) << (3 - ls)) + (x >> ls);
+    d_off = ((x + (int)__umulhi(bid, start.turn_share)) & ((1 << ls) - 1)) * start.d_slice;
   }
   // (the unit is the same for the whole wavefront, so that its bounds come through the scalar cache)
   const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if constexpr (BLOCK) {
-    ArgBlock &a = unit_args();
-    const int n_rows = a.n_block_rows;
+    const int n_rows = start.n_block_rows;
     if (bid < n_rows) {
+      ArgBlock &a = unit_args();
+      if (bid >= a.plan.n_multi) return;
       extern __shared__ __attribute__((aligned(16))) float block_part[];
-      const int nvec = a.d_slice / VEC;
+      const int nvec = start.d_slice / VEC;
       const int row = scalar_load(a.plan.mrow, bid);
       const int2 ee = scalar_load_pair(a.row_ptr, row);
       int e0 = ee.x, e1 = ee.y;
@@ -86,13 +81,28 @@ __global__ void __launch_bounds__(BLOCK ? kBlockWaves * kWave : 256, MAXCH == 1 
       return;
     }
     bid -= n_rows;
-    nblk -= n_rows;
   }
-  for (int unit = bid * kWaves + wid; unit < n_units; unit += nblk * kWaves) {
+  // A static unit per wavefront, and the kept boundary rows (their count is on the device): in workgroups of their own,
+  // extra_share in 2^32 of the groups of 8, or on all wavefronts after their units.
+  int unit = bid * kWaves + wid, end = start.n_units, step = start.extra_step;
+  if (const unsigned share = start.extra_share) {
+    const int group_bits = 3 - start.log2_slices, group = bid >> group_bits, in_group = bid & ((1 << group_bits) - 1);
+    const int before = __umulhi(group, share);  // such groups before this one
+    if ((int)__umulhi(group + 1, share) != before) {
+      unit = end + ((before << group_bits) + in_group) * kWaves + wid;
+      end += scalar_load(unit_args().n_extra_dev, 0);
+    } else {
+      unit = (((group - before) << group_bits) + in_group) * kWaves + wid;
+      step = end;
+    }
+  } else if (const int32_t *n = unit_args().n_extra_dev) {
+    end += scalar_load(n, 0);
+  }
+  for (; unit < end; unit += step) {
     ArgBlock &a = unit_args();
-    const int nvec = a.d_slice / VEC;
-    int row = a.n_split + (unit - a.n_units), slot = -1;
-    if (unit < a.n_units) {
+    const int nvec = a.head.d_slice / VEC;
+    int row = a.n_split + (unit - a.head.n_units), slot = -1;
+    if (unit < a.head.n_units) {
       const int2 u = scalar_load(a.units, unit);
       row = u.x;
       slot = u.y;
@@ -180,10 +190,10 @@ __global__ void __launch_bounds__(256) spmm_combine_kernel(const SpmmArgs a) {
 
 
 template <int VEC>
-static hipError_t launch_spmm_vec(const SpmmArgs &a_in, int64_t max_units, bool multi_only, int32_t avg_len, bool transposed, hipStream_t s) {
+static hipError_t launch_spmm_vec(const SpmmArgs &a_in, int64_t extra_rows, bool multi_only, int32_t avg_len, bool transposed, hipStream_t s) {
   SpmmArgs a = a_in;
   // multi_only: the segments of the multi-segment rows, i.e. the partial-sum slots
-  a.n_units = multi_only ? a.plan.n_part : a.plan.n_seg;
+  a.head.n_units = multi_only ? a.plan.n_part : a.plan.n_seg;
   a.units = multi_only ? a.plan.part_unit : a.plan.seg_unit;
   // Wide rows are cut into slices of 128 floats (64 where rows are long enough to keep a
   // wavefront busy with a quarter of its lanes per neighbour): narrower slices lose more to the repeated index walk than
@@ -206,41 +216,61 @@ static hipError_t launch_spmm_vec(const SpmmArgs &a_in, int64_t max_units, bool 
     ls = slices(128);
     int from = 64;
     if (transposed)
-      from = ((int64_t)a.n_units << ls) <= 8192 ? 19 : a.n_units < 24576 ? 32 : ls == 0 ? 19 : 24;
+      from = ((int64_t)a.head.n_units << ls) <= 8192 ? 19 : a.head.n_units < 24576 ? 32 : ls == 0 ? 19 : 24;
     if (avg_len >= from) ls = slices(64);
   }
-  a.log2_slices = ls;
-  a.d_slice = a.d >> ls;
+  a.head.log2_slices = ls;
+  a.head.d_slice = a.d >> ls;
   // The pass over the partial sums is a launch of 3 to 5 us.  Where the longest row has few segments, a workgroup per such
   // row saves it; its workgroups of eight wavefronts wait for their longest row, which costs more where wavefronts are many and
   // run at the rate of the LDS or vector pipes, i.e. in slices of 33 to 64 floats: those cross at about 20000 units (12000
   // rows in 2 slices 29.2 us, in blocks 30.2; 20000 in 2 38, 43; in 4 67, 80; 30000 whole rows 26.4, 27.6), rows of 9 to 32
   // floats at 50000 to 100000, wider ones not up to 100000 (128 floats: 12000 rows 36 and 33 us, 100000 155 and 149).
-  const bool narrow_slice = a.d_slice > 32 && a.d_slice <= 64;
+  const bool narrow_slice = a.head.d_slice > 32 && a.head.d_slice <= 64;
   const bool block_rows = !multi_only && a.plan.n_multi > 0 && a.plan.max_seg <= kBlockWaves &&
                           ((int64_t)a.plan.n_seg << ls) <= (narrow_slice ? 20480 : 65536);
-  a.n_block_rows = block_rows ? a.plan.n_multi : 0;
   const int waves = block_rows ? kBlockWaves : 4;
-  const int nvec = a.d_slice / VEC;
+  const int nvec = a.head.d_slice / VEC;
   const int full_nvec = a.d / VEC;
-  // one wavefront per static segment; the kept boundary rows, whose count lives on the device,
-  // are strided over by a bounded number of extra blocks (blocks past the count would only cost
-  // dispatch time)
-  const int64_t extra_blocks = multi_only ? 0 : std::min<int64_t>((max_units - a.n_units + waves - 1) / waves, 8192);
-  unsigned blocks = (unsigned)(a.n_block_rows + ((int64_t)a.n_units + waves - 1) / waves + std::max<int64_t>(extra_blocks, 0));
+  // One wavefront per static segment.  The kept boundary rows are a few entries each.  Where all wavefronts go on to them
+  // after their segment, the launch ends in a long stretch of short rows, bound by the rate at which workgroups start, while
+  // the wavefronts wait for the store of their first row (19 800 rows in four slices beside 52 800 segments: 110 of 640 us).
+  // Dealt among the workgroups of the segments, a row to a wavefront, they go by beside the long rows (all transposed aggregates
+  // of a step, us: that graph 2000 -> 1770; 25000 rows of 75 entries 255 -> 224; 90000 rows of 50 325 -> 284; 578125 rows of 22
+  // 1712 -> 1671).  Launches of short rows alone gain nothing by it: below 9 entries a row all wavefronts go on (90000 rows 414
+  // us, dealt 430; 200000 rows 802 and 856; 400000 rows 1893 and 1978), and in launches of two rounds of wavefronts or less
+  // the long rows start first (12000 rows of 110 entries, 100 floats: 57 and 60).  Four rows to a wavefront where slices make the workgroups
+  // too many (197 758 rows beside 52 800 segments in four slices: 2591 and 2427 us).  They are dealt in groups of a workgroup
+  // per XCD and slice, so that no XCD has more of them, and at a share that is no simple fraction (one in six exactly: the same
+  // shader engines had all of them, 1369 and 1565 us).
+  const int64_t per = 8 >> ls;
+  auto groups = [&](int64_t n) { return (n + per - 1) / per; };
+  const int64_t unit_groups = groups((a.head.n_units + waves - 1) / waves);
+  const bool dealt = extra_rows >= 0 && avg_len >= 9 && ((int64_t)a.head.n_units << ls) >= 16384;
+  int64_t extra_groups = 0;
+  if (dealt) {
+    const int rows = waves * (ls >= 2 && extra_rows >= 2 * (int64_t)a.head.n_units ? 4 : 1);
+    extra_groups = groups((extra_rows + rows - 1) / rows);
+    extra_groups += extra_groups / 32 + 1;  // (never none: any number is walked)
+  } else if (extra_rows >= 0) {
+    extra_groups = groups(std::min<int64_t>((extra_rows + waves - 1) / waves, 8192));
+  }
+  const int64_t all_groups = unit_groups + extra_groups;
+  a.head.n_block_rows = block_rows ? (int32_t)(groups(a.plan.n_multi) * per) : 0;
+  a.head.extra_share = dealt ? (uint32_t)((((uint64_t)extra_groups << 32) + all_groups - 1) / all_groups) : 0;
+  a.head.extra_step = (int32_t)((dealt ? extra_groups : all_groups) * per * waves);
+  const unsigned each = (unsigned)(a.head.n_block_rows + all_groups * per);  // workgroups of a slice
   const unsigned cblocks = block_rows ? 0u : (unsigned)((a.plan.n_multi + 3) / 4);
-  const size_t block_lds = (size_t)kBlockWaves * a.d_slice * sizeof(float);  // at most 64 KB
-  if (blocks == 0) return hipSuccess;
+  const size_t block_lds = (size_t)kBlockWaves * a.head.d_slice * sizeof(float);  // at most 64 KB
+  if (each == 0) return hipSuccess;
+  const unsigned blocks = each << ls;
   if (ls > 0) {
-    const unsigned per = 8 >> ls;
-    const unsigned each = (blocks + per - 1) / per * per;  // workgroups of a slice
     // The slices in turn pay where a turn is long beside filling the L2 anew and the launch is several rounds of
     // workgroups (whole launches, fixed and in turn, us): 6000 rows of 250 entries and 512 floats 221 -> 215, 256 floats
     // 140 -> 138; 25000 rows of 75 entries 405 -> 397, 248 -> 240; 12000 rows of 75 192 -> 193, 121 -> 123; 50000 rows of 19
     // 367 -> 370, 226 -> 223; 6000 rows of 75 104 -> 108.
     const bool in_turn = (int64_t)avg_len * a.n_split >= 1250000;
-    a.turn_blocks = in_turn ? (int)((each + (1u << ls) - 1) >> ls) : 0;
-    blocks = each / per * 8;
+    a.head.turn_share = in_turn ? (uint32_t)(((uint64_t)1 << (32 + ls)) / each) : 0;  // each > 2^ls then
   }
   if (a.d_store != a.d) {  // padded sources, dense narrower outputs: d < 128, four floats per lane
     if constexpr (VEC == 4) {
@@ -289,12 +319,12 @@ static hipError_t launch_spmm_vec(const SpmmArgs &a_in, int64_t max_units, bool 
   return hipGetLastError();
 }
 
-static hipError_t launch_spmm(const SpmmArgs &a, int64_t max_units, bool multi_only, int32_t avg_len, bool transposed, hipStream_t s) {
+static hipError_t launch_spmm(const SpmmArgs &a, int64_t extra_rows, bool multi_only, int32_t avg_len, bool transposed, hipStream_t s) {
   if (a.d_store != a.d && (a.d_store < 1 || a.d_store > a.d || a.d >= 128 || a.d % 4 != 0 || a.mask_src || a.init))
     return hipErrorInvalidValue;  // padded sources: narrow rows without mask or initial value only
-  if (a.d % 4 == 0) return launch_spmm_vec<4>(a, max_units, multi_only, avg_len, transposed, s);
-  if (a.d % 2 == 0) return launch_spmm_vec<2>(a, max_units, multi_only, avg_len, transposed, s);
-  return launch_spmm_vec<1>(a, max_units, multi_only, avg_len, transposed, s);
+  if (a.d % 4 == 0) return launch_spmm_vec<4>(a, extra_rows, multi_only, avg_len, transposed, s);
+  if (a.d % 2 == 0) return launch_spmm_vec<2>(a, extra_rows, multi_only, avg_len, transposed, s);
+  return launch_spmm_vec<1>(a, extra_rows, multi_only, avg_len, transposed, s);
 }
 
 hipError_t spmm_fwd(const SegPlan &plan, int32_t n_in, int32_t d, const int32_t *row_ptr,
@@ -304,7 +334,7 @@ hipError_t spmm_fwd(const SegPlan &plan, int32_t n_in, int32_t d, const int32_t 
   SpmmArgs a = spmm_fwd_args(plan, n_in, d, row_ptr, col_idx, w_in, w_ptr, row_scale, H_in, Hu, partials, A, part);
   a.relu = relu;
   if (d_store > 0) a.d_store = d_store;
-  return launch_spmm(a, plan.n_seg, long_rows_only, plan.avg_len, false, s);
+  return launch_spmm(a, -1, long_rows_only, plan.avg_len, false, s);
 }
 
 hipError_t spmm_bwd(const SegPlan &plan, int32_t n_in, int32_t n_halo, int32_t d,
@@ -312,7 +342,7 @@ hipError_t spmm_bwd(const SegPlan &plan, int32_t n_in, int32_t n_halo, int32_t d
                     const int32_t *n_kept, const float *w_in, const float *w_halo, const int32_t *halo_ptr, const float *row_scale,
                     const float *dis_halo, float s_halo, const float *dA, const float *mask_src,
                     const float *init, bool skip_self, int32_t avg_len, float *partials, float *dH_in, float *dhalo,
-                    hipStream_t s, int32_t d_store) {
+                    int32_t expected_halo, hipStream_t s, int32_t d_store) {
   SpmmArgs a{};
   const bool halo_rows = dhalo && n_halo > 0;
   a.plan = plan; a.n_extra_dev = halo_rows ? n_kept : nullptr; a.d = d; a.d_store = d_store > 0 ? d_store : d;
@@ -321,7 +351,7 @@ hipError_t spmm_bwd(const SegPlan &plan, int32_t n_in, int32_t n_halo, int32_t d
   a.out0 = dH_in; a.out1 = dhalo; a.out_scale0 = row_scale; a.mask_src = mask_src;
   a.kept_ids = kept_ids; a.dis_halo = dis_halo; a.s_halo = s_halo;
   a.init = init; a.skip_self = skip_self;
-  return launch_spmm(a, (int64_t)plan.n_seg + (halo_rows ? n_halo : 0), false, avg_len, true, s);
+  return launch_spmm(a, halo_rows ? expected_halo : -1, false, avg_len, true, s);
 }
 
 // ------------------------------------------------------------------------------------------

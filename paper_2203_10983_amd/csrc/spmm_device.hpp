@@ -24,10 +24,25 @@ __device__ __forceinline__ void vec_fma(float (&acc)[VEC], float w, const typena
 
 struct SpmmArgs {
   SegPlan plan;                // static segmentation of rows 0..n_split-1
-  int32_t n_units;             // work units of the kernel: segments of the plan, (row, partial-sum slot or -1)
-  const int2 *units;
-  int32_t n_block_rows;        // BLOCK kernels: workgroups in front that own a multi-segment row of the plan each
+  // feature slicing over the XCDs (log2_slices = 0: off).  Workgroups are handed to the 8 XCDs in
+  // turn, so workgroup b runs on XCD b % 8; with S = 2^log2_slices that XCD only ever touches the
+  // d_slice = d / S floats of one slice of every feature row at a time, and its private L2 holds S
+  // times as many distinct rows.  The slices are not equally fast:
+  // where rows are a multiple of 1 KB apart, one 128-byte line in eight is gathered as if half of the L2's channels held it
+  // (5.1 M random pieces of 128 bytes out of rows of 1 KB: 8000 rows 30 us, that line 37; 29125 rows 32 us, 46), and with one
+  // slice for the whole launch the XCDs of that slice end last (10 M entries of 256 floats: 628 us, the others 490 to 517).
+  // So an XCD takes the slices in turn.
+  struct Head {                // what a workgroup needs to find its work, in one scalar load
+    int32_t log2_slices, d_slice;
+    uint32_t turn_share;       // turn of workgroup b of a slice: b * turn_share / 2^32 (0: the XCDs stay)
+    int32_t n_units;           // work units of the kernel: segments of the plan, (row, partial-sum slot or -1)
+    int32_t n_block_rows;      // BLOCK kernels: workgroups in front, of which the first n_multi own a multi-segment row of the plan each
+    uint32_t extra_share;      // the *n_extra_dev further rows: share of the workgroups that are theirs alone, in 2^32 (0: none are)
+    int32_t extra_step;        // wavefronts that share these rows
+    int32_t unused;
+  } head;
   const int32_t *n_extra_dev;  // nullable: *n_extra_dev further single-segment rows follow (kept boundary)
+  const int2 *units;
   int32_t d;                   // floats per gathered row = row stride of src0, src1 and the partial sums
   const int32_t *row_ptr, *col_idx;
   int32_t n_split;             // columns < n_split read src0; others src1 (weight 1)
@@ -58,16 +73,6 @@ struct SpmmArgs {
   const int32_t *row_take;     // then use row_take[row] entries instead of the rest (nullable)
   const float *init;           // out0 row = scale * (init row + sum) (nullable)
   bool skip_self;              // entries with column == row contribute nothing (mean aggregator)
-  // feature slicing over the XCDs (log2_slices = 0: off).  Workgroups are handed to the 8 XCDs in
-  // turn, so workgroup b runs on XCD b % 8; with S = 2^log2_slices that XCD only ever touches the
-  // d_slice = d / S floats of one slice of every feature row at a time, and its private L2 holds S
-  // times as many distinct rows.  The slices are not equally fast:
-  // where rows are a multiple of 1 KB apart, one 128-byte line in eight is gathered as if half of the L2's channels held it
-  // (5.1 M random pieces of 128 bytes out of rows of 1 KB: 8000 rows 30 us, that line 37; 29125 rows 32 us, 46), and with one
-  // slice for the whole launch the XCDs of that slice end last (10 M entries of 256 floats: 628 us, the others 490 to 517).
-  // So an XCD takes the slices in turn.
-  int32_t log2_slices, d_slice;
-  int32_t turn_blocks;  // workgroups of a slice after which its XCDs go on to the next slice (0: they stay)
   bool relu;                   // rows < n_split: max(., 0) after the scale (update-first layers)
   // columns stored per output row = row stride of out0 / out1; less than d when the sources are
   // padded to a multiple of 4 floats (then no mask, no init, no slices; read by the NARROW kernels only)
@@ -82,6 +87,13 @@ __device__ __forceinline__ ArgBlock &unit_args() {
   auto *p = (ArgBlock *)__builtin_amdgcn_kernarg_segment_ptr();
   asm volatile("" : "+s"(p));
   return *p;
+}
+
+using HeadWords = int __attribute__((ext_vector_type(8), aligned(4)));
+static_assert(sizeof(SpmmArgs::Head) == sizeof(HeadWords));
+__device__ __forceinline__ SpmmArgs::Head unit_head() {
+  const HeadWords w = *reinterpret_cast<const __attribute__((address_space(4))) HeadWords *>(&unit_args().head);
+  return __builtin_bit_cast(SpmmArgs::Head, w);
 }
 
 // p[i] through the scalar cache, for an i that is the same on the whole wavefront and memory that the kernel does not write.
@@ -111,7 +123,7 @@ inline SpmmArgs spmm_fwd_args(const SegPlan &plan, int32_t n_in, int32_t d, cons
   a.kept_ids = nullptr; a.dis_halo = nullptr; a.s_halo = 0.f;
   a.row_skip = part.row_skip; a.row_take = part.row_take; a.init = part.init;
   a.skip_self = part.skip_self;
-  a.log2_slices = 0; a.d_slice = d; a.relu = false;
+  a.head.log2_slices = 0; a.head.d_slice = d; a.relu = false;
   return a;
 }
 
