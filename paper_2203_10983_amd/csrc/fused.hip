@@ -7,8 +7,8 @@
 // The aggregate is bound by the rate at which the L2s pull neighbour rows from the fabric and
 // leaves the matrix cores idle; the update of a 128-wide layer needs almost as much time for
 // re-reading the aggregated rows as for its arithmetic.  Here a workgroup of 8 wavefronts
-// aggregates a tile of 64 rows straight into LDS (each finished row also goes to global memory,
-// because the weight gradient of the backward pass is A^T dZ), then multiplies the tile by W with
+// aggregates a tile of 64 rows straight into LDS (the tile then also goes to global memory,
+// because the weight gradient of the backward pass is A^T dZ) and multiplies the tile by W with
 // v_mfma_f32_32x32x2_f32 while the other workgroups of the compute unit keep gathering.  W comes
 // from L2 in 16-row pieces through a double-buffered LDS tile.
 //
@@ -51,12 +51,15 @@ __global__ void __launch_bounds__(kFThreads, 6) __attribute__((amdgpu_num_sgpr(9
   // ---- phase 0: the tile's row bounds into LDS (one coalesced read instead of a dependent chain
   // per row).  s_e0/s_e1: entries to gather; s_e1 < 0 marks a row finished by the segmented pass.
   __shared__ int s_e0[kFM], s_e1[kFM], s_wd[kFM];  // s_wd: from an entry to its place in w_in
+  __shared__ float s_scale[kFM];
   __shared__ unsigned char s_order[kFM];  // the tile's rows, longest class first
   __shared__ int next_row;
   if (threadIdx.x < kFM) {
     const int row = row0 + threadIdx.x;
     int e0 = 0, e1 = 0, wd = 0;
+    float scale = 1.f;
     if (row < a.n_split) {
+      if (a.out_scale0) scale = a.out_scale0[row];
       e0 = a.row_ptr[row];
       e1 = a.row_ptr[row + 1];
       if (a.w_in) wd = a.w_ptr[row] - e0;
@@ -67,6 +70,7 @@ __global__ void __launch_bounds__(kFThreads, 6) __attribute__((amdgpu_num_sgpr(9
     s_e0[threadIdx.x] = e0;
     s_e1[threadIdx.x] = e1;
     s_wd[threadIdx.x] = wd;
+    s_scale[threadIdx.x] = scale;
     // A long row that is taken last keeps the whole tile waiting: the rows are taken in classes of falling length
     // (21 entries a row and a power-law tail: 696 -> 677 us).  The lanes of this wavefront are the rows.
     const int len = e1 - e0, cls = len > 0 ? 32 - __clz(len) : 0;
@@ -145,7 +149,14 @@ __global__ void __launch_bounds__(kFThreads, 6) __attribute__((amdgpu_num_sgpr(9
           gather_batch<VEC, 1, LPR>(p_l, w_l, cnt, nvec, acc);
         }
         fold_groups<VEC, 1, LPR>(acc);
-        if (g == 0) finish_row<VEC, 1>(a, row, sl, nvec, 0, acc, lds_row);
+        if (g == 0 && sl < nvec) {
+          const float scale = s_scale[lrow];
+          V x = V{};
+          if (a.init) x = reinterpret_cast<const V *>(a.init + (size_t)row * d)[sl];
+          const float *px = reinterpret_cast<const float *>(&x);
+#pragma unroll
+          for (int i = 0; i < VEC; ++i) lds_row[sl * VEC + i] = (a.init ? acc[0][i] + px[i] : acc[0][i]) * scale;
+        }
       }
       for (int k = d + lane; k < k_pad; k += kWave) lds_row[k] = 0.f;  // depth padding
     }
@@ -202,6 +213,19 @@ __global__ void __launch_bounds__(kFThreads, 6) __attribute__((amdgpu_num_sgpr(9
   };
   float4 wv = load_w(0, 0);  // in flight across the barrier that ends the gather
   __syncthreads();
+  // The gathered rows go to A out of the tile.  A wavefront that stored each row as it finished it would wait for that store
+  // with the loads of its next row, which the memory counter puts behind it (layers of 578125 rows 678 -> 655 us, of the
+  // mean aggregator on 306250 rows 614 -> 602, of 306250 rows of 100 floats unchanged).
+  for (int r = wid * (kFM / 8) + g; r < (wid + 1) * (kFM / 8); r += kWave / LPR) {
+    const int row = row0 + r;
+    if (row < a.n_split && s_e1[r] >= 0 && sl < nvec) {
+      V o;
+      float *po = reinterpret_cast<float *>(&o);
+#pragma unroll
+      for (int i = 0; i < VEC; ++i) po[i] = As[r * kFLda + sl * VEC + i];
+      __builtin_nontemporal_store(o, reinterpret_cast<V *>(a.out0 + (size_t)row * d) + sl);
+    }
+  }
   if constexpr (SAGE) {
     // [z | h] [W_n ; W_s]: both operands pass through the one LDS tile, so the accumulators of every
     // column tile (at most two: d_out <= 256) stay live across the two products.

@@ -128,11 +128,10 @@ inline SpmmArgs spmm_fwd_args(const SegPlan &plan, int32_t n_in, int32_t d, cons
 }
 
 // Scale, optional ReLU mask and store of one finished row slice held as acc[c][i].
-// lds_row (nullable): the finished values are also written there, element iv*VEC+i at lds_row[iv*VEC+i].
 // NARROW: the sources are padded (d_store < d), the output rows are dense with d_store columns.
 template <int VEC, int MAXCH, bool NARROW = false, typename Args>
 __device__ __forceinline__ void finish_row(Args &a, int row, int sl, int nvec, int d_off,
-                                           float (&acc)[MAXCH][VEC], float *lds_row = nullptr) {
+                                           float (&acc)[MAXCH][VEC]) {
   using V = typename Vec<VEC>::T;
   const int d = a.d, ds = NARROW ? (int)a.d_store : d;
   float scale;
@@ -184,10 +183,6 @@ __device__ __forceinline__ void finish_row(Args &a, int row, int sl, int nvec, i
 #pragma unroll
         for (int i = 0; i < VEC; ++i)
           if (iv * VEC + i < ds) out[iv * VEC + i] = po[i];
-      }
-      if (lds_row) {
-#pragma unroll
-        for (int i = 0; i < VEC; ++i) lds_row[iv * VEC + i] = po[i];
       }
     }
   }
