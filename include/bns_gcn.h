@@ -210,7 +210,9 @@ bns_status bns_graph_replay(bns_ctx *ctx, int32_t n_epochs, void *stream);
  * three plans give the same results up to rounding (Appendix A writes Z = P H W without
  * parentheses); they differ in kernel boundaries, in what BNS_VIEW_A holds and in what the phase
  * timers attribute to BNS_PHASE_SPMM_FWD / BNS_PHASE_GEMM_FWD.
- *   BNS_LAYER_TWO_KERNELS  aggregate (Eq. 1), then update (Eq. 2); BNS_VIEW_A = the aggregate.
+ *   BNS_LAYER_TWO_KERNELS  aggregate (Eq. 1), then update (Eq. 2); BNS_VIEW_A = the aggregate.  (On up to some
+ *                          thousand rows both in one launch, a few rows at a time, with the same bits;
+ *                          two while either phase is timed.)
  *   BNS_LAYER_ONE_KERNEL   the same two steps in one kernel: input width a multiple of 4 between 68
  *                          and 128, at least 32768 inner nodes (98304 if a row of the local graph has
  *                          more than 256 entries); the mean-aggregator layer, whose update is twice as deep, only

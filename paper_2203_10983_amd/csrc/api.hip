@@ -138,6 +138,23 @@ bool one_kernel_layer(const bns_ctx *ctx, int d_in, int d_out) {
 // not cut the 16-deep groups that a depth is zero-padded to.
 bool concat_in_one(int d_in) { return d_in % 16 == 0; }
 
+// Do a and b, of na and nb floats, share memory?
+bool overlap(const float *a, size_t na, const float *b, size_t nb) {
+  const uintptr_t x = (uintptr_t)a, y = (uintptr_t)b;
+  return x < y + nb * sizeof(float) && y < x + na * sizeof(float);
+}
+// Aggregate and update of a layer of a small partition in one launch, a few rows per workgroup?  A launch and a pass over
+// the aggregate less; with more rows than fill the chip the weights, read anew for every tile, cost more than they save, and a row
+// of several segments, which its workgroup gathers alone, does so sooner.  Steps, two launches per layer / one (us): without such
+// rows 500 rows 64-16-8 45 / 37, 500 rows 128-128-128-47 77 / 59, 3000 rows of 10 entries 108 / 93, 6500 129 / 114, 9000 141 / 137
+// and with 45 entries 162 / 164, 12000 160 / 158; with them 1000 rows of 45 entries 118 / 102, 3000 136 / 130, 4500 146 / 155.
+constexpr int kTileMaxRows = 8192, kTileMaxRowsLong = 3584, kTileMaxSegments = 8;
+bool tile_layer(const bns_ctx *ctx, int layer) {
+  const SegPlan &plan = ctx->ws.plan_f;
+  return ctx->part.n_in <= (plan.n_multi > 0 ? kTileMaxRowsLong : kTileMaxRows) && plan.max_seg <= kTileMaxSegments &&
+         tile_layer_supported(plan, ctx->dims[layer - 1], ctx->dims[layer]);
+}
+
 bool valid_desc(const bns_partition_desc *p, const bns_model_desc *m) {
   if (!p || !m || !m->dims) return false;
   if (p->n_in < 1 || p->n_halo < 0 || p->nnz0 < p->n_in || p->e_in < p->n_in || p->e_bd < 0) return false;
@@ -409,6 +426,18 @@ bns_status layer_fwd_impl(bns_ctx *ctx, int layer, double p, const float *H_in, 
                                            w_in, w_ptr, row_scale, H_in, halo_h, ctx->ws.spmm_partials, A_saved,
                                            part, W, H_out, relu, dropout_of(ctx, layer, relu), s, sage));
     return BNS_OK;
+  }
+  if (tile_layer(ctx, layer) && !timed(ctx, BNS_PHASE_SPMM_FWD) && !timed(ctx, BNS_PHASE_GEMM_FWD)) {
+    const size_t n_w = (size_t)(sage ? 2 : 1) * d_in * d_out, n_a = (size_t)n_in * d_in, n_h = (size_t)n_in * d_out;
+    const auto meets = [&](const float *out, size_t n) {  // (one kernel reads what two have read before the second writes)
+      return overlap(out, n, H_in, n_a) || overlap(out, n, halo_h, (size_t)B * d_in) || overlap(out, n, W, n_w);
+    };
+    if (!meets(A_saved, n_a) && !meets(H_out, n_h)) {
+      BNS_TRY("tile_layer_fwd", tile_layer_fwd(ctx->ws.plan_f, n_in, d_in, d_out, ctx->cur_row_ptr, ctx->cur_col_idx, w_in, w_ptr,
+                                               row_scale, H_in, halo_h, ctx->ws.spmm_partials, A_saved, part, W, H_out, relu,
+                                               dropout_of(ctx, layer, relu), sage, concat_in_one(d_in), s));
+      return BNS_OK;
+    }
   }
   {
     PhaseTimer t(ctx, BNS_PHASE_SPMM_FWD, s);

@@ -205,6 +205,15 @@ struct Dropout {
   uint32_t k0 = 0, k1 = 0, c2 = 0, epoch = 0;
   const uint32_t *epoch_dev = nullptr;  // nullable: the epoch index is read from device memory
 };
+// ---- tile.hip: aggregate and update of a layer of a small partition in one launch --------------
+// As spmm_fwd and then gemm_rows_f32 on [A | H_in (sage)] W with the plain W: the same bits.  concat: the two halves of the mean
+// aggregator's update are one product (else two, added).  Neither A nor H_out may share memory with H_in, Hu or W.
+bool tile_layer_supported(const SegPlan &plan, int32_t d_in, int32_t d_out);
+hipError_t tile_layer_fwd(const SegPlan &plan, int32_t n_in, int32_t d_in, int32_t d_out, const int32_t *row_ptr,
+                          const int32_t *col_idx, const float *w_in, const int32_t *w_ptr, const float *row_scale,
+                          const float *H_in, const float *Hu, float *partials, float *A, const SpmmRowPart &part, const float *W,
+                          float *H_out, bool relu, const Dropout &drop, bool sage, bool concat, hipStream_t s);
+
 // C[M,N] = [A | A2] B (+ the previous C if accumulate), B [K,N] packed; then, if relu, max(., 0) and dropout (when
 // drop.scale != 0).  A, A2 [M, lda]: the depth below a_split (a multiple of 16) is A's, the rest A2's (nullable).
 // pad: the columns N..ldc-1 are set to zero (ldc at most N rounded up to a multiple of 4; not with relu or

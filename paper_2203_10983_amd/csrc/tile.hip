@@ -1,0 +1,230 @@
+// A layer of a small partition in one launch: aggregate (Eq. 1), then update (Eq. 2) of a few rows in one workgroup.
+//
+// On some thousand rows neither step fills the chip: a launch is 2 to 3 us of starting and draining beside about 2 us of
+// dependent reads, whatever its size.  A workgroup of 8 wavefronts owns a tile of 8 or 16 rows, gathers them into LDS with the
+// code and the order of sums of spmm_kernel, and multiplies them by W with v_mfma_f32_16x16x4_f32, a wavefront per 16 or
+// 32 columns.  That instruction is a chain of fused multiply-adds in depth order, as v_mfma_f32_32x32x2_f32 is (40960 sums of 128 products of
+// operands of any size: equal bits, and equal to fmaf), so that the results are those of spmm_kernel and gemm_rows_f32_kernel.
+// W is asked for before the gather, straight from the caller's matrix: 16 columns of 4 depths are a load of 256 bytes.
+#include "spmm_device.hpp"
+#include "split_bf16.hpp"
+
+namespace bns {
+
+namespace {
+
+constexpr int kTileRows = 16, kTileWaves = 8;
+constexpr int kTileDepth = 128;  // widest input row
+constexpr int kTileLd = kTileDepth + 4;  // 4 floats on from row to row: the 64 operands of an instruction are in 64 banks
+
+struct TileArgs {
+  SpmmArgs sp;
+  const float *W;       // [d_in, d_out]; SAGE: [2 d_in, d_out], neighbour half first
+  const float *H_self;  // SAGE: the layer's input
+  float *H_out;
+  int32_t d_out, rows;  // rows of a tile
+  bool relu;
+  bool concat;          // SAGE: both halves of the update are one chain of sums (else two, added)
+  Dropout drop;
+};
+
+typedef float f32x2u __attribute__((ext_vector_type(2), aligned(4)));
+
+template <int LPR, int VW, bool SAGE>
+__global__ void __launch_bounds__(kTileWaves * kWave, 4) tile_layer_kernel(const TileArgs f) {
+  using V = typename Vec<4>::T;
+  __shared__ __attribute__((aligned(16))) float As[SAGE ? 2 : 1][kTileRows * kTileLd];
+  const SpmmArgs &a = f.sp;
+  const int lane = lane_id(), wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int d = a.d, nvec = d / 4, N = f.d_out;
+  const int row0 = blockIdx.x * f.rows, rows = min(f.rows, a.n_split - row0);
+
+  // ---- the wavefront's columns of W: a lane holds VW of them at depths 4 m + lane / 16 ----
+  const int l16 = lane & 15, g4 = lane >> 4;
+  const int n0 = wid * 16 * VW;
+  const int col = min(n0 + l16 * VW, N - VW);  // lanes past the last column repeat it
+  float w[LPR][VW];  // d / 4 <= LPR
+  auto load_w = [&](const float *Wm) {
+    if (n0 >= N) return;
+    const float *p = Wm + (size_t)g4 * N + col;
+#pragma unroll
+    for (int m = 0; m < LPR; ++m)
+      if (m < nvec) {
+        if constexpr (VW == 2) {
+          const f32x2u x = *reinterpret_cast<const f32x2u *>(p + (size_t)(4 * m) * N);
+          w[m][0] = x[0];
+          w[m][1] = x[1];
+        } else {
+          w[m][0] = p[(size_t)(4 * m) * N];
+        }
+      }
+  };
+  load_w(f.W);
+  if constexpr (SAGE) {  // the rows' own features
+    for (int idx = threadIdx.x; idx < rows * nvec; idx += kTileWaves * kWave) {
+      const int r = idx / nvec, c4 = idx - r * nvec;
+      *reinterpret_cast<V *>(&As[1][r * kTileLd + c4 * 4]) = reinterpret_cast<const V *>(f.H_self + (size_t)(row0 + r) * d)[c4];
+    }
+  }
+
+  // ---- aggregate ----
+  const int g = lane / LPR, sl = lane % LPR;
+  auto put_row = [&](int row, int piece, const float (&acc)[1][4]) {  // as finish_row, and into the tile
+    const float scale = a.out_scale0 ? scalar_load(a.out_scale0, row) : 1.f;
+    if (piece >= nvec) return;
+    V o;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) o[i] = acc[0][i];
+    if (a.init) o += reinterpret_cast<const V *>(a.init + (size_t)row * d)[piece];
+    o *= scale;
+    *reinterpret_cast<V *>(&As[0][(row - row0) * kTileLd + piece * 4]) = o;
+    reinterpret_cast<V *>(a.out0 + (size_t)row * d)[piece] = o;
+  };
+  auto entries = [&](int row, int &e0, int &e1) {
+    const int2 ee = scalar_load_pair(a.row_ptr, row);
+    const InnerWeights iw = inner_weights(a, row, ee.x, ee.y);
+    e0 = ee.x;
+    e1 = ee.y;
+    if (a.row_skip) e0 += scalar_load(a.row_skip, row);
+    if (a.row_take) e1 = e0 + scalar_load(a.row_take, row);
+    return iw;
+  };
+  float acc[1][4];
+  if (a.plan.n_multi == 0) {
+    for (int r = wid; r < rows; r += kTileWaves) {
+      int e0, e1;
+      const InnerWeights iw = entries(row0 + r, e0, e1);
+      gather_segment<4, 1, LPR>(a, row0 + r, iw, e0, e1, 0, nvec, acc);
+      if (g == 0) put_row(row0 + r, sl, acc);
+    }
+  } else {  // a wavefront per segment; the sums of rows of several segments are added in ascending order
+    const int end = scalar_load(a.plan.seg_ptr, row0 + rows);
+    for (int u = scalar_load(a.plan.seg_ptr, row0) + wid; u < end; u += kTileWaves) {
+      const int2 unit = scalar_load(a.plan.seg_unit, u);
+      const int row = unit.x, slot = unit.y;
+      int e0, e1;
+      const InnerWeights iw = entries(row, e0, e1);
+      if (slot >= 0) {
+        const int seg = slot - scalar_load(a.plan.part_ptr, row);
+        const int2 ss = scalar_load_pair(a.plan.seg_ptr, row);
+        const int chunk = (e1 - e0 + (ss.y - ss.x) - 1) / (ss.y - ss.x);
+        e0 = min(e1, e0 + seg * chunk);
+        e1 = min(e1, e0 + chunk);
+      }
+      gather_segment<4, 1, LPR>(a, row, iw, e0, e1, 0, nvec, acc);
+      if (g != 0) continue;
+      if (slot < 0) put_row(row, sl, acc);
+      else if (sl < nvec) reinterpret_cast<V *>(a.partials + (size_t)slot * d)[sl] = V{acc[0][0], acc[0][1], acc[0][2], acc[0][3]};
+    }
+    __syncthreads();
+    for (int r = wid; r < rows; r += kTileWaves) {
+      const int row = row0 + r;
+      const int2 ss = scalar_load_pair(a.plan.seg_ptr, row);
+      const int nseg = ss.y - ss.x;
+      if (nseg <= 1) continue;
+      const float *part = a.partials + (size_t)scalar_load(a.plan.part_ptr, row) * d;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) acc[0][i] = 0.f;
+      if (lane < nvec)
+        for (int s = 0; s < nseg; ++s) {
+          const V x = reinterpret_cast<const V *>(part + (size_t)s * d)[lane];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) acc[0][i] += x[i];
+        }
+      put_row(row, lane, acc);
+    }
+  }
+  __syncthreads();
+  if (n0 >= N) return;
+
+  // ---- update ----
+  f32x4 sum[VW];
+#pragma unroll
+  for (int c = 0; c < VW; ++c) sum[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto product = [&](const float *tile) {  // (the tile's rows past the last one hold anything: an operand's row is one result's row)
+    const float *as = tile + l16 * kTileLd + g4;
+#pragma unroll
+    for (int m = 0; m < LPR; ++m)
+      if (m < nvec) {
+        const float x = as[4 * m];
+#pragma unroll
+        for (int c = 0; c < VW; ++c) sum[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(x, w[m][c], sum[c], 0, 0, 0);
+      }
+  };
+  product(As[0]);
+  if constexpr (SAGE) {
+    load_w(f.W + (size_t)d * N);
+    f32x4 first[VW];
+#pragma unroll
+    for (int c = 0; c < VW; ++c) {
+      first[c] = f.concat ? f32x4{0.f, 0.f, 0.f, 0.f} : sum[c];
+      if (!f.concat) sum[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    product(As[1]);
+    if (!f.concat)
+#pragma unroll
+      for (int c = 0; c < VW; ++c) sum[c] += first[c];
+  }
+  // a lane holds rows 4 (lane / 16) .. + 3 of its columns
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int lrow = 4 * g4 + r;
+    float x[VW];
+#pragma unroll
+    for (int c = 0; c < VW; ++c) {
+      x[c] = sum[c][r];
+      if (f.relu) {
+        x[c] = fmaxf(x[c], 0.f);
+        if (f.drop.scale != 0.f) x[c] = dropout_keeps(f.drop, row0 + lrow, col + c) ? x[c] * f.drop.scale : 0.f;
+      }
+    }
+    if (lrow >= rows) continue;
+    float *const to = f.H_out + (size_t)(row0 + lrow) * N + col;
+    if constexpr (VW == 2) *reinterpret_cast<f32x2u *>(to) = f32x2u{x[0], x[1]};
+    else *to = x[0];
+  }
+}
+
+}  // namespace
+
+bool tile_layer_supported(const SegPlan &plan, int32_t d_in, int32_t d_out) {
+  // rows of 4 to 32 lanes (128 floats are cut into slices from 64 entries a row on); the weights of 32 columns at 128
+  // depths are more registers than there are
+  return d_in % 4 == 0 && d_in > 8 && d_in <= kTileDepth && (d_in < kTileDepth || plan.avg_len < 64) && d_out >= 1 &&
+         d_out <= (d_in <= 64 ? 32 : 16) * kTileWaves;
+}
+
+hipError_t tile_layer_fwd(const SegPlan &plan, int32_t n_in, int32_t d_in, int32_t d_out, const int32_t *row_ptr,
+                          const int32_t *col_idx, const float *w_in, const int32_t *w_ptr, const float *row_scale,
+                          const float *H_in, const float *Hu, float *partials, float *A, const SpmmRowPart &part, const float *W,
+                          float *H_out, bool relu, const Dropout &drop, bool sage, bool concat, hipStream_t s) {
+  if (!tile_layer_supported(plan, d_in, d_out)) return hipErrorInvalidValue;
+  if (n_in <= 0) return hipSuccess;
+  TileArgs f;
+  f.sp = spmm_fwd_args(plan, n_in, d_in, row_ptr, col_idx, w_in, w_ptr, row_scale, H_in, Hu, partials, A, part);
+  f.W = W;
+  f.H_self = sage ? H_in : nullptr;
+  f.H_out = H_out;
+  f.d_out = d_out;
+  // Half a tile where whole ones are fewer than the compute units: a row per wavefront (steps of 128-128-128-47, tiles of
+  // 16 and 8, us: 1000 rows 66 / 64, of 45 entries 93 / 84; 3000 92 / 91; 4500 98 / 106).
+  f.rows = n_in <= 3584 ? kTileRows / 2 : kTileRows;
+  f.relu = relu;
+  f.concat = concat;
+  f.drop = drop;
+  const unsigned blocks = (unsigned)((n_in + f.rows - 1) / f.rows);
+#define BNS_TILE(LPR, VW)                                                                       \
+  do {                                                                                           \
+    if (sage) tile_layer_kernel<LPR, VW, true><<<blocks, kTileWaves * kWave, 0, s>>>(f);        \
+    else tile_layer_kernel<LPR, VW, false><<<blocks, kTileWaves * kWave, 0, s>>>(f);            \
+  } while (0)
+  const bool wide = d_out > 16 * kTileWaves;
+  if (d_in > 64) BNS_TILE(32, 1);
+  else if (d_in > 32) { if (wide) BNS_TILE(16, 2); else BNS_TILE(16, 1); }
+  else if (d_in > 16) { if (wide) BNS_TILE(8, 2); else BNS_TILE(8, 1); }
+  else { if (wide) BNS_TILE(4, 2); else BNS_TILE(4, 1); }
+#undef BNS_TILE
+  return hipGetLastError();
+}
+
+}  // namespace bns

@@ -1,0 +1,90 @@
+"""Layers of small partitions, aggregate and update in one launch, against the two launches that run while their phases are
+timed: the same sums in the same order, so the same bits.  Random graphs with hubs of up to eight segments of 256 entries."""
+import types
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+TIMED = (1 << 3) | (1 << 4)  # aggregate, update
+
+
+def _partition(n, deg, hub, n_halo, rng):
+    """n rows of about deg entries, row n // 2 with hub; symmetric inner part with self-loops, boundary nodes next to a few rows."""
+    pairs = {(v, v) for v in range(n)}
+    for _ in range(int(n * deg / 2)):
+        a, b = (int(x) for x in rng.integers(0, n, 2))
+        pairs |= {(a, b), (b, a)}
+    for b in rng.choice(n, size=min(n, hub), replace=False):
+        pairs |= {(n // 2, int(b)), (int(b), n // 2)}
+    inner = np.array(sorted(pairs), dtype=np.int64)
+    halo = np.array(sorted({(b, int(v)) for b in range(n_halo) for v in rng.integers(0, n, 1 + b % 4)}), dtype=np.int64).reshape(-1, 2)
+    both = np.concatenate([inner, np.stack([halo[:, 1], n + halo[:, 0]], 1)])
+    both = both[np.lexsort((both[:, 1], both[:, 0]))]
+    ptr = lambda of, m: np.concatenate([[0], np.cumsum(np.bincount(of, minlength=m))])  # noqa: E731
+    i32 = lambda x: np.ascontiguousarray(x, dtype=np.int32)  # noqa: E731
+    return types.SimpleNamespace(
+        part_id=0, n_in=n, n_halo=n_halo, nnz0=len(both), e_in=len(inner), e_bd=len(halo), row_ptr0=i32(ptr(both[:, 0], n)), col0=i32(both[:, 1]),
+        t_in_ptr=i32(ptr(inner[:, 0], n)), t_in_col=i32(inner[:, 1]), halo_ptr=i32(ptr(halo[:, 0], n_halo)), halo_col=i32(halo[:, 1]),
+        halo_gid=np.arange(n, n + n_halo, dtype=np.int64), deg_in=i32(np.bincount(both[:, 0], minlength=n)),
+        deg_halo=i32(np.bincount(halo[:, 0], minlength=n_halo) + 1))
+
+
+@pytest.mark.parametrize("n,deg,hub,dims,layer_kind,drop,cached", [
+    (1, 0, 0, (12, 16, 1), 0, 0.0, False), (7, 2, 0, (64, 16, 8), 0, 0.0, False), (17, 3, 0, (16, 129, 12, 2), 1, 0.3, False),
+    (500, 5, 0, (64, 172, 8), 0, 0.5, True), (600, 8, 560, (128, 128, 47), 0, 0.0, False), (2100, 4, 2048, (100, 128, 17), 1, 0.0, True),
+    (3584, 20, 300, (32, 256, 16), 1, 0.3, False), (3585, 20, 0, (60, 33, 9), 0, 0.0, False), (8192, 3, 0, (36, 128, 20, 5), 1, 0.0, False)])
+def test_one_launch_equals_two(n, deg, hub, dims, layer_kind, drop, cached):
+    import torch
+    import paper_2203_10983_amd as pkg
+    dev = torch.device("cuda:0")
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(n)
+    n_halo, L = n // 2 + 1, len(dims) - 1
+    P = _partition(n, deg, hub, n_halo, np.random.default_rng(n))
+    r = lambda *s: torch.randn(*s, device=dev, generator=gen)  # noqa: E731
+    X, halo = r(n, dims[0]), [r(n_halo, d) for d in dims[:-1]]
+    W = [r((1 + layer_kind) * a, b) / a ** 0.5 for a, b in zip(dims, dims[1:])]
+    labels = torch.randint(0, dims[-1], (n,), device=dev, generator=gen, dtype=torch.int32)
+    out = []
+    for mask in (TIMED, 0):
+        ctx = pkg.Context(P, list(dims), 0, layer_kind=layer_kind, device=dev)
+        ctx.set_dropout(drop)
+        if cached:
+            ctx.cache_input_aggregate(X)
+        if mask:
+            ctx.profile_enable(mask, 256)
+        dW, loss = [torch.zeros_like(w) for w in W], torch.zeros(1, device=dev)
+        dhalo = [None] + [torch.zeros(n_halo, d, device=dev) for d in dims[1:-1]]
+        for epoch in range(2):
+            ctx.train_step(3, epoch, 0.5, X, halo, labels, W, dW, dhalo, loss, 0.0)
+        torch.cuda.synchronize()
+        if mask:
+            assert ctx.profile_read()["gemm_fwd"][1] >= 2 * L  # two launches
+        A = [ctx.ws_tensor(pkg.VIEW_A, l, torch.float32).clone() for l in range(1, L + 1)]
+        out.append(A + [ctx.ws_tensor(pkg.VIEW_H, l, torch.float32).clone() for l in range(1, L + 1)])
+        ctx.close()
+    for two, one in zip(*out):
+        assert torch.isfinite(two).all() and torch.equal(two, one)
+
+
+def test_in_place_layer_keeps_two_launches():
+    """H_out on top of H_in: every row is gathered before one is overwritten."""
+    import torch
+    import paper_2203_10983_amd as pkg
+    dev = torch.device("cuda:0")
+    n, d = 700, 64
+    P = _partition(n, 6, 0, 50, np.random.default_rng(5))
+    ctx = pkg.Context(P, [d, d], 0, device=dev)
+    i32 = lambda k: torch.zeros(k, dtype=torch.int32, device=dev)  # noqa: E731
+    kept, remap, n_kept, nnz = i32(50), i32(50), i32(1), i32(1)
+    ctx.sample_boundary(1, 0, 0.5, kept, remap, n_kept)
+    csr = i32(n + 1), i32(P.nnz0), i32(n + 51), i32(P.nnz0)
+    ctx.build_sampled_csr(remap, kept, n_kept, *csr, nnz)
+    X, Xb, W = (torch.randn(k, d, device=dev) for k in (n, 50, d))
+    A, H = torch.zeros(n, d, device=dev), torch.zeros(n, d, device=dev)
+    ctx.gcn_layer_fwd(1, 0.5, X, Xb, W, A, H, True)
+    ctx.gcn_layer_fwd(1, 0.5, X, Xb, W, A, X, True)
+    assert torch.equal(X, H)
+    ctx.close()
