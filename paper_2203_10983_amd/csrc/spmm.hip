@@ -86,7 +86,9 @@ __global__ void __launch_bounds__(BLOCK ? kBlockWaves * kWave : 256, MAXCH == 1 
   // extra_share in 2^32 of the groups of 8, or on all wavefronts after their units.
   int unit = bid * kWaves + wid, end = start.n_units, step = start.extra_step;
   if (const unsigned share = start.extra_share) {
-    const int group_bits = 3 - start.log2_slices, group = bid >> group_bits, in_group = bid & ((1 << group_bits) - 1);
+    const int group_bits = 3 - start.log2_slices, in_group = bid & ((1 << group_bits) - 1);
+    int group = bid >> group_bits;
+    if ((group | 31) < start.n_groups) group = (group & ~31) | (int)(__brev(group) >> 27);
     const int before = __umulhi(group, share);  // such groups before this one
     if ((int)__umulhi(group + 1, share) != before) {
       unit = end + ((before << group_bits) + in_group) * kWaves + wid;
@@ -237,19 +239,23 @@ static hipError_t launch_spmm_vec(const SpmmArgs &a_in, int64_t extra_rows, bool
   // the wavefronts wait for the store of their first row (19 800 rows in four slices beside 52 800 segments: 110 of 640 us).
   // Dealt among the workgroups of the segments, a row to a wavefront, they go by beside the long rows (all transposed aggregates
   // of a step, us: that graph 2000 -> 1770; 25000 rows of 75 entries 255 -> 224; 90000 rows of 50 325 -> 284; 578125 rows of 22
-  // 1712 -> 1671).  Launches of short rows alone gain nothing by it: below 9 entries a row all wavefronts go on (90000 rows 414
-  // us, dealt 430; 200000 rows 802 and 856; 400000 rows 1893 and 1978), and in launches of two rounds of wavefronts or less
-  // the long rows start first (12000 rows of 110 entries, 100 floats: 57 and 60).  Four rows to a wavefront where slices make the workgroups
-  // too many (197 758 rows beside 52 800 segments in four slices: 2591 and 2427 us).  They are dealt in groups of a workgroup
-  // per XCD and slice, so that no XCD has more of them, and at a share that is no simple fraction (one in six exactly: the same
-  // shader engines had all of them, 1369 and 1565 us).
+  // 1712 -> 1671).  Launches of short rows alone gain nothing by it, the less the narrower their rows: below 13 entries a row all
+  // wavefronts go on (90000 rows of 8 entries 414 us, dealt 430; 300000 of 11.5 and 128 floats 446, 456; 60000 of 13.2 121, 101),
+  // of rows of up to 64 floats below 24 (150000 rows of 17 entries, 64 floats 176, 185; 400000 of 16 327, 334; 60000 of 25.5 64, 60),
+  // and in launches of two rounds of wavefronts or less the long rows start first (12000 rows of 110 entries, 100 floats: 57
+  // and 60).  Two rows to a wavefront where the workgroups are many and short (one row and two: 150000 rows of 25 entries
+  // beside as many short ones, 100 floats 280 and 273, 64 floats 191 and 183; 60000 109 and 115), four in slices
+  // (197 758 rows beside 52 800 segments in four slices: 2591 and 2427 us).  They are dealt in groups of a workgroup
+  // per XCD and slice, so that no XCD has more of them, at a share that is no simple fraction (one in six exactly: the same
+  // shader engines had all of them, 1369 and 1565 us), and over every 32 groups in the order of the reversed bits, because near such a fraction
+  // the same ones have all of them for hundreds of groups on end (150000 rows beside as many, 64 floats 215 -> 198, 256 floats 625 -> 565).
   const int64_t per = 8 >> ls;
   auto groups = [&](int64_t n) { return (n + per - 1) / per; };
   const int64_t unit_groups = groups((a.head.n_units + waves - 1) / waves);
-  const bool dealt = extra_rows >= 0 && avg_len >= 9 && ((int64_t)a.head.n_units << ls) >= 16384;
+  const bool dealt = extra_rows >= 0 && avg_len >= (a.d > 64 ? 13 : 24) && ((int64_t)a.head.n_units << ls) >= 16384;
   int64_t extra_groups = 0;
   if (dealt) {
-    const int rows = waves * (ls >= 2 && extra_rows >= 2 * (int64_t)a.head.n_units ? 4 : 1);
+    const int rows = waves * (ls >= 2 && extra_rows >= 2 * (int64_t)a.head.n_units ? 4 : a.head.n_units >= 100000 ? 2 : 1);
     extra_groups = groups((extra_rows + rows - 1) / rows);
     extra_groups += extra_groups / 32 + 1;  // (never none: any number is walked)
   } else if (extra_rows >= 0) {
@@ -258,6 +264,7 @@ static hipError_t launch_spmm_vec(const SpmmArgs &a_in, int64_t extra_rows, bool
   const int64_t all_groups = unit_groups + extra_groups;
   a.head.n_block_rows = block_rows ? (int32_t)(groups(a.plan.n_multi) * per) : 0;
   a.head.extra_share = dealt ? (uint32_t)((((uint64_t)extra_groups << 32) + all_groups - 1) / all_groups) : 0;
+  a.head.n_groups = (int32_t)all_groups;
   a.head.extra_step = (int32_t)((dealt ? extra_groups : all_groups) * per * waves);
   const unsigned each = (unsigned)(a.head.n_block_rows + all_groups * per);  // workgroups of a slice
   const unsigned cblocks = block_rows ? 0u : (unsigned)((a.plan.n_multi + 3) / 4);

@@ -39,7 +39,7 @@ struct SpmmArgs {
     int32_t n_block_rows;      // BLOCK kernels: workgroups in front, of which the first n_multi own a multi-segment row of the plan each
     uint32_t extra_share;      // the *n_extra_dev further rows: share of the workgroups that are theirs alone, in 2^32 (0: none are)
     int32_t extra_step;        // wavefronts that share these rows
-    int32_t unused;
+    int32_t n_groups;          // all groups, theirs and the units'
   } head;
   const int32_t *n_extra_dev;  // nullable: *n_extra_dev further single-segment rows follow (kept boundary)
   const int2 *units;

@@ -1,5 +1,5 @@
-"""Aggregates whose XCDs take the feature slices in turn, with the kept boundary rows dealt among the inner ones (one or four to
-a wavefront, or none kept at all), against fp64.
+"""Aggregates whose XCDs take the feature slices in turn, with the kept boundary rows dealt among the inner ones (one, two or
+four to a wavefront, or none kept at all), against fp64.
 
 Cliques with self-loops, large and many enough for the launch to take turns (1 250 000 entries), each boundary node next to a
 few inner ones; degrees count the entries, so that the inner part of A H0 is a clique sum."""
@@ -30,7 +30,7 @@ def _partition(cliques, size, n_halo, rng):
 
 
 @pytest.mark.parametrize("cliques,size,d,n_halo,p", [(20, 257, 256, 1, 1.0), (20, 257, 512, 3001, 0.5), (79, 128, 128, 5000, 0.3),
-                                                     (79, 128, 200, 700, 1.0), (5, 515, 256, 16000, 1.0), (79, 128, 128, 300, 0.0)])
+                                                     (79, 128, 200, 700, 1.0), (5, 515, 256, 16000, 1.0), (79, 128, 128, 300, 0.0), (6300, 16, 128, 20000, 0.5)])
 def test_aggregate_in_turns(cliques, size, d, n_halo, p):
     import torch
     import paper_2203_10983_amd as pkg
