@@ -155,6 +155,18 @@ bool tile_layer(const bns_ctx *ctx, int layer) {
          tile_layer_supported(plan, ctx->dims[layer - 1], ctx->dims[layer]);
 }
 
+// Its backward pass, likewise: the transposed aggregate (at the output width, in rows of gather_stride floats), then the product?
+// rows: inner ones and expected boundary rows.  Here the two launches keep up sooner (steps, two per layer and one, us: 64-16-8
+// 500 rows 38 / 36, 64-128-128-47 700 rows 61 / 57, 1500 of 15 entries 84 / 81, 2500 91 / 90, 5000 98 / 100; mean aggregator
+// 64-64-128-8 1500 rows 79 / 76, 5000 107 / 107; with rows of several segments 64-128-128-47, 1500 rows of 15 entries 103 / 101, of
+// 45 115 / 118).
+constexpr int kTileBwdMaxRows = 3072, kTileBwdMaxSegments = 3, kTileBwdMaxLen = 32;
+bool tile_layer_bwd(const bns_ctx *ctx, int layer, int64_t rows) {
+  const SegPlan &plan = ctx->ws.plan_b;
+  return rows <= kTileBwdMaxRows && (plan.n_multi == 0 || (plan.max_seg <= kTileBwdMaxSegments && plan.avg_len <= kTileBwdMaxLen)) &&
+         tile_layer_bwd_supported(gather_stride(ctx->dims[layer - 1], ctx->dims[layer]), ctx->dims[layer - 1], ctx->layer_kind == 1);
+}
+
 bool valid_desc(const bns_partition_desc *p, const bns_model_desc *m) {
   if (!p || !m || !m->dims) return false;
   if (p->n_in < 1 || p->n_halo < 0 || p->nnz0 < p->n_in || p->e_in < p->n_in || p->e_bd < 0) return false;
@@ -471,10 +483,10 @@ bns_status layer_fwd_impl(bns_ctx *ctx, int layer, double p, const float *H_in, 
 }
 
 // Does the backward pass of `layer` gather its dZ at the output width, in padded rows?
-bool pads_gradient(const bns_ctx *ctx, int layer, bool update_first, bool input_gradient) {
+bool pads_gradient(const bns_ctx *ctx, int layer, double p, bool update_first, bool input_gradient) {
   const int d_in = ctx->dims[layer - 1], d_out = ctx->dims[layer];
   if (gather_stride(d_in, d_out) == d_out) return false;
-  return update_first || (ctx->layer_kind == 0 && input_gradient && d_out < d_in);
+  return update_first || ((ctx->layer_kind == 0 || tile_layer_bwd(ctx, layer, ctx->part.n_in + (int64_t)expected_kept(ctx, p))) && input_gradient && d_out < d_in);
 }
 
 // The weight gradients of several layers, to be run together.
@@ -594,6 +606,24 @@ bns_status layer_bwd_impl(bns_ctx *ctx, int layer, double p, const float *dZ, co
   if (!batch) {
     const bns_status st = run_batch(ctx, &own, TnLoss{}, s);
     if (st != BNS_OK) return st;
+  }
+  const int ld_g = gather_stride(d_in, d_out);
+  if (dH_in && tile_layer_bwd(ctx, layer, n_in + (dhalo ? (int64_t)expected_kept(ctx, p) : 0)) && !timed(ctx, BNS_PHASE_SPMM_BWD) && !timed(ctx, BNS_PHASE_GEMM_DA) &&
+      (ld_g == d_out || dz_padded || ctx->layer_kind == 0)) {
+    const size_t n_w = (size_t)(ctx->layer_kind == 1 ? 2 : 1) * d_in * d_out, n_h = (size_t)n_in * d_in;
+    const auto meets = [&](const float *out, size_t n) {
+      return overlap(out, n, dZ, (size_t)n_in * d_out) || overlap(out, n, W, n_w) || (mask_src && overlap(out, n, mask_src, n_h));
+    };
+    if (!meets(dH_in, n_h) && !(dhalo && meets(dhalo, (size_t)B * d_in))) {
+      if (ld_g != d_out && !dz_padded) BNS_TRY("pad_rows", pad_rows(n_in, d_out, ld_g, dZ, ctx->ws.G2, s));
+      const bool gcn = ctx->layer_kind == 0;
+      BNS_TRY("tile_layer_bwd", tile_layer_bwd(ctx->ws.plan_b, n_in, B, ld_g, d_in, d_out, ctx->cur_t_row_ptr, ctx->cur_t_col_idx,
+                                               ctx->cur_kept, ctx->cur_n_kept, ctx->ws.w_bwd, ctx->ws.w_halo, ctx->part.halo_ptr,
+                                               gcn ? ctx->ws.dis_in : nullptr, gcn ? ctx->ws.dis_halo : nullptr, halo_scale(p),
+                                               ld_g != d_out ? ctx->ws.G2 : dZ, W, Wb, mask_src, ms, !gcn, ctx->ws.spmm_partials,
+                                               dH_in, dhalo, expected_kept(ctx, p), s));
+      return BNS_OK;
+    }
   }
   if (ctx->layer_kind == 1) {
     if (dH_in) {
@@ -914,7 +944,7 @@ static bns_status train_step_impl(bns_ctx *ctx, uint64_t seed, uint32_t epoch, c
   const int C = ctx->dims[L];
   TnLoss loss_sum{w.loss_partials, 0, loss};
   // where the last layer's backward pass gathers padded rows of dZ, the loss leaves them beside dZ
-  const bool pad_last = pads_gradient(ctx, L, layer_plan(ctx, L, X) == BNS_LAYER_UPDATE_FIRST, L > 1);
+  const bool pad_last = pads_gradient(ctx, L, p, layer_plan(ctx, L, X) == BNS_LAYER_UPDATE_FIRST, L > 1);
   const int ld = gather_stride(ctx->dims[L - 1], C);
   float *dZ_pad = pad_last ? w.G2 : nullptr;
   {

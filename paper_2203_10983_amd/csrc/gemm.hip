@@ -55,21 +55,10 @@ struct RowsArgs {
 
 enum RowsEpilogue { kPlain = 0, kMask = 1, kPair = 2 };
 
-// An infinite operand has no split (its other pieces are NaN), nor has one beyond 3.389e38, which rounds to an infinite
-// piece, and a product near the top of the range can overflow in its first piece alone.  All of these end in a result that
-// is not finite, and such a result is formed once more as the plain fp32 sum, so that infinities and NaN come out as from the operands
-// themselves.  Looking costs an instruction per result and tile; a product all of whose results are NaN takes some 50 to 80
-// times as long (89625 x 512 x 512: 11 and 20 ms), one infinite element a few times.
-__device__ __forceinline__ float nonfinite_seed(float z, const f32x4 &v) {  // z stays 0 while all values are finite
-#pragma unroll
-  for (int e = 0; e < 4; ++e) z = fmaf(v[e], 0.f, z);
-  return z;
-}
 // The value of the lane whose number differs in the last bit.
 __device__ __forceinline__ float quad_swap(float x) {
   return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0xb1, 0xf, 0xf, true));  // quad_perm:[1,0,3,2]
 }
-__device__ __forceinline__ bool is_finite(float x) { return fabsf(x) <= 3.40282347e38f; }
 
 template <int R, int NC, int EPI>
 __global__ void __launch_bounds__(256, R * NC > 8 || NC > 6 ? 3 : 4) gemm_rows_kernel(const RowsArgs a) {

@@ -214,6 +214,16 @@ hipError_t tile_layer_fwd(const SegPlan &plan, int32_t n_in, int32_t d_in, int32
                           const float *H_in, const float *Hu, float *partials, float *A, const SpmmRowPart &part, const float *W,
                           float *H_out, bool relu, const Dropout &drop, bool sage, bool concat, hipStream_t s);
 
+// dH[u,:] = alpha * (P^T dZ [+ dZ of u (sage: by the second half of W)]) W^T, zeroed where mask <= 0 (nullable), and for the kept
+// boundary nodes (dhalo nullable) without alpha and mask: as spmm_bwd (its arguments; dZ has rows of d floats, zeros from d_out
+// on) and gemm_rows (on W packed as one matrix), the aggregate first.  Neither dH nor dhalo may share memory with dZ, W or mask.
+bool tile_layer_bwd_supported(int32_t d, int32_t d_in, bool sage);
+hipError_t tile_layer_bwd(const SegPlan &plan, int32_t n_in, int32_t n_halo, int32_t d, int32_t d_in, int32_t d_out, const int32_t *t_row_ptr,
+                          const int32_t *t_col_idx, const int32_t *kept_ids, const int32_t *n_kept, const float *w_in, const float *w_halo,
+                          const int32_t *halo_ptr, const float *row_scale, const float *dis_halo, float s_halo, const float *dZ,
+                          const float *W, const void *Bp, const float *mask, float alpha, bool sage, float *partials, float *dH, float *dhalo,
+                          int32_t expected_halo, hipStream_t s);
+
 // C[M,N] = [A | A2] B (+ the previous C if accumulate), B [K,N] packed; then, if relu, max(., 0) and dropout (when
 // drop.scale != 0).  A, A2 [M, lda]: the depth below a_split (a multiple of 16) is A's, the rest A2's (nullable).
 // pad: the columns N..ldc-1 are set to zero (ldc at most N rounded up to a multiple of 4; not with relu or

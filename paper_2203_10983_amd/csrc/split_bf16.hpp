@@ -17,7 +17,7 @@
 //
 // v_mfma_f32_16x16x32_bf16 runs at sixteen times the rate of the fp32 instruction, so six of them
 // take 6/16 of its time.  Operands that are not finite, or round to an infinite hi (above 3.389e38), have no split:
-// gemm.hip forms their results once more without one.
+// their results are formed once more without one.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -81,6 +81,18 @@ __device__ __forceinline__ void mfma_split(f32x4 (&t)[R], const Frag3 &x, const 
     for (int r = 0; r < R; ++r)
       t[r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x.p[px[i]], y[r].p[py[i]], t[r], 0, 0, 0);
 }
+
+// An infinite operand has no split (its other pieces are NaN), nor has one beyond 3.389e38, which rounds to an infinite
+// piece, and a product near the top of the range can overflow in its first piece alone.  All of these end in a result that
+// is not finite, and such a result is formed once more as the plain fp32 sum, so that infinities and NaN come out as from the operands
+// themselves.  Looking costs an instruction per result and tile; a product all of whose results are NaN takes some 50 to 80
+// times as long (89625 x 512 x 512: 11 and 20 ms), one infinite element a few times.
+__device__ __forceinline__ float nonfinite_seed(float z, const f32x4 &v) {  // z stays 0 while all values are finite
+#pragma unroll
+  for (int e = 0; e < 4; ++e) z = fmaf(v[e], 0.f, z);
+  return z;
+}
+__device__ __forceinline__ bool is_finite(float x) { return fabsf(x) <= 3.40282347e38f; }
 
 // One 16-byte-per-lane copy from global memory straight into LDS (lane i lands at lds + 16 i; both
 // arguments as the whole wavefront sees them).  Written as assembly so that the compiler does not

@@ -1,4 +1,5 @@
-// A layer of a small partition in one launch: aggregate (Eq. 1), then update (Eq. 2) of a few rows in one workgroup.
+// A layer of a small partition in one launch, forward: aggregate (Eq. 1), then update (Eq. 2) of a few rows in one workgroup; and
+// backward: transposed aggregate, then product with W^T.
 //
 // On some thousand rows neither step fills the chip: a launch is 2 to 3 us of starting and draining beside about 2 us of
 // dependent reads, whatever its size.  A workgroup of 8 wavefronts owns a tile of 8 or 16 rows, gathers them into LDS with the
@@ -29,6 +30,71 @@ struct TileArgs {
 };
 
 typedef float f32x2u __attribute__((ext_vector_type(2), aligned(4)));
+
+// The rows row0 .. + rows of the aggregate, in the order of sums of spmm_kernel: put(row, piece, sums) on the lanes that hold
+// them.  Rows from a.n_split on are kept boundary rows of a transposed aggregate.
+template <int LPR, typename Put>
+__device__ __forceinline__ void gather_tile(const SpmmArgs &a, int row0, int rows, Put put) {
+  using V = typename Vec<4>::T;
+  const int lane = lane_id(), wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int g = lane / LPR, sl = lane % LPR;
+  const int d = a.d, nvec = d / 4;
+  auto entries = [&](int row, int &e0, int &e1) {
+    const int2 ee = scalar_load_pair(a.row_ptr, row);
+    const InnerWeights iw = inner_weights(a, row, ee.x, ee.y);
+    e0 = ee.x;
+    e1 = ee.y;
+    if (a.row_skip) e0 += scalar_load(a.row_skip, row);
+    if (a.row_take) e1 = e0 + scalar_load(a.row_take, row);
+    return iw;
+  };
+  float acc[1][4];
+  if (a.plan.n_multi == 0 || row0 >= a.n_split) {
+    for (int r = wid; r < rows; r += kTileWaves) {
+      int e0, e1;
+      const InnerWeights iw = entries(row0 + r, e0, e1);
+      gather_segment<4, 1, LPR>(a, row0 + r, iw, e0, e1, 0, nvec, acc);
+      if (g == 0) put(row0 + r, sl, acc);
+    }
+    return;
+  }
+  // a wavefront per segment; the sums of rows of several segments are added in ascending order
+  const int end = scalar_load(a.plan.seg_ptr, row0 + rows);
+  for (int u = scalar_load(a.plan.seg_ptr, row0) + wid; u < end; u += kTileWaves) {
+    const int2 unit = scalar_load(a.plan.seg_unit, u);
+    const int row = unit.x, slot = unit.y;
+    int e0, e1;
+    const InnerWeights iw = entries(row, e0, e1);
+    if (slot >= 0) {
+      const int seg = slot - scalar_load(a.plan.part_ptr, row);
+      const int2 ss = scalar_load_pair(a.plan.seg_ptr, row);
+      const int chunk = (e1 - e0 + (ss.y - ss.x) - 1) / (ss.y - ss.x);
+      e0 = min(e1, e0 + seg * chunk);
+      e1 = min(e1, e0 + chunk);
+    }
+    gather_segment<4, 1, LPR>(a, row, iw, e0, e1, 0, nvec, acc);
+    if (g != 0) continue;
+    if (slot < 0) put(row, sl, acc);
+    else if (sl < nvec) reinterpret_cast<V *>(a.partials + (size_t)slot * d)[sl] = V{acc[0][0], acc[0][1], acc[0][2], acc[0][3]};
+  }
+  __syncthreads();
+  for (int r = wid; r < rows; r += kTileWaves) {
+    const int row = row0 + r;
+    const int2 ss = scalar_load_pair(a.plan.seg_ptr, row);
+    const int nseg = ss.y - ss.x;
+    if (nseg <= 1) continue;
+    const float *part = a.partials + (size_t)scalar_load(a.plan.part_ptr, row) * d;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) acc[0][i] = 0.f;
+    if (lane < nvec)
+      for (int s = 0; s < nseg; ++s) {
+        const V x = reinterpret_cast<const V *>(part + (size_t)s * d)[lane];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[0][i] += x[i];
+      }
+    put(row, lane, acc);
+  }
+}
 
 template <int LPR, int VW, bool SAGE>
 __global__ void __launch_bounds__(kTileWaves * kWave, 4) tile_layer_kernel(const TileArgs f) {
@@ -67,9 +133,7 @@ __global__ void __launch_bounds__(kTileWaves * kWave, 4) tile_layer_kernel(const
     }
   }
 
-  // ---- aggregate ----
-  const int g = lane / LPR, sl = lane % LPR;
-  auto put_row = [&](int row, int piece, const float (&acc)[1][4]) {  // as finish_row, and into the tile
+  gather_tile<LPR>(a, row0, rows, [&](int row, int piece, const float (&acc)[1][4]) {  // as finish_row, and into the tile
     const float scale = a.out_scale0 ? scalar_load(a.out_scale0, row) : 1.f;
     if (piece >= nvec) return;
     V o;
@@ -79,61 +143,7 @@ __global__ void __launch_bounds__(kTileWaves * kWave, 4) tile_layer_kernel(const
     o *= scale;
     *reinterpret_cast<V *>(&As[0][(row - row0) * kTileLd + piece * 4]) = o;
     reinterpret_cast<V *>(a.out0 + (size_t)row * d)[piece] = o;
-  };
-  auto entries = [&](int row, int &e0, int &e1) {
-    const int2 ee = scalar_load_pair(a.row_ptr, row);
-    const InnerWeights iw = inner_weights(a, row, ee.x, ee.y);
-    e0 = ee.x;
-    e1 = ee.y;
-    if (a.row_skip) e0 += scalar_load(a.row_skip, row);
-    if (a.row_take) e1 = e0 + scalar_load(a.row_take, row);
-    return iw;
-  };
-  float acc[1][4];
-  if (a.plan.n_multi == 0) {
-    for (int r = wid; r < rows; r += kTileWaves) {
-      int e0, e1;
-      const InnerWeights iw = entries(row0 + r, e0, e1);
-      gather_segment<4, 1, LPR>(a, row0 + r, iw, e0, e1, 0, nvec, acc);
-      if (g == 0) put_row(row0 + r, sl, acc);
-    }
-  } else {  // a wavefront per segment; the sums of rows of several segments are added in ascending order
-    const int end = scalar_load(a.plan.seg_ptr, row0 + rows);
-    for (int u = scalar_load(a.plan.seg_ptr, row0) + wid; u < end; u += kTileWaves) {
-      const int2 unit = scalar_load(a.plan.seg_unit, u);
-      const int row = unit.x, slot = unit.y;
-      int e0, e1;
-      const InnerWeights iw = entries(row, e0, e1);
-      if (slot >= 0) {
-        const int seg = slot - scalar_load(a.plan.part_ptr, row);
-        const int2 ss = scalar_load_pair(a.plan.seg_ptr, row);
-        const int chunk = (e1 - e0 + (ss.y - ss.x) - 1) / (ss.y - ss.x);
-        e0 = min(e1, e0 + seg * chunk);
-        e1 = min(e1, e0 + chunk);
-      }
-      gather_segment<4, 1, LPR>(a, row, iw, e0, e1, 0, nvec, acc);
-      if (g != 0) continue;
-      if (slot < 0) put_row(row, sl, acc);
-      else if (sl < nvec) reinterpret_cast<V *>(a.partials + (size_t)slot * d)[sl] = V{acc[0][0], acc[0][1], acc[0][2], acc[0][3]};
-    }
-    __syncthreads();
-    for (int r = wid; r < rows; r += kTileWaves) {
-      const int row = row0 + r;
-      const int2 ss = scalar_load_pair(a.plan.seg_ptr, row);
-      const int nseg = ss.y - ss.x;
-      if (nseg <= 1) continue;
-      const float *part = a.partials + (size_t)scalar_load(a.plan.part_ptr, row) * d;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) acc[0][i] = 0.f;
-      if (lane < nvec)
-        for (int s = 0; s < nseg; ++s) {
-          const V x = reinterpret_cast<const V *>(part + (size_t)s * d)[lane];
-#pragma unroll
-          for (int i = 0; i < 4; ++i) acc[0][i] += x[i];
-        }
-      put_row(row, lane, acc);
-    }
-  }
+  });
   __syncthreads();
   if (n0 >= N) return;
 
@@ -185,6 +195,140 @@ __global__ void __launch_bounds__(kTileWaves * kWave, 4) tile_layer_kernel(const
   }
 }
 
+// The gradient of the layer's input: dH = mask(P^T dZ W^T), the rows of the inner nodes and, on the workgroups behind theirs,
+// those of the kept boundary nodes.  The transposed aggregate comes first whatever the widths: its rows stay in LDS.  The product is
+// that of gemm_rows_kernel, on the same packed weights (of a chain of fp32 instructions the error was 1.1 to 1.9 times that of the split).
+struct TileBwdArgs {
+  SpmmArgs sp;          // src0: dZ with rows of d floats, of which d_out count (the others are zero); out_scale0, s_halo, ...
+  const float *W;       // [d_in, d_out]; SAGE: [2 d_in, d_out]
+  const void *Bp;       // the same, packed and split
+  const float *mask;    // nullable: [n_in, d_in]
+  float *dH, *dhalo;    // [n_in, d_in], [.., d_in]
+  int32_t d_in, d_out, rows, n_tiles;  // tiles of inner rows
+  float alpha;          // of the inner rows
+};
+
+template <int LPR, bool SAGE>
+__global__ void __launch_bounds__(kTileWaves * kWave, 4) tile_layer_bwd_kernel(const TileBwdArgs f) {
+  using V = typename Vec<4>::T;
+  constexpr int S = (LPR * 4 + 31) / 32;  // depth steps at most
+  __shared__ __attribute__((aligned(16))) float As[SAGE ? 2 : 1][kTileRows * kTileLd];
+  const SpmmArgs &a = f.sp;
+  const int lane = lane_id(), wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int d = a.d, nvec = d / 4, N = f.d_in, K = f.d_out, steps = (K + 31) / 32;
+  const int l16 = lane & 15, g4 = lane >> 4;
+  const int n0 = wid * 16;  // the wavefront's columns; a lane ends up with n0 + 4 (lane / 16) .. + 3 of row lane % 16
+  const int T = ((SAGE ? 2 * N : N) + 15) / 16;
+  // Column `from` + n0 + lane % 16 of the packed weights (N % 4 == 0 where `from` is not 0), zeros behind the last one.  Those of the
+  // first step are asked for before the gather, the others behind it: more of them before it hold up its first reads (step of
+  // 64-100-100-47, mean aggregator, 1500 rows: 79.1 us, with two 80.8, four 81.7).
+  auto load_w = [&](bf16x8 (&w)[S][3], int from, int s0, int s1) {
+    if (n0 >= N) return;
+    const int col = min(from + n0 + l16, T * 16 - 1);
+    const char *p = static_cast<const char *>(f.Bp) + (size_t)(col / 16) * kFragSet + (g4 * 16 + col % 16) * 16;
+#pragma unroll
+    for (int s = 0; s < S; ++s)
+      if (s >= s0 && s < s1 && s < steps)
+#pragma unroll
+        for (int i = 0; i < 3; ++i) w[s][i] = *reinterpret_cast<const bf16x8 *>(p + (size_t)s * T * kFragSet + i * kFragBytes);
+  };
+  const int n_kept = a.n_extra_dev ? scalar_load(a.n_extra_dev, 0) : 0;
+  const bool halo = (int)blockIdx.x >= f.n_tiles;
+  for (int tile = halo ? (int)blockIdx.x - f.n_tiles : (int)blockIdx.x;; tile += (int)gridDim.x - f.n_tiles) {
+    const int r0 = tile * f.rows;  // of the inner or of the kept boundary rows
+    if (r0 >= (halo ? n_kept : a.n_split)) return;
+    const int rows = min(f.rows, (halo ? n_kept : a.n_split) - r0), row0 = halo ? a.n_split + r0 : r0;
+    bf16x8 w[S][3];
+    load_w(w, 0, 0, 1);
+    const bool own = SAGE && !halo;
+    const int pad = 8 * steps - nvec;  // pieces behind a row up to the depth of the product
+    for (int idx = threadIdx.x; idx < kTileRows * pad; idx += kTileWaves * kWave)
+#pragma unroll
+      for (int t = 0; t < (SAGE ? 2 : 1); ++t)
+        *reinterpret_cast<V *>(&As[t][idx / pad * kTileLd + (nvec + idx % pad) * 4]) = V{0.f, 0.f, 0.f, 0.f};
+    if (own)
+      for (int idx = threadIdx.x; idx < rows * nvec; idx += kTileWaves * kWave) {
+        const int r = idx / nvec, c4 = idx - r * nvec;
+        *reinterpret_cast<V *>(&As[SAGE ? 1 : 0][r * kTileLd + c4 * 4]) = reinterpret_cast<const V *>(a.src0 + (size_t)(row0 + r) * d)[c4];
+      }
+    const int col = n0 + 4 * g4, left = N - col;
+    const bool stores = l16 < rows && left > 0;
+    const size_t at = (size_t)(r0 + l16) * N + col;
+    f32x4 mask = {1.f, 1.f, 1.f, 1.f};
+    if (f.mask && !halo && stores) {
+      if (left >= 4) mask = *reinterpret_cast<const f32x4u *>(f.mask + at);
+      else
+#pragma unroll
+        for (int e = 0; e < 3; ++e)
+          if (e < left) mask[e] = f.mask[at + e];
+    }
+    gather_tile<LPR>(a, row0, rows, [&](int row, int piece, const float (&acc)[1][4]) {
+      float scale = 1.f;
+      if (!halo) {
+        if (a.out_scale0) scale = scalar_load(a.out_scale0, row);
+      } else {
+        scale = a.dis_halo ? a.s_halo * scalar_load(a.dis_halo, scalar_load(a.kept_ids, row - a.n_split)) : a.s_halo;
+      }
+      if (piece < nvec) *reinterpret_cast<V *>(&As[0][(row - row0) * kTileLd + piece * 4]) = V{acc[0][0], acc[0][1], acc[0][2], acc[0][3]} * scale;
+    });
+    load_w(w, 0, 1, S);
+    __syncthreads();
+    if (n0 < N) {
+      f32x4 v = {0.f, 0.f, 0.f, 0.f};
+      auto product = [&](const float *tile_rows, int from) {
+        const float *as = tile_rows + l16 * kTileLd + 4 * g4;
+        f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < S; ++s)
+          if (s < steps) {
+            const Frag3 fa[1] = {split8(*reinterpret_cast<const f32x4 *>(as + 32 * s), *reinterpret_cast<const f32x4 *>(as + 32 * s + 16))};
+            const Frag3 fb = {{w[s][0], w[s][1], w[s][2]}};
+            f32x4 part[1];
+            mfma_split<1>(part, fb, fa);
+            sum += part[0];
+            if (from == 0 && own) load_w(w, N, s, s + 1);  // the other half's
+          }
+        v += (from + col) / 16 & 1 ? -sum : sum;  // odd tiles are packed negated
+      };
+      product(As[0], 0);
+      if (own) {
+        product(As[SAGE ? 1 : 0], N);
+      }
+      if (stores && nonfinite_seed(0.f, v) != 0.f) {  // (NaN)
+#pragma unroll 1
+        for (int e = 0; e < 4; ++e) {
+          if (e < left && !is_finite(v[0])) {
+            float x = 0.f;
+#pragma unroll 1
+            for (int h = 0; h < (own ? 2 : 1); ++h)
+#pragma unroll 1
+              for (int k = 0; k < K; ++k) x = fmaf(As[SAGE ? h : 0][l16 * kTileLd + k], f.W[((size_t)h * N + col + e) * K + k], x);
+            v[0] = x;
+          }
+          v = f32x4{v[1], v[2], v[3], v[0]};
+        }
+      }
+      if (stores) {
+        if (!halo)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[e] = f.mask ? mask[e] > 0.f ? v[e] * f.alpha : 0.f : v[e] * f.alpha;
+        float *const to = (halo ? f.dhalo : f.dH) + at;
+        if (left >= 4) *reinterpret_cast<f32x4u *>(to) = v;
+        else
+#pragma unroll
+          for (int e = 0; e < 3; ++e)
+            if (e < left) to[e] = v[e];
+      }
+    }
+    if (!halo) return;
+    __syncthreads();  // the tile is read before it is filled again
+  }
+}
+
+// Half a tile where whole ones are fewer than the compute units: a row per wavefront (steps of 128-128-128-47, forward layers in tiles of
+// 16 and 8, us: 1000 rows 66 / 64, of 45 entries 93 / 84; 3000 92 / 91; 4500 98 / 106).
+int tile_rows(int32_t n) { return n <= 3584 ? kTileRows / 2 : kTileRows; }
+
 }  // namespace
 
 bool tile_layer_supported(const SegPlan &plan, int32_t d_in, int32_t d_out) {
@@ -206,9 +350,7 @@ hipError_t tile_layer_fwd(const SegPlan &plan, int32_t n_in, int32_t d_in, int32
   f.H_self = sage ? H_in : nullptr;
   f.H_out = H_out;
   f.d_out = d_out;
-  // Half a tile where whole ones are fewer than the compute units: a row per wavefront (steps of 128-128-128-47, tiles of
-  // 16 and 8, us: 1000 rows 66 / 64, of 45 entries 93 / 84; 3000 92 / 91; 4500 98 / 106).
-  f.rows = n_in <= 3584 ? kTileRows / 2 : kTileRows;
+  f.rows = tile_rows(n_in);
   f.relu = relu;
   f.concat = concat;
   f.drop = drop;
@@ -223,6 +365,50 @@ hipError_t tile_layer_fwd(const SegPlan &plan, int32_t n_in, int32_t d_in, int32
   else if (d_in > 32) { if (wide) BNS_TILE(16, 2); else BNS_TILE(16, 1); }
   else if (d_in > 16) { if (wide) BNS_TILE(8, 2); else BNS_TILE(8, 1); }
   else { if (wide) BNS_TILE(4, 2); else BNS_TILE(4, 1); }
+#undef BNS_TILE
+  return hipGetLastError();
+}
+
+bool tile_layer_bwd_supported(int32_t d, int32_t d_in, bool sage) {
+  return d % 4 == 0 && d > 4 && d <= kTileDepth && d_in <= 16 * kTileWaves && (!sage || d_in % 4 == 0);
+}
+
+hipError_t tile_layer_bwd(const SegPlan &plan, int32_t n_in, int32_t n_halo, int32_t d, int32_t d_in, int32_t d_out, const int32_t *t_row_ptr,
+                          const int32_t *t_col_idx, const int32_t *kept_ids, const int32_t *n_kept, const float *w_in, const float *w_halo,
+                          const int32_t *halo_ptr, const float *row_scale, const float *dis_halo, float s_halo, const float *dZ,
+                          const float *W, const void *Bp, const float *mask, float alpha, bool sage, float *partials, float *dH, float *dhalo,
+                          int32_t expected_halo, hipStream_t s) {
+  if (!tile_layer_bwd_supported(d, d_in, sage) || d_out > d || d_out < 1) return hipErrorInvalidValue;
+  if (n_in <= 0) return hipSuccess;
+  const bool halo_rows = dhalo && n_halo > 0;
+  TileBwdArgs f{};
+  SpmmArgs &a = f.sp;
+  a.plan = plan; a.n_extra_dev = halo_rows ? n_kept : nullptr; a.d = a.d_store = d;
+  a.row_ptr = t_row_ptr; a.col_idx = t_col_idx; a.n_split = n_in;
+  a.src0 = dZ; a.w_in = w_in; a.w_ptr = t_row_ptr; a.w_halo = w_halo; a.halo_ptr = halo_ptr; a.partials = partials;
+  a.out_scale0 = row_scale; a.kept_ids = kept_ids; a.dis_halo = dis_halo; a.s_halo = s_halo; a.skip_self = sage;
+  f.W = W;
+  f.Bp = Bp;
+  f.mask = mask;
+  f.dH = dH;
+  f.dhalo = dhalo;
+  f.d_in = d_in;
+  f.d_out = d_out;
+  f.rows = tile_rows(n_in + (halo_rows ? expected_halo : 0));
+  f.n_tiles = (n_in + f.rows - 1) / f.rows;
+  f.alpha = alpha;
+  // (any number of boundary rows is walked)
+  const unsigned blocks = (unsigned)(f.n_tiles + (halo_rows ? expected_halo / f.rows + 1 : 0));
+#define BNS_TILE(LPR)                                                                           \
+  do {                                                                                          \
+    if (sage) tile_layer_bwd_kernel<LPR, true><<<blocks, kTileWaves * kWave, 0, s>>>(f);       \
+    else tile_layer_bwd_kernel<LPR, false><<<blocks, kTileWaves * kWave, 0, s>>>(f);           \
+  } while (0)
+  if (d > 64) BNS_TILE(32);
+  else if (d > 32) BNS_TILE(16);
+  else if (d > 16) BNS_TILE(8);
+  else if (d > 8) BNS_TILE(4);
+  else BNS_TILE(2);
 #undef BNS_TILE
   return hipGetLastError();
 }

@@ -1,5 +1,7 @@
-"""Layers of small partitions, aggregate and update in one launch, against the two launches that run while their phases are
-timed: the same sums in the same order, so the same bits.  Random graphs with hubs of up to eight segments of 256 entries."""
+"""Layers of small partitions, aggregate and product in one launch, against the two launches that run while their phases are
+timed.  Forward, and backward where the output is the narrower side, the same sums in the same order, so the same bits; else the
+transposed aggregate has changed places with the product, and both results lie within a few roundings (2^-24) of the exact one.
+Random graphs with hubs of up to eight segments of 256 entries."""
 import types
 
 import numpy as np
@@ -7,7 +9,7 @@ import pytest
 
 pytestmark = pytest.mark.gpu
 
-TIMED = (1 << 3) | (1 << 4)  # aggregate, update
+TIMED = (1 << 3) | (1 << 4) | (1 << 7) | (1 << 8)  # aggregate, update, and their backward passes
 
 
 def _partition(n, deg, hub, n_halo, rng):
@@ -34,7 +36,9 @@ def _partition(n, deg, hub, n_halo, rng):
 @pytest.mark.parametrize("n,deg,hub,dims,layer_kind,drop,cached", [
     (1, 0, 0, (12, 16, 1), 0, 0.0, False), (7, 2, 0, (64, 16, 8), 0, 0.0, False), (17, 3, 0, (16, 129, 12, 2), 1, 0.3, False),
     (500, 5, 0, (64, 172, 8), 0, 0.5, True), (600, 8, 560, (128, 128, 47), 0, 0.0, False), (2100, 4, 2048, (100, 128, 17), 1, 0.0, True),
-    (3584, 20, 300, (32, 256, 16), 1, 0.3, False), (3585, 20, 0, (60, 33, 9), 0, 0.0, False), (8192, 3, 0, (36, 128, 20, 5), 1, 0.0, False)])
+    (3584, 20, 300, (32, 256, 16), 1, 0.3, False), (3585, 20, 0, (60, 33, 9), 0, 0.0, False), (8192, 3, 0, (36, 128, 20, 5), 1, 0.0, False),
+    (1, 0, 0, (8, 8, 8), 0, 0.0, False), (9, 2, 0, (5, 33, 12), 0, 0.0, False), (700, 12, 600, (16, 100, 100, 47), 1, 0.3, False),
+    (700, 12, 600, (64, 128, 36, 12), 0, 0.3, False), (2600, 4, 0, (12, 128, 128, 128), 1, 0.0, False)])
 def test_one_launch_equals_two(n, deg, hub, dims, layer_kind, drop, cached):
     import torch
     import paper_2203_10983_amd as pkg
@@ -54,7 +58,7 @@ def test_one_launch_equals_two(n, deg, hub, dims, layer_kind, drop, cached):
         if cached:
             ctx.cache_input_aggregate(X)
         if mask:
-            ctx.profile_enable(mask, 256)
+            ctx.profile_enable(mask, 512)
         dW, loss = [torch.zeros_like(w) for w in W], torch.zeros(1, device=dev)
         dhalo = [None] + [torch.zeros(n_halo, d, device=dev) for d in dims[1:-1]]
         for epoch in range(2):
@@ -63,10 +67,17 @@ def test_one_launch_equals_two(n, deg, hub, dims, layer_kind, drop, cached):
         if mask:
             assert ctx.profile_read()["gemm_fwd"][1] >= 2 * L  # two launches
         A = [ctx.ws_tensor(pkg.VIEW_A, l, torch.float32).clone() for l in range(1, L + 1)]
-        out.append(A + [ctx.ws_tensor(pkg.VIEW_H, l, torch.float32).clone() for l in range(1, L + 1)])
+        dZ = [ctx.ws_tensor(pkg.VIEW_DZ, l, torch.float32).clone() for l in range(1, L)]
+        out.append((A + [ctx.ws_tensor(pkg.VIEW_H, l, torch.float32).clone() for l in range(1, L + 1)], dZ + dhalo[1:]))
         ctx.close()
-    for two, one in zip(*out):
+    for two, one in zip(out[0][0], out[1][0]):
         assert torch.isfinite(two).all() and torch.equal(two, one)
+    narrowing = layer_kind == 0 and all(b < a for a, b in zip(dims[1:], dims[2:]))
+    for two, one in zip(out[0][1], out[1][1]):
+        if narrowing:
+            assert torch.equal(two, one)
+        else:  # six roundings of the split product and two of the aggregate's on either side, through up to two layers
+            assert (two.double() - one.double()).norm() <= 32 * 2.0 ** -24 * two.double().norm()
 
 
 def test_in_place_layer_keeps_two_launches():
@@ -88,3 +99,33 @@ def test_in_place_layer_keeps_two_launches():
     ctx.gcn_layer_fwd(1, 0.5, X, Xb, W, A, X, True)
     assert torch.equal(X, H)
     ctx.close()
+
+
+def test_backward_with_infinite_gradients():
+    """Products that are not finite are formed again as plain sums, in one launch as in two."""
+    import torch
+    import paper_2203_10983_amd as pkg
+    dev = torch.device("cuda:0")
+    n, d_in, d_out, nb = 300, 64, 16, 40
+    P = _partition(n, 6, 0, nb, np.random.default_rng(6))
+    i32 = lambda k: torch.zeros(k, dtype=torch.int32, device=dev)  # noqa: E731
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(6)
+    dZ, A, X, W = (torch.randn(*s, device=dev, generator=gen) for s in ((n, d_out), (n, d_in), (n, d_in), (d_in, d_out)))
+    dZ[3, 2], dZ[7, 5], dZ[11, 0] = float("inf"), float("-inf"), float("nan")
+    out = []
+    for mask in (TIMED, 0):
+        ctx = pkg.Context(P, [d_in, d_in, d_out], 0, device=dev)
+        ctx.profile_enable(mask, 16)
+        kept, remap, n_kept, nnz = i32(nb), i32(nb), i32(1), i32(1)
+        ctx.sample_boundary(1, 0, 0.5, kept, remap, n_kept)
+        csr = i32(n + 1), i32(P.nnz0), i32(n + nb + 1), i32(P.nnz0)
+        ctx.build_sampled_csr(remap, kept, n_kept, *csr, nnz)
+        dH, dhalo, dW = torch.zeros(n, d_in, device=dev), torch.zeros(nb, d_in, device=dev), torch.zeros_like(W)
+        ctx.gcn_layer_bwd(2, 0.5, dZ, None, A, X, W, dW, dH, dhalo)
+        out.append((dH, dhalo))
+        torch.cuda.synchronize()
+        ctx.close()
+    for two, one in zip(*out):
+        torch.testing.assert_close(one, two, rtol=0, atol=0, equal_nan=True)
+    assert torch.isinf(out[1][0]).any() and torch.isnan(out[1][0]).any() and torch.isfinite(out[1][0]).any()
