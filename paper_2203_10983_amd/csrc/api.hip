@@ -365,10 +365,11 @@ int layer_plan(const bns_ctx *ctx, int layer, const float *X) {
 
 // update_first: H_out = act(P [H_in W ; Hu W]) instead of act((P [H_in ; Hu]) W); A_saved then
 // receives H_in W (the aggregate of the inputs is never formed).  prepare (nullable): the weights to pack, when
-// neither they nor the boundary records are ready.
+// neither they nor the boundary records are ready.  loss (nullable): of the last layer's output; where it is formed on the way,
+// its n_partials is set.
 bns_status layer_fwd_impl(bns_ctx *ctx, int layer, double p, const float *H_in, const float *halo_h,
                           const float *W, float *A_saved, float *H_out, bool relu, bool update_first,
-                          const PackJobs *prepare, hipStream_t s) {
+                          const PackJobs *prepare, TileLoss *loss, hipStream_t s) {
   const int n_in = ctx->part.n_in, B = ctx->part.n_halo;
   const int d_in = ctx->dims[layer - 1], d_out = ctx->dims[layer];
   const bool sage = ctx->layer_kind == 1;
@@ -447,7 +448,8 @@ bns_status layer_fwd_impl(bns_ctx *ctx, int layer, double p, const float *H_in, 
     if (!meets(A_saved, n_a) && !meets(H_out, n_h)) {
       BNS_TRY("tile_layer_fwd", tile_layer_fwd(ctx->ws.plan_f, n_in, d_in, d_out, ctx->cur_row_ptr, ctx->cur_col_idx, w_in, w_ptr,
                                                row_scale, H_in, halo_h, ctx->ws.spmm_partials, A_saved, part, W, H_out, relu,
-                                               dropout_of(ctx, layer, relu), sage, concat_in_one(d_in), s));
+                                               dropout_of(ctx, layer, relu), sage, concat_in_one(d_in),
+                                               loss && d_out <= kTileLossWidth && !timed(ctx, BNS_PHASE_LOSS) ? loss : nullptr, s));
       return BNS_OK;
     }
   }
@@ -875,7 +877,7 @@ bns_status bns_gcn_layer_fwd(bns_ctx *ctx, int32_t layer, double p, const float 
   hipStream_t s = static_cast<hipStream_t>(stream);
   PackJobs jobs;
   add_pack_jobs(ctx, layer, W, true, false, &jobs);
-  return layer_fwd_impl(ctx, layer, p, H_in, halo_h, W, A_saved, H_out, relu != 0, false, &jobs, s);
+  return layer_fwd_impl(ctx, layer, p, H_in, halo_h, W, A_saved, H_out, relu != 0, false, &jobs, nullptr, s);
 }
 
 bns_status bns_gcn_layer_bwd(bns_ctx *ctx, int32_t layer, double p, const float *dH_out, const float *H_out,
@@ -933,28 +935,34 @@ static bns_status train_step_impl(bns_ctx *ctx, uint64_t seed, uint32_t epoch, c
   bns_status st = sample_and_build_impl(ctx, seed, epoch, epoch_dev, p, jobs, s);
   if (st != BNS_OK) return st;
 
-  const float *H_prev = X;
-  for (int l = 1; l <= L; ++l) {
-    st = layer_fwd_impl(ctx, l, p, H_prev, ctx->part.n_halo > 0 ? halo_h[l - 1] : nullptr, W[l - 1], w.A[l],
-                        w.H[l], l < L, layer_plan(ctx, l, X) == BNS_LAYER_UPDATE_FIRST, nullptr, s);
-    if (st != BNS_OK) return st;
-    H_prev = w.H[l];
-  }
-
   const int C = ctx->dims[L];
   TnLoss loss_sum{w.loss_partials, 0, loss};
   // where the last layer's backward pass gathers padded rows of dZ, the loss leaves them beside dZ
   const bool pad_last = pads_gradient(ctx, L, p, layer_plan(ctx, L, X) == BNS_LAYER_UPDATE_FIRST, L > 1);
-  const int ld = gather_stride(ctx->dims[L - 1], C);
-  float *dZ_pad = pad_last ? w.G2 : nullptr;
-  {
+  TileLoss last;
+  last.labels = static_cast<const int32_t *>(labels);
+  last.dZ = w.dZ[L];
+  last.dZ_pad = pad_last ? w.G2 : nullptr;
+  last.partials = w.loss_partials;
+  last.ld = gather_stride(ctx->dims[L - 1], C);
+
+  const float *H_prev = X;
+  for (int l = 1; l <= L; ++l) {
+    st = layer_fwd_impl(ctx, l, p, H_prev, ctx->part.n_halo > 0 ? halo_h[l - 1] : nullptr, W[l - 1], w.A[l],
+                        w.H[l], l < L, layer_plan(ctx, l, X) == BNS_LAYER_UPDATE_FIRST, nullptr, l == L && ctx->loss_kind == 0 ? &last : nullptr, s);
+    if (st != BNS_OK) return st;
+    H_prev = w.H[l];
+  }
+
+  loss_sum.n = last.n_partials;
+  if (loss_sum.n == 0) {
     PhaseTimer t(ctx, BNS_PHASE_LOSS, s);
     if (ctx->loss_kind == 0)
-      BNS_TRY("loss_softmax_ce", loss_softmax_ce(n_in, C, w.H[L], static_cast<const int32_t *>(labels), w.dZ[L], ld, dZ_pad,
-                                                 w.loss_partials, &loss_sum.n, s));
+      BNS_TRY("loss_softmax_ce", loss_softmax_ce(n_in, C, w.H[L], last.labels, last.dZ, last.ld, last.dZ_pad,
+                                                 last.partials, &loss_sum.n, s));
     else
-      BNS_TRY("loss_sigmoid_bce", loss_sigmoid_bce(n_in, C, w.H[L], static_cast<const uint8_t *>(labels), w.dZ[L], ld, dZ_pad,
-                                                   w.loss_partials, &loss_sum.n, s));
+      BNS_TRY("loss_sigmoid_bce", loss_sigmoid_bce(n_in, C, w.H[L], static_cast<const uint8_t *>(labels), last.dZ, last.ld, last.dZ_pad,
+                                                   last.partials, &loss_sum.n, s));
   }
 
   // dZ[l] is the gradient w.r.t. the pre-activation of layer l; the backward pass of layer l writes

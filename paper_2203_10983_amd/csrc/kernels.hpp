@@ -208,11 +208,18 @@ struct Dropout {
 // ---- tile.hip: aggregate and update of a layer of a small partition in one launch --------------
 // As spmm_fwd and then gemm_rows_f32 on [A | H_in (sage)] W with the plain W: the same bits.  concat: the two halves of the mean
 // aggregator's update are one product (else two, added).  Neither A nor H_out may share memory with H_in, Hu or W.
+// loss (nullable, d_out <= kTileLossWidth, no relu): of the output, as loss_softmax_ce, in the same launch.
+struct TileLoss {
+  const int32_t *labels = nullptr;
+  float *dZ = nullptr, *dZ_pad = nullptr, *partials = nullptr;
+  int32_t ld = 0, n_partials = 0;  // n_partials: set by the call
+};
+constexpr int kTileLossWidth = 128;
 bool tile_layer_supported(const SegPlan &plan, int32_t d_in, int32_t d_out);
 hipError_t tile_layer_fwd(const SegPlan &plan, int32_t n_in, int32_t d_in, int32_t d_out, const int32_t *row_ptr,
                           const int32_t *col_idx, const float *w_in, const int32_t *w_ptr, const float *row_scale,
                           const float *H_in, const float *Hu, float *partials, float *A, const SpmmRowPart &part, const float *W,
-                          float *H_out, bool relu, const Dropout &drop, bool sage, bool concat, hipStream_t s);
+                          float *H_out, bool relu, const Dropout &drop, bool sage, bool concat, TileLoss *loss, hipStream_t s);
 
 // dH[u,:] = alpha * (P^T dZ [+ dZ of u (sage: by the second half of W)]) W^T, zeroed where mask <= 0 (nullable), and for the kept
 // boundary nodes (dhalo nullable) without alpha and mask: as spmm_bwd (its arguments; dZ has rows of d floats, zeros from d_out

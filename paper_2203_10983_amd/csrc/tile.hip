@@ -6,6 +6,8 @@
 // code and the order of sums of spmm_kernel, and multiplies them by W with v_mfma_f32_16x16x4_f32, a wavefront per 16 or
 // 32 columns.  That instruction is a chain of fused multiply-adds in depth order, as v_mfma_f32_32x32x2_f32 is (40960 sums of 128 products of
 // operands of any size: equal bits, and equal to fmaf), so that the results are those of spmm_kernel and gemm_rows_f32_kernel.
+// The last layer forms the softmax loss and its gradient on the way (steps of 500 rows 64-16-8 36 -> 34 us, 3500 rows
+// 64-128-47 3 % less; the sigmoid loss, an exponential and a logarithm per element of few columns, gained nothing here).
 // W is asked for before the gather, straight from the caller's matrix: 16 columns of 4 depths are a load of 256 bytes.
 #include "spmm_device.hpp"
 #include "split_bf16.hpp"
@@ -27,7 +29,51 @@ struct TileArgs {
   bool relu;
   bool concat;          // SAGE: both halves of the update are one chain of sums (else two, added)
   Dropout drop;
+  TileLoss loss;
 };
+
+// The gradient of one node's cross-entropy from its logits z, by LPR lanes that hold up to four classes each: the steps and the order of
+// sums of softmax_ce_kernel.  Returns the node's loss on lane 0 of the group.
+template <int LPR>
+__device__ __forceinline__ float ce_row(const float *z, int C, int y, bool ok, float *g, float *gp, int ld) {
+  const int sl = lane_id() % LPR;
+  float x[4], m = -INFINITY, se = 0.f, zy = 0.f;  // y: negative outside the training set
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int c = sl + k * LPR;
+    x[k] = ok && c < C ? z[c] : -INFINITY;
+    m = fmaxf(m, x[k]);
+  }
+#pragma unroll
+  for (int off = LPR / 2; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, kWave));
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int c = sl + k * LPR;
+    if (c == y) zy = x[k];
+    x[k] = c < C ? expf(x[k] - m) : 0.f;
+    se += x[k];
+  }
+#pragma unroll
+  for (int off = LPR / 2; off > 0; off >>= 1) {
+    se += __shfl_xor(se, off, kWave);
+    zy += __shfl_xor(zy, off, kWave);
+  }
+  if (!ok) return 0.f;
+  const float inv = 1.f / se;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int c = sl + k * LPR;
+    const float o = y < 0 || c >= C ? 0.f : x[k] * inv - (c == y ? 1.f : 0.f);
+    if (c < C) g[c] = o;
+    if (gp && c < ld) gp[c] = o;
+  }
+  return sl == 0 && y >= 0 ? (m + logf(se)) - zy : 0.f;
+}
+
+// Lanes per node, and the node of a tile that a lane has a share of: one pass takes a whole tile.
+__device__ __forceinline__ int ce_lanes(int C) { return C <= 32 ? 8 : C <= 64 ? 16 : 32; }
+__device__ __forceinline__ int ce_node(int C) { return threadIdx.x / ce_lanes(C); }
+static_assert(kTileWaves * kWave / 32 >= kTileRows && kTileLossWidth <= 4 * 32);
 
 typedef float f32x2u __attribute__((ext_vector_type(2), aligned(4)));
 
@@ -96,7 +142,9 @@ __device__ __forceinline__ void gather_tile(const SpmmArgs &a, int row0, int row
   }
 }
 
-template <int LPR, int VW, bool SAGE>
+// LOSS: also the softmax cross-entropy of the last layer's output and its gradient.
+
+template <int LPR, int VW, bool SAGE, bool LOSS = false>
 __global__ void __launch_bounds__(kTileWaves * kWave, 4) tile_layer_kernel(const TileArgs f) {
   using V = typename Vec<4>::T;
   __shared__ __attribute__((aligned(16))) float As[SAGE ? 2 : 1][kTileRows * kTileLd];
@@ -126,6 +174,9 @@ __global__ void __launch_bounds__(kTileWaves * kWave, 4) tile_layer_kernel(const
       }
   };
   load_w(f.W);
+  int label = -1;
+  if constexpr (LOSS)
+    if (ce_node(N) < rows) label = f.loss.labels[row0 + ce_node(N)];
   if constexpr (SAGE) {  // the rows' own features
     for (int idx = threadIdx.x; idx < rows * nvec; idx += kTileWaves * kWave) {
       const int r = idx / nvec, c4 = idx - r * nvec;
@@ -145,13 +196,15 @@ __global__ void __launch_bounds__(kTileWaves * kWave, 4) tile_layer_kernel(const
     reinterpret_cast<V *>(a.out0 + (size_t)row * d)[piece] = o;
   });
   __syncthreads();
-  if (n0 >= N) return;
+  if (!LOSS && n0 >= N) return;
 
   // ---- update ----
   f32x4 sum[VW];
 #pragma unroll
   for (int c = 0; c < VW; ++c) sum[c] = f32x4{0.f, 0.f, 0.f, 0.f};
-  auto product = [&](const float *tile) {  // (the tile's rows past the last one hold anything: an operand's row is one result's row)
+  auto product = [&](const float *tile) {
+    if (LOSS && n0 >= N) return;
+    // (the tile's rows past the last one hold anything: an operand's row is one result's row)
     const float *as = tile + l16 * kTileLd + g4;
 #pragma unroll
     for (int m = 0; m < LPR; ++m)
@@ -176,6 +229,8 @@ __global__ void __launch_bounds__(kTileWaves * kWave, 4) tile_layer_kernel(const
       for (int c = 0; c < VW; ++c) sum[c] += first[c];
   }
   // a lane holds rows 4 (lane / 16) .. + 3 of its columns
+  __shared__ float Zs[LOSS ? kTileRows * kTileLd : 1];
+  float loss = 0.f;
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
     const int lrow = 4 * g4 + r;
@@ -188,10 +243,33 @@ __global__ void __launch_bounds__(kTileWaves * kWave, 4) tile_layer_kernel(const
         if (f.drop.scale != 0.f) x[c] = dropout_keeps(f.drop, row0 + lrow, col + c) ? x[c] * f.drop.scale : 0.f;
       }
     }
-    if (lrow >= rows) continue;
+    if (lrow >= rows || (LOSS && n0 + l16 >= N)) continue;
     float *const to = f.H_out + (size_t)(row0 + lrow) * N + col;
     if constexpr (VW == 2) *reinterpret_cast<f32x2u *>(to) = f32x2u{x[0], x[1]};
     else *to = x[0];
+    if constexpr (LOSS) Zs[lrow * kTileLd + col] = x[0];
+  }
+  if constexpr (LOSS) {
+    __syncthreads();
+    const TileLoss &l = f.loss;
+    const int node = ce_node(N);
+    const bool ok = node < rows;
+    const float *z = Zs + (ok ? node : 0) * kTileLd;
+    const size_t row = row0 + (ok ? node : 0);
+    float *const g = l.dZ + row * N, *const gp = l.dZ_pad ? l.dZ_pad + row * l.ld : nullptr;
+    if (N <= 32) loss = ce_row<8>(z, N, label, ok, g, gp, l.ld);
+    else if (N <= 64) loss = ce_row<16>(z, N, label, ok, g, gp, l.ld);
+    else loss = ce_row<32>(z, N, label, ok, g, gp, l.ld);
+    loss = wave_sum(loss);
+    __shared__ float part[kTileWaves];
+    if (lane == 0) part[wid] = loss;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      float sum = 0.f;
+#pragma unroll
+      for (int i = 0; i < kTileWaves; ++i) sum += part[i];
+      f.loss.partials[blockIdx.x] = sum;
+    }
   }
 }
 
@@ -341,8 +419,8 @@ bool tile_layer_supported(const SegPlan &plan, int32_t d_in, int32_t d_out) {
 hipError_t tile_layer_fwd(const SegPlan &plan, int32_t n_in, int32_t d_in, int32_t d_out, const int32_t *row_ptr,
                           const int32_t *col_idx, const float *w_in, const int32_t *w_ptr, const float *row_scale,
                           const float *H_in, const float *Hu, float *partials, float *A, const SpmmRowPart &part, const float *W,
-                          float *H_out, bool relu, const Dropout &drop, bool sage, bool concat, hipStream_t s) {
-  if (!tile_layer_supported(plan, d_in, d_out)) return hipErrorInvalidValue;
+                          float *H_out, bool relu, const Dropout &drop, bool sage, bool concat, TileLoss *loss, hipStream_t s) {
+  if (!tile_layer_supported(plan, d_in, d_out) || (loss && d_out > kTileLossWidth)) return hipErrorInvalidValue;
   if (n_in <= 0) return hipSuccess;
   TileArgs f;
   f.sp = spmm_fwd_args(plan, n_in, d_in, row_ptr, col_idx, w_in, w_ptr, row_scale, H_in, Hu, partials, A, part);
@@ -354,11 +432,18 @@ hipError_t tile_layer_fwd(const SegPlan &plan, int32_t n_in, int32_t d_in, int32
   f.relu = relu;
   f.concat = concat;
   f.drop = drop;
+  if (loss) f.loss = *loss;
   const unsigned blocks = (unsigned)((n_in + f.rows - 1) / f.rows);
-#define BNS_TILE(LPR, VW)                                                                       \
-  do {                                                                                           \
-    if (sage) tile_layer_kernel<LPR, VW, true><<<blocks, kTileWaves * kWave, 0, s>>>(f);        \
-    else tile_layer_kernel<LPR, VW, false><<<blocks, kTileWaves * kWave, 0, s>>>(f);            \
+  if (loss) loss->n_partials = (int32_t)blocks;
+#define BNS_TILE_KIND(LPR, VW, LOSS)                                                                  \
+  do {                                                                                                \
+    if (sage) tile_layer_kernel<LPR, VW, true, LOSS><<<blocks, kTileWaves * kWave, 0, s>>>(f);       \
+    else tile_layer_kernel<LPR, VW, false, LOSS><<<blocks, kTileWaves * kWave, 0, s>>>(f);           \
+  } while (0)
+#define BNS_TILE(LPR, VW)                                     \
+  do {                                                        \
+    if (VW == 1 && loss) BNS_TILE_KIND(LPR, 1, true);         \
+    else BNS_TILE_KIND(LPR, VW, false);                       \
   } while (0)
   const bool wide = d_out > 16 * kTileWaves;
   if (d_in > 64) BNS_TILE(32, 1);
@@ -366,6 +451,7 @@ hipError_t tile_layer_fwd(const SegPlan &plan, int32_t n_in, int32_t d_in, int32
   else if (d_in > 16) { if (wide) BNS_TILE(8, 2); else BNS_TILE(8, 1); }
   else { if (wide) BNS_TILE(4, 2); else BNS_TILE(4, 1); }
 #undef BNS_TILE
+#undef BNS_TILE_KIND
   return hipGetLastError();
 }
 

@@ -9,7 +9,7 @@ import pytest
 
 pytestmark = pytest.mark.gpu
 
-TIMED = (1 << 3) | (1 << 4) | (1 << 7) | (1 << 8)  # aggregate, update, and their backward passes
+TIMED = (1 << 3) | (1 << 4) | (1 << 5) | (1 << 7) | (1 << 8)  # aggregate, update, loss, and the backward passes of the first two
 
 
 def _partition(n, deg, hub, n_halo, rng):
@@ -50,8 +50,8 @@ def test_one_launch_equals_two(n, deg, hub, dims, layer_kind, drop, cached):
     r = lambda *s: torch.randn(*s, device=dev, generator=gen)  # noqa: E731
     X, halo = r(n, dims[0]), [r(n_halo, d) for d in dims[:-1]]
     W = [r((1 + layer_kind) * a, b) / a ** 0.5 for a, b in zip(dims, dims[1:])]
-    labels = torch.randint(0, dims[-1], (n,), device=dev, generator=gen, dtype=torch.int32)
-    out = []
+    labels = torch.randint(-1, dims[-1], (n,), device=dev, generator=gen, dtype=torch.int32)  # -1: outside the training set
+    out, losses = [], []
     for mask in (TIMED, 0):
         ctx = pkg.Context(P, list(dims), 0, layer_kind=layer_kind, device=dev)
         ctx.set_dropout(drop)
@@ -66,12 +66,15 @@ def test_one_launch_equals_two(n, deg, hub, dims, layer_kind, drop, cached):
         torch.cuda.synchronize()
         if mask:
             assert ctx.profile_read()["gemm_fwd"][1] >= 2 * L  # two launches
-        A = [ctx.ws_tensor(pkg.VIEW_A, l, torch.float32).clone() for l in range(1, L + 1)]
+        A = [ctx.ws_tensor(pkg.VIEW_A, l, torch.float32).clone() for l in range(1, L + 1)] + [ctx.ws_tensor(pkg.VIEW_DZ, L, torch.float32).clone()]
+        losses.append(loss.double())
         dZ = [ctx.ws_tensor(pkg.VIEW_DZ, l, torch.float32).clone() for l in range(1, L)]
         out.append((A + [ctx.ws_tensor(pkg.VIEW_H, l, torch.float32).clone() for l in range(1, L + 1)], dZ + dhalo[1:]))
         ctx.close()
     for two, one in zip(out[0][0], out[1][0]):
         assert torch.isfinite(two).all() and torch.equal(two, one)
+    # positive terms, added in other orders: per node, wavefront, workgroup, then all
+    assert (losses[0] - losses[1]).abs() <= 24 * 2.0 ** -24 * losses[0]
     narrowing = layer_kind == 0 and all(b < a for a, b in zip(dims[1:], dims[2:]))
     for two, one in zip(out[0][1], out[1][1]):
         if narrowing:
