@@ -765,7 +765,7 @@ bns_status sample_and_build_impl(bns_ctx *ctx, uint64_t seed, uint32_t epoch, co
   PhaseTimer t(ctx, BNS_PHASE_SAMPLE, s);
   BNS_TRY("sample_build_small",
           sample_build_small(P.halo_gid, P.n_halo, seed, epoch, epoch_dev, (uint32_t)P.part_id, threshold, w.ballots,
-                             w.kept_ids, w.remap, w.counters, w.kept_start, P.n_in, P.e_in, P.e_bd, w.split, w.kpos,
+                             w.kept_ids, w.remap, w.counters, w.kept_start, P.n_in, P.e_in, P.e_bd, w.split,
                              w.row_ptr, w.col_idx, w.counters + 1, P.halo_ptr, P.halo_col, w.t_row_ptr, w.t_col_idx,
                              w.halo_rec, ctx->layer_kind == 1 ? nullptr : w.dis_halo, halo_scale(p), &pack, s));
   ctx->cur_kept = w.kept_ids;

@@ -1,7 +1,8 @@
 """Layers of small partitions, aggregate and product in one launch, against the two launches that run while their phases are
 timed.  Forward, and backward where the output is the narrower side, the same sums in the same order, so the same bits; else the
 transposed aggregate has changed places with the product, and both results lie within a few roundings (2^-24) of the exact one.
-Random graphs with hubs of up to eight segments of 256 entries."""
+Random graphs with hubs of up to eight segments of 256 entries.  And the subgraph of
+such a step, whose launch the stand-alone calls do not take, at that launch's limits."""
 import types
 
 import numpy as np
@@ -12,8 +13,8 @@ pytestmark = pytest.mark.gpu
 TIMED = (1 << 3) | (1 << 4) | (1 << 5) | (1 << 7) | (1 << 8)  # aggregate, update, loss, and the backward passes of the first two
 
 
-def _partition(n, deg, hub, n_halo, rng):
-    """n rows of about deg entries, row n // 2 with hub; symmetric inner part with self-loops, boundary nodes next to a few rows."""
+def _partition(n, deg, hub, n_halo, rng, lists=4):
+    """n rows of about deg entries, row n // 2 with hub; symmetric inner part with self-loops, boundary nodes next to 1 to `lists` rows."""
     pairs = {(v, v) for v in range(n)}
     for _ in range(int(n * deg / 2)):
         a, b = (int(x) for x in rng.integers(0, n, 2))
@@ -21,7 +22,7 @@ def _partition(n, deg, hub, n_halo, rng):
     for b in rng.choice(n, size=min(n, hub), replace=False):
         pairs |= {(n // 2, int(b)), (int(b), n // 2)}
     inner = np.array(sorted(pairs), dtype=np.int64)
-    halo = np.array(sorted({(b, int(v)) for b in range(n_halo) for v in rng.integers(0, n, 1 + b % 4)}), dtype=np.int64).reshape(-1, 2)
+    halo = np.array(sorted({(b, int(v)) for b in range(n_halo) for v in rng.integers(0, n, 1 + b % lists)}), dtype=np.int64).reshape(-1, 2)
     both = np.concatenate([inner, np.stack([halo[:, 1], n + halo[:, 0]], 1)])
     both = both[np.lexsort((both[:, 1], both[:, 0]))]
     ptr = lambda of, m: np.concatenate([[0], np.cumsum(np.bincount(of, minlength=m))])  # noqa: E731
@@ -132,3 +133,34 @@ def test_backward_with_infinite_gradients():
     for two, one in zip(*out):
         torch.testing.assert_close(one, two, rtol=0, atol=0, equal_nan=True)
     assert torch.isinf(out[1][0]).any() and torch.isnan(out[1][0]).any() and torch.isfinite(out[1][0]).any()
+
+
+@pytest.mark.parametrize("n,deg,n_halo,lists,p,one", [(3, 1, 1, 1, 1.0, True), (1023, 4, 1025, 2, 0.5, True), (2000, 3, 8192, 1, 1.0, True),
+                                                      (2000, 3, 8193, 1, 1.0, False), (1000, 40, 4900, 4, 0.3, True), (900, 3, 5200, 4, 0.3, False),
+                                                      (1950, 40, 2000, 3, 0.0, True), (2200, 40, 2000, 3, 0.9, False)])
+def test_subgraph_of_a_step_at_the_limits(n, deg, n_halo, lists, p, one):
+    import torch
+    import paper_2203_10983_amd as pkg
+    dev = torch.device("cuda:0")
+    P = _partition(n, deg, 0, n_halo, np.random.default_rng(n_halo), lists)
+    assert one == (n_halo <= 8192 and P.e_bd <= 12288 and n + P.e_in <= 81920)
+    ctx = pkg.Context(P, [8, 8], 0, device=dev)
+    i32 = lambda k: torch.zeros(k, dtype=torch.int32, device=dev)  # noqa: E731
+    f32 = lambda *s: torch.zeros(*s, device=dev)  # noqa: E731
+    ctx.profile_enable(3, 16)
+    W = [torch.randn(8, 8, device=dev)]
+    ctx.train_step(11, 2, p, f32(n, 8), [f32(n_halo, 8)], i32(n), W, [f32(8, 8)], [None], f32(1), 0.0)
+    torch.cuda.synchronize()
+    assert (ctx.profile_read()["build"][1] == 0) == one
+    view = lambda w: ctx.ws_tensor(w, 0, torch.int32).clone()  # noqa: E731
+    got = [view(v) for v in (pkg.VIEW_KEPT_IDS, pkg.VIEW_REMAP, pkg.VIEW_ROW_PTR, pkg.VIEW_COL_IDX, pkg.VIEW_T_ROW_PTR, pkg.VIEW_T_COL_IDX)]
+    counts = int(view(pkg.VIEW_N_KEPT)[0]), int(view(pkg.VIEW_NNZ)[0])
+    kept, remap, n_kept, nnz = i32(n_halo), i32(n_halo), i32(1), i32(1)
+    ctx.sample_boundary(11, 2, p, kept, remap, n_kept)
+    csr = i32(n + 1), i32(P.nnz0), i32(n + n_halo + 1), i32(P.nnz0)
+    ctx.build_sampled_csr(remap, kept, n_kept, *csr, nnz)
+    K, m = int(n_kept), int(nnz)
+    assert counts == (K, m)
+    for a, b, k in zip(got, (kept, remap) + csr, (K, n_halo, n + 1, m, n + K + 1, m)):
+        assert torch.equal(a[:k], b[:k])
+    ctx.close()
