@@ -905,7 +905,8 @@ bns_status bns_gcn_layer_bwd(bns_ctx *ctx, int32_t layer, double p, const float 
                         nullptr, s);
 }
 
-static bns_status train_step_impl(bns_ctx *ctx, uint64_t seed, uint32_t epoch, const uint32_t *epoch_dev, double p,
+// epoch_dev (nullable): the epoch index is read from there instead, and counted up by the last launch.
+static bns_status train_step_impl(bns_ctx *ctx, uint64_t seed, uint32_t epoch, uint32_t *epoch_dev, double p,
                                   const float *X, const float *const *halo_h, const void *labels,
                                   float *const *W, float *const *dW, float *const *dhalo, float *loss, float lr,
                                   void *stream) {
@@ -936,7 +937,7 @@ static bns_status train_step_impl(bns_ctx *ctx, uint64_t seed, uint32_t epoch, c
   if (st != BNS_OK) return st;
 
   const int C = ctx->dims[L];
-  TnLoss loss_sum{w.loss_partials, 0, loss};
+  TnLoss loss_sum{w.loss_partials, 0, loss, epoch_dev};
   // where the last layer's backward pass gathers padded rows of dZ, the loss leaves them beside dZ
   const bool pad_last = pads_gradient(ctx, L, p, layer_plan(ctx, L, X) == BNS_LAYER_UPDATE_FIRST, L > 1);
   TileLoss last;
@@ -1012,12 +1013,10 @@ bns_status bns_graph_capture(bns_ctx *ctx, uint64_t seed, uint32_t first_epoch, 
   const uint32_t saved_mask = ctx->prof.mask;
   ctx->prof.mask = 0;
   bns_status st = train_step_impl(ctx, seed, 0, epoch_dev, p, X, halo_h, labels, W, dW, dhalo, loss, lr, stream);
-  hipError_t e_bump = st == BNS_OK ? bump_counter(epoch_dev, s) : hipSuccess;
   hipGraph_t graph = nullptr;
   hipError_t e_end = hipStreamEndCapture(s, &graph);
   ctx->prof.mask = saved_mask;
   if (st != BNS_OK) { if (graph) (void)hipGraphDestroy(graph); return st; }
-  if (e_bump != hipSuccess) { if (graph) (void)hipGraphDestroy(graph); return hip_fail(ctx, "bump_counter", e_bump); }
   if (e_end != hipSuccess) return hip_fail(ctx, "hipStreamEndCapture", e_end);
   hipError_t e_inst = hipGraphInstantiate(&ctx->graph_exec, graph, nullptr, nullptr, 0);
   (void)hipGraphDestroy(graph);

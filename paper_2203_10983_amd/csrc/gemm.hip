@@ -515,6 +515,7 @@ struct TnSums {
   const float *loss_partials;
   int n_loss;
   float *loss;
+  uint32_t *bump;
 };
 
 template <int NW>
@@ -531,6 +532,7 @@ __global__ void __launch_bounds__(NW * 64) gemm_tn_reduce_kernel(const TnSums jo
       float s = 0.f;
       for (int w = 0; w < NW; ++w) s += part[0][w];
       *jobs.loss = s;
+      if (jobs.bump) *jobs.bump += 1;
     }
     return;
   }
@@ -700,6 +702,7 @@ hipError_t gemm_tn(const TnGemm *g, int32_t n, const TnLoss &loss, hipStream_t s
   sums.loss_partials = loss.partials;
   sums.n_loss = loss.n;
   sums.loss = loss.out;
+  sums.bump = loss.bump;
   const unsigned blocks = (unsigned)(sums.blocks + (loss.out ? 1 : 0));
   if (blocks == 0) return hipSuccess;
   if (many) gemm_tn_reduce_kernel<16><<<blocks, 1024, 0, s>>>(sums);

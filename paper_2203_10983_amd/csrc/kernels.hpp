@@ -298,6 +298,7 @@ struct TnLoss {
   const float *partials = nullptr;
   int32_t n = 0;
   float *out = nullptr;
+  uint32_t *bump = nullptr;  // nullable, with out: *bump += 1 (the epoch of a captured step, whose last launch this is)
 };
 constexpr int kMaxTnJobs = 16;
 size_t gemm_tn_partials(int32_t M, int32_t N, int32_t K, int32_t K_other);
@@ -321,8 +322,7 @@ hipError_t sgd_update(int64_t n, float *W, const float *dW, float lr, hipStream_
 // Adam step t (1-based) on n weights; m, v are the caller's moment buffers.
 hipError_t adam_update(int64_t n, float *W, const float *dW, float *m, float *v, float lr, float b1,
                        float b2, float eps, int32_t t, hipStream_t s);
-// *counter = value / *counter += 1 (one thread; the device-side epoch index of graph replay)
+// *counter = value (one thread; the device-side epoch index of graph replay)
 hipError_t set_counter(uint32_t *counter, uint32_t value, hipStream_t s);
-hipError_t bump_counter(uint32_t *counter, hipStream_t s);
 
 }  // namespace bns

@@ -265,15 +265,9 @@ hipError_t adam_update(int64_t n, float *W, const float *dW, float *m, float *v,
   return hipGetLastError();
 }
 
-__global__ void counter_kernel(uint32_t *counter, uint32_t value, bool bump) {
-  *counter = bump ? *counter + 1u : value;
-}
+__global__ void counter_kernel(uint32_t *counter, uint32_t value) { *counter = value; }
 hipError_t set_counter(uint32_t *counter, uint32_t value, hipStream_t s) {
-  counter_kernel<<<1, 1, 0, s>>>(counter, value, false);
-  return hipGetLastError();
-}
-hipError_t bump_counter(uint32_t *counter, hipStream_t s) {
-  counter_kernel<<<1, 1, 0, s>>>(counter, 0u, true);
+  counter_kernel<<<1, 1, 0, s>>>(counter, value);
   return hipGetLastError();
 }
 
