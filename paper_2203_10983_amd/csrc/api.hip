@@ -93,6 +93,7 @@ struct bns_ctx {
   uint64_t cur_seed = 0;           // seed / epoch of the latest boundary sample: the dropout draw uses them
   uint32_t cur_epoch = 0;
   const uint32_t *cur_epoch_dev = nullptr;
+  bool cur_counted = false;             // the kept boundary entries of the latest sample are counted in the workspace
   hipGraphExec_t graph_exec = nullptr;  // captured training step (bns_graph_capture)
   std::string err;
 };
@@ -706,8 +707,7 @@ constexpr int kPackLayers = kMaxPackJobs / 4;  // layers whose jobs fit one laun
 
 BdCount bd_count(const bns_ctx *ctx) { return BdCount{ctx->part.e_bd, ctx->ws.split.bd_b, ctx->ws.bd_mask, ctx->ws.bd_sums}; }
 
-// pack (nullable): a training step's: weights to pack beside the sampling, and the records of the kept nodes and the
-// count of the kept boundary entries too
+// pack (nullable): a training step's: weights to pack beside the sampling, and the records of the kept nodes too
 bns_status sample_impl(bns_ctx *ctx, uint64_t seed, uint32_t epoch, const uint32_t *epoch_dev, double p,
                        int32_t *kept_ids, int32_t *remap, int32_t *n_kept, const PackJobs *pack, hipStream_t s) {
   const uint64_t threshold = (uint64_t)std::floor(p * 4294967296.0);
@@ -717,7 +717,8 @@ bns_status sample_impl(bns_ctx *ctx, uint64_t seed, uint32_t epoch, const uint32
           sample_boundary(ctx->part.halo_gid, ctx->part.n_halo, seed, epoch, epoch_dev, (uint32_t)ctx->part.part_id,
                           threshold, ctx->ws.ballots, ctx->ws.tile_sums, kept_ids, remap, n_kept, ctx->part.halo_ptr,
                           (int32_t)ctx->part.e_in, ctx->ws.kept_start, pack ? ctx->ws.halo_rec : nullptr,
-                          ctx->layer_kind == 1 ? nullptr : ctx->ws.dis_halo, halo_scale(p), pack, pack ? &count : nullptr, s));
+                          ctx->layer_kind == 1 ? nullptr : ctx->ws.dis_halo, halo_scale(p), pack, &count, s));
+  ctx->cur_counted = true;
   ctx->cur_kept = kept_ids;
   ctx->cur_remap = remap;
   ctx->cur_n_kept = n_kept;
@@ -728,7 +729,7 @@ bns_status sample_impl(bns_ctx *ctx, uint64_t seed, uint32_t epoch, const uint32
 }
 
 bns_status build_impl(bns_ctx *ctx, int32_t *row_ptr, int32_t *col_idx, int32_t *t_row_ptr,
-                      int32_t *t_col_idx, int32_t *nnz, bool counted, hipStream_t s) {
+                      int32_t *t_col_idx, int32_t *nnz, hipStream_t s) {
   const bns_partition_desc &P = ctx->part;
   PhaseTimer t(ctx, BNS_PHASE_BUILD, s);
   SubgraphBuild g{};
@@ -742,7 +743,7 @@ bns_status build_impl(bns_ctx *ctx, int32_t *row_ptr, int32_t *col_idx, int32_t 
   g.row_ptr = row_ptr; g.col_idx = col_idx; g.nnz = nnz; g.t_row_ptr = t_row_ptr; g.t_col_idx = t_col_idx;
   // the workspace arrays hold the static rows since bns_create
   g.static_rows = !(t_row_ptr == ctx->ws.t_row_ptr && t_col_idx == ctx->ws.t_col_idx);
-  BNS_TRY("build_subgraph", build_subgraph(g, counted, s));
+  BNS_TRY("build_subgraph", build_subgraph(g, ctx->cur_counted, s));
   ctx->cur_row_ptr = row_ptr;
   ctx->cur_col_idx = col_idx;
   ctx->cur_t_row_ptr = t_row_ptr;
@@ -759,7 +760,7 @@ bns_status sample_and_build_impl(bns_ctx *ctx, uint64_t seed, uint32_t epoch, co
   if (!sample_build_small_fits(P.n_in, P.n_halo, P.e_in, P.e_bd)) {
     const bns_status st = sample_impl(ctx, seed, epoch, epoch_dev, p, w.kept_ids, w.remap, w.counters, &pack, s);
     if (st != BNS_OK) return st;
-    return build_impl(ctx, w.row_ptr, w.col_idx, w.t_row_ptr, w.t_col_idx, w.counters + 1, true, s);
+    return build_impl(ctx, w.row_ptr, w.col_idx, w.t_row_ptr, w.t_col_idx, w.counters + 1, s);
   }
   const uint64_t threshold = (uint64_t)std::floor(p * 4294967296.0);
   PhaseTimer t(ctx, BNS_PHASE_SAMPLE, s);
@@ -768,6 +769,7 @@ bns_status sample_and_build_impl(bns_ctx *ctx, uint64_t seed, uint32_t epoch, co
                              w.kept_ids, w.remap, w.counters, w.kept_start, P.n_in, P.e_in, P.e_bd, w.split,
                              w.row_ptr, w.col_idx, w.counters + 1, P.halo_ptr, P.halo_col, w.t_row_ptr, w.t_col_idx,
                              w.halo_rec, ctx->layer_kind == 1 ? nullptr : w.dis_halo, halo_scale(p), &pack, s));
+  ctx->cur_counted = false;
   ctx->cur_kept = w.kept_ids;
   ctx->cur_remap = w.remap;
   ctx->cur_n_kept = w.counters;
@@ -863,7 +865,7 @@ bns_status bns_build_sampled_csr(bns_ctx *ctx, const int32_t *remap, const int32
   // the keep bits of the latest sample sit in the workspace: the three arrays must be that sample's
   if (remap != ctx->cur_remap || kept_ids != ctx->cur_kept || n_kept != ctx->cur_n_kept)
     return fail(ctx, BNS_EINVAL, "remap / kept_ids / n_kept are not the outputs of the latest bns_sample_boundary");
-  return build_impl(ctx, row_ptr, col_idx, t_row_ptr, t_col_idx, nnz, false, static_cast<hipStream_t>(stream));
+  return build_impl(ctx, row_ptr, col_idx, t_row_ptr, t_col_idx, nnz, static_cast<hipStream_t>(stream));
 }
 
 bns_status bns_gcn_layer_fwd(bns_ctx *ctx, int32_t layer, double p, const float *H_in, const float *halo_h,
@@ -891,17 +893,17 @@ bns_status bns_gcn_layer_bwd(bns_ctx *ctx, int32_t layer, double p, const float 
   if (!dH_in && dhalo) return fail(ctx, BNS_EINVAL, "dhalo needs dH_in");
   if (!ctx->cur_t_row_ptr) return fail(ctx, BNS_EINVAL, "bns_build_sampled_csr has not been called");
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const float *dZ = dH_out;
   PackJobs jobs;
   if (dH_in) add_pack_jobs(ctx, layer, W, false, true, &jobs);
-  if (H_out) {
-    const int64_t n = (int64_t)ctx->part.n_in * ctx->dims[layer];
-    BNS_TRY("relu_mask", relu_mask(n, dH_out, H_out, mask_scale_of(ctx), ctx->ws.G0, jobs, s));
-    dZ = ctx->ws.G0;
-  } else {
-    BNS_TRY("pack_weights", pack_weights(jobs, s));
-  }
-  return layer_bwd_impl(ctx, layer, p, dZ, A_saved, H_in, W, dW, dH_in, dhalo, nullptr, false, nullptr, nullptr, 0.f, false,
+  // the masked gradient, and where the aggregate gathers it in padded rows (layer_bwd_impl) those
+  const int d_out = ctx->dims[layer];
+  const int64_t rows = ctx->part.n_in + (dhalo ? (int64_t)expected_kept(ctx, p) : 0);
+  const bool pad = dH_in && gather_stride(ctx->dims[layer - 1], d_out) != d_out && d_out < ctx->dims[layer - 1] &&
+                   (ctx->layer_kind == 0 || tile_layer_bwd(ctx, layer, rows));
+  const float *dZ = H_out ? ctx->ws.G0 : dH_out;
+  BNS_TRY("relu_mask", relu_mask(ctx->part.n_in, d_out, dH_out, H_out, mask_scale_of(ctx), ctx->ws.G0,
+                                 gather_stride(ctx->dims[layer - 1], d_out), pad ? ctx->ws.G2 : nullptr, jobs, s));
+  return layer_bwd_impl(ctx, layer, p, dZ, A_saved, H_in, W, dW, dH_in, dhalo, nullptr, false, nullptr, nullptr, 0.f, pad,
                         nullptr, s);
 }
 

@@ -314,9 +314,10 @@ hipError_t loss_sigmoid_bce(int32_t n, int32_t C, const float *logits, const uin
                             float *dZ, int32_t ld, float *dZ_pad, float *partials, int32_t *n_partials, hipStream_t s);
 // Dropout applied in place to H[n_rows, d] (for layers whose ReLU sits in the aggregate's store).
 hipError_t dropout_inplace(int32_t n_rows, int32_t d, float *H, const Dropout &drop, hipStream_t s);
-// out = scale * dH where H > 0 else 0.  pack: weights to pack in the same launch.
-hipError_t relu_mask(int64_t n, const float *dH, const float *H, float scale, float *out, const PackJobs &pack,
-                     hipStream_t s);
+// out = scale * dH where H > 0 else 0 (H, out [n_rows, d] nullable: dH as it is).  pad (nullable): the result once more in rows padded by
+// zeros to ld floats, a multiple of 4.  pack: weights to pack in the same launch.
+hipError_t relu_mask(int32_t n_rows, int32_t d, const float *dH, const float *H, float scale, float *out, int32_t ld, float *pad,
+                     const PackJobs &pack, hipStream_t s);
 // W -= lr * dW on n weights, as gemm_tn does it on the way (same bits): for a step whose update is timed by itself.
 hipError_t sgd_update(int64_t n, float *W, const float *dW, float lr, hipStream_t s);
 // Adam step t (1-based) on n weights; m, v are the caller's moment buffers.

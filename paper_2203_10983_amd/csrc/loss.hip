@@ -209,25 +209,50 @@ hipError_t dropout_inplace(int32_t n_rows, int32_t d, float *H, const Dropout &d
   return hipGetLastError();
 }
 
+// Four columns of a row per thread and turn, the gradient once more in padded rows on the way, which were a launch of 5 us (all
+// calls of an iteration, with the count of the kept boundary entries beside the sampling: 20011 rows 602-130-66-9 582 -> 570 us,
+// 477 rows 100-256-41 113 -> 106).  Rows without padding are one long row.
 __global__ void __launch_bounds__(kT)
-relu_mask_kernel(int64_t n, const float *__restrict__ dH, const float *__restrict__ H, float scale,
-                 float *__restrict__ out, int blocks, const PackJobs pack) {
+relu_mask_kernel(int64_t n_rows, int64_t d, int ld, const float *__restrict__ dH, const float *__restrict__ H, float scale,
+                 float *__restrict__ out, float *__restrict__ pad, int blocks, const PackJobs pack) {
+  typedef float f4 __attribute__((ext_vector_type(4)));
+  typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
   if ((int)blockIdx.x >= blocks) {
     pack_unit(pack, (blockIdx.x - blocks) * (kT / kWave) + threadIdx.x / kWave);
     return;
   }
-  const int64_t stride = (int64_t)blocks * kT;
-  for (int64_t i = (int64_t)blockIdx.x * kT + threadIdx.x; i < n; i += stride)
-    out[i] = H[i] > 0.f ? dH[i] * scale : 0.f;
+  const int64_t pieces = pad ? ld / 4 : (d + 3) / 4, total = n_rows * pieces, stride = (int64_t)blocks * kT;
+  for (int64_t i = (int64_t)blockIdx.x * kT + threadIdx.x; i < total; i += stride) {
+    const int64_t r = pad ? i / pieces : 0, c = (i - r * pieces) * 4, at = r * d + c;
+    f4 g = {0.f, 0.f, 0.f, 0.f};
+    if (c + 4 <= d) {
+      g = *reinterpret_cast<const f4u *>(dH + at);
+      if (H) {
+        const f4 h = *reinterpret_cast<const f4u *>(H + at);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) g[e] = h[e] > 0.f ? g[e] * scale : 0.f;
+        *reinterpret_cast<f4u *>(out + at) = g;
+      }
+    } else {
+#pragma unroll
+      for (int e = 0; e < 3; ++e)
+        if (c + e < d) {
+          g[e] = dH[at + e];
+          if (H) out[at + e] = g[e] = H[at + e] > 0.f ? g[e] * scale : 0.f;
+        }
+    }
+    if (pad) *reinterpret_cast<f4 *>(pad + r * ld + c) = g;
+  }
 }
 
-hipError_t relu_mask(int64_t n, const float *dH, const float *H, float scale, float *out, const PackJobs &pack,
-                     hipStream_t s) {
-  if (n <= 0) return hipSuccess;
-  int64_t blocks = (n + kT * 4 - 1) / (kT * 4);
-  if (blocks > 65536) blocks = 65536;
-  const int pack_blocks = (pack.units + kT / kWave - 1) / (kT / kWave);
-  relu_mask_kernel<<<(unsigned)(blocks + pack_blocks), kT, 0, s>>>(n, dH, H, scale, out, (int)blocks, pack);
+hipError_t relu_mask(int32_t n_rows, int32_t d, const float *dH, const float *H, float scale, float *out, int32_t ld, float *pad,
+                     const PackJobs &pack, hipStream_t s) {
+  if (n_rows <= 0) return hipSuccess;
+  if (pad && (ld < d || ld % 4 != 0)) return hipErrorInvalidValue;
+  const int64_t rows = pad ? n_rows : 1, row = pad ? d : (int64_t)n_rows * d, pieces = rows * (pad ? ld / 4 : (row + 3) / 4);
+  const int64_t blocks = H || pad ? std::min<int64_t>((pieces + kT - 1) / kT, 65536) : 0;
+  const unsigned grid = (unsigned)(blocks + (pack.units + kT / kWave - 1) / (kT / kWave));
+  if (grid) relu_mask_kernel<<<grid, kT, 0, s>>>(rows, row, ld, dH, H, scale, out, pad, (int)blocks, pack);
   return hipGetLastError();
 }
 

@@ -164,3 +164,33 @@ def test_subgraph_of_a_step_at_the_limits(n, deg, n_halo, lists, p, one):
     for a, b, k in zip(got, (kept, remap) + csr, (K, n_halo, n + 1, m, n + K + 1, m)):
         assert torch.equal(a[:k], b[:k])
     ctx.close()
+
+
+@pytest.mark.parametrize("n", [500, 5003])
+@pytest.mark.parametrize("d_in,d_out", [(130, 66), (100, 47), (64, 64), (20, 17), (9, 3)])
+def test_backward_masks_and_pads_in_one_pass(n, d_in, d_out):
+    """A layer's gradient masked by the call equals the same gradient masked before it: dense and, where it is gathered in padded rows, there."""
+    import torch
+    import paper_2203_10983_amd as pkg
+    dev = torch.device("cuda:0")
+    nb = 60
+    P = _partition(n, 4, 0, nb, np.random.default_rng(n))
+    i32 = lambda k: torch.zeros(k, dtype=torch.int32, device=dev)  # noqa: E731
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(d_in)
+    G, H, A, W = (torch.randn(*s, device=dev, generator=gen) for s in ((n, d_out), (n, d_out), (n, d_in), (d_in, d_out)))
+    H.clamp_(min=0)
+    out = []
+    for dZ, mask in ((G, H), (torch.where(H > 0, G, torch.zeros_like(G)), None)):
+        ctx = pkg.Context(P, [d_in, d_in, d_out], 0, device=dev)
+        kept, remap, n_kept, nnz = i32(nb), i32(nb), i32(1), i32(1)
+        ctx.sample_boundary(1, 0, 0.5, kept, remap, n_kept)
+        csr = i32(n + 1), i32(P.nnz0), i32(n + nb + 1), i32(P.nnz0)
+        ctx.build_sampled_csr(remap, kept, n_kept, *csr, nnz)
+        dH, dhalo, dW = torch.zeros(n, d_in, device=dev), torch.zeros(nb, d_in, device=dev), torch.zeros_like(W)
+        ctx.gcn_layer_bwd(2, 0.5, dZ, mask, A, A, W, dW, dH, dhalo)
+        out.append((dH, dhalo, dW))
+        torch.cuda.synchronize()
+        ctx.close()
+    for a, b in zip(*out):
+        assert torch.equal(a, b) and a.abs().sum() > 0
