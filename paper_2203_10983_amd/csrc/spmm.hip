@@ -8,7 +8,7 @@
 // transposed pattern, and every output element is produced in a fixed order.
 //
 // Inside a segment the lanes span the feature dimension with VEC-wide loads, so every neighbour
-// row is read as one contiguous, coalesced piece.  When a feature row needs fewer than 64 lanes
+// row is read as one contiguous, coalesced piece (four floats to a lane, whatever the width, from 9 on).  When a feature row needs fewer than 64 lanes
 // (LPR = lanes per row < 64) the wavefront walks 64/LPR neighbours at once and folds the partial
 // sums at the end.  Column indices and their weights are fetched 64 at a time, one per lane,
 // and handed to the loop by cross-lane reads, four neighbours in flight per step.
@@ -22,9 +22,10 @@ namespace bns {
 // BLOCK: workgroups of kBlockWaves wavefronts; the first a.n_block_rows of them own a multi-segment row each, one
 // wavefront per segment, and add the partial sums in LDS (same order as spmm_combine_kernel, same bits).
 constexpr int kBlockWaves = 8;
-template <int VEC, int MAXCH, int LPR, bool NARROW = false, bool BLOCK = false>
+template <int VEC, int MAXCH, int LPR, bool NARROW = false, bool BLOCK = false, bool RAGGED = false>
 __global__ void __launch_bounds__(BLOCK ? kBlockWaves * kWave : 256, MAXCH == 1 ? 8 : 1) spmm_kernel(const SpmmArgs) {
-  using V = typename Vec<VEC>::T;
+  using V = typename Vec<VEC, RAGGED>::T;
+  constexpr int kCut = RAGGED ? VEC - 1 : 0;  // (a last piece that is not whole)
   constexpr int kWaves = BLOCK ? kBlockWaves : 4;
   const int lane = lane_id();
   const int g = lane / LPR, sl = lane % LPR;
@@ -41,10 +42,11 @@ __global__ void __launch_bounds__(BLOCK ? kBlockWaves * kWave : 256, MAXCH == 1 
     const int n_rows = start.n_block_rows;
     if (bid < n_rows) {
       ArgBlock &a = unit_args();
-      if (bid >= a.plan.n_multi) return;
       extern __shared__ __attribute__((aligned(16))) float block_part[];
-      const int nvec = start.d_slice / VEC;
-      const int row = scalar_load(a.plan.mrow, bid);
+      const int ds = start.d_slice, width = RAGGED ? min(ds, a.d - d_off) : ds, nvec = (width + kCut) / VEC;
+      const int n_multi = a.plan.n_multi;  // (asked for beside the row, which the others wait for)
+      const int row = scalar_load(a.plan.mrow, min(bid, n_multi - 1));
+      if (bid >= n_multi) return;
       const int2 ee = scalar_load_pair(a.row_ptr, row);
       int e0 = ee.x, e1 = ee.y;
       const InnerWeights iw = inner_weights(a, row, e0, e1);
@@ -56,13 +58,13 @@ __global__ void __launch_bounds__(BLOCK ? kBlockWaves * kWave : 256, MAXCH == 1 
       float acc[MAXCH][VEC];
       if (wid < nseg) {
         const int b = min(e1, e0 + wid * chunk);
-        gather_segment<VEC, MAXCH, LPR>(a, row, iw, b, min(e1, b + chunk), d_off, nvec, acc);
+        gather_segment<VEC, MAXCH, LPR, RAGGED>(a, row, iw, b, min(e1, b + chunk), d_off, nvec, acc, width);
         if (g == 0) {
 #pragma unroll
           for (int c = 0; c < MAXCH; ++c)
             if (c * kWave + sl < nvec)
 #pragma unroll
-              for (int i = 0; i < VEC; ++i) block_part[wid * nvec * VEC + (c * kWave + sl) * VEC + i] = acc[c][i];
+              for (int i = 0; i < VEC; ++i) block_part[wid * ds + piece_at<VEC, RAGGED>(c * kWave + sl, width) + i] = acc[c][i];
         }
       }
       __syncthreads();
@@ -76,8 +78,8 @@ __global__ void __launch_bounds__(BLOCK ? kBlockWaves * kWave : 256, MAXCH == 1 
         for (int c = 0; c < MAXCH; ++c)
           if (c * kWave + lane < nvec)
 #pragma unroll
-            for (int i = 0; i < VEC; ++i) acc[c][i] += block_part[s * nvec * VEC + (c * kWave + lane) * VEC + i];
-      finish_row<VEC, MAXCH, NARROW>(unit_args(), row, lane, nvec, d_off, acc);
+            for (int i = 0; i < VEC; ++i) acc[c][i] += block_part[s * ds + piece_at<VEC, RAGGED>(c * kWave + lane, width) + i];
+      finish_row<VEC, MAXCH, NARROW, RAGGED>(unit_args(), row, lane, nvec, d_off, acc, width);
       return;
     }
     bid -= n_rows;
@@ -102,7 +104,7 @@ __global__ void __launch_bounds__(BLOCK ? kBlockWaves * kWave : 256, MAXCH == 1 
   }
   for (; unit < end; unit += step) {
     ArgBlock &a = unit_args();
-    const int nvec = a.head.d_slice / VEC;
+    const int width = RAGGED ? min(a.head.d_slice, a.d - d_off) : a.head.d_slice, nvec = (width + kCut) / VEC;
     int row = a.n_split + (unit - a.head.n_units), slot = -1;
     if (unit < a.head.n_units) {
       const int2 u = scalar_load(a.units, unit);
@@ -126,15 +128,15 @@ __global__ void __launch_bounds__(BLOCK ? kBlockWaves * kWave : 256, MAXCH == 1 
     }
 
     float acc[MAXCH][VEC];
-    gather_segment<VEC, MAXCH, LPR>(a, row, iw, e0, e1, d_off, nvec, acc);
+    gather_segment<VEC, MAXCH, LPR, RAGGED>(a, row, iw, e0, e1, d_off, nvec, acc, width);
 
     ArgBlock &b = unit_args();
     if (g != 0) {
       // only the first lane group holds the folded sums
     } else if (slot < 0) {
-      finish_row<VEC, MAXCH, NARROW>(b, row, sl, nvec, d_off, acc);
+      finish_row<VEC, MAXCH, NARROW, RAGGED>(b, row, sl, nvec, d_off, acc, width);
     } else {
-      V *part = reinterpret_cast<V *>(b.partials + (size_t)slot * b.d + d_off);
+      float *part = b.partials + (size_t)slot * b.d + d_off;
 #pragma unroll
       for (int c = 0; c < MAXCH; ++c) {
         const int iv = c * kWave + sl;
@@ -143,7 +145,7 @@ __global__ void __launch_bounds__(BLOCK ? kBlockWaves * kWave : 256, MAXCH == 1 
           float *po = reinterpret_cast<float *>(&o);
 #pragma unroll
           for (int i = 0; i < VEC; ++i) po[i] = acc[c][i];
-          part[iv] = o;
+          *reinterpret_cast<V *>(part + piece_at<VEC, RAGGED>(iv, width)) = o;
         }
       }
     }
@@ -151,15 +153,15 @@ __global__ void __launch_bounds__(BLOCK ? kBlockWaves * kWave : 256, MAXCH == 1 
 }
 
 // Rows cut into several segments: add the partial sums in ascending segment order.
-template <int VEC, int MAXCH, bool NARROW = false>
+template <int VEC, int MAXCH, bool NARROW = false, bool RAGGED = false>
 __global__ void __launch_bounds__(256) spmm_combine_kernel(const SpmmArgs a) {
-  using V = typename Vec<VEC>::T;
+  using V = typename Vec<VEC, RAGGED>::T;
   const int lane = lane_id();
   const int j = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (j >= a.plan.n_multi) return;
   const int row = a.plan.mrow[j];
   const int nseg = a.plan.seg_ptr[row + 1] - a.plan.seg_ptr[row];
-  const int d = a.d, nvec = d / VEC;
+  const int d = a.d, nvec = (d + (RAGGED ? VEC - 1 : 0)) / VEC;
   const float *part = a.partials + (size_t)a.plan.part_ptr[row] * d;
   float acc[MAXCH][VEC];
 #pragma unroll
@@ -171,11 +173,11 @@ __global__ void __launch_bounds__(256) spmm_combine_kernel(const SpmmArgs a) {
     V x[CU][MAXCH];
 #pragma unroll
     for (int t = 0; t < CU; ++t) {
-      const V *ps = reinterpret_cast<const V *>(part + (size_t)(s0 + t) * d);
+      const float *ps = part + (size_t)(s0 + t) * d;
 #pragma unroll
       for (int c = 0; c < MAXCH; ++c) {
         const int iv = c * kWave + lane;
-        x[t][c] = (s0 + t < nseg && iv < nvec) ? ps[iv] : V{};
+        x[t][c] = (s0 + t < nseg && iv < nvec) ? *reinterpret_cast<const V *>(ps + piece_at<VEC, RAGGED>(iv, d)) : V{};
       }
     }
 #pragma unroll
@@ -187,11 +189,11 @@ __global__ void __launch_bounds__(256) spmm_combine_kernel(const SpmmArgs a) {
         for (int i = 0; i < VEC; ++i) acc[c][i] += px[i];
       }
   }
-  finish_row<VEC, MAXCH, NARROW>(a, row, lane, nvec, 0, acc);
+  finish_row<VEC, MAXCH, NARROW, RAGGED>(a, row, lane, nvec, 0, acc, d);
 }
 
 
-template <int VEC>
+template <int VEC, bool RAGGED>
 static hipError_t launch_spmm_vec(const SpmmArgs &a_in, int64_t extra_rows, bool multi_only, int32_t avg_len, bool transposed, hipStream_t s) {
   SpmmArgs a = a_in;
   // multi_only: the segments of the multi-segment rows, i.e. the partial-sum slots
@@ -212,7 +214,7 @@ static hipError_t launch_spmm_vec(const SpmmArgs &a_in, int64_t extra_rows, bool
   if (VEC == 4 && !multi_only) {
     auto slices = [&](int target) {
       int l = 0;
-      while (l < 3 && (a.d >> (l + 1)) >= target && a.d % (VEC << (l + 1)) == 0) ++l;
+      while (l < 3 && (a.d >> (l + 1)) >= target && (RAGGED || a.d % (VEC << (l + 1)) == 0)) ++l;
       return l;
     };
     ls = slices(128);
@@ -222,7 +224,7 @@ static hipError_t launch_spmm_vec(const SpmmArgs &a_in, int64_t extra_rows, bool
     if (avg_len >= from) ls = slices(64);
   }
   a.head.log2_slices = ls;
-  a.head.d_slice = a.d >> ls;
+  a.head.d_slice = RAGGED && ls > 0 ? ((a.d + (1 << ls) - 1) / (1 << ls) + 3) / 4 * 4 : a.d >> ls;  // (the last one of a ragged row is narrower)
   // The pass over the partial sums is a launch of 3 to 5 us.  Where the longest row has few segments, a workgroup per such
   // row saves it; its workgroups of eight wavefronts wait for their longest row, which costs more where wavefronts are many and
   // run at the rate of the LDS or vector pipes, i.e. in slices of 33 to 64 floats: those cross at about 20000 units (12000
@@ -232,8 +234,8 @@ static hipError_t launch_spmm_vec(const SpmmArgs &a_in, int64_t extra_rows, bool
   const bool block_rows = !multi_only && a.plan.n_multi > 0 && a.plan.max_seg <= kBlockWaves &&
                           ((int64_t)a.plan.n_seg << ls) <= (narrow_slice ? 20480 : 65536);
   const int waves = block_rows ? kBlockWaves : 4;
-  const int nvec = a.head.d_slice / VEC;
-  const int full_nvec = a.d / VEC;
+  const int nvec = (a.head.d_slice + VEC - 1) / VEC;
+  const int full_nvec = (a.d + VEC - 1) / VEC;
   // One wavefront per static segment.  The kept boundary rows are a few entries each.  Where all wavefronts go on to them
   // after their segment, the launch ends in a long stretch of short rows, bound by the rate at which workgroups start, while
   // the wavefronts wait for the store of their first row (19 800 rows in four slices beside 52 800 segments: 110 of 640 us).
@@ -280,7 +282,7 @@ static hipError_t launch_spmm_vec(const SpmmArgs &a_in, int64_t extra_rows, bool
     a.head.turn_share = in_turn ? (uint32_t)(((uint64_t)1 << (32 + ls)) / each) : 0;  // each > 2^ls then
   }
   if (a.d_store != a.d) {  // padded sources, dense narrower outputs: d < 128, four floats per lane
-    if constexpr (VEC == 4) {
+    if constexpr (VEC == 4 && !RAGGED) {
 #define BNS_SPMM_NARROW(LPR)                                                                                \
   do {                                                                                                      \
     if (block_rows) spmm_kernel<4, 1, LPR, true, true><<<blocks, kBlockWaves * kWave, block_lds, s>>>(a); \
@@ -296,42 +298,59 @@ static hipError_t launch_spmm_vec(const SpmmArgs &a_in, int64_t extra_rows, bool
     }
     return hipErrorInvalidValue;
   }
-#define BNS_SPMM(MAXCH, LPR)                                                                                     \
-  do {                                                                                                           \
-    if (block_rows) spmm_kernel<VEC, MAXCH, LPR, false, true><<<blocks, kBlockWaves * kWave, block_lds, s>>>(a); \
-    else spmm_kernel<VEC, MAXCH, LPR><<<blocks, 256, 0, s>>>(a);                                               \
+#define BNS_SPMM(MAXCH, LPR)                                                                                              \
+  do {                                                                                                                    \
+    if (block_rows) spmm_kernel<VEC, MAXCH, LPR, false, true, RAGGED><<<blocks, kBlockWaves * kWave, block_lds, s>>>(a); \
+    else spmm_kernel<VEC, MAXCH, LPR, false, false, RAGGED><<<blocks, 256, 0, s>>>(a);                                  \
   } while (0)
-  if (nvec <= 1) BNS_SPMM(1, 1);
-  else if (nvec <= 2) BNS_SPMM(1, 2);
-  else if (nvec <= 4) BNS_SPMM(1, 4);
-  else if (nvec <= 8) BNS_SPMM(1, 8);
-  else if (nvec <= 16) BNS_SPMM(1, 16);
-  else if (nvec <= 32) BNS_SPMM(1, 32);
-  else if (nvec <= 64) BNS_SPMM(1, 64);
-  else if (nvec <= 128) BNS_SPMM(2, 64);
-  else if (nvec <= 256) BNS_SPMM(4, 64);
-  else if (nvec <= 384) BNS_SPMM(6, 64);
-  else if (nvec <= 512) BNS_SPMM(8, 64);
-  else return hipErrorInvalidValue;
-#undef BNS_SPMM
-  if (cblocks) {
-#define BNS_COMBINE(MAXCH) spmm_combine_kernel<VEC, MAXCH><<<cblocks, 256, 0, s>>>(a)
-    if (full_nvec <= 64) BNS_COMBINE(1);
-    else if (full_nvec <= 128) BNS_COMBINE(2);
-    else if (full_nvec <= 256) BNS_COMBINE(4);
-    else if (full_nvec <= 384) BNS_COMBINE(6);
-    else BNS_COMBINE(8);
-#undef BNS_COMBINE
+#define BNS_COMBINE(MAXCH) spmm_combine_kernel<VEC, MAXCH, false, RAGGED><<<cblocks, 256, 0, s>>>(a)
+  if constexpr (VEC < 4) {
+    if (nvec <= 1) BNS_SPMM(1, 1);
+    else if (nvec <= 2) BNS_SPMM(1, 2);
+    else if (nvec <= 4) BNS_SPMM(1, 4);
+    else if (nvec <= 8) BNS_SPMM(1, 8);
+    else return hipErrorInvalidValue;
+    if (cblocks) BNS_COMBINE(1);
+  } else {
+    if (nvec <= 1) BNS_SPMM(1, 1);
+    else if (nvec <= 2) BNS_SPMM(1, 2);
+    else if (nvec <= 4) BNS_SPMM(1, 4);
+    else if (nvec <= 8) BNS_SPMM(1, 8);
+    else if (nvec <= 16) BNS_SPMM(1, 16);
+    else if (nvec <= 32) BNS_SPMM(1, 32);
+    else if (nvec <= 64) BNS_SPMM(1, 64);
+    else if (nvec <= 128) BNS_SPMM(2, 64);
+    else if (nvec <= 192) BNS_SPMM(3, 64);
+    else if (nvec <= 256) BNS_SPMM(4, 64);
+    else if (nvec <= 384) BNS_SPMM(6, 64);
+    else if (nvec <= 512) BNS_SPMM(8, 64);
+    else return hipErrorInvalidValue;
+    if (cblocks) {
+      if (full_nvec <= 64) BNS_COMBINE(1);
+      else if (full_nvec <= 128) BNS_COMBINE(2);
+      else if (full_nvec <= 256) BNS_COMBINE(4);
+      else if (full_nvec <= 384) BNS_COMBINE(6);
+      else BNS_COMBINE(8);
+    }
   }
+#undef BNS_COMBINE
+#undef BNS_SPMM
   return hipGetLastError();
 }
 
 static hipError_t launch_spmm(const SpmmArgs &a, int64_t extra_rows, bool multi_only, int32_t avg_len, bool transposed, hipStream_t s) {
   if (a.d_store != a.d && (a.d_store < 1 || a.d_store > a.d || a.d >= 128 || a.d % 4 != 0 || a.mask_src || a.init))
     return hipErrorInvalidValue;  // padded sources: narrow rows without mask or initial value only
-  if (a.d % 4 == 0) return launch_spmm_vec<4>(a, extra_rows, multi_only, avg_len, transposed, s);
-  if (a.d % 2 == 0) return launch_spmm_vec<2>(a, extra_rows, multi_only, avg_len, transposed, s);
-  return launch_spmm_vec<1>(a, extra_rows, multi_only, avg_len, transposed, s);
+  if (a.d % 4 == 0) return launch_spmm_vec<4, false>(a, extra_rows, multi_only, avg_len, transposed, s);
+  // Widths that are no multiple of 4: 16-byte loads at 4-byte alignment, and slices as for the others, where loads of 8 or 4 bytes
+  // took up to four times as many instructions (130 floats: 65 lanes, a second load for the last one) and could not be
+  // sliced.  Forward and transposed, us: 60000 rows of 45 entries, 31 floats 75 -> 62 and 130 -> 91, 66 120 -> 108 and 225 -> 144, 130
+  // 232 -> 197 and 443 -> 235, 258 413 -> 403 and 660 -> 404, 602 907 -> 855 and 1235 -> 846; 20011 rows of 14, 9 floats the same,
+  // 66 34 -> 28 and 45 -> 35, 130 56 -> 39 and 81 -> 50, 602 145 -> 111 and 189 -> 126.  Up to 8 floats a row is one or two
+  // pieces, of which a wavefront has more than there are entries (20011 rows, 6 floats: 17.7 and 19.8 us, in pieces of 16 bytes 18.5 and 20.6).
+  if (a.d > 8) return launch_spmm_vec<4, true>(a, extra_rows, multi_only, avg_len, transposed, s);
+  if (a.d % 2 == 0) return launch_spmm_vec<2, false>(a, extra_rows, multi_only, avg_len, transposed, s);
+  return launch_spmm_vec<1, false>(a, extra_rows, multi_only, avg_len, transposed, s);
 }
 
 hipError_t spmm_fwd(const SegPlan &plan, int32_t n_in, int32_t d, const int32_t *row_ptr,

@@ -8,16 +8,25 @@
 
 namespace bns {
 
-typedef float v2f __attribute__((ext_vector_type(2)));
 typedef float v4f __attribute__((ext_vector_type(4)));
-template <int VEC> struct Vec;
+typedef float v4fu __attribute__((ext_vector_type(4), aligned(4)));
+typedef float v2f __attribute__((ext_vector_type(2)));
+template <int VEC, bool RAGGED = false> struct Vec;
 template <> struct Vec<1> { using T = float; };
 template <> struct Vec<2> { using T = v2f; };
 template <> struct Vec<4> { using T = v4f; };
+// RAGGED: rows of a width that is no multiple of 4 still go four floats to a lane, at any alignment of 4 bytes: the last piece
+// of a row or slice is moved back to end with it, and the columns that it shares with the piece before it come out of both lanes alike.
+template <> struct Vec<4, true> { using T = v4fu; };
+
+// First column of piece iv of a row (or slice of one) of `width` floats.
+template <int VEC, bool RAGGED>
+__device__ __forceinline__ int piece_at(int iv, int width) {
+  return RAGGED ? min(iv * VEC, width - VEC) : iv * VEC;
+}
 
 template <int VEC>
-__device__ __forceinline__ void vec_fma(float (&acc)[VEC], float w, const typename Vec<VEC>::T &v) {
-  const float *p = reinterpret_cast<const float *>(&v);
+__device__ __forceinline__ void vec_fma(float (&acc)[VEC], float w, const float *p) {
 #pragma unroll
   for (int i = 0; i < VEC; ++i) acc[i] = fmaf(w, p[i], acc[i]);
 }
@@ -128,11 +137,11 @@ inline SpmmArgs spmm_fwd_args(const SegPlan &plan, int32_t n_in, int32_t d, cons
 }
 
 // Scale, optional ReLU mask and store of one finished row slice held as acc[c][i].
-// NARROW: the sources are padded (d_store < d), the output rows are dense with d_store columns.
-template <int VEC, int MAXCH, bool NARROW = false, typename Args>
+// NARROW: the sources are padded (d_store < d), the output rows are dense with d_store columns.  width: of the slice, for RAGGED rows.
+template <int VEC, int MAXCH, bool NARROW = false, bool RAGGED = false, typename Args>
 __device__ __forceinline__ void finish_row(Args &a, int row, int sl, int nvec, int d_off,
-                                           float (&acc)[MAXCH][VEC]) {
-  using V = typename Vec<VEC>::T;
+                                           float (&acc)[MAXCH][VEC], int width = 0) {
+  using V = typename Vec<VEC, RAGGED>::T;
   const int d = a.d, ds = NARROW ? (int)a.d_store : d;
   float scale;
   float *out;
@@ -153,12 +162,13 @@ __device__ __forceinline__ void finish_row(Args &a, int row, int sl, int nvec, i
   for (int c = 0; c < MAXCH; ++c) {
     const int iv = c * kWave + sl;
     if (iv < nvec) {
+      const int at = piece_at<VEC, RAGGED>(iv, width);
       V o;
       float *po = reinterpret_cast<float *>(&o);
 #pragma unroll
       for (int i = 0; i < VEC; ++i) po[i] = acc[c][i];
       if (init) {
-        const V x0 = reinterpret_cast<const V *>(init)[iv];
+        const V x0 = *reinterpret_cast<const V *>(init + at);
         const float *p0 = reinterpret_cast<const float *>(&x0);
 #pragma unroll
         for (int i = 0; i < VEC; ++i) po[i] += p0[i];
@@ -170,7 +180,7 @@ __device__ __forceinline__ void finish_row(Args &a, int row, int sl, int nvec, i
         for (int i = 0; i < VEC; ++i) po[i] = fmaxf(po[i], 0.f);
       }
       if (mask) {
-        const V m = __builtin_nontemporal_load(reinterpret_cast<const V *>(mask) + iv);  // read once
+        const V m = __builtin_nontemporal_load(reinterpret_cast<const V *>(mask + at));  // read once
         const float *pm = reinterpret_cast<const float *>(&m);
 #pragma unroll
         for (int i = 0; i < VEC; ++i) po[i] = pm[i] > 0.f ? po[i] : 0.f;
@@ -178,7 +188,7 @@ __device__ __forceinline__ void finish_row(Args &a, int row, int sl, int nvec, i
       if constexpr (!NARROW) {
         // streamed out: a non-temporal store leaves the L2 to the feature rows being gathered
         // (measured: 1.7 % of a training step on the largest workload)
-        __builtin_nontemporal_store(o, reinterpret_cast<V *>(out) + iv);
+        __builtin_nontemporal_store(o, reinterpret_cast<V *>(out + at));
       } else {  // padded sources: the output rows are dense and hold the first ds columns
 #pragma unroll
         for (int i = 0; i < VEC; ++i)
@@ -245,21 +255,21 @@ __device__ __forceinline__ unsigned row_bcast(unsigned x) {
 
 // 4 VEC bytes at an address that was put together from its halves.  The address space has to be said: the compiler
 // takes such a pointer for a generic one and makes a flat load of it, which also waits for the LDS pipe.
-template <typename V>
-__device__ __forceinline__ V load_row_piece(unsigned hi, unsigned lo, int at) {
-  using G = const __attribute__((address_space(1))) V;
+template <int VEC, bool RAGGED>
+__device__ __forceinline__ typename Vec<VEC, RAGGED>::T load_row_piece(unsigned hi, unsigned lo, int at) {
+  using V = typename Vec<VEC, RAGGED>::T;
   typedef unsigned u2 __attribute__((ext_vector_type(2)));
-  return *reinterpret_cast<G *>(__builtin_bit_cast(unsigned long long, (u2){lo, hi}) + (unsigned)at * 4u);
+  return *reinterpret_cast<const __attribute__((address_space(1))) V *>(__builtin_bit_cast(unsigned long long, (u2){lo, hi}) + (unsigned)at * 4u);
 }
 
 // acc += sum over the cnt <= 64 entries of a batch, held one per lane (batch_entry; address p_l, weight w_l, zero past
 // the end), of w * feature row.  The lanes span the feature dimension (VEC floats per lane, MAXCH pieces of 64
 // lanes); with LPR < 64 lanes per row the wavefront walks EP = 64/LPR neighbours at once, UNR loads in flight, and
-// every lane group keeps its own partial sums (fold_groups adds them).
-template <int VEC, int MAXCH, int LPR, bool DPP = false>
+// every lane group keeps its own partial sums (fold_groups adds them).  width: of the slice, for RAGGED rows.
+template <int VEC, int MAXCH, int LPR, bool DPP = false, bool RAGGED = false>
 __device__ __forceinline__ void gather_batch(unsigned long long p_l, float w_l, int cnt, int nvec,
-                                             float (&acc)[MAXCH][VEC]) {
-  using V = typename Vec<VEC>::T;
+                                             float (&acc)[MAXCH][VEC], int width = 0) {
+  using V = typename Vec<VEC, RAGGED>::T;
   static_assert(!DPP || (MAXCH == 1 && LPR == 16), "a feature row per DPP row of 16 lanes");
   constexpr int EP = kWave / LPR;  // neighbours walked at once
   constexpr int UNR = MAXCH == 1 && LPR >= 16 ? 8 : 4;
@@ -299,9 +309,10 @@ __device__ __forceinline__ void gather_batch(unsigned long long p_l, float w_l, 
         const int iv = c * kWave + sl;
         if (TAIL || MAXCH > 1) {
           v[t][c] = V{};
-          if ((EP == 1 || (t0 + t) * EP + g < cnt) && iv < nvec) v[t][c] = load_row_piece<V>(hi, lo, iv * VEC);
+          if ((EP == 1 || (t0 + t) * EP + g < cnt) && iv < nvec)
+            v[t][c] = load_row_piece<VEC, RAGGED>(hi, lo, piece_at<VEC, RAGGED>(iv, width));
         } else {  // lanes past the row's pieces repeat the last one and store nothing
-          v[t][c] = load_row_piece<V>(hi, lo, min(iv, nvec - 1) * VEC);
+          v[t][c] = load_row_piece<VEC, RAGGED>(hi, lo, RAGGED ? piece_at<VEC, RAGGED>(iv, width) : min(iv, nvec - 1) * VEC);
         }
       }
     };
@@ -315,7 +326,7 @@ __device__ __forceinline__ void gather_batch(unsigned long long p_l, float w_l, 
     for (int t = 0; t < UNR; ++t) {
       if (TAIL && (t0 + t) * EP >= cnt) break;
 #pragma unroll
-      for (int c = 0; c < MAXCH; ++c) vec_fma<VEC>(acc[c], __uint_as_float(w[t]), v[t][c]);
+      for (int c = 0; c < MAXCH; ++c) vec_fma<VEC>(acc[c], __uint_as_float(w[t]), reinterpret_cast<const float *>(&v[t][c]));
     }
   };
   if constexpr (DPP) {
@@ -348,9 +359,9 @@ __device__ __forceinline__ void fold_groups(float (&acc)[MAXCH][VEC]) {
 // Sum of w * (feature row) over the entries [e0, e1) of `row`, at most a few hundred of them;
 // lane group 0 (lanes < LPR) ends up with the result.  d_off / nvec: first feature column and
 // number of VEC-pieces handled.
-template <int VEC, int MAXCH, int LPR, typename Args>
+template <int VEC, int MAXCH, int LPR, bool RAGGED = false, typename Args>
 __device__ __forceinline__ void gather_segment(Args &a, int row, const InnerWeights iw, int e0, int e1,
-                                               int d_off, int nvec, float (&acc)[MAXCH][VEC]) {
+                                               int d_off, int nvec, float (&acc)[MAXCH][VEC], int width = 0) {
 #pragma unroll
   for (int c = 0; c < MAXCH; ++c)
 #pragma unroll
@@ -360,7 +371,7 @@ __device__ __forceinline__ void gather_segment(Args &a, int row, const InnerWeig
     // one neighbour per lane: its feature-row address and weight
     unsigned long long p_l = 0;
     float w_l = 0.f;
-    constexpr bool DPP = dpp_gather(MAXCH, LPR);
+    constexpr bool DPP = !RAGGED && dpp_gather(MAXCH, LPR);  // (ragged ones would spill three registers)
     const int mine = batch_entry<LPR, DPP>();
     if (mine < cnt) {
       const int e = base + mine;
@@ -368,7 +379,7 @@ __device__ __forceinline__ void gather_segment(Args &a, int row, const InnerWeig
       const int c = a.col_idx[e];
       entry_source(a, row, c, d_off, p_l, w_l, [&] { return iw.w ? w_e : 1.f; });
     }
-    gather_batch<VEC, MAXCH, LPR, DPP>(p_l, w_l, cnt, nvec, acc);
+    gather_batch<VEC, MAXCH, LPR, DPP, RAGGED>(p_l, w_l, cnt, nvec, acc, width);
   }
   fold_groups<VEC, MAXCH, LPR>(acc);
 }

@@ -74,3 +74,46 @@ def test_aggregate_in_turns(cliques, size, d, n_halo, p):
     torch.testing.assert_close(dhalo[:K].double(), ref_dhalo[kept], **tol)
     assert bool((dhalo[K:] == 7.0).all())
     ctx.close()
+
+
+@pytest.mark.parametrize("d", [2, 3, 5, 6, 7, 18, 33, 65, 66, 129, 130, 258, 263, 510, 602, 770, 1022])
+@pytest.mark.parametrize("cliques,size,n_halo", [(40, 23, 90), (2, 300, 70), (1, 2305, 50)])
+def test_rows_of_any_width(d, cliques, size, n_halo):
+    """Widths that are no multiple of four: the last four columns of a row overlap those before them.  Rows of one segment, of
+    two (a workgroup each) and of ten (partial sums); nothing is written past the last row."""
+    import torch
+    import paper_2203_10983_amd as pkg
+    dev = torch.device("cuda:0")
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(d)
+    P = _partition(cliques, size, n_halo, np.random.default_rng(size))
+    n, e = P.n_in, d
+    i32 = lambda k: torch.zeros(k, dtype=torch.int32, device=dev)  # noqa: E731
+    ctx = pkg.Context(P, [d, e], 1, device=dev)
+    kept, remap, n_kept, nnz = i32(n_halo), i32(n_halo), i32(1), i32(1)
+    ctx.sample_boundary(1, 0, 1.0, kept, remap, n_kept)
+    csr = i32(n + 1), i32(P.nnz0), i32(n + n_halo + 1), i32(P.nnz0)  # must outlive the layer calls
+    ctx.build_sampled_csr(remap, kept, n_kept, *csr, nnz)
+    X, Xb, W, dH = (torch.randn(*k, device=dev, generator=gen) for k in ((n, d), (n_halo, d), (d, e), (n, e)))
+    W /= d ** 0.5
+    A, dX, dhalo = (torch.full((k + 1, d), 7.0, device=dev) for k in (n, n, n_halo))  # one row more than there is
+    H, dW = torch.zeros(n, e, device=dev), torch.zeros(d, e, device=dev)
+    ctx.gcn_layer_fwd(1, 1.0, X, Xb, W, A[:n], H, False)
+    ctx.gcn_layer_bwd(1, 1.0, dH, None, A[:n], X, W, dW, dX[:n], dhalo[:n_halo])
+    torch.cuda.synchronize()
+    s_in, s_bd = (torch.from_numpy(x).to(dev).double().rsqrt()[:, None] for x in (P.deg_in, P.deg_halo))
+    clique = torch.arange(n, device=dev) // size
+
+    def inner(x):
+        return torch.zeros(cliques, x.shape[1], device=dev, dtype=torch.float64).index_add_(0, clique, x)[clique]
+
+    node = torch.repeat_interleave(torch.arange(n_halo, device=dev), torch.from_numpy(np.diff(P.halo_ptr)).to(dev))
+    of = torch.from_numpy(P.halo_col).long().to(dev)
+    G = dH.double() @ W.double().T
+    ref_A = s_in * inner(s_in * X).index_add_(0, of, (s_bd * Xb)[node])
+    ref_dhalo = torch.zeros(n_halo, d, device=dev, dtype=torch.float64).index_add_(0, node, (s_in * G)[of]) * s_bd
+    # a sum of k terms in chains of at most 256 per partial sum; elements of G are sums of d products, together of size 1
+    for x, ref in ((A, ref_A), (dX, s_in * inner(s_in * G)), (dhalo, ref_dhalo)):
+        torch.testing.assert_close(x[:-1].double(), ref, rtol=1e-5, atol=3e-5)
+        assert bool((x[-1] == 7.0).all())
+    ctx.close()
