@@ -757,7 +757,7 @@ bns_status sample_and_build_impl(bns_ctx *ctx, uint64_t seed, uint32_t epoch, co
                                  const PackJobs &pack, hipStream_t s) {
   Layout &w = ctx->ws;
   const bns_partition_desc &P = ctx->part;
-  if (!sample_build_small_fits(P.n_in, P.n_halo, P.e_in, P.e_bd)) {
+  if (!sample_build_small_fits(P.n_in, P.n_halo, P.e_in, P.e_bd, expected_kept(ctx, p))) {
     const bns_status st = sample_impl(ctx, seed, epoch, epoch_dev, p, w.kept_ids, w.remap, w.counters, &pack, s);
     if (st != BNS_OK) return st;
     return build_impl(ctx, w.row_ptr, w.col_idx, w.t_row_ptr, w.t_col_idx, w.counters + 1, s);

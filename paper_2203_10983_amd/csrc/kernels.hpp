@@ -99,13 +99,17 @@ hipError_t copy_static_rows(int32_t n_in, int64_t e_in, const int32_t *t_in_ptr,
 
 // ---- small.hip: selection step + subgraph step of a small partition in one launch -------------
 // One workgroup runs the stages of sample_boundary and build_subgraph back to back and writes the same arrays (t_row_ptr / t_col_idx must already
-// hold the static rows of the inner nodes).  Only for sizes within the limits below: the boundary nodes and entries are what its LDS
-// holds, the inner work is where one workgroup takes as long as the four launches of the general path (steps of 64-16-8, general and
-// small, us: 2000 rows of 15 entries 50 / 38, of 40 49 / 46, 3500 of 15 56 / 49, of 25 56 / 56).
-constexpr int kSmallMaxHalo = 8192;              // boundary nodes
-constexpr int kSmallMaxBoundaryEntries = 12288;  // entries with a boundary column
-constexpr int kSmallMaxInnerWork = 81920;        // inner nodes + inner entries
-bool sample_build_small_fits(int32_t n_in, int32_t n_halo, int64_t e_in, int64_t e_bd);
+// hold the static rows of the inner nodes).  Its LDS holds so many boundary nodes and entries:
+constexpr int kSmallMaxHalo = 8192;             // boundary nodes
+constexpr int kSmallMaxBoundaryEntries = 8192;  // entries with a boundary column
+// and it pays where one workgroup takes less time than the four launches of the general path.  What it takes goes by the inner entries, 2
+// per inner node, 8 per boundary entry and 4 per boundary node to be expected (the two stages, general and small, us, the
+// general ones with about 5 for their second bracket: 1500 rows with 31308 inner entries beside 3000 boundary nodes at p = 0.1 27 / 18, at 65000
+// of this measure 6000 with 23996 beside 3000 at p = 0.1 28 / 17, beyond it 1500 with 75266 beside 300 22 / 18, 6000 with 23996 beside 11468
+// boundary entries at p = 1 26 / 26, 6000 with 53956 beside 7500 at p = 1 35 / 59; a step of 9093 rows of 8 entries beside
+// 4487 nodes and 11375 entries at p = 1 131 / 162).
+constexpr int kSmallMaxWork = 65536;
+bool sample_build_small_fits(int32_t n_in, int32_t n_halo, int64_t e_in, int64_t e_bd, int32_t expected_kept);
 hipError_t sample_build_small(const int64_t *halo_gid, int32_t n_halo, uint64_t seed, uint32_t epoch,
                               const uint32_t *epoch_dev, uint32_t part_id, uint64_t threshold, uint64_t *ballots,
                               int32_t *kept_ids, int32_t *remap, int32_t *n_kept, int32_t *kept_start,

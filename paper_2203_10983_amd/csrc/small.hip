@@ -241,9 +241,9 @@ __global__ void __launch_bounds__(kSmallThreads) sample_build_small_kernel(const
 
 }  // namespace
 
-bool sample_build_small_fits(int32_t n_in, int32_t n_halo, int64_t e_in, int64_t e_bd) {
+bool sample_build_small_fits(int32_t n_in, int32_t n_halo, int64_t e_in, int64_t e_bd, int32_t expected_kept) {
   return n_halo <= kSmallMaxHalo && e_bd <= kSmallMaxBoundaryEntries &&
-         (int64_t)n_in + e_in <= kSmallMaxInnerWork;
+         e_in + 2 * (int64_t)n_in + 8 * e_bd + 4 * (int64_t)expected_kept <= kSmallMaxWork;
 }
 
 hipError_t sample_build_small(const int64_t *halo_gid, int32_t n_halo, uint64_t seed, uint32_t epoch,
@@ -252,7 +252,7 @@ hipError_t sample_build_small(const int64_t *halo_gid, int32_t n_halo, uint64_t 
                               int32_t n_in, int64_t e_in, int64_t e_bd, const StaticSplit &sp, int32_t *row_ptr, int32_t *col_idx, int32_t *nnz, const int32_t *halo_ptr,
                               const int32_t *halo_col, int32_t *t_row_ptr, int32_t *t_col_idx, int2 *rec, const float *dis_halo,
                               float s_halo, const PackJobs *pack, hipStream_t s) {
-  if (!sample_build_small_fits(n_in, n_halo, e_in, e_bd)) return hipErrorInvalidValue;
+  if (n_halo > kSmallMaxHalo || e_bd > kSmallMaxBoundaryEntries || e_in > INT32_MAX) return hipErrorInvalidValue;
   SmallArgs a;
   a.halo_gid = halo_gid;
   a.n_halo = n_halo;
