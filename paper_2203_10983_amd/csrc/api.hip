@@ -1015,6 +1015,7 @@ bns_status bns_graph_capture(bns_ctx *ctx, uint64_t seed, uint32_t first_epoch, 
   const uint32_t saved_mask = ctx->prof.mask;
   ctx->prof.mask = 0;
   bns_status st = train_step_impl(ctx, seed, 0, epoch_dev, p, X, halo_h, labels, W, dW, dhalo, loss, lr, stream);
+  ctx->cur_counted = false;  // recorded, not run
   hipGraph_t graph = nullptr;
   hipError_t e_end = hipStreamEndCapture(s, &graph);
   ctx->prof.mask = saved_mask;
@@ -1029,6 +1030,7 @@ bns_status bns_graph_capture(bns_ctx *ctx, uint64_t seed, uint32_t first_epoch, 
 bns_status bns_graph_replay(bns_ctx *ctx, int32_t n_epochs, void *stream) {
   if (!ctx || n_epochs < 0) return BNS_EINVAL;
   if (!ctx->graph_exec) return fail(ctx, BNS_EINVAL, "bns_graph_capture has not been called");
+  if (n_epochs > 0) ctx->cur_counted = false;  // the keep bits are the replay's from here on, whose one-launch form does not count
   for (int i = 0; i < n_epochs; ++i)
     BNS_TRY("hipGraphLaunch", hipGraphLaunch(ctx->graph_exec, static_cast<hipStream_t>(stream)));
   return BNS_OK;
