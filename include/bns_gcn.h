@@ -139,7 +139,8 @@ bns_status bns_sample_boundary_noalloc(const int64_t *halo_gid, int32_t n_halo, 
  * its transpose for the backward pass.
  *   remap, kept_ids, n_kept: the sample, exactly the three arrays the latest bns_sample_boundary on
  *             this context filled (that call also left the keep bits in the workspace, which this
- *             one reads); other pointers -> BNS_EINVAL
+ *             one reads); other pointers, or a replay of a captured step since, which draws its own
+ *             sample into the arrays of bns_ws_view -> BNS_EINVAL
  *   row_ptr   dev int32[n_in+1], col_idx dev int32[nnz0] (capacity): inner columns unchanged,
  *             kept boundary column n_in+b renumbered n_in+remap[b], order preserved
  *   t_row_ptr dev int32[n_in+n_halo+1] (first n_in+*n_kept+1 valid), t_col_idx dev int32[nnz0]:

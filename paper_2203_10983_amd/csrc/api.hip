@@ -94,6 +94,7 @@ struct bns_ctx {
   uint32_t cur_epoch = 0;
   const uint32_t *cur_epoch_dev = nullptr;
   bool cur_counted = false;             // the kept boundary entries of the latest sample are counted in the workspace
+  const int32_t *drawn = nullptr;       // remap of the sample whose keep bits and row starts sit in the workspace: the latest that ran
   hipGraphExec_t graph_exec = nullptr;  // captured training step (bns_graph_capture)
   std::string err;
 };
@@ -719,6 +720,7 @@ bns_status sample_impl(bns_ctx *ctx, uint64_t seed, uint32_t epoch, const uint32
                           (int32_t)ctx->part.e_in, ctx->ws.kept_start, pack ? ctx->ws.halo_rec : nullptr,
                           ctx->layer_kind == 1 ? nullptr : ctx->ws.dis_halo, halo_scale(p), pack, &count, s));
   ctx->cur_counted = true;
+  ctx->drawn = remap;
   ctx->cur_kept = kept_ids;
   ctx->cur_remap = remap;
   ctx->cur_n_kept = n_kept;
@@ -770,6 +772,7 @@ bns_status sample_and_build_impl(bns_ctx *ctx, uint64_t seed, uint32_t epoch, co
                              w.row_ptr, w.col_idx, w.counters + 1, P.halo_ptr, P.halo_col, w.t_row_ptr, w.t_col_idx,
                              w.halo_rec, ctx->layer_kind == 1 ? nullptr : w.dis_halo, halo_scale(p), &pack, s));
   ctx->cur_counted = false;
+  ctx->drawn = w.remap;
   ctx->cur_kept = w.kept_ids;
   ctx->cur_remap = w.remap;
   ctx->cur_n_kept = w.counters;
@@ -865,6 +868,8 @@ bns_status bns_build_sampled_csr(bns_ctx *ctx, const int32_t *remap, const int32
   // the keep bits of the latest sample sit in the workspace: the three arrays must be that sample's
   if (remap != ctx->cur_remap || kept_ids != ctx->cur_kept || n_kept != ctx->cur_n_kept)
     return fail(ctx, BNS_EINVAL, "remap / kept_ids / n_kept are not the outputs of the latest bns_sample_boundary");
+  if (ctx->part.n_halo > 0 && remap != ctx->drawn)
+    return fail(ctx, BNS_EINVAL, "remap / kept_ids / n_kept do not hold the latest sample: a replayed step has drawn another one since, or a captured one has not run");
   return build_impl(ctx, row_ptr, col_idx, t_row_ptr, t_col_idx, nnz, static_cast<hipStream_t>(stream));
 }
 
@@ -1014,8 +1019,10 @@ bns_status bns_graph_capture(bns_ctx *ctx, uint64_t seed, uint32_t first_epoch, 
   // of the capture, and there is no return in between
   const uint32_t saved_mask = ctx->prof.mask;
   ctx->prof.mask = 0;
+  const int32_t *const drawn = ctx->drawn;
   bns_status st = train_step_impl(ctx, seed, 0, epoch_dev, p, X, halo_h, labels, W, dW, dhalo, loss, lr, stream);
   ctx->cur_counted = false;  // recorded, not run
+  ctx->drawn = drawn;
   hipGraph_t graph = nullptr;
   hipError_t e_end = hipStreamEndCapture(s, &graph);
   ctx->prof.mask = saved_mask;
@@ -1030,7 +1037,10 @@ bns_status bns_graph_capture(bns_ctx *ctx, uint64_t seed, uint32_t first_epoch, 
 bns_status bns_graph_replay(bns_ctx *ctx, int32_t n_epochs, void *stream) {
   if (!ctx || n_epochs < 0) return BNS_EINVAL;
   if (!ctx->graph_exec) return fail(ctx, BNS_EINVAL, "bns_graph_capture has not been called");
-  if (n_epochs > 0) ctx->cur_counted = false;  // the keep bits are the replay's from here on, whose one-launch form does not count
+  if (n_epochs > 0) {  // the keep bits are the replay's from here on, whose one-launch form does not count
+    ctx->cur_counted = false;
+    ctx->drawn = ctx->ws.remap;
+  }
   for (int i = 0; i < n_epochs; ++i)
     BNS_TRY("hipGraphLaunch", hipGraphLaunch(ctx->graph_exec, static_cast<hipStream_t>(stream)));
   return BNS_OK;

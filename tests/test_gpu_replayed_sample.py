@@ -15,7 +15,7 @@ class _Program:
     def __init__(self):
         import torch
         import paper_2203_10983_amd as pkg
-        self.torch = torch
+        self.torch, self.pkg = torch, pkg
         dev = torch.device("cuda:0")
         n, n_halo, d = 600, 7000, 8
         self.P = _partition(n, 3, 0, n_halo, np.random.default_rng(n), lists=1)
@@ -84,4 +84,26 @@ def test_build_after_a_capture_on_the_sample_before_it():
     g.capture(6, 1.0)
     g.ctx.build_sampled_csr(*g.in_workspace, *g.csr)
     g.check(5, 0.1)
+    g.ctx.close()
+
+
+def test_build_refuses_a_sample_that_a_replay_has_replaced():
+    """The row starts in the workspace are those of the replay's kept nodes: with the lists of other nodes a build could write past
+    the end of the transposed columns.  So is one on a captured step that has not run.  A new sample is accepted again."""
+    g = _Program()
+    g.capture(7, 0.1)
+    refused = "do not hold the latest sample"
+    with pytest.raises(g.pkg.BnsError, match=refused):
+        g.ctx.build_sampled_csr(*g.in_workspace, *g.csr)
+    g.sample(g.own, 3, 0.9)
+    g.replay(0)
+    g.ctx.build_sampled_csr(*g.own, *g.csr)
+    g.check(3, 0.9)
+    g.replay(2)
+    with pytest.raises(g.pkg.BnsError, match=refused) as e:
+        g.ctx.build_sampled_csr(*g.own, *g.csr)
+    assert e.value.status == 1
+    g.sample(g.own, 4, 0.5)
+    g.ctx.build_sampled_csr(*g.own, *g.csr)
+    g.check(4, 0.5)
     g.ctx.close()
