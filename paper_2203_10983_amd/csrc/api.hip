@@ -95,6 +95,7 @@ struct bns_ctx {
   const uint32_t *cur_epoch_dev = nullptr;
   bool cur_counted = false;             // the kept boundary entries of the latest sample are counted in the workspace
   const int32_t *drawn = nullptr;       // remap of the sample whose keep bits and row starts sit in the workspace: the latest that ran
+  bool ws_built = false;                // a subgraph has been written to the workspace arrays (a capture alone writes none)
   hipGraphExec_t graph_exec = nullptr;  // captured training step (bns_graph_capture)
   std::string err;
 };
@@ -706,6 +707,9 @@ void add_pack_jobs(const bns_ctx *ctx, int l, const float *W, bool fwd, bool bwd
 }
 constexpr int kPackLayers = kMaxPackJobs / 4;  // layers whose jobs fit one launch
 
+// Are the arrays of the workspace current and still unwritten, i.e. has a step been captured and none been run?
+bool no_subgraph(const bns_ctx *ctx) { return ctx->cur_row_ptr == ctx->ws.row_ptr && !ctx->ws_built; }
+
 BdCount bd_count(const bns_ctx *ctx) { return BdCount{ctx->part.e_bd, ctx->ws.split.bd_b, ctx->ws.bd_mask, ctx->ws.bd_sums}; }
 
 // pack (nullable): a training step's: weights to pack beside the sampling, and the records of the kept nodes too
@@ -746,6 +750,7 @@ bns_status build_impl(bns_ctx *ctx, int32_t *row_ptr, int32_t *col_idx, int32_t 
   // the workspace arrays hold the static rows since bns_create
   g.static_rows = !(t_row_ptr == ctx->ws.t_row_ptr && t_col_idx == ctx->ws.t_col_idx);
   BNS_TRY("build_subgraph", build_subgraph(g, ctx->cur_counted, s));
+  if (row_ptr == ctx->ws.row_ptr) ctx->ws_built = true;
   ctx->cur_row_ptr = row_ptr;
   ctx->cur_col_idx = col_idx;
   ctx->cur_t_row_ptr = t_row_ptr;
@@ -773,6 +778,7 @@ bns_status sample_and_build_impl(bns_ctx *ctx, uint64_t seed, uint32_t epoch, co
                              w.halo_rec, ctx->layer_kind == 1 ? nullptr : w.dis_halo, halo_scale(p), &pack, s));
   ctx->cur_counted = false;
   ctx->drawn = w.remap;
+  ctx->ws_built = true;
   ctx->cur_kept = w.kept_ids;
   ctx->cur_remap = w.remap;
   ctx->cur_n_kept = w.counters;
@@ -881,6 +887,7 @@ bns_status bns_gcn_layer_fwd(bns_ctx *ctx, int32_t layer, double p, const float 
   if (!H_in || !W || !A_saved || !H_out || (ctx->part.n_halo > 0 && !halo_h))
     return fail(ctx, BNS_EINVAL, "null pointer");
   if (!ctx->cur_row_ptr) return fail(ctx, BNS_EINVAL, "bns_build_sampled_csr has not been called");
+  if (no_subgraph(ctx)) return fail(ctx, BNS_EINVAL, "the captured step has not run: there is no sampled subgraph yet");
   hipStream_t s = static_cast<hipStream_t>(stream);
   PackJobs jobs;
   add_pack_jobs(ctx, layer, W, true, false, &jobs);
@@ -897,6 +904,7 @@ bns_status bns_gcn_layer_bwd(bns_ctx *ctx, int32_t layer, double p, const float 
   if (ctx->layer_kind == 1 && !H_in) return fail(ctx, BNS_EINVAL, "the mean-aggregator layer needs H_in");
   if (!dH_in && dhalo) return fail(ctx, BNS_EINVAL, "dhalo needs dH_in");
   if (!ctx->cur_t_row_ptr) return fail(ctx, BNS_EINVAL, "bns_build_sampled_csr has not been called");
+  if (no_subgraph(ctx)) return fail(ctx, BNS_EINVAL, "the captured step has not run: there is no sampled subgraph yet");
   hipStream_t s = static_cast<hipStream_t>(stream);
   PackJobs jobs;
   if (dH_in) add_pack_jobs(ctx, layer, W, false, true, &jobs);
@@ -1020,9 +1028,11 @@ bns_status bns_graph_capture(bns_ctx *ctx, uint64_t seed, uint32_t first_epoch, 
   const uint32_t saved_mask = ctx->prof.mask;
   ctx->prof.mask = 0;
   const int32_t *const drawn = ctx->drawn;
+  const bool ws_built = ctx->ws_built;
   bns_status st = train_step_impl(ctx, seed, 0, epoch_dev, p, X, halo_h, labels, W, dW, dhalo, loss, lr, stream);
   ctx->cur_counted = false;  // recorded, not run
   ctx->drawn = drawn;
+  ctx->ws_built = ws_built;
   hipGraph_t graph = nullptr;
   hipError_t e_end = hipStreamEndCapture(s, &graph);
   ctx->prof.mask = saved_mask;
@@ -1040,6 +1050,7 @@ bns_status bns_graph_replay(bns_ctx *ctx, int32_t n_epochs, void *stream) {
   if (n_epochs > 0) {  // the keep bits are the replay's from here on, whose one-launch form does not count
     ctx->cur_counted = false;
     ctx->drawn = ctx->ws.remap;
+    ctx->ws_built = true;
   }
   for (int i = 0; i < n_epochs; ++i)
     BNS_TRY("hipGraphLaunch", hipGraphLaunch(ctx->graph_exec, static_cast<hipStream_t>(stream)));

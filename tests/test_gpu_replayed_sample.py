@@ -107,3 +107,23 @@ def test_build_refuses_a_sample_that_a_replay_has_replaced():
     g.ctx.build_sampled_csr(*g.own, *g.csr)
     g.check(4, 0.5)
     g.ctx.close()
+
+
+def test_layers_are_refused_while_a_captured_step_has_not_run():
+    """A capture makes the workspace arrays current; until a step has run they hold nothing to gather by."""
+    g = _Program()
+    g.sample(g.own, 3, 0.5)
+    g.ctx.build_sampled_csr(*g.own, *g.csr)
+    g.capture(7, 0.1)
+    X, (Xb,), _, (W,), (dW,) = g.args[:5]
+    A, H = g.torch.zeros_like(X), g.torch.zeros_like(X)
+    fwd = lambda: g.ctx.gcn_layer_fwd(1, 0.1, X, Xb, W, A, H, False)  # noqa: E731
+    for call in (fwd, lambda: g.ctx.gcn_layer_bwd(1, 0.1, X, None, X, None, W, dW, A, None)):
+        with pytest.raises(g.pkg.BnsError, match="has not run") as e:
+            call()
+        assert e.value.status == 1
+    g.replay(1)
+    fwd()
+    g.torch.cuda.synchronize()
+    assert g.torch.equal(A, g.ctx.ws_tensor(g.pkg.VIEW_A, 1, g.torch.float32).view_as(A))
+    g.ctx.close()
