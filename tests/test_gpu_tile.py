@@ -1,8 +1,10 @@
 """Layers of small partitions, aggregate and product in one launch, against the two launches that run while their phases are
 timed.  Forward, and backward where the output is the narrower side, the same sums in the same order, so the same bits; else the
 transposed aggregate has changed places with the product, and both results lie within a few roundings (2^-24) of the exact one.
-Random graphs with hubs of up to eight segments of 256 entries.  And the subgraph of
+Random graphs with hubs of up to eight segments of 256 entries; on either side of each limit, and which form runs is
+counted in launches.  And the subgraph of
 such a step, whose launch the stand-alone calls do not take, at that launch's limits."""
+import ctypes as C
 import types
 
 import numpy as np
@@ -34,13 +36,58 @@ def _partition(n, deg, hub, n_halo, rng, lists=4):
         deg_halo=i32(np.bincount(halo[:, 0], minlength=n_halo) + 1))
 
 
-@pytest.mark.parametrize("n,deg,hub,dims,layer_kind,drop,cached", [
-    (1, 0, 0, (12, 16, 1), 0, 0.0, False), (7, 2, 0, (64, 16, 8), 0, 0.0, False), (17, 3, 0, (16, 129, 12, 2), 1, 0.3, False),
-    (500, 5, 0, (64, 172, 8), 0, 0.5, True), (600, 8, 560, (128, 128, 47), 0, 0.0, False), (2100, 4, 2048, (100, 128, 17), 1, 0.0, True),
-    (3584, 20, 300, (32, 256, 16), 1, 0.3, False), (3585, 20, 0, (60, 33, 9), 0, 0.0, False), (8192, 3, 0, (36, 128, 20, 5), 1, 0.0, False),
-    (1, 0, 0, (8, 8, 8), 0, 0.0, False), (9, 2, 0, (5, 33, 12), 0, 0.0, False), (700, 12, 600, (16, 100, 100, 47), 1, 0.3, False),
-    (700, 12, 600, (64, 128, 36, 12), 0, 0.3, False), (2600, 4, 0, (12, 128, 128, 128), 1, 0.0, False)])
-def test_one_launch_equals_two(n, deg, hub, dims, layer_kind, drop, cached):
+def _launches(call):
+    """Kernels that a call puts on its stream: it is recorded, counted and not run."""
+    import torch
+    import paper_2203_10983_amd as pkg
+    hip, graph, nodes = pkg.load_library(), C.c_void_p(), C.c_size_t()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(torch.cuda.Stream()):
+        stream = C.c_void_p(torch.cuda.current_stream().cuda_stream)
+        assert hip.hipStreamBeginCapture(stream, 1) == 0
+        try:
+            call()
+        finally:
+            assert hip.hipStreamEndCapture(stream, C.byref(graph)) == 0
+    assert hip.hipGraphGetNodes(graph, None, C.byref(nodes)) == 0 and hip.hipGraphDestroy(graph) == 0
+    return nodes.value
+
+
+def _one_launch_layers(ctx, P, dims, layer_kind, cached_X):
+    """Per layer call: does it run as one launch, forward (beside the records of the kept rows) and backward (beside what a call
+    without an input gradient launches)?  By the rules that a step goes by."""
+    import torch
+    i32 = lambda k: torch.zeros(k, dtype=torch.int32, device="cuda:0")  # noqa: E731
+    f32 = lambda *k: torch.zeros(*k, device="cuda:0")  # noqa: E731
+    n, nb = P.n_in, P.n_halo
+    kept, remap, n_kept = i32(nb), i32(nb), i32(1)
+    csr = i32(n + 1), i32(P.nnz0), i32(n + nb + 1), i32(P.nnz0), i32(1)
+    ctx.sample_boundary(3, 0, 0.5, kept, remap, n_kept)
+    ctx.build_sampled_csr(remap, kept, n_kept, *csr)
+    fwd, bwd = [], []
+    for l, (a, b) in enumerate(zip(dims, dims[1:]), 1):
+        H_in, Hu, W, dW = cached_X if l == 1 and cached_X is not None else f32(n, a), f32(nb, a), f32((1 + layer_kind) * a, b), f32((1 + layer_kind) * a, b)
+        A, H, G, dH, dhalo = f32(n, a), f32(n, b), f32(n, b), f32(n, a), f32(nb, a)
+        fwd.append(_launches(lambda: ctx.gcn_layer_fwd(l, 0.5, H_in, Hu, W, A, H, False)) == 2)
+        with_dH = _launches(lambda: ctx.gcn_layer_bwd(l, 0.5, G, H, A, H_in, W, dW, dH, dhalo))
+        bwd.append(with_dH - _launches(lambda: ctx.gcn_layer_bwd(l, 0.5, G, H, A, H_in, W, dW, None, None)) == 1)
+    return "".join("21"[x] for x in fwd), "".join("21"[x] for x in bwd[1:])
+
+
+# segments: of the longest row, forward and transposed.  fwd, bwd (from layer 2 on): launches of aggregate and product, in one (1) or
+# each in its own (2 or more).
+@pytest.mark.parametrize("n,deg,hub,dims,layer_kind,drop,cached,segments,fwd,bwd", [
+    (1, 0, 0, (12, 16, 1), 0, 0.0, False, (1, 1), "11", "2"), (7, 2, 0, (64, 16, 8), 0, 0.0, False, (1, 1), "11", "1"),
+    (17, 3, 0, (16, 129, 12, 2), 1, 0.3, False, (1, 1), "121", "22"), (500, 5, 0, (64, 172, 8), 0, 0.5, True, (1, 1), "12", "2"),
+    (600, 8, 560, (128, 128, 47), 0, 0.0, False, (3, 3), "11", "1"), (2100, 4, 2000, (100, 128, 17), 1, 0.0, True, (8, 8), "11", "2"),
+    (2100, 4, 2048, (100, 128, 17), 1, 0.0, True, (9, 8), "22", "2"), (3584, 20, 300, (32, 256, 16), 1, 0.3, False, (2, 2), "12", "2"),
+    (3585, 20, 300, (32, 36, 16), 1, 0.0, False, (2, 2), "22", "2"), (3585, 20, 0, (60, 33, 9), 0, 0.0, False, (1, 1), "12", "2"),
+    (8192, 3, 0, (36, 128, 20, 5), 1, 0.0, False, (1, 1), "111", "22"), (8193, 3, 0, (36, 128, 5), 0, 0.0, False, (1, 1), "22", "2"),
+    (1, 0, 0, (8, 8, 8), 0, 0.0, False, (1, 1), "22", "1"), (9, 2, 0, (5, 33, 12), 0, 0.0, False, (1, 1), "22", "1"),
+    (700, 12, 600, (16, 100, 100, 47), 1, 0.3, False, (3, 3), "111", "11"), (700, 12, 600, (64, 128, 36, 12), 0, 0.3, False, (3, 3), "111", "11"),
+    (900, 4, 800, (64, 64, 36), 0, 0.0, True, (4, 4), "11", "2"), (2457, 4, 0, (12, 128, 128, 128), 1, 0.0, False, (1, 1), "111", "11"),
+    (2458, 4, 0, (12, 128, 128, 128), 1, 0.0, False, (1, 1), "111", "22"), (2600, 4, 0, (12, 128, 128, 128), 1, 0.0, False, (1, 1), "111", "22")])
+def test_one_launch_equals_two(n, deg, hub, dims, layer_kind, drop, cached, segments, fwd, bwd):
     import torch
     import paper_2203_10983_amd as pkg
     dev = torch.device("cuda:0")
@@ -48,6 +95,7 @@ def test_one_launch_equals_two(n, deg, hub, dims, layer_kind, drop, cached):
     gen.manual_seed(n)
     n_halo, L = n // 2 + 1, len(dims) - 1
     P = _partition(n, deg, hub, n_halo, np.random.default_rng(n))
+    assert segments == tuple(-(-int(np.diff(ptr).max()) // 256) for ptr in (P.row_ptr0, P.t_in_ptr))
     r = lambda *s: torch.randn(*s, device=dev, generator=gen)  # noqa: E731
     X, halo = r(n, dims[0]), [r(n_halo, d) for d in dims[:-1]]
     W = [r((1 + layer_kind) * a, b) / a ** 0.5 for a, b in zip(dims, dims[1:])]
@@ -67,6 +115,11 @@ def test_one_launch_equals_two(n, deg, hub, dims, layer_kind, drop, cached):
         torch.cuda.synchronize()
         if mask:
             assert ctx.profile_read()["gemm_fwd"][1] >= 2 * L  # two launches
+        else:
+            assert _one_launch_layers(ctx, P, dims, layer_kind, X if cached else None) == (fwd, bwd)
+            # (a step on arrays of the workspace again, as the views below are)
+            ctx.train_step(3, 1, 0.5, X, halo, labels, W, dW, dhalo, loss, 0.0)
+            torch.cuda.synchronize()
         A = [ctx.ws_tensor(pkg.VIEW_A, l, torch.float32).clone() for l in range(1, L + 1)] + [ctx.ws_tensor(pkg.VIEW_DZ, L, torch.float32).clone()]
         losses.append(loss.double())
         dZ = [ctx.ws_tensor(pkg.VIEW_DZ, l, torch.float32).clone() for l in range(1, L)]
