@@ -102,13 +102,14 @@ hipError_t copy_static_rows(int32_t n_in, int64_t e_in, const int32_t *t_in_ptr,
 // hold the static rows of the inner nodes).  Its LDS holds so many boundary nodes and entries:
 constexpr int kSmallMaxHalo = 8192;             // boundary nodes
 constexpr int kSmallMaxBoundaryEntries = 8192;  // entries with a boundary column
-// and it pays where one workgroup takes less time than the four launches of the general path.  What it takes goes by the inner entries, 2
-// per inner node, 8 per boundary entry and 4 per boundary node to be expected (the two stages, general and small, us, the
-// general ones with about 5 for their second bracket: 1500 rows with 31308 inner entries beside 3000 boundary nodes at p = 0.1 27 / 18, at 65000
-// of this measure 6000 with 23996 beside 3000 at p = 0.1 28 / 17, beyond it 1500 with 75266 beside 300 22 / 18, 6000 with 23996 beside 11468
-// boundary entries at p = 1 26 / 26, 6000 with 53956 beside 7500 at p = 1 35 / 59; a step of 9093 rows of 8 entries beside
-// 4487 nodes and 11375 entries at p = 1 131 / 162).
-constexpr int kSmallMaxWork = 65536;
+// and it pays where one workgroup takes less time than the four launches of the general path.  Per thousand it takes about 0.15 us
+// for inner entries, 0.4 for inner nodes, 0.5 for boundary nodes and 2.3 for kept ones more than they do, and 0.4 for boundary entries, of
+// which there are few enough to leave them out (steps of 64-16-8, general and one launch, us: 600 rows with 2990 inner entries beside
+// 300 boundary nodes and 7979 entries at p = 0.1 46.4 / 34.3, 1500 with 31308 beside 3500 and 8142 at p = 1 60.5 / 56.6, 8000 with 23996
+// beside 5000 and 8099 at p = 0.1 61.1 / 54.7, 2000 with 61540 beside 300 and 1497 45.9 / 40.5; beyond the line 500 with 28732
+// beside 5000 and 8088 at p = 1 59.4 / 61.6, 2000 with 61540 beside the same 58.4 / 65.9, 8000 with 63974 beside 300 and 8095
+// at p = 0.1 57.8 / 60.3).  Of 175 partitions below the line none was slower in one launch; of 153 beyond it 51 would be faster, by 3 us.
+constexpr int kSmallMaxWork = 81920;  // inner entries + 3 per inner node + 1 per boundary node + 12 per boundary node to be expected
 bool sample_build_small_fits(int32_t n_in, int32_t n_halo, int64_t e_in, int64_t e_bd, int32_t expected_kept);
 hipError_t sample_build_small(const int64_t *halo_gid, int32_t n_halo, uint64_t seed, uint32_t epoch,
                               const uint32_t *epoch_dev, uint32_t part_id, uint64_t threshold, uint64_t *ballots,

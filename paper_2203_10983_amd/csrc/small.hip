@@ -243,7 +243,7 @@ __global__ void __launch_bounds__(kSmallThreads) sample_build_small_kernel(const
 
 bool sample_build_small_fits(int32_t n_in, int32_t n_halo, int64_t e_in, int64_t e_bd, int32_t expected_kept) {
   return n_halo <= kSmallMaxHalo && e_bd <= kSmallMaxBoundaryEntries &&
-         e_in + 2 * (int64_t)n_in + 8 * e_bd + 4 * (int64_t)expected_kept <= kSmallMaxWork;
+         e_in + 3 * (int64_t)n_in + n_halo + 12 * (int64_t)expected_kept <= kSmallMaxWork;
 }
 
 hipError_t sample_build_small(const int64_t *halo_gid, int32_t n_halo, uint64_t seed, uint32_t epoch,
@@ -283,7 +283,8 @@ hipError_t sample_build_small(const int64_t *halo_gid, int32_t n_halo, uint64_t 
   a.s_halo = s_halo;
   const PackJobs jobs = pack ? *pack : PackJobs{};
   const int pack_blocks = (jobs.units + kSmallThreads / kWave - 1) / (kSmallThreads / kWave);
-  // (ten replayed epochs of 500 rows beside 330 boundary nodes: 361.7 us at the larger limits, 360.5)
+  // (ten replayed epochs, at the larger limits and so, us: 500 rows beside 330 boundary nodes 341 / 331, 900 beside 700 347 / 337, 400
+  // beside 100 330 / 330; single steps within 1 us of each other, either way)
   if (n_halo <= kSmallThreads && e_bd <= kSmallThreads)
     sample_build_small_kernel<1, 1><<<1 + pack_blocks, kSmallThreads, 0, s>>>(a, jobs);
   else

@@ -188,15 +188,16 @@ def test_backward_with_infinite_gradients():
     assert torch.isinf(out[1][0]).any() and torch.isnan(out[1][0]).any() and torch.isfinite(out[1][0]).any()
 
 
-@pytest.mark.parametrize("n,deg,n_halo,lists,p,one", [(3, 1, 1, 1, 1.0, True), (1023, 4, 1025, 2, 0.5, True), (300, 3, 7900, 1, 0.0, True),
-                                                      (300, 3, 8192, 1, 0.0, False), (900, 3, 2900, 4, 0.1, True), (900, 3, 2900, 4, 1.0, False),
-                                                      (1200, 40, 100, 3, 1.0, True), (1600, 40, 100, 3, 1.0, False)])
+@pytest.mark.parametrize("n,deg,n_halo,lists,p,one", [(3, 1, 1, 1, 1.0, True), (1023, 4, 1025, 2, 0.5, True), (300, 3, 8192, 1, 0.0, True),
+                                                      (300, 3, 8193, 1, 0.0, False), (900, 3, 2900, 4, 1.0, True), (900, 3, 3400, 4, 0.1, False),
+                                                      (2000, 3, 5000, 1, 1.0, True), (2000, 3, 5600, 1, 1.0, False),
+                                                      (1700, 40, 100, 3, 1.0, True), (1900, 40, 100, 3, 1.0, False)])
 def test_subgraph_of_a_step_at_the_limits(n, deg, n_halo, lists, p, one):
     import torch
     import paper_2203_10983_amd as pkg
     dev = torch.device("cuda:0")
     P = _partition(n, deg, 0, n_halo, np.random.default_rng(n_halo), lists)
-    assert one == (P.e_in + 2 * n + 8 * P.e_bd + 4 * np.ceil(p * n_halo) <= 65536)
+    assert one == (max(n_halo, P.e_bd) <= 8192 and P.e_in + 3 * n + n_halo + 12 * np.ceil(p * n_halo) <= 81920)
     ctx = pkg.Context(P, [8, 8], 0, device=dev)
     i32 = lambda k: torch.zeros(k, dtype=torch.int32, device=dev)  # noqa: E731
     f32 = lambda *s: torch.zeros(*s, device=dev)  # noqa: E731
