@@ -158,7 +158,8 @@ bool tile_layer(const bns_ctx *ctx, int layer) {
          tile_layer_supported(plan, ctx->dims[layer - 1], ctx->dims[layer]);
 }
 
-// Its backward pass, likewise: the transposed aggregate (at the output width, in rows of gather_stride floats), then the product?
+// Its backward pass, likewise: the transposed aggregate (at the output width, in rows of gather_stride floats), then the product?  (The two
+// launches multiply first where the output is not narrower and in mean-aggregator layers: the same result up to rounding.)
 // rows: inner ones and expected boundary rows.  Here the two launches keep up sooner (steps, two per layer and one, us: 64-16-8
 // 500 rows 38 / 36, 64-128-128-47 700 rows 61 / 57, 1500 of 15 entries 84 / 81, 2500 91 / 90, 5000 98 / 100; mean aggregator
 // 64-64-128-8 1500 rows 79 / 76, 5000 107 / 107; with rows of several segments 64-128-128-47, 1500 rows of 15 entries 103 / 101, of
@@ -177,7 +178,8 @@ bool valid_desc(const bns_partition_desc *p, const bns_model_desc *m) {
   if (m->n_layers < 1 || (m->loss_kind != 0 && m->loss_kind != 1)) return false;
   if (m->layer_kind != 0 && m->layer_kind != 1) return false;
   for (int l = 0; l <= m->n_layers; ++l) {
-    // the aggregate holds a row in at most 8 pieces of 64 lanes x (4, 2 or 1) floats
+    // The aggregate holds a row in at most 8 pieces of 64 lanes x 4 floats.  The lower limits of the other widths are from when their
+    // lanes took 2 floats or 1; no wider row of theirs has been tested.
     const int d = m->dims[l], cap = d % 4 == 0 ? 2048 : d % 2 == 0 ? 1024 : 512;
     if (d < 1 || d > cap) return false;
   }

@@ -19,8 +19,9 @@
 
 namespace bns {
 
-// BLOCK: workgroups of kBlockWaves wavefronts; the first a.n_block_rows of them own a multi-segment row each, one
-// wavefront per segment, and add the partial sums in LDS (same order as spmm_combine_kernel, same bits).
+// BLOCK: workgroups of kBlockWaves wavefronts; the first plan.n_multi of them own a multi-segment row each, one
+// wavefront per segment, and add the partial sums in LDS (same order as spmm_combine_kernel, same bits).  In front of the
+// others are head.n_block_rows workgroups, n_multi rounded up to whole groups; those past n_multi have nothing to do.
 constexpr int kBlockWaves = 8;
 template <int VEC, int MAXCH, int LPR, bool NARROW = false, bool BLOCK = false, bool RAGGED = false>
 __global__ void __launch_bounds__(BLOCK ? kBlockWaves * kWave : 256, MAXCH == 1 ? 8 : 1) spmm_kernel(const SpmmArgs) {
@@ -247,7 +248,9 @@ static hipError_t launch_spmm_vec(const SpmmArgs &a_in, int64_t extra_rows, bool
   // and in launches of two rounds of wavefronts or less the long rows start first (12000 rows of 110 entries, 100 floats: 57
   // and 60).  Two rows to a wavefront where the workgroups are many and short (one row and two: 150000 rows of 25 entries
   // beside as many short ones, 100 floats 280 and 273, 64 floats 191 and 183; 60000 109 and 115), four in slices
-  // (197 758 rows beside 52 800 segments in four slices: 2591 and 2427 us).  They are dealt in groups of a workgroup
+  // beside at least as many short rows again (one and four, us: 197 758 rows beside 52 800 segments, 256 floats 2591 and 2427; steps at p = 1
+  // of 30000 rows of 111 entries beside 120000 boundary nodes, 256 floats 1499 and 1455, beside 75000 1244 and 1228; 12000 of 74 beside 48000, 512
+  // floats 768 and 755; of 42 such steps of 12000 to 60000 rows 19 gained 0.3 to 3 %, none lost more than 0.5 %).  They are dealt in groups of a workgroup
   // per XCD and slice, so that no XCD has more of them, at a share that is no simple fraction (one in six exactly: the same
   // shader engines had all of them, 1369 and 1565 us), and over every 32 groups in the order of the reversed bits, because near such a fraction
   // the same ones have all of them for hundreds of groups on end (150000 rows beside as many, 64 floats 215 -> 198, 256 floats 625 -> 565).
