@@ -146,7 +146,7 @@ __global__ void __launch_bounds__(BLOCK ? kBlockWaves * kWave : 256, MAXCH == 1 
           float *po = reinterpret_cast<float *>(&o);
 #pragma unroll
           for (int i = 0; i < VEC; ++i) po[i] = acc[c][i];
-          *reinterpret_cast<V *>(part + piece_at<VEC, RAGGED>(iv, width)) = o;
+          *piece_of<VEC, RAGGED>(part, iv, width) = o;
         }
       }
     }
@@ -178,7 +178,7 @@ __global__ void __launch_bounds__(256) spmm_combine_kernel(const SpmmArgs a) {
 #pragma unroll
       for (int c = 0; c < MAXCH; ++c) {
         const int iv = c * kWave + lane;
-        x[t][c] = (s0 + t < nseg && iv < nvec) ? *reinterpret_cast<const V *>(ps + piece_at<VEC, RAGGED>(iv, d)) : V{};
+        x[t][c] = (s0 + t < nseg && iv < nvec) ? *piece_of<VEC, RAGGED>(ps, iv, d) : V{};
       }
     }
 #pragma unroll

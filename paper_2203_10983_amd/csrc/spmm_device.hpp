@@ -24,6 +24,15 @@ template <int VEC, bool RAGGED>
 __device__ __forceinline__ int piece_at(int iv, int width) {
   return RAGGED ? min(iv * VEC, width - VEC) : iv * VEC;
 }
+// That piece of the row at `row`.  Whole rows are indexed by pieces: with an offset in floats a gather of 33 to 64 floats took a register
+// more than it has and waited for its sixth load before it asked for the last two (transposed aggregates of 46925 rows of
+// 15 entries beside 93850 boundary nodes, 48 floats 75.6 -> 71.6 us, 74011 of 29 beside 148022 114.9 -> 112.6).
+template <int VEC, bool RAGGED, typename F>
+__device__ __forceinline__ auto *piece_of(F *row, int iv, int width) {
+  using V = std::conditional_t<std::is_const_v<F>, const typename Vec<VEC, RAGGED>::T, typename Vec<VEC, RAGGED>::T>;
+  if constexpr (RAGGED) return reinterpret_cast<V *>(row + piece_at<VEC, true>(iv, width));
+  else return reinterpret_cast<V *>(row) + iv;
+}
 
 template <int VEC>
 __device__ __forceinline__ void vec_fma(float (&acc)[VEC], float w, const float *p) {
@@ -162,13 +171,12 @@ __device__ __forceinline__ void finish_row(Args &a, int row, int sl, int nvec, i
   for (int c = 0; c < MAXCH; ++c) {
     const int iv = c * kWave + sl;
     if (iv < nvec) {
-      const int at = piece_at<VEC, RAGGED>(iv, width);
       V o;
       float *po = reinterpret_cast<float *>(&o);
 #pragma unroll
       for (int i = 0; i < VEC; ++i) po[i] = acc[c][i];
       if (init) {
-        const V x0 = *reinterpret_cast<const V *>(init + at);
+        const V x0 = *piece_of<VEC, RAGGED>(init, iv, width);
         const float *p0 = reinterpret_cast<const float *>(&x0);
 #pragma unroll
         for (int i = 0; i < VEC; ++i) po[i] += p0[i];
@@ -180,7 +188,7 @@ __device__ __forceinline__ void finish_row(Args &a, int row, int sl, int nvec, i
         for (int i = 0; i < VEC; ++i) po[i] = fmaxf(po[i], 0.f);
       }
       if (mask) {
-        const V m = __builtin_nontemporal_load(reinterpret_cast<const V *>(mask + at));  // read once
+        const V m = __builtin_nontemporal_load(piece_of<VEC, RAGGED>(mask, iv, width));  // read once
         const float *pm = reinterpret_cast<const float *>(&m);
 #pragma unroll
         for (int i = 0; i < VEC; ++i) po[i] = pm[i] > 0.f ? po[i] : 0.f;
@@ -188,7 +196,7 @@ __device__ __forceinline__ void finish_row(Args &a, int row, int sl, int nvec, i
       if constexpr (!NARROW) {
         // streamed out: a non-temporal store leaves the L2 to the feature rows being gathered
         // (measured: 1.7 % of a training step on the largest workload)
-        __builtin_nontemporal_store(o, reinterpret_cast<V *>(out + at));
+        __builtin_nontemporal_store(o, piece_of<VEC, RAGGED>(out, iv, width));
       } else {  // padded sources: the output rows are dense and hold the first ds columns
 #pragma unroll
         for (int i = 0; i < VEC; ++i)
