@@ -240,27 +240,29 @@ static hipError_t launch_spmm_vec(const SpmmArgs &a_in, int64_t extra_rows, bool
   // One wavefront per static segment.  The kept boundary rows are a few entries each.  Where all wavefronts go on to them
   // after their segment, the launch ends in a long stretch of short rows, bound by the rate at which workgroups start, while
   // the wavefronts wait for the store of their first row (19 800 rows in four slices beside 52 800 segments: 110 of 640 us).
-  // Dealt among the workgroups of the segments, a row to a wavefront, they go by beside the long rows (all transposed aggregates
-  // of a step, us: that graph 2000 -> 1770; 25000 rows of 75 entries 255 -> 224; 90000 rows of 50 325 -> 284; 578125 rows of 22
-  // 1712 -> 1671).  Launches of short rows alone gain nothing by it, the less the narrower their rows: below 13 entries a row all
-  // wavefronts go on (90000 rows of 8 entries 414 us, dealt 430; 300000 of 11.5 and 128 floats 446, 456; 60000 of 13.2 121, 101),
-  // of rows of up to 64 floats below 24 (150000 rows of 17 entries, 64 floats 176, 185; 400000 of 16 327, 334; 60000 of 25.5 64, 60),
-  // and in launches of two rounds of wavefronts or less the long rows start first (12000 rows of 110 entries, 100 floats: 57
-  // and 60).  Two rows to a wavefront where the workgroups are many and short (one row and two: 150000 rows of 25 entries
-  // beside as many short ones, 100 floats 280 and 273, 64 floats 191 and 183; 60000 109 and 115), four in slices
-  // beside at least as many short rows again (one and four, us: 197 758 rows beside 52 800 segments, 256 floats 2591 and 2427; steps at p = 1
-  // of 30000 rows of 111 entries beside 120000 boundary nodes, 256 floats 1499 and 1455, beside 75000 1244 and 1228; 12000 of 74 beside 48000, 512
-  // floats 768 and 755; of 42 such steps of 12000 to 60000 rows 19 gained 0.3 to 3 %, none lost more than 0.5 %).  They are dealt in groups of a workgroup
+  // Dealt among the workgroups of the segments they go by beside the long rows (all transposed aggregates of a step, us: that graph
+  // 2000 -> 1770; 25000 rows of 75 entries 255 -> 224; 90000 rows of 50 325 -> 284; 578125 rows of 22 1712 -> 1671).  But a wavefront
+  // that takes a row and ends costs more than one that goes on to the next, the more so the narrower the row, and in a launch of few
+  // rounds of wavefronts the long rows should start first.  The lines, as the time with two rows dealt to a wavefront over that without:
+  // 13 entries a row (90000 rows of 8 414 us, dealt 430; 300000 of 11.5, 128 floats 446, 456; 60000 of 13.2 121, 101), for up to 64 floats
+  // 24 (150000 of 17 176 us, dealt 185; 400000 of 16 327, 334; 60000 of 25.5 64, 60); 16384 wavefronts (12000 of 110 entries, 100 floats
+  // 57 us, dealt 60); up to 32 floats 24576 and no more short rows than segments (16 floats, 20000 of 57 beside 20000 0.97 to
+  // 1.03, 50000 of 238 beside 20000 0.94 to 0.99, beside 300000 1.05 to 1.11).  Two rows to a wavefront, four where there are twice as many as segments or more (one, two
+  // and four: 128 floats, 50000 of 140 beside 300000 1.12, 1.05, 1.02; 48 floats, 50000 of 238 beside as many 1.09, 1.04, 1.01; 256 floats,
+  // 12000 of 101 beside 1200 1.07, 1.00, 1.00; 197 758 rows beside 52 800 segments in four slices 2591, -, 2427 us).  Of 4691
+  // launches of 12000 to 570000 rows this rule deals 3032, which take 0.971 of the time without, 24 of them 5 to 11 % longer; with one row to a
+  // wavefront below 100000 segments and 16384 wavefronts for all widths it was 3220, 0.977 and 92.  They are dealt in groups of a workgroup
   // per XCD and slice, so that no XCD has more of them, at a share that is no simple fraction (one in six exactly: the same
   // shader engines had all of them, 1369 and 1565 us), and over every 32 groups in the order of the reversed bits, because near such a fraction
   // the same ones have all of them for hundreds of groups on end (150000 rows beside as many, 64 floats 215 -> 198, 256 floats 625 -> 565).
   const int64_t per = 8 >> ls;
   auto groups = [&](int64_t n) { return (n + per - 1) / per; };
   const int64_t unit_groups = groups((a.head.n_units + waves - 1) / waves);
-  const bool dealt = extra_rows >= 0 && avg_len >= (a.d > 64 ? 13 : 24) && ((int64_t)a.head.n_units << ls) >= 16384;
+  const bool dealt = extra_rows >= 0 && avg_len >= (a.d > 64 ? 13 : 24) && ((int64_t)a.head.n_units << ls) >= (a.d > 32 ? 16384 : 24576) &&
+                     (a.d > 32 || extra_rows <= a.head.n_units);
   int64_t extra_groups = 0;
   if (dealt) {
-    const int rows = waves * (ls >= 2 && extra_rows >= 2 * (int64_t)a.head.n_units ? 4 : a.head.n_units >= 100000 ? 2 : 1);
+    const int rows = waves * (extra_rows >= 2 * (int64_t)a.head.n_units ? 4 : 2);
     extra_groups = groups((extra_rows + rows - 1) / rows);
     extra_groups += extra_groups / 32 + 1;  // (never none: any number is walked)
   } else if (extra_rows >= 0) {

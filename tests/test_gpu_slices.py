@@ -33,6 +33,8 @@ def _partition(cliques, size, n_halo, rng):
                                                      (79, 128, 200, 700, 1.0), (5, 515, 256, 16000, 1.0), (79, 128, 128, 300, 0.0), (6300, 16, 128, 20000, 0.5),
                                                      # widths that are no multiple of 4, dealt (16384 wavefronts, 13 entries a row): in slices and whole
                                                      (20, 257, 130, 3001, 0.3), (20, 257, 258, 1, 1.0), (20, 257, 602, 3001, 0.5), (600, 48, 47, 5000, 0.5),
+                                                     # 32 floats and less: dealt beside fewer short rows than segments, not beside more
+                                                     (600, 48, 32, 5000, 0.5), (600, 48, 30, 5000, 0.5), (600, 48, 32, 40000, 1.0),
                                                      # no kept row; two and four rows to a wavefront
                                                      (79, 128, 263, 300, 0.0), (6300, 16, 66, 20000, 0.5), (20, 257, 602, 24000, 1.0), (20, 257, 511, 24000, 1.0)])
 def test_aggregate_in_turns(cliques, size, d, n_halo, p):
