@@ -242,13 +242,17 @@ __device__ __forceinline__ void entry_source(Args &a, int row, int c, int d_off,
 // Rows of at most 64 floats sit in L2 more often than not, and then the three cross-lane reads per load (two address
 // halves and the weight, through the LDS pipe) bound the gather: that pipe was busy half of the time.  With 16 lanes
 // per row the broadcast inside a lane group is one DPP move instead (a plain vector instruction): 685 -> 651 us on
-// 32.9 M entries of 64 floats in L2, 228 -> 195 us for the padded 41-float rows of the same graph.  Rows of 32 lanes
+// 32.9 M entries of 64 floats in L2, 228 -> 195 us for the padded 41-float rows of the same graph.  With 8 lanes it is two
+// moves, and eight loads are in flight instead of four: 32 floats, 29125 rows of 340 entries 81 -> 78 us, with 19800
+// boundary rows 123 -> 108; 100000 rows of 15 beside 50000 boundary rows 96 -> 86.  Rows of 32 lanes
 // come from beyond L2 and are bound by the fabric, and the DPP form (over two rows of 16 lanes) was the slower one
 // there: 836 -> 910 us on 12.8 M entries of 128 floats, one-kernel layer 694 -> 780.
-constexpr bool dpp_gather(int maxch, int lpr) { return maxch == 1 && lpr == 16; }
+constexpr bool dpp_gather(int maxch, int lpr) { return maxch == 1 && (lpr == 16 || lpr == 8); }
 
-// Which entry of a batch of 64 a lane fetches.  The wavefront walks EP = 64 / LPR entries per step, lane group g
-// entry EP t + g in step t; for the DPP form that entry is fetched by lane t of the group.
+// Which entry of a batch of 64 a lane holds.  The wavefront walks EP = 64 / LPR entries per step, lane group g
+// entry EP t + g in step t; for the DPP form that entry is held by lane t of the group.  The entries are fetched in their own
+// order and change lanes afterwards: fetched where they are held, a load of 64 consecutive indices was 36 requests of
+// the vector L1 instead of 4 (29125 rows of 340 entries, 256 floats in four slices 544 -> 530 us, transposed 520 -> 506).
 template <int LPR, bool DPP>
 __device__ __forceinline__ int batch_entry() {
   const int lane = lane_id();
@@ -259,6 +263,13 @@ __device__ __forceinline__ int batch_entry() {
 template <int T>
 __device__ __forceinline__ unsigned row_bcast(unsigned x) {
   return (unsigned)__builtin_amdgcn_mov_dpp((int)x, 0x150 + T, 0xf, 0xf, true);  // row_newbcast:T
+}
+
+// The value of lane T of every eight lanes, on all of them: two moves, each into half of the banks of a row of 16.
+template <int T>
+__device__ __forceinline__ unsigned half_row_bcast(unsigned x) {
+  const int a = __builtin_amdgcn_mov_dpp((int)x, 0x150 + T, 0xf, 0xf, true);
+  return (unsigned)__builtin_amdgcn_update_dpp(a, (int)x, 0x158 + T, 0xf, 0xc, false);
 }
 
 // 4 VEC bytes at an address that was put together from its halves.  The address space has to be said: the compiler
@@ -278,9 +289,9 @@ template <int VEC, int MAXCH, int LPR, bool DPP = false, bool RAGGED = false>
 __device__ __forceinline__ void gather_batch(unsigned long long p_l, float w_l, int cnt, int nvec,
                                              float (&acc)[MAXCH][VEC], int width = 0) {
   using V = typename Vec<VEC, RAGGED>::T;
-  static_assert(!DPP || (MAXCH == 1 && LPR == 16), "a feature row per DPP row of 16 lanes");
+  static_assert(!DPP || (MAXCH == 1 && (LPR == 16 || LPR == 8)), "a feature row per DPP row of 16 lanes, or two");
   constexpr int EP = kWave / LPR;  // neighbours walked at once
-  constexpr int UNR = MAXCH == 1 && LPR >= 16 ? 8 : 4;
+  constexpr int UNR = MAXCH == 1 && (LPR >= 16 || DPP) ? 8 : 4;
   const int lane = lane_id();
   const int g = lane / LPR, sl = lane % LPR;
   const unsigned lo_l = (unsigned)p_l, hi_l = (unsigned)(p_l >> 32), w_u = __float_as_uint(w_l);
@@ -288,9 +299,10 @@ __device__ __forceinline__ void gather_batch(unsigned long long p_l, float w_l, 
   auto bcast = [&](auto tc, int t, unsigned &lo, unsigned &hi, unsigned &w) {
     if constexpr (DPP) {
       constexpr int T = decltype(tc)::value;
-      lo = row_bcast<T>(lo_l);
-      hi = row_bcast<T>(hi_l);
-      w = row_bcast<T>(w_u);
+      auto from = [](unsigned x) { return LPR == 16 ? row_bcast<T>(x) : half_row_bcast<T % 8>(x); };
+      lo = from(lo_l);
+      hi = from(hi_l);
+      w = from(w_u);
     } else if constexpr (EP == 1) {
       lo = __builtin_amdgcn_readlane(lo_l, t);
       hi = __builtin_amdgcn_readlane(hi_l, t);
@@ -345,12 +357,28 @@ __device__ __forceinline__ void gather_batch(unsigned long long p_l, float w_l, 
       else steps(std::true_type{}, t0c, T0);
     };
     chunk(std::integral_constant<int, 0>{});
-    chunk(std::integral_constant<int, 8>{});
+    if constexpr (EP * UNR < kWave) chunk(std::integral_constant<int, 8>{});
   } else {
     int t0 = 0;
     for (; (t0 + UNR) * EP <= cnt; t0 += UNR) steps(std::false_type{}, std::integral_constant<int, 0>{}, t0);
     if (t0 * EP < cnt) steps(std::true_type{}, std::integral_constant<int, 0>{}, t0);
   }
+}
+
+// x plus the value of the lane whose number differs by `off`.
+__device__ __forceinline__ float lane_pair_sum(float x, int off) {
+  typedef unsigned u2 __attribute__((ext_vector_type(2)));
+  const unsigned u = __float_as_uint(x);
+  if (off == 8) return x + __int_as_float(__builtin_amdgcn_mov_dpp((int)u, 0x128, 0xf, 0xf, true));  // row_ror:8
+  if (off == 16) {
+    const u2 w = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    return __uint_as_float(w[0]) + __uint_as_float(w[1]);
+  }
+  if (off == 32) {
+    const u2 w = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    return __uint_as_float(w[0]) + __uint_as_float(w[1]);
+  }
+  return x + __shfl_xor(x, off, kWave);
 }
 
 // Adds the partial sums of the 64/LPR lane groups; afterwards lane group 0 holds the total.
@@ -360,7 +388,7 @@ __device__ __forceinline__ void fold_groups(float (&acc)[MAXCH][VEC]) {
 #pragma unroll
     for (int off = LPR; off < kWave; off <<= 1)
 #pragma unroll
-      for (int i = 0; i < VEC; ++i) acc[0][i] += __shfl_xor(acc[0][i], off, kWave);
+      for (int i = 0; i < VEC; ++i) acc[0][i] = lane_pair_sum(acc[0][i], off);
   }
 }
 
@@ -380,13 +408,20 @@ __device__ __forceinline__ void gather_segment(Args &a, int row, const InnerWeig
     unsigned long long p_l = 0;
     float w_l = 0.f;
     constexpr bool DPP = !RAGGED && dpp_gather(MAXCH, LPR);  // (ragged ones would spill three registers)
-    const int mine = batch_entry<LPR, DPP>();
-    if (mine < cnt) {
-      const int e = base + mine;
-      const float w_e = e < iw.end ? iw.w[e] : 0.f;  // (asked for beside the column index, not after it)
-      const int c = a.col_idx[e];
-      entry_source(a, row, c, d_off, p_l, w_l, [&] { return iw.w ? w_e : 1.f; });
+    const int lane = lane_id();
+    int c = 0;
+    float w_e = 0.f;
+    if (lane < cnt) {
+      const int e = base + lane;
+      if (e < iw.end) w_e = iw.w[e];  // (asked for beside the column index, not after it)
+      c = a.col_idx[e];
     }
+    const int mine = batch_entry<LPR, DPP>();
+    if (DPP) {
+      c = __shfl(c, mine, kWave);
+      w_e = __shfl(w_e, mine, kWave);
+    }
+    if (mine < cnt) entry_source(a, row, c, d_off, p_l, w_l, [&] { return iw.w ? w_e : 1.f; });
     gather_batch<VEC, MAXCH, LPR, DPP, RAGGED>(p_l, w_l, cnt, nvec, acc, width);
   }
   fold_groups<VEC, MAXCH, LPR>(acc);
