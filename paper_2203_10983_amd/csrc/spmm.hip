@@ -195,7 +195,7 @@ __global__ void __launch_bounds__(256) spmm_combine_kernel(const SpmmArgs a) {
 
 
 template <int VEC, bool RAGGED>
-static hipError_t launch_spmm_vec(const SpmmArgs &a_in, int64_t extra_rows, bool multi_only, int32_t avg_len, bool transposed, hipStream_t s) {
+static hipError_t launch_spmm_vec(const SpmmArgs &a_in, int64_t extra_rows, bool multi_only, float halo_share, int32_t avg_len, bool transposed, hipStream_t s) {
   SpmmArgs a = a_in;
   // multi_only: the segments of the multi-segment rows, i.e. the partial-sum slots
   a.head.n_units = multi_only ? a.plan.n_part : a.plan.n_seg;
@@ -223,6 +223,14 @@ static hipError_t launch_spmm_vec(const SpmmArgs &a_in, int64_t extra_rows, bool
     if (transposed)
       from = ((int64_t)a.head.n_units << ls) <= 8192 ? 19 : a.head.n_units < 24576 ? 32 : ls == 0 ? 19 : 24;
     if (avg_len >= from) ls = slices(64);
+  } else if (VEC == 4 && !RAGGED && multi_only && halo_share <= 0.15f) {
+    // Segments of long rows keep a wavefront busy at any width, so that their slices are as narrow as a 128-byte line (whole
+    // lines: any other cut would fetch some twice).  128 floats, whole / slices of 64 / of 32, us: 306250 rows of 45 entries
+    // 313 / 281 / 261, 100000 of 92 245 / 207 / 182, of 196 547 / 481 / 414, 250 in every row 796 / 760 / 684; 578125 of 21
+    // 274 / 264 / 266; 250000 of 20 73 / 71 / 73.  An entry of a boundary row is looked up in the kept nodes' records
+    // in every slice, a line each beside the four of its features: with 9 % of them 400000 rows of 20 216 / 191 / 180,
+    // with 24 % 306250 rows of 59 456 / 462 / 505, with 23 % 578125 of 29 410 / 430 / 482.
+    while (ls < 3 && (a.d >> (ls + 1)) >= 32 && a.d % (32 << (ls + 1)) == 0) ++ls;
   }
   a.head.log2_slices = ls;
   a.head.d_slice = RAGGED && ls > 0 ? ((a.d + (1 << ls) - 1) / (1 << ls) + 3) / 4 * 4 : a.d >> ls;  // (the last one of a ragged row is narrower)
@@ -343,19 +351,19 @@ static hipError_t launch_spmm_vec(const SpmmArgs &a_in, int64_t extra_rows, bool
   return hipGetLastError();
 }
 
-static hipError_t launch_spmm(const SpmmArgs &a, int64_t extra_rows, bool multi_only, int32_t avg_len, bool transposed, hipStream_t s) {
+static hipError_t launch_spmm(const SpmmArgs &a, int64_t extra_rows, bool multi_only, float halo_share, int32_t avg_len, bool transposed, hipStream_t s) {
   if (a.d_store != a.d && (a.d_store < 1 || a.d_store > a.d || a.d >= 128 || a.d % 4 != 0 || a.mask_src || a.init))
     return hipErrorInvalidValue;  // padded sources: narrow rows without mask or initial value only
-  if (a.d % 4 == 0) return launch_spmm_vec<4, false>(a, extra_rows, multi_only, avg_len, transposed, s);
+  if (a.d % 4 == 0) return launch_spmm_vec<4, false>(a, extra_rows, multi_only, halo_share, avg_len, transposed, s);
   // Widths that are no multiple of 4: 16-byte loads at 4-byte alignment, and slices as for the others, where loads of 8 or 4 bytes
   // took up to four times as many instructions (130 floats: 65 lanes, a second load for the last one) and could not be
   // sliced.  Forward and transposed, us: 60000 rows of 45 entries, 31 floats 75 -> 62 and 130 -> 91, 66 120 -> 108 and 225 -> 144, 130
   // 232 -> 197 and 443 -> 235, 258 413 -> 403 and 660 -> 404, 602 907 -> 855 and 1235 -> 846; 20011 rows of 14, 9 floats the same,
   // 66 34 -> 28 and 45 -> 35, 130 56 -> 39 and 81 -> 50, 602 145 -> 111 and 189 -> 126.  Up to 8 floats a row is one or two
   // pieces, of which a wavefront has more than there are entries (20011 rows, 6 floats: 17.7 and 19.8 us, in pieces of 16 bytes 18.5 and 20.6).
-  if (a.d > 8) return launch_spmm_vec<4, true>(a, extra_rows, multi_only, avg_len, transposed, s);
-  if (a.d % 2 == 0) return launch_spmm_vec<2, false>(a, extra_rows, multi_only, avg_len, transposed, s);
-  return launch_spmm_vec<1, false>(a, extra_rows, multi_only, avg_len, transposed, s);
+  if (a.d > 8) return launch_spmm_vec<4, true>(a, extra_rows, multi_only, halo_share, avg_len, transposed, s);
+  if (a.d % 2 == 0) return launch_spmm_vec<2, false>(a, extra_rows, multi_only, halo_share, avg_len, transposed, s);
+  return launch_spmm_vec<1, false>(a, extra_rows, multi_only, halo_share, avg_len, transposed, s);
 }
 
 hipError_t spmm_fwd(const SegPlan &plan, int32_t n_in, int32_t d, const int32_t *row_ptr,
@@ -365,7 +373,7 @@ hipError_t spmm_fwd(const SegPlan &plan, int32_t n_in, int32_t d, const int32_t 
   SpmmArgs a = spmm_fwd_args(plan, n_in, d, row_ptr, col_idx, w_in, w_ptr, row_scale, H_in, Hu, partials, A, part);
   a.relu = relu;
   if (d_store > 0) a.d_store = d_store;
-  return launch_spmm(a, -1, long_rows_only, plan.avg_len, false, s);
+  return launch_spmm(a, -1, long_rows_only, part.halo_share, plan.avg_len, false, s);
 }
 
 hipError_t spmm_bwd(const SegPlan &plan, int32_t n_in, int32_t n_halo, int32_t d,
@@ -382,7 +390,7 @@ hipError_t spmm_bwd(const SegPlan &plan, int32_t n_in, int32_t n_halo, int32_t d
   a.out0 = dH_in; a.out1 = dhalo; a.out_scale0 = row_scale; a.mask_src = mask_src;
   a.kept_ids = kept_ids; a.dis_halo = dis_halo; a.s_halo = s_halo;
   a.init = init; a.skip_self = skip_self;
-  return launch_spmm(a, halo_rows ? expected_halo : -1, false, avg_len, true, s);
+  return launch_spmm(a, halo_rows ? expected_halo : -1, false, 0.f, avg_len, true, s);
 }
 
 // ------------------------------------------------------------------------------------------
