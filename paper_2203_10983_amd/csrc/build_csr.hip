@@ -140,10 +140,27 @@ __device__ __forceinline__ void bd_fill_tile(const FillArgs &a) {
     cnt += __popcll(mask[i]);
   }
   if (lane == 0) wave_cnt[wid] = cnt;
-  // kept boundary entries in the tiles before this one: summed here from the raw per-tile counts (ends with a barrier)
-  int run = tiles_before<kBdThreads>(a.bd.sums, blockIdx.x, a.bd_tiles, nullptr);
-  for (int w = 0; w < wid; ++w) run += wave_cnt[w];
+  // the reads of a stage all at once: they hang on each other (node and row, rank and place)
   const unsigned long long lower = (1ull << lane) - 1ull;
+  int node[kBdPasses], row[kBdPasses];
+#pragma unroll
+  for (int i = 0; i < kBdPasses; ++i) {
+    const int64_t k = base + i * kWave + lane;
+    const bool kept = (mask[i] >> lane) & 1ull;  // (then k < e_bd)
+    node[i] = kept ? a.bd.bd_b[k] : 0;
+    row[i] = kept ? a.bd_row[k] : 0;
+  }
+  // kept boundary entries in the tiles before this one: summed here from the raw per-tile counts (ends with a barrier)
+  int before[1], total[1];
+  tiles_before<kBdThreads, 1>(a.bd.sums, blockIdx.x, a.bd_tiles, false, before, total);
+#pragma unroll
+  for (int i = 0; i < kBdPasses; ++i)
+    if ((mask[i] >> lane) & 1ull) {
+      node[i] = a.n_in + a.remap[node[i]];
+      row[i] = a.inner_ptr[row[i] + 1];
+    }
+  int run = before[0];
+  for (int w = 0; w < wid; ++w) run += wave_cnt[w];
 #pragma unroll
   for (int i = 0; i < kBdPasses; ++i) {
     const int64_t k = base + i * kWave + lane;
@@ -151,7 +168,7 @@ __device__ __forceinline__ void bd_fill_tile(const FillArgs &a) {
     const int pos = run + __popcll(mask[i] & lower);
     if (k < e_bd) {
       a.kpos[k] = pos;
-      if (kept) a.col_idx[a.inner_ptr[a.bd_row[k] + 1] + pos] = a.n_in + a.remap[a.bd.bd_b[k]];
+      if (kept) a.col_idx[row[i] + pos] = node[i];
       if (k == e_bd - 1) a.kpos[e_bd] = pos + (kept ? 1 : 0);
     }
     run += __popcll(mask[i]);
@@ -231,13 +248,6 @@ finish_csr_kernel(int32_t n_in, int64_t e_in, int64_t e_bd, const int32_t *__res
     copy_static(st, n_in, e_in, blockIdx.x - blocks, gridDim.x - blocks);
     return;
   }
-  const int64_t stride = (int64_t)blocks * kThreads;
-  const int64_t t0 = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  for (int64_t v = t0; v <= n_in; v += stride) {
-    const int r = inner_ptr[v] + (e_bd > 0 ? kpos[bd_ptr[v]] : 0);
-    row_ptr[v] = r;
-    if (v == n_in) *nnz = r;
-  }
   // a tile of kFinishTile entries per workgroup and its reads all at once: they hang on each other (in_bdp, kpos, place)
   const int64_t j0 = (int64_t)blockIdx.x * kFinishTile + threadIdx.x;
   int c[kFinishPasses], k[kFinishPasses];
@@ -246,6 +256,13 @@ finish_csr_kernel(int32_t n_in, int64_t e_in, int64_t e_bd, const int32_t *__res
     const int64_t j = j0 + i * kThreads;
     c[i] = j < e_in ? in_col[j] : 0;
     k[i] = j < e_in && e_bd > 0 ? in_bdp[j] : -1;
+  }
+  const int64_t stride = (int64_t)blocks * kThreads;
+  const int64_t t0 = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+  for (int64_t v = t0; v <= n_in; v += stride) {
+    const int r = inner_ptr[v] + (e_bd > 0 ? kpos[bd_ptr[v]] : 0);
+    row_ptr[v] = r;
+    if (v == n_in) *nnz = r;
   }
 #pragma unroll
   for (int i = 0; i < kFinishPasses; ++i) k[i] = k[i] >= 0 ? kpos[k[i]] : 0;

@@ -14,7 +14,8 @@ namespace bns {
 __host__ __device__ inline int k_steps(int K) { return (K + 31) / 32; }
 __host__ __device__ inline int col_tiles(int N) { return (N + 15) / 16; }
 
-// One wavefront packs unit u of the jobs: one depth step of one column tile.
+// One wavefront packs unit u of the jobs: one depth step of one column tile.  Its elements are read without a branch between them, behind
+// which each would wait for the one before (packing of 602 x 130 beside 15000 records, both forms: 9.4 -> 4.7 us).
 __device__ __forceinline__ void pack_unit(const PackJobs &jobs, int u) {
   int q = 0;
   for (; q < jobs.n; ++q) {
@@ -34,8 +35,12 @@ __device__ __forceinline__ void pack_unit(const PackJobs &jobs, int u) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const int k = s * 32 + j * 16 + g * 4 + e;
-        v[j][e] = k < job.K && n < job.N ? job.W[(size_t)n * job.K + k] : 0.f;
+        v[j][e] = job.W[(size_t)min(n, job.N - 1) * job.K + min(k, job.K - 1)];
       }
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[j][e] = s * 32 + j * 16 + g * 4 + e < job.K && n < job.N ? v[j][e] : 0.f;
     const Frag3 f = t & 1 ? split8<true>(v[0], v[1]) : split8(v[0], v[1]);
     char *out = static_cast<char *>(job.out) + (size_t)u * kFragSet + lane * 16;
 #pragma unroll
@@ -44,15 +49,17 @@ __device__ __forceinline__ void pack_unit(const PackJobs &jobs, int u) {
     const int T = (job.N + 31) / 32, s = u / T, t = u % T;
     const int n = t * 32 + (lane & 31);
     char *out = static_cast<char *>(job.out) + (size_t)u * 4096 + lane * 16;
+    f32x4 v[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        v[j][i] = job.W[(size_t)min(s * 32 + j * 8 + i * 2 + (lane >> 5), job.K - 1) * job.N + min(n, job.N - 1)];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      f32x4 v;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int k = s * 32 + j * 8 + i * 2 + (lane >> 5);
-        v[i] = k < job.K && n < job.N ? job.W[(size_t)k * job.N + n] : 0.f;
-      }
-      *reinterpret_cast<f32x4 *>(out + j * 1024) = v;
+      for (int i = 0; i < 4; ++i) v[j][i] = s * 32 + j * 8 + i * 2 + (lane >> 5) < job.K && n < job.N ? v[j][i] : 0.f;
+      *reinterpret_cast<f32x4 *>(out + j * 1024) = v[j];
     }
   }
 }

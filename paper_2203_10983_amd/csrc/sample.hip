@@ -14,8 +14,8 @@ __device__ __forceinline__ uint32_t philox4x32_10_word0(uint32_t c0, uint32_t c1
   return c0;
 }
 
-constexpr int kSampleThreads = 256;
-constexpr int kSampleIters = kScanTile / kSampleThreads;  // 8 wave-words per wave and tile
+constexpr int kSampleThreads = kBdThreads;  // one launch carries both
+constexpr int kSampleIters = kScanTile / kSampleThreads;  // passes over a tile
 constexpr int kWordsPerTile = kScanTile / kWave;          // 32
 
 // Pass 1: keep flags as one 64-bit ballot word per 64 consecutive boundary nodes, and the
@@ -35,20 +35,32 @@ sample_flags_kernel(const int64_t *__restrict__ halo_gid, int32_t n_halo, uint32
   if (epoch_dev) epoch = *epoch_dev;  // epoch counter kept on the device (graph replay)
   const int lane = lane_id();
   int cnt = 0, len = 0;
+  uint64_t gid[kSampleIters];
+  bool keep[kSampleIters];
 #pragma unroll
   for (int it = 0; it < kSampleIters; ++it) {
     const int64_t b = (int64_t)blockIdx.x * kScanTile + it * kSampleThreads + threadIdx.x;
-    bool keep = false;
-    if (b < n_halo) {
-      const uint64_t gid = (uint64_t)halo_gid[b];
-      const uint32_t u = philox4x32_10_word0((uint32_t)gid, (uint32_t)(gid >> 32), epoch, part_id,
-                                             k0, k1);
-      keep = (uint64_t)u < threshold;
-    }
-    const uint64_t word = __ballot(keep);
+    gid[it] = b < n_halo ? (uint64_t)halo_gid[b] : 0;
+  }
+#pragma unroll
+  for (int it = 0; it < kSampleIters; ++it) {
+    const int64_t b = (int64_t)blockIdx.x * kScanTile + it * kSampleThreads + threadIdx.x;
+    const uint32_t u = philox4x32_10_word0((uint32_t)gid[it], (uint32_t)(gid[it] >> 32), epoch, part_id, k0, k1);
+    keep[it] = b < n_halo && (uint64_t)u < threshold;
+    const uint64_t word = __ballot(keep[it]);
     if (lane == 0 && b < n_halo) ballots[b >> 6] = word;
     cnt += (lane == 0) ? __popcll(word) : 0;
-    if (keep && halo_ptr) len += halo_ptr[b + 1] - halo_ptr[b];
+  }
+  if (halo_ptr) {
+    int end[kSampleIters], begin[kSampleIters];
+#pragma unroll
+    for (int it = 0; it < kSampleIters; ++it) {
+      const int64_t b = (int64_t)blockIdx.x * kScanTile + it * kSampleThreads + threadIdx.x;
+      begin[it] = keep[it] ? halo_ptr[b] : 0;
+      end[it] = keep[it] ? halo_ptr[b + 1] : 0;
+    }
+#pragma unroll
+    for (int it = 0; it < kSampleIters; ++it) len += end[it] - begin[it];
   }
   __shared__ int red[2][kSampleThreads / kWave];
   cnt = wave_sum(cnt);
@@ -92,32 +104,43 @@ sample_write_kernel(int32_t n_halo, const uint64_t *__restrict__ ballots,
   __shared__ int word_prefix[kWordsPerTile + 1];
   __shared__ int kept_b[kScanTile];
   const int lane = lane_id();
-  int total = 0, len_total = 0;
-  const int base = tiles_before<kSampleThreads>(tile_counts, blockIdx.x, tiles, blockIdx.x == 0 ? &total : nullptr);
-  int run = first;
-  if (halo_ptr)
-    run += tiles_before<kSampleThreads>(tile_counts + tiles, blockIdx.x, tiles,
-                                        blockIdx.x == 0 ? &len_total : nullptr);
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    *n_kept = total;
-    if (halo_ptr) kept_start[total] = first + len_total;
-  }
+  __shared__ uint64_t words[kWordsPerTile];
   const int64_t word0 = (int64_t)blockIdx.x * kWordsPerTile;
   const int64_t n_words = ((int64_t)n_halo + kWave - 1) / kWave;
   if (threadIdx.x < kWave) {
     const int64_t w = word0 + threadIdx.x;
-    const int c = (threadIdx.x < kWordsPerTile && w < n_words) ? __popcll(ballots[w]) : 0;
+    const uint64_t word = threadIdx.x < kWordsPerTile && w < n_words ? ballots[w] : 0ull;
+    const int c = __popcll(word);
     const int inc = wave_inclusive_scan(c);
-    if (threadIdx.x < kWordsPerTile) word_prefix[threadIdx.x] = inc - c;
+    if (threadIdx.x < kWordsPerTile) {
+      words[threadIdx.x] = word;
+      word_prefix[threadIdx.x] = inc - c;
+    }
     if (threadIdx.x == kWordsPerTile - 1) word_prefix[kWordsPerTile] = inc;  // kept nodes of the tile
   }
-  __syncthreads();
+  // kept nodes and the length of their lists in the tiles before this one (ends with a barrier)
+  int before[2], total[2];
+  if (halo_ptr) {
+    tiles_before<kSampleThreads, 2>(tile_counts, blockIdx.x, tiles, blockIdx.x == 0, before, total);
+  } else {
+    int b1[1], t1[1];
+    tiles_before<kSampleThreads, 1>(tile_counts, blockIdx.x, tiles, blockIdx.x == 0, b1, t1);
+    before[0] = b1[0];
+    total[0] = t1[0];
+    before[1] = total[1] = 0;
+  }
+  const int base = before[0];
+  int run = first + before[1];
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    *n_kept = total[0];
+    if (halo_ptr) kept_start[total[0]] = first + total[1];
+  }
 #pragma unroll
   for (int it = 0; it < kSampleIters; ++it) {
     const int local = it * kSampleThreads + threadIdx.x;
     const int64_t b = (int64_t)blockIdx.x * kScanTile + local;
     if (b < n_halo) {
-      const uint64_t word = ballots[b >> 6];
+      const uint64_t word = words[local >> 6];
       if ((word >> lane) & 1ull) {
         const int r = word_prefix[local >> 6] + __popcll(word & ((1ull << lane) - 1ull));
         kept_b[r] = (int32_t)b;
@@ -132,12 +155,17 @@ sample_write_kernel(int32_t n_halo, const uint64_t *__restrict__ ballots,
   for (int r0 = 0; r0 < tile_kept; r0 += kSampleThreads) {  // block-uniform trip count
     const int r = r0 + threadIdx.x;
     const int b = r < tile_kept ? kept_b[r] : -1;
+    int len = 0;
+    float dis = 1.f;
+    if (b >= 0) {
+      if (halo_ptr) len = halo_ptr[b + 1] - halo_ptr[b];
+      if (rec && dis_halo) dis = dis_halo[b];
+    }
     if (b >= 0) {
       kept_ids[base + r] = b;
-      if (rec) rec[base + r] = make_int2(b, __float_as_int(dis_halo ? s_halo * dis_halo[b] : s_halo));
+      if (rec) rec[base + r] = make_int2(b, __float_as_int(dis_halo ? s_halo * dis : s_halo));
     }
     if (halo_ptr) {
-      const int len = b >= 0 ? halo_ptr[b + 1] - halo_ptr[b] : 0;
       int sum;
       const int before = block_exclusive_scan<kSampleThreads>(len, &sum);
       if (b >= 0) kept_start[base + r] = run + before;
@@ -151,7 +179,6 @@ hipError_t sample_boundary(const int64_t *halo_gid, int32_t n_halo, uint64_t see
                            int32_t *tile_sums, int32_t *kept_ids, int32_t *remap, int32_t *n_kept,
                            const int32_t *halo_ptr, int32_t first, int32_t *kept_start, int2 *rec, const float *dis_halo, float s_halo,
                            const PackJobs *pack, const BdCount *count, hipStream_t s) {
-  static_assert(kSampleThreads == kBdThreads, "one launch carries both");
   if (!kept_start) halo_ptr = nullptr;
   const int nb = scan_tiles(n_halo) > 0 ? scan_tiles(n_halo) : 1;
   const PackJobs jobs = pack ? *pack : PackJobs{};
