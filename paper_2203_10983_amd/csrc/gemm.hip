@@ -21,9 +21,14 @@
 // one kernel adds them in a fixed order and puts the elements where they belong.
 //
 // What bounds them: the 128-wide products move 1 KB per row for 32 k flops and are bound by memory (dZ W^T on 578125 rows
-// 128 us, 4.6 TB/s; A^T dZ 141), the 512-wide ones by the matrix cores, six bf16 instructions per fp32 product (at the
-// dense rate 417 TFLOP/s of fp32 products): 89625 x 512 x 512 235 us (200 TFLOP/s) and 265 (177), where the splitting
+// 117 us, 5.1 TB/s; A^T dZ 128), the 512-wide ones by the matrix cores, six bf16 instructions per fp32 product (at the
+// dense rate 417 TFLOP/s of fp32 products): 89625 x 512 x 512 205 us (229 TFLOP/s) and 236 (199), where the splitting
 // beside the instructions takes the rest.
+//
+// Both ask for a step's rows while the one before is multiplied, and that only holds while no read stands behind a branch of
+// its own: where the last columns and rows, and rows by index, had such branches, the reads were waited for one by one.  Without
+// them, us: A^T dZ of 197758 rows by index x 602 x 256 547 -> 400, 306250 x 128 x 47 99 -> 62, 128 x 128 145 -> 117, 578125 x 128 x 172
+// 213 -> 170, 9570 rows of three layers 20 -> 15; dZ W^T of 578125 x 172 x 128 190 -> 173, 306250 x 47 x 128 102 -> 94.
 #include <algorithm>
 #include <type_traits>
 
@@ -99,12 +104,9 @@ __global__ void __launch_bounds__(256, R * NC > 8 || NC > 6 ? 3 : 4) gemm_rows_k
       if ((s + 1) * 32 <= p.K) {
 #pragma unroll
         for (int r = 0; r < R; ++r) ar[r][j] = *reinterpret_cast<const f32x4u *>(row_a[r] + k);
-      } else if ((p.K & 3) == 0) {  // pieces in or out as a whole
+      } else if (p.K >= 4) {  // settle() takes what is past the end away
 #pragma unroll
-        for (int r = 0; r < R; ++r) ar[r][j] = k < p.K ? *reinterpret_cast<const f32x4u *>(row_a[r] + k) : f32x4{0.f, 0.f, 0.f, 0.f};
-      } else if (k + 4 <= p.K) {
-#pragma unroll
-        for (int r = 0; r < R; ++r) ar[r][j] = *reinterpret_cast<const f32x4u *>(row_a[r] + k);
+        for (int r = 0; r < R; ++r) ar[r][j] = *reinterpret_cast<const f32x4u *>(row_a[r] + piece_start(k, p.K));
       } else {
 #pragma unroll
         for (int r = 0; r < R; ++r)
@@ -112,6 +114,13 @@ __global__ void __launch_bounds__(256, R * NC > 8 || NC > 6 ? 3 : 4) gemm_rows_k
           for (int e = 0; e < 4; ++e) ar[r][j][e] = k + e < p.K ? row_a[r][k + e] : 0.f;
       }
     }
+  };
+  auto settle = [&](int s) {
+    if ((s + 1) * 32 <= p.K || p.K < 4) return;
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int r = 0; r < R; ++r) ar[r][j] = row_end(ar[r][j], s * 32 + j * 16 + g * 4, p.K);
   };
   const unsigned lds0 = lds_offset_of(&Bs[0][0]);
   const int nt = min(NC, a.T - t0);  // column tiles of this block (uniform)
@@ -144,6 +153,7 @@ __global__ void __launch_bounds__(256, R * NC > 8 || NC > 6 ? 3 : 4) gemm_rows_k
       lds_dma_wait();
       __syncthreads();  // this step's weights are in LDS, and everybody is done with the other buffer
     }
+    settle(s);
 #pragma unroll
     for (int r = 0; r < R; ++r) fa[r] = split8(ar[r][0], ar[r][1]);
     const bool last = s + 1 == S;
@@ -360,16 +370,17 @@ __global__ void __launch_bounds__(256, 3) gemm_tn_kernel(const TnJobs jobs) {
   const int c4 = u % gcount, kg = u / gcount;
   const bool active = kg < KG;
   const float *src;
-  int ld, cols;  // columns in range at src (0..4)
+  int ld, cols, width;  // columns in range at src (0..4), of the whole row
   if (is_b) {
     src = a.B + n0 + c4 * 4;
-    ld = a.N;
+    ld = width = a.N;
     cols = a.N - (n0 + c4 * 4);
   } else {
     const int c = m0 + c4 * 4;
     src = a.A + c;
     ld = a.lda;
-    cols = (a.A2 ? a.a_split : a.M) - c;
+    width = a.A2 ? a.a_split : a.M;
+    cols = width - c;
     if (a.A2 && cols <= 0) {
       src = a.A2 + c - a.a_split;
       cols = a.M - c;
@@ -378,34 +389,45 @@ __global__ void __launch_bounds__(256, 3) gemm_tn_kernel(const TnJobs jobs) {
   const bool straddle = !is_b && a.A2 && cols > 0 && cols < 4;  // a_split % 4 != 0: one group takes from both
   const int row_of_a2 = straddle ? m0 + c4 * 4 - a.a_split : 0;
   cols = straddle ? min(4, a.M - (m0 + c4 * 4)) : max(0, min(4, cols));
-  const int32_t *rows = is_b ? nullptr : a.rows;  // A's rows by index
+  const bool by_piece = !straddle && width >= 4;  // four columns at once, the last four of a row where fewer are left
+  if (by_piece) src -= 4 - cols;
+  // A's rows by index: the indices of two steps in LDS, asked for one step before the rows that wait for them
+  __shared__ __attribute__((aligned(16))) int index[2][KS];
+  const bool by_index = a.rows && !is_b;
+  int next_index = 0;
+  auto ask_index = [&](int k0) { return a.rows[min(k0 + t, k_end - 1)]; };
+  const bool reads = active && cols > 0;
   f32x4 v[8];
-  auto load = [&](int k0) {
-    const int k = k0 + kg * 8;
-    if (!active) return;
-    if (cols == 4 && !straddle && k + 8 <= k_end) {
-      if (rows) {
-        int r[8];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) r[j] = rows[k + j];
+  for (int j = 0; j < 8; ++j) v[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  // (no branch around a single load: the next one would wait for it.  Rows past the end repeat the last one, settle() clears them)
+  auto load = [&](int k0, int buf) {
+    if (!reads) return;
+    int r[8];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) v[j] = *reinterpret_cast<const f32x4u *>(src + (size_t)r[j] * ld);
-      } else {
+    for (int j = 0; j < 8; ++j) r[j] = by_index ? index[buf][kg * 8 + j] : min(k0 + kg * 8 + j, k_end - 1);
+    if (by_piece) {
 #pragma unroll
-        for (int j = 0; j < 8; ++j) v[j] = *reinterpret_cast<const f32x4u *>(src + (size_t)(k + j) * ld);
-      }
+      for (int j = 0; j < 8; ++j) v[j] = *reinterpret_cast<const f32x4u *>(src + (size_t)r[j] * ld);
     } else {
+      const float *at[4];
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const int r = k + j < k_end ? (rows ? rows[k + j] : k + j) : 0;
+      for (int e = 0; e < 4; ++e) at[e] = straddle && row_of_a2 + e >= 0 ? a.A2 + row_of_a2 + min(e, cols - 1) : src + min(e, cols - 1);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          float xv = 0.f;
-          if (e < cols && k + j < k_end)
-            xv = straddle && row_of_a2 + e >= 0 ? a.A2[(size_t)r * ld + row_of_a2 + e] : src[(size_t)r * ld + e];
-          v[j][e] = xv;
-        }
-      }
+      for (int j = 0; j < 8; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[j][e] = at[e][(size_t)r[j] * ld];
+    }
+  };
+  auto settle = [&](int k0) {
+    const int k = k0 + kg * 8;
+    if (!reads || (cols == 4 && k + 8 <= k_end)) return;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      f32x4 x = v[j];
+      if (by_piece) x = row_end(x, 4 - cols, 4);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[j][e] = e < cols && k + j < k_end ? x[e] : 0.f;
     }
   };
   // column 4 c4 + i sits in slot 4 i + c4 % 4 of its tile (so that four lanes store 64 contiguous bytes)
@@ -427,15 +449,29 @@ __global__ void __launch_bounds__(256, 3) gemm_tn_kernel(const TnJobs jobs) {
   for (int j = 0; j < NT; ++j)
 #pragma unroll
     for (int i = 0; i < MT; ++i) acc[j][i] = f32x4{0.f, 0.f, 0.f, 0.f};
-  if (k_begin < k_end) load(k_begin);
+  if (k_begin < k_end) {
+    if (a.rows) {
+      if (t < KS) {
+        index[0][t] = ask_index(k_begin);
+        index[1][t] = ask_index(k_begin + KS);
+      }
+      __syncthreads();
+    }
+    load(k_begin, 0);
+  }
+  int buf = 0;
   for (int k0 = k_begin; k0 < k_end; k0 += KS) {
+    settle(k0);
     __syncthreads();  // the previous step's fragments have been read
+    if (a.rows && t < KS && k0 > k_begin) index[buf ^ 1][t] = next_index;
     if (active) {
       if (neg) stage(std::true_type{});
       else stage(std::false_type{});
     }
     __syncthreads();
-    if (k0 + KS < k_end) load(k0 + KS);
+    buf ^= 1;
+    if (k0 + KS < k_end) load(k0 + KS, buf);
+    if (a.rows && t < KS) next_index = ask_index(k0 + 2 * KS);
 #pragma unroll
     for (int ks = 0; ks < KS / 32; ++ks) {
       const char *base = lds + (size_t)ks * TILES * kTnTile + lane * 16;

@@ -35,6 +35,23 @@ typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 constexpr int kFragBytes = 1024;             // one operand fragment: 64 lanes x 8 bf16 (16 rows x 32 k)
 constexpr int kFragSet = 3 * kFragBytes;     // its three pieces
 
+// The last piece of a row whose length is no multiple of 4 is read four floats from the end: behind a branch per element each
+// read would wait for the one before.  row_end() makes of it the piece that starts at k, in a row of n >= 4 floats: moved down,
+// zero past the end.
+__device__ __forceinline__ int piece_start(int k, int n) { return min(k, n - 4); }
+__device__ __forceinline__ f32x4 row_end(const f32x4 &x, int k, int n) {
+  const int by = k - piece_start(k, n);
+  const bool one = by & 1, two = by & 2, all = by >= 4;
+  f32x4 y;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) y[e] = one ? (e < 3 ? x[e + 1 < 4 ? e + 1 : 3] : 0.f) : x[e];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) y[e] = two ? (e < 2 ? y[e + 2 < 4 ? e + 2 : 3] : 0.f) : y[e];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) y[e] = all ? 0.f : y[e];
+  return y;
+}
+
 // The pieces of two values, packed in pairs (first value in the low half).
 __device__ __forceinline__ void split_pair(float x, float y, unsigned &hi, unsigned &mid, unsigned &lo) {
   hi = __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2){x, y}, bf16x2));
