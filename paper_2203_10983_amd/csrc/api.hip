@@ -141,11 +141,6 @@ bool one_kernel_layer(const bns_ctx *ctx, int d_in, int d_out) {
 // not cut the 16-deep groups that a depth is zero-padded to.
 bool concat_in_one(int d_in) { return d_in % 16 == 0; }
 
-// Do a and b, of na and nb floats, share memory?
-bool overlap(const float *a, size_t na, const float *b, size_t nb) {
-  const uintptr_t x = (uintptr_t)a, y = (uintptr_t)b;
-  return x < y + nb * sizeof(float) && y < x + na * sizeof(float);
-}
 // Aggregate and update of a layer of a small partition in one launch, a few rows per workgroup?  A launch and a pass over
 // the aggregate less; with more rows than fill the chip the weights, read anew for every tile, cost more than they save, and a row
 // of several segments, which its workgroup gathers alone, does so sooner.  Steps, two launches per layer / one (us): without such

@@ -548,28 +548,45 @@ struct TnSums {
   TnSum j[kMaxTnJobs];
   int n, blocks;
   float lr;
-  const float *loss_partials;
-  int n_loss;
-  float *loss;
-  uint32_t *bump;
+  TnLoss loss;
 };
+
+// The sum of the partial losses, by NW wavefronts; part: room for one float per wavefront.
+template <int NW>
+__device__ __forceinline__ void sum_loss(const TnLoss &loss, float *part) {
+  const int lane = lane_id(), wid = threadIdx.x >> 6;
+  float x = 0.f;
+  for (int i = threadIdx.x; i < loss.n; i += NW * 64) x += loss.partials[i];
+  x = wave_sum(x);
+  if (lane == 0) part[wid] = x;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    float s = 0.f;
+    for (int w = 0; w < NW; ++w) s += part[w];
+    *loss.out = s;
+    if (loss.bump) *loss.bump += 1;
+  }
+}
+
+// a + b, c + d, ... in pairs, then the pairs.
+template <int NW>
+__device__ __forceinline__ float sum_in_pairs(const float (&part)[NW][256], int e) {
+  float p[NW];
+#pragma unroll
+  for (int w = 0; w < NW; ++w) p[w] = part[w][e];
+#pragma unroll
+  for (int h = NW / 2; h > 0; h /= 2)
+#pragma unroll
+    for (int w = 0; w < h; ++w) p[w] += p[w + h];
+  return p[0];
+}
 
 template <int NW>
 __global__ void __launch_bounds__(NW * 64) gemm_tn_reduce_kernel(const TnSums jobs) {
   __shared__ float part[NW][256];
   const int lane = lane_id(), wid = threadIdx.x >> 6;
   if ((int)blockIdx.x == jobs.blocks) {
-    float x = 0.f;
-    for (int i = threadIdx.x; i < jobs.n_loss; i += NW * 64) x += jobs.loss_partials[i];
-    x = wave_sum(x);
-    if (lane == 0) part[0][wid] = x;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      float s = 0.f;
-      for (int w = 0; w < NW; ++w) s += part[0][w];
-      *jobs.loss = s;
-      if (jobs.bump) *jobs.bump += 1;
-    }
+    sum_loss<NW>(jobs.loss, part[0]);
     return;
   }
   int q = 0;
@@ -596,14 +613,7 @@ __global__ void __launch_bounds__(NW * 64) gemm_tn_reduce_kernel(const TnSums jo
   __syncthreads();
   const int e = threadIdx.x;
   if (e >= 256) return;
-  float p[NW];
-#pragma unroll
-  for (int w = 0; w < NW; ++w) p[w] = part[w][e];
-#pragma unroll
-  for (int h = NW / 2; h > 0; h /= 2)
-#pragma unroll
-    for (int w = 0; w < h; ++w) p[w] += p[w + h];
-  const float s = p[0];
+  const float s = sum_in_pairs<NW>(part, e);
   // element e: lane e / 4, register e % 4; its slots in the two 16-column tiles are 4 (lane / 16) + e % 4
   // (columns of B) and lane % 16 (columns of A), slot q standing for column 4 (q % 4) + q / 4
   const int per_wave = a.mt * a.nt_wave, l = e >> 2, w4 = f / per_wave, ji = f % per_wave;
@@ -612,6 +622,78 @@ __global__ void __launch_bounds__(NW * 64) gemm_tn_reduce_kernel(const TnSums jo
   const int n = (tile % a.tiles_n) * (32 * a.nt_wave) + ((w4 & 1) * a.nt_wave + j) * 16 + 4 * (e & 3) + (l >> 4);
   if (m >= a.M || n >= a.N) return;
   const size_t at = (size_t)m * a.N + n;
+  a.C[at] = s;
+  if (a.W) a.W[at] -= jobs.lr * s;
+}
+
+// ---- few rows: product and sum in one launch -------------------------------------------------------
+// A workgroup of 16 wavefronts owns a tile of 16 x 16 of a gradient; wavefront w takes the depths 32 w .. + 31 of every 512 straight
+// from memory into the operand layout (a lane reads eight depths of one column, 16 lanes 64 contiguous bytes of a row).
+struct TnSmallJob {
+  const float *A, *A2, *B;
+  float *C, *W;
+  int M, N, K, a_split, lda, tiles_n, first;
+};
+struct TnSmallJobs {
+  TnSmallJob j[kMaxTnJobs];
+  int n, blocks;
+  float lr;
+  TnLoss loss;
+};
+constexpr int kTnSmallWaves = 16;
+
+__global__ void __launch_bounds__(kTnSmallWaves * kWave) gemm_tn_small_kernel(const TnSmallJobs jobs) {
+  constexpr int NW = kTnSmallWaves;
+  __shared__ float part[NW][256];
+  const int lane = lane_id(), wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if ((int)blockIdx.x == jobs.blocks) {
+    sum_loss<NW>(jobs.loss, part[0]);
+    return;
+  }
+  int q = 0;
+  while (q + 1 < jobs.n && (int)blockIdx.x >= jobs.j[q + 1].first) ++q;
+  const TnSmallJob &a = jobs.j[q];
+  const int tile = (int)blockIdx.x - a.first, m0 = tile / a.tiles_n * 16, n0 = tile % a.tiles_n * 16;
+  const int m = min(m0 + (lane & 15), a.M - 1), n = min(n0 + (lane & 15), a.N - 1), g = lane >> 4;  // (lanes past the end are not stored)
+  const float *const pa = a.A2 && m >= a.a_split ? a.A2 + (m - a.a_split) : a.A + m;
+  const float *const pb = a.B + n;
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  for (int k0 = wid * 32; k0 < a.K; k0 += NW * 32) {
+    f32x4 x[2], y[2];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const int k = min(k0 + g * 8 + e, a.K - 1);
+      x[e / 4][e % 4] = pa[(size_t)k * a.lda];
+      y[e / 4][e % 4] = pb[(size_t)k * a.N];
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const bool in = k0 + g * 8 + e < a.K;
+      x[e / 4][e % 4] = in ? x[e / 4][e % 4] : 0.f;
+      y[e / 4][e % 4] = in ? y[e / 4][e % 4] : 0.f;
+    }
+    const Frag3 fy = split8(y[0], y[1]);
+    Frag3 fx[1];
+    fx[0] = wid & 1 ? split8<true>(x[0], x[1]) : split8(x[0], x[1]);  // (odd sums run negated: mfma_split)
+    f32x4 t[1];
+    mfma_split<1>(t, fy, fx);
+    acc += t[0];
+  }
+  *reinterpret_cast<f32x4 *>(&part[wid][lane * 4]) = wid & 1 ? -acc : acc;
+  __syncthreads();
+  const int e = threadIdx.x;
+  if (e >= 256) return;
+  float s = sum_in_pairs<NW>(part, e);
+  // element e: lane e / 4, register e % 4, that is column (lane % 16) of A and 4 (lane / 16) + e % 4 of B
+  const int cm = m0 + ((e >> 2) & 15), cn = n0 + (e >> 6) * 4 + (e & 3);
+  if (cm >= a.M || cn >= a.N) return;
+  if (!is_finite(s)) {
+    const float *const px = a.A2 && cm >= a.a_split ? a.A2 + (cm - a.a_split) : a.A + cm;
+    s = 0.f;
+#pragma unroll 1
+    for (int k = 0; k < a.K; ++k) s = fmaf(px[(size_t)k * a.lda], a.B[(size_t)k * a.N + cn], s);
+  }
+  const size_t at = (size_t)cm * a.N + cn;
   a.C[at] = s;
   if (a.W) a.W[at] -= jobs.lr * s;
 }
@@ -649,6 +731,37 @@ void tn_tiles(int32_t M, int32_t N, int64_t K, TnPlan *b) {
 
 int tn_splits(int64_t K, int64_t chunk) { return (int)std::max<int64_t>(1, (K + chunk - 1) / chunk); }
 
+// Product and sum in one launch?  It saves the launch of the sums, 3 to 4 us, and those of further tile shapes; a round of 512
+// workgroups and 512 rows takes 1.7 to 2.3 us.  The line: three rounds, six where the products alone are two launches or more.
+// Steps, general way / so, us: 64-16-8, 400 rows (one round) 29.5 / 24.9, 1000 (2) 32.0 / 29.2, 2000 (4) 36.0 / 35.9, 3000 (6) 43.8 / 47.3;
+// 128-128-128-47, 400 rows 50.5 / 45.4, 1000 55.4 / 53.6, 2000 66.6 / 67.4; with several launches, mean aggregator 100-66-66-9, 400 rows 89.6 / 78.5,
+// 2000 107 / 98, 3000 115 / 111, 5000 (10) 126 / 130, 300-512-512-100, 400 rows (4) 132 / 124, 1000 (8) 141 / 142.  Not where a
+// gradient or the weights lie in the same memory as an operand: the other way has read all before it writes.
+bool tn_small(const TnGemm *g, int32_t n, int launches, TnSmallJobs *out) {
+  constexpr int kRound = 512;
+  int64_t blocks = 0, rows = 0;
+  for (int i = 0; i < n; ++i) {
+    if (g[i].rows || g[i].k_dev || g[i].accumulate) return false;
+    const int tiles_n = (g[i].N + 15) / 16;
+    const int lda = g[i].A2 ? g[i].a_split : g[i].M;
+    out->j[out->n++] = TnSmallJob{g[i].A, g[i].A2, g[i].B, g[i].C, g[i].lr > 0.f ? g[i].W : nullptr, g[i].M, g[i].N, g[i].K, g[i].a_split, lda, tiles_n,
+                                  (int)blocks};
+    if (g[i].lr > 0.f) out->lr = g[i].lr;
+    blocks += (int64_t)((g[i].M + 15) / 16) * tiles_n;
+    rows = std::max<int64_t>(rows, g[i].K);
+  }
+  out->blocks = (int)blocks;
+  if (n == 0 || ((blocks + kRound - 1) / kRound) * ((rows + kRound - 1) / kRound) > (launches > 1 ? 6 : 3)) return false;
+  for (int i = 0; i < n; ++i)
+    for (int k = 0; k < n; ++k) {
+      const size_t result = (size_t)g[i].M * g[i].N, a = (size_t)g[k].K * out->j[k].lda;
+      for (const float *w : {(const float *)g[i].C, (const float *)out->j[i].W})
+        if (w && (overlap(w, result, g[k].A, a) || (g[k].A2 && overlap(w, result, g[k].A2, a)) || overlap(w, result, g[k].B, (size_t)g[k].K * g[k].N)))
+          return false;
+    }
+  return true;
+}
+
 template <int MB, int NB>
 void launch_tn(const TnJobs &jobs, unsigned blocks, hipStream_t s) {
   gemm_tn_kernel<MB, NB><<<blocks, 256, 0, s>>>(jobs);
@@ -685,6 +798,20 @@ hipError_t gemm_tn(const TnGemm *g, int32_t n, const TnLoss &loss, hipStream_t s
     if (alone[i]) plan[i].splits = (int)splits;
   }
   auto same = [&](int i, int k) { return !alone[k] && !alone[i] && plan[k].mb == plan[i].mb && plan[k].nb == plan[i].nb; };
+  {
+    TnSmallJobs small{};
+    int launches = 0;  // of the products, otherwise
+    for (int i = 0; i < n; ++i) {
+      bool first = true;
+      for (int k = 0; k < i; ++k) first &= !same(k, i);
+      launches += first;
+    }
+    if (tn_small(g, n, launches, &small)) {
+      small.loss = loss;
+      gemm_tn_small_kernel<<<(unsigned)(small.blocks + (loss.out ? 1 : 0)), kTnSmallWaves * kWave, 0, s>>>(small);
+      return hipGetLastError();
+    }
+  }
   for (int i = 0; i < n; ++i) {
     if (alone[i]) continue;
     auto blocks = [&](int64_t chunk) {
@@ -735,10 +862,7 @@ hipError_t gemm_tn(const TnGemm *g, int32_t n, const TnLoss &loss, hipStream_t s
   }
   bool many = false;
   for (int i = 0; i < sums.n; ++i) many |= std::max(sums.j[i].splits, sums.j[i].splits2) > 32;
-  sums.loss_partials = loss.partials;
-  sums.n_loss = loss.n;
-  sums.loss = loss.out;
-  sums.bump = loss.bump;
+  sums.loss = loss;
   const unsigned blocks = (unsigned)(sums.blocks + (loss.out ? 1 : 0));
   if (blocks == 0) return hipSuccess;
   if (many) gemm_tn_reduce_kernel<16><<<blocks, 1024, 0, s>>>(sums);

@@ -306,6 +306,11 @@ struct TnLoss {
   float *out = nullptr;
   uint32_t *bump = nullptr;  // nullable, with out: *bump += 1 (the epoch of a captured step, whose last launch this is)
 };
+// Do a and b, of na and nb floats, share memory?
+inline bool overlap(const float *a, size_t na, const float *b, size_t nb) {
+  const uintptr_t x = (uintptr_t)a, y = (uintptr_t)b;
+  return x < y + nb * sizeof(float) && y < x + na * sizeof(float);
+}
 constexpr int kMaxTnJobs = 16;
 size_t gemm_tn_partials(int32_t M, int32_t N, int32_t K, int32_t K_other);
 hipError_t gemm_tn(const TnGemm *g, int32_t n, const TnLoss &loss, hipStream_t s);

@@ -63,6 +63,13 @@ def test_products(n, d_in, d_out, kind):
     ctx.close()
 
 
+@pytest.mark.parametrize("kind", [0, 1], ids=["gcn", "sage"])
+@pytest.mark.parametrize("n,d_in,d_out", [(512, 17, 33), (513, 33, 9), (1536, 66, 47), (1537, 66, 47), (400, 602, 256), (512, 300, 509)], ids=lambda v: str(v))
+def test_products_of_few_rows(n, d_in, d_out, kind):
+    """On either side of the lines up to which A^T dZ is a single launch: 512 rows, three times as many, 512 tiles."""
+    test_products(n, d_in, d_out, kind)
+
+
 @pytest.mark.parametrize("half_zero", [False, True], ids=["normal", "masked"])
 @pytest.mark.parametrize("n,d_in,d_out", [(2000, 96, 128), (2000, 64, 512), (4000, 512, 512), (4099, 128, 172), (60000, 128, 128)],
                          ids=lambda v: str(v))
