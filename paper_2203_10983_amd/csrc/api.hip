@@ -140,6 +140,8 @@ bool one_kernel_layer(const bns_ctx *ctx, int d_in, int d_out) {
 // The concatenated update [z | h] [W_n ; W_s] of the mean-aggregator layer as one product: the seam must
 // not cut the 16-deep groups that a depth is zero-padded to.
 bool concat_in_one(int d_in) { return d_in % 16 == 0; }
+// Bytes of K rows of a layer's packed forward weights.
+size_t packed_fwd_bytes(int32_t d_in, int32_t K, int32_t N) { return fwd_by_splits(d_in) ? packed_bytes(K, N) : packed_bytes_f32(K, N); }
 
 // Aggregate and update of a layer of a small partition in one launch, a few rows per workgroup?  A launch and a pass over
 // the aggregate less; with more rows than fill the chip the weights, read anew for every tile, cost more than they save, and a row
@@ -273,7 +275,7 @@ size_t carve(Carver &c, const bns_partition_desc *p, const bns_model_desc *m, La
       else w.G_halo[l] = w.Hu2;
       hu2_taken = true;
     }
-    w.Wf[l] = c.take<char>(std::max(packed_bytes_f32(kw * m->dims[l - 1], m->dims[l]), kw * packed_bytes_f32(m->dims[l - 1], m->dims[l])));
+    w.Wf[l] = c.take<char>(std::max(packed_fwd_bytes(m->dims[l - 1], kw * m->dims[l - 1], m->dims[l]), kw * packed_fwd_bytes(m->dims[l - 1], m->dims[l - 1], m->dims[l])));
     w.Wb[l] = c.take<char>(kw * packed_bytes(m->dims[l], m->dims[l - 1]));
     w.A[l] = c.take<float>(n_in * (size_t)m->dims[l - 1]);
     if (behind[l] && w.A[l]) w.G_in[l] = w.A[l] + behind[l];
@@ -394,7 +396,7 @@ bns_status layer_fwd_impl(bns_ctx *ctx, int layer, double p, const float *H_in, 
         g.m2_expected = expected_kept(ctx, p);
         g.m2_dev = ctx->cur_n_kept;
       }
-      BNS_TRY("gemm_rows_f32", gemm_rows_f32(g, s));
+      BNS_TRY("gemm_fwd", gemm_fwd(g, W, s));
     }
     PhaseTimer t(ctx, BNS_PHASE_SPMM_FWD, s);
     BNS_TRY("spmm_fwd", spmm_fwd(ctx->ws.plan_f, n_in, ld, ctx->cur_row_ptr, ctx->cur_col_idx, ctx->ws.w_fwd,
@@ -474,14 +476,15 @@ bns_status layer_fwd_impl(bns_ctx *ctx, int layer, double p, const float *H_in, 
       g.a_split = d_in;
       g.K = 2 * d_in;
     } else if (sage) {  // z W_n + h W_s
-      BNS_TRY("gemm_rows_f32(nbr)", gemm_rows_f32(g, s));
+      BNS_TRY("gemm_fwd(nbr)", gemm_fwd(g, W, s));
+      W += (size_t)d_in * d_out;
       g.A = H_in;
-      g.Bp = ctx->ws.Wf[layer] + packed_bytes_f32(d_in, d_out);
+      g.Bp = ctx->ws.Wf[layer] + packed_fwd_bytes(d_in, d_in, d_out);
       g.accumulate = true;
     }
     g.relu = relu;
     g.drop = dropout_of(ctx, layer, relu);
-    BNS_TRY("gemm_rows_f32(update)", gemm_rows_f32(g, s));
+    BNS_TRY("gemm_fwd(update)", gemm_fwd(g, W, s));
   }
   return BNS_OK;
 }
@@ -527,7 +530,7 @@ bns_status layer_bwd_impl(bns_ctx *ctx, int layer, double p, const float *dZ, co
     RowsGemm g{};
     g.M = n_in;
     g.N = C2 ? 2 * d_in : d_in;
-    g.K = d_out;
+    g.K = g.lda = d_out;
     g.A = G;
     g.W = W;
     g.Bp = Wb;
@@ -680,19 +683,19 @@ bns_status layer_bwd_impl(bns_ctx *ctx, int layer, double p, const float *dZ, co
 void add_pack_jobs(const bns_ctx *ctx, int l, const float *W, bool fwd, bool bwd, PackJobs *jobs) {
   const int32_t kw = ctx->layer_kind == 1 ? 2 : 1, d_in = ctx->dims[l - 1], d_out = ctx->dims[l];
   const size_t half = (size_t)d_in * d_out;
-  auto add = [&](const float *w, char *out, int32_t K, int32_t N, bool split) {
+  auto add = [&](const float *w, char *out, int32_t K, int32_t N, bool split, bool of_fwd = false) {
     PackJob &j = jobs->j[jobs->n++];
-    j = PackJob{w, out, K, N, split};
+    j = PackJob{w, out, K, N, split, of_fwd};
     jobs->units += pack_units(j);
   };
   // a layer in one kernel reads its weights as they are
   if (fwd && (!one_kernel_layer(ctx, d_in, d_out) ||
               update_first_shape(ctx->layer_kind, d_in, d_out))) {
     if (kw == 2 && !concat_in_one(d_in)) {  // the two halves apart
-      add(W, ctx->ws.Wf[l], d_in, d_out, false);
-      add(W + half, ctx->ws.Wf[l] + packed_bytes_f32(d_in, d_out), d_in, d_out, false);
+      add(W, ctx->ws.Wf[l], d_in, d_out, fwd_by_splits(d_in), true);
+      add(W + half, ctx->ws.Wf[l] + packed_fwd_bytes(d_in, d_in, d_out), d_in, d_out, fwd_by_splits(d_in), true);
     } else {
-      add(W, ctx->ws.Wf[l], kw * d_in, d_out, false);
+      add(W, ctx->ws.Wf[l], kw * d_in, d_out, fwd_by_splits(d_in), true);
     }
   }
   if (bwd) {

@@ -1,8 +1,8 @@
-// The backward products of the update (Eq. 2) on the matrix cores: fp32 operands and results, products by
-// three-way bf16 splitting (split_bf16.hpp).
+// The backward products of the update (Eq. 2), and the forward ones of wide layers, on the matrix cores: fp32 operands and
+// results, products by three-way bf16 splitting (split_bf16.hpp).
 //
-//   gemm_rows   C = A B   dA = dZ W^T: a tall A [M, K] times a weight matrix, which pack_weights has
-//               split and laid out as operand fragments
+//   gemm_rows   C = A B   dA = dZ W^T, H = [A | A2] W: a tall A [M, K] times a weight matrix, which
+//               pack_weights has split and laid out as operand fragments
 //   gemm_tn     C = [A | A2]^T B  weight gradient dW = A^T dZ, the depth (rows) split over the chip
 //
 // gemm_rows: a workgroup of 4 wavefronts walks row tiles; a wavefront owns 16 R rows and NC column
@@ -23,7 +23,8 @@
 // What bounds them: the 128-wide products move 1 KB per row for 32 k flops and are bound by memory (dZ W^T on 578125 rows
 // 117 us, 5.1 TB/s; A^T dZ 128), the 512-wide ones by the matrix cores, six bf16 instructions per fp32 product (at the
 // dense rate 417 TFLOP/s of fp32 products): 89625 x 512 x 512 205 us (229 TFLOP/s) and 236 (199), where the splitting
-// beside the instructions takes the rest.
+// beside the instructions takes the rest.  Forward, against the fp32 matrix instruction, in a step, us: 89625 x 512 x 512 430 -> 258,
+// 89625 x 300 x 512 253 -> 161, 89625 x 1024 x 512 790 -> 490, 226887 rows, most of them by record, x 602 x 256 617 -> 367, 20011 x 602 x 130 55 -> 37.
 //
 // Both ask for a step's rows while the one before is multiplied, and that only holds while no read stands behind a branch of
 // its own: where the last columns and rows, and rows by index, had such branches, the reads were waited for one by one.  Without
@@ -58,11 +59,41 @@ struct RowsArgs {
   int T, S, nblk;  // column tiles, depth steps, column blocks
 };
 
-enum RowsEpilogue { kPlain = 0, kMask = 1, kPair = 2 };
+// The last three are a forward product's: with ReLU and dropout, added to what is there, with a second set of rows by record.
+enum RowsEpilogue { kPlain, kMask, kPair, kFwd, kFwdAdd, kFwdRec };
 
 // The value of the lane whose number differs in the last bit.
 __device__ __forceinline__ float quad_swap(float x) {
   return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0xb1, 0xf, 0xf, true));  // quad_perm:[1,0,3,2]
+}
+
+// Adds ReLU and dropout and stores `left` (0 to 4) of the columns col .. col + 3 of a row of a forward product.  All lanes draw for the dropout, those that
+// store nothing too: a wavefront with few of its lanes active takes longer over it.
+template <bool ADD>
+__device__ __forceinline__ void fwd_store(const RowsGemm &p, f32x4 v, int left, int row, int col, float *d) {
+  if constexpr (ADD) {
+    if (left == 4) v += *reinterpret_cast<const f32x4u *>(d);
+    else
+#pragma unroll
+      for (int e = 0; e < 3; ++e)
+        if (e < left) v[e] += d[e];
+  }
+  if (p.relu) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = fmaxf(v[e], 0.f);
+    if (p.drop.scale != 0.f) {
+#pragma unroll 1
+      for (int e = 0; e < 4; ++e) {
+        const float y = dropout_keeps(p.drop, row, col + e) ? v[0] * p.drop.scale : 0.f;
+        v = f32x4{v[1], v[2], v[3], y};
+      }
+    }
+  }
+  if (left == 4) *reinterpret_cast<f32x4u *>(d) = v;
+  else
+#pragma unroll
+    for (int e = 0; e < 3; ++e)
+      if (e < left) d[e] = v[e];
 }
 
 template <int R, int NC, int EPI>
@@ -70,7 +101,8 @@ __global__ void __launch_bounds__(256, R * NC > 8 || NC > 6 ? 3 : 4) gemm_rows_k
   constexpr int kRows = 64 * R;  // rows of a workgroup's tile
   __shared__ __attribute__((aligned(16))) char Bs[2][NC * kFragSet];
   const RowsGemm &p = a.g;
-  const int M = p.M, M2 = EPI != kPair && p.A_more ? min(p.M2, *p.m2_dev) : 0;
+  constexpr bool kForward = EPI >= kFwd, kMore = EPI != kPair && EPI != kFwd && EPI != kFwdAdd;
+  const int M = p.M, M2 = kMore && p.A_more ? min(p.M2, *p.m2_dev) : 0;
   // workgroup b runs on XCD b % 8: the column blocks of one row tile follow each other on one XCD, so
   // that they find its rows in that XCD's L2
   const int x = blockIdx.x & 7, q = blockIdx.x >> 3;
@@ -86,15 +118,24 @@ __global__ void __launch_bounds__(256, R * NC > 8 || NC > 6 ? 3 : 4) gemm_rows_k
   const int S = a.S;
 
   f32x4 ar[R][2];
-  const float *row_a[R];
+  const float *row_a[R], *row_a2[R];
+  float row_scale[R];  // kFwdRec: of the rows whose values ar holds
+  const bool two = kForward && p.A2 != nullptr;  // then a_split % 16 == 0
   auto set_rows = [&](int tl) {
-    const bool more = EPI != kPair && tl >= n_first;
+    const bool more = kMore && tl >= n_first;
     const float *A = more ? p.A_more : p.A;
     const int end = more ? M2 : M, first = (more ? tl - n_first : tl) * kRows;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      const int row = min(end - 1, first + wid * 16 * R + r * 16 + l16);  // rows past the end are not stored
-      row_a[r] = A + (size_t)row * p.K;
+      int row = min(end - 1, first + wid * 16 * R + r * 16 + l16);  // rows past the end are not stored
+      row_scale[r] = 1.f;
+      if (EPI == kFwdRec && more) {
+        const int2 rec = p.rec[row];
+        row = rec.x;
+        row_scale[r] = __int_as_float(rec.y);
+      }
+      row_a[r] = A + (size_t)row * p.lda;
+      if (EPI == kFwd) row_a2[r] = two ? p.A2 + (size_t)row * p.lda - p.a_split : nullptr;
     }
   };
   auto load_a = [&](int s) {
@@ -103,7 +144,7 @@ __global__ void __launch_bounds__(256, R * NC > 8 || NC > 6 ? 3 : 4) gemm_rows_k
       const int k = s * 32 + j * 16 + g * 4;
       if ((s + 1) * 32 <= p.K) {
 #pragma unroll
-        for (int r = 0; r < R; ++r) ar[r][j] = *reinterpret_cast<const f32x4u *>(row_a[r] + k);
+        for (int r = 0; r < R; ++r) ar[r][j] = *reinterpret_cast<const f32x4u *>((EPI == kFwd && two && s * 32 + j * 16 >= p.a_split ? row_a2[r] : row_a[r]) + k);
       } else if (p.K >= 4) {  // settle() takes what is past the end away
 #pragma unroll
         for (int r = 0; r < R; ++r) ar[r][j] = *reinterpret_cast<const f32x4u *>(row_a[r] + piece_start(k, p.K));
@@ -116,6 +157,11 @@ __global__ void __launch_bounds__(256, R * NC > 8 || NC > 6 ? 3 : 4) gemm_rows_k
     }
   };
   auto settle = [&](int s) {
+    if constexpr (EPI == kFwdRec)
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) ar[r][j] *= row_scale[r];
     if ((s + 1) * 32 <= p.K || p.K < 4) return;
 #pragma unroll
     for (int j = 0; j < 2; ++j)
@@ -181,12 +227,13 @@ __global__ void __launch_bounds__(256, R * NC > 8 || NC > 6 ? 3 : 4) gemm_rows_k
       constexpr bool kTrade = NC > 1;
       constexpr int W = kTrade ? 2 : 1, NP = (NC + W - 1) / W;  // tiles, and rows, of a trade
       const int odd = kTrade ? l16 & 1 : 0;
-      const int n_end = p.N, col0 = (t0 + odd) * 16 + g * 4;
-      const bool more = EPI != kPair && tile >= n_first;
+      const int n_end = EPI == kFwdRec && p.pad ? p.ldc : p.N, col0 = (t0 + odd) * 16 + g * 4;  // pad: the packed weights are zero there
+      const bool more = kMore && tile >= n_first;
       const int end = more ? M2 : M, row0 = (more ? tile - n_first : tile) * kRows + wid * 16 * R + l16 - odd;
       const float scale = more ? 1.f : p.alpha;
       const float alpha = (t0 + odd) & 1 ? -scale : scale;  // odd tiles are summed negated
       float nonfinite = 0.f;
+      unsigned again = 0;  // forward: pieces to be formed once more, which are not stored before
 #pragma unroll
       for (int r = 0; r < R; ++r)
 #pragma unroll
@@ -208,11 +255,23 @@ __global__ void __launch_bounds__(256, R * NC > 8 || NC > 6 ? 3 : 4) gemm_rows_k
 #pragma unroll
           for (int h = 0; h < W; ++h) {
             const int row = row0 + r * 16 + h;
-            if (row >= end || left <= 0) continue;
             f32x4 v = out[h];
-            nonfinite = nonfinite_seed(nonfinite, v);
             const size_t at = (size_t)row * p.ldc + col;
             const float a = W == 1 && (t0 + c) & 1 ? -scale : alpha;
+            if constexpr (kForward) {
+              float *const d = (more ? p.C_more : p.C) + at;
+#pragma unroll
+              for (int e = 0; e < 4; ++e) v[e] *= a;
+              const bool in = row < end && left > 0;
+              if (in && nonfinite_seed(0.f, v) != 0.f) {
+                again |= 1u << ((r * NP + c) * W + h);
+                continue;
+              }
+              fwd_store<EPI == kFwdAdd>(p, v, in ? min(left, 4) : 0, row, col, d);
+              continue;
+            }
+            if (row >= end || left <= 0) continue;
+            nonfinite = nonfinite_seed(nonfinite, v);
             if (EPI == kMask && !more) {
               const float *const ms = p.mask + at;
               f32x4 m = {0.f, 0.f, 0.f, 0.f};
@@ -235,7 +294,30 @@ __global__ void __launch_bounds__(256, R * NC > 8 || NC > 6 ? 3 : 4) gemm_rows_k
                 if (e < left) d[e] = v[e];
           }
         }
-      if (nonfinite != 0.f) {  // (NaN)
+      if constexpr (kForward) {
+#pragma unroll 1
+        for (; again; again &= again - 1) {
+          const int q = __ffs(again) - 1, c = q / W % NP, row = row0 + q / (NP * W) * 16 + q % W, col = col0 + c * 16 * W;
+          const int left = min(4, n_end - col);
+          int row_in = row;
+          const float *A = more ? p.A_more : p.A;
+          float by = 1.f;
+          if (EPI == kFwdRec && more) {
+            const int2 rec = p.rec[row];
+            row_in = rec.x;
+            by = __int_as_float(rec.y);
+          }
+          f32x4 x = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+          for (int k = 0; k < p.K; ++k) {
+            const float *const from = two && k >= p.a_split ? p.A2 - p.a_split : A;
+            const float y = from[(size_t)row_in * p.lda + k] * by;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) x[e] = col + e < p.N ? fmaf(y, p.W[(size_t)k * p.N + col + e], x[e]) : 0.f;
+          }
+          fwd_store<EPI == kFwdAdd>(p, x, left, row, col, (more ? p.C_more : p.C) + (size_t)row * p.ldc + col);
+        }
+      } else if (nonfinite != 0.f) {  // (NaN)
         const float *A = more ? p.A_more : p.A;
 #pragma unroll 1
         for (int q = 0; q < R * NP * W; ++q) {
@@ -283,7 +365,10 @@ static void launch_rows(const RowsArgs &a, int nc, unsigned grid, hipStream_t s)
 }
 template <int R>
 static void launch_rows(const RowsArgs &a, int nc, unsigned grid, hipStream_t s) {
-  if (a.g.C2) launch_rows<R, kPair>(a, nc, grid, s);
+  if (a.g.fwd && (a.g.rec || a.g.pad)) launch_rows<R, kFwdRec>(a, nc, grid, s);
+  else if (a.g.fwd && a.g.accumulate) launch_rows<R, kFwdAdd>(a, nc, grid, s);
+  else if (a.g.fwd) launch_rows<R, kFwd>(a, nc, grid, s);
+  else if (a.g.C2) launch_rows<R, kPair>(a, nc, grid, s);
   else if (a.g.mask) launch_rows<R, kMask>(a, nc, grid, s);
   else launch_rows<R, kPlain>(a, nc, grid, s);
 }
@@ -292,6 +377,11 @@ hipError_t gemm_rows(const RowsGemm &g, hipStream_t s) {
   if (g.M <= 0 || g.N <= 0) return hipSuccess;
   if (g.C2 ? g.c_split % 4 != 0 || g.ldc < g.c_split || g.N > 2 * g.c_split : g.ldc < g.N) return hipErrorInvalidValue;
   if (g.C2 && (g.mask || g.A_more)) return hipErrorInvalidValue;
+  if (g.fwd ? g.C2 || g.mask || g.lda < (g.A2 ? g.a_split : g.K) || (g.A2 && (g.a_split % 16 != 0 || g.K != 2 * g.a_split)) ||
+                  (g.A2 && (g.accumulate || g.rec)) || (g.rec && (g.accumulate || g.relu || !g.m2_dev)) || (g.A_more && !g.rec) ||
+                  (g.pad && (g.ldc > (g.N + 3) / 4 * 4 || g.A2 || g.relu || g.accumulate))
+            : g.A2 || g.rec || g.relu || g.pad || g.accumulate || g.lda != g.K)
+    return hipErrorInvalidValue;
   RowsArgs a;
   a.g = g;
   a.T = col_tiles(g.N);
@@ -317,6 +407,18 @@ hipError_t gemm_rows(const RowsGemm &g, hipStream_t s) {
   if (R == 2) launch_rows<2>(a, nc, grid, s);
   else launch_rows<1>(a, nc, grid, s);
   return hipGetLastError();
+}
+
+hipError_t gemm_fwd(const RowsF32 &f, const float *W, hipStream_t s) {
+  if (!fwd_by_splits(f.A2 ? f.a_split : f.K)) return gemm_rows_f32(f, s);
+  RowsGemm g{};
+  g.fwd = true;
+  g.M = f.M; g.N = f.N; g.K = f.K; g.A = f.A; g.W = W; g.Bp = f.Bp; g.C = f.C; g.ldc = f.ldc;
+  g.alpha = 1.f;
+  g.A2 = f.A2; g.a_split = f.a_split; g.lda = f.lda;
+  g.relu = f.relu; g.pad = f.pad; g.accumulate = f.accumulate; g.drop = f.drop;
+  g.rec = f.rec; g.A_more = f.A_rec; g.C_more = f.C_rec; g.M2 = f.M2; g.m2_expected = f.m2_expected; g.m2_dev = f.m2_dev;
+  return gemm_rows(g, s);
 }
 
 // ---- transposed products, depth split over the chip ----------------------------------------------

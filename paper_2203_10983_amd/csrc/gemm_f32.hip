@@ -1,9 +1,9 @@
 // The forward product H = [A | A2] W (Eq. 2) on the fp32 matrix instruction, v_mfma_f32_32x32x2_f32.
 //
-// The forward chain decides which hidden units a ReLU switches on, and a unit within rounding of
-// zero is switched by another order of summation.  So every forward product, whatever its kernel, adds
-// the same terms in the same order: a chain over depth pairs (0,1), (2,3), ... from zero.  The backward
-// products have no such decision behind them and run faster on split bf16 operands (gemm.hip).
+// Of layers whose input is up to 128 wide, which other kernels multiply too (one launch for a layer, one kernel for a layer).  The
+// forward chain decides which hidden units a ReLU switches on, and a unit within rounding of zero is switched by another order
+// of summation.  So all of these add the same terms in the same order: a chain over depth pairs (0,1), (2,3), ... from zero.
+// The products of wider layers and the backward ones run faster on split bf16 operands (gemm.hip, fwd_by_splits).
 //
 // A workgroup of 4 wavefronts walks row tiles of 128; a wavefront owns 32 rows and NC column tiles of
 // 32.  Its rows come straight from global memory: a lane reads four consecutive depths of its row, and
@@ -13,8 +13,7 @@
 // product of a single step once, to stay): one 16-byte LDS read feeds four instructions, and the matrix pipe is what is left
 // to wait for.  The weights are the second operand of the instruction: a lane ends up with a column, and a wavefront stores
 // 128 consecutive bytes of a row (with four columns per lane, 32-byte pieces of 32 rows: 32 -> 128 on 578125 rows 94 us, 79).
-// What bounds it: the matrix pipe where the depth is large (89625 x 512 x 512 369 us, 127 of 157 TFLOP/s), the stores where
-// it is a step or two.
+// What bounds it: the matrix pipe where the depth is large, the stores where it is a step or two.
 #include <algorithm>
 #include <type_traits>
 

@@ -25,7 +25,7 @@ struct PackJob {
   const float *W;
   void *out;
   int32_t K, N;
-  bool split;
+  bool split, fwd;
 };
 constexpr int kMaxPackJobs = 16;
 struct PackJobs {
@@ -259,6 +259,13 @@ struct RowsF32 {
   Dropout drop;
 };
 hipError_t gemm_rows_f32(const RowsF32 &g, hipStream_t s);
+// The same from W [K, N] by the split products of gemm.hip where fwd_by_splits(depth of each of A and A2) says so (Bp packed
+// accordingly).  They are faster and closer to the exact sums at every depth (2-norm of the error, normal operands, beside the fp32
+// chain: 130 columns 0.6e-7 and 2.1e-7, 256 0.7 and 2.9,
+// 512 0.9 and 4.1, 602 1.0 and 4.4).
+// The line: layers with an input of up to 128 columns may run as one launch or one kernel instead, with the bits of the fp32 chain.
+inline bool fwd_by_splits(int32_t d_in) { return d_in > 128; }
+hipError_t gemm_fwd(const RowsF32 &g, const float *W, hipStream_t s);
 
 // C[M,N] = alpha * A B with A [M,K], B [K,N] packed and split, from W [N,K].  At most one of: C2 (nullable): columns from c_split (a
 // multiple of 4) on go to C2, both with row stride ldc; mask (nullable, [M, ldc]): C is zeroed where mask <= 0.
@@ -275,6 +282,15 @@ struct RowsGemm {
   float *C_more;
   int32_t M2, m2_expected;
   const int32_t *m2_dev;
+  // rows of A are lda apart (fwd unset: K)
+  int32_t lda;
+  // a forward product, W [K, N]: its arguments as in RowsF32 (A_rec is A_more)
+  bool fwd;
+  const float *A2;
+  int32_t a_split;
+  bool relu, pad, accumulate;
+  const int2 *rec;
+  Dropout drop;
 };
 hipError_t gemm_rows(const RowsGemm &g, hipStream_t s);
 

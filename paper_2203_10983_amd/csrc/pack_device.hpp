@@ -1,5 +1,5 @@
 // Weight matrices as operand fragments, 1 KB each (64 lanes x 16 bytes), zero outside the matrix:
-//   split: of W [N, K] transposed, for gemm_rows.  For depth step s of 32 and column tile t of 16, at
+//   split: of W [N, K] transposed (fwd: of W [K, N] as it is), for gemm_rows.  For depth step s of 32 and column tile t of 16, at
 //     ((s * tiles + t) * 3 + piece) KB, lane l's 8 values are column 16 t + l % 16 at the depths
 //     32 s + 16 (e / 4) + 4 (l / 16) + e % 4, e = 0..7, negated in odd tiles (mfma_split)
 //   fp32: of W [K, N], for gemm_rows_f32.  For depth step s of 32, column tile t of 32 and depth group j of 8, at
@@ -35,7 +35,7 @@ __device__ __forceinline__ void pack_unit(const PackJobs &jobs, int u) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const int k = s * 32 + j * 16 + g * 4 + e;
-        v[j][e] = job.W[(size_t)min(n, job.N - 1) * job.K + min(k, job.K - 1)];
+        v[j][e] = job.W[(size_t)min(n, job.N - 1) * (job.fwd ? 1 : job.K) + (size_t)min(k, job.K - 1) * (job.fwd ? job.N : 1)];
       }
 #pragma unroll
     for (int j = 0; j < 2; ++j)

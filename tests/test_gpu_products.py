@@ -105,6 +105,122 @@ def test_backward_products_round_once_a_step(n, d_in, d_out, half_zero):
     ctx.close()
 
 
+def _layer(n, d_in, d_out, kind, part=None):
+    import torch
+    import paper_2203_10983_amd as pkg
+    i32 = lambda k: torch.zeros(k, dtype=torch.int32, device="cuda:0")  # noqa: E731
+    ctx = pkg.Context(part or _loops(n), [d_in, d_out], 0, device=torch.device("cuda:0"), layer_kind=kind)
+    kept, remap, n_kept, nnz = i32(1), i32(1), i32(1), i32(1)
+    ctx.sample_boundary(1, 0, 0.5, kept, remap, n_kept)
+    csr = i32(n + 1), i32(n), i32(n + 1), i32(n)
+    ctx.build_sampled_csr(remap, kept, n_kept, *csr, nnz)
+    return ctx, (kept, remap, n_kept, nnz, csr)
+
+
+# the split forward products, from 129 input columns on: one product of both halves (144, 160), two added (130, 301), odd depths, every
+# number of column tiles from 1 to 8, few rows and many
+@pytest.mark.parametrize("kind", [0, 1], ids=["gcn", "sage"])
+@pytest.mark.parametrize("n,d_in,d_out", [(1, 129, 1), (65, 130, 17), (200, 144, 33), (517, 301, 50), (1000, 131, 79), (2000, 160, 96), (3000, 602, 112),
+                                          (4099, 512, 128), (70001, 130, 130), (40000, 256, 172)], ids=lambda v: str(v))
+def test_forward_products_of_wide_layers(n, d_in, d_out, kind):
+    """Each element within the allowance, the whole as close as sums that round once a 32-deep step at the size of the running one
+    (2^-24 (1 + 0.5 sqrt(steps)), derived in test_backward_products_round_once_a_step), and once more where two products are added;
+    few rows give the bits that many give."""
+    import torch
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(n + d_out)
+    f32 = lambda *s: torch.randn(*s, device="cuda:0", generator=gen)  # noqa: E731
+    X, W = f32(n, d_in), f32((1 + kind) * d_in, d_out)
+    got = {}
+    for m in (n, (n + 2) // 3):
+        ctx, keep = _layer(m, d_in, d_out, kind)
+        A, H = torch.empty(m, d_in, device="cuda:0"), torch.full((m, d_out), 7.0, device="cuda:0")
+        ctx.gcn_layer_fwd(1, 0.5, X[:m], None, W, A, H, False)
+        R = torch.full_like(H, 7.0)
+        ctx.gcn_layer_fwd(1, 0.5, X[:m], None, W, A, R, True)
+        torch.cuda.synchronize()
+        assert torch.equal(R, H.clamp(min=0))
+        got[m] = H
+        ctx.close()
+    assert torch.equal(got[(n + 2) // 3], got[n][:(n + 2) // 3])
+    Z, Wd = X.double(), W[kind * d_in:].double()
+    ref, size = Z @ Wd, Z.abs() @ Wd.abs()
+    assert ((got[n].double() - ref).abs() <= 4.0 * 2.0 ** -24 * (1 + d_in ** 0.5) * size).all()
+    if n * d_out >= 1000:  # (a handful of elements has no typical error)
+        err = ((got[n].double() - ref).norm() / ref.norm()).item()
+        assert err <= 2.0 ** -24 * (1 + 0.5 * (((1 + kind) * d_in + 31) // 32) ** 0.5), err
+
+
+@pytest.mark.parametrize("relu", [False, True], ids=["last", "relu"])
+@pytest.mark.parametrize("kind", [0, 1], ids=["gcn", "sage"])
+@pytest.mark.parametrize("d_in,d_out", [(144, 20), (130, 49), (301, 172)], ids=lambda v: str(v))
+def test_infinities_and_nan_in_forward_products(d_in, d_out, kind, relu):
+    """As test_infinities_and_nan_in_backward_products; max(NaN, 0) of a hidden unit is 0, as it is for the narrower layers."""
+    import torch
+    n = 300
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(d_in)
+    f32 = lambda *s: torch.rand(*s, device="cuda:0", generator=gen) + 0.5  # noqa: E731  (one sign: no infinities cancel by chance)
+    X, W = f32(n, d_in), f32((1 + kind) * d_in, d_out)
+    inf, half, top = float("inf"), kind * d_in, 3.40e38  # top: rounds to an infinite bf16
+    W[half + 7] *= 0.1
+    X[5, 3], X[n - 1, d_in - 1], X[17, 0], X[33, 7], X[60, 1] = inf, -inf, float("nan"), top, top
+    W[half + 1, 2], W[half + d_in - 1, 7] = inf, -inf
+    X[40, 1] = 0.0                                       # 0 * inf
+    ctx, keep = _layer(n, d_in, d_out, kind)
+    A, H = torch.empty(n, d_in, device="cuda:0"), torch.full((n, d_out), 7.0, device="cuda:0")
+    ctx.gcn_layer_fwd(1, 0.5, X, None, W, A, H, relu)
+    torch.cuda.synchronize()
+    Z = torch.cat([A, X], 1) if kind else X  # (the mean over no neighbours: zero, or NaN where zero times infinity is)
+    ref = torch.stack([(row[:, None] * W.cpu()).double().sum(0) for row in Z.cpu()]).float()  # products that overflow do so in fp32
+    if relu:
+        ref = torch.where(ref.isnan(), 0.0, ref).clamp(min=0)
+    got = H.cpu()
+    assert torch.equal(got.isnan(), ref.isnan())
+    assert torch.equal(got.isinf(), ref.isinf()) and torch.equal(got[got.isinf()], ref[ref.isinf()])
+    ok = ref.isfinite()
+    assert 0 < int(ok.sum()) < ok.numel() and torch.allclose(got[ok], ref[ok], rtol=1e-5, atol=0)
+    ctx.close()
+
+
+def test_infinities_in_a_product_before_the_aggregate():
+    """A layer that multiplies first reads kept boundary rows by record, scaled on their way in, and pads its odd width."""
+    import torch
+    import paper_2203_10983_amd as pkg
+    n, nb, d_in, d_out = 150000, 300, 160, 41
+    P = _loops(n)
+    P.n_halo = P.e_bd = nb  # boundary node u is a neighbour of node u
+    P.nnz0 = n + nb
+    P.row_ptr0 = (np.arange(n + 1) + np.minimum(np.arange(n + 1), nb)).astype(np.int32)
+    P.col0 = np.concatenate([np.stack([np.arange(nb), n + np.arange(nb)], 1).ravel(), np.arange(nb, n)]).astype(np.int32)
+    P.halo_ptr, P.halo_col = np.arange(nb + 1, dtype=np.int32), np.arange(nb, dtype=np.int32)
+    P.halo_gid, P.deg_halo = n + np.arange(nb, dtype=np.int64), np.full(nb, 2, np.int32)
+    P.deg_in = np.diff(P.row_ptr0).astype(np.int32)
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(1)
+    f32 = lambda *s: torch.rand(*s, device="cuda:0", generator=gen) + 0.5  # noqa: E731
+    X, halo, W = f32(n, d_in), f32(nb, d_in), f32(d_in, d_out)
+    inf, top = float("inf"), 3.40e38
+    W[7] *= 0.1
+    X[400, 3], X[n - 1, d_in - 1], X[70001, 5], X[501, 7] = inf, -inf, float("nan"), top
+    halo[3, 4], halo[nb - 1, 0], halo[100, 159], halo[200, 7] = inf, float("nan"), -inf, top
+    ctx = pkg.Context(P, [d_in, d_out], 0, device=torch.device("cuda:0"))
+    assert ctx.layer_plan(1) == pkg.LAYER_UPDATE_FIRST
+    dW, loss = torch.zeros_like(W), torch.zeros(1, device="cuda:0")
+    ctx.train_step(1, 0, 1.0, X, [halo], torch.zeros(n, dtype=torch.int32, device="cuda:0"), [W], [dW], [None], loss, 0.0)
+    torch.cuda.synchronize()
+    got = ctx.ws_tensor(pkg.VIEW_H, 1, torch.float32).view(n, d_out).cpu().double()
+    d = torch.from_numpy(P.deg_in).double()
+    S = X.cpu().double() / d[:, None]
+    S[:nb] += halo.cpu().double() / 2
+    ref = S @ W.cpu().double()
+    assert torch.equal(got.isfinite(), ref.isfinite()) and int((~ref.isfinite()).sum()) == 6 * d_out
+    assert torch.equal(got.isnan(), ref.isnan()) and torch.equal(got[got.isinf()], ref[ref.isinf()])
+    ok = ref.isfinite()
+    assert torch.allclose(got[ok], ref[ok], rtol=1e-5, atol=0)
+    ctx.close()
+
+
 @pytest.mark.parametrize("kind", [0, 1], ids=["gcn", "sage"])
 @pytest.mark.parametrize("n,d_in,d_out", [(70, 16, 16), (300, 50, 20), (300, 20, 52), (4000, 128, 130)], ids=lambda v: str(v))
 def test_infinities_and_nan_in_backward_products(n, d_in, d_out, kind):
