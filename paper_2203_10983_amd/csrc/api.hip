@@ -140,8 +140,6 @@ bool one_kernel_layer(const bns_ctx *ctx, int d_in, int d_out) {
 // The concatenated update [z | h] [W_n ; W_s] of the mean-aggregator layer as one product: the seam must
 // not cut the 16-deep groups that a depth is zero-padded to.
 bool concat_in_one(int d_in) { return d_in % 16 == 0; }
-// Bytes of K rows of a layer's packed forward weights.
-size_t packed_fwd_bytes(int32_t d_in, int32_t K, int32_t N) { return fwd_by_splits(d_in) ? packed_bytes(K, N) : packed_bytes_f32(K, N); }
 
 // Aggregate and update of a layer of a small partition in one launch, a few rows per workgroup?  A launch and a pass over
 // the aggregate less; with more rows than fill the chip the weights, read anew for every tile, cost more than they save, and a row
@@ -166,6 +164,24 @@ bool tile_layer_bwd(const bns_ctx *ctx, int layer, int64_t rows) {
   const SegPlan &plan = ctx->ws.plan_b;
   return rows <= kTileBwdMaxRows && (plan.n_multi == 0 || (plan.max_seg <= kTileBwdMaxSegments && plan.avg_len <= kTileBwdMaxLen)) &&
          tile_layer_bwd_supported(gather_stride(ctx->dims[layer - 1], ctx->dims[layer]), ctx->dims[layer - 1], ctx->layer_kind == 1);
+}
+
+// The forward product of `layer` by splits (gemm.hip) instead of the fp32 chain?  It is faster and closer to the exact sums (2-norm of
+// the error, normal operands, beside the chain: depth 128 0.6e-7 and 2.0e-7, 256 0.7 and 2.9, 512 0.9 and 4.1, 602 1.0 and 4.4).
+// Only the last layer's: sums in another order switch hidden units within rounding of zero, and one such unit of a node
+// with few neighbours is a visible part of the gradient of the boundary nodes next to it.  A layer that may run as one launch has the
+// bits of the chain there.  Up to 64 columns the stores bound either.  Products in a step, chain and splits, us: 578125 rows, 256 -> 172 542 and 338,
+// 89625 rows, 1024 -> 100 218 and 117, 110645 of 512 -> 100 151 and 87, 226887 of 256 -> 41 78 and 62.
+bool fwd_by_splits(const bns_ctx *ctx, int layer) {
+  return layer + 1 == (int)ctx->dims.size() && ctx->dims[layer - 1] > 64 && !tile_layer(ctx, layer);
+}
+hipError_t fwd_product(const bns_ctx *ctx, int layer, const RowsF32 &g, const float *W, hipStream_t s) {
+  return fwd_by_splits(ctx, layer) ? gemm_fwd_split(g, W, s) : gemm_rows_f32(g, s);
+}
+// Bytes of the first of the two matrices of a layer whose halves are packed apart.
+size_t packed_fwd_half(const bns_ctx *ctx, int layer) {
+  const int d_in = ctx->dims[layer - 1], d_out = ctx->dims[layer];
+  return fwd_by_splits(ctx, layer) ? packed_bytes(d_in, d_out) : packed_bytes_f32(d_in, d_out);
 }
 
 bool valid_desc(const bns_partition_desc *p, const bns_model_desc *m) {
@@ -261,6 +277,7 @@ size_t carve(Carver &c, const bns_partition_desc *p, const bns_model_desc *m, La
   bool hu2_taken = false;
   for (size_t l = 1; l <= L; ++l) {
     const int32_t kw = m->layer_kind == 1 ? 2 : 1;
+    size_t wf_bytes = 0;
     const bool first = update_first_shape(m->layer_kind, m->dims[l - 1], m->dims[l]);
     w.tn[l] = c.take<float>(std::max(gemm_tn_partials(kw * m->dims[l - 1], m->dims[l], p->n_in, 0),
                                      first ? gemm_tn_partials(m->dims[l - 1], m->dims[l], p->n_in, p->n_halo) : 0));
@@ -275,7 +292,11 @@ size_t carve(Carver &c, const bns_partition_desc *p, const bns_model_desc *m, La
       else w.G_halo[l] = w.Hu2;
       hu2_taken = true;
     }
-    w.Wf[l] = c.take<char>(std::max(packed_fwd_bytes(m->dims[l - 1], kw * m->dims[l - 1], m->dims[l]), kw * packed_fwd_bytes(m->dims[l - 1], m->dims[l - 1], m->dims[l])));
+    for (const int32_t k : {kw * m->dims[l - 1], m->dims[l - 1]}) {  // one product or two, by either instruction
+      const int32_t n = kw * m->dims[l - 1] / k;
+      wf_bytes = std::max({wf_bytes, n * packed_bytes_f32(k, m->dims[l]), n * packed_bytes(k, m->dims[l])});
+    }
+    w.Wf[l] = c.take<char>(wf_bytes);
     w.Wb[l] = c.take<char>(kw * packed_bytes(m->dims[l], m->dims[l - 1]));
     w.A[l] = c.take<float>(n_in * (size_t)m->dims[l - 1]);
     if (behind[l] && w.A[l]) w.G_in[l] = w.A[l] + behind[l];
@@ -396,7 +417,7 @@ bns_status layer_fwd_impl(bns_ctx *ctx, int layer, double p, const float *H_in, 
         g.m2_expected = expected_kept(ctx, p);
         g.m2_dev = ctx->cur_n_kept;
       }
-      BNS_TRY("gemm_fwd", gemm_fwd(g, W, s));
+      BNS_TRY("fwd_product", fwd_product(ctx, layer, g, W, s));
     }
     PhaseTimer t(ctx, BNS_PHASE_SPMM_FWD, s);
     BNS_TRY("spmm_fwd", spmm_fwd(ctx->ws.plan_f, n_in, ld, ctx->cur_row_ptr, ctx->cur_col_idx, ctx->ws.w_fwd,
@@ -476,15 +497,15 @@ bns_status layer_fwd_impl(bns_ctx *ctx, int layer, double p, const float *H_in, 
       g.a_split = d_in;
       g.K = 2 * d_in;
     } else if (sage) {  // z W_n + h W_s
-      BNS_TRY("gemm_fwd(nbr)", gemm_fwd(g, W, s));
+      BNS_TRY("fwd_product(nbr)", fwd_product(ctx, layer, g, W, s));
       W += (size_t)d_in * d_out;
       g.A = H_in;
-      g.Bp = ctx->ws.Wf[layer] + packed_fwd_bytes(d_in, d_in, d_out);
+      g.Bp = ctx->ws.Wf[layer] + packed_fwd_half(ctx, layer);
       g.accumulate = true;
     }
     g.relu = relu;
     g.drop = dropout_of(ctx, layer, relu);
-    BNS_TRY("gemm_fwd(update)", gemm_fwd(g, W, s));
+    BNS_TRY("fwd_product(update)", fwd_product(ctx, layer, g, W, s));
   }
   return BNS_OK;
 }
@@ -692,10 +713,10 @@ void add_pack_jobs(const bns_ctx *ctx, int l, const float *W, bool fwd, bool bwd
   if (fwd && (!one_kernel_layer(ctx, d_in, d_out) ||
               update_first_shape(ctx->layer_kind, d_in, d_out))) {
     if (kw == 2 && !concat_in_one(d_in)) {  // the two halves apart
-      add(W, ctx->ws.Wf[l], d_in, d_out, fwd_by_splits(d_in), true);
-      add(W + half, ctx->ws.Wf[l] + packed_fwd_bytes(d_in, d_in, d_out), d_in, d_out, fwd_by_splits(d_in), true);
+      add(W, ctx->ws.Wf[l], d_in, d_out, fwd_by_splits(ctx, l), true);
+      add(W + half, ctx->ws.Wf[l] + packed_fwd_half(ctx, l), d_in, d_out, fwd_by_splits(ctx, l), true);
     } else {
-      add(W, ctx->ws.Wf[l], kw * d_in, d_out, fwd_by_splits(d_in), true);
+      add(W, ctx->ws.Wf[l], kw * d_in, d_out, fwd_by_splits(ctx, l), true);
     }
   }
   if (bwd) {

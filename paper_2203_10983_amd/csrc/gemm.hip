@@ -1,4 +1,4 @@
-// The backward products of the update (Eq. 2), and the forward ones of wide layers, on the matrix cores: fp32 operands and
+// The backward products of the update (Eq. 2), and the forward one of the last layer, on the matrix cores: fp32 operands and
 // results, products by three-way bf16 splitting (split_bf16.hpp).
 //
 //   gemm_rows   C = A B   dA = dZ W^T, H = [A | A2] W: a tall A [M, K] times a weight matrix, which
@@ -23,8 +23,7 @@
 // What bounds them: the 128-wide products move 1 KB per row for 32 k flops and are bound by memory (dZ W^T on 578125 rows
 // 117 us, 5.1 TB/s; A^T dZ 128), the 512-wide ones by the matrix cores, six bf16 instructions per fp32 product (at the
 // dense rate 417 TFLOP/s of fp32 products): 89625 x 512 x 512 205 us (229 TFLOP/s) and 236 (199), where the splitting
-// beside the instructions takes the rest.  Forward, against the fp32 matrix instruction, in a step, us: 89625 x 512 x 512 430 -> 258,
-// 89625 x 300 x 512 253 -> 161, 89625 x 1024 x 512 790 -> 490, 226887 rows, most of them by record, x 602 x 256 617 -> 367, 20011 x 602 x 130 55 -> 37.
+// beside the instructions takes the rest.
 //
 // Both ask for a step's rows while the one before is multiplied, and that only holds while no read stands behind a branch of
 // its own: where the last columns and rows, and rows by index, had such branches, the reads were waited for one by one.  Without
@@ -409,8 +408,7 @@ hipError_t gemm_rows(const RowsGemm &g, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t gemm_fwd(const RowsF32 &f, const float *W, hipStream_t s) {
-  if (!fwd_by_splits(f.A2 ? f.a_split : f.K)) return gemm_rows_f32(f, s);
+hipError_t gemm_fwd_split(const RowsF32 &f, const float *W, hipStream_t s) {
   RowsGemm g{};
   g.fwd = true;
   g.M = f.M; g.N = f.N; g.K = f.K; g.A = f.A; g.W = W; g.Bp = f.Bp; g.C = f.C; g.ldc = f.ldc;

@@ -1,9 +1,9 @@
 // The forward product H = [A | A2] W (Eq. 2) on the fp32 matrix instruction, v_mfma_f32_32x32x2_f32.
 //
-// Of layers whose input is up to 128 wide, which other kernels multiply too (one launch for a layer, one kernel for a layer).  The
-// forward chain decides which hidden units a ReLU switches on, and a unit within rounding of zero is switched by another order
-// of summation.  So all of these add the same terms in the same order: a chain over depth pairs (0,1), (2,3), ... from zero.
-// The products of wider layers and the backward ones run faster on split bf16 operands (gemm.hip, fwd_by_splits).
+// The forward chain decides which hidden units a ReLU switches on, and a unit within rounding of
+// zero is switched by another order of summation.  So every forward product of a hidden layer, whatever its kernel, adds
+// the same terms in the same order: a chain over depth pairs (0,1), (2,3), ... from zero.  The last layer's and the backward
+// products have no such decision behind them and run faster on split bf16 operands (gemm.hip).
 //
 // A workgroup of 4 wavefronts walks row tiles of 128; a wavefront owns 32 rows and NC column tiles of
 // 32.  Its rows come straight from global memory: a lane reads four consecutive depths of its row, and

@@ -259,13 +259,8 @@ struct RowsF32 {
   Dropout drop;
 };
 hipError_t gemm_rows_f32(const RowsF32 &g, hipStream_t s);
-// The same from W [K, N] by the split products of gemm.hip where fwd_by_splits(depth of each of A and A2) says so (Bp packed
-// accordingly).  They are faster and closer to the exact sums at every depth (2-norm of the error, normal operands, beside the fp32
-// chain: 130 columns 0.6e-7 and 2.1e-7, 256 0.7 and 2.9,
-// 512 0.9 and 4.1, 602 1.0 and 4.4).
-// The line: layers with an input of up to 128 columns may run as one launch or one kernel instead, with the bits of the fp32 chain.
-inline bool fwd_by_splits(int32_t d_in) { return d_in > 128; }
-hipError_t gemm_fwd(const RowsF32 &g, const float *W, hipStream_t s);
+// The same from W [K, N] by the split products of gemm.hip (Bp packed accordingly).
+hipError_t gemm_fwd_split(const RowsF32 &g, const float *W, hipStream_t s);
 
 // C[M,N] = alpha * A B with A [M,K], B [K,N] packed and split, from W [N,K].  At most one of: C2 (nullable): columns from c_split (a
 // multiple of 4) on go to C2, both with row stride ldc; mask (nullable, [M, ldc]): C is zeroed where mask <= 0.

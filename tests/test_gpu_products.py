@@ -117,12 +117,12 @@ def _layer(n, d_in, d_out, kind, part=None):
     return ctx, (kept, remap, n_kept, nnz, csr)
 
 
-# the split forward products, from 129 input columns on: one product of both halves (144, 160), two added (130, 301), odd depths, every
+# the split forward products of a last layer: one product of both halves (144, 160), two added (130, 301), odd depths, every
 # number of column tiles from 1 to 8, few rows and many
 @pytest.mark.parametrize("kind", [0, 1], ids=["gcn", "sage"])
-@pytest.mark.parametrize("n,d_in,d_out", [(1, 129, 1), (65, 130, 17), (200, 144, 33), (517, 301, 50), (1000, 131, 79), (2000, 160, 96), (3000, 602, 112),
-                                          (4099, 512, 128), (70001, 130, 130), (40000, 256, 172)], ids=lambda v: str(v))
-def test_forward_products_of_wide_layers(n, d_in, d_out, kind):
+@pytest.mark.parametrize("n,d_in,d_out", [(1, 129, 1), (9000, 66, 17), (200, 144, 33), (517, 301, 50), (1000, 131, 79), (2000, 160, 96), (3000, 602, 112),
+                                          (4099, 512, 128), (20001, 65, 130), (40000, 256, 172), (30000, 128, 64)], ids=lambda v: str(v))
+def test_forward_products_of_last_layers(n, d_in, d_out, kind):
     """Each element within the allowance, the whole as close as sums that round once a 32-deep step at the size of the running one
     (2^-24 (1 + 0.5 sqrt(steps)), derived in test_backward_products_round_once_a_step), and once more where two products are added;
     few rows give the bits that many give."""
