@@ -251,6 +251,7 @@ size_t carve(Carver &c, const bns_partition_desc *p, const bns_model_desc *m, La
     pl.part_ptr = c.take<int32_t>(n_in + 1);
     pl.mrow = c.take<int32_t>(seg_max_multi(nnz));
     pl.part_unit = c.take<int2>(seg_max_parts(nnz));
+    pl.order = c.take<int2>(seg_max_segments(n_in, nnz));
     pl.n_seg = pl.n_part = pl.n_multi = 0;
   }
   w.seg_tmp_a = c.take<int32_t>(n_in + 1);
@@ -856,10 +857,11 @@ bns_status bns_create(bns_ctx **out, const bns_partition_desc *part, const bns_m
   if (ctx->ws.w_fwd) BNS_TRY("entry_weights(fwd)", entry_weights(part->e_in, ctx->ws.split.in_col, w_col, ctx->ws.w_fwd, s));
   BNS_TRY("entry_weights(bwd)", entry_weights(part->e_in, part->t_in_col, w_col, ctx->ws.w_bwd, s));
   BNS_TRY("entry_weights(halo)", entry_weights(part->e_bd, part->halo_col, w_col, ctx->ws.w_halo, s));
-  BNS_TRY("build_seg_plan(fwd)", build_seg_plan(part->n_in, part->nnz0, part->row_ptr0, &ctx->ws.plan_f, ctx->ws.seg_tmp_a,
-                                                 ctx->ws.seg_tmp_b, ctx->ws.tile_sums, s));
-  BNS_TRY("build_seg_plan(bwd)", build_seg_plan(part->n_in, part->e_in, part->t_in_ptr, &ctx->ws.plan_b, ctx->ws.seg_tmp_a,
-                                                 ctx->ws.seg_tmp_b, ctx->ws.tile_sums, s));
+  int32_t *const counts = reinterpret_cast<int32_t *>(ctx->ws.spmm_partials);
+  BNS_TRY("build_seg_plan(fwd)", build_seg_plan(part->n_in, part->nnz0, part->row_ptr0, part->col0, (int64_t)part->n_in + part->n_halo,
+                                                 &ctx->ws.plan_f, ctx->ws.seg_tmp_a, ctx->ws.seg_tmp_b, counts, ctx->ws.tile_sums, s));
+  BNS_TRY("build_seg_plan(bwd)", build_seg_plan(part->n_in, part->e_in, part->t_in_ptr, part->t_in_col, part->n_in,
+                                                 &ctx->ws.plan_b, ctx->ws.seg_tmp_a, ctx->ws.seg_tmp_b, counts, ctx->ws.tile_sums, s));
   // the rows of the inner nodes in the workspace's transposed CSR are the same in every epoch
   BNS_TRY("copy_static_rows", copy_static_rows(part->n_in, part->e_in, part->t_in_ptr, part->t_in_col, ctx->ws.t_row_ptr,
                                                ctx->ws.t_col_idx, s));

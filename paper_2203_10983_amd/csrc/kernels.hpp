@@ -131,6 +131,7 @@ struct SegPlan {
   int32_t *part_ptr;  // int32[n_rows+1] first partial-sum slot of each multi-segment row
   int32_t *mrow;      // int32[n_multi]  rows with more than one segment
   int2 *part_unit;    // int2[n_part]    row of each partial-sum slot, slot
+  int2 *order;        // int2[n_seg]     the units as launches take them: the n_part of long rows by column, then the other rows
   int32_t n_seg, n_part, n_multi;  // host copies of the totals
   int32_t max_seg;                 // segments of the longest row
   int32_t avg_len;                 // entries per row of the static pattern (launch heuristics)
@@ -139,9 +140,10 @@ inline int64_t seg_max_segments(int64_t rows, int64_t nnz) { return rows + nnz /
 inline int64_t seg_max_parts(int64_t nnz) { return 2 * (nnz / kSegLen) + 2; }
 inline int64_t seg_max_multi(int64_t nnz) { return nnz / kSegLen + 1; }
 // Fills *plan (its arrays must be allocated to the bounds above) and waits for the stream.
-// tmp_a: scratch int32[n_rows], tmp_b: scratch int32[n_rows+1].  nnz: entries of the pattern.
-hipError_t build_seg_plan(int32_t n_rows, int64_t nnz, const int32_t *row_ptr, SegPlan *plan, int32_t *tmp_a,
-                          int32_t *tmp_b, int32_t *tile_sums, hipStream_t s);
+// tmp_a: scratch int32[n_rows], tmp_b: scratch int32[n_rows+1], counts: scratch int32[seg_max_parts(nnz)].  nnz: entries of the
+// pattern, col: their columns, below n_cols.
+hipError_t build_seg_plan(int32_t n_rows, int64_t nnz, const int32_t *row_ptr, const int32_t *col, int64_t n_cols, SegPlan *plan,
+                          int32_t *tmp_a, int32_t *tmp_b, int32_t *counts, int32_t *tile_sums, hipStream_t s);
 
 // A[v,:] = row_scale[v] * ( init[v,:] + sum_{u<n_in in row v} w_u H_in[u,:] + sum_{kept r in row v} Hu[r,:] )
 // w_in (one weight per entry of the static inner list, which starts at w_ptr[v] for row v) / row_scale nullable (= 1).

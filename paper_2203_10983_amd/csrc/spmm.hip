@@ -111,7 +111,6 @@ __global__ void __launch_bounds__(BLOCK ? kBlockWaves * kWave : 256, MAXCH == 1 
       const int2 u = scalar_load(a.units, unit);
       row = u.x;
       slot = u.y;
-      if (BLOCK && slot >= 0) continue;
     }
     const int2 ee = scalar_load_pair(a.row_ptr, row);
     int e0 = ee.x, e1 = ee.y;
@@ -197,9 +196,9 @@ __global__ void __launch_bounds__(256) spmm_combine_kernel(const SpmmArgs a) {
 template <int VEC, bool RAGGED>
 static hipError_t launch_spmm_vec(const SpmmArgs &a_in, int64_t extra_rows, bool multi_only, float halo_share, int32_t avg_len, bool transposed, hipStream_t s) {
   SpmmArgs a = a_in;
-  // multi_only: the segments of the multi-segment rows, i.e. the partial-sum slots
-  a.head.n_units = multi_only ? a.plan.n_part : a.plan.n_seg;
-  a.units = multi_only ? a.plan.part_unit : a.plan.seg_unit;
+  // multi_only: the segments of the multi-segment rows, which come first
+  const int64_t n_units = a.head.n_units = multi_only ? a.plan.n_part : a.plan.n_seg;
+  a.units = a.plan.order;
   // Wide rows are cut into slices of 128 floats (64 where rows are long enough to keep a
   // wavefront busy with a quarter of its lanes per neighbour): narrower slices lose more to the repeated index walk than
   // the L2 gains.  In the transposed pass that line is counted in entries per row of the whole launch, the short rows of the
@@ -221,7 +220,7 @@ static hipError_t launch_spmm_vec(const SpmmArgs &a_in, int64_t extra_rows, bool
     ls = slices(128);
     int from = 64;
     if (transposed)
-      from = ((int64_t)a.head.n_units << ls) <= 8192 ? 19 : a.head.n_units < 24576 ? 32 : ls == 0 ? 19 : 24;
+      from = (n_units << ls) <= 8192 ? 19 : n_units < 24576 ? 32 : ls == 0 ? 19 : 24;
     if (avg_len >= from) ls = slices(64);
   } else if (VEC == 4 && !RAGGED && multi_only && halo_share <= 0.15f) {
     // Segments of long rows keep a wavefront busy at any width, so that their slices are as narrow as a 128-byte line (whole
@@ -265,12 +264,16 @@ static hipError_t launch_spmm_vec(const SpmmArgs &a_in, int64_t extra_rows, bool
   // the same ones have all of them for hundreds of groups on end (150000 rows beside as many, 64 floats 215 -> 198, 256 floats 625 -> 565).
   const int64_t per = 8 >> ls;
   auto groups = [&](int64_t n) { return (n + per - 1) / per; };
+  if (block_rows) {  // the rows of one segment are left
+    a.units += a.plan.n_part;
+    a.head.n_units -= a.plan.n_part;
+  }
   const int64_t unit_groups = groups((a.head.n_units + waves - 1) / waves);
-  const bool dealt = extra_rows >= 0 && avg_len >= (a.d > 64 ? 13 : 24) && ((int64_t)a.head.n_units << ls) >= (a.d > 32 ? 16384 : 24576) &&
-                     (a.d > 32 || extra_rows <= a.head.n_units);
+  const bool dealt = extra_rows >= 0 && avg_len >= (a.d > 64 ? 13 : 24) && (n_units << ls) >= (a.d > 32 ? 16384 : 24576) &&
+                     (a.d > 32 || extra_rows <= n_units);
   int64_t extra_groups = 0;
   if (dealt) {
-    const int rows = waves * (extra_rows >= 2 * (int64_t)a.head.n_units ? 4 : 2);
+    const int rows = waves * (extra_rows >= 2 * n_units ? 4 : 2);
     extra_groups = groups((extra_rows + rows - 1) / rows);
     extra_groups += extra_groups / 32 + 1;  // (never none: any number is walked)
   } else if (extra_rows >= 0) {
@@ -415,15 +418,63 @@ seg_multi_kernel(int32_t n_rows, const int32_t *__restrict__ seg_ptr, int which,
 __global__ void __launch_bounds__(256)
 seg_fill_kernel(int32_t n_rows, const int32_t *__restrict__ seg_ptr, const int32_t *__restrict__ mpos,
                 const int32_t *__restrict__ part_ptr, int2 *__restrict__ seg_unit,
-                int32_t *__restrict__ mrow, int2 *__restrict__ part_unit) {
+                int32_t *__restrict__ mrow, int2 *__restrict__ part_unit, int2 *__restrict__ order) {
   const int v = blockIdx.x * 256 + threadIdx.x;
   if (v >= n_rows) return;
   const int s0 = seg_ptr[v], s1 = seg_ptr[v + 1];
   for (int s = s0; s < s1; ++s) seg_unit[s] = make_int2(v, s1 - s0 > 1 ? part_ptr[v] + s - s0 : -1);
   if (s1 - s0 > 1) {
     mrow[mpos[v]] = v;
-    for (int s = 0; s < s1 - s0; ++s) part_unit[part_ptr[v] + s] = make_int2(v, part_ptr[v] + s);
+    for (int s = 0; s < s1 - s0; ++s) part_unit[part_ptr[v] + s] = order[part_ptr[v] + s] = make_int2(v, part_ptr[v] + s);
+  } else {
+    order[part_ptr[n_rows] + v - mpos[v]] = make_int2(v, -1);
   }
+}
+
+// The segments of the long rows by the column of their middle entry, in kBuckets steps: a counting sort, stable.  What bounds the
+// gathers is the rate at which the L2s pull missed lines.  A segment of a row of many covers a small part of the columns, so that
+// the segments in flight together share their feature rows while these are in the L2s; in the order of the rows each part of the columns
+// came by again with every row.  The sums and their order are what they are in any order of the units.  Us, by row -> by column:
+// 29125 rows of 340 entries, 256 floats in slices of 64 500 -> 422, beside 197758 boundary nodes all kept 842 -> 650, transposed
+// 500 -> 434 and 677 -> 640; transposed 306250 rows of 45, 128 floats 763 -> 695, 578125 of 21 815 -> 789; the long rows alone, in
+// slices of 32, 251 -> 172 and 252 -> 184.  By the column of the first entry 1 to 12 % slower (204 -> 230 for the long rows of the 306250, 100
+// floats).  With an eighth of the columns to each XCD, so that a line is in one L2 alone, the long rows are no faster (175 and 193) and the
+// XCDs that have the boundary columns end last (650 -> 725).  Shorter segments are narrower, but their partial sums eat that up (transposed,
+// 128 entries 434 + 12 -> 418 + 22 and 789 + 9 -> 762 + 17, 64 entries 460 + 41).
+// A tile is kOrderTile segments; counts[bucket * tiles + tile].
+constexpr int kBuckets = 1024, kOrderTile = 4096, kOrderMin = 4096;
+__device__ __forceinline__ void segment_buckets(uint16_t *keys, int n, const int2 *units, const int32_t *row_ptr, const int32_t *col, int64_t n_cols,
+                                                const int32_t *seg_ptr, const int32_t *part_ptr) {
+  for (int i = threadIdx.x; i < n; i += kBuckets) {
+    const int2 u = units[i];
+    const int r0 = row_ptr[u.x], r1 = row_ptr[u.x + 1], nseg = seg_ptr[u.x + 1] - seg_ptr[u.x];
+    const int chunk = (r1 - r0 + nseg - 1) / nseg;
+    const int e = min(r0 + (u.y - part_ptr[u.x]) * chunk + chunk / 2, r1 - 1);
+    keys[i] = (uint16_t)((int64_t)col[e] * kBuckets / n_cols);
+  }
+  __syncthreads();
+}
+
+__global__ void __launch_bounds__(kBuckets)
+seg_order_count_kernel(int n, const int2 *units, const int32_t *row_ptr, const int32_t *col, int64_t n_cols, const int32_t *seg_ptr,
+                       const int32_t *part_ptr, int32_t *counts) {
+  __shared__ uint16_t keys[kOrderTile];
+  const int i0 = blockIdx.x * kOrderTile, m = min(kOrderTile, n - i0);
+  segment_buckets(keys, m, units + i0, row_ptr, col, n_cols, seg_ptr, part_ptr);
+  int mine = 0;
+  for (int i = 0; i < m; ++i) mine += keys[i] == threadIdx.x;
+  counts[threadIdx.x * gridDim.x + blockIdx.x] = mine;
+}
+
+__global__ void __launch_bounds__(kBuckets)
+seg_order_write_kernel(int n, const int2 *units, const int32_t *row_ptr, const int32_t *col, int64_t n_cols, const int32_t *seg_ptr,
+                       const int32_t *part_ptr, const int32_t *starts, int2 *order) {
+  __shared__ uint16_t keys[kOrderTile];
+  const int i0 = blockIdx.x * kOrderTile, m = min(kOrderTile, n - i0);
+  segment_buckets(keys, m, units + i0, row_ptr, col, n_cols, seg_ptr, part_ptr);
+  int at = starts[threadIdx.x * gridDim.x + blockIdx.x];
+  for (int i = 0; i < m; ++i)
+    if (keys[i] == threadIdx.x) order[at++] = units[i0 + i];
 }
 
 // *out = the most segments of a row, over the *n multi-segment rows (1 if there is none)
@@ -442,8 +493,8 @@ seg_max_kernel(const int32_t *__restrict__ n, const int32_t *__restrict__ mrow, 
   }
 }
 
-hipError_t build_seg_plan(int32_t n_rows, int64_t nnz, const int32_t *row_ptr, SegPlan *plan, int32_t *tmp_a,
-                          int32_t *tmp_b, int32_t *tile_sums, hipStream_t s) {
+hipError_t build_seg_plan(int32_t n_rows, int64_t nnz, const int32_t *row_ptr, const int32_t *col, int64_t n_cols, SegPlan *plan,
+                          int32_t *tmp_a, int32_t *tmp_b, int32_t *counts, int32_t *tile_sums, hipStream_t s) {
   const unsigned blocks = (unsigned)((n_rows + 255) / 256);
   seg_count_kernel<<<blocks, 256, 0, s>>>(n_rows, row_ptr, tmp_a);
   hipError_t e = scan_exclusive_i32(tmp_a, plan->seg_ptr, n_rows, nullptr, tile_sums, nullptr, 0, s);
@@ -455,7 +506,7 @@ hipError_t build_seg_plan(int32_t n_rows, int64_t nnz, const int32_t *row_ptr, S
   e = scan_exclusive_i32(tmp_a, tmp_b, n_rows, nullptr, tile_sums, nullptr, 0, s);
   if (e != hipSuccess) return e;
   seg_fill_kernel<<<blocks, 256, 0, s>>>(n_rows, plan->seg_ptr, tmp_b, plan->part_ptr, plan->seg_unit, plan->mrow,
-                                         plan->part_unit);
+                                         plan->part_unit, plan->order);
   seg_max_kernel<<<1, 1024, 0, s>>>(tmp_b + n_rows, plan->mrow, plan->seg_ptr, tmp_a);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
@@ -476,7 +527,15 @@ hipError_t build_seg_plan(int32_t n_rows, int64_t nnz, const int32_t *row_ptr, S
   plan->n_multi = tot[2];
   plan->max_seg = tot[3];
   plan->avg_len = n_rows > 0 ? (int32_t)(nnz / n_rows) : 0;
-  return hipSuccess;
+  if (plan->n_part < kOrderMin) return hipSuccess;  // (all of them are in flight at once)
+  const int tiles = (plan->n_part + kOrderTile - 1) / kOrderTile, n_counts = tiles * kBuckets;  // 2 n_counts <= n_part
+  int32_t *const starts = counts + n_counts;                                                    // n_counts + 1
+  seg_order_count_kernel<<<tiles, kBuckets, 0, s>>>(plan->n_part, plan->part_unit, row_ptr, col, n_cols, plan->seg_ptr, plan->part_ptr, counts);
+  e = scan_exclusive_i32(counts, starts, n_counts, nullptr, tile_sums, nullptr, 0, s);
+  if (e != hipSuccess) return e;
+  seg_order_write_kernel<<<tiles, kBuckets, 0, s>>>(plan->n_part, plan->part_unit, row_ptr, col, n_cols, plan->seg_ptr, plan->part_ptr, starts,
+                                                    plan->order);
+  return hipGetLastError();
 }
 
 // ------------------------------------------------------------------------------------------

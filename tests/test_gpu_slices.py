@@ -83,10 +83,10 @@ def test_aggregate_in_turns(cliques, size, d, n_halo, p):
 
 
 @pytest.mark.parametrize("d", [2, 3, 5, 6, 7, 18, 33, 65, 66, 129, 130, 258, 263, 510, 602, 770, 1022])
-@pytest.mark.parametrize("cliques,size,n_halo", [(40, 23, 90), (2, 300, 70), (1, 2305, 50)])
+@pytest.mark.parametrize("cliques,size,n_halo", [(40, 23, 90), (2, 300, 70), (1, 2305, 50), (4, 512, 90)])
 def test_rows_of_any_width(d, cliques, size, n_halo):
     """Widths that are no multiple of four: the last four columns of a row overlap those before them.  Rows of one segment, of
-    two (a workgroup each) and of ten (partial sums); nothing is written past the last row."""
+    two (a workgroup each) and of ten (partial sums), and 4096 segments, which are taken by column; nothing is written past the last row."""
     import torch
     import paper_2203_10983_amd as pkg
     dev = torch.device("cuda:0")
