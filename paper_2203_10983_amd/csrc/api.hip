@@ -40,9 +40,8 @@ struct Layout {
   // scratch shared by all calls
   int32_t *tile_sums, *kept_start;
   uint64_t *ballots;
-  int32_t *kpos;
-  uint64_t *bd_mask;   // keep flags of the boundary entries and their number per tile
-  int32_t *bd_sums;
+  uint64_t *bd_mask;   // keep flags of the boundary entries, their number per tile and per tile before each word
+  int32_t *bd_sums, *bd_before;
   // boundary rows at the output width: Hu of GCN layers that shrink (their gradient), Hu2 of update-first layers
   float *Hu, *Hu2, *G0, *G1, *G2, *loss_partials;
   int2 *halo_rec;  // per kept boundary node: (boundary index, weight) for the aggregates that read the rows in place
@@ -231,7 +230,7 @@ size_t carve(Carver &c, const bns_partition_desc *p, const bns_model_desc *m, La
   w.ballots = c.take<uint64_t>((B + 63) / 64 + 1);
   w.bd_mask = c.take<uint64_t>((p->e_bd + 63) / 64);
   w.bd_sums = c.take<int32_t>(scan_tiles(p->e_bd));
-  w.kpos = c.take<int32_t>(p->e_bd + 1);
+  w.bd_before = c.take<int32_t>((p->e_bd + 63) / 64);
   w.Hu = c.take<float>(B * d_out_max);
   w.Hu2 = c.take<float>(B * d_first_max);
   w.halo_rec = c.take<int2>(B + 1);
@@ -329,6 +328,7 @@ bns_status hip_fail(bns_ctx *ctx, const char *what, hipError_t e) {
 // A launch that carries work of two kinds is taken apart while the phase that it would be counted for is timed.
 bool timed(const bns_ctx *ctx, int phase) { return ((ctx->prof.mask >> phase) & 1u) && ctx->prof.used < ctx->prof.start.size(); }
 
+constexpr int kNoPhase = -1;
 // Brackets the kernels enqueued during its lifetime with two events (only if the phase is enabled).
 struct PhaseTimer {
   Profiler *p = nullptr;
@@ -336,7 +336,7 @@ struct PhaseTimer {
   size_t slot = 0;
   PhaseTimer(bns_ctx *ctx, int phase, hipStream_t stream) : s(stream) {
     Profiler &pr = ctx->prof;
-    if (!((pr.mask >> phase) & 1u) || pr.used >= pr.start.size()) return;
+    if (phase == kNoPhase || !((pr.mask >> phase) & 1u) || pr.used >= pr.start.size()) return;
     p = &pr;
     slot = pr.used++;
     pr.phase[slot] = phase;
@@ -734,14 +734,15 @@ constexpr int kPackLayers = kMaxPackJobs / 4;  // layers whose jobs fit one laun
 // Are the arrays of the workspace current and still unwritten, i.e. has a step been captured and none been run?
 bool no_subgraph(const bns_ctx *ctx) { return ctx->cur_row_ptr == ctx->ws.row_ptr && !ctx->ws_built; }
 
-BdCount bd_count(const bns_ctx *ctx) { return BdCount{ctx->part.e_bd, ctx->ws.split.bd_b, ctx->ws.bd_mask, ctx->ws.bd_sums}; }
+BdCount bd_count(const bns_ctx *ctx) { return BdCount{ctx->part.e_bd, ctx->ws.split.bd_b, ctx->ws.bd_mask, ctx->ws.bd_sums, ctx->ws.bd_before}; }
 
 // pack (nullable): a training step's: weights to pack beside the sampling, and the records of the kept nodes too
 bns_status sample_impl(bns_ctx *ctx, uint64_t seed, uint32_t epoch, const uint32_t *epoch_dev, double p,
-                       int32_t *kept_ids, int32_t *remap, int32_t *n_kept, const PackJobs *pack, hipStream_t s) {
+                       int32_t *kept_ids, int32_t *remap, int32_t *n_kept, const PackJobs *pack, hipStream_t s,
+                       int phase = BNS_PHASE_SAMPLE) {
   const uint64_t threshold = (uint64_t)std::floor(p * 4294967296.0);
   const BdCount count = bd_count(ctx);
-  PhaseTimer t(ctx, BNS_PHASE_SAMPLE, s);
+  PhaseTimer t(ctx, phase, s);
   BNS_TRY("sample_boundary",
           sample_boundary(ctx->part.halo_gid, ctx->part.n_halo, seed, epoch, epoch_dev, (uint32_t)ctx->part.part_id,
                           threshold, ctx->ws.ballots, ctx->ws.tile_sums, kept_ids, remap, n_kept, ctx->part.halo_ptr,
@@ -759,9 +760,9 @@ bns_status sample_impl(bns_ctx *ctx, uint64_t seed, uint32_t epoch, const uint32
 }
 
 bns_status build_impl(bns_ctx *ctx, int32_t *row_ptr, int32_t *col_idx, int32_t *t_row_ptr,
-                      int32_t *t_col_idx, int32_t *nnz, hipStream_t s) {
+                      int32_t *t_col_idx, int32_t *nnz, hipStream_t s, int phase = BNS_PHASE_BUILD) {
   const bns_partition_desc &P = ctx->part;
-  PhaseTimer t(ctx, BNS_PHASE_BUILD, s);
+  PhaseTimer t(ctx, phase, s);
   SubgraphBuild g{};
   g.n_in = P.n_in; g.n_halo = P.n_halo; g.e_in = P.e_in;
   g.sp = ctx->ws.split;
@@ -769,7 +770,6 @@ bns_status build_impl(bns_ctx *ctx, int32_t *row_ptr, int32_t *col_idx, int32_t 
   g.ballots = ctx->ws.ballots;
   g.remap = ctx->cur_remap; g.kept_ids = ctx->cur_kept; g.n_kept = ctx->cur_n_kept; g.kept_start = ctx->ws.kept_start;
   g.t_in_ptr = P.t_in_ptr; g.t_in_col = P.t_in_col; g.halo_ptr = P.halo_ptr; g.halo_col = P.halo_col;
-  g.kpos = ctx->ws.kpos;
   g.row_ptr = row_ptr; g.col_idx = col_idx; g.nnz = nnz; g.t_row_ptr = t_row_ptr; g.t_col_idx = t_col_idx;
   // the workspace arrays hold the static rows since bns_create
   g.static_rows = !(t_row_ptr == ctx->ws.t_row_ptr && t_col_idx == ctx->ws.t_col_idx);
@@ -782,19 +782,20 @@ bns_status build_impl(bns_ctx *ctx, int32_t *row_ptr, int32_t *col_idx, int32_t 
   return BNS_OK;
 }
 
-// Selection step + subgraph step of a training step, into the workspace arrays: one launch for a
-// small partition (timed as the sample phase), else the two calls above.
+// Selection step + subgraph step of a training step, into the workspace arrays: timed as the sample phase for a small partition, and up to
+// kOneLaunchMaxWork one launch, else the two calls above.
 bns_status sample_and_build_impl(bns_ctx *ctx, uint64_t seed, uint32_t epoch, const uint32_t *epoch_dev, double p,
                                  const PackJobs &pack, hipStream_t s) {
   Layout &w = ctx->ws;
   const bns_partition_desc &P = ctx->part;
-  if (!sample_build_small_fits(P.n_in, P.n_halo, P.e_in, P.e_bd, expected_kept(ctx, p))) {
-    const bns_status st = sample_impl(ctx, seed, epoch, epoch_dev, p, w.kept_ids, w.remap, w.counters, &pack, s);
+  const bool small = sample_build_small_fits(P.n_in, P.n_halo, P.e_in, P.e_bd, expected_kept(ctx, p));
+  PhaseTimer t(ctx, small ? (int)BNS_PHASE_SAMPLE : kNoPhase, s);
+  if (!small || small_work(P.n_in, P.n_halo, P.e_in, expected_kept(ctx, p)) > kOneLaunchMaxWork) {
+    const bns_status st = sample_impl(ctx, seed, epoch, epoch_dev, p, w.kept_ids, w.remap, w.counters, &pack, s, small ? kNoPhase : (int)BNS_PHASE_SAMPLE);
     if (st != BNS_OK) return st;
-    return build_impl(ctx, w.row_ptr, w.col_idx, w.t_row_ptr, w.t_col_idx, w.counters + 1, s);
+    return build_impl(ctx, w.row_ptr, w.col_idx, w.t_row_ptr, w.t_col_idx, w.counters + 1, s, small ? kNoPhase : (int)BNS_PHASE_BUILD);
   }
   const uint64_t threshold = (uint64_t)std::floor(p * 4294967296.0);
-  PhaseTimer t(ctx, BNS_PHASE_SAMPLE, s);
   BNS_TRY("sample_build_small",
           sample_build_small(P.halo_gid, P.n_halo, seed, epoch, epoch_dev, (uint32_t)P.part_id, threshold, w.ballots,
                              w.kept_ids, w.remap, w.counters, w.kept_start, P.n_in, P.e_in, P.e_bd, w.split,

@@ -8,7 +8,8 @@
 // gives every kept boundary entry, every inner entry and every row start its final position
 // without any per-row loop, so power-law rows cost nothing extra.
 //
-//   kpos[k]     = kept boundary entries before boundary entry k            (prefix sum)
+//   kpos[k]     = kept boundary entries before boundary entry k, from the keep flags, their counts per tile and
+//                 within a tile per word
 //   row_ptr[v]  = inner_ptr[v] + kpos[bd_ptr[v]]
 //   inner entry j of row v      -> col_idx[j + kpos[bd_ptr[v]]]
 //   kept boundary entry k, row v -> col_idx[inner_ptr[v+1] + kpos[k]]
@@ -113,33 +114,54 @@ bd_count_kernel(const BdCount c, const uint64_t *__restrict__ ballots) {
   bd_count_tile(c, ballots, blockIdx.x);
 }
 
-struct FillArgs {
-  // kept boundary entries of the sampled CSR
+struct StaticRows {
+  const int32_t *ptr, *col;
+  int32_t *t_row_ptr, *t_col_idx;
+};
+
+template <int NT>
+__device__ __forceinline__ void copy_static(const StaticRows &st, int32_t n_in, int64_t e_in, int block, int n_blocks) {
+  for (int64_t i = (int64_t)block * NT + threadIdx.x; i < n_in + 1 + e_in; i += (int64_t)n_blocks * NT) {
+    if (i <= n_in) st.t_row_ptr[i] = st.ptr[i];
+    else st.t_col_idx[i - n_in - 1] = st.col[i - n_in - 1];
+  }
+}
+
+struct BuildArgs {
+  // the inner entries and the row starts of the sampled CSR
   int32_t n_in;
+  int64_t e_in;
+  const int32_t *inner_ptr, *bd_ptr, *in_col, *in_bdp;
+  int32_t *row_ptr, *nnz;
+  int entry_blocks, row_blocks;
+  // its kept boundary entries
   BdCount bd;
   int bd_tiles;
-  const int32_t *bd_row, *remap, *inner_ptr;
-  int32_t *kpos, *col_idx;
+  const int32_t *bd_row, *remap;
+  int32_t *col_idx;
   // rows of the kept boundary nodes in the transposed CSR
   const int32_t *n_kept, *kept_ids, *halo_ptr, *halo_col, *kept_start;
   int32_t *t_tail_ptr, *t_col_idx;
+  int list_blocks;
+  // the rows of the inner nodes in the transposed CSR, which never change (the transpose of the inner-inner block), where the
+  // destination does not hold them yet
+  StaticRows st;
+  int copy_blocks;
 };
 
-// Positions of a tile's boundary entries, from the keep flags: those inside a pass come from the population count of
-// the lower lanes' bits.  A kept entry also gets its place in col_idx; the 4-byte rank is only fetched for those.
-__device__ __forceinline__ void bd_fill_tile(const FillArgs &a) {
-  __shared__ int wave_cnt[kBdWaves];
+// Places of a tile's boundary entries, from the keep flags: those inside a pass come from the population count of
+// the lower lanes' bits.  The 4-byte rank is only fetched for the kept ones.
+__device__ __forceinline__ void bd_fill_tile(const BuildArgs &a, int tile) {
   const int lane = lane_id(), wid = threadIdx.x / kWave;
-  const int64_t e_bd = a.bd.e_bd;
-  const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)wid * (kBdPasses * kWave);
+  const int64_t base = (int64_t)tile * kScanTile + (int64_t)wid * (kBdPasses * kWave);
   unsigned long long mask[kBdPasses];
-  int cnt = 0;
+  int word_before[kBdPasses];
 #pragma unroll
   for (int i = 0; i < kBdPasses; ++i) {
-    mask[i] = base + i * kWave < e_bd ? a.bd.mask[(base >> 6) + i] : 0ull;
-    cnt += __popcll(mask[i]);
+    const bool in = base + i * kWave < a.bd.e_bd;
+    mask[i] = in ? a.bd.mask[(base >> 6) + i] : 0ull;
+    word_before[i] = in ? a.bd.before[(base >> 6) + i] : 0;
   }
-  if (lane == 0) wave_cnt[wid] = cnt;
   // the reads of a stage all at once: they hang on each other (node and row, rank and place)
   const unsigned long long lower = (1ull << lane) - 1ull;
   int node[kBdPasses], row[kBdPasses];
@@ -152,26 +174,43 @@ __device__ __forceinline__ void bd_fill_tile(const FillArgs &a) {
   }
   // kept boundary entries in the tiles before this one: summed here from the raw per-tile counts (ends with a barrier)
   int before[1], total[1];
-  tiles_before<kBdThreads, 1>(a.bd.sums, blockIdx.x, a.bd_tiles, false, before, total);
+  tiles_before<kBdThreads, 1>(a.bd.sums, tile, a.bd_tiles, false, before, total);
 #pragma unroll
   for (int i = 0; i < kBdPasses; ++i)
     if ((mask[i] >> lane) & 1ull) {
       node[i] = a.n_in + a.remap[node[i]];
       row[i] = a.inner_ptr[row[i] + 1];
     }
-  int run = before[0];
-  for (int w = 0; w < wid; ++w) run += wave_cnt[w];
 #pragma unroll
-  for (int i = 0; i < kBdPasses; ++i) {
-    const int64_t k = base + i * kWave + lane;
-    const bool kept = (mask[i] >> lane) & 1ull;
-    const int pos = run + __popcll(mask[i] & lower);
-    if (k < e_bd) {
-      a.kpos[k] = pos;
-      if (kept) a.col_idx[row[i] + pos] = node[i];
-      if (k == e_bd - 1) a.kpos[e_bd] = pos + (kept ? 1 : 0);
-    }
-    run += __popcll(mask[i]);
+  for (int i = 0; i < kBdPasses; ++i)
+    if ((mask[i] >> lane) & 1ull) a.col_idx[row[i] + before[0] + word_before[i] + __popcll(mask[i] & lower)] = node[i];
+}
+
+// kpos[k[i]] of a workgroup's boundary entries k[i] <= e_bd, of which k_first is the smallest: the kept entries of the tiles before, of the words
+// before in the tile, of the word's lower bits.
+template <int N>
+__device__ __forceinline__ void kept_before(const BuildArgs &a, int64_t k_first, int (&k)[N]) {
+  const int64_t e_bd = a.bd.e_bd;
+  const int first = (int)min(k_first / kScanTile, (int64_t)a.bd_tiles - 1);
+  unsigned long long mask[N];
+  int word[N];
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const int64_t w = min((int64_t)k[i], e_bd - 1) >> 6;
+    mask[i] = a.bd.mask[w];
+    word[i] = a.bd.before[w];
+  }
+  int before[1], total[1];
+  tiles_before<kBdThreads, 1>(a.bd.sums, first, a.bd_tiles, false, before, total);
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const int64_t at = min((int64_t)k[i], e_bd - 1);
+    int sum = before[0] + word[i];
+#pragma unroll 4
+    for (int t = first; t < (int)(at / kScanTile); ++t) sum += a.bd.sums[t];
+    // (bits past the last entry are clear)
+    const int bit = (int)(at & 63);
+    k[i] = sum + __popcll(mask[i] & ((1ull << bit) - 1ull)) + (k[i] > at ? (int)((mask[i] >> bit) & 1ull) : 0);
   }
 }
 
@@ -182,7 +221,7 @@ __device__ __forceinline__ void bd_fill_tile(const FillArgs &a) {
 // (197 758 boundary nodes with up to 5 800 neighbours: 81 us with eight lanes for each list, now 16).
 constexpr int kLongList = 256;
 constexpr int kListsPerBlock = kBdThreads / 8;
-__device__ __forceinline__ void kept_rows_fill(const FillArgs &a, int block, int n_blocks) {
+__device__ __forceinline__ void kept_rows_fill(const BuildArgs &a, int block, int n_blocks) {
   __shared__ int n_long, long_src[kListsPerBlock], long_len[kListsPerBlock], long_dst[kListsPerBlock];
   const int sub = threadIdx.x & 7;
   const int n = *a.n_kept;
@@ -214,61 +253,58 @@ __device__ __forceinline__ void kept_rows_fill(const FillArgs &a, int block, int
   }
 }
 
-__global__ void __launch_bounds__(kBdThreads) fill_kernel(const FillArgs a) {
-  if ((int)blockIdx.x < a.bd_tiles) bd_fill_tile(a);
-  else kept_rows_fill(a, blockIdx.x - a.bd_tiles, gridDim.x - a.bd_tiles);
+constexpr int kEntryPasses = 4, kEntryTile = kEntryPasses * kBdThreads;
+
+// Row starts and inner entries follow in closed form from the keep flags: row v's entries move down by the kept boundary entries of the
+// rows before it, kpos[bd_ptr[v]], and every inner entry carries its row's bd_ptr.
+__device__ __forceinline__ void inner_entries(const BuildArgs &a, int block) {
+  // the reads of a stage all at once: they hang on each other (in_bdp, flags, place)
+  const int64_t tile0 = (int64_t)block * kEntryTile, j0 = tile0 + threadIdx.x;
+  int c[kEntryPasses], k[kEntryPasses];
+#pragma unroll
+  for (int i = 0; i < kEntryPasses; ++i) {
+    const int64_t j = min(j0 + i * kBdThreads, a.e_in - 1);
+    c[i] = a.in_col[j];
+    k[i] = a.in_bdp[j];
+  }
+  if (a.bd.e_bd > 0) kept_before(a, a.in_bdp[tile0], k);
+#pragma unroll
+  for (int i = 0; i < kEntryPasses; ++i)
+    if (j0 + i * kBdThreads < a.e_in) a.col_idx[j0 + i * kBdThreads + k[i]] = c[i];
 }
 
-// Row starts and the inner entries in one launch: both follow in closed form from kpos (row v's
-// entries move down by the kept boundary entries of the rows before it, kpos[bd_ptr[v]]; every
-// inner entry carries its row's bd_ptr, so it needs one gather).
-// The workgroups from `blocks` on copy the rows of the inner nodes in the transposed CSR, which never change (the
-// transpose of the inner-inner block), where the destination does not hold them yet.
-struct StaticRows {
-  const int32_t *ptr, *col;
-  int32_t *t_row_ptr, *t_col_idx;
-};
-
-__device__ __forceinline__ void copy_static(const StaticRows &st, int32_t n_in, int64_t e_in, int block, int n_blocks) {
-  for (int64_t i = (int64_t)block * kThreads + threadIdx.x; i < n_in + 1 + e_in; i += (int64_t)n_blocks * kThreads) {
-    if (i <= n_in) st.t_row_ptr[i] = st.ptr[i];
-    else st.t_col_idx[i - n_in - 1] = st.col[i - n_in - 1];
+__device__ __forceinline__ void row_starts(const BuildArgs &a, int block) {
+  const int v0 = block * kEntryTile;  // (n_in + kEntryTile fits)
+  int r[kEntryPasses], k[kEntryPasses];
+#pragma unroll
+  for (int i = 0; i < kEntryPasses; ++i) {
+    const int v = min(v0 + i * kBdThreads + (int)threadIdx.x, a.n_in);
+    r[i] = a.inner_ptr[v];
+    k[i] = a.bd_ptr[v];
+  }
+  if (a.bd.e_bd > 0) kept_before(a, a.bd_ptr[v0], k);
+#pragma unroll
+  for (int i = 0; i < kEntryPasses; ++i) {
+    const int v = v0 + i * kBdThreads + (int)threadIdx.x;
+    if (v <= a.n_in) a.row_ptr[v] = r[i] + k[i];
+    if (v == a.n_in) *a.nnz = r[i] + k[i];
   }
 }
 
-constexpr int kFinishPasses = 8, kFinishTile = kFinishPasses * kThreads;
-
-__global__ void __launch_bounds__(kThreads)
-finish_csr_kernel(int32_t n_in, int64_t e_in, int64_t e_bd, const int32_t *__restrict__ inner_ptr,
-                  const int32_t *__restrict__ bd_ptr, const int32_t *__restrict__ kpos,
-                  const int32_t *__restrict__ in_col, const int32_t *__restrict__ in_bdp,
-                  int32_t *__restrict__ row_ptr, int32_t *__restrict__ col_idx, int32_t *__restrict__ nnz, int blocks,
-                  const StaticRows st) {
-  if ((int)blockIdx.x >= blocks) {
-    copy_static(st, n_in, e_in, blockIdx.x - blocks, gridDim.x - blocks);
-    return;
-  }
-  // a tile of kFinishTile entries per workgroup and its reads all at once: they hang on each other (in_bdp, kpos, place)
-  const int64_t j0 = (int64_t)blockIdx.x * kFinishTile + threadIdx.x;
-  int c[kFinishPasses], k[kFinishPasses];
-#pragma unroll
-  for (int i = 0; i < kFinishPasses; ++i) {
-    const int64_t j = j0 + i * kThreads;
-    c[i] = j < e_in ? in_col[j] : 0;
-    k[i] = j < e_in && e_bd > 0 ? in_bdp[j] : -1;
-  }
-  const int64_t stride = (int64_t)blocks * kThreads;
-  const int64_t t0 = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  for (int64_t v = t0; v <= n_in; v += stride) {
-    const int r = inner_ptr[v] + (e_bd > 0 ? kpos[bd_ptr[v]] : 0);
-    row_ptr[v] = r;
-    if (v == n_in) *nnz = r;
-  }
-#pragma unroll
-  for (int i = 0; i < kFinishPasses; ++i) k[i] = k[i] >= 0 ? kpos[k[i]] : 0;
-#pragma unroll
-  for (int i = 0; i < kFinishPasses; ++i)
-    if (j0 + i * kThreads < e_in) col_idx[j0 + i * kThreads + k[i]] = c[i];
+// Everything at once: what one part needs of another, the places of the entries, it counts again from the keep flags.  With the
+// boundary entries and their places (kpos) in a launch before that of the inner entries, the two and this one, us: 9570 rows beside 23300
+// boundary nodes 11.7 -> 6.3, 20011 beside 30011 14.6 -> 9.1, 29125 beside 197758 45.4 -> 37.1, 306250 beside 746157 53.0 -> 46.8, 578125
+// beside 3.1 M 68.0 -> 64.4.
+__global__ void __launch_bounds__(kBdThreads) build_kernel(const BuildArgs a) {
+  int block = blockIdx.x;
+  if (block < a.list_blocks) return kept_rows_fill(a, block, a.list_blocks);
+  block -= a.list_blocks;
+  if (block < a.bd_tiles) return bd_fill_tile(a, block);
+  block -= a.bd_tiles;
+  if (block < a.row_blocks) return row_starts(a, block);
+  block -= a.row_blocks;
+  if (block < a.entry_blocks) return inner_entries(a, block);
+  copy_static<kBdThreads>(a.st, a.n_in, a.e_in, block - a.entry_blocks, a.copy_blocks);
 }
 
 hipError_t build_subgraph(const SubgraphBuild &g, bool counted, hipStream_t s) {
@@ -281,31 +317,29 @@ hipError_t build_subgraph(const SubgraphBuild &g, bool counted, hipStream_t s) {
   // eight lanes per list, for as many lists as there may be: beyond this many workgroups, most of which would find no
   // kept node left, each one takes several
   const int list_blocks = (int)std::min<int64_t>(((int64_t)g.n_halo + kListsPerBlock - 1) / kListsPerBlock, 4096);
-  if (tiles + list_blocks > 0) {
-    FillArgs a{};
-    a.n_in = g.n_in;
-    a.bd = g.bd;
-    a.bd_tiles = tiles;
-    a.bd_row = g.sp.bd_row; a.remap = g.remap; a.inner_ptr = g.sp.inner_ptr;
-    a.kpos = g.kpos; a.col_idx = g.col_idx;
-    a.n_kept = g.n_kept; a.kept_ids = g.kept_ids; a.halo_ptr = g.halo_ptr; a.halo_col = g.halo_col; a.kept_start = g.kept_start;
-    a.t_tail_ptr = g.t_row_ptr + g.n_in; a.t_col_idx = g.t_col_idx;
-    fill_kernel<<<tiles + list_blocks, kBdThreads, 0, s>>>(a);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-  }
-  const int64_t work = std::max<int64_t>(g.e_in, (int64_t)g.n_in + 1);
-  const int blocks = (int)((work + kFinishTile - 1) / kFinishTile);
-  const int copy = g.static_rows ? std::min(blocks, 16384) : 0;
-  finish_csr_kernel<<<blocks + copy, kThreads, 0, s>>>(g.n_in, g.e_in, g.bd.e_bd, g.sp.inner_ptr, g.sp.bd_ptr, g.kpos,
-                                                       g.sp.in_col, g.sp.in_bdp, g.row_ptr, g.col_idx, g.nnz, blocks,
-                                                       StaticRows{g.t_in_ptr, g.t_in_col, g.t_row_ptr, g.t_col_idx});
+  BuildArgs a{};
+  a.n_in = g.n_in;
+  a.e_in = g.e_in;
+  a.inner_ptr = g.sp.inner_ptr; a.bd_ptr = g.sp.bd_ptr; a.in_col = g.sp.in_col; a.in_bdp = g.sp.in_bdp;
+  a.row_ptr = g.row_ptr; a.nnz = g.nnz;
+  a.entry_blocks = (int)((g.e_in + kEntryTile - 1) / kEntryTile);
+  a.row_blocks = g.n_in / kEntryTile + 1;
+  a.bd = g.bd;
+  a.bd_tiles = tiles;
+  a.bd_row = g.sp.bd_row; a.remap = g.remap; a.col_idx = g.col_idx;
+  a.n_kept = g.n_kept; a.kept_ids = g.kept_ids; a.halo_ptr = g.halo_ptr; a.halo_col = g.halo_col; a.kept_start = g.kept_start;
+  a.t_tail_ptr = g.t_row_ptr + g.n_in; a.t_col_idx = g.t_col_idx;
+  a.list_blocks = list_blocks;
+  a.st = StaticRows{g.t_in_ptr, g.t_in_col, g.t_row_ptr, g.t_col_idx};
+  a.copy_blocks = g.static_rows ? std::min(a.entry_blocks, 16384) : 0;
+  build_kernel<<<list_blocks + tiles + a.row_blocks + a.entry_blocks + a.copy_blocks, kBdThreads, 0, s>>>(a);
   return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------------- set-up
 __global__ void __launch_bounds__(kThreads)
 copy_static_kernel(const StaticRows st, int32_t n_in, int64_t e_in) {
-  copy_static(st, n_in, e_in, blockIdx.x, gridDim.x);
+  copy_static<kThreads>(st, n_in, e_in, blockIdx.x, gridDim.x);
 }
 
 hipError_t copy_static_rows(int32_t n_in, int64_t e_in, const int32_t *t_in_ptr, const int32_t *t_in_col,

@@ -54,6 +54,7 @@ struct BdCount {
   const int32_t *bd_b = nullptr;  // boundary node of every boundary entry
   uint64_t *mask = nullptr;       // uint64[ceil(e_bd/64)]: keep flags
   int32_t *sums = nullptr;        // int32[scan_tiles(e_bd)]: kept entries per tile
+  int32_t *before = nullptr;      // int32[ceil(e_bd/64)]: kept entries of the tile before the flags of a word
 };
 hipError_t sample_boundary(const int64_t *halo_gid, int32_t n_halo, uint64_t seed, uint32_t epoch,
                            const uint32_t *epoch_dev, uint32_t part_id, uint64_t threshold, uint64_t *ballots,
@@ -87,7 +88,6 @@ struct SubgraphBuild {
   const int32_t *remap, *kept_ids, *n_kept;
   const int32_t *kept_start;   // row starts of the kept nodes as sample_boundary left them, int32[n_kept+1]
   const int32_t *t_in_ptr, *t_in_col, *halo_ptr, *halo_col;
-  int32_t *kpos;               // scratch int32[e_bd+1]
   int32_t *row_ptr, *col_idx, *nnz, *t_row_ptr, *t_col_idx;
   bool static_rows;            // also write the rows of the inner nodes (the transposed inner-inner block, the same every
                                // epoch: a destination that already holds them can skip it)
@@ -102,14 +102,16 @@ hipError_t copy_static_rows(int32_t n_in, int64_t e_in, const int32_t *t_in_ptr,
 // hold the static rows of the inner nodes).  Its LDS holds so many boundary nodes and entries:
 constexpr int kSmallMaxHalo = 8192;             // boundary nodes
 constexpr int kSmallMaxBoundaryEntries = 8192;  // entries with a boundary column
-// and it pays where one workgroup takes less time than the four launches of the general path.  Per thousand it takes about 0.15 us
-// for inner entries, 0.4 for inner nodes, 0.5 for boundary nodes and 2.3 for kept ones more than they do, and 0.4 for boundary entries, of
-// which there are few enough to leave them out (steps of 64-16-8, general and one launch, us: 600 rows with 2990 inner entries beside
-// 300 boundary nodes and 7979 entries at p = 0.1 46.4 / 34.3, 1500 with 31308 beside 3500 and 8142 at p = 1 60.5 / 56.6, 8000 with 23996
-// beside 5000 and 8099 at p = 0.1 61.1 / 54.7, 2000 with 61540 beside 300 and 1497 45.9 / 40.5; beyond the line 500 with 28732
-// beside 5000 and 8088 at p = 1 59.4 / 61.6, 2000 with 61540 beside the same 58.4 / 65.9, 8000 with 63974 beside 300 and 8095
-// at p = 0.1 57.8 / 60.3).  Of 175 partitions below the line none was slower in one launch; of 153 beyond it 51 would be faster, by 3 us.
-constexpr int kSmallMaxWork = 81920;  // inner entries + 3 per inner node + 1 per boundary node + 12 per boundary node to be expected
+// and a partition that fits it is timed as one phase up to kSmallMaxWork.  One launch pays where one workgroup takes less time than the three
+// launches of the general path, up to kOneLaunchMaxWork (steps of 64-16-8, general and one launch, us: 600 rows with 2992 inner entries
+// beside 300 boundary nodes and 7637 entries at p = 0.1, work 5452, 32.7 / 28.8; 2535 with 22045 beside 604 and 1445, 30986, 38.5 / 35.3; 1622 with
+// 33052 beside 315 and 402 at p = 1, 42013, 36.5 / 34.3; 2781 with 26611 beside 1421 and 3336 at p = 0.5, 44907, 42.9 / 42.4; beyond it 8000 with 23998 beside
+// 5000 and 7999 at p = 0.1, 58998, 48.7 / 53.0; 2434 with 26870 beside 2475 and 2771 at p = 1, 66347, 45.0 / 49.1; 2000 with 61556 beside
+// 300 and 1397, 68216, 38.0 / 39.0; 1500 with 31262 beside 3500 and 8095 at p = 1, 81262, 42.8 / 52.3).
+constexpr int kSmallMaxWork = 81920, kOneLaunchMaxWork = 51200;
+inline int64_t small_work(int32_t n_in, int32_t n_halo, int64_t e_in, int32_t expected_kept) {
+  return e_in + 3 * (int64_t)n_in + n_halo + 12 * (int64_t)expected_kept;
+}
 bool sample_build_small_fits(int32_t n_in, int32_t n_halo, int64_t e_in, int64_t e_bd, int32_t expected_kept);
 hipError_t sample_build_small(const int64_t *halo_gid, int32_t n_halo, uint64_t seed, uint32_t epoch,
                               const uint32_t *epoch_dev, uint32_t part_id, uint64_t threshold, uint64_t *ballots,

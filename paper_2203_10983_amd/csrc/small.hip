@@ -1,6 +1,6 @@
 // Selection step and subgraph step of Algorithm 1 for a small partition, in one launch.
 //
-// The general path spends four launches per epoch on these two steps, each a few microseconds long
+// The general path spends three launches per epoch on these two steps, each a few microseconds long
 // whatever the size; for a partition of some ten thousand entries that is a fifth to a third of the whole
 // training step.  Here one workgroup of 1024 threads runs the same stages back to back, with a
 // barrier where the general path has a kernel boundary.  What bounds it is the chain of dependent reads, so the static
@@ -243,7 +243,7 @@ __global__ void __launch_bounds__(kSmallThreads) sample_build_small_kernel(const
 
 bool sample_build_small_fits(int32_t n_in, int32_t n_halo, int64_t e_in, int64_t e_bd, int32_t expected_kept) {
   return n_halo <= kSmallMaxHalo && e_bd <= kSmallMaxBoundaryEntries &&
-         e_in + 3 * (int64_t)n_in + n_halo + 12 * (int64_t)expected_kept <= kSmallMaxWork;
+         small_work(n_in, n_halo, e_in, expected_kept) <= kSmallMaxWork;
 }
 
 hipError_t sample_build_small(const int64_t *halo_gid, int32_t n_halo, uint64_t seed, uint32_t epoch,
