@@ -23,7 +23,7 @@ namespace bns {
 // wavefront per segment, and add the partial sums in LDS (same order as spmm_combine_kernel, same bits).  In front of the
 // others are head.n_block_rows workgroups, n_multi rounded up to whole groups; those past n_multi have nothing to do.
 constexpr int kBlockWaves = 8;
-template <int VEC, int MAXCH, int LPR, bool NARROW = false, bool BLOCK = false, bool RAGGED = false>
+template <int VEC, int MAXCH, int LPR, bool NARROW = false, bool BLOCK = false, bool RAGGED = false, bool SHORT = false>
 __global__ void __launch_bounds__(BLOCK ? kBlockWaves * kWave : 256, MAXCH == 1 ? 8 : 1) spmm_kernel(const SpmmArgs) {
   using V = typename Vec<VEC, RAGGED>::T;
   constexpr int kCut = RAGGED ? VEC - 1 : 0;  // (a last piece that is not whole)
@@ -101,9 +101,10 @@ __global__ void __launch_bounds__(BLOCK ? kBlockWaves * kWave : 256, MAXCH == 1 
       step = end;
     }
   } else if (const int32_t *n = unit_args().n_extra_dev) {
-    end += scalar_load(n, 0);
+    const int extra = scalar_load(n, 0);
+    end += SHORT ? (extra + kShortRows - 1) / kShortRows : extra;
   }
-  for (; unit < end; unit += step) {
+  for (int next = 0; unit < end; unit += SHORT ? 0 : step) {  // SHORT: the kept boundary rows are units of kShortRows, `next` the one to go on with
     ArgBlock &a = unit_args();
     const int width = RAGGED ? min(a.head.d_slice, a.d - d_off) : a.head.d_slice, nvec = (width + kCut) / VEC;
     int row = a.n_split + (unit - a.head.n_units), slot = -1;
@@ -111,6 +112,20 @@ __global__ void __launch_bounds__(BLOCK ? kBlockWaves * kWave : 256, MAXCH == 1 
       const int2 u = scalar_load(a.units, unit);
       row = u.x;
       slot = u.y;
+      if (SHORT) unit += step;
+    } else if constexpr (SHORT) {
+      const int r0 = (unit - a.head.n_units) * kShortRows, n = min(kShortRows, scalar_load(a.n_extra_dev, 0) - r0);
+      row = a.n_split + r0;
+      if (next == 0 && scalar_load(a.row_ptr, row + n) - scalar_load(a.row_ptr, row) <= kWave) {
+        short_rows<VEC, LPR, NARROW, RAGGED>(a, r0, n, d_off, nvec, width);
+        unit += step;
+        continue;
+      }
+      row += next;  // one after another
+      if (++next == n) {
+        next = 0;
+        unit += step;
+      }
     }
     const int2 ee = scalar_load_pair(a.row_ptr, row);
     int e0 = ee.x, e1 = ee.y;
@@ -225,10 +240,10 @@ static hipError_t launch_spmm_vec(const SpmmArgs &a_in, int64_t extra_rows, bool
   } else if (VEC == 4 && !RAGGED && multi_only && halo_share <= 0.15f) {
     // Segments of long rows keep a wavefront busy at any width, so that their slices are as narrow as a 128-byte line (whole
     // lines: any other cut would fetch some twice).  128 floats, whole / slices of 64 / of 32, us: 306250 rows of 45 entries
-    // 313 / 281 / 261, 100000 of 92 245 / 207 / 182, of 196 547 / 481 / 414, 250 in every row 796 / 760 / 684; 578125 of 21
-    // 274 / 264 / 266; 250000 of 20 73 / 71 / 73.  An entry of a boundary row is looked up in the kept nodes' records
-    // in every slice, a line each beside the four of its features: with 9 % of them 400000 rows of 20 216 / 191 / 180,
-    // with 24 % 306250 rows of 59 456 / 462 / 505, with 23 % 578125 of 29 410 / 430 / 482.
+    // 216 / 180 / 172, 100000 of 92 131 / 107 / 113, of 196 306 / 264 / 270; 578125 of 21 216 / 189 / 185; 250000 of 20
+    // 74 / 61 / 58.  An entry of a boundary row is looked up in the kept nodes' records in every slice, a line each beside the
+    // four of its features: with 9 % of them 306250 rows of 50 266 / 233 / 229, with 26 % 578125 of 28 346 / 354 / 370 (with 24 % 306250 of 59
+    // 349 / 353 / 326).
     while (ls < 3 && (a.d >> (ls + 1)) >= 32 && a.d % (32 << (ls + 1)) == 0) ++ls;
   }
   a.head.log2_slices = ls;
@@ -271,12 +286,18 @@ static hipError_t launch_spmm_vec(const SpmmArgs &a_in, int64_t extra_rows, bool
   const int64_t unit_groups = groups((a.head.n_units + waves - 1) / waves);
   const bool dealt = extra_rows >= 0 && avg_len >= (a.d > 64 ? 13 : 24) && (n_units << ls) >= (a.d > 32 ? 16384 : 24576) &&
                      (a.d > 32 || extra_rows <= n_units);
+  // Eight at a time (short_rows) where they are not dealt, every wavefront has so many to go on to, and they are no fewer than the
+  // segments, whose gather has a register or two less then with 16 lanes to a row.  Us, one at a time -> eight: 578125 rows beside 3.1 M boundary
+  // rows of 1.4 entries, 128 floats 1758 -> 1287, 66 floats 1496 -> 962, 16 floats 1392 -> 643, beside 1.54 M 1169 -> 1045, beside 308000 787 -> 787;
+  // 89625 beside 211000, 512 floats 610 -> 517, 130 floats 198 -> 180; 306250 beside 746000, 48 floats 546 -> 499; beside fewer than segments 578125 beside
+  // 154000, 64 floats 466 -> 503.  Dealt and by eight, 306250 beside 746000, 128 floats 964 -> 984, 29125 beside 197758, 256 floats 690 -> 667: left.
+  const bool by_eight = VEC == 4 && !dealt && !block_rows && nvec <= kWave && extra_rows >= std::max<int64_t>(65536, n_units);
   int64_t extra_groups = 0;
   if (dealt) {
     const int rows = waves * (extra_rows >= 2 * n_units ? 4 : 2);
     extra_groups = groups((extra_rows + rows - 1) / rows);
     extra_groups += extra_groups / 32 + 1;  // (never none: any number is walked)
-  } else if (extra_rows >= 0) {
+  } else if (extra_rows >= 0) {  // (as many wavefronts by eight: there are more such units than are in flight)
     extra_groups = groups(std::min<int64_t>((extra_rows + waves - 1) / waves, 8192));
   }
   const int64_t all_groups = unit_groups + extra_groups;
@@ -302,6 +323,7 @@ static hipError_t launch_spmm_vec(const SpmmArgs &a_in, int64_t extra_rows, bool
 #define BNS_SPMM_NARROW(LPR)                                                                                \
   do {                                                                                                      \
     if (block_rows) spmm_kernel<4, 1, LPR, true, true><<<blocks, kBlockWaves * kWave, block_lds, s>>>(a); \
+    else if (by_eight) spmm_kernel<4, 1, LPR, true, false, false, true><<<blocks, 256, 0, s>>>(a);        \
     else spmm_kernel<4, 1, LPR, true><<<blocks, 256, 0, s>>>(a);                                          \
   } while (0)
       if (nvec <= 4) BNS_SPMM_NARROW(4);
@@ -317,6 +339,7 @@ static hipError_t launch_spmm_vec(const SpmmArgs &a_in, int64_t extra_rows, bool
 #define BNS_SPMM(MAXCH, LPR)                                                                                              \
   do {                                                                                                                    \
     if (block_rows) spmm_kernel<VEC, MAXCH, LPR, false, true, RAGGED><<<blocks, kBlockWaves * kWave, block_lds, s>>>(a); \
+    else if (VEC == 4 && MAXCH == 1 && by_eight) spmm_kernel<VEC, MAXCH, LPR, false, false, RAGGED, VEC == 4 && MAXCH == 1><<<blocks, 256, 0, s>>>(a); \
     else spmm_kernel<VEC, MAXCH, LPR, false, false, RAGGED><<<blocks, 256, 0, s>>>(a);                                  \
   } while (0)
 #define BNS_COMBINE(MAXCH) spmm_combine_kernel<VEC, MAXCH, false, RAGGED><<<cblocks, 256, 0, s>>>(a)

@@ -427,4 +427,102 @@ __device__ __forceinline__ void gather_segment(Args &a, int row, const InnerWeig
   fold_groups<VEC, MAXCH, LPR>(acc);
 }
 
+// The kept boundary rows r0 .. r0 + n - 1, n <= kShortRows, of a transposed aggregate: a few entries each, one after another in the CSR.
+// A row at a time is a chain of four reads that hang on each other (row start, node and its list, column, features) beside a few
+// hundred bytes of data.  Here the lanes fetch what the rows and all their entries need at once, and the first two steps of four
+// rows are in flight together.  The order of every sum is that of gather_segment.
+// For rows of at most 64 entries together.
+constexpr int kShortRows = 8;
+template <int VEC, int LPR, bool NARROW, bool RAGGED, typename Args>
+__device__ __forceinline__ void short_rows(Args &a, int r0, int n, int d_off, int nvec, int width) {
+  using V = typename Vec<VEC, RAGGED>::T;
+  constexpr int EP = kWave / LPR;
+  int lane = lane_id();
+  asm volatile("" : "+v"(lane));  // (nothing that follows from it is kept in registers beside the segments' gather)
+  const int g = lane / LPR, sl = lane % LPR;
+  const int d = a.d, ds = NARROW ? (int)a.d_store : d;
+  const int start = a.row_ptr[a.n_split + r0 + min(lane, n)];
+  const int node = a.kept_ids[r0 + min(lane, n - 1)];
+  const int list = a.w_in ? a.halo_ptr[node] : 0;
+  const float scale_l = a.dis_halo ? a.s_halo * a.dis_halo[node] : a.s_halo;
+  auto store = [&](int i, float (&acc)[1][VEC]) {
+    const float scale = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(scale_l), i));
+    if (g != 0 || sl >= nvec) return;
+    float *const out = a.out1 + (size_t)(r0 + i) * ds + d_off;
+    V o;
+    float *po = reinterpret_cast<float *>(&o);
+#pragma unroll
+    for (int k = 0; k < VEC; ++k) po[k] = acc[0][k] * scale;
+    if constexpr (!NARROW) {
+      __builtin_nontemporal_store(o, piece_of<VEC, RAGGED>(out, sl, width));
+    } else {
+#pragma unroll
+      for (int k = 0; k < VEC; ++k)
+        if (sl * VEC + k < ds) out[sl * VEC + k] = po[k];
+    }
+  };
+  const int first = __builtin_amdgcn_readlane(start, 0), total = __builtin_amdgcn_readlane(start, n) - first;  // <= 64
+  // an entry per lane
+  unsigned lo_l = 0, hi_l = 0, w_l = 0;
+  int place = 0;  // of its weight
+  for (int i = 0; i < n; ++i) {
+    const int e0 = __builtin_amdgcn_readlane(start, i), l0 = __builtin_amdgcn_readlane(list, i);
+    place = first + lane >= e0 ? l0 + (first + lane - e0) : place;
+  }
+  if (lane < total) {
+    const int c = a.col_idx[first + lane];
+    const float w = a.w_in ? a.w_halo[place] : 1.f;
+    const unsigned long long p = (unsigned long long)(a.src0 + (size_t)c * d + d_off);
+    lo_l = (unsigned)p;
+    hi_l = (unsigned)(p >> 32);
+    w_l = __float_as_uint(w);
+  }
+  auto piece = [&](int e, bool in, float &w) {  // of entry e of the batch
+    const unsigned lo = __shfl(lo_l, e, kWave), hi = __shfl(hi_l, e, kWave), wu = __shfl(w_l, e, kWave);
+    V v{};
+    w = 0.f;
+    if (in && sl < nvec) {
+      v = load_row_piece<VEC, RAGGED>(hi, lo, piece_at<VEC, RAGGED>(sl, width));
+      w = __uint_as_float(wu);
+    }
+    return v;
+  };
+  for (int i0 = 0; i0 < n; i0 += 4) {
+    V v[4];
+    float w[4];
+    auto row = [&](int k, int &at, int &cnt) {
+      const int i = min(i0 + k, n - 1);
+      at = __builtin_amdgcn_readlane(start, i) - first;
+      cnt = __builtin_amdgcn_readlane(start, i + 1) - first - at;
+    };
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      int at, cnt;
+      row(k, at, cnt);
+      v[k] = piece(at + g, g < cnt, w[k]);
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      if (i0 + k < n) {
+        int at, cnt;
+        row(k, at, cnt);
+        float acc[1][VEC];
+#pragma unroll
+        for (int j = 0; j < VEC; ++j) acc[0][j] = 0.f;
+        vec_fma<VEC>(acc[0], w[k], reinterpret_cast<const float *>(&v[k]));
+        for (int t = 1; t * EP < cnt; t += 3) {
+          V x[3];
+          float y[3];
+#pragma unroll
+          for (int j = 0; j < 3; ++j) x[j] = piece(at + (t + j) * EP + g, (t + j) * EP + g < cnt, y[j]);
+#pragma unroll
+          for (int j = 0; j < 3; ++j) vec_fma<VEC>(acc[0], y[j], reinterpret_cast<const float *>(&x[j]));
+        }
+        fold_groups<VEC, 1, LPR>(acc);
+        store(i0 + k, acc);
+      }
+    }
+  }
+}
+
 }  // namespace bns

@@ -123,3 +123,54 @@ def test_rows_of_any_width(d, cliques, size, n_halo):
         torch.testing.assert_close(x[:-1].double(), ref, rtol=1e-5, atol=3e-5)
         assert bool((x[-1] == 7.0).all())
     ctx.close()
+
+
+@pytest.mark.parametrize("d,e,p", [(12, 12, 1.0), (33, 33, 0.97), (64, 47, 0.97), (64, 64, 1.0), (66, 66, 1.0), (128, 128, 0.97), (130, 130, 1.0), (200, 256, 1.0), (256, 256, 0.97),
+                                   (512, 512, 1.0)])
+def test_many_short_rows(d, e, p):
+    """Kept boundary rows that a wavefront takes eight at a time: rows of one to three entries, groups of more than
+    64 entries, a last group that is not whole."""
+    import torch
+    import paper_2203_10983_amd as pkg
+    dev = torch.device("cuda:0")
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(d)
+    n, nb = 3000, 70003
+    rng = np.random.default_rng(d)
+    count = 1 + np.arange(nb) % 3
+    count[3::500] = 80
+    node = np.repeat(np.arange(nb), count)
+    k = np.arange(len(node)) - np.repeat(np.cumsum(count) - count, count)
+    of = (rng.integers(0, n, nb)[node] + 31 * k) % n
+    by_node = np.lexsort((of, node))
+    node, of = node[by_node], of[by_node]
+    row, col = np.concatenate([np.arange(n), of]), np.concatenate([np.arange(n), n + node])
+    order = np.lexsort((col, row))
+    ptr = lambda x, m: np.concatenate([[0], np.cumsum(np.bincount(x, minlength=m))])  # noqa: E731
+    i32 = lambda x: np.ascontiguousarray(x, dtype=np.int32)  # noqa: E731
+    P = types.SimpleNamespace(
+        part_id=0, n_in=n, n_halo=nb, nnz0=len(col), e_in=n, e_bd=len(node), row_ptr0=i32(ptr(row, n)), col0=i32(col[order]), t_in_ptr=i32(np.arange(n + 1)),
+        t_in_col=i32(np.arange(n)), halo_ptr=i32(ptr(node, nb)), halo_col=i32(of), halo_gid=np.arange(n, n + nb, dtype=np.int64),
+        deg_in=i32(np.bincount(row, minlength=n)), deg_halo=i32(count + 1))
+    z32 = lambda m: torch.zeros(m, dtype=torch.int32, device=dev)  # noqa: E731
+    ctx = pkg.Context(P, [d, e], 1, device=dev)
+    kept, remap, n_kept, nnz = z32(nb), z32(nb), z32(1), z32(1)
+    ctx.sample_boundary(1, 0, p, kept, remap, n_kept)
+    csr = z32(n + 1), z32(P.nnz0), z32(n + nb + 1), z32(P.nnz0)  # must outlive the layer calls
+    ctx.build_sampled_csr(remap, kept, n_kept, *csr, nnz)
+    X, Xb, W, dZ = (torch.randn(*s, device=dev, generator=gen) for s in ((n, d), (nb, d), (d, e), (n, e)))
+    W /= d ** 0.5
+    A, dX, dhalo, dW = torch.zeros(n, d, device=dev), torch.zeros(n, d, device=dev), torch.full((nb + 1, d), 7.0, device=dev), torch.zeros(d, e, device=dev)
+    ctx.gcn_layer_bwd(1, p, dZ, None, A, X, W, dW, dX, dhalo[:nb])
+    torch.cuda.synchronize()
+    K = int(n_kept)
+    assert K >= 65536 and (p == 1.0 or K % 8)
+    s_in, s_bd = (torch.from_numpy(x).to(dev).double().rsqrt()[:, None] for x in (P.deg_in, P.deg_halo))
+    G = s_in * (dZ.double() @ W.double().T)
+    node, of = torch.from_numpy(node).to(dev), torch.from_numpy(of).to(dev)
+    ref = torch.zeros(nb, d, device=dev, dtype=torch.float64).index_add_(0, node, G[of]) * s_bd / p
+    # sums of at most 80 elements, each a sum of e products that is of size 1
+    torch.testing.assert_close(dhalo[:K].double(), ref[kept[:K].long()], rtol=1e-5, atol=3e-5)
+    torch.testing.assert_close(dX.double(), s_in * G, rtol=1e-5, atol=3e-5)
+    assert bool((dhalo[K:] == 7.0).all())
+    ctx.close()
