@@ -234,7 +234,17 @@ hipError_t gemm_rows_f32(const RowsF32 &g, hipStream_t s) {
   const int64_t row_tiles = (g.M + 127) / 128 + (g.rec ? (g.m2_expected + 127) / 128 : 0);
   a.nblk = a.S == 1 ? (a.T + 1) / 2 : (a.T + 3) / 4;
   while (row_tiles * a.nblk < 512 && a.nblk < a.T) a.nblk = std::min(a.nblk * 2, a.T);
-  const int nc = (a.T + a.nblk - 1) / a.nblk;
+  int nc = (a.T + a.nblk - 1) / a.nblk;
+  a.nblk = (a.T + nc - 1) / nc;
+  // Or fewer yet, where all workgroups are still resident and the compute unit with the most tiles has a tenth less of them (us, by the rules
+  // above / so: 10000 rows and 7500 by record, 602 -> 130, 411 workgroups of two tiles 52.0 / 685 of one 45.7; 15000 and 2000, 300 -> 130, 402 of two
+  // 30.0 / 670 of one 25.9; 40000, 130 -> 130, 626 of three 34.2 / 939 of two 31.7).  With as many on the fullest unit the wider ones
+  // read their rows less often: 20011, 602 -> 130, 471 of two 50.4 / 785 of one 55.1; 29125 and 19800, 602 -> 256, 766 of four 131 / 1532 of two 141.
+  auto most = [&](int nblk) { return (row_tiles * nblk + 255) / 256 * ((a.T + nblk - 1) / nblk); };  // on one of 256 units
+  if (a.S > 1)
+    for (int n = a.nblk + 1; n <= a.T; ++n)
+      if (row_tiles * n <= ((a.T + n - 1) / n > 2 ? 768 : 1024) && 10 * most(n) <= 9 * most(a.nblk)) a.nblk = n;
+  nc = (a.T + a.nblk - 1) / a.nblk;
   a.nblk = (a.T + nc - 1) / nc;
   int64_t octets = (row_tiles + 7) / 8;
   if (a.S > 1) octets = std::min<int64_t>(octets, std::max<int64_t>(1, (nc > 2 ? 768 : 1024) / (8 * a.nblk)));

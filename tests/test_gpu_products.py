@@ -326,3 +326,32 @@ def test_dropout_of_few_rows_is_that_of_many(d_in, d_out, kind):
     on = got[70001, 0.0] > 0
     k, m = int((on & dropped).sum()), int(on.sum())
     assert abs(k - m / 2) <= 5 * (m / 4) ** 0.5
+
+
+@pytest.mark.parametrize("n,d_in,d_out", [(17000, 300, 130), (17409, 602, 130), (40000, 130, 130), (20011, 602, 130), (30011, 66, 290)], ids=lambda v: str(v))
+def test_forward_products_however_their_columns_are_dealt(n, d_in, d_out):
+    """A hidden layer's product, whose columns go to workgroups by how many tiles the fullest compute unit gets: each element within
+    the allowance, and the bits of the same rows in a product that deals them otherwise."""
+    import torch
+    import paper_2203_10983_amd as pkg
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(n)
+    f32 = lambda *s: torch.randn(*s, device="cuda:0", generator=gen)  # noqa: E731
+    i32 = lambda k: torch.zeros(k, dtype=torch.int32, device="cuda:0")  # noqa: E731
+    X, W = f32(n, d_in), f32(d_in, d_out)
+    got = []
+    for m in (n, 9100):
+        ctx = pkg.Context(_loops(m), [d_in, d_out, 8], 0, device=torch.device("cuda:0"))
+        kept, remap, n_kept, nnz = i32(1), i32(1), i32(1), i32(1)
+        ctx.sample_boundary(1, 0, 0.5, kept, remap, n_kept)
+        csr = i32(m + 1), i32(m), i32(m + 1), i32(m)
+        ctx.build_sampled_csr(remap, kept, n_kept, *csr, nnz)
+        A, H = torch.empty(m, d_in, device="cuda:0"), torch.full((m + 1, d_out), 7.0, device="cuda:0")
+        ctx.gcn_layer_fwd(1, 0.5, X[:m], None, W, A, H[:m], True)
+        torch.cuda.synchronize()
+        assert bool((H[m] == 7.0).all())
+        got.append(H[:m])
+        ctx.close()
+    assert torch.equal(got[1], got[0][:9100])
+    ref, size = (X.double() @ W.double()).clamp(min=0), X.double().abs() @ W.double().abs()
+    assert ((got[0].double() - ref).abs() <= 4.0 * 2.0 ** -24 * (1 + d_in ** 0.5) * size).all()
