@@ -466,6 +466,19 @@ seg_fill_kernel(int32_t n_rows, const int32_t *__restrict__ seg_ptr, const int32
 // 128 entries 434 + 12 -> 418 + 22 and 789 + 9 -> 762 + 17, 64 entries 460 + 41).
 // A tile is kOrderTile segments; counts[bucket * tiles + tile].
 constexpr int kBuckets = 1024, kOrderTile = 4096, kOrderMin = 4096;
+// Calls f(i) for the thread's own keys among the m of the tile, in ascending order, eight to a read of the LDS.  f leaves no store to memory in
+// the loop: those held it up (set-up of 578125 rows 8.2 -> 7.9 ms, 7.5 without the order).
+template <typename F>
+__device__ __forceinline__ void each_match(const uint16_t *keys, int m, F f) {
+  typedef unsigned u4 __attribute__((ext_vector_type(4)));
+  for (int i = 0; i < m; i += 8) {
+    const u4 w = *reinterpret_cast<const u4 *>(keys + i);
+#pragma unroll
+    for (int k = 0; k < 8; ++k)
+      if (((w[k / 2] >> (16 * (k & 1))) & 0xffffu) == threadIdx.x && i + k < m) f(i + k);
+  }
+}
+
 __device__ __forceinline__ void segment_buckets(uint16_t *keys, int n, const int2 *units, const int32_t *row_ptr, const int32_t *col, int64_t n_cols,
                                                 const int32_t *seg_ptr, const int32_t *part_ptr) {
   for (int i = threadIdx.x; i < n; i += kBuckets) {
@@ -473,7 +486,7 @@ __device__ __forceinline__ void segment_buckets(uint16_t *keys, int n, const int
     const int r0 = row_ptr[u.x], r1 = row_ptr[u.x + 1], nseg = seg_ptr[u.x + 1] - seg_ptr[u.x];
     const int chunk = (r1 - r0 + nseg - 1) / nseg;
     const int e = min(r0 + (u.y - part_ptr[u.x]) * chunk + chunk / 2, r1 - 1);
-    keys[i] = (uint16_t)((int64_t)col[e] * kBuckets / n_cols);
+    keys[i] = (uint16_t)max((int64_t)0, min((int64_t)col[e] * kBuckets / n_cols, (int64_t)kBuckets - 1));
   }
   __syncthreads();
 }
@@ -481,23 +494,25 @@ __device__ __forceinline__ void segment_buckets(uint16_t *keys, int n, const int
 __global__ void __launch_bounds__(kBuckets)
 seg_order_count_kernel(int n, const int2 *units, const int32_t *row_ptr, const int32_t *col, int64_t n_cols, const int32_t *seg_ptr,
                        const int32_t *part_ptr, int32_t *counts) {
-  __shared__ uint16_t keys[kOrderTile];
+  __shared__ __attribute__((aligned(16))) uint16_t keys[kOrderTile];
   const int i0 = blockIdx.x * kOrderTile, m = min(kOrderTile, n - i0);
   segment_buckets(keys, m, units + i0, row_ptr, col, n_cols, seg_ptr, part_ptr);
   int mine = 0;
-  for (int i = 0; i < m; ++i) mine += keys[i] == threadIdx.x;
+  each_match(keys, m, [&](int) { ++mine; });
   counts[threadIdx.x * gridDim.x + blockIdx.x] = mine;
 }
 
 __global__ void __launch_bounds__(kBuckets)
 seg_order_write_kernel(int n, const int2 *units, const int32_t *row_ptr, const int32_t *col, int64_t n_cols, const int32_t *seg_ptr,
                        const int32_t *part_ptr, const int32_t *starts, int2 *order) {
-  __shared__ uint16_t keys[kOrderTile];
+  __shared__ __attribute__((aligned(16))) uint16_t keys[kOrderTile];
+  __shared__ int32_t place[kOrderTile];
   const int i0 = blockIdx.x * kOrderTile, m = min(kOrderTile, n - i0);
   segment_buckets(keys, m, units + i0, row_ptr, col, n_cols, seg_ptr, part_ptr);
   int at = starts[threadIdx.x * gridDim.x + blockIdx.x];
-  for (int i = 0; i < m; ++i)
-    if (keys[i] == threadIdx.x) order[at++] = units[i0 + i];
+  each_match(keys, m, [&](int i) { place[i] = at++; });
+  __syncthreads();
+  for (int i = threadIdx.x; i < m; i += kBuckets) order[place[i]] = units[i0 + i];
 }
 
 // *out = the most segments of a row, over the *n multi-segment rows (1 if there is none)
