@@ -441,13 +441,11 @@ bns_status layer_fwd_impl(bns_ctx *ctx, int layer, double p, const float *H_in, 
   SpmmRowPart part;
   part.halo_rec = B > 0 ? ctx->ws.halo_rec : nullptr;
   part.skip_self = sage;
-  part.halo_share = (float)(p * ctx->part.e_bd / (ctx->part.e_in + p * ctx->part.e_bd));
   if (layer == 1 && ctx->cache_X != nullptr && ctx->cache_X == H_in) {
     // inner neighbours are the same every epoch: their sum is cached, only the kept boundary
     // tail of each row is aggregated now
     part.row_skip = ctx->ws.split.n_inner;
     part.init = ctx->ws.C0;
-    part.halo_share = 1.f;
   }
   const float *w_in = ctx->ws.w_fwd;
   const int32_t *w_ptr = ctx->ws.split.inner_ptr;

@@ -161,7 +161,6 @@ struct SpmmRowPart {
   // halo_rec (from halo_records): Hu is then the whole boundary-feature table [n_halo, d] as the
   // caller holds it; kept node r reads its row halo_rec[r].x with weight as_float(halo_rec[r].y)
   const int2 *halo_rec = nullptr;
-  float halo_share = 0.f;  // share of the entries that are expected to be kept boundary ones (launch heuristics)
 };
 // rec[r] = (kept_ids[r], s_halo * dis_halo[kept_ids[r]]) for r < *n_kept (dis_halo nullable = 1): what the
 // aggregate needs to read the kept boundary rows where they are instead of a gathered, scaled copy.

@@ -167,6 +167,104 @@ __global__ void __launch_bounds__(BLOCK ? kBlockWaves * kWave : 256, MAXCH == 1 
   }
 }
 
+// The segments of the long rows ahead of a one-kernel layer of 128 floats, in two slices over the XCDs.  Whole rows of 128 go to 32 lanes each, so that a
+// segment has two running sums, and a launch must not give it others: sums in another order switch hidden units within rounding of
+// zero.  64 lanes on a slice would make four sums (of 64 floats) or eight (of 32).  So a wavefront takes two segments, which follow each other
+// in the columns' order: 32 lanes to a segment, 16 to an entry, four entries to a load.  The next batch's columns and
+// weights are asked for before a batch is gathered: there is one chain of reads for two segments.
+// Us, whole rows / so / with eight sums (not kept): 306250 rows of 45 entries 210 / 182 / 159, 578125 of 21 212 / 200 / 182, 100000 of 92 130 / 117 / 114, of
+// 196 309 / 277 / 275, 250000 of 20 74 / 71 / 59; with 9 % of boundary entries, which are looked up in the kept nodes' records in every slice, 306250 of 50
+// 259 / 245 / 227, with 24 % of 59 354 / 343, with 26 % 578125 of 28 349 / 358.  One segment to a wavefront, two floats to a lane, the first four 183, 194, 135,
+// 332; four segments in slices of 32 floats 176, 207, 133, 310.
+constexpr int kLongPerWave = 2;
+template <int T0, typename F>
+__device__ __forceinline__ void eight_steps(F f) {
+  f(std::integral_constant<int, T0>{}); f(std::integral_constant<int, T0 + 1>{}); f(std::integral_constant<int, T0 + 2>{}); f(std::integral_constant<int, T0 + 3>{});
+  f(std::integral_constant<int, T0 + 4>{}); f(std::integral_constant<int, T0 + 5>{}); f(std::integral_constant<int, T0 + 6>{}); f(std::integral_constant<int, T0 + 7>{});
+}
+__global__ void __launch_bounds__(256, 8) spmm_long_kernel(const SpmmArgs) {
+  constexpr int VEC = 4, kLanes = kWave / kLongPerWave, EP = 2, kSteps = kLanes / EP;  // lanes of a segment, entries to a step, steps of a batch
+  const SpmmArgs::Head start = unit_head();
+  const int ls = start.log2_slices, x = blockIdx.x & 7;
+  const int bid = ((blockIdx.x >> 3) << (3 - ls)) + (x >> ls);
+  const int d_off = ((x + (int)__umulhi(bid, start.turn_share)) & ((1 << ls) - 1)) * start.d_slice;
+  const int lane = lane_id(), ln = lane % kLanes, g = ln / kSteps, sl = lane % kSteps;
+  const int first = (bid * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) * kLongPerWave, unit = first + lane / kLanes;
+  ArgBlock &a = unit_args();
+  const int2 u = a.units[min(unit, start.n_units - 1)];
+  const int row = u.x;
+  int e0 = a.row_ptr[row], e1 = a.row_ptr[row + 1], w_at = 0, w_end = e0;  // the weight of entry e < w_end is w_in[e + w_at]
+  if (a.w_in) {
+    const int w0 = a.w_ptr[row];
+    w_at = w0 - e0;
+    w_end = e0 + (a.w_ptr[row + 1] - w0);
+  }
+  const int s0 = a.plan.seg_ptr[row], nseg = a.plan.seg_ptr[row + 1] - s0, seg = u.y - a.plan.part_ptr[row];
+  if (a.row_skip) e0 += a.row_skip[row];
+  if (a.row_take) e1 = e0 + a.row_take[row];
+  const int chunk = (e1 - e0 + nseg - 1) / nseg;
+  e0 = min(e1, e0 + seg * chunk);
+  e1 = unit < start.n_units ? min(e1, e0 + chunk) : e0;
+  float acc[1][VEC] = {};
+  int c_next = 0;
+  float w_next = 0.f;
+  auto ask = [&](int e, int n) {
+    if (ln < n) {
+      if (e < w_end) w_next = a.w_in[e + w_at];
+      c_next = a.col_idx[e];
+    }
+  };
+  int e = e0 + ln, cnt = e1 - e0;  // (cnt: 0 and less where the other segment is the longer one)
+  ask(e, cnt);
+  for (; __any(cnt > 0); cnt -= kLanes) {
+    // step t takes entries EP t + g of the batch; lane t of the sixteen holds that one (fetched in their own order: batch_entry)
+    int l = lane_id();
+    asm volatile("" : "+v"(l));  // (found again rather than kept in registers beside the gather)
+    const int mine = (l % kSteps) * EP + l / kSteps % EP, from = l / kLanes * kLanes + mine;
+    const int c = __shfl(c_next, from, kWave);
+    const float w_e = __shfl(w_next, from, kWave);
+    w_next = 0.f;
+    e += kLanes;
+    ask(e, cnt - kLanes);
+    unsigned long long p_l = 0;
+    float w_l = 0.f;
+    if (mine < cnt) entry_source(a, row, c, d_off, p_l, w_l, [&] { return a.w_in ? w_e : 1.f; });
+    const unsigned lo_l = (unsigned)p_l, hi_l = (unsigned)(p_l >> 32), w_u = __float_as_uint(w_l);
+    auto steps = [&](auto whole, auto t0) {
+      constexpr int T0 = decltype(t0)::value;
+      Vec<VEC>::T v[8];
+      eight_steps<T0>([&](auto tc) {
+        constexpr int t = decltype(tc)::value;
+        const unsigned lo = row_bcast<t>(lo_l), hi = row_bcast<t>(hi_l);
+        v[t - T0] = Vec<VEC>::T{};
+        if (decltype(whole)::value || t * EP + g < cnt) v[t - T0] = load_row_piece<VEC, false>(hi, lo, sl * VEC);
+      });
+      eight_steps<T0>([&](auto tc) {
+        constexpr int t = decltype(tc)::value;
+        vec_fma<VEC>(acc[0], __uint_as_float(row_bcast<t>(w_u)), reinterpret_cast<const float *>(&v[t - T0]));
+      });
+    };
+    const std::integral_constant<int, 0> t0;
+    const std::integral_constant<int, 8> t8;
+    if (__all(cnt >= 8 * EP)) steps(std::true_type{}, t0);
+    else steps(std::false_type{}, t0);
+    if (__all(cnt >= 16 * EP)) steps(std::true_type{}, t8);
+    else if (__any(cnt > 8 * EP)) steps(std::false_type{}, t8);
+  }
+#pragma unroll
+  for (int i = 0; i < VEC; ++i) acc[0][i] = lane_pair_sum(acc[0][i], kSteps);
+  if (g != 0) return;
+  ArgBlock &b = unit_args();
+  int at = lane_id();
+  asm volatile("" : "+v"(at));
+  const int done = first + at / kLanes;
+  if (done >= start.n_units) return;
+  Vec<VEC>::T o;
+#pragma unroll
+  for (int i = 0; i < VEC; ++i) reinterpret_cast<float *>(&o)[i] = acc[0][i];
+  reinterpret_cast<Vec<VEC>::T *>(b.partials + (size_t)b.units[done].y * b.d + d_off)[sl] = o;
+}
+
 // Rows cut into several segments: add the partial sums in ascending segment order.
 template <int VEC, int MAXCH, bool NARROW = false, bool RAGGED = false>
 __global__ void __launch_bounds__(256) spmm_combine_kernel(const SpmmArgs a) {
@@ -209,7 +307,7 @@ __global__ void __launch_bounds__(256) spmm_combine_kernel(const SpmmArgs a) {
 
 
 template <int VEC, bool RAGGED>
-static hipError_t launch_spmm_vec(const SpmmArgs &a_in, int64_t extra_rows, bool multi_only, float halo_share, int32_t avg_len, bool transposed, hipStream_t s) {
+static hipError_t launch_spmm_vec(const SpmmArgs &a_in, int64_t extra_rows, bool multi_only, int32_t avg_len, bool transposed, hipStream_t s) {
   SpmmArgs a = a_in;
   // multi_only: the segments of the multi-segment rows, which come first
   const int64_t n_units = a.head.n_units = multi_only ? a.plan.n_part : a.plan.n_seg;
@@ -224,7 +322,7 @@ static hipError_t launch_spmm_vec(const SpmmArgs &a_in, int64_t extra_rows, bool
   //     with 21.3 87 -> 80; 300000 with 21.3 508 -> 474; 886000 with 14.5 853 -> 991, with 19.6 1108 -> 1132), more slices from
   //     24 on (60000 rows of 256 with 21.3 150 -> 153, with 26 182 -> 165; of 512 277 -> 289, 332 -> 307);
   //   neither, in between: from 32 on (9000 rows of 512 with 26.9 entries 41 -> 48, 16000 70 -> 81; 16000 of 256 with 56.6 70 -> 68).
-  // A forward row keeps the slices, and with them the order of its sum, that it has always had (from 64 entries on).
+  // A forward row keeps the order of its sum, and so its slices (from 64 entries on): see spmm_long_kernel.
   int ls = 0;
   if (VEC == 4 && !multi_only) {
     auto slices = [&](int target) {
@@ -237,15 +335,9 @@ static hipError_t launch_spmm_vec(const SpmmArgs &a_in, int64_t extra_rows, bool
     if (transposed)
       from = (n_units << ls) <= 8192 ? 19 : n_units < 24576 ? 32 : ls == 0 ? 19 : 24;
     if (avg_len >= from) ls = slices(64);
-  } else if (VEC == 4 && !RAGGED && multi_only && halo_share <= 0.15f) {
-    // Segments of long rows keep a wavefront busy at any width, so that their slices are as narrow as a 128-byte line (whole
-    // lines: any other cut would fetch some twice).  128 floats, whole / slices of 64 / of 32, us: 306250 rows of 45 entries
-    // 216 / 180 / 172, 100000 of 92 131 / 107 / 113, of 196 306 / 264 / 270; 578125 of 21 216 / 189 / 185; 250000 of 20
-    // 74 / 61 / 58.  An entry of a boundary row is looked up in the kept nodes' records in every slice, a line each beside the
-    // four of its features: with 9 % of them 306250 rows of 50 266 / 233 / 229, with 26 % 578125 of 28 346 / 354 / 370 (with 24 % 306250 of 59
-    // 349 / 353 / 326).
-    while (ls < 3 && (a.d >> (ls + 1)) >= 32 && a.d % (32 << (ls + 1)) == 0) ++ls;
   }
+  const bool by_two = VEC == 4 && !RAGGED && multi_only && a.d == 128;  // spmm_long_kernel: the one width of whole lines in two slices (68 to 128 there are)
+  if (by_two) ls = 1;
   a.head.log2_slices = ls;
   a.head.d_slice = RAGGED && ls > 0 ? ((a.d + (1 << ls) - 1) / (1 << ls) + 3) / 4 * 4 : a.d >> ls;  // (the last one of a ragged row is narrower)
   // The pass over the partial sums is a launch of 3 to 5 us.  Where the longest row has few segments, a workgroup per such
@@ -256,7 +348,7 @@ static hipError_t launch_spmm_vec(const SpmmArgs &a_in, int64_t extra_rows, bool
   const bool narrow_slice = a.head.d_slice > 32 && a.head.d_slice <= 64;
   const bool block_rows = !multi_only && a.plan.n_multi > 0 && a.plan.max_seg <= kBlockWaves &&
                           ((int64_t)a.plan.n_seg << ls) <= (narrow_slice ? 20480 : 65536);
-  const int waves = block_rows ? kBlockWaves : 4;
+  const int waves = block_rows ? kBlockWaves : 4, wave_units = by_two ? kLongPerWave : 1;
   const int nvec = (a.head.d_slice + VEC - 1) / VEC;
   const int full_nvec = (a.d + VEC - 1) / VEC;
   // One wavefront per static segment.  The kept boundary rows are a few entries each.  Where all wavefronts go on to them
@@ -283,7 +375,7 @@ static hipError_t launch_spmm_vec(const SpmmArgs &a_in, int64_t extra_rows, bool
     a.units += a.plan.n_part;
     a.head.n_units -= a.plan.n_part;
   }
-  const int64_t unit_groups = groups((a.head.n_units + waves - 1) / waves);
+  const int64_t unit_groups = groups((a.head.n_units + waves * wave_units - 1) / (waves * wave_units));
   const bool dealt = extra_rows >= 0 && avg_len >= (a.d > 64 ? 13 : 24) && (n_units << ls) >= (a.d > 32 ? 16384 : 24576) &&
                      (a.d > 32 || extra_rows <= n_units);
   // Eight at a time (short_rows) where they are not dealt, every wavefront has so many to go on to, and they are no fewer than the
@@ -351,7 +443,8 @@ static hipError_t launch_spmm_vec(const SpmmArgs &a_in, int64_t extra_rows, bool
     else return hipErrorInvalidValue;
     if (cblocks) BNS_COMBINE(1);
   } else {
-    if (nvec <= 1) BNS_SPMM(1, 1);
+    if (by_two) spmm_long_kernel<<<blocks, 256, 0, s>>>(a);
+    else if (nvec <= 1) BNS_SPMM(1, 1);
     else if (nvec <= 2) BNS_SPMM(1, 2);
     else if (nvec <= 4) BNS_SPMM(1, 4);
     else if (nvec <= 8) BNS_SPMM(1, 8);
@@ -377,19 +470,19 @@ static hipError_t launch_spmm_vec(const SpmmArgs &a_in, int64_t extra_rows, bool
   return hipGetLastError();
 }
 
-static hipError_t launch_spmm(const SpmmArgs &a, int64_t extra_rows, bool multi_only, float halo_share, int32_t avg_len, bool transposed, hipStream_t s) {
+static hipError_t launch_spmm(const SpmmArgs &a, int64_t extra_rows, bool multi_only, int32_t avg_len, bool transposed, hipStream_t s) {
   if (a.d_store != a.d && (a.d_store < 1 || a.d_store > a.d || a.d >= 128 || a.d % 4 != 0 || a.mask_src || a.init))
     return hipErrorInvalidValue;  // padded sources: narrow rows without mask or initial value only
-  if (a.d % 4 == 0) return launch_spmm_vec<4, false>(a, extra_rows, multi_only, halo_share, avg_len, transposed, s);
+  if (a.d % 4 == 0) return launch_spmm_vec<4, false>(a, extra_rows, multi_only, avg_len, transposed, s);
   // Widths that are no multiple of 4: 16-byte loads at 4-byte alignment, and slices as for the others, where loads of 8 or 4 bytes
   // took up to four times as many instructions (130 floats: 65 lanes, a second load for the last one) and could not be
   // sliced.  Forward and transposed, us: 60000 rows of 45 entries, 31 floats 75 -> 62 and 130 -> 91, 66 120 -> 108 and 225 -> 144, 130
   // 232 -> 197 and 443 -> 235, 258 413 -> 403 and 660 -> 404, 602 907 -> 855 and 1235 -> 846; 20011 rows of 14, 9 floats the same,
   // 66 34 -> 28 and 45 -> 35, 130 56 -> 39 and 81 -> 50, 602 145 -> 111 and 189 -> 126.  Up to 8 floats a row is one or two
   // pieces, of which a wavefront has more than there are entries (20011 rows, 6 floats: 17.7 and 19.8 us, in pieces of 16 bytes 18.5 and 20.6).
-  if (a.d > 8) return launch_spmm_vec<4, true>(a, extra_rows, multi_only, halo_share, avg_len, transposed, s);
-  if (a.d % 2 == 0) return launch_spmm_vec<2, false>(a, extra_rows, multi_only, halo_share, avg_len, transposed, s);
-  return launch_spmm_vec<1, false>(a, extra_rows, multi_only, halo_share, avg_len, transposed, s);
+  if (a.d > 8) return launch_spmm_vec<4, true>(a, extra_rows, multi_only, avg_len, transposed, s);
+  if (a.d % 2 == 0) return launch_spmm_vec<2, false>(a, extra_rows, multi_only, avg_len, transposed, s);
+  return launch_spmm_vec<1, false>(a, extra_rows, multi_only, avg_len, transposed, s);
 }
 
 hipError_t spmm_fwd(const SegPlan &plan, int32_t n_in, int32_t d, const int32_t *row_ptr,
@@ -399,7 +492,7 @@ hipError_t spmm_fwd(const SegPlan &plan, int32_t n_in, int32_t d, const int32_t 
   SpmmArgs a = spmm_fwd_args(plan, n_in, d, row_ptr, col_idx, w_in, w_ptr, row_scale, H_in, Hu, partials, A, part);
   a.relu = relu;
   if (d_store > 0) a.d_store = d_store;
-  return launch_spmm(a, -1, long_rows_only, part.halo_share, plan.avg_len, false, s);
+  return launch_spmm(a, -1, long_rows_only, plan.avg_len, false, s);
 }
 
 hipError_t spmm_bwd(const SegPlan &plan, int32_t n_in, int32_t n_halo, int32_t d,
@@ -416,7 +509,7 @@ hipError_t spmm_bwd(const SegPlan &plan, int32_t n_in, int32_t n_halo, int32_t d
   a.out0 = dH_in; a.out1 = dhalo; a.out_scale0 = row_scale; a.mask_src = mask_src;
   a.kept_ids = kept_ids; a.dis_halo = dis_halo; a.s_halo = s_halo;
   a.init = init; a.skip_self = skip_self;
-  return launch_spmm(a, halo_rows ? expected_halo : -1, false, 0.f, avg_len, true, s);
+  return launch_spmm(a, halo_rows ? expected_halo : -1, false, avg_len, true, s);
 }
 
 // ------------------------------------------------------------------------------------------

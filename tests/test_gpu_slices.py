@@ -174,3 +174,74 @@ def test_many_short_rows(d, e, p):
     torch.testing.assert_close(dX.double(), s_in * G, rtol=1e-5, atol=3e-5)
     assert bool((dhalo[K:] == 7.0).all())
     ctx.close()
+
+
+def _long_row_sums(rows, X, Xb, kept, n, w_halo, nseg):
+    """Sums of rows of several segments, rounding by rounding: a segment's entries go in turn to two running sums (32 lanes to an entry,
+    half a wavefront), which are added; the segments are added in ascending order.  All weights are 0, 1 or w_halo, a power of two."""
+    out = []
+    for (v, cols), k in zip(rows, nseg):
+        x = np.stack([X[c] * np.float32(c != v) if c < n else Xb[kept[c - n]] * np.float32(w_halo) for c in cols])
+        chunk, total = max(1, -(-len(cols) // k)), np.zeros(X.shape[1], np.float32)
+        for s in range(0, len(cols), chunk):
+            acc = np.zeros((2, X.shape[1]), np.float32)
+            for e, row in enumerate(x[s:s + chunk]):
+                acc[e % 2] += row
+            total += acc[0] + acc[1]
+        out.append(total)
+    return np.stack(out)
+
+
+@pytest.mark.parametrize("cached", [False, True])
+@pytest.mark.parametrize("n", [3000, 20000, 98304])  # layers of one launch, of two, and of one after the long rows
+@pytest.mark.parametrize("d,bd", [(128, 20), (128, 200), (100, 20), (68, 200)])
+def test_order_of_the_sums_of_long_rows(d, bd, n, cached):
+    """Which hidden units a ReLU switches on hangs on the last bit of a forward sum: its order is that of the width alone, whatever the
+    share of the boundary entries, the route of the layer and the slices of a launch."""
+    import torch
+    import paper_2203_10983_amd as pkg
+    dev = torch.device("cuda:0")
+    rng = np.random.default_rng(d + bd + n)
+    nb, p = 2000, 0.5
+    long = np.sort(rng.choice(n, size=24, replace=False))
+    deg = np.full(n, 4)
+    deg[long] = rng.integers(257, 1300, long.size)
+    n_bd = np.zeros(n, dtype=np.int64)
+    n_bd[long] = bd
+    lists = [np.unique(np.append(rng.integers(0, n, deg[v]), v)) for v in range(n)]
+    bds = [np.sort(rng.choice(nb, size=k, replace=False)) for k in n_bd]
+    bds[0] = np.arange(nb)  # (every boundary node has a neighbour)
+    cols = [np.concatenate([a, n + b]) for a, b in zip(lists, bds)]
+    row, col = np.repeat(np.arange(n), [len(c) for c in cols]), np.concatenate(cols)
+    inner = col < n
+    t, h = np.lexsort((row[inner], col[inner])), np.lexsort((row[~inner], col[~inner]))
+    i32 = lambda x: np.ascontiguousarray(x, dtype=np.int32)  # noqa: E731
+    ptr = lambda of, m: i32(np.concatenate([[0], np.cumsum(np.bincount(of, minlength=m))]))  # noqa: E731
+    P = types.SimpleNamespace(
+        part_id=0, n_in=n, n_halo=nb, nnz0=len(col), e_in=int(inner.sum()), e_bd=int((~inner).sum()), row_ptr0=ptr(row, n), col0=i32(col),
+        t_in_ptr=ptr(col[inner], n), t_in_col=i32(row[inner][t]), halo_ptr=ptr(col[~inner] - n, nb), halo_col=i32(row[~inner][h]),
+        halo_gid=np.arange(n, n + nb, dtype=np.int64), deg_in=i32(np.full(n, 1025)), deg_halo=i32(np.full(nb, 1025)))
+    z32 = lambda m: torch.zeros(m, dtype=torch.int32, device=dev)  # noqa: E731
+    ctx = pkg.Context(P, [d, 8], 0, device=dev, layer_kind=1)
+    kept, remap, n_kept, nnz = z32(nb), z32(nb), z32(1), z32(1)
+    ctx.sample_boundary(3, 0, p, kept, remap, n_kept)
+    csr = z32(n + 1), z32(P.nnz0), z32(n + nb + 1), z32(P.nnz0)
+    ctx.build_sampled_csr(remap, kept, n_kept, *csr, nnz)
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(d)
+    X, Xb, W = (torch.randn(*s, device=dev, generator=gen) for s in ((n, d), (nb, d), (2 * d, 8)))
+    A, H = torch.zeros(n, d, device=dev), torch.zeros(n, 8, device=dev)
+    if cached:
+        ctx.cache_input_aggregate(X)
+    ctx.gcn_layer_fwd(1, p, X, Xb, W, A, H, False)
+    torch.cuda.synchronize()
+    rp, ci, of = csr[0].cpu().numpy(), csr[1].cpu().numpy(), kept.cpu().numpy()
+    rows = [(v, ci[rp[v]:rp[v + 1]]) for v in long]
+    parts = [[(v, c[c < n]) for v, c in rows], [(v, c[c >= n]) for v, c in rows]] if cached else [rows]
+    nseg = [-(-len(cols[v]) // 256) for v in long]
+    sums = [_long_row_sums(r, X.cpu().numpy(), Xb.cpu().numpy(), of, n, 1 / p, nseg) for r in parts]
+    want = (sums[1] + sums[0] if cached else sums[0]) * np.float32(1.0 / 1024)
+    got = A.cpu().numpy()[long]
+    assert np.allclose(got, want, rtol=1e-4, atol=1e-5)  # (or the weights are not those of the docstring)
+    assert np.array_equal(got, want)
+    ctx.close()
