@@ -300,8 +300,8 @@ bns_status bns_ws_view(const bns_ctx *ctx, bns_view which, int32_t layer, void *
 typedef enum {
   BNS_PHASE_SAMPLE = 0,   /* sample_boundary kernels; in bns_train_step on a small partition (at most
                              8192 boundary nodes and 8192 boundary entries, and inner entries + 3 per inner node
-                             + 1 and 12 p per boundary node at most 81920) the selection and the
-                             subgraph step together, up to 51200 one launch             */
+                             + 1 and 12 p per boundary node at most 51200) the one launch that runs
+                             the selection and the subgraph step together               */
   BNS_PHASE_BUILD = 1,    /* sampled CSR + transposed CSR (no bracket where the sample phase covers it)  */
   BNS_PHASE_GATHER = 2,   /* layer calls: records of the kept boundary rows (x 1/p); a step has them from SAMPLE */
   BNS_PHASE_SPMM_FWD = 3, /* aggregate                                     */

@@ -328,7 +328,6 @@ bns_status hip_fail(bns_ctx *ctx, const char *what, hipError_t e) {
 // A launch that carries work of two kinds is taken apart while the phase that it would be counted for is timed.
 bool timed(const bns_ctx *ctx, int phase) { return ((ctx->prof.mask >> phase) & 1u) && ctx->prof.used < ctx->prof.start.size(); }
 
-constexpr int kNoPhase = -1;
 // Brackets the kernels enqueued during its lifetime with two events (only if the phase is enabled).
 struct PhaseTimer {
   Profiler *p = nullptr;
@@ -336,7 +335,7 @@ struct PhaseTimer {
   size_t slot = 0;
   PhaseTimer(bns_ctx *ctx, int phase, hipStream_t stream) : s(stream) {
     Profiler &pr = ctx->prof;
-    if (phase == kNoPhase || !((pr.mask >> phase) & 1u) || pr.used >= pr.start.size()) return;
+    if (!((pr.mask >> phase) & 1u) || pr.used >= pr.start.size()) return;
     p = &pr;
     slot = pr.used++;
     pr.phase[slot] = phase;
@@ -736,11 +735,10 @@ BdCount bd_count(const bns_ctx *ctx) { return BdCount{ctx->part.e_bd, ctx->ws.sp
 
 // pack (nullable): a training step's: weights to pack beside the sampling, and the records of the kept nodes too
 bns_status sample_impl(bns_ctx *ctx, uint64_t seed, uint32_t epoch, const uint32_t *epoch_dev, double p,
-                       int32_t *kept_ids, int32_t *remap, int32_t *n_kept, const PackJobs *pack, hipStream_t s,
-                       int phase = BNS_PHASE_SAMPLE) {
+                       int32_t *kept_ids, int32_t *remap, int32_t *n_kept, const PackJobs *pack, hipStream_t s) {
   const uint64_t threshold = (uint64_t)std::floor(p * 4294967296.0);
   const BdCount count = bd_count(ctx);
-  PhaseTimer t(ctx, phase, s);
+  PhaseTimer t(ctx, BNS_PHASE_SAMPLE, s);
   BNS_TRY("sample_boundary",
           sample_boundary(ctx->part.halo_gid, ctx->part.n_halo, seed, epoch, epoch_dev, (uint32_t)ctx->part.part_id,
                           threshold, ctx->ws.ballots, ctx->ws.tile_sums, kept_ids, remap, n_kept, ctx->part.halo_ptr,
@@ -758,9 +756,9 @@ bns_status sample_impl(bns_ctx *ctx, uint64_t seed, uint32_t epoch, const uint32
 }
 
 bns_status build_impl(bns_ctx *ctx, int32_t *row_ptr, int32_t *col_idx, int32_t *t_row_ptr,
-                      int32_t *t_col_idx, int32_t *nnz, hipStream_t s, int phase = BNS_PHASE_BUILD) {
+                      int32_t *t_col_idx, int32_t *nnz, hipStream_t s) {
   const bns_partition_desc &P = ctx->part;
-  PhaseTimer t(ctx, phase, s);
+  PhaseTimer t(ctx, BNS_PHASE_BUILD, s);
   SubgraphBuild g{};
   g.n_in = P.n_in; g.n_halo = P.n_halo; g.e_in = P.e_in;
   g.sp = ctx->ws.split;
@@ -780,20 +778,19 @@ bns_status build_impl(bns_ctx *ctx, int32_t *row_ptr, int32_t *col_idx, int32_t 
   return BNS_OK;
 }
 
-// Selection step + subgraph step of a training step, into the workspace arrays: timed as the sample phase for a small partition, and up to
-// kOneLaunchMaxWork one launch, else the two calls above.
+// Selection step + subgraph step of a training step, into the workspace arrays: one launch for a
+// small partition (timed as the sample phase), else the two calls above.
 bns_status sample_and_build_impl(bns_ctx *ctx, uint64_t seed, uint32_t epoch, const uint32_t *epoch_dev, double p,
                                  const PackJobs &pack, hipStream_t s) {
   Layout &w = ctx->ws;
   const bns_partition_desc &P = ctx->part;
-  const bool small = sample_build_small_fits(P.n_in, P.n_halo, P.e_in, P.e_bd, expected_kept(ctx, p));
-  PhaseTimer t(ctx, small ? (int)BNS_PHASE_SAMPLE : kNoPhase, s);
-  if (!small || small_work(P.n_in, P.n_halo, P.e_in, expected_kept(ctx, p)) > kOneLaunchMaxWork) {
-    const bns_status st = sample_impl(ctx, seed, epoch, epoch_dev, p, w.kept_ids, w.remap, w.counters, &pack, s, small ? kNoPhase : (int)BNS_PHASE_SAMPLE);
+  if (!sample_build_small_fits(P.n_in, P.n_halo, P.e_in, P.e_bd, expected_kept(ctx, p))) {
+    const bns_status st = sample_impl(ctx, seed, epoch, epoch_dev, p, w.kept_ids, w.remap, w.counters, &pack, s);
     if (st != BNS_OK) return st;
-    return build_impl(ctx, w.row_ptr, w.col_idx, w.t_row_ptr, w.t_col_idx, w.counters + 1, s, small ? kNoPhase : (int)BNS_PHASE_BUILD);
+    return build_impl(ctx, w.row_ptr, w.col_idx, w.t_row_ptr, w.t_col_idx, w.counters + 1, s);
   }
   const uint64_t threshold = (uint64_t)std::floor(p * 4294967296.0);
+  PhaseTimer t(ctx, BNS_PHASE_SAMPLE, s);
   BNS_TRY("sample_build_small",
           sample_build_small(P.halo_gid, P.n_halo, seed, epoch, epoch_dev, (uint32_t)P.part_id, threshold, w.ballots,
                              w.kept_ids, w.remap, w.counters, w.kept_start, P.n_in, P.e_in, P.e_bd, w.split,

@@ -102,16 +102,12 @@ hipError_t copy_static_rows(int32_t n_in, int64_t e_in, const int32_t *t_in_ptr,
 // hold the static rows of the inner nodes).  Its LDS holds so many boundary nodes and entries:
 constexpr int kSmallMaxHalo = 8192;             // boundary nodes
 constexpr int kSmallMaxBoundaryEntries = 8192;  // entries with a boundary column
-// and a partition that fits it is timed as one phase up to kSmallMaxWork.  One launch pays where one workgroup takes less time than the three
-// launches of the general path, up to kOneLaunchMaxWork (steps of 64-16-8, general and one launch, us: 600 rows with 2992 inner entries
+// and it pays where one workgroup takes less time than the three launches of the general path, up to kSmallMaxWork (steps of 64-16-8, general and one launch, us: 600 rows with 2992 inner entries
 // beside 300 boundary nodes and 7637 entries at p = 0.1, work 5452, 32.7 / 28.8; 2535 with 22045 beside 604 and 1445, 30986, 38.5 / 35.3; 1622 with
 // 33052 beside 315 and 402 at p = 1, 42013, 36.5 / 34.3; 2781 with 26611 beside 1421 and 3336 at p = 0.5, 44907, 42.9 / 42.4; beyond it 8000 with 23998 beside
 // 5000 and 7999 at p = 0.1, 58998, 48.7 / 53.0; 2434 with 26870 beside 2475 and 2771 at p = 1, 66347, 45.0 / 49.1; 2000 with 61556 beside
 // 300 and 1397, 68216, 38.0 / 39.0; 1500 with 31262 beside 3500 and 8095 at p = 1, 81262, 42.8 / 52.3).
-constexpr int kSmallMaxWork = 81920, kOneLaunchMaxWork = 51200;
-inline int64_t small_work(int32_t n_in, int32_t n_halo, int64_t e_in, int32_t expected_kept) {
-  return e_in + 3 * (int64_t)n_in + n_halo + 12 * (int64_t)expected_kept;
-}
+constexpr int kSmallMaxWork = 51200;  // inner entries + 3 per inner node + 1 per boundary node + 12 per boundary node to be expected
 bool sample_build_small_fits(int32_t n_in, int32_t n_halo, int64_t e_in, int64_t e_bd, int32_t expected_kept);
 hipError_t sample_build_small(const int64_t *halo_gid, int32_t n_halo, uint64_t seed, uint32_t epoch,
                               const uint32_t *epoch_dev, uint32_t part_id, uint64_t threshold, uint64_t *ballots,

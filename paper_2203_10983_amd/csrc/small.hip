@@ -243,7 +243,7 @@ __global__ void __launch_bounds__(kSmallThreads) sample_build_small_kernel(const
 
 bool sample_build_small_fits(int32_t n_in, int32_t n_halo, int64_t e_in, int64_t e_bd, int32_t expected_kept) {
   return n_halo <= kSmallMaxHalo && e_bd <= kSmallMaxBoundaryEntries &&
-         small_work(n_in, n_halo, e_in, expected_kept) <= kSmallMaxWork;
+         e_in + 3 * (int64_t)n_in + n_halo + 12 * (int64_t)expected_kept <= kSmallMaxWork;
 }
 
 hipError_t sample_build_small(const int64_t *halo_gid, int32_t n_halo, uint64_t seed, uint32_t epoch,

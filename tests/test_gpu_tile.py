@@ -190,14 +190,23 @@ def test_backward_with_infinite_gradients():
 
 @pytest.mark.parametrize("n,deg,n_halo,lists,p,one", [(3, 1, 1, 1, 1.0, True), (1023, 4, 1025, 2, 0.5, True), (300, 3, 8192, 1, 0.0, True),
                                                       (300, 3, 8193, 1, 0.0, False), (900, 3, 2900, 4, 1.0, True), (900, 3, 3400, 4, 0.1, False),
-                                                      (2000, 3, 5000, 1, 1.0, True), (2000, 3, 5600, 1, 1.0, False),
-                                                      (1700, 40, 100, 3, 1.0, True), (1900, 40, 100, 3, 1.0, False)])
+                                                      (2000, 3, 2850, 1, 1.0, True), (2000, 3, 2870, 1, 1.0, False),
+                                                      (1150, 40, 100, 3, 1.0, True), (1158, 40, 100, 3, 1.0, False)])
 def test_subgraph_of_a_step_at_the_limits(n, deg, n_halo, lists, p, one):
+    """Sampling and subgraph of a step in one launch or three, on either side of each limit, as its launches and its timers say; the same arrays."""
     import torch
     import paper_2203_10983_amd as pkg
     dev = torch.device("cuda:0")
     P = _partition(n, deg, 0, n_halo, np.random.default_rng(n_halo), lists)
-    assert one == (max(n_halo, P.e_bd) <= 8192 and P.e_in + 3 * n + n_halo + 12 * np.ceil(p * n_halo) <= 81920)
+    assert one == (max(n_halo, P.e_bd) <= 8192 and P.e_in + 3 * n + n_halo + 12 * np.ceil(p * n_halo) <= 51200)
+    launches = []
+    for Q in (P, _partition(n, deg, 0, 8193, np.random.default_rng(n_halo), 1)):  # (too many boundary nodes for one launch)
+        f32 = lambda *s: torch.zeros(*s, device=dev)  # noqa: E731
+        args = (p, f32(n, 8), [f32(Q.n_halo, 8)], torch.zeros(n, dtype=torch.int32, device=dev), [f32(8, 8)], [f32(8, 8)], [None], f32(1), 0.0)
+        ctx = pkg.Context(Q, [8, 8], 0, device=dev)
+        launches.append(_launches(lambda: ctx.train_step(11, 2, *args)))
+        ctx.close()
+    assert n == 3 or launches[0] == launches[1] - (2 if one else 0)  # (8193 boundary nodes make long rows of three)
     ctx = pkg.Context(P, [8, 8], 0, device=dev)
     i32 = lambda k: torch.zeros(k, dtype=torch.int32, device=dev)  # noqa: E731
     f32 = lambda *s: torch.zeros(*s, device=dev)  # noqa: E731
