@@ -186,12 +186,48 @@ __device__ __forceinline__ void bd_fill_tile(const BuildArgs &a, int tile) {
     if ((mask[i] >> lane) & 1ull) a.col_idx[row[i] + before[0] + word_before[i] + __popcll(mask[i] & lower)] = node[i];
 }
 
-// kpos[k[i]] of a workgroup's boundary entries k[i] <= e_bd, of which k_first is the smallest: the kept entries of the tiles before, of the words
+// sum[i] of the thread: kept boundary entries of the tiles from `first` up to tile at(i), at most `last`, for N values of i.  Added up by the whole
+// workgroup, a span of tiles at a time.  (What the thread finds stays in LDS: the ordinary case has no register to spare for it.)
+constexpr int kSpanItems = 4, kSpan = kSpanItems * kBdThreads;
+template <int N, typename F>
+__device__ __forceinline__ void tiles_between(const BuildArgs &a, int first, int last, F at, int (*sum)[kBdThreads]) {
+  __shared__ int until[kSpan];  // kept entries of the span's tiles before each one
+#pragma unroll
+  for (int i = 0; i < N; ++i) sum[i][threadIdx.x] = 0;
+#pragma unroll 1
+  for (int t0 = first; t0 < last; t0 += kSpan) {
+    int x[kSpanItems], mine = 0, all;
+#pragma unroll
+    for (int j = 0; j < kSpanItems; ++j) {
+      const int t = t0 + threadIdx.x * kSpanItems + j;
+      x[j] = t < last ? a.bd.sums[t] : 0;
+      mine += x[j];
+    }
+    int run = block_exclusive_scan<kBdThreads>(mine, &all);
+#pragma unroll
+    for (int j = 0; j < kSpanItems; ++j) {
+      until[threadIdx.x * kSpanItems + j] = run;
+      run += x[j];
+    }
+    __syncthreads();
+#pragma unroll 1
+    for (int i = 0; i < N; ++i) {
+      const int t = at(i);
+      sum[i][threadIdx.x] += t >= t0 + kSpan ? all : t > t0 ? until[t - t0] : 0;
+    }
+    __syncthreads();
+  }
+}
+
+// kpos[k[i]] of a workgroup's boundary entries k[i] <= e_bd, k_first to k_last: the kept entries of the tiles before, of the words
 // before in the tile, of the word's lower bits.
-template <int N>
-__device__ __forceinline__ void kept_before(const BuildArgs &a, int64_t k_first, int (&k)[N]) {
+template <int N, bool TOGETHER>
+__device__ __forceinline__ void kept_before(const BuildArgs &a, int64_t k_first, int64_t k_last, int (&k)[N]) {
   const int64_t e_bd = a.bd.e_bd;
   const int first = (int)min(k_first / kScanTile, (int64_t)a.bd_tiles - 1);
+  __shared__ int between[TOGETHER ? N : 1][kBdThreads];
+  if constexpr (TOGETHER)
+    tiles_between<N>(a, first, (int)(min(k_last, e_bd - 1) / kScanTile), [&](int i) { return (int)(min((int64_t)k[i], e_bd - 1) / kScanTile); }, between);
   unsigned long long mask[N];
   int word[N];
 #pragma unroll
@@ -206,12 +242,23 @@ __device__ __forceinline__ void kept_before(const BuildArgs &a, int64_t k_first,
   for (int i = 0; i < N; ++i) {
     const int64_t at = min((int64_t)k[i], e_bd - 1);
     int sum = before[0] + word[i];
+    if constexpr (TOGETHER) sum += between[i][threadIdx.x];
+    else
 #pragma unroll 4
-    for (int t = first; t < (int)(at / kScanTile); ++t) sum += a.bd.sums[t];
+      for (int t = first; t < (int)(at / kScanTile); ++t) sum += a.bd.sums[t];
     // (bits past the last entry are clear)
     const int bit = (int)(at & 63);
     k[i] = sum + __popcll(mask[i] & ((1ull << bit) - 1ull)) + (k[i] > at ? (int)((mask[i] >> bit) & 1ull) : 0);
   }
+}
+// A workgroup's entries lie in a tile or a few, and a thread adds up the tiles between the first one and its own by itself.  Where boundary
+// entries far outnumber rows and inner entries they lie in thousands of tiles: there the workgroup adds them up together (2000 rows of
+// 4000 and of 16000 boundary entries, us: 199 -> 33 and 859 -> 142).
+constexpr int kTilesAlone = 16;
+template <int N>
+__device__ __forceinline__ void kept_before(const BuildArgs &a, int64_t k_first, int64_t k_last, int (&k)[N]) {
+  if (k_last - k_first <= kTilesAlone * kScanTile) kept_before<N, false>(a, k_first, k_last, k);
+  else kept_before<N, true>(a, k_first, k_last, k);
 }
 
 // Rows of the kept boundary nodes in the transposed CSR: kept node r (boundary node b =
@@ -267,7 +314,7 @@ __device__ __forceinline__ void inner_entries(const BuildArgs &a, int block) {
     c[i] = a.in_col[j];
     k[i] = a.in_bdp[j];
   }
-  if (a.bd.e_bd > 0) kept_before(a, a.in_bdp[tile0], k);
+  if (a.bd.e_bd > 0) kept_before(a, a.in_bdp[tile0], a.in_bdp[min(tile0 + kEntryTile, a.e_in) - 1], k);
 #pragma unroll
   for (int i = 0; i < kEntryPasses; ++i)
     if (j0 + i * kBdThreads < a.e_in) a.col_idx[j0 + i * kBdThreads + k[i]] = c[i];
@@ -282,7 +329,7 @@ __device__ __forceinline__ void row_starts(const BuildArgs &a, int block) {
     r[i] = a.inner_ptr[v];
     k[i] = a.bd_ptr[v];
   }
-  if (a.bd.e_bd > 0) kept_before(a, a.bd_ptr[v0], k);
+  if (a.bd.e_bd > 0) kept_before(a, a.bd_ptr[v0], a.bd_ptr[min(v0 + kEntryTile - 1, a.n_in)], k);
 #pragma unroll
   for (int i = 0; i < kEntryPasses; ++i) {
     const int v = v0 + i * kBdThreads + (int)threadIdx.x;
@@ -294,7 +341,8 @@ __device__ __forceinline__ void row_starts(const BuildArgs &a, int block) {
 // Everything at once: what one part needs of another, the places of the entries, it counts again from the keep flags.  With the
 // boundary entries and their places (kpos) in a launch before that of the inner entries, the two and this one, us: 9570 rows beside 23300
 // boundary nodes 11.7 -> 6.3, 20011 beside 30011 14.6 -> 9.1, 29125 beside 197758 45.4 -> 37.1, 306250 beside 746157 53.0 -> 46.8, 578125
-// beside 3.1 M 68.0 -> 64.4.
+// beside 3.1 M 68.0 -> 64.4.  Every workgroup adds up the counts of all tiles before its own, which grows with the square of the partition and is not
+// felt yet where a device is full: 63 M inner entries and 45 M boundary entries 610 -> 500, 75 M 986 -> 747.
 __global__ void __launch_bounds__(kBdThreads) build_kernel(const BuildArgs a) {
   int block = blockIdx.x;
   if (block < a.list_blocks) return kept_rows_fill(a, block, a.list_blocks);
