@@ -293,7 +293,7 @@ def test_input_gradient_may_overwrite_what_it_came_from(kind, shared, d_out):
 
 
 @pytest.mark.parametrize("kind", [0, 1], ids=["gcn", "sage"])
-@pytest.mark.parametrize("d_in,d_out", [(64, 33), (64, 66), (36, 98), (64, 129), (16, 1)])
+@pytest.mark.parametrize("d_in,d_out", [(64, 33), (64, 66), (36, 98), (64, 129), (16, 1), (130, 33), (144, 47), (144, 172), (301, 9)])
 def test_dropout_of_few_rows_is_that_of_many(d_in, d_out, kind):
     """An element's draw depends on its row, column, layer and epoch alone, and its sum on nothing but its terms: the same
     rows give the same bits whatever tiles the number of rows leads to."""
