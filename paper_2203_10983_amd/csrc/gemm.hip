@@ -262,7 +262,7 @@ __global__ void __launch_bounds__(256, R * NC > 8 || NC > 6 ? 3 : 4) gemm_rows_k
 #pragma unroll
               for (int e = 0; e < 4; ++e) v[e] *= a;
               const bool in = row < end && left > 0;
-              if (in && nonfinite_seed(0.f, v) != 0.f) {
+              if (in && (nonfinite_seed(0.f, v) != 0.f || any_tiny(v))) {
                 again |= 1u << ((r * NP + c) * W + h);
                 continue;
               }

@@ -13,7 +13,8 @@
 //   dZ W^T, depth  64: 4.7e-8 (1.4e-7, 0.9e-7)   128: 5.7e-8 (2.0e-7, 1.5e-7)   512: 8.9e-8 (4.1e-7, 3.4e-7)
 //   A^T dZ, 60000 rows of 128 x 128: 1.0e-7 (1.9e-7, 2.7e-7)   300000: 1.2e-7 (3.4e-7, 3.2e-7)
 // The additions are free in gemm_rows; in gemm_tn they cost 4 to 8 % on tiles of 128 x 128.
-// Below 2^-110 the lo piece, then the mid piece are subnormal: such an operand is held to an absolute 2^-134.
+// Below 2^-110 the lo piece, then the mid piece are subnormal: such an operand is held to an absolute 2^-134.  Forward results that may
+// suffer from it are formed once more without a split (any_tiny).
 //
 // v_mfma_f32_16x16x32_bf16 runs at sixteen times the rate of the fp32 instruction, so six of them
 // take 6/16 of its time.  Operands that are not finite, or round to an infinite hi (above 3.389e38), have no split:
@@ -108,6 +109,15 @@ __device__ __forceinline__ float nonfinite_seed(float z, const f32x4 &v) {  // z
 #pragma unroll
   for (int e = 0; e < 4; ++e) z = fmaf(v[e], 0.f, z);
   return z;
+}
+// Any of the values other than zero and below 2^-64?  Operands below 2^-110 have pieces below the bf16 range and are held to an absolute
+// 2^-134.  A result that feels it is small itself, unless it has operands above 2^30 on the other side (2^-134 of 1024 terms against 2^-24 of
+// 2^-64).  Dead rows and columns are exactly zero and pass.  Looking costs nothing that could be measured (578125 rows, 256 -> 172).
+__device__ __forceinline__ bool any_tiny(const f32x4 &v) {
+  unsigned least = ~0u;  // of twice the bits less one: zeros count as the largest
+#pragma unroll
+  for (int e = 0; e < 4; ++e) least = min(least, (__float_as_uint(v[e]) << 1) - 1u);
+  return least < (__float_as_uint(0x1p-64f) << 1) - 1u;
 }
 __device__ __forceinline__ bool is_finite(float x) { return fabsf(x) <= 3.40282347e38f; }
 

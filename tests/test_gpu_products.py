@@ -183,6 +183,30 @@ def test_infinities_and_nan_in_forward_products(d_in, d_out, kind, relu):
     ctx.close()
 
 
+@pytest.mark.parametrize("x,w", [(1e-33, 1.0), (1e-36, 1.0), (1.0, 1e-36), (1e-38, 1e4), (1e-30, 1e-4)])
+@pytest.mark.parametrize("kind", [0, 1], ids=["gcn", "sage"])
+@pytest.mark.parametrize("d_in,d_out", [(144, 20), (130, 49), (301, 172)], ids=lambda v: str(v))
+def test_forward_products_of_small_operands(d_in, d_out, kind, x, w):
+    """Operands whose last bits lie below the range of bf16 give what sums in fp32 give: each element within a rounding of its terms'
+    size at every step, and of the smallest number there is."""
+    import torch
+    n = 300
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(d_in)
+    X, W = x * torch.randn(n, d_in, device="cuda:0", generator=gen), w * torch.randn((1 + kind) * d_in, d_out, device="cuda:0", generator=gen)
+    X[7], W[:, 3] = 0.0, 0.0
+    ctx, keep = _layer(n, d_in, d_out, kind)
+    A, H = torch.empty(n, d_in, device="cuda:0"), torch.full((n, d_out), 7.0, device="cuda:0")
+    ctx.gcn_layer_fwd(1, 0.5, X, None, W, A, H, False)
+    torch.cuda.synchronize()
+    Z = torch.cat([A, X], 1) if kind else A
+    ref, size = Z.double() @ W.double(), Z.double().abs() @ W.double().abs()
+    k = Z.shape[1]
+    assert ((H.double() - ref).abs() <= 4.0 * (2.0 ** -24 * (1 + k ** 0.5) * size + 2.0 ** -149 * k)).all()
+    assert bool((H[7] == 0).all()) and bool((H[:, 3] == 0).all()) and int((H != 0).sum()) == (n - 1) * (d_out - 1)
+    ctx.close()
+
+
 def test_infinities_in_a_product_before_the_aggregate():
     """A layer that multiplies first reads kept boundary rows by record, scaled on their way in, and pads its odd width."""
     import torch
