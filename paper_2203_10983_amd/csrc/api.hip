@@ -168,8 +168,12 @@ bool tile_layer_bwd(const bns_ctx *ctx, int layer, int64_t rows) {
 // The forward product of `layer` by splits (gemm.hip) instead of the fp32 chain?  It is faster and closer to the exact sums (2-norm of
 // the error, normal operands, beside the chain: depth 128 0.6e-7 and 2.0e-7, 256 0.7 and 2.9, 512 0.9 and 4.1, 602 1.0 and 4.4).
 // Only the last layer's: sums in another order switch hidden units within rounding of zero, and one such unit of a node
-// with few neighbours is a visible part of the gradient of the boundary nodes next to it.  A layer that may run as one launch has the
-// bits of the chain there.  Up to 64 columns the stores bound either.  Products in a step, chain and splits, us: 578125 rows, 256 -> 172 542 and 338,
+// with few neighbours is a visible part of the gradient of the boundary nodes next to it.  Within a step no unit hangs on the logits; their last
+// bits reach the weights through the gradients, and there they do what those of the weight gradients' sums do: a unit of a later epoch may
+// switch (ten epochs from the same start, by splits and by the chain, largest difference of a gradient over its rms: 306250 rows
+// 3e-6, 89625 rows with 512 hidden units 5e-6 up to the second epoch, 0.03 in the fourth).  A layer that may run as one launch has the
+// bits of the chain there.  Up to a depth (d_in, also where the mean aggregator's product is twice as deep) of 64 the stores bound either.
+// Products in a step, chain and splits, us: 578125 rows, 256 -> 172 542 and 338,
 // 89625 rows, 1024 -> 100 218 and 117, 110645 of 512 -> 100 151 and 87, 226887 of 256 -> 41 78 and 62.
 bool fwd_by_splits(const bns_ctx *ctx, int layer) {
   return layer + 1 == (int)ctx->dims.size() && ctx->dims[layer - 1] > 64 && !tile_layer(ctx, layer);

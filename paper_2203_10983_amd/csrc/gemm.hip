@@ -29,6 +29,8 @@
 // its own: where the last columns and rows, and rows by index, had such branches, the reads were waited for one by one.  Without
 // them, us: A^T dZ of 197758 rows by index x 602 x 256 547 -> 400, 306250 x 128 x 47 99 -> 62, 128 x 128 145 -> 117, 578125 x 128 x 172
 // 213 -> 170, 9570 rows of three layers 20 -> 15; dZ W^T of 578125 x 172 x 128 190 -> 173, 306250 x 47 x 128 102 -> 94.
+// It takes registers: the 128 x 128 tiles of A^T dZ and the forward products of 32 rows by 128 columns have three on the stack, which they
+// did not before (89625 x 512 x 512 265 -> 236 all the same).
 #include <algorithm>
 #include <type_traits>
 

@@ -128,7 +128,7 @@ struct SegPlan {
   int2 *seg_unit;     // int2[n_seg]     row of each segment and its partial-sum slot (-1: the row's only segment)
   int32_t *part_ptr;  // int32[n_rows+1] first partial-sum slot of each multi-segment row
   int32_t *mrow;      // int32[n_multi]  rows with more than one segment
-  int2 *part_unit;    // int2[n_part]    row of each partial-sum slot, slot
+  int2 *part_unit;    // int2[n_part]    row of each partial-sum slot, slot (set-up: what order is made from)
   int2 *order;        // int2[n_seg]     the units as launches take them: the n_part of long rows by column, then the other rows
   int32_t n_seg, n_part, n_multi;  // host copies of the totals
   int32_t max_seg;                 // segments of the longest row
@@ -137,7 +137,8 @@ struct SegPlan {
 inline int64_t seg_max_segments(int64_t rows, int64_t nnz) { return rows + nnz / kSegLen + 1; }
 inline int64_t seg_max_parts(int64_t nnz) { return 2 * (nnz / kSegLen) + 2; }
 inline int64_t seg_max_multi(int64_t nnz) { return nnz / kSegLen + 1; }
-// Fills *plan (its arrays must be allocated to the bounds above) and waits for the stream.
+// Fills *plan (its arrays must be allocated to the bounds above).  Waits for the stream before the totals are read; `order` and the use of counts
+// and tile_sums are complete in stream order only, after the call returns.
 // tmp_a: scratch int32[n_rows], tmp_b: scratch int32[n_rows+1], counts: scratch int32[seg_max_parts(nnz)].  nnz: entries of the
 // pattern, col: their columns, below n_cols.
 hipError_t build_seg_plan(int32_t n_rows, int64_t nnz, const int32_t *row_ptr, const int32_t *col, int64_t n_cols, SegPlan *plan,

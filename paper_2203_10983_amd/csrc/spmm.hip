@@ -379,7 +379,7 @@ static hipError_t launch_spmm_vec(const SpmmArgs &a_in, int64_t extra_rows, bool
   const bool dealt = extra_rows >= 0 && avg_len >= (a.d > 64 ? 13 : 24) && (n_units << ls) >= (a.d > 32 ? 16384 : 24576) &&
                      (a.d > 32 || extra_rows <= n_units);
   // Eight at a time (short_rows) where they are not dealt, every wavefront has so many to go on to, and they are no fewer than the
-  // segments, whose gather has a register or two less then with 16 lanes to a row.  Us, one at a time -> eight: 578125 rows beside 3.1 M boundary
+  // segments, whose gather has two or three registers less then with 16 lanes to a row (8 and 12 bytes of scratch).  Us, one at a time -> eight: 578125 rows beside 3.1 M boundary
   // rows of 1.4 entries, 128 floats 1758 -> 1287, 66 floats 1496 -> 962, 16 floats 1392 -> 643, beside 1.54 M 1169 -> 1045, beside 308000 787 -> 787;
   // 89625 beside 211000, 512 floats 610 -> 517, 130 floats 198 -> 180; 306250 beside 746000, 48 floats 546 -> 499; beside fewer than segments 578125 beside
   // 154000, 64 floats 466 -> 503.  Dealt and by eight, 306250 beside 746000, 128 floats 964 -> 984, 29125 beside 197758, 256 floats 690 -> 667: left.
@@ -407,8 +407,8 @@ static hipError_t launch_spmm_vec(const SpmmArgs &a_in, int64_t extra_rows, bool
     // workgroups (whole launches, fixed and in turn, us): 6000 rows of 250 entries and 512 floats 221 -> 215, 256 floats
     // 140 -> 138; 25000 rows of 75 entries 405 -> 397, 248 -> 240; 12000 rows of 75 192 -> 193, 121 -> 123; 50000 rows of 19
     // 367 -> 370, 226 -> 223; 6000 rows of 75 104 -> 108.
-    const bool in_turn = (int64_t)avg_len * a.n_split >= 1250000;
-    a.head.turn_share = in_turn ? (uint32_t)(((uint64_t)1 << (32 + ls)) / each) : 0;  // each > 2^ls then
+    const bool in_turn = (int64_t)avg_len * a.n_split >= 1250000 && each > (1u << ls);  // (there may be a handful of long rows alone)
+    a.head.turn_share = in_turn ? (uint32_t)(((uint64_t)1 << (32 + ls)) / each) : 0;
   }
   if (a.d_store != a.d) {  // padded sources, dense narrower outputs: d < 128, four floats per lane
     if constexpr (VEC == 4 && !RAGGED) {
