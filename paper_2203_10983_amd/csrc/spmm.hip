@@ -552,8 +552,8 @@ seg_fill_kernel(int32_t n_rows, const int32_t *__restrict__ seg_ptr, const int32
 // the segments in flight together share their feature rows while these are in the L2s; in the order of the rows each part of the columns
 // came by again with every row.  The sums and their order are what they are in any order of the units.  Us, by row -> by column:
 // 29125 rows of 340 entries, 256 floats in slices of 64 500 -> 422, beside 197758 boundary nodes all kept 842 -> 650, transposed
-// 500 -> 434 and 677 -> 640; transposed 306250 rows of 45, 128 floats 763 -> 695, 578125 of 21 815 -> 789; the long rows alone, in
-// slices of 32, 251 -> 172 and 252 -> 184.  By the column of the first entry 1 to 12 % slower (204 -> 230 for the long rows of the 306250, 100
+// 500 -> 434 and 677 -> 640; transposed 306250 rows of 45, 128 floats 763 -> 695, 578125 of 21 815 -> 789; the long rows alone, while they
+// went in slices of 32, 251 -> 172 and 252 -> 184 (the slices they go in now: spmm_long_kernel).  By the column of the first entry 1 to 12 % slower (204 -> 230 for the long rows of the 306250, 100
 // floats).  With an eighth of the columns to each XCD, so that a line is in one L2 alone, the long rows are no faster (175 and 193) and the
 // XCDs that have the boundary columns end last (650 -> 725).  Shorter segments are narrower, but their partial sums eat that up (transposed,
 // 128 entries 434 + 12 -> 418 + 22 and 789 + 9 -> 762 + 17, 64 entries 460 + 41).
