@@ -161,7 +161,7 @@ def run_workload(cfg, p, kind, steps, warmup, dropout=0.0, extras=False, cpu_bas
     # with the aggregate: it also writes H_out and reads W there, and A is not read back), or update
     # first (the aggregate then runs at the output width)
     fw = {l: dims[l] if l in first else dims[l - 1] for l in range(1, L + 1)}        # forward aggregate width
-    bw = {l: dims[l] if (kind == 0 and dims[l] < dims[l - 1]) else dims[l - 1] for l in range(2, L + 1)}
+    bw = {l: min(dims[l], dims[l - 1]) for l in range(2, L + 1)}
 
     def fwd_alg(l, cached=False):
         if cached:      # the cached inner sum and the kept boundary rows instead of all neighbours

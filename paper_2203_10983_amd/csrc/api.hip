@@ -42,7 +42,7 @@ struct Layout {
   uint64_t *ballots;
   uint64_t *bd_mask;   // keep flags of the boundary entries, their number per tile and per tile before each word
   int32_t *bd_sums, *bd_before;
-  // boundary rows at the output width: Hu of GCN layers that shrink (their gradient), Hu2 of update-first layers
+  // boundary rows at the output width: Hu of layers that shrink (their gradient), Hu2 of update-first layers
   float *Hu, *Hu2, *G0, *G1, *G2, *loss_partials;
   int2 *halo_rec;  // per kept boundary node: (boundary index, weight) for the aggregates that read the rows in place
   // weight of every static entry with an inner column: forward (GCN only), transposed inner block, boundary nodes' lists
@@ -165,6 +165,15 @@ bool tile_layer_bwd(const bns_ctx *ctx, int layer, int64_t rows) {
          tile_layer_bwd_supported(gather_stride(ctx->dims[layer - 1], ctx->dims[layer]), ctx->dims[layer - 1], ctx->layer_kind == 1);
 }
 
+// The backward pass of a mean-aggregator layer that shrinks: the transposed aggregate at the output width, then
+// [mean^T dZ | dZ] [W_n ; W_s]^T?  (Else the products first, at twice the input width.)  Steps, us, products first / this: last layers 128 -> 47 on 306250 rows
+// of 45 entries 4512 / 4172, 512 -> 100 on 89625 of 21 7426 / 7133; hidden layers of equal widths besides: 128 on 306250 rows the same, 512 on 89625 1.5 %
+// and 128 on 578125 beside 308000 kept boundary rows 1 % slower (the boundary rows' product), hence an eighth narrower.  Not on partitions that may take the
+// one-launch form, whose weights are packed as one matrix.
+bool sage_gathers_first(const bns_ctx *ctx, int layer) {
+  return ctx->layer_kind == 1 && ctx->dims[layer] * 8 <= ctx->dims[layer - 1] * 7 && ctx->part.n_in > kTileBwdMaxRows;
+}
+
 // The forward product of `layer` by splits (gemm.hip) instead of the fp32 chain?  It is faster and closer to the exact sums (2-norm of
 // the error, normal operands, beside the chain: depth 128 0.6e-7 and 2.0e-7, 256 0.7 and 2.9, 512 0.9 and 4.1, 602 1.0 and 4.4).
 // Only the last layer's: sums in another order switch hidden units within rounding of zero, and one such unit of a node
@@ -212,10 +221,10 @@ bool fits_int32(const bns_partition_desc *p, const bns_model_desc *m) {
 
 size_t carve(Carver &c, const bns_partition_desc *p, const bns_model_desc *m, Layout *out) {
   const size_t n_in = p->n_in, B = p->n_halo, L = m->n_layers;
-  size_t d_max = 0, d_out_max = 0, d_first_max = 0;  // d_out_max: of the GCN layers that shrink
+  size_t d_max = 0, d_out_max = 0, d_first_max = 0;  // d_out_max: of the layers that shrink
   for (size_t l = 0; l <= L; ++l) d_max = std::max<size_t>(d_max, m->dims[l]);
   for (size_t l = 0; l < L; ++l) {
-    if (m->layer_kind == 0 && m->dims[l + 1] < m->dims[l]) d_out_max = std::max<size_t>(d_out_max, m->dims[l + 1]);
+    if (m->dims[l + 1] < m->dims[l]) d_out_max = std::max<size_t>(d_out_max, m->dims[l + 1]);
     if (update_first_shape(m->layer_kind, m->dims[l], m->dims[l + 1]))
       d_first_max = std::max<size_t>(d_first_max, gather_stride(m->dims[l], m->dims[l + 1]));
   }
@@ -516,7 +525,7 @@ bns_status layer_fwd_impl(bns_ctx *ctx, int layer, double p, const float *H_in, 
 bool pads_gradient(const bns_ctx *ctx, int layer, double p, bool update_first, bool input_gradient) {
   const int d_in = ctx->dims[layer - 1], d_out = ctx->dims[layer];
   if (gather_stride(d_in, d_out) == d_out) return false;
-  return update_first || ((ctx->layer_kind == 0 || tile_layer_bwd(ctx, layer, ctx->part.n_in + (int64_t)expected_kept(ctx, p))) && input_gradient && d_out < d_in);
+  return update_first || ((ctx->layer_kind == 0 || sage_gathers_first(ctx, layer) || tile_layer_bwd(ctx, layer, ctx->part.n_in + (int64_t)expected_kept(ctx, p))) && input_gradient && d_out < d_in);
 }
 
 // The weight gradients of several layers, to be run together.
@@ -538,23 +547,25 @@ bns_status run_batch(bns_ctx *ctx, TnBatch *batch, const TnLoss &loss, hipStream
 // halo_first (nullable): the boundary features of an update-first layer (A_saved does not hold
 // the aggregate then); the weight gradient is [H_in ; Hu]^T (P^T dZ) instead of A^T dZ.
 // dz_padded: G2 holds dZ with padded rows already (pads_gradient).
+// sage_first: the weights are packed for sage_gathers_first, and neither dH_in nor dhalo shares memory with dZ or W.
 // batch (nullable): collects the weight gradient, to be run when the chain of the layers is through; without one it is
 // run before dH_in and dhalo are written, which may then share memory with dZ, A_saved or H_in.
 bns_status layer_bwd_impl(bns_ctx *ctx, int layer, double p, const float *dZ, const float *A_saved,
                           const float *H_in, const float *W, float *dW, float *dH_in, float *dhalo, const float *mask_src,
                           bool update_first, const float *halo_first, float *W_step, float lr, bool dz_padded,
-                          TnBatch *batch, hipStream_t s) {
+                          bool sage_first, TnBatch *batch, hipStream_t s) {
   const int n_in = ctx->part.n_in, B = ctx->part.n_halo;
   const int d_in = ctx->dims[layer - 1], d_out = ctx->dims[layer];
   const char *Wb = ctx->ws.Wb[layer];
   // C = alpha * G W^T for the inner rows of G at the output width; C2: the mean aggregator's second half; G_more: the
-  // rows of the kept boundary nodes
-  auto gemm_wt = [&](const float *G, float *C, float *C2, const float *mask, float alpha, const float *G_more, float *C_more) {
+  // rows of the kept boundary nodes; G2: times the second half of W, added to C
+  auto gemm_wt = [&](const float *G, float *C, float *C2, const float *mask, float alpha, const float *G_more, float *C_more, const float *G2 = nullptr) {
     RowsGemm g{};
     g.M = n_in;
     g.N = C2 ? 2 * d_in : d_in;
     g.K = g.lda = d_out;
     g.A = G;
+    g.A2 = G2;
     g.W = W;
     g.Bp = Wb;
     g.C = C;
@@ -655,7 +666,7 @@ bns_status layer_bwd_impl(bns_ctx *ctx, int layer, double p, const float *dZ, co
       return BNS_OK;
     }
   }
-  if (ctx->layer_kind == 1) {
+  if (ctx->layer_kind == 1 && !sage_first) {
     if (dH_in) {
       {
         PhaseTimer t(ctx, BNS_PHASE_GEMM_DA, s);  // dZ [W_n ; W_s]^T in one product, split into the two halves
@@ -671,7 +682,9 @@ bns_status layer_bwd_impl(bns_ctx *ctx, int layer, double p, const float *dZ, co
     return BNS_OK;
   }
   if (dH_in && d_out < d_in) {
-    // (P^T dZ) W^T instead of P^T (dZ W^T): the transposed aggregate runs at the narrower width
+    // (P^T dZ) W^T instead of P^T (dZ W^T): the transposed aggregate runs at the narrower width (mean aggregator: and half as much is
+    // written and read between the launches)
+    const bool sage = ctx->layer_kind == 1;
     float *G_in = ctx->ws.G1, *G_halo = dhalo && B > 0 ? ctx->ws.Hu : nullptr;
     {
       PhaseTimer t(ctx, BNS_PHASE_SPMM_BWD, s);
@@ -682,12 +695,12 @@ bns_status layer_bwd_impl(bns_ctx *ctx, int layer, double p, const float *dZ, co
         dZ_g = ctx->ws.G2;
       }
       BNS_TRY("spmm_bwd", spmm_bwd(ctx->ws.plan_b, n_in, B, ld, ctx->cur_t_row_ptr, ctx->cur_t_col_idx,
-                                   ctx->cur_kept, ctx->cur_n_kept, ctx->ws.w_bwd, ctx->ws.w_halo, ctx->part.halo_ptr, ctx->ws.dis_in,
-                                   ctx->ws.dis_halo, halo_scale(p), dZ_g, nullptr, nullptr, false,
+                                   ctx->cur_kept, ctx->cur_n_kept, ctx->ws.w_bwd, ctx->ws.w_halo, ctx->part.halo_ptr, sage ? nullptr : ctx->ws.dis_in,
+                                   sage ? nullptr : ctx->ws.dis_halo, halo_scale(p), dZ_g, nullptr, nullptr, sage,
                                    transposed_len(ctx, p, G_halo), ctx->ws.spmm_partials, G_in, G_halo, expected_kept(ctx, p), s, d_out));
     }
     PhaseTimer t(ctx, BNS_PHASE_GEMM_DA, s);
-    BNS_TRY("gemm_rows(dH)", gemm_wt(G_in, dH_in, nullptr, mask_src, ms, G_halo, dhalo));
+    BNS_TRY("gemm_rows(dH)", gemm_wt(G_in, dH_in, nullptr, mask_src, ms, G_halo, dhalo, sage ? dZ : nullptr));
   } else if (dH_in) {
     {
       PhaseTimer t(ctx, BNS_PHASE_GEMM_DA, s);
@@ -703,7 +716,8 @@ bns_status layer_bwd_impl(bns_ctx *ctx, int layer, double p, const float *dZ, co
 }
 
 // Adds the weights of layer l to the packing jobs, for the forward product and / or for dZ W^T.
-void add_pack_jobs(const bns_ctx *ctx, int l, const float *W, bool fwd, bool bwd, PackJobs *jobs) {
+// halves: the layer's backward pass is that of sage_gathers_first.
+void add_pack_jobs(const bns_ctx *ctx, int l, const float *W, bool fwd, bool bwd, bool halves, PackJobs *jobs) {
   const int32_t kw = ctx->layer_kind == 1 ? 2 : 1, d_in = ctx->dims[l - 1], d_out = ctx->dims[l];
   const size_t half = (size_t)d_in * d_out;
   auto add = [&](const float *w, char *out, int32_t K, int32_t N, bool split, bool of_fwd = false) {
@@ -722,7 +736,7 @@ void add_pack_jobs(const bns_ctx *ctx, int l, const float *W, bool fwd, bool bwd
     }
   }
   if (bwd) {
-    if (kw == 2 && d_in % 4 != 0) {  // the two halves apart (see gemm_wt)
+    if (kw == 2 && (d_in % 4 != 0 || halves)) {  // the two halves apart (see gemm_wt)
       add(W, ctx->ws.Wb[l], d_out, d_in, true);
       add(W + half, ctx->ws.Wb[l] + packed_bytes(d_out, d_in), d_out, d_in, true);
     } else {
@@ -915,7 +929,7 @@ bns_status bns_gcn_layer_fwd(bns_ctx *ctx, int32_t layer, double p, const float 
   if (no_subgraph(ctx)) return fail(ctx, BNS_EINVAL, "the captured step has not run: there is no sampled subgraph yet");
   hipStream_t s = static_cast<hipStream_t>(stream);
   PackJobs jobs;
-  add_pack_jobs(ctx, layer, W, true, false, &jobs);
+  add_pack_jobs(ctx, layer, W, true, false, false, &jobs);
   return layer_fwd_impl(ctx, layer, p, H_in, halo_h, W, A_saved, H_out, relu != 0, false, &jobs, nullptr, s);
 }
 
@@ -931,18 +945,22 @@ bns_status bns_gcn_layer_bwd(bns_ctx *ctx, int32_t layer, double p, const float 
   if (!ctx->cur_t_row_ptr) return fail(ctx, BNS_EINVAL, "bns_build_sampled_csr has not been called");
   if (no_subgraph(ctx)) return fail(ctx, BNS_EINVAL, "the captured step has not run: there is no sampled subgraph yet");
   hipStream_t s = static_cast<hipStream_t>(stream);
-  PackJobs jobs;
-  if (dH_in) add_pack_jobs(ctx, layer, W, false, true, &jobs);
-  // the masked gradient, and where the aggregate gathers it in padded rows (layer_bwd_impl) those
-  const int d_out = ctx->dims[layer];
-  const int64_t rows = ctx->part.n_in + (dhalo ? (int64_t)expected_kept(ctx, p) : 0);
-  const bool pad = dH_in && gather_stride(ctx->dims[layer - 1], d_out) != d_out && d_out < ctx->dims[layer - 1] &&
-                   (ctx->layer_kind == 0 || tile_layer_bwd(ctx, layer, rows));
+  const int d_in = ctx->dims[layer - 1], d_out = ctx->dims[layer];
   const float *dZ = H_out ? ctx->ws.G0 : dH_out;
+  // (the product reads dZ while it writes the two results)
+  const auto meets = [&](const float *out, size_t n) { return overlap(out, n, dZ, (size_t)ctx->part.n_in * d_out) || overlap(out, n, W, (size_t)2 * d_in * d_out); };
+  const bool sage_first = dH_in && sage_gathers_first(ctx, layer) && !meets(dH_in, (size_t)ctx->part.n_in * d_in) &&
+                          !(dhalo && meets(dhalo, (size_t)ctx->part.n_halo * d_in));
+  PackJobs jobs;
+  if (dH_in) add_pack_jobs(ctx, layer, W, false, true, sage_first, &jobs);
+  // the masked gradient, and where the aggregate gathers it in padded rows (layer_bwd_impl) those
+  const int64_t rows = ctx->part.n_in + (dhalo ? (int64_t)expected_kept(ctx, p) : 0);
+  const bool pad = dH_in && gather_stride(d_in, d_out) != d_out && d_out < d_in &&
+                   (ctx->layer_kind == 0 || sage_first || tile_layer_bwd(ctx, layer, rows));
   BNS_TRY("relu_mask", relu_mask(ctx->part.n_in, d_out, dH_out, H_out, mask_scale_of(ctx), ctx->ws.G0,
-                                 gather_stride(ctx->dims[layer - 1], d_out), pad ? ctx->ws.G2 : nullptr, jobs, s));
+                                 gather_stride(d_in, d_out), pad ? ctx->ws.G2 : nullptr, jobs, s));
   return layer_bwd_impl(ctx, layer, p, dZ, A_saved, H_in, W, dW, dH_in, dhalo, nullptr, false, nullptr, nullptr, 0.f, pad,
-                        nullptr, s);
+                        sage_first, nullptr, s);
 }
 
 // epoch_dev (nullable): the epoch index is read from there instead, and counted up by the last launch.
@@ -963,7 +981,7 @@ static bns_status train_step_impl(bns_ctx *ctx, uint64_t seed, uint32_t epoch, u
   // the weights of up to kPackLayers layers are packed beside the sampling, those of deeper models before it
   PackJobs jobs;
   for (int l = L; l >= 1; --l) {
-    add_pack_jobs(ctx, l, W[l - 1], true, l > 1, &jobs);
+    add_pack_jobs(ctx, l, W[l - 1], true, l > 1, sage_gathers_first(ctx, l), &jobs);
     if (l > 1 && (l - 1) % kPackLayers == 0) {
       BNS_TRY("pack_weights", pack_weights(jobs, s));
       jobs = PackJobs{};
@@ -1017,7 +1035,7 @@ static bns_status train_step_impl(bns_ctx *ctx, uint64_t seed, uint32_t epoch, u
                         l > 1 ? w.dZ[l - 1] : nullptr, dh,
                         l > 1 ? w.H[l - 1] : nullptr, layer_plan(ctx, l, X) == BNS_LAYER_UPDATE_FIRST,
                         ctx->part.n_halo > 0 ? halo_h[l - 1] : nullptr, W[l - 1], update_apart ? 0.f : lr, l == L && pad_last,
-                        &batch, s);
+                        sage_gathers_first(ctx, l), &batch, s);
     if (st != BNS_OK) return st;
     if (l == 1 || batch.full()) {
       st = run_batch(ctx, &batch, l == 1 ? loss_sum : TnLoss{}, s);

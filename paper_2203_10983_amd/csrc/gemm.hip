@@ -60,8 +60,9 @@ struct RowsArgs {
   int T, S, nblk;  // column tiles, depth steps, column blocks
 };
 
-// The last three are a forward product's: with ReLU and dropout, added to what is there, with a second set of rows by record.
-enum RowsEpilogue { kPlain, kMask, kPair, kFwd, kFwdAdd, kFwdRec };
+// kTwo: the depth of C's rows goes on in A2 (below).  The last three are a forward product's: with ReLU and dropout, added to what is there, with a
+// second set of rows by record.
+enum RowsEpilogue { kPlain, kMask, kPair, kTwo, kFwd, kFwdAdd, kFwdRec };
 
 // The value of the lane whose number differs in the last bit.
 __device__ __forceinline__ float quad_swap(float x) {
@@ -116,7 +117,9 @@ __global__ void __launch_bounds__(256, R * NC > 8 || NC > 6 ? 3 : 4) gemm_rows_k
 
   const int lane = lane_id(), wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int l16 = lane & 15, g = lane >> 4;
-  const int S = a.S;
+  // kTwo: a row of C takes the steps of A, then those of A2; a row of C_more those of A_more alone
+  auto steps_of = [&](int tl) { return EPI == kTwo && tl < n_first ? 2 * a.S : a.S; };
+  int S = steps_of(tile);
 
   f32x4 ar[R][2];
   const float *row_a[R], *row_a2[R];
@@ -137,27 +140,34 @@ __global__ void __launch_bounds__(256, R * NC > 8 || NC > 6 ? 3 : 4) gemm_rows_k
       }
       row_a[r] = A + (size_t)row * p.lda;
       if (EPI == kFwd) row_a2[r] = two ? p.A2 + (size_t)row * p.lda - p.a_split : nullptr;
+      if (EPI == kTwo) row_a2[r] = more ? row_a[r] : p.A2 + (size_t)row * p.lda;
     }
   };
-  auto load_a = [&](int s) {
+  auto step_in = [&](int s) { return EPI == kTwo && s >= a.S ? s - a.S : s; };  // of its operand
+  auto load_a = [&](int step) {
+    const int s = step_in(step);
+    const float *from[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) from[r] = EPI == kTwo && step >= a.S ? row_a2[r] : row_a[r];
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
       const int k = s * 32 + j * 16 + g * 4;
       if ((s + 1) * 32 <= p.K) {
 #pragma unroll
-        for (int r = 0; r < R; ++r) ar[r][j] = *reinterpret_cast<const f32x4u *>((EPI == kFwd && two && s * 32 + j * 16 >= p.a_split ? row_a2[r] : row_a[r]) + k);
+        for (int r = 0; r < R; ++r) ar[r][j] = *reinterpret_cast<const f32x4u *>((EPI == kFwd && two && s * 32 + j * 16 >= p.a_split ? row_a2[r] : from[r]) + k);
       } else if (p.K >= 4) {  // settle() takes what is past the end away
 #pragma unroll
-        for (int r = 0; r < R; ++r) ar[r][j] = *reinterpret_cast<const f32x4u *>(row_a[r] + piece_start(k, p.K));
+        for (int r = 0; r < R; ++r) ar[r][j] = *reinterpret_cast<const f32x4u *>(from[r] + piece_start(k, p.K));
       } else {
 #pragma unroll
         for (int r = 0; r < R; ++r)
 #pragma unroll
-          for (int e = 0; e < 4; ++e) ar[r][j][e] = k + e < p.K ? row_a[r][k + e] : 0.f;
+          for (int e = 0; e < 4; ++e) ar[r][j][e] = k + e < p.K ? from[r][k + e] : 0.f;
       }
     }
   };
-  auto settle = [&](int s) {
+  auto settle = [&](int step) {
+    const int s = step_in(step);
     if constexpr (EPI == kFwdRec)
 #pragma unroll
       for (int r = 0; r < R; ++r)
@@ -184,7 +194,7 @@ __global__ void __launch_bounds__(256, R * NC > 8 || NC > 6 ? 3 : 4) gemm_rows_k
 #pragma unroll
       for (int r = 0; r < R; ++r) acc[c][r] = f32x4{0.f, 0.f, 0.f, 0.f};
   };
-  const bool stay = S == 1;  // the weights of a single step stay in LDS for all tiles
+  const bool stay = EPI != kTwo && a.S == 1;  // the weights of a single step stay in LDS for all tiles
   set_rows(tile);
   load_b(0, 0);
   load_a(0);
@@ -273,7 +283,7 @@ __global__ void __launch_bounds__(256, R * NC > 8 || NC > 6 ? 3 : 4) gemm_rows_k
             }
             if (row >= end || left <= 0) continue;
             nonfinite = nonfinite_seed(nonfinite, v);
-            if (EPI == kMask && !more) {
+            if ((EPI == kMask || (EPI == kTwo && p.mask)) && !more) {
               const float *const ms = p.mask + at;
               f32x4 m = {0.f, 0.f, 0.f, 0.f};
               if (left >= 4) m = *reinterpret_cast<const f32x4u *>(ms);
@@ -338,6 +348,15 @@ __global__ void __launch_bounds__(256, R * NC > 8 || NC > 6 ? 3 : 4) gemm_rows_k
 #pragma unroll
             for (int e = 0; e < 4; ++e) x[e] = fmaf(y, w[(e < left ? (size_t)e * p.K : 0) + k], x[e]);
           }
+          if (EPI == kTwo && !more) {
+            const float *const w2 = w + (size_t)p.N * p.K;
+#pragma unroll 1
+            for (int k = 0; k < p.K; ++k) {
+              const float y = p.A2[(size_t)row * p.K + k];
+#pragma unroll
+              for (int e = 0; e < 4; ++e) x[e] = fmaf(y, w2[(e < left ? (size_t)e * p.K : 0) + k], x[e]);
+            }
+          }
 #pragma unroll
           for (int e = 0; e < 4; ++e)
             if (e < left && !is_finite(d[e])) d[e] = x[e] * scale;
@@ -346,6 +365,7 @@ __global__ void __launch_bounds__(256, R * NC > 8 || NC > 6 ? 3 : 4) gemm_rows_k
       if (ntile >= n_tiles) break;
       clear();
       tile = ntile;
+      S = steps_of(tile);
     }
     s = ns;
   }
@@ -370,6 +390,7 @@ static void launch_rows(const RowsArgs &a, int nc, unsigned grid, hipStream_t s)
   else if (a.g.fwd && a.g.accumulate) launch_rows<R, kFwdAdd>(a, nc, grid, s);
   else if (a.g.fwd) launch_rows<R, kFwd>(a, nc, grid, s);
   else if (a.g.C2) launch_rows<R, kPair>(a, nc, grid, s);
+  else if (a.g.A2) launch_rows<R, kTwo>(a, nc, grid, s);
   else if (a.g.mask) launch_rows<R, kMask>(a, nc, grid, s);
   else launch_rows<R, kPlain>(a, nc, grid, s);
 }
@@ -381,7 +402,7 @@ hipError_t gemm_rows(const RowsGemm &g, hipStream_t s) {
   if (g.fwd ? g.C2 || g.mask || g.lda < (g.A2 ? g.a_split : g.K) || (g.A2 && (g.a_split % 16 != 0 || g.K != 2 * g.a_split)) ||
                   (g.A2 && (g.accumulate || g.rec)) || (g.rec && (g.accumulate || g.relu || !g.m2_dev)) || (g.A_more && !g.rec) ||
                   (g.pad && (g.ldc > (g.N + 3) / 4 * 4 || g.A2 || g.relu || g.accumulate))
-            : g.A2 || g.rec || g.relu || g.pad || g.accumulate || g.lda != g.K)
+            : (g.A2 && g.C2) || g.rec || g.relu || g.pad || g.accumulate || g.lda != g.K)
     return hipErrorInvalidValue;
   RowsArgs a;
   a.g = g;

@@ -265,6 +265,7 @@ hipError_t gemm_fwd_split(const RowsF32 &g, const float *W, hipStream_t s);
 // C[M,N] = alpha * A B with A [M,K], B [K,N] packed and split, from W [N,K].  At most one of: C2 (nullable): columns from c_split (a
 // multiple of 4) on go to C2, both with row stride ldc; mask (nullable, [M, ldc]): C is zeroed where mask <= 0.
 // A_more (nullable): in the same launch C_more[r] = A_more[r] B for r < *m2_dev (<= M2, about m2_expected); not with C2.
+// A2 (nullable, [M, K]; not with C2): C = alpha * (A B + A2 B2), B2 packed behind B, from the [N, K] that follow in W.
 struct RowsGemm {
   int32_t M, N, K;
   const float *A, *W;
