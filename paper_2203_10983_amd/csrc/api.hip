@@ -264,6 +264,7 @@ size_t carve(Carver &c, const bns_partition_desc *p, const bns_model_desc *m, La
     pl.mrow = c.take<int32_t>(seg_max_multi(nnz));
     pl.part_unit = c.take<int2>(seg_max_parts(nnz));
     pl.order = c.take<int2>(seg_max_segments(n_in, nnz));
+    pl.arrived = c.take<int32_t>(4 * seg_max_parts(nnz));
     pl.n_seg = pl.n_part = pl.n_multi = 0;
   }
   w.seg_tmp_a = c.take<int32_t>(n_in + 1);
@@ -871,6 +872,8 @@ bns_status bns_create(bns_ctx **out, const bns_partition_desc *part, const bns_m
   if (ctx->ws.w_fwd) BNS_TRY("entry_weights(fwd)", entry_weights(part->e_in, ctx->ws.split.in_col, w_col, ctx->ws.w_fwd, s));
   BNS_TRY("entry_weights(bwd)", entry_weights(part->e_in, part->t_in_col, w_col, ctx->ws.w_bwd, s));
   BNS_TRY("entry_weights(halo)", entry_weights(part->e_bd, part->halo_col, w_col, ctx->ws.w_halo, s));
+  for (const auto &[plan, nnz] : {std::pair<const SegPlan &, int64_t>(ctx->ws.plan_f, part->nnz0), std::pair<const SegPlan &, int64_t>(ctx->ws.plan_b, part->e_in)})
+    BNS_TRY("clear counts", hipMemsetAsync(plan.arrived, 0, 4 * seg_max_parts(nnz) * sizeof(int32_t), s));
   int32_t *const counts = reinterpret_cast<int32_t *>(ctx->ws.spmm_partials);
   BNS_TRY("build_seg_plan(fwd)", build_seg_plan(part->n_in, part->nnz0, part->row_ptr0, part->col0, (int64_t)part->n_in + part->n_halo,
                                                  &ctx->ws.plan_f, ctx->ws.seg_tmp_a, ctx->ws.seg_tmp_b, counts, ctx->ws.tile_sums, s));

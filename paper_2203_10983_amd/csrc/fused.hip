@@ -13,7 +13,7 @@
 // from L2 in 16-row pieces through a double-buffered LDS tile.
 //
 // Rows that the static plan cuts into several segments (longer than kSegLen entries) are not
-// gathered here: a segmented pass has finished them before, and their row is read back.
+// gathered here: a segmented pass has left their partial sums, which are added up in ascending order (a launch for that alone took 8 to 11 us).
 #include "spmm_device.hpp"
 
 namespace bns {
@@ -49,7 +49,7 @@ __global__ void __launch_bounds__(kFThreads, 6) __attribute__((amdgpu_num_sgpr(9
   const int row0 = blockIdx.x * kFM;
 
   // ---- phase 0: the tile's row bounds into LDS (one coalesced read instead of a dependent chain
-  // per row).  s_e0/s_e1: entries to gather; s_e1 < 0 marks a row finished by the segmented pass.
+  // per row).  s_e0/s_e1: entries to gather; s_e1 < 0 marks a row of -s_e1 segments, whose first partial sum is s_e0.
   __shared__ int s_e0[kFM], s_e1[kFM], s_wd[kFM];  // s_wd: from an entry to its place in w_in
   __shared__ float s_scale[kFM];
   __shared__ unsigned char s_order[kFM];  // the tile's rows, longest class first
@@ -65,7 +65,11 @@ __global__ void __launch_bounds__(kFThreads, 6) __attribute__((amdgpu_num_sgpr(9
       if (a.w_in) wd = a.w_ptr[row] - e0;
       if (a.row_skip) e0 += a.row_skip[row];
       if (a.row_take) e1 = e0 + a.row_take[row];
-      if (a.plan.seg_ptr[row + 1] - a.plan.seg_ptr[row] > 1) e1 = -1;
+      const int nseg = a.plan.seg_ptr[row + 1] - a.plan.seg_ptr[row];
+      if (nseg > 1) {
+        e0 = a.plan.part_ptr[row];
+        e1 = -nseg;
+      }
     }
     s_e0[threadIdx.x] = e0;
     s_e1[threadIdx.x] = e1;
@@ -73,7 +77,7 @@ __global__ void __launch_bounds__(kFThreads, 6) __attribute__((amdgpu_num_sgpr(9
     s_scale[threadIdx.x] = scale;
     // A long row that is taken last keeps the whole tile waiting: the rows are taken in classes of falling length
     // (21 entries a row and a power-law tail: 696 -> 677 us).  The lanes of this wavefront are the rows.
-    const int len = e1 - e0, cls = len > 0 ? 32 - __clz(len) : 0;
+    const int len = e1 < 0 ? min(-e1, 511) : e1 - e0, cls = len > 0 ? 32 - __clz(len) : 0;
     int before = 0, place = 0;
 #pragma unroll
     for (int c = 9; c >= 0; --c) {  // lengths up to kSegLen = 256
@@ -107,6 +111,16 @@ __global__ void __launch_bounds__(kFThreads, 6) __attribute__((amdgpu_num_sgpr(9
   auto source = [&](int lrow, int e, int c, unsigned long long &p, float &w) {
     entry_source(a, row0 + lrow, c, 0, p, w, [&] { return a.w_in ? a.w_in[e + s_wd[lrow]] : 1.f; });
   };
+  auto finish = [&](int lrow, const float (&acc)[VEC]) {
+    if (g == 0 && sl < nvec) {
+      const float scale = s_scale[lrow];
+      V x = V{};
+      if (a.init) x = reinterpret_cast<const V *>(a.init + (size_t)(row0 + lrow) * d)[sl];
+      const float *px = reinterpret_cast<const float *>(&x);
+#pragma unroll
+      for (int i = 0; i < VEC; ++i) As[lrow * kFLda + sl * VEC + i] = (a.init ? acc[i] + px[i] : acc[i]) * scale;
+    }
+  };
   int j0 = grab();
   int c0 = stage_a(j0);
   int j1 = grab();
@@ -129,13 +143,25 @@ __global__ void __launch_bounds__(kFThreads, 6) __attribute__((amdgpu_num_sgpr(9
 #pragma unroll
           for (int i = 0; i < VEC; ++i) lds_row[sl * VEC + i] = 0.f;
         }
-      } else if (e1 < 0) {  // finished by the segmented pass
-        if (g == 0 && sl < nvec) {
-          const V x = reinterpret_cast<const V *>(a.out0 + (size_t)row * d)[sl];
-          const float *px = reinterpret_cast<const float *>(&x);
+      } else if (e1 < 0) {  // a row of several segments
+        constexpr int CU = 8;  // partial sums fetched together
+        float acc[VEC] = {};
+        const float *part = a.partials + (size_t)e0 * d;
+        const int piece = min(sl, nvec - 1);
+        for (int s0 = 0; s0 < -e1; s0 += CU) {
+          V x[CU];
 #pragma unroll
-          for (int i = 0; i < VEC; ++i) lds_row[sl * VEC + i] = px[i];
+          for (int t = 0; t < CU; ++t) x[t] = reinterpret_cast<const V *>(part + (size_t)min(s0 + t, -e1 - 1) * d)[piece];
+#pragma unroll
+          for (int t = 0; t < CU; ++t) {
+            const float *px = reinterpret_cast<const float *>(&x[t]);
+            if (s0 + t < -e1) {
+#pragma unroll
+              for (int i = 0; i < VEC; ++i) acc[i] += px[i];
+            }
+          }
         }
+        finish(lrow, acc);
       } else {
         float acc[1][VEC];
 #pragma unroll
@@ -149,14 +175,7 @@ __global__ void __launch_bounds__(kFThreads, 6) __attribute__((amdgpu_num_sgpr(9
           gather_batch<VEC, 1, LPR>(p_l, w_l, cnt, nvec, acc);
         }
         fold_groups<VEC, 1, LPR>(acc);
-        if (g == 0 && sl < nvec) {
-          const float scale = s_scale[lrow];
-          V x = V{};
-          if (a.init) x = reinterpret_cast<const V *>(a.init + (size_t)row * d)[sl];
-          const float *px = reinterpret_cast<const float *>(&x);
-#pragma unroll
-          for (int i = 0; i < VEC; ++i) lds_row[sl * VEC + i] = (a.init ? acc[0][i] + px[i] : acc[0][i]) * scale;
-        }
+        finish(lrow, acc[0]);
       }
       for (int k = d + lane; k < k_pad; k += kWave) lds_row[k] = 0.f;  // depth padding
     }
@@ -218,7 +237,7 @@ __global__ void __launch_bounds__(kFThreads, 6) __attribute__((amdgpu_num_sgpr(9
   // mean aggregator on 306250 rows 614 -> 602, of 306250 rows of 100 floats unchanged).
   for (int r = wid * (kFM / 8) + g; r < (wid + 1) * (kFM / 8); r += kWave / LPR) {
     const int row = row0 + r;
-    if (row < a.n_split && s_e1[r] >= 0 && sl < nvec) {
+    if (row < a.n_split && sl < nvec) {
       V o;
       float *po = reinterpret_cast<float *>(&o);
 #pragma unroll

@@ -129,6 +129,7 @@ struct SegPlan {
   int32_t *part_ptr;  // int32[n_rows+1] first partial-sum slot of each multi-segment row
   int32_t *mrow;      // int32[n_multi]  rows with more than one segment
   int2 *part_unit;    // int2[n_part]    row of each partial-sum slot, slot (set-up: what order is made from)
+  int32_t *arrived;   // int32[4 * n_part] per row and slice, at 4 * part_ptr[row] + slice: segments finished in the launch that runs (zero between launches)
   int2 *order;        // int2[n_seg]     the units as launches take them: the n_part of long rows by column, then the other rows
   int32_t n_seg, n_part, n_multi;  // host copies of the totals
   int32_t max_seg;                 // segments of the longest row

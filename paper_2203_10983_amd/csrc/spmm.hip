@@ -19,8 +19,50 @@
 
 namespace bns {
 
+// (A launch of many long rows: launch_spmm_vec.)  A segment's partial sum is on its way: the wavefront that is the last of its row (and slice) to get here adds up the row, in ascending order of the segments.
+// The partial sums are written and read at the agent's scope, so that nothing has to be flushed; the store has ended before the segment is counted.
+template <int VEC, int MAXCH, int LPR, bool NARROW, bool RAGGED>
+__device__ __forceinline__ void finish_long_row(int row, int d_off) {
+  using V = typename Vec<VEC, RAGGED>::T;
+  ArgBlock &a = unit_args();
+  if (a.plan.arrived == nullptr) return;  // a launch behind this one adds them up
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  int lane = lane_id();
+  asm volatile("" : "+v"(lane));  // (found again rather than kept in registers beside the gather)
+  const int slot0 = scalar_load(a.plan.part_ptr, row);
+  const int2 seg = scalar_load_pair(a.plan.seg_ptr, row);
+  const int nseg = seg.y - seg.x;
+  int32_t *const count = a.plan.arrived + 4 * slot0 + d_off / a.head.d_slice;
+  int before = 0;
+  if (lane == 0) before = __hip_atomic_fetch_add(count, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (__builtin_amdgcn_readfirstlane(before) != nseg - 1) return;
+  if (lane == 0) __hip_atomic_store(count, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // for the next launch
+  if (lane >= LPR) return;
+  const int width = RAGGED ? min(a.head.d_slice, a.d - d_off) : a.head.d_slice, nvec = (width + (RAGGED ? VEC - 1 : 0)) / VEC;
+  const float *const part = a.partials + (size_t)slot0 * a.d + d_off;
+  float acc[MAXCH][VEC] = {};
+  constexpr int CU = MAXCH == 1 ? 8 : 4;  // partial sums fetched together
+  for (int s0 = 0; s0 < nseg; s0 += CU) {
+    V x[CU][MAXCH];
+#pragma unroll
+    for (int t = 0; t < CU; ++t)
+#pragma unroll
+      for (int c = 0; c < MAXCH; ++c)  // (a piece past the end of the row is the last one again)
+        x[t][c] = shared_load<VEC, V>(part + (size_t)min(s0 + t, nseg - 1) * a.d, piece_at<VEC, RAGGED>(min(c * kWave + lane, nvec - 1), width));
+#pragma unroll
+    for (int t = 0; t < CU; ++t) {
+      if (s0 + t >= nseg) break;
+#pragma unroll
+      for (int c = 0; c < MAXCH; ++c)
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) acc[c][i] += reinterpret_cast<const float *>(&x[t][c])[i];
+    }
+  }
+  finish_row<VEC, MAXCH, NARROW, RAGGED>(unit_args(), row, lane, nvec, d_off, acc, width);
+}
+
 // BLOCK: workgroups of kBlockWaves wavefronts; the first plan.n_multi of them own a multi-segment row each, one
-// wavefront per segment, and add the partial sums in LDS (same order as spmm_combine_kernel, same bits).  In front of the
+// wavefront per segment, and add the partial sums in LDS (same order as finish_long_row, same bits).  In front of the
 // others are head.n_block_rows workgroups, n_multi rounded up to whole groups; those past n_multi have nothing to do.
 constexpr int kBlockWaves = 8;
 template <int VEC, int MAXCH, int LPR, bool NARROW = false, bool BLOCK = false, bool RAGGED = false, bool SHORT = false>
@@ -160,10 +202,12 @@ __global__ void __launch_bounds__(BLOCK ? kBlockWaves * kWave : 256, MAXCH == 1 
           float *po = reinterpret_cast<float *>(&o);
 #pragma unroll
           for (int i = 0; i < VEC; ++i) po[i] = acc[c][i];
-          *piece_of<VEC, RAGGED>(part, iv, width) = o;
+          if (b.plan.arrived) shared_store<VEC>(part, piece_at<VEC, RAGGED>(iv, width), o);
+          else *piece_of<VEC, RAGGED>(part, iv, width) = o;
         }
       }
     }
+    if (!BLOCK && slot >= 0) finish_long_row<VEC, MAXCH, LPR, NARROW, RAGGED>(row, d_off);
   }
 }
 
@@ -350,7 +394,6 @@ static hipError_t launch_spmm_vec(const SpmmArgs &a_in, int64_t extra_rows, bool
                           ((int64_t)a.plan.n_seg << ls) <= (narrow_slice ? 20480 : 65536);
   const int waves = block_rows ? kBlockWaves : 4, wave_units = by_two ? kLongPerWave : 1;
   const int nvec = (a.head.d_slice + VEC - 1) / VEC;
-  const int full_nvec = (a.d + VEC - 1) / VEC;
   // One wavefront per static segment.  The kept boundary rows are a few entries each.  Where all wavefronts go on to them
   // after their segment, the launch ends in a long stretch of short rows, bound by the rate at which workgroups start, while
   // the wavefronts wait for the store of their first row (19 800 rows in four slices beside 52 800 segments: 110 of 640 us).
@@ -371,6 +414,11 @@ static hipError_t launch_spmm_vec(const SpmmArgs &a_in, int64_t extra_rows, bool
   // the same ones have all of them for hundreds of groups on end (150000 rows beside as many, 64 floats 215 -> 198, 256 floats 625 -> 565).
   const int64_t per = 8 >> ls;
   auto groups = [&](int64_t n) { return (n + per - 1) / per; };
+  // Else the last wavefront of a row adds it up (finish_long_row), and waits for its store and its count first, some 2 us: where most wavefronts have such
+  // a segment that costs more than the launch.  The launch and its sums / so, us: 40500 segments in four slices 434 / 440 (transposed, 31900 485 / 493), in
+  // one 126 / 123 (207 / 206), 23400 in one 216 / 205, transposed 20100 in two 697 / 690, 16900 in one 791 / 785, 200 in one 28 / 23 (20011 rows).
+  const bool by_last = !multi_only && !block_rows && ((int64_t)a.plan.n_part << ls) <= 65536;
+  if (!by_last) a.plan.arrived = nullptr;
   if (block_rows) {  // the rows of one segment are left
     a.units += a.plan.n_part;
     a.head.n_units -= a.plan.n_part;
@@ -398,8 +446,9 @@ static hipError_t launch_spmm_vec(const SpmmArgs &a_in, int64_t extra_rows, bool
   a.head.n_groups = (int32_t)all_groups;
   a.head.extra_step = (int32_t)((dealt ? extra_groups : all_groups) * per * waves);
   const unsigned each = (unsigned)(a.head.n_block_rows + all_groups * per);  // workgroups of a slice
-  const unsigned cblocks = block_rows ? 0u : (unsigned)((a.plan.n_multi + 3) / 4);
   const size_t block_lds = (size_t)kBlockWaves * a.head.d_slice * sizeof(float);  // at most 64 KB
+  const unsigned cblocks = multi_only || block_rows || by_last ? 0u : (unsigned)((a.plan.n_multi + 3) / 4);
+  const int full_nvec = (a.d + VEC - 1) / VEC;
   if (each == 0) return hipSuccess;
   const unsigned blocks = each << ls;
   if (ls > 0) {

@@ -206,6 +206,26 @@ __device__ __forceinline__ void finish_row(Args &a, int row, int sl, int nvec, i
   }
 }
 
+// Memory that other compute units write or read in the same launch: accesses at the agent's scope, past the caches of one XCD.  base: the same
+// on the whole wavefront.
+constexpr int kAgentScope = 16;  // sc1
+template <int VEC, typename V>
+__device__ __forceinline__ void shared_store(float *base, int at, const V &v) {
+  typedef unsigned u2 __attribute__((ext_vector_type(2)));
+  typedef unsigned u4 __attribute__((ext_vector_type(4)));
+  const auto r = __builtin_amdgcn_make_buffer_rsrc(base, 0, -1, 0x00020000);
+  if constexpr (VEC == 4) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, v), r, at * 4, 0, kAgentScope);
+  else if constexpr (VEC == 2) __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, v), r, at * 4, 0, kAgentScope);
+  else __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, at * 4, 0, kAgentScope);
+}
+template <int VEC, typename V>
+__device__ __forceinline__ V shared_load(const float *base, int at) {
+  const auto r = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(base), 0, -1, 0x00020000);
+  if constexpr (VEC == 4) return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b128(r, at * 4, 0, kAgentScope));
+  else if constexpr (VEC == 2) return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b64(r, at * 4, 0, kAgentScope));
+  else return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b32(r, at * 4, 0, kAgentScope));
+}
+
 // Weights of a row's entries [.., end) with an inner column: w[e] for entry e (w null: 1).
 struct InnerWeights {
   const float *w;
