@@ -797,10 +797,32 @@ bns_status build_impl(bns_ctx *ctx, int32_t *row_ptr, int32_t *col_idx, int32_t 
   return BNS_OK;
 }
 
+// What the first layer of a training step reads; done: its forward pass was part of the subgraph's launch.
+struct FirstLayer {
+  const float *X, *halo_h, *W;
+  bool done = false;
+};
+
+// The first layer's forward pass in the launch of a small partition's subgraph?  Where it would be a launch of few rows on its own (tile_layer) and has no
+// rows of several segments.  Steps, two launches / one, us: 64-16-8, 400 rows 25.5 / 21.6, 64-128-47, 1000 rows of 6 entries 32.5 / 28.3,
+// 100-128-128-47, 2000 of 12 64.7 / 61.9, 128-128-128-47, 3000 of 13 77.1 / 76.0, 64-256-41, 4500 of 7 75.7 / 69.6, mean aggregator 100-100-41, 2500 of 18
+// 62.6 / 54.7, 128-128-41, 6000 of 5 69.9 / 70.3.  Not while one of the phases is timed.
+bool first_in_subgraph_launch(const bns_ctx *ctx, const FirstLayer &first) {
+  if (ctx->n_layers < 2 || ctx->ws.plan_f.n_multi > 0 || layer_plan(ctx, 1, first.X) != BNS_LAYER_TWO_KERNELS || !tile_layer(ctx, 1)) return false;
+  for (int phase : {BNS_PHASE_SAMPLE, BNS_PHASE_BUILD, BNS_PHASE_SPMM_FWD, BNS_PHASE_GEMM_FWD})
+    if (timed(ctx, phase)) return false;
+  const size_t d_in = ctx->dims[0], d_out = ctx->dims[1], n_a = ctx->part.n_in * d_in, n_h = ctx->part.n_in * d_out;
+  const auto meets = [&](const float *out, size_t n) {  // (as before tile_layer_fwd)
+    return overlap(out, n, first.X, n_a) || overlap(out, n, first.halo_h, ctx->part.n_halo * d_in) ||
+           overlap(out, n, first.W, (ctx->layer_kind == 1 ? 2 : 1) * d_in * d_out);
+  };
+  return !meets(ctx->ws.A[1], n_a) && !meets(ctx->ws.H[1], n_h);
+}
+
 // Selection step + subgraph step of a training step, into the workspace arrays: one launch for a
 // small partition (timed as the sample phase), else the two calls above.
 bns_status sample_and_build_impl(bns_ctx *ctx, uint64_t seed, uint32_t epoch, const uint32_t *epoch_dev, double p,
-                                 const PackJobs &pack, hipStream_t s) {
+                                 const PackJobs &pack, FirstLayer *first, hipStream_t s) {
   Layout &w = ctx->ws;
   const bns_partition_desc &P = ctx->part;
   if (!sample_build_small_fits(P.n_in, P.n_halo, P.e_in, P.e_bd, expected_kept(ctx, p))) {
@@ -808,13 +830,29 @@ bns_status sample_and_build_impl(bns_ctx *ctx, uint64_t seed, uint32_t epoch, co
     if (st != BNS_OK) return st;
     return build_impl(ctx, w.row_ptr, w.col_idx, w.t_row_ptr, w.t_col_idx, w.counters + 1, s);
   }
-  const uint64_t threshold = (uint64_t)std::floor(p * 4294967296.0);
-  PhaseTimer t(ctx, BNS_PHASE_SAMPLE, s);
-  BNS_TRY("sample_build_small",
-          sample_build_small(P.halo_gid, P.n_halo, seed, epoch, epoch_dev, (uint32_t)P.part_id, threshold, w.ballots,
-                             w.kept_ids, w.remap, w.counters, w.kept_start, P.n_in, P.e_in, P.e_bd, w.split,
-                             w.row_ptr, w.col_idx, w.counters + 1, P.halo_ptr, P.halo_col, w.t_row_ptr, w.t_col_idx,
-                             w.halo_rec, ctx->layer_kind == 1 ? nullptr : w.dis_halo, halo_scale(p), &pack, s));
+  const bool sage = ctx->layer_kind == 1;
+  SmallArgs a;
+  a.halo_gid = P.halo_gid; a.n_halo = P.n_halo;
+  a.k0 = (uint32_t)seed; a.k1 = (uint32_t)(seed >> 32); a.epoch = epoch; a.epoch_dev = epoch_dev; a.part_id = (uint32_t)P.part_id;
+  a.threshold = (uint64_t)std::floor(p * 4294967296.0);
+  a.ballots = w.ballots; a.kept_ids = w.kept_ids; a.remap = w.remap; a.n_kept = w.counters; a.kept_start = w.kept_start;
+  a.n_in = P.n_in; a.e_in = (int32_t)P.e_in; a.e_bd = (int32_t)P.e_bd;
+  a.sp = w.split; a.row_ptr = w.row_ptr; a.col_idx = w.col_idx; a.nnz = w.counters + 1;
+  a.halo_ptr = P.halo_ptr; a.halo_col = P.halo_col; a.t_tail_ptr = w.t_row_ptr + P.n_in; a.t_col_idx = w.t_col_idx;
+  a.rec = w.halo_rec; a.dis_halo = sage ? nullptr : w.dis_halo; a.s_halo = halo_scale(p);
+  ctx->cur_seed = seed;  // (the dropout of the first layer's output draws by them)
+  ctx->cur_epoch = epoch;
+  ctx->cur_epoch_dev = epoch_dev;
+  first->done = first_in_subgraph_launch(ctx, *first);
+  if (first->done) {
+    const bool cached = ctx->cache_X != nullptr && ctx->cache_X == first->X;
+    BNS_TRY("sample_build_first",
+            sample_build_first(a, pack, ctx->dims[0], ctx->dims[1], w.w_fwd, sage ? w.inv_deg : w.dis_in, first->X, first->halo_h, w.A[1],
+                               cached ? w.C0 : nullptr, first->W, w.H[1], true, dropout_of(ctx, 1, true), sage, concat_in_one(ctx->dims[0]), w.plan_f, s));
+  } else {
+    PhaseTimer t(ctx, BNS_PHASE_SAMPLE, s);
+    BNS_TRY("sample_build_small", sample_build_small(a, pack, s));
+  }
   ctx->cur_counted = false;
   ctx->drawn = w.remap;
   ctx->ws_built = true;
@@ -994,7 +1032,8 @@ static bns_status train_step_impl(bns_ctx *ctx, uint64_t seed, uint32_t epoch, u
     BNS_TRY("pack_weights", pack_weights(jobs, s));
     jobs = PackJobs{};
   }
-  bns_status st = sample_and_build_impl(ctx, seed, epoch, epoch_dev, p, jobs, s);
+  FirstLayer first{X, ctx->part.n_halo > 0 ? halo_h[0] : nullptr, W[0]};
+  bns_status st = sample_and_build_impl(ctx, seed, epoch, epoch_dev, p, jobs, &first, s);
   if (st != BNS_OK) return st;
 
   const int C = ctx->dims[L];
@@ -1009,7 +1048,8 @@ static bns_status train_step_impl(bns_ctx *ctx, uint64_t seed, uint32_t epoch, u
   last.ld = gather_stride(ctx->dims[L - 1], C);
 
   const float *H_prev = X;
-  for (int l = 1; l <= L; ++l) {
+  if (first.done) H_prev = w.H[1];
+  for (int l = first.done ? 2 : 1; l <= L; ++l) {
     st = layer_fwd_impl(ctx, l, p, H_prev, ctx->part.n_halo > 0 ? halo_h[l - 1] : nullptr, W[l - 1], w.A[l],
                         w.H[l], l < L, layer_plan(ctx, l, X) == BNS_LAYER_UPDATE_FIRST, nullptr, l == L && ctx->loss_kind == 0 ? &last : nullptr, s);
     if (st != BNS_OK) return st;

@@ -109,12 +109,29 @@ constexpr int kSmallMaxBoundaryEntries = 8192;  // entries with a boundary colum
 // 300 and 1397, 68216, 38.0 / 39.0; 1500 with 31262 beside 3500 and 8095 at p = 1, 81262, 42.8 / 52.3).
 constexpr int kSmallMaxWork = 51200;  // inner entries + 3 per inner node + 1 per boundary node + 12 per boundary node to be expected
 bool sample_build_small_fits(int32_t n_in, int32_t n_halo, int64_t e_in, int64_t e_bd, int32_t expected_kept);
-hipError_t sample_build_small(const int64_t *halo_gid, int32_t n_halo, uint64_t seed, uint32_t epoch,
-                              const uint32_t *epoch_dev, uint32_t part_id, uint64_t threshold, uint64_t *ballots,
-                              int32_t *kept_ids, int32_t *remap, int32_t *n_kept, int32_t *kept_start,
-                              int32_t n_in, int64_t e_in, int64_t e_bd, const StaticSplit &sp, int32_t *row_ptr, int32_t *col_idx, int32_t *nnz, const int32_t *halo_ptr,
-                              const int32_t *halo_col, int32_t *t_row_ptr, int32_t *t_col_idx, int2 *rec, const float *dis_halo,
-                              float s_halo, const PackJobs *pack, hipStream_t s);
+// (kSmallThreads threads of a workgroup)
+struct SmallArgs {
+  // selection step
+  const int64_t *halo_gid;
+  int32_t n_halo;
+  uint32_t k0, k1, epoch;
+  const uint32_t *epoch_dev;
+  uint32_t part_id;
+  uint64_t threshold;
+  uint64_t *ballots;
+  int32_t *kept_ids, *remap, *n_kept, *kept_start;
+  // subgraph step
+  int32_t n_in, e_in, e_bd;
+  StaticSplit sp;
+  int32_t *row_ptr, *col_idx, *nnz;
+  // transposed rows of the kept nodes
+  const int32_t *halo_ptr, *halo_col;
+  int32_t *t_tail_ptr, *t_col_idx;
+  int2 *rec;  // per kept node: boundary index, weight
+  const float *dis_halo;
+  float s_halo;
+};
+hipError_t sample_build_small(const SmallArgs &a, const PackJobs &pack, hipStream_t s);
 
 struct Dropout;  // defined with the GEMMs below
 
@@ -231,6 +248,13 @@ hipError_t tile_layer_fwd(const SegPlan &plan, int32_t n_in, int32_t d_in, int32
 // dH[u,:] = alpha * (P^T dZ [+ dZ of u (sage: by the second half of W)]) W^T, zeroed where mask <= 0 (nullable), and for the kept
 // boundary nodes (dhalo nullable) without alpha and mask: as spmm_bwd (its arguments; dZ has rows of d floats, zeros from d_out
 // on) and gemm_rows (on W packed as one matrix), the aggregate first.  Neither dH nor dhalo may share memory with dZ, W or mask.
+// ---- first.hip: sample_build_small and the first layer's tile_layer_fwd in one launch ------------
+// For a plan without rows of several segments and a layer that is not the last.  cached (nullable): the sum over the inner entries, as
+// SpmmRowPart::init.  Same bits as the two launches.
+hipError_t sample_build_first(const SmallArgs &small, const PackJobs &pack, int32_t d_in, int32_t d_out, const float *w_in, const float *row_scale,
+                              const float *H_in, const float *halo_h, float *A, const float *cached, const float *W, float *H_out,
+                              bool relu, const Dropout &drop, bool sage, bool concat, const SegPlan &plan, hipStream_t s);
+
 bool tile_layer_bwd_supported(int32_t d, int32_t d_in, bool sage);
 hipError_t tile_layer_bwd(const SegPlan &plan, int32_t n_in, int32_t n_halo, int32_t d, int32_t d_in, int32_t d_out, const int32_t *t_row_ptr,
                           const int32_t *t_col_idx, const int32_t *kept_ids, const int32_t *n_kept, const float *w_in, const float *w_halo,
