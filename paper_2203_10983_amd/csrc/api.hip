@@ -42,7 +42,7 @@ struct Layout {
   uint64_t *ballots;
   uint64_t *bd_mask;   // keep flags of the boundary entries, their number per tile and per tile before each word
   int32_t *bd_sums, *bd_before;
-  // boundary rows at the output width: Hu of layers that shrink (their gradient), Hu2 of update-first layers
+  // boundary rows at the output width: Hu of GCN layers that shrink and of mean-aggregator layers that gather first (their gradient), Hu2 of update-first layers
   float *Hu, *Hu2, *G0, *G1, *G2, *loss_partials;
   int2 *halo_rec;  // per kept boundary node: (boundary index, weight) for the aggregates that read the rows in place
   // weight of every static entry with an inner column: forward (GCN only), transposed inner block, boundary nodes' lists
@@ -168,10 +168,14 @@ bool tile_layer_bwd(const bns_ctx *ctx, int layer, int64_t rows) {
 // The backward pass of a mean-aggregator layer that shrinks: the transposed aggregate at the output width, then
 // [mean^T dZ | dZ] [W_n ; W_s]^T?  (Else the products first, at twice the input width.)  Steps, us, products first / this: last layers 128 -> 47 on 306250 rows
 // of 45 entries 4512 / 4172, 512 -> 100 on 89625 of 21 7426 / 7133; hidden layers of equal widths besides: 128 on 306250 rows the same, 512 on 89625 1.5 %
-// and 128 on 578125 beside 308000 kept boundary rows 1 % slower (the boundary rows' product), hence an eighth narrower.  Not on partitions that may take the
-// one-launch form, whose weights are packed as one matrix.
+// and 128 on 578125 beside 308000 kept boundary rows 1 % slower (the boundary rows' product), hence an eighth narrower.  Not in layer 1, which has
+// no input gradient in a step (its boundary rows need no workspace then), nor on partitions that may take the one-launch form, whose weights are
+// packed as one matrix.
+bool sage_gathers_first(int layer_kind, int32_t n_in, int layer, int d_in, int d_out) {
+  return layer_kind == 1 && layer > 1 && d_out * 8 <= d_in * 7 && n_in > kTileBwdMaxRows;
+}
 bool sage_gathers_first(const bns_ctx *ctx, int layer) {
-  return ctx->layer_kind == 1 && ctx->dims[layer] * 8 <= ctx->dims[layer - 1] * 7 && ctx->part.n_in > kTileBwdMaxRows;
+  return sage_gathers_first(ctx->layer_kind, ctx->part.n_in, layer, ctx->dims[layer - 1], ctx->dims[layer]);
 }
 
 // The forward product of `layer` by splits (gemm.hip) instead of the fp32 chain?  It is faster and closer to the exact sums (2-norm of
@@ -221,10 +225,10 @@ bool fits_int32(const bns_partition_desc *p, const bns_model_desc *m) {
 
 size_t carve(Carver &c, const bns_partition_desc *p, const bns_model_desc *m, Layout *out) {
   const size_t n_in = p->n_in, B = p->n_halo, L = m->n_layers;
-  size_t d_max = 0, d_out_max = 0, d_first_max = 0;  // d_out_max: of the layers that shrink
+  size_t d_max = 0, d_out_max = 0, d_first_max = 0;  // d_out_max: of the layers whose boundary rows have a gradient of that width
   for (size_t l = 0; l <= L; ++l) d_max = std::max<size_t>(d_max, m->dims[l]);
   for (size_t l = 0; l < L; ++l) {
-    if (m->dims[l + 1] < m->dims[l]) d_out_max = std::max<size_t>(d_out_max, m->dims[l + 1]);
+    if (m->layer_kind == 0 ? m->dims[l + 1] < m->dims[l] : sage_gathers_first(m->layer_kind, p->n_in, (int)l + 1, m->dims[l], m->dims[l + 1])) d_out_max = std::max<size_t>(d_out_max, m->dims[l + 1]);
     if (update_first_shape(m->layer_kind, m->dims[l], m->dims[l + 1]))
       d_first_max = std::max<size_t>(d_first_max, gather_stride(m->dims[l], m->dims[l + 1]));
   }

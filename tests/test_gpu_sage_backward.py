@@ -1,5 +1,5 @@
 """Mean-aggregator layers that shrink: their backward pass gathers the gradient at the output width and multiplies
-[mean^T dZ | dZ] by [W_n ; W_s]^T afterwards (from 3073 rows on)."""
+[mean^T dZ | dZ] by [W_n ; W_s]^T afterwards (from 3073 rows and the second layer on)."""
 import pytest
 
 import test_gpu_parity as parity
@@ -29,7 +29,7 @@ def test_products(n, d_in, d_out, huge):
     gen.manual_seed(n + d_in)
     f32 = lambda *s: torch.randn(*s, device=dev, generator=gen)  # noqa: E731
     i32 = lambda k: torch.zeros(k, dtype=torch.int32, device=dev)  # noqa: E731
-    ctx = pkg.Context(_loops(n), [d_in, d_out], 0, device=dev, layer_kind=1)
+    ctx = pkg.Context(_loops(n), [8, d_in, d_out], 0, device=dev, layer_kind=1)
     kept, remap, n_kept, nnz = i32(1), i32(1), i32(1), i32(1)
     ctx.sample_boundary(1, 0, 0.5, kept, remap, n_kept)
     csr = i32(n + 1), i32(n), i32(n + 1), i32(n)
@@ -44,7 +44,7 @@ def test_products(n, d_in, d_out, huge):
     ref, size = dZ.double() @ W[d_in:].double().t(), dZ.double().abs() @ W[d_in:].double().abs().t()
     dW, dX = torch.zeros_like(W), torch.full((n, d_in), 7.0, device=dev)
     for out in (dX, shared.view(n, d_in)):    # the second in the place of dZ
-        ctx.gcn_layer_bwd(1, 0.5, dZ, None, A, X, W, dW, out, None)
+        ctx.gcn_layer_bwd(2, 0.5, dZ, None, A, X, W, dW, out, None)
         torch.cuda.synchronize()
         over = (out.double() - ref).abs() / (4.0 * 2.0 ** -24 * (1 + d_out ** 0.5) * size + 1e-300)
         assert over.max() <= 1.0, f"{over.max().item():.3g} of the allowance"
