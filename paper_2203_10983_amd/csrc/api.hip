@@ -468,7 +468,7 @@ bns_status layer_fwd_impl(bns_ctx *ctx, int layer, double p, const float *H_in, 
   const int32_t *w_ptr = ctx->ws.split.inner_ptr;
   const float *row_scale = sage ? ctx->ws.inv_deg : ctx->ws.dis_in;
   if (one_kernel_layer(ctx, d_in, d_out)) {
-    // aggregate and update in one kernel; the rows cut into several segments are finished first
+    // aggregate and update in one kernel; the partial sums of the rows cut into several segments come first
     {
       PhaseTimer t(ctx, BNS_PHASE_SPMM_LONG, s);
       BNS_TRY("spmm_fwd(long rows)", spmm_fwd(ctx->ws.plan_f, n_in, d_in, ctx->cur_row_ptr, ctx->cur_col_idx, w_in, w_ptr,

@@ -190,12 +190,13 @@ hipError_t spmm_fwd(const SegPlan &plan, int32_t n_in, int32_t d, const int32_t 
 // d_store (spmm_fwd and spmm_bwd; 0 = d): the sources and partial sums have rows of d floats of which
 // only the first d_store count (rows padded to a multiple of 4 floats so that a narrow odd width is
 // gathered with 16-byte loads); the outputs are dense [., d_store].  Then d < 128, no mask, no init.
-// pad_rows makes such a padded copy (pad columns zero).
+// pad_rows makes such a padded copy (pad columns zero).  long_rows_only: the partial sums of the rows of several segments, for spmm_gemm_fwd,
+// and nothing else.
 hipError_t pad_rows(int32_t n_rows, int32_t d, int32_t ld, const float *src, float *dst, hipStream_t s);
 // Aggregate and update of one GCN layer in one kernel (Eq. 1 then Eq. 2): a workgroup aggregates 64
 // rows into LDS (and stores them to A, which the backward pass needs), then multiplies the tile by
-// W on the matrix cores while other workgroups of the same compute unit keep gathering.  Rows cut
-// into several segments must have been finished before by spmm_fwd(..., long_rows_only = true).
+// W on the matrix cores while other workgroups of the same compute unit keep gathering.  The partial sums of
+// rows cut into several segments must have been left in `partials` by spmm_fwd(..., long_rows_only = true).
 // Needs d_in % 4 == 0 and 64 < d_in <= 128 (spmm_gemm_fwd_supported).
 // concat_self: the update of the mean-aggregator layer, H_out = act([A | H_in] W) with W [2 d_in, d_out]
 // (neighbour half first): the tile is multiplied by W_n, overwritten with the rows' own features and

@@ -3,9 +3,9 @@
 // Work unit: one 64-lane wavefront owns one SEGMENT of an output row, at most kSegLen
 // neighbours.  Power-law graphs put a large share of all edges into a few very long rows; cutting
 // every row into bounded segments keeps the wavefronts balanced.  A row with one segment is
-// finished by its wavefront; a row with several gets one partial sum per segment, and a second
-// small kernel adds them in ascending order (or, in short launches, the workgroup that owns the row).  No atomics anywhere: the backward pass walks the
-// transposed pattern, and every output element is produced in a fixed order.
+// finished by its wavefront; a row with several gets one partial sum per segment, and these are added in ascending order by whoever
+// launch_spmm_vec says: the workgroup that owns the row, the wavefront that finishes its last segment, or a second small kernel.  No atomics on values
+// anywhere: the backward pass walks the transposed pattern, and every output element is produced in a fixed order.
 //
 // Inside a segment the lanes span the feature dimension with VEC-wide loads, so every neighbour
 // row is read as one contiguous, coalesced piece (four floats to a lane, whatever the width, from 9 on).  When a feature row needs fewer than 64 lanes
