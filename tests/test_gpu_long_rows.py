@@ -1,4 +1,4 @@
-"""Rows of several segments: added up by the wavefront that is the last to finish one (up to 40960 segments and slices, 9 to 64 to the longest
+"""Rows of several segments: added up by the wavefront that is the last to finish one (up to 45056 segments and slices, 9 to 64 to the longest
 row) or by a launch behind, call after call, with the same bits."""
 import types
 
@@ -68,7 +68,7 @@ def _hubs(segments, n, n_filled, fill):
 
 
 @pytest.mark.parametrize("d", [6, 64, 130, 256, 300])  # 256: in two slices, 300: two pieces to a lane
-@pytest.mark.parametrize("segments,n_filled,by_last", [((9, 17, 64), 20480, True), ((65, 2000), 32768, False)], ids=["up-to-64", "longer"])
+@pytest.mark.parametrize("segments,n_filled,by_last", [((9, 17, 64), 22528, True), ((65, 2000), 32768, False)], ids=["up-to-64", "longer"])
 def test_rows_of_many_segments(segments, n_filled, by_last, d):
     """The same rows beside n_filled others of one segment, and of two, which are too many segments for the wavefronts to add up: the second takes one launch
     more where the first has none for the sums, and the bits are the same."""
