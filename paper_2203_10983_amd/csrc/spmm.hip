@@ -47,15 +47,19 @@ __device__ __forceinline__ void finish_long_row(int row, int d_off) {
 #pragma unroll
     for (int t = 0; t < CU; ++t)
 #pragma unroll
-      for (int c = 0; c < MAXCH; ++c)  // (a piece past the end of the row is the last one again)
+      for (int c = 0; c < MAXCH; ++c)  // (a piece past the end of the row, and a segment past the last one, are the last one again)
         x[t][c] = shared_load<VEC, V>(part + (size_t)min(s0 + t, nseg - 1) * a.d, piece_at<VEC, RAGGED>(min(c * kWave + lane, nvec - 1), width));
+    asm volatile("" ::: "memory");  // none of them moves behind a condition below, where it would be waited for before the next
 #pragma unroll
     for (int t = 0; t < CU; ++t) {
-      if (s0 + t >= nseg) break;
+      const bool there = s0 + t < nseg;
 #pragma unroll
       for (int c = 0; c < MAXCH; ++c)
 #pragma unroll
-        for (int i = 0; i < VEC; ++i) acc[c][i] += reinterpret_cast<const float *>(&x[t][c])[i];
+        for (int i = 0; i < VEC; ++i) {
+          const float sum = acc[c][i] + reinterpret_cast<const float *>(&x[t][c])[i];
+          acc[c][i] = there ? sum : acc[c][i];
+        }
     }
   }
   finish_row<VEC, MAXCH, NARROW, RAGGED>(unit_args(), row, lane, nvec, d_off, acc, width);
