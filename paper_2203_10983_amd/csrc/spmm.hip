@@ -19,8 +19,10 @@
 
 namespace bns {
 
-// (A launch of many long rows: launch_spmm_vec.)  A segment's partial sum is on its way: the wavefront that is the last of its row (and slice) to get here adds up the row, in ascending order of the segments.
-// The partial sums are written and read at the agent's scope, so that nothing has to be flushed; the store has ended before the segment is counted.
+// Where launch_spmm_vec says so: a segment's partial sum is on its way, and the wavefront that is the last of its row (and slice) to get here adds up the row, in
+// ascending order of the segments.  The partial sums are written and read at the agent's scope (shared_store, shared_load), past the caches of one XCD, so that
+// nothing has to be flushed; on the one side the store has ended before the segment is counted, on the other no partial sum is asked for before the count has
+// come back and says that all have.  With plain loads, or loads asked for earlier, the last wavefront would add up what its own L2 had held before.
 template <int VEC, int MAXCH, int LPR, bool NARROW, bool RAGGED>
 __device__ __forceinline__ void finish_long_row(int row, int d_off) {
   using V = typename Vec<VEC, RAGGED>::T;
@@ -36,6 +38,7 @@ __device__ __forceinline__ void finish_long_row(int row, int d_off) {
   int before = 0;
   if (lane == 0) before = __hip_atomic_fetch_add(count, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   if (__builtin_amdgcn_readfirstlane(before) != nseg - 1) return;
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");  // (no instruction: the loads below stay below)
   if (lane == 0) __hip_atomic_store(count, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // for the next launch
   if (lane >= LPR) return;
   const int width = RAGGED ? min(a.head.d_slice, a.d - d_off) : a.head.d_slice, nvec = (width + (RAGGED ? VEC - 1 : 0)) / VEC;
