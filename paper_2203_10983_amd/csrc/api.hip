@@ -810,9 +810,12 @@ struct FirstLayer {
 // The first layer's forward pass in the launch of a small partition's subgraph?  Where it would be a launch of few rows on its own (tile_layer) and has no
 // rows of several segments.  Steps, two launches / one, us: 64-16-8, 400 rows 25.5 / 21.6, 64-128-47, 1000 rows of 6 entries 32.5 / 28.3,
 // 100-128-128-47, 2000 of 12 64.7 / 61.9, 128-128-128-47, 3000 of 13 77.1 / 76.0, 64-256-41, 4500 of 7 75.7 / 69.6, mean aggregator 100-100-41, 2500 of 18
-// 62.6 / 54.7, 128-128-41, 6000 of 5 69.9 / 70.3.  Not while one of the phases is timed.
+// 62.6 / 54.7, 128-128-41, 6000 of 5 69.9 / 70.3.  So not for rows of more than 64 floats where the tiles are of 16 rows: a compute unit holds one
+// of these workgroups (85 to 101 KB of LDS), and their wavefronts have two rows each to look up and to gather.  Not while one of the phases is timed.
+constexpr int kFirstWideMaxRows = 3584;  // of tile_rows
 bool first_in_subgraph_launch(const bns_ctx *ctx, const FirstLayer &first) {
   if (ctx->n_layers < 2 || ctx->ws.plan_f.n_multi > 0 || layer_plan(ctx, 1, first.X) != BNS_LAYER_TWO_KERNELS || !tile_layer(ctx, 1)) return false;
+  if (ctx->dims[0] > 64 && ctx->part.n_in > kFirstWideMaxRows) return false;
   for (int phase : {BNS_PHASE_SAMPLE, BNS_PHASE_BUILD, BNS_PHASE_SPMM_FWD, BNS_PHASE_GEMM_FWD})
     if (timed(ctx, phase)) return false;
   const size_t d_in = ctx->dims[0], d_out = ctx->dims[1], n_a = ctx->part.n_in * d_in, n_h = ctx->part.n_in * d_out;

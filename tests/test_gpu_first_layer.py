@@ -5,6 +5,8 @@ import types
 import numpy as np
 import pytest
 
+from test_gpu_tile import _launches
+
 pytestmark = pytest.mark.gpu
 
 
@@ -28,6 +30,26 @@ def _partition(n, deg, n_halo, bd_most, rng):
                                  t_in_ptr=ptr(t // n, n), t_in_col=i32(t % n), halo_ptr=ptr(h // n, n_halo) if n_halo else np.zeros(1, np.int32), halo_col=i32(h % n) if n_halo else np.zeros(0, np.int32),
                                  halo_gid=np.arange(n_halo, dtype=np.int64) * 7 + (1 << 33), deg_in=i32(np.bincount(row, minlength=n)),
                                  deg_halo=i32(np.bincount(col[~inner] - n, minlength=n_halo) + 2 if n_halo else np.zeros(0)))
+
+
+def _fits(P, p):
+    """The host's conditions for one launch of the subgraph, and for a first layer without rows of several segments."""
+    return (max(P.n_halo, P.e_bd) <= 8192 and P.e_in + 3 * P.n_in + P.n_halo + 12 * np.ceil(p * P.n_halo) <= 51200 and P.n_in <= 8192 and
+            np.diff(P.row_ptr0).max() <= 256)
+
+
+def _launches_saved(ctx, P, dims, kind, p):
+    """Launches that a step has less than the same step with the subgraph, the first layer's aggregate and its one product apart: 2 where all are one launch, 1 where
+    the first layer is one beside the subgraph's.  (Features on top of the saved aggregate keep them apart; such a step is recorded and never run.)"""
+    import torch
+    import paper_2203_10983_amd as pkg
+    f32 = lambda *s: torch.zeros(*s, device="cuda:0")  # noqa: E731
+    n, nb = P.n_in, P.n_halo
+    W = [f32((1 + kind) * a, b) for a, b in zip(dims, dims[1:])]
+    rest = ([f32(nb, a) for a in dims[:-1]], torch.zeros(n, dtype=torch.int32, device="cuda:0"), W, [f32(*w.shape) for w in W],
+            [None] + [f32(nb, a) for a in dims[1:-1]], f32(1), 0.0)
+    apart, now = (_launches(lambda: ctx.train_step(11, 0, p, X, *rest)) for X in (ctx.ws_tensor(pkg.VIEW_A, 1, torch.float32), f32(n, dims[0])))
+    return apart - now - (kind == 1 and dims[0] % 16 != 0)  # (a mean aggregator of such a width has two products)
 
 
 @pytest.mark.parametrize("kind", [0, 1], ids=["gcn", "sage"])
@@ -77,4 +99,20 @@ def test_bits_of_two_launches(n, deg, n_halo, bd_most, dims, p, q, cached, kind)
         for a, b in zip(one[:-1], two[:-1]):
             assert torch.equal(a, b)
         assert torch.allclose(one[-1], two[-1], rtol=1e-6)  # partial sums of other rows
+    ctx.close()
+
+
+@pytest.mark.parametrize("kind", [0, 1], ids=["gcn", "sage"])
+@pytest.mark.parametrize("n,d,one", [(3584, 128, True), (3585, 128, False), (3585, 100, False), (3585, 64, True)])
+def test_wide_rows_of_many_tiles_have_a_launch_of_their_own(n, d, one, kind):
+    """Counted beside the same step on features that share memory with the layer's results, which has the subgraph, the aggregate and the update
+    apart (recorded, not run)."""
+    import torch
+    import paper_2203_10983_amd as pkg
+    dev = torch.device("cuda:0")
+    P = _partition(n, 2, 700, 1, np.random.default_rng(n))
+    dims = [d, 40, 8]
+    assert _fits(P, 0.1)
+    ctx = pkg.Context(P, dims, 0, device=dev, layer_kind=kind)
+    assert _launches_saved(ctx, P, dims, kind, 0.1) == (2 if one else 1)
     ctx.close()
