@@ -58,6 +58,12 @@ def narrow_first():
     return _finish("edge-narrow-first", part, [512, 101, 7], 0, 19)
 
 
+def narrow_second():
+    """narrow_first's graph with the wide layer second: 512 -> 101 has an input gradient, of four depth steps (eight with a mean
+    aggregator's own rows) over 32 column tiles, and boundary rows behind it."""
+    return _finish("edge-narrow-second", narrow_first().part, [16, 512, 101], 0, 20)
+
+
 def star(n=3000):
     """One inner hub adjacent to every inner node (a row of 3000 entries: many segments) and one
     boundary hub adjacent to every inner node (a transposed row far longer than a segment), plus
@@ -142,4 +148,4 @@ def degree_ordered():
     return make_workload(3, scale=32, local_order="degree")
 
 
-EDGE = {"e-starw-large": star_wide_large, "e-dense-large": dense_rows_large, "e-degree": degree_ordered, "e-dense": dense_rows, "e-nobd": no_boundary, "e-max": widest, "e-nobdw": no_boundary_wide, "e-narrow": narrow_first, "e-star": star, "e-starw": star_wide, "e-single": single_node, "e-wide": wide_odd}
+EDGE = {"e-starw-large": star_wide_large, "e-dense-large": dense_rows_large, "e-degree": degree_ordered, "e-dense": dense_rows, "e-nobd": no_boundary, "e-max": widest, "e-nobdw": no_boundary_wide, "e-narrow": narrow_first, "e-narrow2": narrow_second, "e-star": star, "e-starw": star_wide, "e-single": single_node, "e-wide": wide_odd}
