@@ -82,6 +82,14 @@ def mfma_regimes():
             "peak": FP32_MFMA_PEAK_TFLOPS, "compute_units": cus, "regimes": rows}
 
 
+def backward_width(d_in, d_out, kind, n_in):
+    """Floats per row that the transposed aggregate of a layer from the second on gathers: the narrower side's in a GCN layer; in a mean-aggregator
+    layer the input's, unless it shrinks by an eighth or more on more than 3072 rows."""
+    if kind == 1 and not (8 * d_out <= 7 * d_in and n_in > 3072):
+        return d_in
+    return min(d_in, d_out)
+
+
 def run_workload(cfg, p, kind, steps, warmup, dropout=0.0, extras=False, cpu_baseline=True, calibrate=False,
                  local_order="native"):
     """Times one workload; -> dict.  extras: also the graph-replay and the cached-input variants,
@@ -161,7 +169,7 @@ def run_workload(cfg, p, kind, steps, warmup, dropout=0.0, extras=False, cpu_bas
     # with the aggregate: it also writes H_out and reads W there, and A is not read back), or update
     # first (the aggregate then runs at the output width)
     fw = {l: dims[l] if l in first else dims[l - 1] for l in range(1, L + 1)}        # forward aggregate width
-    bw = {l: min(dims[l], dims[l - 1]) for l in range(2, L + 1)}
+    bw = {l: backward_width(dims[l - 1], dims[l], kind, n_in) for l in range(2, L + 1)}
 
     def fwd_alg(l, cached=False):
         if cached:      # the cached inner sum and the kept boundary rows instead of all neighbours
