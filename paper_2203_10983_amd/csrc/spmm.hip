@@ -356,7 +356,7 @@ __global__ void __launch_bounds__(256) spmm_combine_kernel(const SpmmArgs a) {
   finish_row<VEC, MAXCH, NARROW, RAGGED>(a, row, lane, nvec, 0, acc, d);
 }
 
-constexpr int kByLastMaxParts = 45056, kByLastMaxSegments = 64;  // of by_last below
+constexpr int kByLastMaxParts = 45056, kByLastMaxSegments = 64, kResidentWaves = 8192;  // of by_last below
 template <int VEC, bool RAGGED>
 static hipError_t launch_spmm_vec(const SpmmArgs &a_in, int64_t extra_rows, bool multi_only, int32_t avg_len, bool transposed, hipStream_t s) {
   SpmmArgs a = a_in;
@@ -424,9 +424,11 @@ static hipError_t launch_spmm_vec(const SpmmArgs &a_in, int64_t extra_rows, bool
   // Else the last wavefront of a row adds it up (finish_long_row), and waits for its store and its count first, some 2 us: where most wavefronts have such
   // a segment that costs more than the launch.  The launch and its sums / so, us: 40500 segments in four slices 434 / 440 (transposed, 31900 485 / 493), in
   // one 126 / 123 (207 / 206), 23400 in one 216 / 205, transposed 20100 in two 697 / 690, 16900 in one 791 / 785, 200 in one 28 / 23 (20011 rows).  Nothing is timed
-  // between 40500 segments and slices and 127600, nor with rows of more segments than the 54 of these graphs: both lines lie where the known gains
-  // end (the 40500 are 40300 to 41500 in graphs of the same kind).
-  const bool by_last = !multi_only && !block_rows && ((int64_t)a.plan.n_part << ls) <= kByLastMaxParts && a.plan.max_seg <= kByLastMaxSegments;
+  // between 40500 segments and slices and 127600, so the line lies where the known gains end (the 40500 are 40300 to 41500 in graphs of the same kind).  Nor
+  // with rows of more segments than the 54 of these graphs: what such a row's last wavefront takes, a wait for every eight of them, has to go by beside the rows
+  // of one segment, which come behind the long rows.  So no longer rows than 64 segments, unless there is a round of the chip's wavefronts for every wait.
+  const bool aside = a.plan.max_seg <= kByLastMaxSegments || ((n_units - a.plan.n_part) << ls) >= (int64_t)a.plan.max_seg * (kResidentWaves / 8);
+  const bool by_last = !multi_only && !block_rows && ((int64_t)a.plan.n_part << ls) <= kByLastMaxParts && aside;
   if (!by_last) a.plan.arrived = nullptr;
   if (block_rows) {  // the rows of one segment are left
     a.units += a.plan.n_part;

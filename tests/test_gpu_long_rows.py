@@ -1,5 +1,5 @@
 """Rows of several segments: added up by the wavefront that is the last to finish one (up to 45056 segments and slices, 9 to 64 to the longest
-row) or by a launch behind, call after call, with the same bits."""
+row, or more beside many short rows) or by a launch behind, call after call, with the same bits."""
 import types
 
 import numpy as np
@@ -68,7 +68,8 @@ def _hubs(segments, n, n_filled, fill):
 
 
 @pytest.mark.parametrize("d", [6, 64, 130, 256, 300])  # 256: in two slices, 300: two pieces to a lane
-@pytest.mark.parametrize("segments,n_filled,by_last", [((9, 17, 64), 22528, True), ((65, 2000), 32768, False)], ids=["up-to-64", "longer"])
+@pytest.mark.parametrize("segments,n_filled,by_last", [((9, 17, 64), 22528, True), ((17, 100), 22528, True), ((65, 2000), 32768, False)],
+                         ids=["up-to-64", "longer-aside", "longer"])
 def test_rows_of_many_segments(segments, n_filled, by_last, d):
     """The same rows beside n_filled others of one segment, and of two, which are too many segments for the wavefronts to add up: the second takes one launch
     more where the first has none for the sums, and the bits are the same."""
@@ -84,6 +85,7 @@ def test_rows_of_many_segments(segments, n_filled, by_last, d):
         P = _hubs(segments, n, n_filled, fill)
         per_row = -(-np.diff(P.row_ptr0) // 256)
         n_part = int(per_row[per_row > 1].sum())
+        assert by_last == (max(segments) <= 64 or n - len(segments) >= 1024 * max(segments))
         assert per_row.max() == max(segments) and P.nnz0 < 64 * n and n_part == sum(segments) + (2 * n_filled if fill == 257 else 0)
         i32 = lambda k: torch.zeros(k, dtype=torch.int32, device=dev)  # noqa: E731
         ctx = pkg.Context(P, [d, 4], 0, device=dev)
