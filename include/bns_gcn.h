@@ -292,8 +292,8 @@ bns_status bns_ws_view(const bns_ctx *ctx, bns_view which, int32_t layer, void *
  * gather) and updates them in the last launch of the weight gradients.  While SAMPLE (GATHER) or SGD is
  * timed, that work gets launches of its own, with the same results, so that a phase holds its own kernels only; the
  * packing then belongs to no phase.  Where a step's selection and subgraph steps are one launch (below) and its first layer would be one
- * more (no row of more than 256 entries), both are one launch while none of SAMPLE, BUILD, SPMM_FWD and GEMM_FWD is timed, with the same
- * results.  On partitions of up to 3072 rows (inner ones and boundary nodes times p) the backward pass
+ * more (no row of more than 256 entries; rows of more than 64 floats: up to 3584 of them), both are one launch while none of SAMPLE, BUILD,
+ * SPMM_FWD and GEMM_FWD is timed, with the same results.  On partitions of up to 3072 rows (inner ones and boundary nodes times p) the backward pass
  * of a layer, transposed aggregate and product with W^T, is one launch of that order while neither SPMM_BWD nor GEMM_DA is
  * timed and dH_in and dhalo share no memory with dH_out and W.  Its two launches have the same bits for a GCN layer that narrows; a
  * mean-aggregator layer and one that does not narrow multiply first there, so that dH_in and dhalo differ in rounding

@@ -13,7 +13,7 @@
 // from L2 in 16-row pieces through a double-buffered LDS tile.
 //
 // Rows that the static plan cuts into several segments (longer than kSegLen entries) are not
-// gathered here: a segmented pass has left their partial sums, which are added up in ascending order (a launch for that alone took 8 to 11 us).
+// gathered here: a segmented pass has left their partial sums, which are added up in ascending order (the launch for that alone: launch_spmm_vec).
 #include "spmm_device.hpp"
 
 namespace bns {

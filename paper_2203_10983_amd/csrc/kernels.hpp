@@ -146,7 +146,8 @@ struct SegPlan {
   int32_t *part_ptr;  // int32[n_rows+1] first partial-sum slot of each multi-segment row
   int32_t *mrow;      // int32[n_multi]  rows with more than one segment
   int2 *part_unit;    // int2[n_part]    row of each partial-sum slot, slot (set-up: what order is made from)
-  int32_t *arrived;   // int32[4 * n_part] per row and slice, at 4 * part_ptr[row] + slice: segments finished in the launch that runs (zero between launches)
+  int32_t *arrived;   // int32[4 * n_part] per row and slice, at 4 * part_ptr[row] + slice: segments finished in the launch that runs (zero between launches).  Eight slices
+                      // at most, and a row that is counted has two slots at least
   int2 *order;        // int2[n_seg]     the units as launches take them: the n_part of long rows by column, then the other rows
   int32_t n_seg, n_part, n_multi;  // host copies of the totals
   int32_t max_seg;                 // segments of the longest row
@@ -249,19 +250,19 @@ hipError_t tile_layer_fwd(const SegPlan &plan, int32_t n_in, int32_t d_in, int32
 // dH[u,:] = alpha * (P^T dZ [+ dZ of u (sage: by the second half of W)]) W^T, zeroed where mask <= 0 (nullable), and for the kept
 // boundary nodes (dhalo nullable) without alpha and mask: as spmm_bwd (its arguments; dZ has rows of d floats, zeros from d_out
 // on) and gemm_rows (on W packed as one matrix), the aggregate first.  Neither dH nor dhalo may share memory with dZ, W or mask.
-// ---- first.hip: sample_build_small and the first layer's tile_layer_fwd in one launch ------------
-// For a plan without rows of several segments and a layer that is not the last.  cached (nullable): the sum over the inner entries, as
-// SpmmRowPart::init.  Same bits as the two launches.
-hipError_t sample_build_first(const SmallArgs &small, const PackJobs &pack, int32_t d_in, int32_t d_out, const float *w_in, const float *row_scale,
-                              const float *H_in, const float *halo_h, float *A, const float *cached, const float *W, float *H_out,
-                              bool relu, const Dropout &drop, bool sage, bool concat, const SegPlan &plan, hipStream_t s);
-
 bool tile_layer_bwd_supported(int32_t d, int32_t d_in, bool sage);
 hipError_t tile_layer_bwd(const SegPlan &plan, int32_t n_in, int32_t n_halo, int32_t d, int32_t d_in, int32_t d_out, const int32_t *t_row_ptr,
                           const int32_t *t_col_idx, const int32_t *kept_ids, const int32_t *n_kept, const float *w_in, const float *w_halo,
                           const int32_t *halo_ptr, const float *row_scale, const float *dis_halo, float s_halo, const float *dZ,
                           const float *W, const void *Bp, const float *mask, float alpha, bool sage, float *partials, float *dH, float *dhalo,
                           int32_t expected_halo, hipStream_t s);
+
+// ---- first.hip: sample_build_small and the first layer's tile_layer_fwd in one launch ------------
+// For a plan without rows of several segments and a layer that is not the last.  cached (nullable): the sum over the inner entries, as
+// SpmmRowPart::init.  Same bits as the two launches.
+hipError_t sample_build_first(const SmallArgs &small, const PackJobs &pack, int32_t d_in, int32_t d_out, const float *w_in, const float *row_scale,
+                              const float *H_in, const float *halo_h, float *A, const float *cached, const float *W, float *H_out,
+                              bool relu, const Dropout &drop, bool sage, bool concat, const SegPlan &plan, hipStream_t s);
 
 // C[M,N] = [A | A2] B (+ the previous C if accumulate), B [K,N] packed; then, if relu, max(., 0) and dropout (when
 // drop.scale != 0).  A, A2 [M, lda]: the depth below a_split (a multiple of 16) is A's, the rest A2's (nullable).

@@ -131,10 +131,8 @@ __device__ __forceinline__ void gather_tile(const SpmmArgs &a, int row0, int row
   }
 }
 
-// LOSS: also the softmax cross-entropy of the last layer's output and its gradient.
-
-// The tile's number and the number of a thread among its kTileWaves wavefronts; As: its rows.  gather(row0, rows, put): gather_tile or
-// what takes its place.  Every thread of the workgroup gets to the same barriers, also where a tile has no rows.
+// A layer's forward pass on one tile.  LOSS: also the softmax cross-entropy of the last layer's output and its gradient.  tile_no, thread: the tile's number and
+// that of a thread among its kTileWaves wavefronts; As: its rows.  gather(row0, rows, put): gather_tile or what takes its place.  Every thread of the workgroup gets to the same barriers, also where a tile has no rows.
 template <int LPR, int VW, bool SAGE, bool LOSS, typename Gather>
 __device__ __forceinline__ void tile_layer(const TileArgs &f, int tile_no, int thread, float (&As)[SAGE ? 2 : 1][kTileRows * kTileLd], Gather gather) {
   using V = typename Vec<4>::T;
