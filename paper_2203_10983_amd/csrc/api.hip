@@ -375,18 +375,22 @@ int32_t transposed_len(const bns_ctx *ctx, double p, bool halo_rows) {
 }
 float halo_scale(double p) { return p > 0.0 ? (float)(1.0 / p) : 0.f; }  // 1/p is never formed at p = 0
 
-// Dropout of hidden layer `layer` in the current epoch (off when the rate is 0 or the layer has no ReLU).
-Dropout dropout_of(const bns_ctx *ctx, int layer, bool relu) {
+// Dropout of hidden layer `layer` in an epoch (off when the rate is 0 or the layer has no ReLU).
+Dropout dropout_of(const bns_ctx *ctx, int layer, bool relu, uint64_t seed, uint32_t epoch, const uint32_t *epoch_dev) {
   Dropout d;
   if (!relu || ctx->drop_q <= 0.0) return d;
   d.threshold = (uint64_t)std::floor((1.0 - ctx->drop_q) * 4294967296.0);
   d.scale = (float)(1.0 / (1.0 - ctx->drop_q));
-  d.k0 = (uint32_t)ctx->cur_seed;
-  d.k1 = (uint32_t)(ctx->cur_seed >> 32) ^ 0x64726F70u;
+  d.k0 = (uint32_t)seed;
+  d.k1 = (uint32_t)(seed >> 32) ^ 0x64726F70u;
   d.c2 = ((uint32_t)ctx->part.part_id << 8) | (uint32_t)layer;
-  d.epoch = ctx->cur_epoch;
-  d.epoch_dev = ctx->cur_epoch_dev;
+  d.epoch = epoch;
+  d.epoch_dev = epoch_dev;
   return d;
+}
+// In that of the latest sample.
+Dropout dropout_of(const bns_ctx *ctx, int layer, bool relu) {
+  return dropout_of(ctx, layer, relu, ctx->cur_seed, ctx->cur_epoch, ctx->cur_epoch_dev);
 }
 // Slope of a surviving hidden unit: 1/(1-q) under dropout, else 1.
 float mask_scale_of(const bns_ctx *ctx) {
@@ -847,15 +851,13 @@ bns_status sample_and_build_impl(bns_ctx *ctx, uint64_t seed, uint32_t epoch, co
   a.sp = w.split; a.row_ptr = w.row_ptr; a.col_idx = w.col_idx; a.nnz = w.counters + 1;
   a.halo_ptr = P.halo_ptr; a.halo_col = P.halo_col; a.t_tail_ptr = w.t_row_ptr + P.n_in; a.t_col_idx = w.t_col_idx;
   a.rec = w.halo_rec; a.dis_halo = sage ? nullptr : w.dis_halo; a.s_halo = halo_scale(p);
-  ctx->cur_seed = seed;  // (the dropout of the first layer's output draws by them)
-  ctx->cur_epoch = epoch;
-  ctx->cur_epoch_dev = epoch_dev;
   first->done = first_in_subgraph_launch(ctx, *first);
   if (first->done) {
     const bool cached = ctx->cache_X != nullptr && ctx->cache_X == first->X;
     BNS_TRY("sample_build_first",
             sample_build_first(a, pack, ctx->dims[0], ctx->dims[1], w.w_fwd, sage ? w.inv_deg : w.dis_in, first->X, first->halo_h, w.A[1],
-                               cached ? w.C0 : nullptr, first->W, w.H[1], true, dropout_of(ctx, 1, true), sage, concat_in_one(ctx->dims[0]), w.plan_f, s));
+                               cached ? w.C0 : nullptr, first->W, w.H[1], true, dropout_of(ctx, 1, true, seed, epoch, epoch_dev), sage, concat_in_one(ctx->dims[0]),
+                               w.plan_f, s));
   } else {
     PhaseTimer t(ctx, BNS_PHASE_SAMPLE, s);
     BNS_TRY("sample_build_small", sample_build_small(a, pack, s));
